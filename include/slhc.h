@@ -151,15 +151,13 @@ const char* slhc_last_error(void);              /* thread-local, never NULL  */
  * k-NN graph (paper Sec. 3.1.1, Alg. "Fused k-NN" with its epilogues in Appendix A).
  *
  * For every row i the k rows j != i with the smallest (||x_i - x_j||^2, j), ascending.
- * The distance tile x_i . x_j is computed on fp32 MFMA and only used to discard pairs that
+ * The distance tile x_i . x_j is computed on the MFMA (from rows rounded to float16 with a bound on what the rounding
+ * can do, unless SLHC_FP32_FILTER or SLHC_PANEL_ORDER asks for the list kernels) and only used to discard pairs that
  * cannot enter a row's list; a pair that may enter is re-evaluated as sum_t (x_it - x_jt)^2
  * in fp32, so the reported value of (i,j) equals that of (j,i) bit for bit and duplicates are at
  * exactly 0.  A row is never its own neighbour (excluded by index, not by distance).
- * (How many pairs reach the re-evaluation depends on the rows' squared norms against their distances.
- * slhc_knn_graph, slhc_knn_graph_opt and slhc_slhc* multiply a copy of X taken relative to its column
- * means, so an offset shared by all rows costs nothing; slhc_knn_graph_static, slhc_cross_1nn and
- * slhc_fused_1nn multiply the rows as they are, and on rows whose common offset dwarfs their distances
- * they re-evaluate most pairs: same results, far slower.  Centre such data before calling them.)
+ * (How many pairs reach the re-evaluation depends on the rows' norms against their distances.  The copies that are
+ * multiplied are taken relative to a central value of every column, so an offset shared by all rows costs nothing.)
  *
  *   X         DEVICE in   [N*d]
  *   nbr_idx   DEVICE out  [N*k] row-major int32
@@ -180,9 +178,9 @@ int slhc_knn_graph_opt(const float* X, int64_t N, int32_t d, int32_t k,
 /*
  * slhc_knn_graph for callers that cannot allocate and have no workspace to pass: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and the same
- * result as slhc_knn_graph, bit for bit; the scratch they need (a block of counters and one
- * float per row) is a fixed device array inside the library of 256 + 4 * SLHC_STATIC_MAX_ROWS
- * bytes, which every GPU the library runs on holds until the process ends.  The call allocates
+ * result as slhc_knn_graph, bit for bit; the scratch they need is a fixed device array inside the library of 128 MiB,
+ * which every GPU the library runs on holds until the process ends.  It holds the float16 copy of about 300 000 rows of
+ * 128 features; larger inputs go through the float32-product list kernels (same result, slower).  The call allocates
  * and frees nothing, on the device or on the host (its first call on a device looks up the
  * array's address).  N > SLHC_STATIC_MAX_ROWS is rejected with SLHC_UNSUPPORTED.
  * All calls on one GPU share that array: two calls that overlap in time on one GPU (different
@@ -262,8 +260,7 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour,
  * For each query row q < m: the index row j < n that minimises (||Q_q - Y_j||^2, j), and that
  * distance.  Same filter-then-re-evaluate arithmetic as slhc_knn_graph; nothing is excluded (a
  * query that also is an index row finds itself at distance 0).  With few query rows the index rows
- * are split over the workgroups and the partial minima are merged by a 64-bit atomic minimum over
- * (distance bits, index), so the result does not depend on the split.
+ * are split over the workgroups; the result does not depend on the split.
  *
  *   Q        DEVICE in  [m*d]        Y         DEVICE in  [n*d]
  *   out_idx  DEVICE out [m] int32    out_dist  DEVICE out [m] float32

@@ -1,0 +1,76 @@
+// Launch interface of the half-precision nearest-row engine (near_kernels.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace slhc {
+
+// What the copies of one problem share (device): the power of two the rows are multiplied by, and the largest
+// relative distance of a row from its rounded copy.
+struct NearScale {
+    float scale;
+    unsigned int eps_bits;
+    float spare[2];
+};
+
+// The rows of a matrix rounded to float16, in tiles of 128 in the order the matrix instruction reads them.
+// Position p of the copy holds row (p % 128) * tiles + p / 128, so every tile is an even sample of the rows.
+struct NearCopy {
+    unsigned char* frag;       // [tiles][steps of 16 columns][4 blocks of 32 rows][64 lanes][16 bytes]
+    float* negh;               // [tiles * 128] minus the half norm; -inf: no such row, +inf: values beyond float16
+    int32_t* colour;           // [tiles * 128] or nullptr
+    uint32_t* best;            // [tiles * 128] or nullptr: scratch of 1-NN searches for these rows as queries,
+    int32_t* count;            // and the same; near_make clears both
+    bool finite_padding;       // -1e38 instead of -inf (near_assign)
+    int rows, tiles;
+};
+
+inline int near_tiles(long long n) { return (int)((n + 127) / 128); }
+// steps of 16 columns: beyond 128 columns whole chunks of 64
+inline int near_steps(int d) { return d <= 128 ? (d + 15) / 16 : (d + 63) / 64 * 4; }
+inline size_t near_frag_bytes(long long n, int d) { return (size_t)near_tiles(n) * (size_t)near_steps(d) * 4096; }
+
+struct NearBuffers {           // scratch of one call
+    NearScale* scale;
+    float* shift;              // [d]
+    float* partial;            // near_stats_scratch_floats(d)
+    unsigned char* batch; size_t batch_bytes;     // bounds, group maxima, entries and counts of one batch of queries
+    int32_t* todo;             // [2 + panels of 128 queries]: count, spare, panels left to the list kernels
+    int32_t* todo_mark;        // [panels]
+    long long todo_panels;
+};
+
+struct NearProblem {
+    const float* Xq; const float* Xc;      // the rows themselves (exact evaluation)
+    int d, k;
+    const int32_t* q_rows;                 // row of Xq behind query i (nullptr: i); entries outside [0, nq_rows) answer "nothing"
+    int nq, nq_rows, nc;
+    int exclude_self;                      // queries are the candidates; a row is not its own neighbour
+    int coloured;                          // only candidates of another colour count
+    int32_t* out_idx; float* out_dist;     // [nq, k]
+    int32_t* evaluated;                    // optional [nq]: exactly evaluated pairs are added per query
+};
+
+size_t near_stats_scratch_floats(int d);
+// (kk: k, plus one where a query meets itself)
+size_t near_batch_bytes(long long nq, long long nc, int d, int kk);       // what NearBuffers::batch wants (less also works, down to one panel)
+size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk);
+bool near_supported(int d);
+
+// (clears `clear` [clear_words], optional, on the way)
+hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s);
+// fills `out` from rows (clear_todo: and clears the panels left to the list kernels, as near_stats does)
+// `rows` (nullptr: 0 .. n-1 of a matrix with n_src rows); hn / nonfinite (optional): the float32
+// half norms by row and the flag of launch_half_norms; colour (optional): by row
+hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
+                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo = false);
+// the colours of the rows of `c` into c.colour
+hipError_t near_colours(const NearCopy& c, const int32_t* colour, hipStream_t s);
+// For every row of q the row of c with the (nearly) largest product value, i.e. a nearest row up to the rounding of the
+// copies, and the distance to that row: one pass.  best_at: [q.tiles * 128] words of scratch; c has finite padding.
+hipError_t near_assign(const NearCopy& q, const NearCopy& c, const float* Xq, const int32_t* q_rows, const float* Xc, int d,
+                       const NearBuffers& b, unsigned long long* best_at, int32_t* out_idx, float* out_dist, hipStream_t s);
+hipError_t near_search(const NearProblem& p, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s);
+
+}  // namespace slhc

@@ -1,0 +1,1378 @@
+// Nearest rows by float16 tile products: threshold, emit, select.
+//
+// The tile products of the sweeps only decide which pairs are evaluated exactly, so what they need is not float32
+// products but a bound on what rounding can do.  Here every row is rounded ONCE to float16 (relative to a central
+// value of every column and times a power of two) and the products of the rounded rows are exact: 11 x 11 bits.  The
+// distance of the rounded rows then differs from that of the rows by no more than the two rows moved,
+//     |D(x, y) - D(x', y')| <= |x - x'| + |y - y'|      (triangle inequality),
+// a few 1e-4 of the rows' norms.  One v_mfma_f32_32x32x16_f16 per 16 columns does what the split bfloat16 copy needs
+// three instructions for, on half the bytes.
+//
+// A k-NN search runs in four launches instead of keeping lists inside the sweep:
+//   1. maxima   every query takes the largest product value in each of 32 groups per part of an even sample of the
+//               candidates; the k-th largest of all its group maxima is a threshold that k candidates reach;
+//   2. bounds   that value per query, turned into the product value any of its k nearest rows must reach;
+//   3. emit     all candidates against that fixed bound; the few that pass are appended to a buffer of the lane that
+//               found them (no list, no exact evaluation, no exchange between lanes in the loop);
+//   4. select   per query: a tighter bound from what was emitted, exact evaluation of what is left, ranks.
+// A 1-NN search needs no first pass: its bound follows the best product value seen so far.
+//
+// Every reported distance is the same float32 sum in the same order as in the list kernels (sweep_kernels.hip), so
+// the results are the same bits.  A query whose candidates do not fit its buffers even after tightening (masses of
+// ties) is left to the list kernels through a device-side list of panels.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "near_kernels.h"
+
+namespace slhc {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int TILE = 128;
+constexpr int FRAG_STEP = 4096;            // bytes of a tile per 16 columns
+constexpr int REG_STEPS = 8;               // up to 128 columns the query fragments stay in registers
+constexpr float F16_LIMIT = 60000.f;       // larger values (after scaling) do not fit
+constexpr float F16_FLUSH = 6.103515625e-05f;   // 2^-14: smaller ones are rounded to 0, so no subnormal is ever multiplied
+constexpr int SAMPLE_RUNS = 64, SAMPLE_PER_RUN = 32;
+constexpr int MAX_ENTRIES = 1024;          // entries of one query over all its buffers
+constexpr int GROUPS = 32;                 // group maxima per query and part
+constexpr float INF = __builtin_inff();
+constexpr float LOWEST = -3.4028234663852886e38f;      // a bound every product value of a real row reaches
+#define NEVER __builtin_nanf("")                       // a bound nothing reaches, +inf included
+
+// What the arithmetic on the rounded rows can be off by.  An instruction aligns its 16 products and the accumulator
+// to the largest magnitude, one bit below its last place, cuts the rest off, adds and rounds: at most 18 units of
+// 2^-24 of that magnitude.  The accumulator starts at minus half the candidate's squared norm, so no partial sum
+// exceeds n_c / 2 + |x_q||x_c| <= n_c + n_q / 2, and after `steps` instructions the value is off by at most
+// e (n_c + n_q / 2), e = 9 steps 2^-23.  nu: the relative error of a squared norm (8 ceil(steps / 8) + 8 rounded
+// additions).  The stored half norms are lowered by what belongs to the candidate: a value `acc` is never below the
+// true one by more than e n_q / 2.
+struct NearBoundArgs { float e, nu, h_of_n, eps, delta, gamma, tiny; };
+static float near_e(int steps) { return 9.f * (float)steps * 1.02f * 1.1920928955078125e-07f; }
+static float near_nu(int steps) { return (float)(8 * ((steps + 7) / 8) + 8) * 5.9604644775390625e-08f; }
+
+// The product value any row within (scaled, squared) distance t2 of the query reaches; h: the query's stored half norm.
+__device__ inline float near_bound_at(float t2, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    // what the exact evaluation's own rounding can hide, and underflow of its squares
+    const float t = __builtin_sqrtf(t2 * (1.f + a.gamma) + a.tiny);
+    const float rho_q = a.eps * norm + a.delta;
+    // a candidate within t of the query has a norm of at most norm + t + both displacements
+    const float rho_c = (a.eps * (norm + t + rho_q) + a.delta) * (1.f + 1e-3f);
+    const float reach = (t + rho_q + rho_c) * (1.f + 1e-6f);
+    return n * (0.5f - 0.5f * a.nu - 0.5f * a.e - 2.4e-7f) - 0.5f * reach * reach * (1.f + 1e-6f);
+}
+// From a product value some candidate shows: an upper bound of that candidate's distance (its squared norm n_c is at
+// most (|x_q| + D)^2 <= 1.25 n_q + 5 D^2), and from it the bound for all candidates that may be as near.
+__device__ inline float near_bound_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    const float of_c = 4.f * a.e + 2.f * a.nu;
+    const float d2 = fmaxf(0.f, n * (1.f + a.nu + a.e + 1.25f * of_c + 4.8e-7f) - 2.f * acc) * (1.f + 6.f * of_c);
+    const float dd = __builtin_sqrtf(d2);
+    const float rho_q = a.eps * norm + a.delta;
+    const float rho_c = (a.eps * (norm + dd) + a.delta) * (1.f + 1e-3f);
+    const float t = (dd + rho_q + rho_c) * (1.f + 1e-6f);
+    return near_bound_at(t * t * (1.f + a.gamma), h, a);
+}
+
+__device__ inline NearBoundArgs near_args(const NearScale* sc, int steps, int d, float e, float nu)
+{
+    NearBoundArgs a;
+    a.e = e; a.nu = nu;
+    a.h_of_n = 0.5f - 0.5f * nu - e;
+    a.eps = fminf(__uint_as_float(sc->eps_bits), 4.8876e-4f) * (1.f + 1e-3f);      // 2^-11 at most
+    a.delta = F16_FLUSH * __builtin_sqrtf((float)d);
+    a.gamma = (float)(2 * (d + 16)) * 1.1920928955078125e-07f;
+    a.tiny = (float)d * 2.350988701644575e-38f * sc->scale * sc->scale;            // d * 2^-125
+    return a;
+}
+
+// ---------------------------------------------------------------------------------------------- sample of the rows
+// Column means of SAMPLE_RUNS runs of evenly spaced rows, and per run the largest distance of a value from its run's
+// mean.  One workgroup per run and 256 columns; the additions of a run keep a fixed order.
+__global__ void __launch_bounds__(256) near_runs_kernel(const float* __restrict__ X, int n, int d, float* __restrict__ partial,
+                                                        float* __restrict__ run_max, NearScale* __restrict__ sc,
+                                                        uint32_t* __restrict__ clear, int clear_words, int32_t* __restrict__ todo,
+                                                        long long todo_words)
+{
+    {   // words that later launches of this call expect to be 0
+        const long long at = ((long long)blockIdx.y * gridDim.x + blockIdx.x) * 256 + threadIdx.x;
+        const long long step = (long long)gridDim.x * gridDim.y * 256;
+        for (long long i = at; i < todo_words; i += step) todo[i] = 0;
+        for (long long i = at; i < clear_words; i += step) clear[i] = 0u;
+    }
+    __shared__ float sums[256], cnts[256], mx[256];
+    const int run = blockIdx.x, tid = threadIdx.x;
+    const int c0 = blockIdx.y * 256;
+    const int cols = d - c0 < 256 ? d - c0 : 256;
+    int width = 1;
+    while (width < cols) width <<= 1;                       // threads per row
+    const int sub = 256 / width;                            // rows side by side
+    const int c = tid % width, g = tid / width;
+    const int samples = n < SAMPLE_RUNS * SAMPLE_PER_RUN ? n : SAMPLE_RUNS * SAMPLE_PER_RUN;
+    const int i0 = (int)((long long)run * samples / SAMPLE_RUNS), i1 = (int)((long long)(run + 1) * samples / SAMPLE_RUNS);
+    float v[SAMPLE_PER_RUN];
+    float sum = 0.f, cnt = 0.f;
+#pragma unroll
+    for (int j = 0; j < SAMPLE_PER_RUN; ++j) {
+        const int i = i0 + g + j * sub;
+        v[j] = __builtin_nanf("");
+        if (c < cols && i < i1) v[j] = X[(size_t)((long long)i * n / samples) * d + c0 + c];
+    }
+#pragma unroll
+    for (int j = 0; j < SAMPLE_PER_RUN; ++j)
+        if (fabsf(v[j]) < INF) { sum += v[j]; cnt += 1.f; }        // false for NaN
+    sums[tid] = sum; cnts[tid] = cnt;
+    __syncthreads();
+    float mean = 0.f;
+    {
+        float s = 0.f, m = 0.f;
+        for (int q = 0; q < sub; ++q) { s += sums[q * width + c]; m += cnts[q * width + c]; }
+        mean = m > 0.f ? s / m : __builtin_nanf("");
+    }
+    float far = 0.f;
+#pragma unroll
+    for (int j = 0; j < SAMPLE_PER_RUN; ++j) {
+        const float e = fabsf(v[j] - mean);
+        if (e < INF) far = fmaxf(far, e);
+    }
+    mx[tid] = far;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if (tid < w) mx[tid] = fmaxf(mx[tid], mx[tid + w]);
+        __syncthreads();
+    }
+    if (g == 0 && c < cols) partial[(size_t)run * d + c0 + c] = mean;
+    if (tid == 0) run_max[blockIdx.y * SAMPLE_RUNS + run] = i1 > i0 ? mx[0] : -1.f;
+    if (run == 0 && blockIdx.y == 0 && tid == 0) { sc->eps_bits = 0u; }
+}
+
+// the two middle values of 64 lanes' valid ones, averaged (0 valid: 0)
+__device__ inline float near_median64(float x, bool valid, int lane)
+{
+    const int n = __popcll(__ballot(valid));
+    int rank = 0;
+    const float key = valid ? x : INF;
+#pragma unroll
+    for (int q = 0; q < 64; ++q) {
+        const float y = __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(key), q));
+        if (y < x || (y == x && q < lane)) ++rank;
+    }
+    float pick = 0.f;
+    if (valid && n > 0) {
+        if (rank == ((n - 1) >> 1)) pick += 0.5f * x;
+        if (rank == (n >> 1)) pick += 0.5f * x;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) pick += __shfl_xor(pick, o);
+    return pick;
+}
+
+// shift[c] = the median of the runs' means (a single far row cannot drag it; a value beyond 2^50 is replaced by 0), and
+// the scale: the power of two that brings the median run's largest value near 2^7.  float16 then has room for rows
+// 500 times larger and keeps its full relative precision for values 2 million times smaller.
+__global__ void __launch_bounds__(256) near_shift_kernel(const float* __restrict__ partial, const float* __restrict__ run_max, int d,
+                                                         float* __restrict__ shift, NearScale* __restrict__ sc)
+{
+    const int lane = threadIdx.x & 63;
+    const int c = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (c < d) {
+        const float x = partial[(size_t)lane * d + c];
+        const float m = near_median64(x, fabsf(x) < INF, lane);
+        if (lane == 0) shift[c] = fabsf(m) <= 1.125899906842624e15f ? m : 0.f;
+    } else if (c == d) {
+        float x = -1.f;
+        const int parts = (d + 255) / 256;
+        for (int y = 0; y < parts; ++y) x = fmaxf(x, run_max[y * SAMPLE_RUNS + lane]);
+        float m = near_median64(x, x > 0.f, lane);
+        if (lane == 0) {
+            int e = 0;
+            if (m > 0.f && m < INF) (void)frexpf(m, &e);              // m = f * 2^e, f in [0.5, 1)
+            int up = 7 - e;
+            up = up < -100 ? -100 : (up > 100 ? 100 : up);
+            sc->scale = ldexpf(1.f, up);
+        }
+    }
+}
+
+size_t near_stats_scratch_floats(int d) { return (size_t)SAMPLE_RUNS * (size_t)d + (size_t)SAMPLE_RUNS * (size_t)((d + 255) / 256); }
+
+hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s)
+{
+    float* run_max = b.partial + (size_t)SAMPLE_RUNS * d;
+    hipLaunchKernelGGL(near_runs_kernel, dim3(SAMPLE_RUNS, (unsigned)((d + 255) / 256)), dim3(256), 0, s, X, n, d, b.partial, run_max, b.scale,
+                       clear, clear_words, b.todo, 2 + 2 * b.todo_panels);
+    hipLaunchKernelGGL(near_shift_kernel, dim3((unsigned)(d / 4 + 1)), dim3(256), 0, s, b.partial, run_max, d, b.shift, b.scale);
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------- the float16 copy
+struct NearMake {
+    const float* X; const int32_t* rows; const int32_t* colour; const float* shift; NearScale* sc;
+    unsigned char* frag; float* negh; int32_t* out_colour; float* hn; unsigned int* nonfinite;
+    int n_src, n, d, tiles, steps; float h_of_n, hn_scale, absent;
+    uint32_t* best; int32_t* count;
+    int32_t* todo; long long todo_words;
+};
+
+// One workgroup per block of 32 rows of a tile; LPR lanes share a row, eight columns each at a time.  The pieces go
+// through LDS so that they leave in whole lines.  Bound by reading X once and writing half of it.
+constexpr int MAKE_STEPS = 8;
+template <int LPR, bool VEC4>
+__global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
+{
+    __shared__ __align__(16) unsigned char stage[MAKE_STEPS * 1024];
+    __shared__ unsigned int eps_max;
+    const int tid = threadIdx.x;
+    const int t = blockIdx.x >> 2, blk = blockIdx.x & 3;
+    constexpr int ROWS = 256 / LPR;                  // rows side by side
+    constexpr int PASSES = ROWS >= 32 ? 1 : 32 / ROWS;
+    const int part = tid % LPR, sub = tid / LPR;
+    const bool mine = sub < 32;
+    const float scale = p.sc->scale;
+    if (tid == 0) eps_max = 0u;
+    for (long long i = (long long)blockIdx.x * 256 + tid; i < p.todo_words; i += (long long)gridDim.x * 256) p.todo[i] = 0;
+    float nn[PASSES], rr[PASSES], xx[PASSES];
+    bool huge[PASSES];
+    long long src[PASSES];
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
+        nn[i] = rr[i] = xx[i] = 0.f; huge[i] = false;
+        const long long at = (long long)(blk * 32 + sub + i * ROWS) * p.tiles + t;
+        long long row = mine && at < p.n ? (p.rows ? (long long)p.rows[at] : at) : -1;
+        if (row >= p.n_src) row = -1;
+        src[i] = row;
+    }
+    for (int s0 = 0; s0 < p.steps; s0 += MAKE_STEPS) {
+        const int ns = p.steps - s0 < MAKE_STEPS ? p.steps - s0 : MAKE_STEPS;
+        for (int oct = part; oct < 2 * ns; oct += LPR) {
+            const int col = 16 * s0 + 8 * oct;
+            float m[8];
+#pragma unroll
+            for (int e = 0; e < 8; ++e) m[e] = col + e < p.d ? p.shift[col + e] : 0.f;
+#pragma unroll
+            for (int i = 0; i < PASSES; ++i) {
+                const int r = sub + i * ROWS;
+                float v[8];
+                const float* x = p.X + (size_t)(src[i] < 0 ? 0 : src[i]) * p.d + col;
+                if (VEC4) {
+                    v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+                    if (src[i] >= 0 && col + 4 <= p.d) a = *reinterpret_cast<const v4f*>(x);
+                    if (src[i] >= 0 && col + 8 <= p.d) b = *reinterpret_cast<const v4f*>(x + 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+                } else {
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = (src[i] >= 0 && col + e < p.d) ? x[e] : 0.f;
+                }
+                v8h h;
+#pragma unroll
+                for (int e = 0; e < 8; ++e) {
+                    const bool live = src[i] >= 0 && col + e < p.d;
+                    xx[i] = __builtin_fmaf(v[e], v[e], xx[i]);
+                    float u = live ? (v[e] - m[e]) * scale : 0.f;
+                    if (fabsf(u) > F16_LIMIT) huge[i] = true;
+                    u = fminf(fmaxf(u, -F16_LIMIT), F16_LIMIT);        // NaN becomes a number here; its row is cut off below
+                    const bool flush = fabsf(u) < F16_FLUSH;
+                    const _Float16 q = flush ? (_Float16)0.f : (_Float16)u;
+                    const float w = (float)q;
+                    h[e] = q;
+                    nn[i] = __builtin_fmaf(w, w, nn[i]);
+                    const float res = flush ? 0.f : u - w;             // (flushed values: delta covers them)
+                    rr[i] = __builtin_fmaf(res, res, rr[i]);
+                }
+                if (mine) *reinterpret_cast<v8h*>(stage + (oct >> 1) * 1024 + ((oct & 1) * 32 + r) * 16) = h;
+            }
+        }
+        __syncthreads();
+        unsigned char* dst = p.frag + ((size_t)t * p.steps + s0) * FRAG_STEP + blk * 1024;
+        for (int i = tid; i < ns * 64; i += 256)
+            *reinterpret_cast<v4f*>(dst + (size_t)(i >> 6) * FRAG_STEP + (i & 63) * 16) = reinterpret_cast<const v4f*>(stage)[i];
+        __syncthreads();
+    }
+#pragma unroll
+    for (int i = 0; i < PASSES; ++i) {
+        float n = nn[i], r = rr[i], x = xx[i];
+        int hg = huge[i] ? 1 : 0;
+#pragma unroll
+        for (int o = 1; o < LPR; o <<= 1) {
+            n += __shfl_xor(n, o); r += __shfl_xor(r, o); x += __shfl_xor(x, o); hg |= __shfl_xor(hg, o);
+        }
+        if (part == 0 && mine) {
+            const int at = t * TILE + blk * 32 + sub + i * ROWS;
+            float nh = -p.h_of_n * n;
+            if (hg) nh = INF;
+            if (src[i] < 0 || !(x < INF)) nh = p.absent;         // no row, or one whose squared norm is not a finite float32
+            p.negh[at] = nh;
+            if (p.out_colour) p.out_colour[at] = src[i] >= 0 && p.colour ? p.colour[src[i]] : -1;
+            if (p.best) p.best[at] = 0u;
+            if (p.count) p.count[at] = 0;
+            if (src[i] >= 0) {
+                if (p.hn) p.hn[src[i]] = p.hn_scale * x;
+                if (p.nonfinite && !(x < INF)) atomicOr(p.nonfinite, 1u);
+                if (!hg && n > 0.f && r > 0.f) atomicMax(&eps_max, __float_as_uint(__builtin_sqrtf(r / n)));
+            }
+        }
+    }
+    __syncthreads();
+    // (2 units in the last place for the roundings of the two sums and of the difference from the shift)
+    if (tid == 0 && eps_max != 0u) {
+        const unsigned int mine_bits = __float_as_uint(__uint_as_float(eps_max) * (1.f + 1e-4f));
+        // most workgroups find the word already there and leave it alone
+        if (__hip_atomic_load(&p.sc->eps_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mine_bits) atomicMax(&p.sc->eps_bits, mine_bits);
+    }
+}
+
+bool near_supported(int d) { return d >= 1; }
+
+hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
+                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo)
+{
+    NearMake p{};
+    p.X = X; p.rows = rows; p.colour = colour; p.shift = b.shift; p.sc = b.scale;
+    p.frag = out.frag; p.negh = out.negh; p.out_colour = out.colour; p.hn = hn; p.nonfinite = nonfinite;
+    p.n_src = n_src; p.n = n; p.d = d; p.tiles = out.tiles; p.steps = near_steps(d); p.h_of_n = 0.5f - 0.5f * near_nu(p.steps) - near_e(p.steps);
+    p.best = out.best; p.count = out.count;
+    p.absent = out.finite_padding ? -1e38f : -INF;
+    p.todo = b.todo; p.todo_words = clear_todo ? 2 + 2 * b.todo_panels : 0;
+    p.hn_scale = 0.5f * (1.0f - (float)(d + 8) * 1.1920928955078125e-07f);         // as launch_half_norms
+    const bool vec4 = d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0;
+    const dim3 grid((unsigned)out.tiles * 4u), block(256);
+    if (p.steps <= 4) {
+        if (vec4) hipLaunchKernelGGL((near_make_kernel<8, true>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((near_make_kernel<8, false>), grid, block, 0, s, p);
+    } else {
+        if (vec4) hipLaunchKernelGGL((near_make_kernel<16, true>), grid, block, 0, s, p);
+        else hipLaunchKernelGGL((near_make_kernel<16, false>), grid, block, 0, s, p);
+    }
+    return hipGetLastError();
+}
+
+// ---------------------------------------------------------------------------------------------- the sweep
+struct NearSweep {
+    const unsigned char* qfrag; const float* qnegh; const int32_t* qcolour; int q_tile0, q_tile1;
+    const unsigned char* cfrag; const float* cnegh; const int32_t* ccolour; int c_tiles;
+    const NearScale* sc; float e, nu; int d, steps;
+    // item = panel * nseg + seg; seg takes tiles seg, seg + nseg, ... of a list of `used` candidate tiles: every
+    // stride-th one (skip = 0), or all but those (skip = 1)
+    int nseg, stride, used, skip;
+    int nsub;                          // buffers per query: the lanes that hold its values, over all segments
+    int kk;                            // candidates a query needs (itself included where it meets itself)
+    const float* bound;                // emit: [queries of the batch]
+    float* maxima; int parts, groups;  // maxima: [nseg * parts][queries of the batch][groups], groups 32 or 8
+    uint2* entries; int32_t* counts; int capl;      // emit: [queries of the batch][2 nseg][capl], [queries][2 nseg]
+                                                    // nearest: [queries of the batch][capl], counts by position
+    unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position
+    uint32_t* best;                    // nearest: largest product value of a query by position (ordered bits)
+    int nq_batch;
+};
+
+enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_BEST = 2, NEAR_NEAREST = 3, NEAR_ARG = 4 };
+
+__device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+// entries are written and read back by one wavefront, past its L1
+__device__ inline unsigned long long near_entry_load(const uint2* e)
+{
+    return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+__device__ inline unsigned int ordered_bits(float x)
+{
+    const unsigned int b = __float_as_uint(x);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+__device__ inline float from_ordered(unsigned int o)
+{
+    return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
+}
+
+// A value that at least kk of the wavefront's values v(i), i < n, reach, and not many more: bisection between the
+// smallest and the largest of them.  Values that are not finite do not count.  Returns LOWEST when fewer than kk are.
+constexpr int BISECT = 13;
+template <typename V>
+__device__ inline float near_kth(int n, int kk, V&& value)
+{
+    float lo = INF, hi = -INF;
+    int have = 0;
+    for (int i = 0; i < n; i += 64) {
+        const float x = value(i);
+        const bool fine = fabsf(x) < INF;
+        have += __popcll(__ballot(fine));
+        lo = fine ? fminf(lo, x) : lo;
+        hi = fine ? fmaxf(hi, x) : hi;
+    }
+    if (have < kk) return LOWEST;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    for (int it = 0; it < BISECT; ++it) {
+        const float mid = 0.5f * lo + 0.5f * hi;
+        int reach = 0;
+        for (int i = 0; i < n; i += 64) {
+            const float x = value(i);
+            reach += __popcll(__ballot(x >= mid && x < INF));
+        }
+        if (reach >= kk) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+// One lane's buffer is about to fill: the whole wavefront reads its n entries, finds the kk-th largest product value
+// (every one of them belongs to a different candidate, so kk candidates reach it) and keeps the entries that may
+// still be among the nearest.  Returns the new bound; *n the number kept.
+__device__ __attribute__((noinline)) float near_refine(uint2* buf, int* n_, int kk, float h, NearBoundArgs a)
+{
+    const int lane = threadIdx.x & 63;
+    const int n = *n_;
+    __builtin_amdgcn_s_waitcnt(0x0f70);
+    const float kth = near_kth(n, kk, [&](int i) {
+        return i + lane < n ? __uint_as_float((unsigned int)near_entry_load(buf + i + lane)) : -INF;
+    });
+    if (kth == LOWEST) return LOWEST;
+    const float bound = near_bound_from(kth, h, a);
+    int kept = 0;
+    for (int i = 0; i < n; i += 64) {
+        const unsigned long long e = i + lane < n ? near_entry_load(buf + i + lane) : 0ull;
+        const bool keep = i + lane < n && __uint_as_float((unsigned int)e) >= bound;
+        const unsigned long long m = __ballot(keep);
+        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+        if (keep) __hip_atomic_store(reinterpret_cast<unsigned long long*>(buf + kept + pre), e, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        kept += __popcll(m);
+    }
+    *n_ = kept;
+    return bound;
+}
+
+// What a lane carries for its two queries (one of each block of 32) through a sweep, and what it does with the values
+// of 64 candidates.
+template <int MODE, bool COLOURED>
+struct NearLane {
+    float h[2], bound[2];
+    int qcol[2];
+    unsigned int off[2], roomy[2];          // byte offsets into the entries: next free, last with room for 32
+    float m[2][16], m1[2];
+    int m1_at[2];
+    NearBoundArgs args;
+    int q_at[2];                            // position of the query, and its number in the batch
+    int lq[2];
+
+    // queries of block `qblk` and the next one of tile `qtile`; `sub`: the buffer of this lane among the p.nsub of a query
+    __device__ inline void start(const NearSweep& p, int qtile, int qblk, int l32, int sub, bool live)
+    {
+        if (MODE == NEAR_EMIT || MODE == NEAR_NEAREST) args = near_args(p.sc, p.steps, p.d, p.e, p.nu);
+        const int qt = live ? qtile : p.q_tile0;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            q_at[qb] = qt * TILE + (qblk + qb) * 32 + l32;
+            lq[qb] = q_at[qb] - p.q_tile0 * TILE;
+            const float nh = p.qnegh[q_at[qb]];
+            h[qb] = -nh;
+            const bool ok = live && fabsf(nh) < INF;
+            bound[qb] = NEVER;
+            if (MODE == NEAR_EMIT && ok) bound[qb] = p.bound[lq[qb]];
+            if (MODE == NEAR_NEAREST && ok) {
+                const unsigned int best = p.best[q_at[qb]];
+                // (none found: nothing is admissible, or values beyond float16 hide it; the latter end up with the list kernels)
+                bound[qb] = best != 0u ? fmaxf(LOWEST, near_bound_from(from_ordered(best), h[qb], args)) : LOWEST;
+            }
+            if (COLOURED) qcol[qb] = p.qcolour[q_at[qb]];
+            if (MODE == NEAR_EMIT) {
+                off[qb] = ((unsigned int)lq[qb] * (unsigned int)p.nsub + (unsigned int)sub) * (unsigned int)p.capl * 8u;
+                roomy[qb] = off[qb] + (unsigned int)(p.capl - 32) * 8u;
+            }
+            m1[qb] = -INF;
+            m1_at[qb] = -1;
+            if (MODE == NEAR_MAXIMA) {
+#pragma unroll
+                for (int r = 0; r < 16; ++r) m[qb][r] = -INF;
+            }
+        }
+    }
+
+    // acc[query block][candidate block]: value r of a lane belongs to candidate 8 (r / 4) + 4 lhalf + r % 4 of its block;
+    // pos0: position of the first of the 64 candidates, col: their colours (LDS)
+    __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf)
+    {
+        const int lane = threadIdx.x & 63;
+        if (COLOURED) {
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4i cc = *reinterpret_cast<const v4i*>(col + (cb * 32 + 8 * g + 4 * lhalf) * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e)
+#pragma unroll
+                        for (int qb = 0; qb < 2; ++qb) acc[qb][cb][4 * g + e] = cc[e] == qcol[qb] ? -INF : acc[qb][cb][4 * g + e];
+                }
+        }
+        if (MODE == NEAR_MAXIMA) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) m[qb][r] = max3(m[qb][r], acc[qb][0][r], acc[qb][1][r]);
+            return;
+        }
+        if (MODE == NEAR_BEST) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) m1[qb] = max3(m1[qb], acc[qb][0][r], acc[qb][1][r]);
+            return;
+        }
+        if (MODE == NEAR_ARG) {
+            // the number of the value within the 64 candidates replaces the five lowest bits of its mantissa (an infinity
+            // would become a NaN: copies used here have finite padding)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                float mx = -INF;
+#pragma unroll
+                for (int i = 0; i < 32; i += 2) {
+                    const float a = __uint_as_float((__float_as_uint(acc[qb][i >> 4][i & 15]) & 0xffffffe0u) | (unsigned int)i);
+                    const float b = __uint_as_float((__float_as_uint(acc[qb][i >> 4][(i & 15) + 1]) & 0xffffffe0u) | (unsigned int)(i + 1));
+                    mx = max3(mx, a, b);
+                }
+                const bool up = mx > m1[qb];
+                m1_at[qb] = up ? pos0 : m1_at[qb];
+                m1[qb] = up ? mx : m1[qb];
+            }
+            return;
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            // maxima of 5, 5, 3 and 3 values of each block (three at a time in one instruction), and of all
+            constexpr int from[5] = {0, 5, 10, 13, 16};
+            float g8[8];
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                const v16f& v = acc[qb][g >> 2];
+                const int r = from[g & 3];
+                g8[g] = max3(v[r], v[r + 1], v[r + 2]);
+                if ((g & 3) < 2) g8[g] = max3(g8[g], v[r + 3], v[r + 4]);
+            }
+            const float mx = fmaxf(max3(max3(g8[0], g8[1], g8[2]), max3(g8[3], g8[4], g8[5]), g8[6]), g8[7]);
+            if (!__any(mx >= bound[qb])) continue;
+#pragma unroll
+            for (int g = 0; g < 8; ++g) {
+                if (__any(g8[g] >= bound[qb])) {
+#pragma unroll
+                    for (int r = from[g & 3]; r < from[(g & 3) + 1]; ++r) {
+                        const float v = acc[qb][g >> 2][r];
+                        if (__any(v >= bound[qb]) && v >= bound[qb]) {
+                            const int pos = pos0 + (g >> 2) * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
+                            if (MODE == NEAR_EMIT) {
+                                *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.entries) + off[qb]) =
+                                    make_uint2(__float_as_uint(v), (unsigned int)pos);
+                                off[qb] += 8u;
+                            } else {
+                                // (a handful per query over all workgroups)
+                                const int at = atomicAdd(p.counts + q_at[qb], 1);
+                                if (at < p.capl) p.entries[(size_t)lq[qb] * p.capl + at] = make_uint2(__float_as_uint(v), (unsigned int)pos);
+                            }
+                        }
+                    }
+                }
+            }
+            if (MODE != NEAR_EMIT) continue;
+            // room for the 32 values that come next, or tighten
+            unsigned long long full = __ballot(off[qb] > roomy[qb]);
+            while (full) {
+                const int who = __builtin_ctzll(full);
+                full &= full - 1;
+                const unsigned int start = (unsigned int)__builtin_amdgcn_readlane((int)roomy[qb], who) - (unsigned int)(p.capl - 32) * 8u;
+                int n = (int)(((unsigned int)__builtin_amdgcn_readlane((int)off[qb], who) - start) >> 3);
+                const float hw = __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(h[qb]), who));
+                const float nb = near_refine(reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.entries) + start), &n, p.kk, hw, args);
+                if (lane == who) {
+                    off[qb] = start + (unsigned int)n * 8u;
+                    bound[qb] = fmaxf(bound[qb], nb);
+                    // ties by the hundred: this query is given up here (count capl + 1) and takes nothing more
+                    if (n > p.capl - 32) { off[qb] = 0u; roomy[qb] = 0xffffffffu; bound[qb] = NEVER; }
+                }
+            }
+        }
+    }
+
+    // one part of the maxima ends
+    __device__ inline void flush(const NearSweep& p, int part_at, int lhalf, bool live)
+    {
+        if (live) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) {
+                float* out = p.maxima + ((size_t)part_at * p.nq_batch + lq[qb]) * p.groups + (p.groups >> 1) * lhalf;
+                v4f few;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4f v = {m[qb][4 * g], m[qb][4 * g + 1], m[qb][4 * g + 2], m[qb][4 * g + 3]};
+                    if (p.groups == GROUPS) *reinterpret_cast<v4f*>(out + 4 * g) = v;
+                    few[g] = fmaxf(max3(v[0], v[1], v[2]), v[3]);
+                }
+                if (p.groups != GROUPS) *reinterpret_cast<v4f*>(out) = few;
+            }
+        }
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) m[qb][r] = -INF;
+    }
+
+    __device__ inline void finish(const NearSweep& p, int sub, int lhalf, bool live)
+    {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) {
+            if (MODE == NEAR_BEST) {
+                const float v = fmaxf(m1[qb], __shfl_xor(m1[qb], 32));
+                if (live && lhalf == 0 && v > -INF && v < INF) atomicMax(p.best + q_at[qb], ordered_bits(v));
+            }
+            if (MODE == NEAR_ARG && live && m1_at[qb] >= 0 && fabsf(m1[qb]) < 1e37f) {
+                const int i = (int)(__float_as_uint(m1[qb]) & 31u), r = i & 15;
+                const int pos = m1_at[qb] + (i >> 4) * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
+                atomicMax(p.best_at + q_at[qb], ((unsigned long long)ordered_bits(m1[qb]) << 32) | (unsigned int)pos);
+            }
+            if (MODE == NEAR_EMIT && live)
+                p.counts[(size_t)lq[qb] * p.nsub + sub] =
+                    roomy[qb] == 0xffffffffu ? p.capl + 1 : (int)((off[qb] + (unsigned int)(p.capl - 32) * 8u - roomy[qb]) >> 3);
+        }
+    }
+};
+
+__device__ inline void near_lds_load(const void* g, void* l, bool quad)
+{
+    if (quad)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+    else
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 4, 0, 0);
+}
+
+__device__ inline int near_tile_at(const NearSweep& p, int seg, int i)
+{
+    const int j = seg + i * p.nseg;
+    return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride;
+}
+
+// Waits for this wavefront's loads into LDS, then for the other wavefronts.
+__device__ inline void near_lds_ready()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+// Up to 128 columns: a wavefront keeps the fragments of its 64 queries (two blocks of 32) in registers and passes over
+// the candidate tiles, which the workgroup's wavefronts bring into LDS together (double buffered, one barrier per
+// tile).  A lane's 16 values of a 32 x 32 block belong to one query, so bounds and counts are registers.
+// Fragment order in memory makes every load and every LDS read consecutive over the lanes.
+template <int KS, int MODE, bool COLOURED>
+__global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
+{
+    extern __shared__ __align__(16) unsigned char near_smem[];
+    constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, colours
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = blockDim.x >> 6;
+    const int panel = blockIdx.x / p.nseg, seg = blockIdx.x - panel * p.nseg;
+    const int qtile = p.q_tile0 + panel * (waves >> 1) + (wave >> 1);
+    const bool live = qtile < p.q_tile1;                 // (whole wavefronts)
+    const int qblk = (wave & 1) * 2;
+
+    NearLane<MODE, COLOURED> mine;
+    mine.start(p, qtile, qblk, l32, 2 * seg + lhalf, live);
+    v8h qf[2][KS];
+    {
+        const size_t qt = live ? qtile : p.q_tile0;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks)
+                qf[qb][ks] = *reinterpret_cast<const v8h*>(p.qfrag + (qt * KS + ks) * FRAG_STEP + (qblk + qb) * 1024 + lane * 16);
+    }
+
+    const int ntiles = seg < p.used ? (p.used - seg + p.nseg - 1) / p.nseg : 0;
+    auto stage = [&](int i) {
+        const size_t t = near_tile_at(p, seg, i);
+        unsigned char* dst = near_smem + (i & 1) * BUF;
+        const unsigned char* src = p.cfrag + t * (KS * FRAG_STEP);
+        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
+        for (int j = wave; j < (COLOURED ? 4 : 2); j += waves) {
+            const void* g = j < 2 ? (const void*)(p.cnegh + t * TILE + j * 64 + lane) : (const void*)(p.ccolour + t * TILE + (j - 2) * 64 + lane);
+            near_lds_load(g, dst + KS * FRAG_STEP + j * 256, false);
+        }
+    };
+    if (ntiles > 0) stage(0);
+    const int per_part = MODE == NEAR_MAXIMA ? (ntiles + p.parts - 1) / p.parts : 0;
+    int part = 0, part_end = per_part;
+    for (int i = 0; i < ntiles; ++i) {
+        near_lds_ready();
+        if (i + 1 < ntiles) stage(i + 1);
+        const unsigned char* tb = near_smem + (i & 1) * BUF;
+        const int pos0 = near_tile_at(p, seg, i) * TILE;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            v16f acc[2][2];
+            v8h cf[2][2];
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(tb + (half * 2 + cb) * 1024 + lane * 16);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                v16f hv;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
+                    hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
+                }
+                acc[0][cb] = hv; acc[1][cb] = hv;
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                // the next step's fragments are on their way while this step is multiplied (the fence keeps the reads
+                // from sinking to their use, which leaves the whole LDS latency between two groups of multiplies)
+                if (ks + 1 < KS) {
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb)
+                        cf[(ks + 1) & 1][cb] = *reinterpret_cast<const v8h*>(tb + (ks + 1) * FRAG_STEP + (half * 2 + cb) * 1024 + lane * 16);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb)
+                        acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
+            }
+            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf);
+        }
+        if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == ntiles)) {
+            mine.flush(p, seg * p.parts + part, lhalf, live);
+            ++part;
+            part_end += per_part;
+        }
+    }
+    if (MODE == NEAR_MAXIMA)
+        for (; part < p.parts; ++part) mine.flush(p, seg * p.parts + part, lhalf, live);
+    mine.finish(p, 2 * seg + lhalf, lhalf, live);
+}
+
+// Beyond 128 columns: 256 queries x 256 candidates per workgroup, both streamed through LDS 64 columns at a time
+// (double buffered), a wavefront holding 64 x 128 of the products.  Consecutive items of an XCD are the segments of
+// neighbouring panels: its 32 workgroups share 8 panels of queries, which stay in its L2, and read the same candidates.
+constexpr int WIDE_STEPS = 4;
+constexpr int WIDE_HALF = 2 * WIDE_STEPS * FRAG_STEP;                   // two tiles' steps: 32 KiB
+constexpr int WIDE_BUF = 2 * WIDE_HALF;
+constexpr int WIDE_LDS = 2 * WIDE_BUF + 2 * 2048;                       // + half norms and colours of 256 candidates, twice
+
+template <int MODE, bool COLOURED>
+__global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
+{
+    extern __shared__ __align__(16) unsigned char near_smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qg = wave >> 1, cg = wave & 1;                            // 64 queries, 128 candidates of the 256 x 256
+    int item = blockIdx.x;
+    {
+        const int per = gridDim.x >> 3;                                 // workgroups b, b + 8, ... share an XCD
+        if (item < per * 8) item = (item & 7) * per + (item >> 3);
+    }
+    const int panel = item / p.nseg, seg = item - panel * p.nseg;
+    const int qtile0 = p.q_tile0 + panel * 2;
+    const int qtile = qtile0 + (qg >> 1);
+    const bool live = qtile < p.q_tile1;
+    const int qblk = (qg & 1) * 2;
+    const int sub = (2 * seg + cg) * 2 + lhalf;
+
+    NearLane<MODE, COLOURED> mine;
+    mine.start(p, qtile, qblk, l32, sub, live);
+
+    const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
+    const int npairs = (p.used + 1) / 2;                                // pairs of listed tiles
+    const int nmine = seg < npairs ? (npairs - seg + p.nseg - 1) / p.nseg : 0;
+    auto listed = [&](int j) -> int { return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride; };
+    const int total = nmine * nchunks;
+    // the loads of step `at` (pair, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the norms with chunk 0
+    auto stage = [&](int i, int chunk, int at) {
+        unsigned char* dst = near_smem + (at & 1) * WIDE_BUF;
+        const int j0 = 2 * (seg + i * p.nseg);
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block]
+            const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
+            size_t t;
+            if (side == 0) t = qtile0 + tile < p.q_tile1 ? qtile0 + tile : qtile0;
+            else t = listed(j0 + tile < p.used ? j0 + tile : j0);
+            const unsigned char* base = side == 0 ? p.qfrag : p.cfrag;
+            near_lds_load(base + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16, dst + piece * 1024, true);
+        }
+        if (chunk == 0 && wave < (COLOURED ? 8 : 4)) {
+            const int tile = (wave >> 1) & 1, half = wave & 1;
+            const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
+            const void* g = wave < 4 ? (const void*)(p.cnegh + t * TILE + half * 64 + lane) : (const void*)(p.ccolour + t * TILE + half * 64 + lane);
+            near_lds_load(g, near_smem + 2 * WIDE_BUF + (i & 1) * 2048 + wave * 256, false);
+        }
+    };
+    const int per_part = MODE == NEAR_MAXIMA ? (nmine + p.parts - 1) / p.parts : 0;
+    int part = 0, part_end = per_part;
+    if (total > 0) stage(0, 0, 0);
+    int at = 0;
+    for (int i = 0; i < nmine; ++i) {
+        const unsigned char* nb = near_smem + 2 * WIDE_BUF + (i & 1) * 2048;
+        v16f acc[2][2][2];                                              // [pair of candidate blocks][query block][candidate block]
+        const bool half_pair = 2 * (seg + i * p.nseg) + cg >= p.used;   // the second tile of the last pair may be missing
+        auto step = [&]() {
+            const unsigned char* qs = near_smem + (at & 1) * WIDE_BUF + (qg >> 1) * (WIDE_STEPS * FRAG_STEP) + qblk * 1024 + lane * 16;
+            const unsigned char* cs = near_smem + (at & 1) * WIDE_BUF + WIDE_HALF + cg * (WIDE_STEPS * FRAG_STEP) + lane * 16;
+            v8h qf[2][2], cf[2][4];
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) qf[0][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
+#pragma unroll
+            for (int st = 0; st < WIDE_STEPS; ++st) {
+                if (st + 1 < WIDE_STEPS) {
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) qf[(st + 1) & 1][qb] = *reinterpret_cast<const v8h*>(qs + (st + 1) * FRAG_STEP + qb * 1024);
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) cf[(st + 1) & 1][cb] = *reinterpret_cast<const v8h*>(cs + (st + 1) * FRAG_STEP + cb * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb)
+                        acc[cb >> 1][qb][cb & 1] =
+                            __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st & 1][cb], qf[st & 1][qb], acc[cb >> 1][qb][cb & 1], 0, 0, 0);
+            }
+        };
+        near_lds_ready();
+        if (at + 1 < total) stage(nchunks > 1 ? i : i + 1, nchunks > 1 ? 1 : 0, at + 1);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            v16f hv;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4f t4 = *reinterpret_cast<const v4f*>(nb + cg * 512 + (cb * 32 + 8 * g + 4 * lhalf) * 4);
+                hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
+            }
+            acc[cb >> 1][0][cb & 1] = hv; acc[cb >> 1][1][cb & 1] = hv;
+        }
+        step();
+        ++at;
+        for (int chunk = 1; chunk < nchunks; ++chunk, ++at) {
+            near_lds_ready();
+            if (at + 1 < total) {
+                const bool wrap = chunk + 1 == nchunks;
+                stage(wrap ? i + 1 : i, wrap ? 0 : chunk + 1, at + 1);
+            }
+            step();
+        }
+        const int j = 2 * (seg + i * p.nseg) + cg;
+        const int pos0 = listed(j < p.used ? j : 0) * TILE;
+        if (!half_pair) {
+            mine.take(p, acc[0], pos0, nb + 1024 + cg * 512, lhalf);
+            mine.take(p, acc[1], pos0 + 64, nb + 1024 + cg * 512 + 256, lhalf);
+        }
+        if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == nmine)) {
+            mine.flush(p, (2 * seg + cg) * p.parts + part, lhalf, live);
+            ++part;
+            part_end += per_part;
+        }
+    }
+    if (MODE == NEAR_MAXIMA)
+        for (; part < p.parts; ++part) mine.flush(p, (2 * seg + cg) * p.parts + part, lhalf, live);
+    mine.finish(p, sub, lhalf, live);
+}
+
+// One wavefront per query: (nearly) the kk-th largest of its group maxima, and the bound that follows.
+__global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restrict__ maxima, int parts, int log_groups, int nq_batch, int q0, int kk,
+                                                          const float* __restrict__ qnegh, const NearScale* __restrict__ sc, float e,
+                                                          float nu, int steps, int d, float* __restrict__ bound)
+{
+    const int lane = threadIdx.x & 63;
+    const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (lq >= nq_batch) return;
+    const int n = parts << log_groups;               // at most 1024
+    float v[16];
+#pragma unroll
+    for (int j = 0; j < 16; ++j) {
+        const int i = j * 64 + lane;
+        v[j] = i < n ? maxima[(((size_t)(i >> log_groups) * nq_batch + lq) << log_groups) + (i & ((1 << log_groups) - 1))] : -INF;
+    }
+    float lo = INF, hi = -INF;
+    int have = 0;
+#pragma unroll
+    for (int j = 0; j < 16; ++j)
+        if (j * 64 < n) {
+            const bool fine = fabsf(v[j]) < INF;
+            have += __popcll(__ballot(fine));
+            lo = fine ? fminf(lo, v[j]) : lo;
+            hi = fine ? fmaxf(hi, v[j]) : hi;
+            v[j] = fine ? v[j] : -INF;
+        }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    if (have >= kk)
+        for (int it = 0; it < BISECT; ++it) {
+            const float mid = 0.5f * lo + 0.5f * hi;
+            int reach = 0;
+#pragma unroll
+            for (int j = 0; j < 16; ++j)
+                if (j * 64 < n) reach += __popcll(__ballot(v[j] >= mid));
+            if (reach >= kk) lo = mid; else hi = mid;
+        }
+    if (lane == 0) {
+        const float nh = qnegh[q0 + lq];
+        const NearBoundArgs a = near_args(sc, steps, d, e, nu);
+        bound[lq] = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
+    }
+}
+
+// ---------------------------------------------------------------------------------------------- selection
+struct NearSelect {
+    const uint2* entries; const int32_t* counts; int nsub, capl, nq_batch, q0, by_position;
+    const float* qnegh; const NearScale* sc; float e, nu; int steps;
+    const float* Xq; const float* Xc; const int32_t* q_rows;
+    int d, k, kk, nq, nq_rows, nc, q_tiles, c_tiles, exclude_self;
+    int32_t* out_idx; float* out_dist; int32_t* evaluated;
+    int32_t* todo; int32_t* todo_mark;
+    int merge;                       // the output rows already hold the list of earlier candidates
+    float* next_bound;               // optional: the bound the list implies, for the candidates still to come
+};
+
+template <bool VEC4>
+__device__ inline v4f near_quad(const float* __restrict__ row, int t, int d)
+{
+    v4f v = {0.f, 0.f, 0.f, 0.f};
+    if (VEC4) {
+        if (t < d) v = *reinterpret_cast<const v4f*>(row + t);
+    } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e)
+            if (t + e < d) v[e] = row[t + e];
+    }
+    return v;
+}
+__device__ inline float near_quad_sqdist(v4f a, v4f b, float s)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) { const float x = a[e] - b[e]; s = __builtin_fmaf(x, x, s); }
+    return s;
+}
+
+// One wavefront per query.  The exact distance adds in the order of group8_sqdist (sweep_kernels.hip): slabs of 64
+// features, lane g of eight adds features 4g.. and 4(g + 8).. of every slab into two sums, xor butterfly 1, 2, 4.
+template <bool VEC4>
+__global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
+{
+    __shared__ unsigned long long keys_[4][MAX_ENTRIES + 64];
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+    const int lq = blockIdx.x * 4 + w;
+    if (lq >= p.nq_batch) return;
+    unsigned long long* keys = keys_[w];
+    const int qpos = p.q0 + lq;
+    const long long qi = (long long)(qpos & (TILE - 1)) * p.q_tiles + (qpos >> 7);
+    if (qi >= p.nq) return;                                     // padding of the last tiles
+    const long long row = p.q_rows ? (long long)p.q_rows[qi] : qi;
+    const float nh = p.qnegh[qpos];
+    if (row < 0 || row >= p.nq_rows || nh == -INF) {            // not a row, or not a finite one
+        for (int j = lane; j < p.k; j += 64) { p.out_idx[qi * p.k + j] = -1; p.out_dist[qi * p.k + j] = INF; }
+        if (p.evaluated && lane == 0) p.evaluated[qi] = 0;
+        return;
+    }
+    // gather the entries of all buffers: counts side by side over the lanes, running totals, then every lane looks up
+    // the buffer its entry lies in
+    int n = 0;
+    bool lost = nh == INF;
+    {
+        const int mine = lane < p.nsub ? p.counts[p.by_position ? (size_t)qpos : (size_t)lq * p.nsub + lane] : 0;
+        lost = lost || __any(mine > p.capl);
+        int upto = mine;
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(upto, o);
+            if (lane >= o) upto += x;
+        }
+        n = lost ? 0 : __builtin_amdgcn_readlane(upto, 63);
+        const unsigned long long* e = reinterpret_cast<const unsigned long long*>(p.entries) + (size_t)lq * p.nsub * p.capl;
+        for (int i = 0; i < n; i += 64) {
+            const int at = i + lane;
+            int sub = 0;                                        // number of buffers that end at or before `at`
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) {
+                const int end = __shfl(upto, sub + o - 1);
+                if (sub + o <= p.nsub && end <= at) sub += o;
+            }
+            const int begin = __shfl(upto - mine, sub & 63);
+            if (at < n) keys[at] = e[(size_t)sub * p.capl + (at - begin)];
+        }
+    }
+    if (lost) {
+        if (lane == 0) {
+            const int panel = (int)(qi >> 7);
+            if (atomicExch(p.todo_mark + panel, 1) == 0) p.todo[2 + atomicAdd(p.todo, 1)] = panel;
+            if (p.next_bound) p.next_bound[lq] = NEVER;
+            if (p.evaluated) p.evaluated[qi] = 0;
+        }
+        return;
+    }
+    __builtin_amdgcn_wave_barrier();
+    // a tighter bound from (nearly) the kk-th largest product value emitted
+    float bound = LOWEST;
+    const NearBoundArgs args = near_args(p.sc, p.steps, p.d, p.e, p.nu);
+    if (n > p.kk + 4) {
+        const float kth = near_kth(n, p.kk, [&](int i) { return i + lane < n ? __uint_as_float((unsigned int)keys[i + lane]) : -INF; });
+        if (kth != LOWEST) bound = near_bound_from(kth, -nh, args);
+    }
+    // keep what reaches it, without the query itself; positions become row numbers
+    int left = 0;
+    for (int i = 0; i < n; i += 64) {
+        unsigned long long e = i + lane < n ? keys[i + lane] : 0ull;
+        const int pos = (int)(e >> 32);
+        const long long cand = (long long)(pos & (TILE - 1)) * p.c_tiles + (pos >> 7);
+        const bool keep = i + lane < n && __uint_as_float((unsigned int)e) >= bound && cand < p.nc && !(p.exclude_self && cand == row);
+        const unsigned long long mask = __ballot(keep);
+        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
+        __builtin_amdgcn_wave_barrier();
+        if (keep) keys[left + pre] = (unsigned long long)cand;
+        left += __popcll(mask);
+        __builtin_amdgcn_wave_barrier();
+    }
+    // exact distances, eight pairs at a time
+    const int grp = lane >> 3, g = lane & 7;
+    const float* xa = p.Xq + (size_t)row * p.d;
+    const v4f q00 = near_quad<VEC4>(xa, 4 * g, p.d), q10 = near_quad<VEC4>(xa, 4 * g + 32, p.d);
+    const v4f q01 = near_quad<VEC4>(xa, 4 * g + 64, p.d), q11 = near_quad<VEC4>(xa, 4 * g + 96, p.d);
+    for (int i = 0; i < left; i += 8) {
+        const bool valid = i + grp < left;
+        const unsigned int cand = (unsigned int)keys[valid ? i + grp : i];
+        const float* xb = p.Xc + (size_t)cand * p.d;
+        float s0 = 0.f, s1 = 0.f;
+        {
+            const v4f b00 = near_quad<VEC4>(xb, 4 * g, p.d), b10 = near_quad<VEC4>(xb, 4 * g + 32, p.d);
+            const v4f b01 = near_quad<VEC4>(xb, 4 * g + 64, p.d), b11 = near_quad<VEC4>(xb, 4 * g + 96, p.d);
+            s0 = near_quad_sqdist(q00, b00, s0); s0 = near_quad_sqdist(q01, b01, s0);
+            s1 = near_quad_sqdist(q10, b10, s1); s1 = near_quad_sqdist(q11, b11, s1);
+        }
+        for (int base = 128; base < p.d; base += 128) {
+            const int t0 = base + 4 * g;
+            const v4f a00 = near_quad<VEC4>(xa, t0, p.d), b00 = near_quad<VEC4>(xb, t0, p.d);
+            const v4f a10 = near_quad<VEC4>(xa, t0 + 32, p.d), b10 = near_quad<VEC4>(xb, t0 + 32, p.d);
+            const v4f a01 = near_quad<VEC4>(xa, t0 + 64, p.d), b01 = near_quad<VEC4>(xb, t0 + 64, p.d);
+            const v4f a11 = near_quad<VEC4>(xa, t0 + 96, p.d), b11 = near_quad<VEC4>(xb, t0 + 96, p.d);
+            s0 = near_quad_sqdist(a00, b00, s0); s0 = near_quad_sqdist(a01, b01, s0);
+            s1 = near_quad_sqdist(a10, b10, s1); s1 = near_quad_sqdist(a11, b11, s1);
+        }
+        s0 += __shfl_xor(s0, 1); s0 += __shfl_xor(s0, 2); s0 += __shfl_xor(s0, 4);
+        s1 += __shfl_xor(s1, 1); s1 += __shfl_xor(s1, 2); s1 += __shfl_xor(s1, 4);
+        const float dist = s0 + s1;
+        __builtin_amdgcn_wave_barrier();
+        if (valid && g == 0) keys[i + grp] = ((unsigned long long)__float_as_uint(dist) << 32) | cand;
+        __builtin_amdgcn_wave_barrier();
+    }
+    if (p.evaluated && lane == 0) p.evaluated[qi] = left + (p.merge ? p.evaluated[qi] : 0);
+    if (p.merge) {
+        for (int j = 0; j < p.k; j += 64)
+            if (j + lane < p.k)
+                keys[left + j + lane] = ((unsigned long long)__float_as_uint(p.out_dist[qi * p.k + j + lane]) << 32) | (unsigned int)p.out_idx[qi * p.k + j + lane];
+        left += p.k;
+        __builtin_amdgcn_wave_barrier();
+    }
+    // ranks by (distance, row): every key against all of them
+    for (int i = 0; i < left; i += 64) {
+        const unsigned long long mine = i + lane < left ? keys[i + lane] : ~0ull;
+        int rank = 0;
+        for (int j = 0; j < left; ++j) rank += keys[j] < mine ? 1 : 0;
+        if (i + lane < left && rank < p.k) {
+            p.out_idx[qi * p.k + rank] = (int32_t)(unsigned int)mine;
+            p.out_dist[qi * p.k + rank] = __uint_as_float((unsigned int)(mine >> 32));
+            if (rank == p.k - 1 && p.next_bound)
+                p.next_bound[lq] = near_bound_at(__uint_as_float((unsigned int)(mine >> 32)) * p.sc->scale * p.sc->scale, -nh, args);
+        }
+    }
+    for (int j = left + lane; j < p.k; j += 64) { p.out_idx[qi * p.k + j] = -1; p.out_dist[qi * p.k + j] = INF; }
+    if (p.next_bound && lane == 0 && left < p.k) p.next_bound[lq] = LOWEST;
+}
+
+// ---------------------------------------------------------------------------------------------- launches
+__global__ void __launch_bounds__(256) near_clear_kernel(unsigned long long* a, long long n)
+{
+    const long long i = (long long)blockIdx.x * 256 + threadIdx.x;
+    if (i < n) a[i] = 0ull;
+}
+
+struct NearPlan {
+    int waves, panel_tiles;             // wavefronts per workgroup, query tiles per panel
+    int nseg, nsub, capl;               // emit
+    int max_seg, max_parts, max_sets, groups, stride, used;      // maxima (used = 0: none, every candidate is emitted)
+    int stages;                         // 2: the sample's exact lists set the bounds for the other candidates
+    int batch_tiles;                    // query tiles per batch
+    size_t per_tile;                    // bytes of batch scratch per query tile
+};
+
+static int near_cus()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess) return 256;
+    if (hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) return 256;
+    return v;
+}
+
+static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batch_bytes)
+{
+    NearPlan p{};
+    const int cus = near_cus();
+    const int QT = near_tiles(nq), CT = near_tiles(nc);
+    const bool wide = near_steps(d) > REG_STEPS;
+    const int units = wide ? (CT + 1) / 2 : CT;          // what the segments share out
+    // lanes of a wavefront row that hold a query's values, per segment
+    const int lanes = wide ? 4 : 2;
+    const int most_seg = kk == 1 ? 64 : (wide ? 4 : (kk > 40 ? 4 : 8));
+    auto segs = [&](int n, int most) {
+        const int panels = (QT + p.panel_tiles - 1) / p.panel_tiles;
+        int s = (p.waves == 8 ? cus : 2 * cus) / panels;
+        if (s > most) s = most;
+        if (s > n) s = n;
+        return s < 1 ? 1 : s;
+    };
+    // the largest workgroups (64 queries per wavefront share what is staged) that still fill the chip
+    for (p.waves = 8;; p.waves >>= 1) {
+        p.panel_tiles = p.waves / 2;
+        if (wide) { p.panel_tiles = 2; break; }
+        const int panels = (QT + p.panel_tiles - 1) / p.panel_tiles;
+        const int slots = p.waves == 8 ? cus : 2 * cus;
+        if (p.waves == 2 || panels * segs(CT, most_seg) * 4 >= slots * 3) break;
+    }
+    p.nseg = segs(units, most_seg);
+    if (wide && p.nseg < 4 && units >= 64) p.nseg = 4;   // (so that an XCD's workgroups share 8 panels, see the kernel)
+    p.nsub = lanes * p.nseg;
+    p.capl = kk == 1 ? 256 : (p.nsub <= 2 ? 512 : (p.nsub <= 4 ? 256 : (p.nsub <= 8 ? 128 : 64)));
+    p.used = 0; p.stride = 1; p.max_seg = 1; p.max_parts = 1; p.groups = GROUPS; p.stages = 1;
+    if (kk > 1 && CT > 2) {
+        // A sample of one tile in `stride`: the maxima pass costs M / stride (M: all tiles at 1.3e15 operations a
+        // second), the entries it leaves cost about 0.12 ns each, kk * stride per query: least at
+        // stride^2 = M / (0.12 ns * kk * queries).  At least 16 tiles; at most 5: beyond that, clusters of a hundred
+        // thousand near-equidistant rows overflow the buffers (1M x 128: at 8 a few queries went to the list kernels).
+        int stride = (int)(__builtin_sqrt((double)nc * 16.0 * near_steps(d) * 1.28e-5 / kk) + 0.5);
+        if (stride > CT / 16) stride = CT / 16;
+        if (stride > 5) stride = 5;
+        if (stride < 1) stride = 1;
+        p.stages = stride >= 3 ? 2 : 1;
+        p.stride = stride;
+        p.used = (CT + stride - 1) / stride;
+        p.max_seg = segs(wide ? (p.used + 1) / 2 : p.used, wide ? 8 : 16);
+        const int sets = p.max_seg * (wide ? 2 : 1);     // sets of group maxima per part
+        const int per_seg = ((wide ? (p.used + 1) / 2 : p.used) + p.max_seg - 1) / p.max_seg;
+        // about six groups per neighbour wanted, in 8 or 32 groups per set
+        p.groups = 6 * kk <= 8 * sets ? 8 : GROUPS;
+        int parts = (6 * kk + p.groups * sets - 1) / (p.groups * sets);
+        if (parts > per_seg) parts = per_seg;
+        if (parts * sets > 32) parts = 32 / sets;
+        p.max_parts = parts < 1 ? 1 : parts;
+        p.max_sets = sets * p.max_parts;
+    }
+    p.per_tile = kk == 1 ? (size_t)TILE * 8 * (size_t)p.capl
+                         : (size_t)TILE * (4 + (size_t)(p.used ? p.max_sets * p.groups * 4 : 0) + (size_t)p.nsub * (4 + 8 * (size_t)p.capl));
+    long long bt = batch_bytes > 8192 ? (long long)((batch_bytes - 8192) / p.per_tile) : 0;
+    if (bt >= QT) bt = QT;
+    else if (bt >= p.panel_tiles) bt = bt / p.panel_tiles * p.panel_tiles;
+    if (bt > 1024) bt = 1024;
+    p.batch_tiles = (int)bt;
+    return p;
+}
+
+size_t near_batch_bytes(long long nq, long long nc, int d, int kk)
+{
+    const NearPlan p = near_plan(nq, nc, d, kk, (size_t)1 << 62);
+    return p.per_tile * (size_t)p.batch_tiles + 8192;
+}
+
+size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk)
+{
+    const NearPlan p = near_plan(nq, nc, d, kk, (size_t)1 << 62);
+    const int most = near_tiles(nq);
+    return p.per_tile * (size_t)(p.panel_tiles < most ? p.panel_tiles : most) + 8192;
+}
+
+template <int MODE, bool COLOURED>
+static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s)
+{
+    const bool wide = p.steps > REG_STEPS;
+    const int per_panel = wide ? 2 : waves / 2;
+    const int panels = (p.q_tile1 - p.q_tile0 + per_panel - 1) / per_panel;
+    const dim3 grid((unsigned)(panels * p.nseg)), block((unsigned)(64 * waves));
+    const size_t lds = wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024);
+    auto run = [&](auto kernel) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, p);
+        return hipGetLastError();
+    };
+    if (wide) return run(&near_wide_kernel<MODE, COLOURED>);
+    switch (p.steps) {
+        case 1: return run(&near_sweep_kernel<1, MODE, COLOURED>);
+        case 2: return run(&near_sweep_kernel<2, MODE, COLOURED>);
+        case 3: return run(&near_sweep_kernel<3, MODE, COLOURED>);
+        case 4: return run(&near_sweep_kernel<4, MODE, COLOURED>);
+        case 5: return run(&near_sweep_kernel<5, MODE, COLOURED>);
+        case 6: return run(&near_sweep_kernel<6, MODE, COLOURED>);
+        case 7: return run(&near_sweep_kernel<7, MODE, COLOURED>);
+        case 8: return run(&near_sweep_kernel<8, MODE, COLOURED>);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
+{
+    const int kk = a.k + (a.exclude_self ? 1 : 0);
+    const NearPlan plan = near_plan(a.nq, a.nc, a.d, kk, b.batch_bytes);
+    if (plan.batch_tiles < 1 || (a.nq + 127) / 128 > b.todo_panels || (a.coloured && (kk != 1 || !q.colour || !c.colour)) ||
+        (kk == 1 && (!q.best || !q.count)))
+        return hipErrorInvalidValue;
+    NearSweep p{};
+    p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour;
+    p.cfrag = c.frag; p.cnegh = c.negh; p.ccolour = c.colour; p.c_tiles = c.tiles;
+    p.sc = b.scale; p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
+    p.kk = kk;
+    p.best = q.best;
+    const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
+    NearSelect sel{};
+    sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
+    sel.Xq = a.Xq; sel.Xc = a.Xc; sel.q_rows = a.q_rows;
+    sel.d = a.d; sel.k = a.k; sel.kk = kk; sel.nq = a.nq; sel.nq_rows = a.nq_rows; sel.nc = a.nc;
+    sel.q_tiles = q.tiles; sel.c_tiles = c.tiles; sel.exclude_self = a.exclude_self;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    for (int t0 = 0; t0 < q.tiles; t0 += plan.batch_tiles) {
+        const int t1 = t0 + plan.batch_tiles < q.tiles ? t0 + plan.batch_tiles : q.tiles;
+        const int nqb = (t1 - t0) * TILE;
+        const dim3 per_query((unsigned)((nqb + 3) / 4));
+        unsigned char* at = b.batch;
+        auto take = [&](size_t bytes) { unsigned char* r = at; at += (bytes + 255) / 256 * 256; return r; };
+        p.q_tile0 = t0; p.q_tile1 = t1; p.nq_batch = nqb;
+        p.capl = sel.capl = plan.capl;
+        sel.nq_batch = nqb; sel.q0 = t0 * TILE;
+        auto select = [&]() -> hipError_t {
+            sel.entries = p.entries; sel.counts = p.counts;
+            if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
+            else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+            return hipGetLastError();
+        };
+        hipError_t e = hipSuccess;
+        if (kk == 1) {
+            p.entries = reinterpret_cast<uint2*>(take((size_t)nqb * plan.capl * 8));
+            p.counts = q.count;
+            p.nseg = plan.nseg; p.stride = 1; p.skip = 0; p.used = c.tiles;
+            e = a.coloured ? near_launch_sweep<NEAR_BEST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_BEST, false>(p, plan.waves, s);
+            if (e != hipSuccess) return e;
+            e = a.coloured ? near_launch_sweep<NEAR_NEAREST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_NEAREST, false>(p, plan.waves, s);
+            if (e != hipSuccess) return e;
+            sel.nsub = 1; sel.by_position = 1;
+            e = select();
+            if (e != hipSuccess) return e;
+            continue;
+        }
+        float* bound = reinterpret_cast<float*>(take((size_t)nqb * 4));
+        float* maxima = reinterpret_cast<float*>(take(plan.used ? (size_t)nqb * plan.max_sets * plan.groups * 4 : 0));
+        p.counts = reinterpret_cast<int32_t*>(take((size_t)nqb * plan.nsub * 4));
+        p.entries = reinterpret_cast<uint2*>(take((size_t)nqb * plan.nsub * plan.capl * 8));
+        p.bound = bound; p.maxima = maxima;
+        p.stride = plan.stride; p.used = plan.used; p.skip = 0;
+        if (plan.used) {
+            p.nseg = plan.max_seg; p.parts = plan.max_parts; p.groups = plan.groups;
+            e = near_launch_sweep<NEAR_MAXIMA, false>(p, plan.waves, s);
+            if (e != hipSuccess) return e;
+        }
+        hipLaunchKernelGGL(near_bounds_kernel, per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
+                           plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound);
+        p.nseg = plan.nseg; p.nsub = plan.nsub;
+        sel.nsub = plan.nsub; sel.by_position = 0; sel.merge = 0; sel.next_bound = nullptr;
+        if (plan.stages == 2) {
+            e = near_launch_sweep<NEAR_EMIT, false>(p, plan.waves, s);
+            if (e != hipSuccess) return e;
+            sel.next_bound = bound;
+            e = select();
+            if (e != hipSuccess) return e;
+            p.skip = 1; p.used = c.tiles - plan.used;
+            sel.merge = 1; sel.next_bound = nullptr;
+        } else {
+            p.stride = 1; p.used = c.tiles;
+        }
+        e = near_launch_sweep<NEAR_EMIT, false>(p, plan.waves, s);
+        if (e != hipSuccess) return e;
+        e = select();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+// ---------------------------------------------------------------------------------------------- colours, assignment
+__global__ void __launch_bounds__(256) near_colours_kernel(const int32_t* __restrict__ colour, int n, int tiles, int32_t* __restrict__ out)
+{
+    const int p = blockIdx.x * 256 + threadIdx.x;
+    if (p >= tiles * TILE) return;
+    const long long row = (long long)(p & (TILE - 1)) * tiles + (p >> 7);
+    out[p] = row < n ? colour[row] : -1;
+}
+
+hipError_t near_colours(const NearCopy& c, const int32_t* colour, hipStream_t s)
+{
+    hipLaunchKernelGGL(near_colours_kernel, dim3((unsigned)((c.tiles + 1) / 2)), dim3(256), 0, s, colour, c.rows, c.tiles, c.colour);
+    return hipGetLastError();
+}
+
+// (product value, position) per query position -> candidate row and exact squared distance by query; eight lanes per query
+template <bool VEC4>
+__global__ void __launch_bounds__(256) near_unpack_kernel(const unsigned long long* __restrict__ best_at, const float* __restrict__ qnegh,
+                                                          const float* __restrict__ Xq, const int32_t* __restrict__ q_rows, int nq,
+                                                          int q_tiles, const float* __restrict__ Xc, int nc, int c_tiles, int d,
+                                                          int32_t* __restrict__ out_idx, float* __restrict__ out_dist)
+{
+    const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
+    const int p = (int)(t >> 3), g = (int)(t & 7);
+    if (p >= q_tiles * TILE) return;
+    const long long qi = (long long)(p & (TILE - 1)) * q_tiles + (p >> 7);
+    if (qi >= nq) return;
+    const unsigned long long key = best_at[p];
+    const int pos = (int)(unsigned int)key;
+    const long long cand = (long long)(pos & (TILE - 1)) * c_tiles + (pos >> 7);
+    const bool fine = key != 0ull && cand < nc && fabsf(qnegh[p]) < 1e37f;
+    float s = 0.f;
+    if (fine) {
+        const float* a = Xq + (size_t)(q_rows ? q_rows[qi] : qi) * d;
+        const float* b = Xc + (size_t)cand * d;
+        for (int c = 4 * g; c < d; c += 32) s = near_quad_sqdist(near_quad<VEC4>(a, c, d), near_quad<VEC4>(b, c, d), s);
+    }
+    s += __shfl_xor(s, 1); s += __shfl_xor(s, 2); s += __shfl_xor(s, 4);
+    if (g == 0) {
+        out_idx[qi] = fine ? (int32_t)cand : 0;
+        out_dist[qi] = fine ? s : INF;
+    }
+}
+
+hipError_t near_assign(const NearCopy& q, const NearCopy& c, const float* Xq, const int32_t* q_rows, const float* Xc, int d,
+                       const NearBuffers& b, unsigned long long* best_at, int32_t* out_idx, float* out_dist, hipStream_t s)
+{
+    if (!c.finite_padding) return hipErrorInvalidValue;
+
+    NearPlan plan = near_plan(q.rows, c.rows, d, 1, (size_t)1 << 62);
+    NearSweep p{};
+    p.qfrag = q.frag; p.qnegh = q.negh; p.q_tile0 = 0; p.q_tile1 = q.tiles;
+    p.cfrag = c.frag; p.cnegh = c.negh; p.c_tiles = c.tiles;
+    p.sc = b.scale; p.d = d; p.steps = near_steps(d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
+    p.nseg = plan.nseg; p.stride = 1; p.used = c.tiles; p.kk = 1;
+    p.best_at = best_at;
+    const long long words = (long long)q.tiles * TILE;
+    hipLaunchKernelGGL(near_clear_kernel, dim3((unsigned)((words + 255) / 256)), dim3(256), 0, s, best_at, words);
+    hipError_t e = near_launch_sweep<NEAR_ARG, false>(p, plan.waves, s);
+    if (e != hipSuccess) return e;
+    const bool vec4 = d % 4 == 0 && ((reinterpret_cast<uintptr_t>(Xq) | reinterpret_cast<uintptr_t>(Xc)) & 15) == 0;
+    const dim3 grid((unsigned)(q.tiles * (TILE * 8 / 256)));
+    if (vec4) hipLaunchKernelGGL((near_unpack_kernel<true>), grid, dim3(256), 0, s, best_at, q.negh, Xq, q_rows, q.rows, q.tiles, Xc, c.rows, c.tiles, d, out_idx, out_dist);
+    else hipLaunchKernelGGL((near_unpack_kernel<false>), grid, dim3(256), 0, s, best_at, q.negh, Xq, q_rows, q.rows, q.tiles, Xc, c.rows, c.tiles, d, out_idx, out_dist);
+    return hipGetLastError();
+}
+
+}  // namespace slhc

@@ -20,6 +20,7 @@
 #include "../../include/slhc.h"
 #include "cluster_kernels.h"
 #include "forest_kernels.h"
+#include "near_kernels.h"
 #include "order_kernels.h"
 #include "sweep_kernels.h"
 
@@ -98,6 +99,21 @@ __global__ void k_zero_words(uint32_t* p, int n)
 {
     const int i = blockIdx.x * blockDim.x + threadIdx.x;
     if (i < n) p[i] = 0u;
+}
+
+// *sum += a[0] + ... + a[n-1]
+__global__ void __launch_bounds__(256) k_sum_words(const int32_t* __restrict__ a, int n, unsigned long long* __restrict__ sum)
+{
+    __shared__ unsigned long long part[256];
+    unsigned long long s = 0;
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < n; i += (long long)gridDim.x * 256) s += (unsigned long long)a[i];
+    part[threadIdx.x] = s;
+    __syncthreads();
+    for (int w = 128; w > 0; w >>= 1) {
+        if ((int)threadIdx.x < w) part[threadIdx.x] += part[threadIdx.x + w];
+        __syncthreads();
+    }
+    if (threadIdx.x == 0 && part[0]) atomicAdd(sum, part[0]);
 }
 
 // Columns the sweeps work on.  A zero column adds fma(0, 0, s) = s to a distance and to a norm, so appending
@@ -369,6 +385,41 @@ bool split_products_ok(int32_t d) { return (d % 32 == 0 && d >= 32 && d <= 128) 
 // wider filter to pay (2M x 32: pruned connection sweeps 30 ms with float32 products, 60 ms with split ones)
 bool split_products_pruned_ok(int32_t d) { return d % 32 == 0 && d >= 64 && d <= 128; }
 
+// Scratch of the half-precision engine (near_kernels.hip): the float16 copy of the candidates, that of separate
+// queries (nq > 0), and the buffers of its passes.
+struct NearWs {
+    slhc::NearCopy c{}, q{};
+    slhc::NearBuffers b{};
+    bool ok = false;
+    // `most`: where the workspace ends (0: no limit); the batch takes what is left of it
+    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = 0)
+    {
+        ok = slhc::near_supported(d);
+        if (!ok) return;
+        auto copy = [&](slhc::NearCopy& x, int64_t n) {
+            x.rows = (int)n; x.tiles = slhc::near_tiles(n);
+            x.frag = w.take<unsigned char>(slhc::near_frag_bytes(n, d));
+            x.negh = w.take<float>((size_t)x.tiles * 128);
+            x.colour = coloured ? w.take<int32_t>((size_t)x.tiles * 128) : nullptr;
+            x.best = w.take<uint32_t>((size_t)x.tiles * 128);
+            x.count = w.take<int32_t>((size_t)x.tiles * 128);
+        };
+        b.scale = w.take<slhc::NearScale>(1);
+        b.shift = w.take<float>((size_t)d + 8);
+        b.partial = w.take<float>(slhc::near_stats_scratch_floats(d));
+        copy(c, nc);
+        if (nq > 0) copy(q, nq); else q = c;
+        const int64_t queries = nq > 0 ? nq : nc;
+        b.todo_panels = (queries + 127) / 128;
+        b.todo = w.take<int32_t>((size_t)(2 + 2 * b.todo_panels));
+        b.todo_mark = b.todo + 2 + b.todo_panels;
+        b.batch_bytes = slhc::near_batch_bytes(queries, nc, d, kk);
+        if (most && w.off + b.batch_bytes > most) b.batch_bytes = most > w.off ? most - w.off : 0;
+        if (b.batch_bytes < slhc::near_least_batch_bytes(queries, nc, d, kk)) { ok = false; return; }
+        b.batch = w.take<unsigned char>(b.batch_bytes);
+    }
+};
+
 // Buffers of the spatially coherent row order (see build_order).
 struct OrderWs {
     float *Xp, *hp, *pdist, *sample, *Xs, *hs, *tile_c, *tile_r, *gap_ws, *tile_gap, *n_w, *n_heights;
@@ -380,6 +431,8 @@ struct OrderWs {
     int32_t *pid, *perm, *inv, *colour_s, *qslot, *tile_colour, *tile_list, *counts, *rank, *shift, *far_count;
     int32_t *n_src, *n_dst, *n_children, *n_sizes;
     uint32_t *tmp_a, *tmp_b, *tmp_c;
+    slhc::NearCopy near_p{};          // float16 copy of the pivots, and scratch of the assignment
+    unsigned long long* best_at;
     void* sort_temp; size_t sort_temp_bytes;
     void* nested_ws; size_t nested_bytes;
     int P1, Pmax, Tmax;
@@ -417,6 +470,10 @@ struct OrderWs {
         pid = c.take<int32_t>(n); perm = c.take<int32_t>(nm); inv = c.take<int32_t>(n); colour_s = c.take<int32_t>(nm);
         qslot = c.take<int32_t>(nm); tile_colour = c.take<int32_t>((size_t)Tmax); tile_list = c.take<int32_t>((size_t)Tmax);
         counts = c.take<int32_t>(pm); rank = c.take<int32_t>(pm); shift = c.take<int32_t>(pm); far_count = c.take<int32_t>(64);
+        near_p.tiles = slhc::near_tiles(Pmax);
+        near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
+        near_p.negh = c.take<float>((size_t)near_p.tiles * 128);
+        best_at = c.take<unsigned long long>((size_t)slhc::near_tiles(N) * 128);
         tmp_a = c.take<uint32_t>(n); tmp_b = c.take<uint32_t>(n); tmp_c = c.take<uint32_t>(n);
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
@@ -446,6 +503,9 @@ struct KnnWs {
     float* shift; float* shift_scratch;
     // scratch of the every-tile sweeps that go range by range (see SweepParams::carry_ws): 2 + panels words
     unsigned int* carry_ws; long long carry_ws_words;
+    NearWs near;                     // every-tile sweeps in half precision
+    bool near_done = false;          // ... made the lists of this call
+    bool near_ready = false;         // the float16 copy of X is made
     bool split_ready = false;        // filled in this call
     bool order_split_ready = false;  // likewise the split copy of the reordered rows
     bool offset_heavy = false;       // the rows' norms are mostly a common offset (see run_knn): split products everywhere
@@ -479,6 +539,8 @@ struct KnnWs {
         carry_ws = c.take<unsigned int>((size_t)carry_ws_words);
         has_order = with_order && prunable(N, d);
         if (has_order) order.carve(c, N, d);
+        // (the queries' copy and the colours serve the every-tile connection sweeps)
+        if (k > 0) near.carve(c, N, N, d, k + 1, true);
         bytes = c.off;
     }
 };
@@ -536,9 +598,24 @@ int make_split_copy(const float* X, int64_t N, int32_t d, KnnWs& ws, hipStream_t
 // `x_split` / `hn_split` / `shift` (optional): X in split bfloat16 halves, the half norms that go with it and the
 // shift both were taken relative to; the pivots
 // then get a split copy of their own (in the buffers of the reordered copy's, which are free until step 4).
-int assign_to_pivots(const float* X, int64_t N, int32_t d, const float* hn, OrderWs& o, int P, hipStream_t s,
-                     const float* x_split = nullptr, const float* hn_split = nullptr, const float* shift = nullptr)
+// `near` (optional): the half-precision engine with the copy of X made; the nearest pivot is then one up to the rounding
+// of the copies, which is all the order needs, in one pass.
+slhc::NearCopy pivot_copy(const OrderWs& o, int P)
 {
+    slhc::NearCopy c = o.near_p;
+    c.rows = P; c.tiles = slhc::near_tiles(P);
+    c.finite_padding = true;
+    return c;
+}
+int assign_to_pivots(const float* X, int64_t N, int32_t d, const float* hn, OrderWs& o, int P, hipStream_t s,
+                     const NearWs* near, const float* x_split = nullptr, const float* hn_split = nullptr, const float* shift = nullptr)
+{
+    if (near) {
+        const slhc::NearCopy c = pivot_copy(o, P);
+        HIP_TRY(slhc::near_make(o.Xp, P, d, nullptr, P, nullptr, near->b, c, nullptr, nullptr, s));
+        HIP_TRY(slhc::near_assign(near->c, c, X, nullptr, o.Xp, d, near->b, o.best_at, o.pid, o.pdist, s));
+        return SLHC_OK;
+    }
     slhc::SweepParams p{};
     p.Xq = X; p.hq = hn; p.NQ = (int)N;
     p.Xc = o.Xp; p.hc = o.hp; p.NC = P;
@@ -568,7 +645,7 @@ int assign_to_pivots(const float* X, int64_t N, int32_t d, const float* hn, Orde
 // `nonfinite`: device word the norm kernel set when a row is not finite; checked first, because
 // nothing below is defined for such rows.
 int build_order(const float* X, int64_t N, int32_t d, const float* hn, const unsigned int* nonfinite, OrderWs& o,
-                hipStream_t s, const float* x_split = nullptr, const float* hn_split = nullptr, const float* shift = nullptr)
+                hipStream_t s, const NearWs* near, const float* x_split = nullptr, const float* hn_split = nullptr, const float* shift = nullptr)
 {
     const int n = (int)N;
     const int P1 = o.P1;
@@ -590,7 +667,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
 
     // ---- 1. pivots and assignment
     HIP_TRY(slhc::order_pick_rows(X, hn, n, d, P1, o.Xp, o.hp, s));
-    int rc = assign_to_pivots(X, N, d, hn, o, P1, s, x_split, hn_split, shift);
+    int rc = assign_to_pivots(X, N, d, hn, o, P1, s, near, x_split, hn_split, shift);
     if (rc != SLHC_OK) return rc;
     const int S = n < OrderWs::SAMPLE ? n : OrderWs::SAMPLE;
     HIP_TRY(slhc::order_pick_f32(o.pdist, n, S, o.sample, s));
@@ -630,6 +707,19 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
         int P2 = (far + 15) / 16;
         if (P2 > o.Pmax - P) P2 = o.Pmax - P;
         HIP_TRY(slhc::order_pick_listed_rows(X, hn, far_rows, far, n, d, P2, o.Xp + (size_t)P * d, o.hp + P, s));
+        if (near) {
+            slhc::NearCopy q = near->q;
+            q.rows = far; q.tiles = slhc::near_tiles(far); q.colour = nullptr;
+            const slhc::NearCopy c = pivot_copy(o, P2);
+            HIP_TRY(slhc::near_make(X, n, d, reinterpret_cast<const int32_t*>(far_rows), far, nullptr, near->b, q, nullptr, nullptr, s));
+            HIP_TRY(slhc::near_make(o.Xp + (size_t)P * d, P2, d, nullptr, P2, nullptr, near->b, c, nullptr, nullptr, s));
+            HIP_TRY(slhc::near_assign(q, c, X, reinterpret_cast<const int32_t*>(far_rows), o.Xp + (size_t)P * d, d, near->b, o.best_at, reinterpret_cast<int32_t*>(o.tmp_b), reinterpret_cast<float*>(o.tmp_c), s));
+            HIP_TRY(slhc::order_adopt_pivots(far_rows, far, n, reinterpret_cast<const int32_t*>(o.tmp_b),
+                                             reinterpret_cast<const float*>(o.tmp_c), P, P2, o.pid, o.pdist, s));
+            P += P2;
+            log.mark("row order: %d far rows -> %d more pivots", far, P2);
+            continue;
+        }
         // the far rows as a compact query matrix (the buffer of the reordered copy is still free)
         HIP_TRY(slhc::order_pick_listed_rows(X, hn, far_rows, far, n, d, far, o.Xs, o.hs, s));
         slhc::SweepParams p{};
@@ -735,14 +825,61 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     return SLHC_OK;
 }
 
+// The every-tile k-NN graph by the half-precision engine: any d, no padded copy, same lists as the list kernels.
+bool near_wanted(const NearWs& near, uint32_t flags) { return near.ok && !(flags & (SLHC_FP32_FILTER | SLHC_PANEL_ORDER)); }
+int run_knn_near(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist, unsigned long long* counters,
+                 float* hn, const NearWs& near, hipStream_t stream, int32_t* evaluated = nullptr, EventPair* ev_norm = nullptr,
+                 EventPair* ev_sweep = nullptr)
+{
+    if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->a, stream));
+    HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, reinterpret_cast<uint32_t*>(counters), 64, stream));
+    HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, near.b, near.c, hn, reinterpret_cast<unsigned int*>(counters + 4), stream));
+    if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->b, stream));
+    if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->a, stream));
+    slhc::NearProblem a{};
+    a.Xq = a.Xc = X; a.d = d; a.k = k;
+    a.nq = a.nq_rows = a.nc = (int)N;
+    a.exclude_self = 1;
+    a.out_idx = nbr_idx; a.out_dist = nbr_dist;
+    a.evaluated = evaluated;
+    HIP_TRY(slhc::near_search(a, near.c, near.c, near.b, stream));
+    slhc::SweepParams p{};                      // the panels it could not finish
+    p.Xq = p.Xc = X; p.hq = p.hc = hn; p.NQ = p.NC = (int)N;
+    p.d = d; p.k = k;
+    p.out_idx = nbr_idx; p.out_dist = nbr_dist;
+    p.exclude_self = 1;
+    p.survivors = counters;
+    p.todo = near.b.todo;
+    HIP_TRY(slhc::launch_knn_sweep(p, stream));
+    if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->b, stream));
+    if (evaluated) {
+        hipLaunchKernelGGL(k_sum_words, dim3(64), dim3(256), 0, stream, evaluated, (int)N, counters);
+        HIP_TRY(hipGetLastError());
+    }
+    return SLHC_OK;
+}
+
 int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist,
             KnnWs& ws, hipStream_t stream, uint32_t flags, bool* pruned_out = nullptr,
             EventPair* ev_norm = nullptr, EventPair* ev_order = nullptr, EventPair* ev_sweep = nullptr)
 {
+    if (!((flags & SLHC_PRUNE) && ws.has_order) && near_wanted(ws.near, flags)) {
+        if (pruned_out) *pruned_out = false;
+        if (ev_order) { HIP_TRY(hipEventRecord(ev_order->a, stream)); HIP_TRY(hipEventRecord(ev_order->b, stream)); }
+        ws.near_done = true;
+        ws.near_ready = true;
+        return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream,
+                            ev_sweep ? reinterpret_cast<int32_t*>(ws.hn_split) : nullptr, ev_norm, ev_sweep);
+    }
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(ws.counters), 64);
     HIP_TRY(hipGetLastError());
     if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->a, stream));
-    HIP_TRY(slhc::launch_half_norms(X, (int)N, d, ws.hn, stream, reinterpret_cast<unsigned int*>(ws.counters + 4)));
+    if (near_wanted(ws.near, flags)) {
+        HIP_TRY(slhc::near_stats(X, (int)N, d, ws.near.b, nullptr, 0, stream));
+        HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, ws.near.b, ws.near.c, ws.hn, reinterpret_cast<unsigned int*>(ws.counters + 4), stream));
+        ws.near_ready = true;
+    } else
+        HIP_TRY(slhc::launch_half_norms(X, (int)N, d, ws.hn, stream, reinterpret_cast<unsigned int*>(ws.counters + 4)));
     if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->b, stream));
     const bool prune = (flags & SLHC_PRUNE) && ws.has_order;
     if (pruned_out) *pruned_out = prune;
@@ -768,6 +905,7 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
             }
         }
         const int rc = build_order(X, N, d, ws.hn, reinterpret_cast<const unsigned int*>(ws.counters + 4), ws.order, stream,
+                                   ws.near_ready ? &ws.near : nullptr,
                                    split ? ws.Xsplit : nullptr, split ? ws.hn_split : nullptr, split ? ws.shift : nullptr);
         if (rc != SLHC_OK) return rc;
     }
@@ -969,11 +1107,12 @@ int host_threads()
     return t < 1 ? 1 : (t > 16 ? 16 : t);
 }
 
-// ---- scratch of slhc_knn_graph_static: the workspace of the unpruned k-NN path (counters + one
-// half norm per row) for up to SLHC_STATIC_MAX_ROWS rows, as a fixed device array.  Every GPU the
+// ---- scratch of slhc_knn_graph_static: the workspace of the every-tile k-NN path as a fixed device array.  At
+// 128 MiB it holds the float16 copy and the buffers of the half-precision engine up to about 300 000 x 128; larger
+// inputs (to SLHC_STATIC_MAX_ROWS rows) go through the list kernels, which need one half norm per row only.  Every GPU the
 // library runs on holds its own copy at its own address until the process ends; host code never
 // uses the array's name as an address, only what hipGetSymbolAddress returns for the current device.
-constexpr size_t STATIC_SCRATCH_BYTES = 256 + (size_t)SLHC_STATIC_MAX_ROWS * sizeof(float);
+constexpr size_t STATIC_SCRATCH_BYTES = (size_t)128 << 20;
 static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
 
 constexpr int MAX_DEVICES = 64;
@@ -1042,6 +1181,9 @@ int slhc_knn_graph_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t*
         const size_t head = padded_copy_bytes(N, d);
         KnnWs ws(static_cast<unsigned char*>(workspace) + head, N, dw, true, k);
         if (workspace_bytes < head + ws.bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, head + ws.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
+        const bool prune = (flags & SLHC_PRUNE) && ws.has_order;
+        if (!prune && near_wanted(ws.near, flags))          // (reads the rows as they are)
+            return run_knn(X, N, d, k, nbr_idx, nbr_dist, ws, static_cast<hipStream_t>(stream), flags);
         if (dw != d) {
             const int rp = pad_columns(X, N, d, dw, static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
             if (rp != SLHC_OK) return rp;
@@ -1074,6 +1216,16 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k, int32
         void* ptr = nullptr;
         const int rs = static_scratch(&ptr);
         if (rs != SLHC_OK) return rs;
+        {
+            // counters, half norms, the float16 copy and its buffers, as far as they fit
+            Carver c(ptr);
+            unsigned long long* counters = c.take<unsigned long long>(32);
+            float* hn = c.take<float>((size_t)N);
+            NearWs near;
+            near.carve(c, N, 0, d, k + 1, false, STATIC_SCRATCH_BYTES);
+            if (near.ok && c.off <= STATIC_SCRATCH_BYTES)
+                return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream));
+        }
         KnnWs ws(ptr, N, d, false);                 // counters (cleared by run_knn) + half norms (all N written)
         if (ws.bytes > STATIC_SCRATCH_BYTES) { set_err("scratch layout %zu > %zu bytes", ws.bytes, STATIC_SCRATCH_BYTES); return SLHC_INTERNAL; }
         return run_knn(X, N, d, k, nbr_idx, nbr_dist, ws, static_cast<hipStream_t>(stream), 0u);
@@ -1159,6 +1311,17 @@ int slhc_probe_panel_loop(int32_t steps, double* tflops, void* workspace, size_t
     });
 }
 
+static void cross_1nn_carve(Carver& c, int64_t N, int32_t d, int64_t m, unsigned long long** counters, float** hn, NearWs* near)
+{
+    unsigned long long* w = c.take<unsigned long long>(32);
+    float* h = c.take<float>((size_t)N);
+    NearWs local;
+    NearWs& n = near ? *near : local;
+    if (m > 0) n.carve(c, N, m, d, 1, true);
+    if (counters) *counters = w;
+    if (hn) *hn = h;
+}
+
 int slhc_cross_1nn_workspace_bytes(int64_t N, int32_t d, int64_t m, size_t* bytes)
 {
     return guarded([&]() -> int {
@@ -1166,7 +1329,9 @@ int slhc_cross_1nn_workspace_bytes(int64_t N, int32_t d, int64_t m, size_t* byte
         const int rc = check_shape(N, d, 1, false);
         if (rc != SLHC_OK) return rc;
         if (m < 0 || m > 2147483647LL) { set_err("bad m"); return SLHC_INVALID_ARG; }
-        *bytes = up(32 * sizeof(unsigned long long)) + up((size_t)N * sizeof(float));
+        Carver c(nullptr);
+        cross_1nn_carve(c, N, d, m, nullptr, nullptr, nullptr);
+        *bytes = c.off;
         return SLHC_OK;
     });
 }
@@ -1181,15 +1346,31 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
         if (rc != SLHC_OK) return rc;
         if (m < 0 || m > 2147483647LL || (!rows && m > N)) { set_err("bad m=%lld", (long long)m); return SLHC_INVALID_ARG; }
         Carver c(workspace);
-        unsigned long long* counters = c.take<unsigned long long>(32);
-        float* hn = c.take<float>((size_t)N);
+        unsigned long long* counters = nullptr;
+        float* hn = nullptr;
+        NearWs near;
+        cross_1nn_carve(c, N, d, m, &counters, &hn, &near);
         if (workspace_bytes < c.off) { set_err("workspace %zu < %zu bytes", workspace_bytes, c.off); return SLHC_WORKSPACE_TOO_SMALL; }
         if (m == 0) return SLHC_OK;
         hipStream_t s = static_cast<hipStream_t>(stream);
-        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(counters), 64);
-        HIP_TRY(hipGetLastError());
-        HIP_TRY(slhc::launch_half_norms(X, (int)N, d, hn, s));
         slhc::SweepParams p{};
+        if (near.ok) {
+            HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, reinterpret_cast<uint32_t*>(counters), 64, s));
+            HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, colour, near.b, near.c, hn, nullptr, s));
+            const bool all = !rows && m == N;            // queries are the candidates
+            if (!all) HIP_TRY(slhc::near_make(X, (int)N, d, rows, (int)m, colour, near.b, near.q, nullptr, nullptr, s));
+            slhc::NearProblem a{};
+            a.Xq = a.Xc = X; a.d = d; a.k = 1;
+            a.q_rows = rows; a.nq = (int)m; a.nq_rows = a.nc = (int)N;
+            a.coloured = 1;
+            a.out_idx = out_idx; a.out_dist = out_dist;
+            HIP_TRY(slhc::near_search(a, all ? near.c : near.q, near.c, near.b, s));
+            p.todo = near.b.todo;
+        } else {
+            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(counters), 64);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(slhc::launch_half_norms(X, (int)N, d, hn, s));
+        }
         p.Xq = p.Xc = X; p.hq = p.hc = hn; p.NQ = p.NC = (int)N; p.d = d; p.k = 1;
         p.out_idx = out_idx; p.out_dist = out_dist;
         p.qcolour = p.ccolour = colour; p.rows = rows; p.m = (int)m;
@@ -1318,12 +1499,13 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
     });
 }
 
-static size_t fused_1nn_layout(void* ws, int64_t m, int64_t n, float** hq, float** hy, unsigned long long** keys)
+static size_t fused_1nn_layout(void* ws, int64_t m, int64_t n, int32_t d, float** hq, float** hy, unsigned long long** keys, NearWs* near)
 {
     Carver c(ws);
     *hq = c.take<float>((size_t)m);
     *hy = c.take<float>((size_t)n);
     *keys = c.take<unsigned long long>((size_t)m);
+    near->carve(c, n, m, d, 1, false);
     return c.off;
 }
 
@@ -1334,7 +1516,8 @@ int slhc_fused_1nn_workspace_bytes(int64_t m, int64_t n, int32_t d, size_t* byte
         if (m < 1 || n < 1 || d < 1) { set_err("need m >= 1, n >= 1, d >= 1"); return SLHC_INVALID_ARG; }
         if (m * (int64_t)d > 2147483647LL || n * (int64_t)d > 2147483647LL) { set_err("m*d or n*d exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
         float *hq, *hy; unsigned long long* keys;
-        *bytes = fused_1nn_layout(nullptr, m, n, &hq, &hy, &keys);
+        NearWs near;
+        *bytes = fused_1nn_layout(nullptr, m, n, d, &hq, &hy, &keys, &near);
         return SLHC_OK;
     });
 }
@@ -1347,17 +1530,31 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
         if (m < 1 || n < 1 || d < 1) { set_err("need m >= 1, n >= 1, d >= 1"); return SLHC_INVALID_ARG; }
         if (m * (int64_t)d > 2147483647LL || n * (int64_t)d > 2147483647LL) { set_err("m*d or n*d exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
         float *hq, *hy; unsigned long long* keys;
-        const size_t need = fused_1nn_layout(workspace, m, n, &hq, &hy, &keys);
+        NearWs near;
+        const size_t need = fused_1nn_layout(workspace, m, n, d, &hq, &hy, &keys, &near);
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         hipStream_t s = static_cast<hipStream_t>(stream);
-        HIP_TRY(slhc::launch_half_norms(Q, (int)m, d, hq, s));
-        HIP_TRY(slhc::launch_half_norms(Y, (int)n, d, hy, s));
         slhc::SweepParams p{};
+        if (near.ok) {
+            HIP_TRY(slhc::near_stats(Y, (int)n, d, near.b, nullptr, 0, s));
+            HIP_TRY(slhc::near_make(Y, (int)n, d, nullptr, (int)n, nullptr, near.b, near.c, hy, nullptr, s));
+            HIP_TRY(slhc::near_make(Q, (int)m, d, nullptr, (int)m, nullptr, near.b, near.q, hq, nullptr, s));
+            slhc::NearProblem a{};
+            a.Xq = Q; a.Xc = Y; a.d = d; a.k = 1;
+            a.nq = a.nq_rows = (int)m; a.nc = (int)n;
+            a.out_idx = out_idx; a.out_dist = out_dist;
+            HIP_TRY(slhc::near_search(a, near.q, near.c, near.b, s));
+            p.todo = near.b.todo;
+        } else {
+            HIP_TRY(slhc::launch_half_norms(Q, (int)m, d, hq, s));
+            HIP_TRY(slhc::launch_half_norms(Y, (int)n, d, hy, s));
+        }
         p.Xq = Q; p.hq = hq; p.NQ = (int)m;
         p.Xc = Y; p.hc = hy; p.NC = (int)n;
         p.d = d; p.k = 1;
         p.out_idx = out_idx; p.out_dist = out_dist;
-        HIP_TRY(slhc::launch_segmented_1nn(p, keys, s));
+        if (p.todo) HIP_TRY(slhc::launch_knn_sweep(p, s));
+        else HIP_TRY(slhc::launch_segmented_1nn(p, keys, s));
         return SLHC_OK;
     });
 }
@@ -1491,7 +1688,8 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     if ((h_surv[4] & 2ull) != 0) { set_err("a work item of the k-NN sweep waited for its predecessor in vain"); return SLHC_INTERNAL; }
     if ((h_surv[4] & 0xffffffffull) != 0) { set_err("a row of X is not finite (NaN, infinity, or a squared norm beyond float32)"); return SLHC_NONFINITE; }
     st.knn_filter_survivors = (int64_t)h_surv[0];
-    st.knn_tile_steps = (int64_t)h_surv[2];
+    const unsigned long long tiles_all = (unsigned long long)((N + 127) / 128) * (unsigned long long)((N + 127) / 128);
+    st.knn_tile_steps = (int64_t)(kws.near_done ? tiles_all : h_surv[2]);
 #ifdef SLHC_STUDY_PANEL_STEPS
     if (pruned) {
         const int T_ = (kws.order.Ns + 127) / 128;
@@ -1507,7 +1705,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     st.ms_order = ev_order.ms();
     st.ms_knn_kernel = ev_knn.ms();
     log.mark("k-NN graph of %lld rows: order %.2f ms, sweep %.2f ms, %llu tile steps", (long long)N, st.ms_order,
-             st.ms_knn_kernel, h_surv[2]);
+             st.ms_knn_kernel, (unsigned long long)st.knn_tile_steps);
     const double t_knn = now_ms();
     st.ms_knn = (float)(t_knn - t_begin);
 
@@ -1529,6 +1727,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     for (int64_t t = 1; t < N; t *= 2) ++max_rounds;
     double ms_connect = 0.0;
     bool first_connect = true;
+    unsigned long long near_tile_steps = 0;        // of connection sweeps in half precision
     // cleared when pruning stops paying: at once when the k-NN sweep already had to multiply more
     // than a quarter of all tile pairs (the data has no structure at the scale of a tile), else by
     // the per-round test below
@@ -1676,7 +1875,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                         p.carry_ws = kws.carry_ws; p.carry_ws_words = kws.carry_ws_words;
                         p.carry_fault = reinterpret_cast<unsigned int*>(kws.counters + 4);
                     }
-                    if (kws.Xsplit && !(flags & SLHC_FP32_FILTER)) {
+                    if (kws.Xsplit && !(flags & SLHC_FP32_FILTER) && !near_wanted(kws.near, flags)) {
                         if (!kws.split_ready) {          // (a pruned k-NN sweep did not need it)
                             const int rs = make_split_copy(X, N, d, kws, s);
                             if (rs != SLHC_OK) return rs;
@@ -1691,6 +1890,31 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if (round_pruned) { HIP_TRY(hipMemsetAsync(study_steps, 0, (size_t)study_panels * 8, s)); p.panel_steps = study_steps; }
 #endif
                 HIP_TRY(hipEventRecord(ev_conn.a, s));
+                if (!round_pruned && near_wanted(kws.near, flags)) {
+                    const NearWs& near = kws.near;
+                    if (!kws.near_ready) {
+                        HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, nullptr, 0, s));
+                        HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, near.b, near.c, nullptr, nullptr, s));
+                        kws.near_ready = true;
+                    }
+                    slhc::NearCopy q = near.q;
+                    q.rows = n; q.tiles = slhc::near_tiles(n);
+                    HIP_TRY(slhc::near_colours(near.c, ws.colour, s));
+                    HIP_TRY(slhc::near_make(X, (int)N, d, rows, n, ws.colour, near.b, q, nullptr, nullptr, s, true));
+                    slhc::NearProblem a{};
+                    a.Xq = a.Xc = X; a.d = d; a.k = 1;
+                    a.q_rows = rows; a.nq = n; a.nq_rows = a.nc = (int)N;
+                    a.coloured = 1;
+                    a.out_idx = ws.q_idx; a.out_dist = ws.q_dist;
+                    a.evaluated = reinterpret_cast<int32_t*>(ws.vals_b);          // free until the edge sort
+                    HIP_TRY(slhc::near_search(a, q, near.c, near.b, s));
+                    hipLaunchKernelGGL(k_sum_words, dim3(16), dim3(256), 0, s, reinterpret_cast<const int32_t*>(ws.vals_b), n, kws.counters + 1);
+                    HIP_TRY(hipGetLastError());
+                    near_tile_steps += (unsigned long long)((n + 127) / 128) * tiles_1d;
+                    p.todo = near.b.todo;
+                    p.carry_ws = nullptr;
+                    HIP_TRY(slhc::launch_cross_1nn_sweep(p, s));
+                } else
                 // keys_a / keys_b are free until the edge sort (the two-phase split above keeps its row lists in keys_a,
                 // in pruned rounds only)
                 HIP_TRY(slhc::launch_segmented_cross_1nn(p, round_pruned ? ws.keys_b : ws.keys_a, s));
@@ -1820,9 +2044,9 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     }
 #endif
     st.connect_filter_survivors = (int64_t)h_surv[1];
-    st.connect_tile_steps = (int64_t)h_surv[3];
+    st.connect_tile_steps = (int64_t)(h_surv[3] + near_tile_steps);
     st.pruned = pruned ? 1 : 0;
-    st.split_products = (kws.split_ready || kws.order_split_ready) ? 1 : 0;
+    st.split_products = (kws.split_ready || kws.order_split_ready || kws.near_done) ? 1 : 0;
     if (pruned) { st.order_pivots = kws.order.P; st.order_padded_rows = kws.order.Ns; }
     const double t_forest = now_ms();
     st.ms_connect = (float)ms_connect;

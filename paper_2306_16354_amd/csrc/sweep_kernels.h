@@ -122,6 +122,9 @@ struct SweepParams {
     long long carry_ws_words;
     int carry_ranges;
     unsigned int* carry_fault;
+    // Every-tile sweeps, optional: only the panels listed on the device, todo[0] of them from todo[2] on (what the
+    // half-precision engine of near_kernels.hip leaves to the list kernels); a launch with none ends at once.
+    const int32_t* todo;
     unsigned long long* survivors;   // optional device counter: pairs that passed the filter
     unsigned long long* tiles_done;  // optional device counter: (panel, tile) steps multiplied
 #ifdef SLHC_PHASE_TIMERS

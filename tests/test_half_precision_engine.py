@@ -1,0 +1,102 @@
+"""The half-precision engine (near_kernels.hip) where its tiles, segments, buffers and fallbacks end: its lists against the
+float32-product list kernels bit for bit, its nearest rows against the oracle."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2306_16354_amd as slhc
+    slhc.load_library()
+    assert torch.cuda.is_available()
+    return slhc
+
+
+def same_lists(lib, X, k):
+    Xd = torch.from_numpy(np.ascontiguousarray(X)).cuda()
+    a = lib.knn_graph(Xd, k, fp32_filter=True)
+    b = lib.knn_graph(Xd, k)
+    torch.cuda.synchronize()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+
+
+# one tile and its edges, the workgroup sizes' edges, one wavefront's 64 queries, 16-column steps, both kernels (128 / 129
+# columns), whole and partial chunks of 64, every list width, one- and two-stage plans
+@pytest.mark.parametrize("N,d,k", [
+    (2, 3, 1), (64, 16, 63), (127, 17, 5), (128, 1, 8), (129, 15, 64), (255, 31, 9), (257, 33, 2), (385, 112, 64),
+    (1025, 113, 16), (2047, 127, 33), (3000, 128, 1), (3001, 129, 7), (2500, 192, 64), (2600, 193, 17), (700, 321, 3),
+    (8193, 64, 12), (33_000, 48, 40), (40_000, 200, 1), (66_001, 20, 31), (140_000, 130, 16),
+])
+def test_lists_at_the_edges(lib, N, d, k):
+    print(f"half-precision lists N={N} d={d} k={k}", flush=True)
+    rng = np.random.default_rng(N + d)
+    centres = rng.uniform(-8, 8, size=(max(2, N // 400), d))
+    same_lists(lib, (centres[rng.integers(0, len(centres), N)] + rng.standard_normal((N, d))).astype(np.float32), k)
+
+
+@pytest.mark.parametrize("kind", ["one_point", "few_points", "far_rows", "beyond_float16", "sorted", "one_column"])
+@pytest.mark.parametrize("d", [24, 150])
+def test_lists_that_overflow_or_leave_float16(lib, kind, d):
+    """Masses of ties fill every buffer and go to the list kernels; rows 10^3 to 10^30 times larger than the rest do not fit
+    float16 after scaling; rows sorted by cluster."""
+    rng = np.random.default_rng(d)
+    N = 5000
+    X = rng.standard_normal((N, d))
+    if kind == "one_point":
+        X[:] = X[0]
+    elif kind == "few_points":
+        X = X[rng.integers(0, 3, N)]
+    elif kind == "far_rows":
+        X[::700] *= 1.0e3
+    elif kind == "beyond_float16":
+        X[::900] *= 1.0e7
+        X[5] = 3.0e17
+    elif kind == "sorted":
+        X = X * 0.1 + np.repeat(rng.uniform(-50, 50, size=(10, d)), N // 10, axis=0)
+    elif kind == "one_column":
+        X[:, 1:] = 0.0
+    print(f"half-precision lists, {kind}, d={d}", flush=True)
+    same_lists(lib, X.astype(np.float32), 12)
+
+
+@pytest.mark.parametrize("m,n,d", [(1, 2, 1), (63, 129, 16), (65, 5000, 17), (130, 128, 128), (300, 9000, 129), (1500, 3000, 40),
+                                   (4, 40_000, 260)])
+def test_nearest_row_of_another_matrix(lib, m, n, d):
+    print(f"half-precision 1-NN m={m} n={n} d={d}", flush=True)
+    rng = np.random.default_rng(m + n + d)
+    Q, Y = rng.standard_normal((m, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    Y[n // 2] = Q[m // 2]
+    gi, gd = lib.fused_1nn(torch.from_numpy(Q).cuda(), torch.from_numpy(Y).cuda())
+    torch.cuda.synchronize()
+    rows = np.unique(np.r_[0, m // 2, m - 1, rng.integers(0, m, 60)])
+    colour = np.r_[np.zeros(m, np.int32), np.ones(n, np.int32)]
+    oi, od = oracle.cross_1nn(np.concatenate([Q, Y]), colour, rows.astype(np.int64))
+    assert np.allclose(gd.cpu().numpy()[rows], od, rtol=1e-5, atol=1e-30)
+    assert (gi.cpu().numpy()[rows] == oi - m).mean() >= 0.99
+
+
+@pytest.mark.parametrize("N,d,m,colours", [(130, 16, 5, 2), (4000, 64, 129, 7), (4000, 129, 600, 3), (20_000, 33, 64, 5000), (3000, 8, 3000, 1)])
+def test_nearest_row_of_another_colour(lib, N, d, m, colours):
+    """Rows in tight clusters of one colour each, so that a query's nearest foreign rows lie within the copies' rounding
+    of each other by the hundred."""
+    print(f"half-precision cross 1-NN N={N} d={d} m={m} colours={colours}", flush=True)
+    rng = np.random.default_rng(N + m)
+    label = rng.integers(0, max(colours, 12), N)
+    X = (rng.uniform(-1000, 1000, size=(max(colours, 12), d))[label] + 0.1 * rng.standard_normal((N, d))).astype(np.float32)
+    colour = (label % colours).astype(np.int32)
+    rows = rng.integers(0, N, m).astype(np.int32)
+    gi, gd = lib.cross_1nn(torch.from_numpy(X).cuda(), torch.from_numpy(colour).cuda(), torch.from_numpy(rows).cuda())
+    torch.cuda.synchronize()
+    gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
+    take = rng.integers(0, m, 50)
+    if colours == 1:
+        assert (gi == -1).all() and np.isinf(gd).all()
+        return
+    oi, od = oracle.cross_1nn(X, colour, rows[take].astype(np.int64))
+    assert np.allclose(gd[take], od, rtol=1e-5)
+    assert (gi[take] == oi).mean() >= 0.99
