@@ -27,10 +27,10 @@
  *     of the calling thread.
  *   - Device memory: the library allocates none; everything it needs is in `workspace`.  Host
  *     memory: the synchronous entry points (slhc_slhc*, slhc_csr_msf, and slhc_knn_graph_opt with
- *     SLHC_PRUNE) allocate pinned staging buffers and HIP events for the duration of the call
- *     (slhc_slhc: up to 28 bytes per row of pinned memory and 16 bytes per row of pageable memory for
- *     the host dendrogram pass) and free them before returning.
- *     The library keeps no mutable state between calls other than the thread-local error text
+ *     SLHC_PRUNE) use pinned staging buffers (slhc_slhc: up to 28 bytes per row for the host dendrogram pass, plus 16
+ *     bytes per row of pageable memory) and HIP events.  Pinned buffers are kept for later calls, at most 256 MiB of
+ *     them over all threads; what goes beyond is given back at once.
+ *     The library keeps no other mutable state between calls than the thread-local error text
  *     (and the fixed scratch array of slhc_knn_graph_static, see there).
  *   - Calls that share a workspace must not overlap in time.  Calls on different streams with
  *     different workspaces and outputs are independent.

@@ -20,12 +20,11 @@ struct ForestState {
     int32_t* cand_u;             // [N] its other endpoint, or -1 when only the bound is known
     uint32_t* best_w;            // [N] per component: min weight bits over exact candidates
     unsigned long long* best_e;  // [N] per component: min (lo << 32 | hi) among those of best_w
-    uint32_t* min_lb;            // [N] per component: min lower-bound bits over unknown vertices
     int32_t* hook;               // [N] per component: component it attaches to this round
     int32_t* qlist;              // [N] rows sent to the cross-component 1-NN
-    int32_t* counters;           // [4]: 0 = queries this round, 1 = edges so far, 2 = hook chains not yet
-                                 //      followed to their end (cleared by forest_round_reset),
-                                 //      3 = site of the first failed index check (0 = none)
+    int32_t* counters;           // 0 = queries this round, 1 = edges so far, 2 = a hook chain waits for the host,
+                                 // 3 = site of the first failed index check (0 = none), 4 = forest complete,
+                                 // 5 = edges at the last forest_publish with `steady`, 6 = rounds (forest_small)
     int32_t* e_lo;               // [N-1] committed edges
     int32_t* e_hi;
     float* e_w;
@@ -56,8 +55,16 @@ hipError_t forest_commit(const ForestState& f, hipStream_t s);
 // Every component root follows the hooks up to `steps` components far and hooks itself there; with
 // `flag`, counters[2] is set when some root has not reached the end of its chain.
 hipError_t forest_jump(const ForestState& f, int steps, bool flag, hipStream_t s);
-// colour[v] = hook[colour[v]]; with only_if_converged the kernel does nothing while counters[2] != 0.
-hipError_t forest_relabel(const ForestState& f, bool only_if_converged, hipStream_t s);
+// colour[v] = end of the chain of hooks from colour[v]; the per-component minima are cleared for the next round.  A chain
+// longer than 64 hooks sets counters[2], and the rounds enqueued behind do nothing: the host finishes the chains
+// (forest_jump), clears the word and calls again with `again`.
+hipError_t forest_follow(const ForestState& f, bool again, hipStream_t s);
+// counters[0 .. 7] to host memory (host[1 ..]) and then `seq` to host[0].  With `steady` the forest also counts as
+// complete when no edge has been added since the last such call.
+hipError_t forest_publish(const ForestState& f, bool steady, int32_t* host, int32_t seq, hipStream_t s);
+// Rounds of a small forest in one launch, until it is complete or rows have to be queried (counters[0] of them in qlist).
+constexpr int FOREST_SMALL_MAX = 12288;
+hipError_t forest_small(const ForestState& f, bool first, hipStream_t s);
 
 // CSR input (offsets [V+1], indices [E], weights [E]).  forest_csr_check flags malformed arrays or
 // weights that are negative / not finite in f.counters[3]; forest_csr_scan fills cand_w / cand_u with
@@ -69,11 +76,13 @@ hipError_t forest_csr_scan(const int32_t* offsets, const int32_t* indices, const
 
 // Sort E edges ascending by (w, lo, hi).  keys/vals are scratch of E elements each; `temp` of
 // edge_sort_temp_bytes(E).  Result in out_lo/out_hi/out_w.
+// Copies of the sorted edges (each nullptr for none): the weights as heights, the end points from edge `from` on in host memory.
+struct EdgeCopies { float* heights; int32_t* host_lo; int32_t* host_hi; int from; };
 size_t edge_sort_temp_bytes(int E);
-hipError_t edge_sort(const int32_t* lo, const int32_t* hi, const float* w, int E,
+hipError_t edge_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int N /* ids are below N */,
                      unsigned long long* keys_a, unsigned long long* keys_b,
                      uint32_t* vals_a, uint32_t* vals_b, void* temp, size_t temp_bytes,
-                     int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s);
+                     int32_t* out_lo, int32_t* out_hi, float* out_w, const EdgeCopies& copies, hipStream_t s);
 
 // Components of the forest made of edges 0..R-1 of a tree's edge list (lo, hi < N): one pass hooks every
 // edge's larger root under the smaller and flattens the labels; `first` initialises label[v] = v.  The
@@ -84,12 +93,12 @@ hipError_t prefix_forest_pass(const int32_t* lo, const int32_t* hi, int R, int N
 hipError_t prefix_forest_keys(const int32_t* lo, const int32_t* label, int R, int N, uint32_t* key, uint32_t* val,
                               hipStream_t s);
 
-// glo[j] = lo[listed[j]], ghi[j] = hi[listed[j]] for j < R (-1 where listed[j] is not below R), and the way
-// back: children[2 listed[j] ..] = cj[2 j ..], sizes[listed[j]] = sj[j].
-hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, int R, int32_t* glo,
-                                int32_t* ghi, hipStream_t s);
-hipError_t prefix_forest_scatter(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int32_t* children,
-                                 int32_t* sizes, hipStream_t s);
+// The grouped edges in list order into host memory (end points, labels, edge numbers), and the way back: children and
+// sizes of all E merges from host memory, the first R in list order.
+hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, const uint32_t* key, int R, int32_t* glo,
+                                int32_t* ghi, uint32_t* gkey, uint32_t* ids, hipStream_t s);
+hipError_t linkage_upload(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int E, int32_t* children,
+                          int32_t* sizes, hipStream_t s);
 
 // Stable sort of n (key, value) pairs of 32-bit words by key (keys below 2^key_bits).
 size_t pair_sort_temp_bytes(int n);

@@ -27,6 +27,7 @@ namespace slhc {
 
 constexpr uint32_t INF_BITS = 0x7f800000u;
 constexpr int TB = 256;
+constexpr int FOLLOW_STEPS = 64;       // hooks a vertex follows in one launch of k_follow
 
 static inline int blocks_for(long long n) { return (int)((n + TB - 1) / TB); }
 
@@ -107,15 +108,21 @@ __device__ inline int block_append(bool mine, int32_t* counter)
     return mine ? wave_base[wave] + pre : -1;
 }
 
+// Rounds may be enqueued ahead of the host's reading: they do nothing once the forest is complete (counters[4], set by
+// k_publish) or while a hook chain of an earlier round waits for the host (counters[2]).
+__device__ inline bool forest_halted(const ForestState& f) { return (f.counters[2] | f.counters[4]) != 0; }
+
 __global__ void __launch_bounds__(TB) k_forest_init(ForestState f)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v < 4) f.counters[v] = 0;          // before the range test: N may be smaller than 4
+    if (v < 8) f.counters[v] = 0;          // before the range test: N may be smaller than 4
     if (v >= f.N) return;
     f.colour[v] = v;
     f.ptr[v] = 0;
     f.ext_idx[v] = -1;
     f.ext_dist[v] = 0.f;
+    f.best_w[v] = INF_BITS;
+    f.best_e[v] = ~0ull;
 }
 
 __global__ void __launch_bounds__(TB) k_round_reset(ForestState f)
@@ -124,9 +131,6 @@ __global__ void __launch_bounds__(TB) k_round_reset(ForestState f)
     if (v >= f.N) return;
     f.best_w[v] = INF_BITS;
     f.best_e[v] = ~0ull;
-    f.min_lb[v] = INF_BITS;
-    // (counters[2], the "hook chains unresolved" flag, is cleared by k_commit: the scan of the next round, and
-    // with it this kernel, is enqueued behind the relabelling, before the host has read the flag)
     if (v == 0) f.counters[0] = 0;
 }
 
@@ -138,8 +142,9 @@ __global__ void __launch_bounds__(TB) k_round_reset(ForestState f)
 template <int G>
 __global__ void __launch_bounds__(TB) k_scan_lists(ForestState f)
 {
-    // the scan for the next round is enqueued before the host knows that the tree is complete
-    if (f.counters[1] >= f.N - 1) return;
+    // the scan for the next round is enqueued before the host knows that the tree is complete, or that a hook chain is
+    // left to it
+    if (f.counters[1] >= f.N - 1 || forest_halted(f)) return;
     const int gid = (int)(((long long)blockIdx.x * TB + threadIdx.x) / G);
     const int j = threadIdx.x & (G - 1);
     const int lane = threadIdx.x & 63;
@@ -162,7 +167,7 @@ __global__ void __launch_bounds__(TB) k_scan_lists(ForestState f)
         if (more && mask) found = base + __builtin_ctzll(mask);
     }
     const bool head = live && j == 0;
-    bool exact = false, bounded = false;
+    bool exact = false;
     uint32_t wbits = INF_BITS;
     if (head && !in_range(c, f.N)) report(f, 2);
     else if (head) {
@@ -191,13 +196,10 @@ __global__ void __launch_bounds__(TB) k_scan_lists(ForestState f)
                 if (ed > lb) lb = ed;
                 f.cand_w[v] = lb;
                 f.cand_u[v] = -1;
-                wbits = __float_as_uint(lb);
-                bounded = true;
             }
         }
     }
     wave_min_into(f.best_w, c, wbits, exact);
-    wave_min_into(f.min_lb, c, wbits, bounded);
 }
 
 // Vertices that only know a lower bound and whose bound does not exceed their component's best
@@ -207,7 +209,7 @@ __global__ void __launch_bounds__(TB_WIDE) k_classify(ForestState f)
 {
     const int v = blockIdx.x * TB_WIDE + threadIdx.x;
     bool need = false;
-    if (f.counters[1] >= f.N - 1) return;                // tree complete (workgroup-uniform)
+    if (f.counters[1] >= f.N - 1 || forest_halted(f)) return;                // (workgroup-uniform)
     if (v < f.N && f.cand_u[v] < 0) {
         const int c = f.colour[v];
         if (in_range(c, f.N)) need = __float_as_uint(f.cand_w[v]) <= f.best_w[c];
@@ -271,19 +273,6 @@ __global__ void __launch_bounds__(TB) k_apply_queries(ForestState f, const int32
     wave_min_into(f.best_w, c, __float_as_uint(w), found);
 }
 
-// slot of this lane among the lanes of `mask` behind *counter (one atomic per wavefront)
-__device__ inline int wave_append(unsigned long long mask, bool mine, int32_t* counter)
-{
-    if (!mask) return -1;
-    const int lane = threadIdx.x & 63;
-    const int leader = __builtin_ctzll(mask);
-    int base = 0;
-    if (lane == leader) base = atomicAdd(counter, __popcll(mask));
-    base = __shfl(base, leader);
-    const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
-    return mine ? base + pre : -1;
-}
-
 // Two-phase connection sweeps.  k_split_queries sends the listed rows whose 128-row panel in the row
 // order is a sampled one (every `stride`-th panel) to part A and the others to part B.  After the
 // sweep over part A has lowered best_w, k_still_needed keeps of part B only the rows whose bound still
@@ -301,8 +290,9 @@ __global__ void __launch_bounds__(TB) k_split_queries(ForestState f, const int32
     }
     const bool sampled = v >= 0 && ((inv[v] >> 7) % stride) == 0;
     const bool other = v >= 0 && !sampled;
-    const int slot_a = wave_append(__ballot(sampled), sampled, &counts[0]);
-    const int slot_b = wave_append(__ballot(other), other, &counts[1]);
+    const int slot_a = block_append<TB>(sampled, &counts[0]);
+    __syncthreads();
+    const int slot_b = block_append<TB>(other, &counts[1]);
     if (sampled) { if (in_range(slot_a, f.N)) part_a[slot_a] = v; else report(f, 10); }
     if (other) { if (in_range(slot_b, f.N)) part_b[slot_b] = v; else report(f, 10); }
 }
@@ -318,14 +308,14 @@ __global__ void __launch_bounds__(TB) k_still_needed(ForestState f, const int32_
         if (!in_range(v, f.N) || !in_range(f.colour[v], f.N)) report(f, 11);
         else keep = __float_as_uint(f.cand_w[v]) <= f.best_w[f.colour[v]];
     }
-    const int slot = wave_append(__ballot(keep), keep, count);
+    const int slot = block_append<TB>(keep, count);
     if (keep) { if (in_range(slot, f.N)) out[slot] = v; else report(f, 11); }
 }
 
 __global__ void __launch_bounds__(TB) k_select_edges(ForestState f)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N) return;
+    if (v >= f.N || forest_halted(f)) return;
     const int u = f.cand_u[v];
     if (u < 0) return;
     const int c = f.colour[v];
@@ -338,13 +328,13 @@ __global__ void __launch_bounds__(TB) k_select_edges(ForestState f)
 // One thread per component root: append the component's edge (once per undirected edge) and
 // record which component it attaches to.  Two components that chose the same edge keep the
 // smaller root.
-constexpr int COMMIT_ITEMS = 8;        // vertices per thread: one atomic on the edge counter per 8192 vertices
+constexpr int COMMIT_ITEMS = 4;        // vertices per thread: one atomic on the edge counter per 4096 vertices (8: half the chip idle at 1M)
 __global__ void __launch_bounds__(TB_WIDE) k_commit(ForestState f)
 {
     __shared__ int wave_count[TB_WIDE / 64];
     __shared__ int wave_base[TB_WIDE / 64];
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    if (blockIdx.x == 0 && threadIdx.x == 0) f.counters[2] = 0;     // set again by k_jump if a hook chain stays unresolved
+    if (forest_halted(f)) return;
     int lo[COMMIT_ITEMS], hi[COMMIT_ITEMS];
     uint32_t wbits[COMMIT_ITEMS];
     unsigned int adds = 0;             // bit i: vertex i of this thread appends its component's edge
@@ -430,18 +420,180 @@ __global__ void __launch_bounds__(TB) k_jump(ForestState f, int steps, int flag)
     }
 }
 
-// With `only_if_converged` the kernel does nothing while counters[2] says that some hook chain has not
-// been followed to its end (the host then finishes the chains and launches it again).
-__global__ void __launch_bounds__(TB) k_relabel(ForestState f, int only_if_converged)
+// Every vertex follows the hooks of its component to their end (hooks of one round: a chain of a few components nearly
+// always), takes that root as its colour, and clears its slots of the per-component minima for the next round.  A root
+// shortens its own hook on the way, which can only help the others.  A chain longer than `steps` leaves its vertices as
+// they are and sets counters[2]: the host finishes it with k_jump and launches this kernel again.
+__global__ void __launch_bounds__(TB) k_follow(ForestState f, int steps, int again)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N) return;
-    if (only_if_converged && f.counters[2] != 0) return;
+    if (v >= f.N || (!again && f.counters[4] != 0)) return;
+    if (v == 0) f.counters[0] = 0;
+    f.best_w[v] = INF_BITS;
+    f.best_e[v] = ~0ull;
     const int c = f.colour[v];
     if (!in_range(c, f.N)) { report(f, 12); return; }
-    const int r = f.hook[c];
-    if (!in_range(r, f.N)) { report(f, 13); return; }
+    int r = c;
+    bool at_root = false;
+    for (int i = 0; i < steps; ++i) {
+        const int h = *reinterpret_cast<volatile int32_t*>(&f.hook[r]);
+        if (!in_range(h, f.N)) { report(f, 13); return; }
+        if (h == r) { at_root = true; break; }
+        r = h;
+    }
+    if (!at_root) { atomicOr(&f.counters[2], 1); return; }
+    if (v == c) f.hook[v] = r;
     f.colour[v] = r;
+}
+
+// The counters, to host memory: words 1 .. n hold counters[0 .. n-1] and word 0 the sequence number, written last.
+// Also notes whether the forest is complete: all N - 1 edges, or (steady != 0) a round that added none.
+__global__ void __launch_bounds__(64) k_publish(int32_t* __restrict__ counters, int N, int steady, int n, int32_t* __restrict__ host,
+                                                int32_t seq)
+{
+    const int i = threadIdx.x;
+    if (i == 0 && steady && counters[2] == 0) {
+        if (counters[1] >= N - 1 || counters[1] == counters[5]) counters[4] = 1;
+        counters[5] = counters[1];
+    }
+    if (i < n) __hip_atomic_store(host + 1 + i, counters[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    if (i == 0) __hip_atomic_store(host, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// All rounds of a forest of at most FOREST_SMALL_MAX vertices in one workgroup, until it is complete or a round has
+// rows to query: at this size a round's handful of launches and its read-back are a hundred times its work (4096 rows:
+// 5 rounds 0.33 ms as separate launches).  Colours, hooks and the per-component minima live in LDS; an edge's end
+// points fit one word there.  Same rules, same edges as the separate kernels.
+//   stage 0: first launch;  1: after a round's queries were applied (k_apply_queries): continue at the selection.
+__global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
+{
+    extern __shared__ __align__(16) unsigned char small_smem[];
+    __shared__ int s_edges, s_queries, s_bad;
+    const int N = f.N, tid = threadIdx.x;
+    unsigned int* bw = reinterpret_cast<unsigned int*>(small_smem);
+    unsigned int* be = bw + N;
+    unsigned short* col = reinterpret_cast<unsigned short*>(be + N);
+    unsigned short* hk = col + N;
+    if (tid == 0) {
+        if (stage == 0) for (int i = 0; i < 8; ++i) f.counters[i] = 0;
+        s_edges = stage == 0 ? 0 : f.counters[1];
+        s_bad = 0;
+    }
+    for (int v = tid; v < N; v += 1024) {
+        if (stage == 0) {
+            col[v] = (unsigned short)v;
+            f.ptr[v] = 0; f.ext_idx[v] = -1; f.ext_dist[v] = 0.f;
+        } else {
+            const int c = f.colour[v];
+            col[v] = (unsigned short)(in_range(c, N) ? c : 0);
+            bw[v] = f.best_w[v];
+        }
+    }
+    __syncthreads();
+    int rounds = stage == 0 ? 0 : f.counters[6];
+    bool selected = stage == 1;               // the candidates of this round are complete
+    for (int guard = 0; guard < 64; ++guard) {
+        if (!selected) {
+            if (tid == 0) s_queries = 0;
+            for (int v = tid; v < N; v += 1024) bw[v] = INF_BITS;
+            __syncthreads();
+            ++rounds;
+            for (int v = tid; v < N; v += 1024) {
+                const unsigned int c = col[v];
+                int found = -1;
+                float w = 0.f;
+                int u = -1;
+                for (int e = f.ptr[v]; e < f.k; ++e) {
+                    u = f.nbr_idx[(size_t)v * f.k + e];
+                    if (!in_range(u, N)) { report(f, 1); continue; }
+                    if (col[u] != c) { found = e; break; }
+                }
+                bool exact = true;
+                if (found >= 0) w = f.nbr_dist[(size_t)v * f.k + found];
+                else {
+                    const int eu = f.ext_idx[v];
+                    const float ed = f.ext_dist[v];
+                    if (eu >= 0 && eu < N && col[eu] != c) { w = ed; u = eu; }
+                    else {
+                        w = f.nbr_dist[(size_t)v * f.k + f.k - 1];
+                        if (ed > w) w = ed;
+                        u = -1;
+                        exact = false;
+                    }
+                }
+                f.ptr[v] = found >= 0 ? found : f.k;
+                f.cand_w[v] = w;
+                f.cand_u[v] = u;
+                if (exact) atomicMin(&bw[c], __float_as_uint(w));
+            }
+            __syncthreads();
+            for (int v = tid; v < N; v += 1024)
+                if (f.cand_u[v] < 0 && __float_as_uint(f.cand_w[v]) <= bw[col[v]]) f.qlist[atomicAdd(&s_queries, 1)] = v;
+            __syncthreads();
+            if (s_queries > 0) {
+                for (int v = tid; v < N; v += 1024) { f.colour[v] = col[v]; f.best_w[v] = bw[v]; }
+                if (tid == 0) { f.counters[0] = s_queries; f.counters[1] = s_edges; f.counters[6] = rounds; }
+                return;
+            }
+        }
+        selected = false;
+        // the component's edge among those of its lightest weight
+        for (int v = tid; v < N; v += 1024) be[v] = ~0u;
+        __syncthreads();
+        for (int v = tid; v < N; v += 1024) {
+            const int u = f.cand_u[v];
+            if (u < 0) continue;
+            const unsigned int c = col[v];
+            if (u >= N) { report(f, 7); continue; }
+            if (__float_as_uint(f.cand_w[v]) != bw[c]) continue;
+            const unsigned int lo = v < u ? v : u, hi = v < u ? u : v;
+            atomicMin(&be[c], (lo << 16) | hi);
+        }
+        __syncthreads();
+        const int before = s_edges;
+        __syncthreads();
+        for (int v = tid; v < N; v += 1024) {
+            if (col[v] != v) continue;
+            unsigned int hook = v;
+            const unsigned int wb = bw[v], e = be[v];
+            if (wb != INF_BITS) {
+                const int elo = (int)(e >> 16), ehi = (int)(e & 0xffffu);
+                if (elo >= N || ehi >= N) { report(f, 8); s_bad = 1; }
+                else {
+                    const int clo = col[elo], chi = col[ehi];
+                    const int other = clo == v ? chi : clo;
+                    if (other == v || (clo != v && chi != v)) { report_with(f, 9, v, elo, ehi, clo, chi, (int)wb); s_bad = 1; }
+                    else {
+                        const bool mutual = bw[other] == wb && be[other] == e;
+                        if (!mutual || v < other) {
+                            const int slot = atomicAdd(&s_edges, 1);
+                            if (slot < N - 1) { f.e_lo[slot] = elo; f.e_hi[slot] = ehi; f.e_w[slot] = __uint_as_float(wb); }
+                        }
+                        hook = mutual && v < other ? v : other;
+                    }
+                }
+            }
+            hk[v] = (unsigned short)hook;
+        }
+        __syncthreads();
+        for (int v = tid; v < N; v += 1024) {
+            if (col[v] != v) continue;
+            unsigned int r = v;
+            for (int i = 0; i < N; ++i) {                 // (a chain visits a component once)
+                const unsigned int h = *reinterpret_cast<volatile unsigned short*>(&hk[r]);
+                if (h == r) break;
+                r = h;
+            }
+            *reinterpret_cast<volatile unsigned short*>(&hk[v]) = (unsigned short)r;
+        }
+        __syncthreads();
+        for (int v = tid; v < N; v += 1024) col[v] = hk[col[v]];
+        __syncthreads();
+        if (s_edges >= N - 1 || s_edges == before || s_bad) break;
+    }
+    for (int v = tid; v < N; v += 1024) f.colour[v] = col[v];
+    if (tid == 0) { f.counters[0] = 0; f.counters[1] = s_edges; f.counters[6] = rounds; }
 }
 
 // Rows per component: sizes[c] += 1 for every row of colour c (entries outside [0, bins) are skipped;
@@ -501,7 +653,7 @@ __global__ void __launch_bounds__(TB) k_csr_scan(const int32_t* __restrict__ off
                                                  const float* __restrict__ weights, int E, ForestState f)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N) return;
+    if (v >= f.N || forest_halted(f)) return;
     // f.ptr[v] != 0: an earlier round found every neighbour of v in v's own component.  Components only
     // grow, so v never has an outgoing edge again; its cand_u stays -1 and its row is not read any more
     // (after a few rounds that is most vertices).
@@ -578,7 +730,20 @@ hipError_t forest_commit(const ForestState& f, hipStream_t s)
     return hipGetLastError();
 }
 hipError_t forest_jump(const ForestState& f, int steps, bool flag, hipStream_t s) { LAUNCH1(k_jump, f.N, s, f, steps, flag ? 1 : 0); }
-hipError_t forest_relabel(const ForestState& f, bool only_if_converged, hipStream_t s) { LAUNCH1(k_relabel, f.N, s, f, only_if_converged ? 1 : 0); }
+hipError_t forest_follow(const ForestState& f, bool again, hipStream_t s) { LAUNCH1(k_follow, f.N, s, f, FOLLOW_STEPS, again ? 1 : 0); }
+hipError_t forest_publish(const ForestState& f, bool steady, int32_t* host, int32_t seq, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, f.counters, f.N, steady ? 1 : 0, 8, host, seq);
+    return hipGetLastError();
+}
+hipError_t forest_small(const ForestState& f, bool first, hipStream_t s)
+{
+    const size_t lds = (size_t)f.N * 12;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_forest_small, dim3(1), dim3(1024), lds, s, f, first ? 0 : 1);
+    return hipGetLastError();
+}
 
 hipError_t forest_csr_check(const int32_t* offsets, const int32_t* indices, const float* weights, int V, int E,
                             int32_t* counters, hipStream_t s)
@@ -595,26 +760,14 @@ hipError_t forest_csr_scan(const int32_t* offsets, const int32_t* indices, const
 // ------------------------------------------------------------------------------- edge sort
 __global__ void __launch_bounds__(TB) k_pack_edges(const int32_t* __restrict__ lo,
                                                    const int32_t* __restrict__ hi,
-                                                   const float* __restrict__ w, int E,
+                                                   const float* __restrict__ w, int bits, int E,
                                                    unsigned long long* __restrict__ keys,
                                                    uint32_t* __restrict__ vals)
 {
     const int i = blockIdx.x * TB + threadIdx.x;
     if (i >= E) return;
-    keys[i] = ((unsigned long long)(unsigned int)lo[i] << 32) | (unsigned int)hi[i];
+    keys[i] = ((unsigned long long)(unsigned int)lo[i] << bits) | (unsigned int)hi[i];
     vals[i] = __float_as_uint(w[i]);
-}
-
-__global__ void __launch_bounds__(TB) k_unpack_edges(const unsigned long long* __restrict__ ends,
-                                                     const uint32_t* __restrict__ wbits, int E,
-                                                     int32_t* __restrict__ lo, int32_t* __restrict__ hi,
-                                                     float* __restrict__ w)
-{
-    const int i = blockIdx.x * TB + threadIdx.x;
-    if (i >= E) return;
-    lo[i] = (int32_t)(ends[i] >> 32);
-    hi[i] = (int32_t)(ends[i] & 0xffffffffull);
-    w[i] = __uint_as_float(wbits[i]);
 }
 
 // ---- components of the forest made of the first R edges of a weight-sorted tree (for the dendrogram) ----
@@ -668,10 +821,11 @@ __global__ void __launch_bounds__(256) k_prefix_keys(const int32_t* __restrict__
     val[e] = (uint32_t)e;
 }
 
-// end points of the grouped edges in list order
+// The grouped edges in list order, straight into host memory: end points, group labels and edge numbers.
 __global__ void __launch_bounds__(256) k_prefix_gather(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
-                                                       const uint32_t* __restrict__ listed, int R,
-                                                       int32_t* __restrict__ glo, int32_t* __restrict__ ghi)
+                                                       const uint32_t* __restrict__ listed, const uint32_t* __restrict__ key, int R,
+                                                       int32_t* __restrict__ glo, int32_t* __restrict__ ghi,
+                                                       uint32_t* __restrict__ gkey, uint32_t* __restrict__ ids)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= R) return;
@@ -679,33 +833,36 @@ __global__ void __launch_bounds__(256) k_prefix_gather(const int32_t* __restrict
     const bool ok = e < (uint32_t)R;
     glo[j] = ok ? lo[e] : -1;
     ghi[j] = ok ? hi[e] : -1;
+    gkey[j] = key[j];
+    ids[j] = e;
 }
 
-// children / sizes computed in list order back to edge order
-__global__ void __launch_bounds__(256) k_prefix_scatter(const uint32_t* __restrict__ listed, const int32_t* __restrict__ cj,
-                                                        const int32_t* __restrict__ sj, int R,
+// children / sizes from host memory: the first R merges in list order back to edge order (listed), the rest as they are
+__global__ void __launch_bounds__(256) k_linkage_upload(const uint32_t* __restrict__ listed, const int2* __restrict__ cj,
+                                                        const int32_t* __restrict__ sj, int R, int E,
                                                         int32_t* __restrict__ children, int32_t* __restrict__ sizes)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= R) return;
-    const uint32_t e = listed[j];
-    if (e >= (uint32_t)R) return;
-    children[2 * (size_t)e] = cj[2 * (size_t)j];
-    children[2 * (size_t)e + 1] = cj[2 * (size_t)j + 1];
+    if (j >= E) return;
+    const uint32_t e = j < R ? listed[j] : (uint32_t)j;
+    if (e >= (uint32_t)E) return;
+    const int2 c = cj[j];
+    children[2 * (size_t)e] = c.x;
+    children[2 * (size_t)e + 1] = c.y;
     sizes[e] = sj[j];
 }
 
-hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, int R, int32_t* glo,
-                                int32_t* ghi, hipStream_t s)
+hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, const uint32_t* key, int R, int32_t* glo,
+                                int32_t* ghi, uint32_t* gkey, uint32_t* ids, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_prefix_gather, dim3((R + 255) / 256), dim3(256), 0, s, lo, hi, listed, R, glo, ghi);
+    hipLaunchKernelGGL(k_prefix_gather, dim3((R + 255) / 256), dim3(256), 0, s, lo, hi, listed, key, R, glo, ghi, gkey, ids);
     return hipGetLastError();
 }
 
-hipError_t prefix_forest_scatter(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int32_t* children,
-                                 int32_t* sizes, hipStream_t s)
+hipError_t linkage_upload(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int E, int32_t* children,
+                          int32_t* sizes, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_prefix_scatter, dim3((R + 255) / 256), dim3(256), 0, s, listed, cj, sj, R, children, sizes);
+    hipLaunchKernelGGL(k_linkage_upload, dim3((E + 255) / 256), dim3(256), 0, s, listed, reinterpret_cast<const int2*>(cj), sj, R, E, children, sizes);
     return hipGetLastError();
 }
 
@@ -725,33 +882,76 @@ hipError_t prefix_forest_keys(const int32_t* lo, const int32_t* label, int R, in
     return hipGetLastError();
 }
 
-size_t edge_sort_temp_bytes(int E)
+// Radix passes from 32 768 pairs on: the library's default sorts up to a million of them by merging, ten and more
+// launches over the whole data (1M edges: 390 us for both sorts, 130 us by radix passes).
+using radix_passes = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config, rocprim::default_config, 32768>;
+
+// Trees of at most 2^16 vertices: weight and both end points fit one 64-bit key, so one sort of keys does.
+constexpr int SMALL_IDS = 1 << 16;
+__global__ void __launch_bounds__(TB) k_pack_small(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
+                                                   const float* __restrict__ w, int E, unsigned long long* __restrict__ keys)
 {
-    size_t a = 0, b = 0;
-    unsigned long long* k64 = nullptr;
-    uint32_t* k32 = nullptr;
-    (void)rocprim::radix_sort_pairs(nullptr, a, k64, k64, k32, k32, (size_t)E, 0, 64, (hipStream_t)0);
-    (void)rocprim::radix_sort_pairs(nullptr, b, k32, k32, k64, k64, (size_t)E, 0, 32, (hipStream_t)0);
-    return ((a > b ? a : b) + 255) & ~(size_t)255;
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i < E) keys[i] = ((unsigned long long)__float_as_uint(w[i]) << 32) | ((unsigned int)lo[i] << 16) | (unsigned int)hi[i];
+}
+// ends: (lo << shift | hi), wbits apart (nullptr: the small form).  heights, host_lo, host_hi: optional copies, the latter
+// two in host memory.
+__global__ void __launch_bounds__(TB) k_unpack_edges(const unsigned long long* __restrict__ ends, const uint32_t* __restrict__ wbits,
+                                                     int shift, int E, int32_t* __restrict__ lo, int32_t* __restrict__ hi,
+                                                     float* __restrict__ w, EdgeCopies c)
+{
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i >= E) return;
+    const unsigned long long e = ends[i];
+    const int a = wbits ? (int)(e >> shift) : (int)((e >> 16) & 0xffffu);
+    const int b = wbits ? (int)(e & ((1ull << shift) - 1ull)) : (int)(e & 0xffffu);
+    const float x = __uint_as_float(wbits ? wbits[i] : (uint32_t)(e >> 32));
+    lo[i] = a; hi[i] = b; w[i] = x;
+    if (c.heights) c.heights[i] = x;
+    if (c.host_lo && i >= c.from) { c.host_lo[i] = a; c.host_hi[i] = b; }
 }
 
-// Two stable least-significant-digit passes: by (lo, hi), then by the weight bits (non-negative
-// floats order like their bit patterns).
-hipError_t edge_sort(const int32_t* lo, const int32_t* hi, const float* w, int E,
+size_t edge_sort_temp_bytes(int E)
+{
+    size_t a = 0, b = 0, d = 0;
+    unsigned long long* k64 = nullptr;
+    uint32_t* k32 = nullptr;
+    (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, a, k64, k64, k32, k32, (size_t)E, 0, 64, (hipStream_t)0);
+    (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, b, k32, k32, k64, k64, (size_t)E, 0, 32, (hipStream_t)0);
+    (void)rocprim::radix_sort_keys<radix_passes>(nullptr, d, k64, k64, (size_t)E, 0, 64, (hipStream_t)0);
+    a = a > b ? a : b;
+    return ((a > d ? a : d) + 255) & ~(size_t)255;
+}
+
+// Up to 2^16 vertices one sort of 64-bit keys; beyond, two stable passes: by (lo, hi), packed into as many bits as N
+// needs, then by the weight bits (non-negative floats order like their bit patterns).
+hipError_t edge_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int N,
                      unsigned long long* keys_a, unsigned long long* keys_b,
                      uint32_t* vals_a, uint32_t* vals_b, void* temp, size_t temp_bytes,
-                     int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s)
+                     int32_t* out_lo, int32_t* out_hi, float* out_w, const EdgeCopies& copies, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_pack_edges, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, E, keys_a, vals_a);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
     size_t tb = temp_bytes;
-    e = rocprim::radix_sort_pairs(temp, tb, keys_a, keys_b, vals_a, vals_b, (size_t)E, 0, 64, s);
+    hipError_t e;
+    if (N <= SMALL_IDS) {
+        hipLaunchKernelGGL(k_pack_small, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, E, keys_a);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = rocprim::radix_sort_keys<radix_passes>(temp, tb, keys_a, keys_b, (size_t)E, 0, 64, s);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(k_unpack_edges, dim3(blocks_for(E)), dim3(TB), 0, s, keys_b, (const uint32_t*)nullptr, 16, E, out_lo, out_hi, out_w, copies);
+        return hipGetLastError();
+    }
+    int bits = 17;
+    while (bits < 31 && (1LL << bits) < (long long)N) ++bits;
+    hipLaunchKernelGGL(k_pack_edges, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, bits, E, keys_a, vals_a);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    e = rocprim::radix_sort_pairs<radix_passes>(temp, tb, keys_a, keys_b, vals_a, vals_b, (size_t)E, 0, (unsigned int)(2 * bits), s);
     if (e != hipSuccess) return e;
     tb = temp_bytes;
-    e = rocprim::radix_sort_pairs(temp, tb, vals_b, vals_a, keys_b, keys_a, (size_t)E, 0, 32, s);
+    e = rocprim::radix_sort_pairs<radix_passes>(temp, tb, vals_b, vals_a, keys_b, keys_a, (size_t)E, 0, 32, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_unpack_edges, dim3(blocks_for(E)), dim3(TB), 0, s, keys_a, vals_a, E, out_lo, out_hi, out_w);
+    hipLaunchKernelGGL(k_unpack_edges, dim3(blocks_for(E)), dim3(TB), 0, s, keys_a, vals_a, bits, E, out_lo, out_hi, out_w, copies);
     return hipGetLastError();
 }
 
@@ -759,7 +959,7 @@ size_t pair_sort_temp_bytes(int n)
 {
     size_t a = 0;
     uint32_t* k32 = nullptr;
-    (void)rocprim::radix_sort_pairs(nullptr, a, k32, k32, k32, k32, (size_t)n, 0, 32, (hipStream_t)0);
+    (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, a, k32, k32, k32, k32, (size_t)n, 0, 32, (hipStream_t)0);
     return (a + 255) & ~(size_t)255;
 }
 
@@ -770,7 +970,7 @@ hipError_t pair_sort_u32(const uint32_t* keys_in, uint32_t* keys_out, const uint
     size_t tb = temp_bytes;
     if (key_bits < 1) key_bits = 1;
     if (key_bits > 32) key_bits = 32;
-    return rocprim::radix_sort_pairs(temp, tb, keys_in, keys_out, vals_in, vals_out, (size_t)n, 0,
+    return rocprim::radix_sort_pairs<radix_passes>(temp, tb, keys_in, keys_out, vals_in, vals_out, (size_t)n, 0,
                                      (unsigned int)key_bits, s);
 }
 

@@ -267,11 +267,142 @@ __global__ void __launch_bounds__(256) k_sample_sums(const float* __restrict__ a
     if (threadIdx.x == 0) { out[0] = sa[0]; out[1] = sb[0]; }
 }
 
-// Pinned host staging for device<->host copies (freed when the call returns).
+// Pinned host memory, kept between calls: taking it from the runtime and giving it back costs tens of microseconds a
+// piece and milliseconds for the staging of a million rows.  At most POOL_LIMIT bytes lie idle; what does not fit goes
+// back to the runtime at once, and the rest when the process ends.  Any thread may take and give blocks.
+class PinnedPool {
+public:
+    struct Block { void* p; size_t bytes; };
+    hipError_t take(size_t bytes, Block* out)
+    {
+        size_t want = 4096;
+        while (want < bytes && want < ((size_t)1 << 20)) want *= 2;
+        if (want < bytes) want = (bytes + ((size_t)1 << 20) - 1) >> 20 << 20;
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            size_t best = idle_.size();
+            for (size_t i = 0; i < idle_.size(); ++i)
+                if (idle_[i].bytes >= want && idle_[i].bytes <= 4 * want && (best == idle_.size() || idle_[i].bytes < idle_[best].bytes)) best = i;
+            if (best < idle_.size()) {
+                *out = idle_[best];
+                idle_bytes_ -= out->bytes;
+                idle_[best] = idle_.back();
+                idle_.pop_back();
+                return hipSuccess;
+            }
+        }
+        void* p = nullptr;
+        const hipError_t e = hipHostMalloc(&p, want, hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent);
+        if (e != hipSuccess) return e;
+        *out = Block{p, want};
+        return hipSuccess;
+    }
+    void give(Block b)
+    {
+        {
+            std::lock_guard<std::mutex> lock(m_);
+            if (idle_bytes_ + b.bytes <= POOL_LIMIT && idle_.size() < 64) {
+                try {
+                    idle_.push_back(b);
+                    idle_bytes_ += b.bytes;
+                    return;
+                } catch (...) { }
+            }
+        }
+        (void)hipHostFree(b.p);
+    }
+private:
+    static constexpr size_t POOL_LIMIT = (size_t)256 << 20;
+    std::mutex m_;
+    std::vector<Block> idle_;
+    size_t idle_bytes_ = 0;
+};
+PinnedPool& pinned_pool() { static PinnedPool* pool = new PinnedPool; return *pool; }       // (never destroyed: the runtime may be gone first)
+
+// A block of the pool for the duration of a call.  The stream's work on it must be over when it is given back:
+// idle() says that it is; otherwise (an early return) the destructor waits for the stream.
 struct PinnedHost {
     void* p = nullptr;
-    hipError_t alloc(size_t bytes) { return hipHostMalloc(&p, bytes, hipHostMallocDefault); }
-    ~PinnedHost() { if (p) (void)hipHostFree(p); }
+    PinnedPool::Block b{nullptr, 0};
+    hipStream_t s;
+    bool busy = true;
+    explicit PinnedHost(hipStream_t stream) : s(stream) {}
+    PinnedHost(const PinnedHost&) = delete;
+    PinnedHost& operator=(const PinnedHost&) = delete;
+    hipError_t alloc(size_t bytes)
+    {
+        const hipError_t e = pinned_pool().take(bytes, &b);
+        if (e == hipSuccess) p = b.p;
+        return e;
+    }
+    void idle() { busy = false; }
+    ~PinnedHost()
+    {
+        if (!p) return;
+        if (busy) (void)hipStreamSynchronize(s);
+        pinned_pool().give(b);
+    }
+};
+
+// words of device memory to host memory, then `seq` to host[0] (one workgroup)
+__global__ void __launch_bounds__(256) k_fetch_words(const uint32_t* __restrict__ src, int n, uint32_t* __restrict__ host, uint32_t seq)
+{
+    for (int i = threadIdx.x; i < n; i += 256) __hip_atomic_store(host + 1 + i, src[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    __threadfence_system();
+    __syncthreads();
+    if (threadIdx.x == 0) __hip_atomic_store(host, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
+// A few words from the device without a copy and a synchronisation (20 us): a kernel behind the work writes them to host
+// memory, with a sequence number last, and the host watches for that number.
+struct Mailbox {
+    PinnedHost box;
+    hipStream_t s;
+    uint32_t seq = 0;
+    static constexpr int WORDS = 4096;
+    explicit Mailbox(hipStream_t stream) : box(stream), s(stream) {}
+    hipError_t open()
+    {
+        const hipError_t e = box.alloc((WORDS + 16) * sizeof(uint32_t));
+        if (e != hipSuccess) return e;
+        slot()[0] = 0u;
+        return hipSuccess;
+    }
+    volatile uint32_t* slot() { return static_cast<volatile uint32_t*>(box.p); }
+    uint32_t* words() { return static_cast<uint32_t*>(box.p); }
+    uint32_t next() { return ++seq; }
+    // until the sequence number last handed out has arrived
+    hipError_t wait()
+    {
+        for (unsigned spins = 0;; ++spins) {
+            if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+#if defined(__x86_64__)
+            __builtin_ia32_pause();
+#endif
+            if ((spins & 4095u) == 4095u) {
+                // an error ends the wait; so does a stream that has run dry without the number
+                const hipError_t q = hipStreamQuery(s);
+                if (q == hipErrorNotReady) continue;
+                if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+                if (q != hipSuccess) return q;
+                const hipError_t w = hipStreamSynchronize(s);
+                if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+                return w != hipSuccess ? w : hipErrorUnknown;
+            }
+        }
+    }
+    // n words at `src` (device), as of everything enqueued so far, to out
+    hipError_t fetch(const void* src, int n, void* out)
+    {
+        if (n < 1 || n > WORDS) return hipErrorInvalidValue;
+        hipLaunchKernelGGL(k_fetch_words, dim3(1), dim3(256), 0, s, static_cast<const uint32_t*>(src), n, words(), next());
+        hipError_t e = hipGetLastError();
+        if (e != hipSuccess) return e;
+        e = wait();
+        if (e != hipSuccess) return e;
+        std::memcpy(out, words() + 1, (size_t)n * 4);
+        return hipSuccess;
+    }
 };
 
 // A pair of HIP events bracketing work on a stream.
@@ -279,7 +410,7 @@ struct EventPair {
     hipEvent_t a = nullptr, b = nullptr;
     hipError_t create() { hipError_t e = hipEventCreate(&a); return e != hipSuccess ? e : hipEventCreate(&b); }
     ~EventPair() { if (a) (void)hipEventDestroy(a); if (b) (void)hipEventDestroy(b); }
-    float ms() const { float t = 0.f; return hipEventElapsedTime(&t, a, b) == hipSuccess ? t : -1.f; }
+    float ms() const { float t = 0.f; return a && b && hipEventElapsedTime(&t, a, b) == hipSuccess ? t : -1.f; }
 };
 
 double now_ms()
@@ -422,14 +553,14 @@ struct NearWs {
 
 // Buffers of the spatially coherent row order (see build_order).
 struct OrderWs {
-    float *Xp, *hp, *pdist, *sample, *Xs, *hs, *tile_c, *tile_r, *gap_ws, *tile_gap, *n_w, *n_heights;
+    float *Xp, *hp, *pdist, *sample, *Xs, *hs, *tile_c, *tile_r, *gap_ws, *tile_gap, *n_w;
     float *Xs_split, *hs_split;      // the reordered copy in split bfloat16 halves and its half norms (nullptr: d does not allow it)
     // a second split copy, every tile relative to the centre of the first tile of its region, with its half norms;
     // region number, first tile and boundary flag per tile (see run_knn; nullptr: the pruned sweeps keep float32 products)
     float *Xs_local, *hs_local, *region_other_min;
     int32_t *tile_region, *tile_first, *tile_last, *tile_boundary;
     int32_t *pid, *perm, *inv, *colour_s, *qslot, *tile_colour, *tile_list, *counts, *rank, *shift, *far_count;
-    int32_t *n_src, *n_dst, *n_children, *n_sizes;
+    int32_t *n_src, *n_dst;
     uint32_t *tmp_a, *tmp_b, *tmp_c;
     slhc::NearCopy near_p{};          // float16 copy of the pivots, and scratch of the assignment
     unsigned long long* best_at;
@@ -478,7 +609,6 @@ struct OrderWs {
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
         n_src = c.take<int32_t>(pm); n_dst = c.take<int32_t>(pm); n_w = c.take<float>(pm);
-        n_children = c.take<int32_t>(2 * pm); n_heights = c.take<float>(pm); n_sizes = c.take<int32_t>(pm);
         const int32_t kp = Pmax - 1 < NESTED_K ? Pmax - 1 : NESTED_K;
         // (the clustering runs on the pivots in use, fewer than Pmax: a k-NN sweep of few panels then also wants
         // its scratch for candidate ranges, which the layout for Pmax rows may not contain)
@@ -550,7 +680,7 @@ struct SlhcWs {
     int32_t* nbr_idx; float* nbr_dist;
     int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *qlist, *q_idx, *counters, *e_lo, *e_hi;
     float *ext_dist, *cand_w, *q_dist, *e_w;
-    uint32_t *best_w, *min_lb, *vals_a, *vals_b;
+    uint32_t *best_w, *vals_a, *vals_b;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
     size_t bytes;
@@ -566,7 +696,7 @@ struct SlhcWs {
         q_idx = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
         ext_dist = c.take<float>(n); cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
-        best_w = c.take<uint32_t>(n); min_lb = c.take<uint32_t>(n);
+        best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
         sort_temp_bytes = std::max(slhc::edge_sort_temp_bytes((int)(N - 1)), slhc::pair_sort_temp_bytes((int)N));   // the second: grouping the dendrogram's edges
@@ -650,7 +780,9 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     const int n = (int)N;
     const int P1 = o.P1;
     PhaseLog log(s);
-    PinnedHost pin;
+    Mailbox mail(s);
+    HIP_TRY(mail.open());
+    PinnedHost pin(s);
     HIP_TRY(pin.alloc(((size_t)OrderWs::SAMPLE + 16 + 6 * (size_t)o.Pmax) * 4));
     float* h_sample = static_cast<float*>(pin.p);
     int32_t* h_count = reinterpret_cast<int32_t*>(h_sample + OrderWs::SAMPLE);
@@ -661,8 +793,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     int32_t* h_rank = h_cells + o.Pmax;
     int32_t* h_shift = h_rank + o.Pmax;
 
-    HIP_TRY(hipMemcpyAsync(h_count + 8, nonfinite, 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mail.fetch(nonfinite, 1, h_count + 8));
     if (h_count[8] != 0) { set_err("a row of X is not finite (NaN, infinity, or a squared norm beyond float32)"); return SLHC_NONFINITE; }
 
     // ---- 1. pivots and assignment
@@ -671,8 +802,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     if (rc != SLHC_OK) return rc;
     const int S = n < OrderWs::SAMPLE ? n : OrderWs::SAMPLE;
     HIP_TRY(slhc::order_pick_f32(o.pdist, n, S, o.sample, s));
-    HIP_TRY(hipMemcpyAsync(h_sample, o.sample, (size_t)S * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mail.fetch(o.sample, S, h_sample));
     log.mark("row order: %d pivots, nearest pivot of every row", P1);
     // Scale of a well-placed cell: 4 x the median positive squared distance to the pivot.  (When the
     // clusters are much smaller than the pivot spacing the median is an inter-cluster distance and no
@@ -695,8 +825,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
         hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(o.far_count), 64);
         HIP_TRY(hipGetLastError());
         HIP_TRY(slhc::order_mark_far(o.pdist, n, tau, o.tmp_a, o.far_count, s));
-        HIP_TRY(hipMemcpyAsync(h_count, o.far_count, 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(mail.fetch(o.far_count, 1, h_count));
         const int far = h_count[0];
         if (far < 0 || far > n) { set_err("row order: bad far-row count %d", far); return SLHC_INTERNAL; }
         if (far == 0) break;
@@ -743,7 +872,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     for (int i = 0; i < P; ++i) head[(size_t)i] = tail[(size_t)i] = up_set[(size_t)i] = i;
     if (P >= 2) {
         const int32_t kp = P - 1 < NESTED_K ? P - 1 : NESTED_K;
-        rc = run_slhc(o.Xp, P, d, kp, o.n_src, o.n_dst, o.n_w, o.n_children, o.n_heights, o.n_sizes, nullptr,
+        rc = run_slhc(o.Xp, P, d, kp, o.n_src, o.n_dst, o.n_w, nullptr, nullptr, nullptr, nullptr,
                       o.nested_ws, s, 0u, false);
         if (rc != SLHC_OK) return rc;
         const size_t E = (size_t)(P - 1);
@@ -820,7 +949,9 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     HIP_TRY(slhc::order_gather_padded(X, hn, o.perm, o.Ns, n, d, o.Xs, o.hs, s));
     HIP_TRY(slhc::order_tile_balls(o.Xs, o.perm, o.Ns, d, o.tile_c, o.tile_r, s));
     if (o.tile_gap) HIP_TRY(slhc::order_tile_gaps(o.tile_c, o.tile_r, (o.Ns + 127) / 128, d, o.tile_gap, s));
-    HIP_TRY(hipStreamSynchronize(s));        // the pinned staging buffer is released on return
+    HIP_TRY(hipStreamSynchronize(s));        // the pinned staging buffer is given back on return
+    pin.idle();
+    mail.box.idle();
     log.mark("row order: %d rows placed in %d (tau %.4g, padding above %.4g), tile balls", n, o.Ns, (double)tau, (double)tau_pad);
     return SLHC_OK;
 }
@@ -894,13 +1025,13 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
                 // rows share an offset far larger than their distances, which then fills the filter's slack and
                 // lets every pair of a tile through.  The split copy is taken relative to the column means; when
                 // that shrinks the norms eightfold or more, the pruned sweeps multiply it too.
-                PinnedHost pin;
-                HIP_TRY(pin.alloc(2 * sizeof(float)));
-                float* h_sums = static_cast<float*>(pin.p);
+                Mailbox mail(stream);
+                HIP_TRY(mail.open());
+                float h_sums[2];
                 hipLaunchKernelGGL(k_sample_sums, dim3(1), dim3(256), 0, stream, ws.hn, ws.hn_split, (int)N, ws.shift_scratch);
                 HIP_TRY(hipGetLastError());
-                HIP_TRY(hipMemcpyAsync(h_sums, ws.shift_scratch, 2 * sizeof(float), hipMemcpyDeviceToHost, stream));
-                HIP_TRY(hipStreamSynchronize(stream));
+                HIP_TRY(mail.fetch(ws.shift_scratch, 2, h_sums));
+                mail.box.idle();
                 ws.offset_heavy = h_sums[0] >= 8.f * h_sums[1];          // false when either sum is NaN
             }
         }
@@ -1383,7 +1514,7 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
 struct CsrWs {
     int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *counters, *e_lo, *e_hi;
     float *ext_dist, *cand_w, *e_w;
-    uint32_t *best_w, *min_lb, *vals_a, *vals_b;
+    uint32_t *best_w, *vals_a, *vals_b;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
     size_t bytes;
@@ -1395,7 +1526,7 @@ struct CsrWs {
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
         ext_dist = c.take<float>(n); cand_w = c.take<float>(n); e_w = c.take<float>(n);
-        best_w = c.take<uint32_t>(n); min_lb = c.take<uint32_t>(n);
+        best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
         sort_temp_bytes = slhc::edge_sort_temp_bytes((int)(V > 1 ? V - 1 : 1));
@@ -1440,59 +1571,87 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         f.N = (int)V; f.k = 1;
         f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist;
         f.cand_w = ws.cand_w; f.cand_u = ws.cand_u; f.best_w = ws.best_w; f.best_e = ws.best_e;
-        f.min_lb = ws.min_lb; f.hook = ws.hook; f.qlist = ws.ptr; f.counters = ws.counters;
+        f.hook = ws.hook; f.qlist = ws.ptr; f.counters = ws.counters;
         f.e_lo = ws.e_lo; f.e_hi = ws.e_hi; f.e_w = ws.e_w;
         HIP_TRY(slhc::forest_init(f, s));
         HIP_TRY(slhc::forest_csr_check(offsets, indices, weights, (int)V, (int)E, ws.counters, s));
-        PinnedHost pin_cnt;
-        HIP_TRY(pin_cnt.alloc(64));
-        int32_t* h_cnt = static_cast<int32_t*>(pin_cnt.p);
-        HIP_TRY(hipMemcpyAsync(h_cnt, ws.counters, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        // Rounds are enqueued one ahead of the host's reading (two mailboxes in turn): the device goes from round to round
+        // without waiting for the host, and the round enqueued behind the last one finds the forest complete and does
+        // nothing.
+        Mailbox mail[2] = {Mailbox(s), Mailbox(s)};
+        HIP_TRY(mail[0].open());
+        HIP_TRY(mail[1].open());
+        int max_rounds = 2;
+        for (int64_t t = 1; t < V; t *= 2) ++max_rounds;
+        int edges = 0, nrounds = 0;
+        auto publish = [&](int which) -> int {
+            HIP_TRY(slhc::forest_publish(f, true, reinterpret_cast<int32_t*>(mail[which].words()), (int32_t)mail[which].next(), s));
+            return SLHC_OK;
+        };
+        // Alg. "MST Algorithm": min edge per vertex, min edge per supervertex, label propagation, until a
+        // round adds no edge (the graph's components are then the forest's trees)
+        auto enqueue_round = [&](int which) -> int {
+            HIP_TRY(slhc::forest_csr_scan(offsets, indices, weights, (int)E, f, s));
+            HIP_TRY(slhc::forest_select_edges(f, s));
+            HIP_TRY(slhc::forest_commit(f, s));
+            HIP_TRY(slhc::forest_follow(f, false, s));
+            return publish(which);
+        };
+        auto read = [&](int which, int32_t* out) -> int {
+            HIP_TRY(mail[which].wait());
+            std::memcpy(out, mail[which].words() + 1, 8 * sizeof(int32_t));
+            return SLHC_OK;
+        };
+        int32_t h_cnt[8];
+        HIP_TRY(mail[0].fetch(ws.counters, 4, h_cnt));
         if (h_cnt[3] != 0) {
             set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", h_cnt[3]);
             return SLHC_INVALID_ARG;
         }
-        int edges = 0, nrounds = 0;
-        int max_rounds = 2;
-        for (int64_t t = 1; t < V; t *= 2) ++max_rounds;
-        // Alg. "MST Algorithm": min edge per vertex, min edge per supervertex, label propagation, until a
-        // round adds no edge (the graph's components are then the forest's trees)
-        while (edges < V - 1) {
-            if (nrounds >= max_rounds) { set_err("no steady state after %d rounds", max_rounds); return SLHC_INTERNAL; }
-            ++nrounds;
-            HIP_TRY(slhc::forest_round_reset(f, s));
-            HIP_TRY(slhc::forest_csr_scan(offsets, indices, weights, (int)E, f, s));
-            HIP_TRY(slhc::forest_select_edges(f, s));
-            HIP_TRY(slhc::forest_commit(f, s));
-            HIP_TRY(slhc::forest_jump(f, 32, false, s));
-            HIP_TRY(slhc::forest_jump(f, 32, true, s));
-            HIP_TRY(slhc::forest_relabel(f, true, s));
-            HIP_TRY(hipMemcpyAsync(h_cnt, ws.counters, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
-            if (h_cnt[2] != 0) {
-                // hook chains longer than the two device passes cover: finish them with the host in the loop
-                for (int jumps = 0; h_cnt[2] != 0; ++jumps) {
-                    if (jumps > 64) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
-                    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ws.counters + 2), 1);
-                    HIP_TRY(hipGetLastError());
-                    HIP_TRY(slhc::forest_jump(f, 32, true, s));
-                    HIP_TRY(hipMemcpyAsync(h_cnt, ws.counters, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                    HIP_TRY(hipStreamSynchronize(s));
-                    if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
+        if (V > 1) {
+            int rc2 = enqueue_round(0);
+            if (rc2 != SLHC_OK) return rc2;
+            for (int at = 0;; at ^= 1) {
+                rc2 = enqueue_round(at ^ 1);                     // the round after the one that is read now
+                if (rc2 != SLHC_OK) return rc2;
+                rc2 = read(at, h_cnt);
+                if (rc2 != SLHC_OK) return rc2;
+                if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
+                if (++nrounds > max_rounds) { set_err("no steady state after %d rounds", max_rounds); return SLHC_INTERNAL; }
+                if (h_cnt[2] != 0) {
+                    // hook chains longer than a launch follows: the round enqueued behind did nothing; finish the chains
+                    // with the host in the loop and take the round up again
+                    rc2 = read(at ^ 1, h_cnt);
+                    if (rc2 != SLHC_OK) return rc2;
+                    for (int jumps = 0; h_cnt[2] != 0; ++jumps) {
+                        if (jumps > 64) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
+                        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ws.counters + 2), 1);
+                        HIP_TRY(hipGetLastError());
+                        HIP_TRY(slhc::forest_jump(f, 32, true, s));
+                        HIP_TRY(mail[0].fetch(ws.counters, 8, h_cnt));
+                        if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
+                    }
+                    HIP_TRY(slhc::forest_follow(f, true, s));
+                    rc2 = publish(at);
+                    if (rc2 == SLHC_OK) rc2 = read(at, h_cnt);
+                    if (rc2 != SLHC_OK) return rc2;
+                    if (h_cnt[4] == 0) {
+                        rc2 = enqueue_round(at ^ 1);
+                        if (rc2 != SLHC_OK) return rc2;
+                    }
                 }
-                HIP_TRY(slhc::forest_relabel(f, false, s));
+                if (h_cnt[1] < edges || h_cnt[1] > V - 1) { set_err("round left %d edges (had %d)", h_cnt[1], edges); return SLHC_INTERNAL; }
+                edges = h_cnt[1];
+                if (h_cnt[4] != 0) break;                 // steady state: a spanning forest
             }
-            if (h_cnt[1] < edges || h_cnt[1] > V - 1) { set_err("round left %d edges (had %d)", h_cnt[1], edges); return SLHC_INTERNAL; }
-            if (h_cnt[1] == edges) break;                 // steady state: a spanning forest
-            edges = h_cnt[1];
         }
         if (edges > 0)
-            HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
-                                    ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, s));
+            HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
+                                    ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
         HIP_TRY(hipMemcpyAsync(colours, ws.colour, (size_t)V * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
         HIP_TRY(hipStreamSynchronize(s));
+        mail[0].box.idle();
+        mail[1].box.idle();
         *n_edges = edges;
         if (rounds) *rounds = nrounds;
         return SLHC_OK;
@@ -1668,23 +1827,26 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
 
     // ---- k-NN graph (Alg. "cuSLINK Algorithm", first step)
     EventPair ev_norm, ev_order, ev_knn, ev_conn;
-    HIP_TRY(ev_norm.create());
-    HIP_TRY(ev_order.create());
-    HIP_TRY(ev_knn.create());
-    HIP_TRY(ev_conn.create());
+    const bool timed = stats != nullptr || log.on;
+    if (timed) {
+        HIP_TRY(ev_norm.create());
+        HIP_TRY(ev_order.create());
+        HIP_TRY(ev_knn.create());
+        HIP_TRY(ev_conn.create());
+    }
     bool pruned = false;
     KnnWs kws(ws.knn_ws, N, d, with_order, k);   // half norms and row order are reused by the connection sweeps
-    rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, &ev_norm, &ev_order, &ev_knn);
+    rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, timed ? &ev_norm : nullptr, timed ? &ev_order : nullptr,
+                 timed ? &ev_knn : nullptr);
     if (rc != SLHC_OK) return rc;
-    // The pinned staging of the dendrogram pass is taken here, while the k-NN sweep runs: pinning 28 bytes per row
-    // takes the host 2 to 3 ms at a million rows, which would otherwise stand between the edge sort and the pass.
-    PinnedHost pin_edges;
-    HIP_TRY(pin_edges.alloc((7 * (size_t)(N - 1) + 16) * sizeof(int32_t)));
-    PinnedHost pin_surv;
-    HIP_TRY(pin_surv.alloc(64));
-    unsigned long long* h_surv = static_cast<unsigned long long*>(pin_surv.p);
-    HIP_TRY(hipMemcpyAsync(h_surv, kws.counters, 5 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    // The pinned staging of the dendrogram pass is taken here, while the k-NN sweep runs: where the pool has none,
+    // pinning 28 bytes per row takes the host 2 to 3 ms at a million rows.
+    PinnedHost pin_edges(s);
+    if (children) HIP_TRY(pin_edges.alloc((7 * (size_t)(N - 1) + 16) * sizeof(int32_t)));
+    Mailbox mail(s);
+    HIP_TRY(mail.open());
+    unsigned long long h_surv[8];
+    HIP_TRY(mail.fetch(kws.counters, 10, h_surv));
     if ((h_surv[4] & 2ull) != 0) { set_err("a work item of the k-NN sweep waited for its predecessor in vain"); return SLHC_INTERNAL; }
     if ((h_surv[4] & 0xffffffffull) != 0) { set_err("a row of X is not finite (NaN, infinity, or a squared norm beyond float32)"); return SLHC_NONFINITE; }
     st.knn_filter_survivors = (int64_t)h_surv[0];
@@ -1715,13 +1877,12 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     f.nbr_idx = ws.nbr_idx; f.nbr_dist = ws.nbr_dist;
     f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist;
     f.cand_w = ws.cand_w; f.cand_u = ws.cand_u; f.best_w = ws.best_w; f.best_e = ws.best_e;
-    f.min_lb = ws.min_lb; f.hook = ws.hook; f.qlist = ws.qlist; f.counters = ws.counters;
+    f.hook = ws.hook; f.qlist = ws.qlist; f.counters = ws.counters;
     f.e_lo = ws.e_lo; f.e_hi = ws.e_hi; f.e_w = ws.e_w;
-    HIP_TRY(slhc::forest_init(f, s));
-    PinnedHost pin_cnt;
-    HIP_TRY(pin_cnt.alloc(64));
-    int32_t* h_cnt = static_cast<int32_t*>(pin_cnt.p);
-    h_cnt[0] = h_cnt[1] = h_cnt[2] = h_cnt[3] = 0;
+    // few vertices: whole rounds in one launch (see k_forest_small), which stops where rows have to be queried
+    const bool small_forest = N <= slhc::FOREST_SMALL_MAX;
+    if (!small_forest) HIP_TRY(slhc::forest_init(f, s));
+    int32_t h_cnt[16] = {0};
     int edges = 0;
     int max_rounds = 2;
     for (int64_t t = 1; t < N; t *= 2) ++max_rounds;
@@ -1744,18 +1905,17 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     // of round r, so the counters that come back carry the edges committed so far, whether the hook
     // chains were followed to their end, and the number of rows the next round has to query.
     auto enqueue_scan = [&]() -> int {
-        HIP_TRY(slhc::forest_round_reset(f, s));
         HIP_TRY(slhc::forest_scan_lists(f, s));
         HIP_TRY(slhc::forest_classify(f, s));
         return SLHC_OK;
     };
     auto read_counters = [&]() -> int {
-        HIP_TRY(hipMemcpyAsync(h_cnt, ws.counters, 4 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(slhc::forest_publish(f, false, reinterpret_cast<int32_t*>(mail.words()), (int32_t)mail.next(), s));
+        HIP_TRY(mail.wait());
+        std::memcpy(h_cnt, mail.words() + 1, 8 * sizeof(int32_t));
         if (h_cnt[3] != 0) {
             // what the failed check saw (counters[16..22], written by the thread whose report came first)
-            HIP_TRY(hipMemcpyAsync(h_cnt + 8, ws.counters + 16, 7 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            HIP_TRY(mail.fetch(ws.counters + 16, 7, h_cnt + 8));
             set_err("forest state check %d failed in round %d (%s rounds, %d connection rounds): %d %d %d %d %d %d", h_cnt[3],
                     st.boruvka_rounds, pruned ? "pruned" : "every-tile", st.connect_rounds,
                     h_cnt[9], h_cnt[10], h_cnt[11], h_cnt[12], h_cnt[13], h_cnt[14]);
@@ -1763,14 +1923,29 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         }
         return SLHC_OK;
     };
-    rc = enqueue_scan();
-    if (rc != SLHC_OK) return rc;
+    if (small_forest) HIP_TRY(slhc::forest_small(f, true, s));
+    else {
+        rc = enqueue_scan();
+        if (rc != SLHC_OK) return rc;
+    }
+    bool conn_pending = false;
     for (;;) {
         rc = read_counters();
         if (rc != SLHC_OK) return rc;
-        if (st.boruvka_rounds > 0) {
+        if (conn_pending) {
+            conn_pending = false;
+            const float ms = ev_conn.ms();
+            st.ms_connect_kernels += ms;
+            ms_connect += ms;
+        }
+        if (small_forest) {
+            if (h_cnt[1] < edges || h_cnt[1] > N - 1 || (h_cnt[1] < N - 1 && h_cnt[0] == 0)) { set_err("rounds left %d edges (had %d)", h_cnt[1], edges); return SLHC_INTERNAL; }
+            edges = h_cnt[1];
+            st.boruvka_rounds = h_cnt[6] - 1;            // (counted again below)
+            if (edges == N - 1) { ++st.boruvka_rounds; break; }
+        } else if (st.boruvka_rounds > 0) {
             if (h_cnt[2] != 0) {
-                // a hook chain longer than the two device passes cover (a path of > 1000 components): finish
+                // a hook chain longer than one launch follows (64 hooks): finish
                 // it with the host in the loop, relabel, and scan again under the final colours
                 for (int jumps = 0; h_cnt[2] != 0; ++jumps) {
                     if (jumps > 64) { set_err("component hooks do not form a forest"); return SLHC_INTERNAL; }
@@ -1780,7 +1955,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     rc = read_counters();
                     if (rc != SLHC_OK) return rc;
                 }
-                HIP_TRY(slhc::forest_relabel(f, false, s));
+                HIP_TRY(slhc::forest_follow(f, true, s));
                 rc = enqueue_scan();
                 if (rc != SLHC_OK) return rc;
                 rc = read_counters();
@@ -1830,8 +2005,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(used), 1);
                     HIP_TRY(hipGetLastError());
                     HIP_TRY(slhc::order_count_used_tiles(o.qslot, o.Ns, used, o.tile_list, s));
-                    HIP_TRY(hipMemcpyAsync(h_cnt + 6, used, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                    HIP_TRY(hipStreamSynchronize(s));
+                    HIP_TRY(mail.fetch(used, 1, h_cnt + 6));
                     const int used_panels = h_cnt[6] > 0 ? h_cnt[6] : 1;
                     used_panels_round += used_panels;
                     int parts = SPLIT_ITEMS_TARGET / used_panels;
@@ -1889,7 +2063,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 const int study_panels = (kws.order.Ns + 127) / 128;
                 if (round_pruned) { HIP_TRY(hipMemsetAsync(study_steps, 0, (size_t)study_panels * 8, s)); p.panel_steps = study_steps; }
 #endif
-                HIP_TRY(hipEventRecord(ev_conn.a, s));
+                if (timed) HIP_TRY(hipEventRecord(ev_conn.a, s));
                 if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;
                     if (!kws.near_ready) {
@@ -1918,10 +2092,11 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 // keys_a / keys_b are free until the edge sort (the two-phase split above keeps its row lists in keys_a,
                 // in pruned rounds only)
                 HIP_TRY(slhc::launch_segmented_cross_1nn(p, round_pruned ? ws.keys_b : ws.keys_a, s));
-                HIP_TRY(hipEventRecord(ev_conn.b, s));
+                if (timed) HIP_TRY(hipEventRecord(ev_conn.b, s));
                 HIP_TRY(slhc::forest_apply_queries(f, rows, ws.q_idx, ws.q_dist, n, round_pruned ? ws.vals_a : nullptr, s));
-                HIP_TRY(hipMemcpyAsync(h_cnt + 7, ws.counters + 3, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                HIP_TRY(hipStreamSynchronize(s));
+                // (every-tile rounds leave the check to the next reading of the counters)
+                h_cnt[7] = 0;
+                if (round_pruned) HIP_TRY(mail.fetch(ws.counters + 3, 1, h_cnt + 7));
                 if (h_cnt[7] == 14) {
                     // an answer inside the query's own component: say what the sweep was given
                     HIP_TRY(hipMemcpy(h_cnt + 8, ws.counters + 16, 7 * sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -1957,7 +2132,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     for (int r = 0; r < 12; ++r) { const int i = order_[(size_t)r]; std::fprintf(stderr, "[study]   panel %d: steps %d kcycles %d\n", i, hs[(size_t)i], hs[(size_t)study_panels + i]); }
                 }
 #endif
-                ms_round_kernels += ev_conn.ms();
+                if (timed && round_pruned) ms_round_kernels += ev_conn.ms();
                 return SLHC_OK;
             };
             int queried = nq;
@@ -1977,16 +2152,14 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(counts), 3);
                 HIP_TRY(hipGetLastError());
                 HIP_TRY(slhc::forest_split_queries(f, ws.qlist, nq, kws.order.inv, TWO_PHASE_STRIDE, part_a, part_b, counts, s));
-                HIP_TRY(hipMemcpyAsync(h_cnt + 4, counts, 2 * sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                HIP_TRY(hipStreamSynchronize(s));
+                HIP_TRY(mail.fetch(counts, 2, h_cnt + 4));
                 const int na = h_cnt[4], nb = h_cnt[5];
                 if (na < 0 || nb < 0 || na + nb != nq) { set_err("query split lost rows (%d + %d of %d)", na, nb, nq); return SLHC_INTERNAL; }
                 if (na > 0) { const int rc = sweep_rows(part_a, na); if (rc != SLHC_OK) return rc; }
                 int nb_left = 0;
                 if (nb > 0) {
                     HIP_TRY(slhc::forest_still_needed(f, part_b, nb, ws.qlist, counts + 2, s));
-                    HIP_TRY(hipMemcpyAsync(h_cnt + 4, counts + 2, sizeof(int32_t), hipMemcpyDeviceToHost, s));
-                    HIP_TRY(hipStreamSynchronize(s));
+                    HIP_TRY(mail.fetch(counts + 2, 1, h_cnt + 4));
                     nb_left = h_cnt[4];
                     if (nb_left < 0 || nb_left > nb) { set_err("query re-filter kept %d of %d rows", nb_left, nb); return SLHC_INTERNAL; }
                     if (nb_left > 0) { const int rc = sweep_rows(ws.qlist, nb_left); if (rc != SLHC_OK) return rc; }
@@ -1997,10 +2170,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if (rc != SLHC_OK) return rc;
             }
             st.connect_query_rows += queried;
-            if (round_pruned) HIP_TRY(hipMemcpyAsync(h_surv, kws.counters, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
+            if (round_pruned) HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
+            else conn_pending = timed;          // one sweep: its time is read when the next counters have arrived
             st.ms_connect_kernels += ms_round_kernels;
-            ms_connect += now_ms() - tc0;
+            if (round_pruned) ms_connect += now_ms() - tc0;
             if (round_pruned) {
                 // Did skipping pay?  A pruned tile step costs more than an every-tile one (queries
                 // stay aligned with tiles, so panels are partly empty, and the surviving tiles are
@@ -2015,22 +2188,19 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if ((int64_t)nq * 8 >= N && steps * 3 > every) connect_pruned = false;
             }
             if (log.on) {
-                HIP_TRY(hipMemcpyAsync(h_surv, kws.counters, 4 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-                HIP_TRY(hipStreamSynchronize(s));
+                HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
                 log.mark("round %d: %d components, %d of %d listed rows queried, sweeps %.2f ms, %llu tile steps so far",
                          st.boruvka_rounds, (int)(N - edges), queried, nq, ms_round_kernels, h_surv[3]);
             }
         }
+        if (small_forest) { HIP_TRY(slhc::forest_small(f, false, s)); continue; }
         HIP_TRY(slhc::forest_select_edges(f, s));
         HIP_TRY(slhc::forest_commit(f, s));
-        HIP_TRY(slhc::forest_jump(f, 32, false, s));          // hooks -> new roots
-        HIP_TRY(slhc::forest_jump(f, 32, true, s));
-        HIP_TRY(slhc::forest_relabel(f, true, s));
+        HIP_TRY(slhc::forest_follow(f, false, s));            // hooks -> new colours
         rc = enqueue_scan();                                  // next round's scan; its counters are read at the top
         if (rc != SLHC_OK) return rc;
     }
-    HIP_TRY(hipMemcpyAsync(h_surv, kws.counters, 5 * sizeof(unsigned long long), hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    HIP_TRY(mail.fetch(kws.counters, 10, h_surv));
     if ((h_surv[4] & 2ull) != 0) { set_err("a work item of a connection sweep waited for its predecessor in vain"); return SLHC_INTERNAL; }
 #ifdef SLHC_PHASE_TIMERS
     if (log.on) {
@@ -2053,81 +2223,73 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     st.ms_boruvka = (float)(t_forest - t_knn - ms_connect);
 
     // ---- sort by weight (Sec. 3.3.1), then the sequential relabelling on the host
-    HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, (int)(N - 1), ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
-                            ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, s));
-    HIP_TRY(hipMemcpyAsync(heights, mst_w, (size_t)(N - 1) * sizeof(float), hipMemcpyDeviceToDevice, s));
-    HIP_TRY(hipStreamSynchronize(s));
-    const double t_sort = now_ms();
-    st.ms_sort = (float)(t_sort - t_forest);
-
     const size_t E = (size_t)(N - 1);
     // Large trees: all but the heaviest sixteenth of the edges are grouped by the component they lie in when
     // only those edges are there (labels on the device, a stable sort by label), and host threads share the
     // groups; see build_dendrogram_parallel.  The arrays of the forest rounds are free by now.
     const int threads = host_threads();
-    int64_t R = 0;
-    uint32_t* key_sorted = reinterpret_cast<uint32_t*>(ws.ptr);
-    uint32_t* listed = reinterpret_cast<uint32_t*>(ws.hook);
-    int32_t* glo = ws.qlist;
-    int32_t* ghi = ws.cand_u;
-    if (N >= DENDROGRAM_THREADS_MIN_ROWS && threads >= 2) {
-        const int64_t heavy = (int64_t)E / 16 > 4096 ? (int64_t)E / 16 : 4096;
-        R = (int64_t)E - heavy;
-        int32_t* changed = ws.counters + 8;
-        int32_t* h_changed = reinterpret_cast<int32_t*>(h_surv + 7);      // last word of the 64-byte staging buffer
-        bool settled = false;
-        for (int pass = 0; pass < 64 && !settled; ++pass) {
-            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(changed), 1);
-            HIP_TRY(hipGetLastError());
-            HIP_TRY(slhc::prefix_forest_pass(mst_src, mst_dst, (int)R, (int)N, ws.colour, changed, pass == 0, s));
-            HIP_TRY(hipMemcpyAsync(h_changed, changed, 4, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipStreamSynchronize(s));
-            settled = *h_changed == 0;
-        }
-        if (settled) {
-            HIP_TRY(slhc::prefix_forest_keys(mst_src, ws.colour, (int)R, (int)N, ws.vals_a, ws.vals_b, s));
-            HIP_TRY(slhc::pair_sort_u32(ws.vals_a, key_sorted, ws.vals_b, listed, (int)R, bits_for(N), ws.sort_temp,
-                                        ws.sort_temp_bytes, s));
-            HIP_TRY(slhc::prefix_forest_gather(mst_src, mst_dst, listed, (int)R, glo, ghi, s));
-        } else {
-            R = 0;
-        }
-    }
+    const bool grouped = children && N >= DENDROGRAM_THREADS_MIN_ROWS && threads >= 2;
+    const int64_t heavy = (int64_t)E / 16 > 4096 ? (int64_t)E / 16 : 4096;
+    int64_t R = grouped ? (int64_t)E - heavy : 0;
     // host staging: end points (grouped part in list order, then the rest in edge order), keys and merge numbers
-    // of the grouped part, children and sizes in the same two parts
-    const size_t Rz = (size_t)R, Tz = E - Rz;
+    // of the grouped part, children and sizes in the same two parts.  Kernels write and read it in place.
     int32_t* h_lo = static_cast<int32_t*>(pin_edges.p);     // [R] grouped, [E - R] rest (5 E + 2 R words in all)
     int32_t* h_hi = h_lo + E;
     int32_t* h_children = h_hi + E;                         // 2E entries, same two parts
     int32_t* h_sizes = h_children + 2 * E;
     uint32_t* h_key = reinterpret_cast<uint32_t*>(h_sizes + E);
-    uint32_t* h_ids = h_key + Rz;
-    if (Rz) {
-        HIP_TRY(hipMemcpyAsync(h_lo, glo, Rz * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(h_hi, ghi, Rz * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(h_key, key_sorted, Rz * 4, hipMemcpyDeviceToHost, s));
-        HIP_TRY(hipMemcpyAsync(h_ids, listed, Rz * 4, hipMemcpyDeviceToHost, s));
+    uint32_t* h_ids = h_key + R;
+    slhc::EdgeCopies copies{};
+    copies.heights = heights;
+    if (children) { copies.host_lo = h_lo; copies.host_hi = h_hi; copies.from = (int)R; }
+    HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, (int)(N - 1), (int)N, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
+                            ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, copies, s));
+    if (!children) {                                        // (the pivots' tree: its edges are all that is wanted)
+        mail.box.idle();
+        return SLHC_OK;
     }
-    HIP_TRY(hipMemcpyAsync(h_lo + Rz, mst_src + Rz, Tz * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipMemcpyAsync(h_hi + Rz, mst_dst + Rz, Tz * 4, hipMemcpyDeviceToHost, s));
-    HIP_TRY(hipStreamSynchronize(s));
+    uint32_t* key_sorted = reinterpret_cast<uint32_t*>(ws.ptr);
+    uint32_t* listed = reinterpret_cast<uint32_t*>(ws.hook);
+    double t_sort = t_forest;
+    if (grouped) {
+        int32_t* changed = ws.counters + 8;
+        int32_t h_changed = 0;
+        bool settled = false;
+        for (int pass = 0; pass < 64 && !settled; ++pass) {
+            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(changed), 1);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(slhc::prefix_forest_pass(mst_src, mst_dst, (int)R, (int)N, ws.colour, changed, pass == 0, s));
+            HIP_TRY(mail.fetch(changed, 1, &h_changed));
+            if (pass == 0) t_sort = now_ms();
+            settled = h_changed == 0;
+        }
+        if (!settled) {                                     // (never seen) the sequential pass on all edges
+            HIP_TRY(hipMemcpyAsync(h_lo, mst_src, E * 4, hipMemcpyDeviceToHost, s));
+            HIP_TRY(hipMemcpyAsync(h_hi, mst_dst, E * 4, hipMemcpyDeviceToHost, s));
+            R = 0;
+        } else {
+        HIP_TRY(slhc::prefix_forest_keys(mst_src, ws.colour, (int)R, (int)N, ws.vals_a, ws.vals_b, s));
+        HIP_TRY(slhc::pair_sort_u32(ws.vals_a, key_sorted, ws.vals_b, listed, (int)R, bits_for(N), ws.sort_temp,
+                                    ws.sort_temp_bytes, s));
+        HIP_TRY(slhc::prefix_forest_gather(mst_src, mst_dst, listed, key_sorted, (int)R, h_lo, h_hi, h_key, h_ids, s));
+        }
+    }
+    HIP_TRY(hipGetLastError());
+    HIP_TRY(mail.fetch(ws.counters, 1, h_cnt));             // everything staged is in host memory
+    if (!grouped) t_sort = now_ms();
+    st.ms_sort = (float)(t_sort - t_forest);
+    const size_t Rz = (size_t)R;
     log.mark("dendrogram: %zu edges staged on the host (%lld grouped for %d threads)", E, (long long)R, threads);
     const bool good = Rz ? build_dendrogram_parallel(N, R, h_key, h_lo, h_hi, h_ids, h_children, h_sizes, h_lo + Rz, h_hi + Rz,
                                                      h_children + 2 * Rz, h_sizes + Rz, threads)
                          : build_dendrogram(h_lo, h_hi, N, h_children, h_sizes);
     if (!good) { set_err("dendrogram: an edge of the sorted tree has an end point outside [0, N)"); return SLHC_INTERNAL; }
     log.mark("dendrogram: union-find");
-    if (Rz) {
-        // the grouped part goes back to edge order on the device (the sort's scratch arrays are free again)
-        int32_t* cj = reinterpret_cast<int32_t*>(ws.keys_a);            // 2R words of the N 64-bit words
-        int32_t* sj = reinterpret_cast<int32_t*>(ws.vals_a);
-        HIP_TRY(hipMemcpyAsync(cj, h_children, Rz * 8, hipMemcpyHostToDevice, s));
-        HIP_TRY(hipMemcpyAsync(sj, h_sizes, Rz * 4, hipMemcpyHostToDevice, s));
-        HIP_TRY(slhc::prefix_forest_scatter(listed, cj, sj, (int)R, children, sizes, s));
-    }
-    HIP_TRY(hipMemcpyAsync(children + 2 * Rz, h_children + 2 * Rz, Tz * 8, hipMemcpyHostToDevice, s));
-    HIP_TRY(hipMemcpyAsync(sizes + Rz, h_sizes + Rz, Tz * 4, hipMemcpyHostToDevice, s));
+    // (the grouped part goes back to edge order on the device)
+    HIP_TRY(slhc::linkage_upload(listed, h_children, h_sizes, (int)R, (int)E, children, sizes, s));
     HIP_TRY(hipStreamSynchronize(s));
+    pin_edges.idle();
+    mail.box.idle();
     const double t_end = now_ms();
     st.ms_dendrogram = (float)(t_end - t_sort);
     st.ms_total = (float)(t_end - t_begin);
