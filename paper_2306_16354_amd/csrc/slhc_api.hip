@@ -1718,13 +1718,13 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
     });
 }
 
-static int flat_clusters_layout(void* ws, int64_t N, int32_t** above, int32_t** flag, int32_t** rank, void** temp,
+static int flat_clusters_layout(void* ws, int64_t N, int32_t** above, int32_t** rank, void** temp,
                                 size_t* temp_bytes, size_t* total)
 {
     Carver c(ws);
     const size_t nodes = 2 * (size_t)N;
     *above = c.take<int32_t>(nodes);
-    *flag = c.take<int32_t>(nodes);
+    (void)c.take<int32_t>(nodes);          // (unused; the size that callers know)
     *rank = c.take<int32_t>(nodes);
     *temp_bytes = slhc::flat_clusters_scan_temp_bytes((int)N);
     *temp = c.take<unsigned char>(*temp_bytes);
@@ -1738,8 +1738,8 @@ int slhc_flat_clusters_workspace_bytes(int64_t N, size_t* bytes)
         if (!bytes) { set_err("bytes is NULL"); return SLHC_INVALID_ARG; }
         if (N < 2) { set_err("need N >= 2 (N=%lld)", (long long)N); return SLHC_INVALID_ARG; }
         if (N > 1073741823LL) { set_err("2N exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
-        int32_t *a, *f, *r; void* t; size_t tb;
-        return flat_clusters_layout(nullptr, N, &a, &f, &r, &t, &tb, bytes);
+        int32_t *a, *r; void* t; size_t tb;
+        return flat_clusters_layout(nullptr, N, &a, &r, &t, &tb, bytes);
     });
 }
 
@@ -1751,10 +1751,10 @@ int slhc_flat_clusters(const int32_t* children, int64_t N, int64_t n_clusters, i
         if (N < 2) { set_err("need N >= 2 (N=%lld)", (long long)N); return SLHC_INVALID_ARG; }
         if (N > 1073741823LL) { set_err("2N exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
         if (n_clusters < 1 || n_clusters > N) { set_err("need 1 <= n_clusters <= N (n_clusters=%lld)", (long long)n_clusters); return SLHC_INVALID_ARG; }
-        int32_t *above, *flag, *rank; void* temp; size_t temp_bytes, total;
-        flat_clusters_layout(workspace, N, &above, &flag, &rank, &temp, &temp_bytes, &total);
+        int32_t *above, *rank; void* temp; size_t temp_bytes, total;
+        flat_clusters_layout(workspace, N, &above, &rank, &temp, &temp_bytes, &total);
         if (workspace_bytes < total) { set_err("workspace %zu < %zu bytes", workspace_bytes, total); return SLHC_WORKSPACE_TOO_SMALL; }
-        HIP_TRY(slhc::flat_clusters(children, (int)N, (int)n_clusters, labels, above, flag, rank, temp, temp_bytes,
+        HIP_TRY(slhc::flat_clusters(children, (int)N, (int)n_clusters, labels, above, rank, temp, temp_bytes,
                                     static_cast<hipStream_t>(stream)));
         return SLHC_OK;
     });
