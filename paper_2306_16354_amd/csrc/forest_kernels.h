@@ -14,8 +14,11 @@ struct ForestState {
     const float* nbr_dist;       // [N, k]
     int32_t* colour;             // [N]
     int32_t* ptr;                // [N] entries before ptr[v] are known to share v's colour
-    int32_t* ext_idx;            // [N] last cross-component 1-NN answer of v (-1: none yet)
+    // what the last cross-component query of v left: a row it reaches (-1: none) and its distance.  ext_low +inf: that row
+    // is v's nearest foreign one (or, without a row, ext_dist a lower bound); else a lower bound on the nearest
+    int32_t* ext_idx;            // [N]
     float* ext_dist;             // [N]
+    float* ext_low;              // [N]
     float* cand_w;               // [N] weight of v's lightest outgoing edge, or a lower bound
     int32_t* cand_u;             // [N] its other endpoint, or -1 when only the bound is known
     uint32_t* best_w;            // [N] per component: min weight bits over exact candidates
@@ -36,9 +39,10 @@ hipError_t forest_scan_lists(const ForestState& f, hipStream_t s);
 hipError_t forest_classify(const ForestState& f, hipStream_t s);
 // qrows[q] is the vertex query q was made for (f.qlist, or a reordered copy of it).  `thresholds`
 // (or nullptr): the per-component thresholds the sweep ran under (SweepParams::comp_best); answers
-// farther than their component's threshold are kept as lower bounds only.
+// farther than their component's threshold are kept as a lower bound and an edge.  `q_low` (or nullptr): distances
+// below which a query has no foreign row.
 hipError_t forest_apply_queries(const ForestState& f, const int32_t* qrows, const int32_t* q_idx,
-                                const float* q_dist, int nq, const uint32_t* thresholds, hipStream_t s);
+                                const float* q_dist, const float* q_low, int nq, const uint32_t* thresholds, hipStream_t s);
 // Two-phase connection sweeps (n > 0): rows of `list` in every `stride`-th 128-row panel of the row
 // order (inv[v] = position of row v) go to part_a, the others to part_b; counts[0], counts[1] (zeroed by
 // the caller) receive the part sizes.  forest_still_needed keeps the rows of `list` that the test of

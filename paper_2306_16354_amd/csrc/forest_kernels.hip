@@ -22,6 +22,7 @@
 #include <rocprim/rocprim.hpp>
 #include <stdint.h>
 #include "forest_kernels.h"
+#include "wave_ops.h"
 
 namespace slhc {
 
@@ -45,69 +46,6 @@ __device__ inline void report_with(const ForestState& f, int site, int a, int b,
     }
 }
 
-// atomicMin that first looks: the per-component minima only decrease, so a value that does not beat
-// what is already there never needs the atomic (a stale, larger value read here only costs an atomic).  In late rounds one component holds most vertices and
-// unfiltered atomics on its single word serialise (measured 6 ms per round at N = 1M).
-__device__ inline void min_into(uint32_t* slot, uint32_t v)
-{
-    if (v < *reinterpret_cast<volatile uint32_t*>(slot)) atomicMin(slot, v);
-}
-__device__ inline void min_into(unsigned long long* slot, unsigned long long v)
-{
-    if (v < *reinterpret_cast<volatile unsigned long long*>(slot)) atomicMin(slot, v);
-}
-
-// Minimum of `v` over the lanes that share a component, one atomic per component and wavefront.  In the
-// late rounds most vertices belong to a few large components, and one atomic per vertex on those few
-// words serialises (measured: 0.7 ms for one kernel at N = 1M).  The first two distinct colours of the
-// wavefront are reduced across lanes; lanes of any further colour fall back to their own atomic, so a
-// wavefront of 64 different colours (the first round) costs two short passes, not 64.
-__device__ inline void wave_min_into(uint32_t* slots, int c, uint32_t v, bool active)
-{
-    const int lane = threadIdx.x & 63;
-    unsigned long long todo = __ballot(active);
-#pragma unroll 1
-    for (int pass = 0; pass < 2 && todo; ++pass) {
-        const int leader = __builtin_ctzll(todo);
-        const int c0 = __shfl(c, leader);
-        const bool mine = active && c == c0;
-        uint32_t m = mine ? v : 0xffffffffu;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const uint32_t other = (uint32_t)__shfl_xor((int)m, o);
-            m = other < m ? other : m;
-        }
-        if (lane == leader) min_into(&slots[c0], m);
-        const unsigned long long served = __ballot(mine);
-        todo &= ~served;
-        active = active && !mine;
-    }
-    if (active) min_into(&slots[c], v);
-}
-
-// Slot of this thread among the threads of the grid that pass `mine`, behind *counter: one atomic per
-// workgroup (per-vertex or per-wavefront atomics on the one counter word serialise: 15 600 of them took
-// 0.18 ms at N = 1M).  Every thread of the workgroup must call it.
-template <int THREADS>
-__device__ inline int block_append(bool mine, int32_t* counter)
-{
-    __shared__ int wave_count[THREADS / 64];
-    __shared__ int wave_base[THREADS / 64];
-    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-    const unsigned long long mask = __ballot(mine);
-    if (lane == 0) wave_count[wave] = __popcll(mask);
-    __syncthreads();
-    if (threadIdx.x == 0) {
-        int total = 0;
-        for (int w = 0; w < THREADS / 64; ++w) { wave_base[w] = total; total += wave_count[w]; }
-        const int base = total > 0 ? atomicAdd(counter, total) : 0;
-        for (int w = 0; w < THREADS / 64; ++w) wave_base[w] += base;
-    }
-    __syncthreads();
-    const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
-    return mine ? wave_base[wave] + pre : -1;
-}
-
 // Rounds may be enqueued ahead of the host's reading: they do nothing once the forest is complete (counters[4], set by
 // k_publish) or while a hook chain of an earlier round waits for the host (counters[2]).
 __device__ inline bool forest_halted(const ForestState& f) { return (f.counters[2] | f.counters[4]) != 0; }
@@ -121,6 +59,7 @@ __global__ void __launch_bounds__(TB) k_forest_init(ForestState f)
     f.ptr[v] = 0;
     f.ext_idx[v] = -1;
     f.ext_dist[v] = 0.f;
+    f.ext_low[v] = __builtin_inff();
     f.best_w[v] = INF_BITS;
     f.best_e[v] = ~0ull;
 }
@@ -181,21 +120,25 @@ __global__ void __launch_bounds__(TB) k_scan_lists(ForestState f)
         } else {
             f.ptr[v] = f.k;
             const int eu = f.ext_idx[v];
-            const float ed = f.ext_dist[v];
+            const float ed = f.ext_dist[v], el = f.ext_low[v];
+            const bool edge = eu >= 0 && eu < f.N && f.colour[eu] != c;
             if (eu >= f.N) report(f, 3);
-            else if (eu >= 0 && f.colour[eu] != c) {      // cached answer still leads out of the component
+            else if (edge && !(el < __builtin_inff())) {      // cached answer still leads out of the component
                 f.cand_w[v] = ed;
                 f.cand_u[v] = eu;
                 wbits = __float_as_uint(ed);
                 exact = true;
             } else {
                 // lower bounds on v's nearest foreign point: its k-th list distance, and whatever the last
-                // cross-component query left in ext_dist (an exact answer that has since joined v's
-                // component, or the component threshold a truncated search was run under; 0 when never queried)
+                // cross-component query left (an exact answer that has since joined v's component, or what a
+                // truncated search knows; 0 when never queried)
                 float lb = f.nbr_dist[(size_t)v * f.k + f.k - 1];
-                if (ed > lb) lb = ed;
+                lb = fmaxf(lb, fminf(ed, el));
                 f.cand_w[v] = lb;
                 f.cand_u[v] = -1;
+                // an edge out of the component that need not be v's lightest still bounds the component's lightest; a
+                // component whose bound it stays will query v, whose own bound is not above it
+                if (edge) { wbits = __float_as_uint(ed); exact = true; }
             }
         }
     }
@@ -230,9 +173,10 @@ __global__ void __launch_bounds__(TB_WIDE) k_classify(ForestState f)
 // learns that no foreign row is nearer than F: it keeps no candidate, and F becomes its lower bound for the
 // following rounds (components only grow).  F = min(start value, lightest edge from a queried row of the
 // component to a foreign row) does not depend on the order in which the panels ran.
+// Such a query's answer, if it has one, is an edge all the same.
 __global__ void __launch_bounds__(TB) k_apply_queries(ForestState f, const int32_t* __restrict__ qrows,
                                                       const int32_t* __restrict__ q_idx,
-                                                      const float* __restrict__ q_dist, int nq,
+                                                      const float* __restrict__ q_dist, const float* __restrict__ q_low, int nq,
                                                       const uint32_t* __restrict__ thresholds)
 {
     const int q = blockIdx.x * TB + threadIdx.x;
@@ -252,18 +196,21 @@ __global__ void __launch_bounds__(TB) k_apply_queries(ForestState f, const int32
             if (thresholds) {
                 const uint32_t fb = thresholds[c];
                 if (!(u >= 0 && __float_as_uint(w) <= fb)) {
-                    const float F = __uint_as_float(fb);
-                    const float old = f.ext_dist[v];
-                    f.ext_idx[v] = -1;
-                    f.ext_dist[v] = F > old ? F : old;
+                    float low = fmaxf(__uint_as_float(fb), fminf(f.ext_dist[v], f.ext_low[v]));
+                    if (q_low && q_low[q] < __builtin_inff()) low = fmaxf(low, q_low[q]);
+                    const bool edge = u >= 0 && low < __builtin_inff();
+                    f.ext_idx[v] = edge ? u : -1;
+                    f.ext_dist[v] = edge ? w : low;
+                    f.ext_low[v] = edge ? low : __builtin_inff();
                     f.cand_u[v] = -1;
-                    f.cand_w[v] = F;
+                    f.cand_w[v] = low;
                     exact = false;
                 }
             }
             if (exact) {
                 f.ext_idx[v] = u;
                 f.ext_dist[v] = w;
+                f.ext_low[v] = __builtin_inff();
                 f.cand_u[v] = u;
                 f.cand_w[v] = w;
                 found = u >= 0;
@@ -483,7 +430,7 @@ __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
     for (int v = tid; v < N; v += 1024) {
         if (stage == 0) {
             col[v] = (unsigned short)v;
-            f.ptr[v] = 0; f.ext_idx[v] = -1; f.ext_dist[v] = 0.f;
+            f.ptr[v] = 0; f.ext_idx[v] = -1; f.ext_dist[v] = 0.f; f.ext_low[v] = __builtin_inff();
         } else {
             const int c = f.colour[v];
             col[v] = (unsigned short)(in_range(c, N) ? c : 0);
@@ -510,14 +457,16 @@ __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
                     if (col[u] != c) { found = e; break; }
                 }
                 bool exact = true;
+                float reach = INFINITY;              // an edge that need not be v's lightest (see k_scan_lists)
                 if (found >= 0) w = f.nbr_dist[(size_t)v * f.k + found];
                 else {
                     const int eu = f.ext_idx[v];
-                    const float ed = f.ext_dist[v];
-                    if (eu >= 0 && eu < N && col[eu] != c) { w = ed; u = eu; }
+                    const float ed = f.ext_dist[v], el = f.ext_low[v];
+                    const bool edge = eu >= 0 && eu < N && col[eu] != c;
+                    if (edge && !(el < INFINITY)) { w = ed; u = eu; }
                     else {
-                        w = f.nbr_dist[(size_t)v * f.k + f.k - 1];
-                        if (ed > w) w = ed;
+                        w = fmaxf(f.nbr_dist[(size_t)v * f.k + f.k - 1], fminf(ed, el));
+                        if (edge) reach = ed;
                         u = -1;
                         exact = false;
                     }
@@ -525,7 +474,8 @@ __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
                 f.ptr[v] = found >= 0 ? found : f.k;
                 f.cand_w[v] = w;
                 f.cand_u[v] = u;
-                if (exact) atomicMin(&bw[c], __float_as_uint(w));
+                if (exact) reach = w;
+                if (reach < INFINITY) atomicMin(&bw[c], __float_as_uint(reach));
             }
             __syncthreads();
             for (int v = tid; v < N; v += 1024)
@@ -700,10 +650,10 @@ hipError_t forest_classify(const ForestState& f, hipStream_t s)
     return hipGetLastError();
 }
 
-hipError_t forest_apply_queries(const ForestState& f, const int32_t* qrows, const int32_t* q_idx,
-                                const float* q_dist, int nq, const uint32_t* thresholds, hipStream_t s)
+hipError_t forest_apply_queries(const ForestState& f, const int32_t* qrows, const int32_t* q_idx, const float* q_dist,
+                                const float* q_low, int nq, const uint32_t* thresholds, hipStream_t s)
 {
-    LAUNCH1(k_apply_queries, nq, s, f, qrows, q_idx, q_dist, nq, thresholds);
+    LAUNCH1(k_apply_queries, nq, s, f, qrows, q_idx, q_dist, q_low, nq, thresholds);
 }
 
 hipError_t forest_split_queries(const ForestState& f, const int32_t* list, int n, const int32_t* inv, int stride,

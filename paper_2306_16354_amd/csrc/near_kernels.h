@@ -11,18 +11,23 @@ namespace slhc {
 struct NearScale {
     float scale;
     unsigned int eps_bits;
-    float spare[2];
+    unsigned int huge;         // not 0: some row has values beyond float16
+    float spare;
 };
 
 // The rows of a matrix rounded to float16, in tiles of 128 in the order the matrix instruction reads them.
-// Position p of the copy holds row (p % 128) * tiles + p / 128, so every tile is an even sample of the rows.
+// Position p of the copy holds row (p % 128) * tiles + p / 128, so every tile is an even sample of the rows; with
+// `in_order` it holds row p.
 struct NearCopy {
     unsigned char* frag;       // [tiles][steps of 16 columns][4 blocks of 32 rows][64 lanes][16 bytes]
     float* negh;               // [tiles * 128] minus the half norm; -inf: no such row, +inf: values beyond float16
+    float* negh_best;          // [tiles * 128] or nullptr: the same with -inf for the latter (candidates of 1-NN searches)
     int32_t* colour;           // [tiles * 128] or nullptr
     uint32_t* best;            // [tiles * 128] or nullptr: scratch of 1-NN searches for these rows as queries,
-    int32_t* count;            // and the same; near_make clears both
+    int32_t* count;            // and the same; near_make clears all
+    unsigned long long* best_at;    // likewise: largest product value and where (near_link)
     bool finite_padding;       // -1e38 instead of -inf (near_assign)
+    bool in_order;
     int rows, tiles;
 };
 
@@ -36,7 +41,7 @@ struct NearBuffers {           // scratch of one call
     float* shift;              // [d]
     float* partial;            // near_stats_scratch_floats(d)
     unsigned char* batch; size_t batch_bytes;     // bounds, group maxima, entries and counts of one batch of queries
-    int32_t* todo;             // [2 + panels of 128 queries]: count, spare, panels left to the list kernels
+    int32_t* todo;             // [2 + panels of 128 queries]: count, queries left by near_link, panels left to the list kernels
     int32_t* todo_mark;        // [panels]
     long long todo_panels;
 };
@@ -61,16 +66,30 @@ bool near_supported(int d);
 // (clears `clear` [clear_words], optional, on the way)
 hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s);
 // fills `out` from rows (clear_todo: and clears the panels left to the list kernels, as near_stats does)
-// `rows` (nullptr: 0 .. n-1 of a matrix with n_src rows); hn / nonfinite (optional): the float32
+// `rows` (nullptr: 0 .. n-1 of a matrix with n_src rows; n_dev: only the first *n_dev of them); hn / nonfinite (optional): the float32
 // half norms by row and the flag of launch_half_norms; colour (optional): by row
 hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
-                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo = false);
+                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo = false,
+                     const int32_t* n_dev = nullptr);
 // the colours of the rows of `c` into c.colour
 hipError_t near_colours(const NearCopy& c, const int32_t* colour, hipStream_t s);
 // For every row of q the row of c with the (nearly) largest product value, i.e. a nearest row up to the rounding of the
 // copies, and the distance to that row: one pass.  best_at: [q.tiles * 128] words of scratch; c has finite padding.
 hipError_t near_assign(const NearCopy& q, const NearCopy& c, const float* Xq, const int32_t* q_rows, const float* Xc, int d,
                        const NearBuffers& b, unsigned long long* best_at, int32_t* out_idx, float* out_dist, hipStream_t s);
+// The queries of a connection round (1-NN among the rows of other colours, all of one matrix).  A component needs its
+// lightest outgoing edge only, so after one pass that leaves every query an interval for its distance, the component's
+// threshold falls to the smallest upper end of its queries, and only the queries whose lower end does not exceed it are
+// searched for and evaluated.  The others answer the row that their upper end belongs to.
+struct NearLink {
+    const float* X; int d, n_rows;
+    const int32_t* rows; int n;            // the queries
+    const int32_t* colour;                 // [n_rows]
+    uint32_t* threshold;                   // [n_rows] by colour, float bits: known outgoing edges, lowered here
+    int32_t* out_idx; float *out_dist, *out_low; int32_t* evaluated;     // [n]; out_low: the lower ends
+    int32_t *rows_left, *slot_left; float* bound_left;         // [n] scratch
+};
+hipError_t near_link(const NearLink& p, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s);
 hipError_t near_search(const NearProblem& p, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s);
 
 }  // namespace slhc

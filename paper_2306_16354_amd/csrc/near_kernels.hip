@@ -23,6 +23,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "near_kernels.h"
+#include "wave_ops.h"
 
 namespace slhc {
 
@@ -69,7 +70,7 @@ __device__ inline float near_bound_at(float t2, float h, const NearBoundArgs& a)
 }
 // From a product value some candidate shows: an upper bound of that candidate's distance (its squared norm n_c is at
 // most (|x_q| + D)^2 <= 1.25 n_q + 5 D^2), and from it the bound for all candidates that may be as near.
-__device__ inline float near_bound_from(float acc, float h, const NearBoundArgs& a)
+__device__ inline float near_distance_from(float acc, float h, const NearBoundArgs& a)
 {
     const float n = h / a.h_of_n;
     const float norm = __builtin_sqrtf(n);
@@ -78,8 +79,23 @@ __device__ inline float near_bound_from(float acc, float h, const NearBoundArgs&
     const float dd = __builtin_sqrtf(d2);
     const float rho_q = a.eps * norm + a.delta;
     const float rho_c = (a.eps * (norm + dd) + a.delta) * (1.f + 1e-3f);
-    const float t = (dd + rho_q + rho_c) * (1.f + 1e-6f);
+    return (dd + rho_q + rho_c) * (1.f + 1e-6f);
+}
+__device__ inline float near_bound_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float t = near_distance_from(acc, h, a);
     return near_bound_at(t * t * (1.f + a.gamma), h, a);
+}
+// near_bound_at the other way round: no row whose product value is `acc` at most is within this (scaled, squared) distance.
+__device__ inline float near_lower_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    const float rho_q = a.eps * norm + a.delta;
+    const float reach2 = 2.f * (n * (0.5f - 0.5f * a.nu - 0.5f * a.e - 2.4e-7f) * (1.f - 1e-6f) - acc) * (1.f - 4e-6f);
+    const float reach = __builtin_sqrtf(fmaxf(0.f, reach2)) * (1.f - 4e-6f);
+    const float t = (reach - rho_q - (a.eps * (norm + rho_q) + a.delta) * (1.f + 2e-3f)) / (1.f + a.eps * (1.f + 2e-3f)) * (1.f - 4e-6f);
+    return t > 0.f ? fmaxf(0.f, (t * t * (1.f - 4e-6f) - a.tiny) / (1.f + a.gamma) * (1.f - 4e-6f)) : 0.f;
 }
 
 __device__ inline NearBoundArgs near_args(const NearScale* sc, int steps, int d, float e, float nu)
@@ -151,7 +167,7 @@ __global__ void __launch_bounds__(256) near_runs_kernel(const float* __restrict_
     }
     if (g == 0 && c < cols) partial[(size_t)run * d + c0 + c] = mean;
     if (tid == 0) run_max[blockIdx.y * SAMPLE_RUNS + run] = i1 > i0 ? mx[0] : -1.f;
-    if (run == 0 && blockIdx.y == 0 && tid == 0) { sc->eps_bits = 0u; }
+    if (run == 0 && blockIdx.y == 0 && tid == 0) { sc->eps_bits = 0u; sc->huge = 0u; }
 }
 
 // the two middle values of 64 lanes' valid ones, averaged (0 valid: 0)
@@ -216,9 +232,10 @@ hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32
 // ---------------------------------------------------------------------------------------------- the float16 copy
 struct NearMake {
     const float* X; const int32_t* rows; const int32_t* colour; const float* shift; NearScale* sc;
-    unsigned char* frag; float* negh; int32_t* out_colour; float* hn; unsigned int* nonfinite;
-    int n_src, n, d, tiles, steps; float h_of_n, hn_scale, absent;
-    uint32_t* best; int32_t* count;
+    unsigned char* frag; float *negh, *negh_best; int32_t* out_colour; float* hn; unsigned int* nonfinite;
+    int n_src, n, d, tiles, steps, in_order; float h_of_n, hn_scale, absent;
+    const int32_t* n_dev;
+    uint32_t* best; int32_t* count; unsigned long long* best_at;
     int32_t* todo; long long todo_words;
 };
 
@@ -232,6 +249,8 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     __shared__ unsigned int eps_max;
     const int tid = threadIdx.x;
     const int t = blockIdx.x >> 2, blk = blockIdx.x & 3;
+    const int n_in = p.n_dev ? (*p.n_dev < p.n ? *p.n_dev : p.n) : p.n;
+    if (p.n_dev && t * TILE >= n_in) return;         // (copies of unknown length are in order)
     constexpr int ROWS = 256 / LPR;                  // rows side by side
     constexpr int PASSES = ROWS >= 32 ? 1 : 32 / ROWS;
     const int part = tid % LPR, sub = tid / LPR;
@@ -245,8 +264,9 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
         nn[i] = rr[i] = xx[i] = 0.f; huge[i] = false;
-        const long long at = (long long)(blk * 32 + sub + i * ROWS) * p.tiles + t;
-        long long row = mine && at < p.n ? (p.rows ? (long long)p.rows[at] : at) : -1;
+        const int in_tile = blk * 32 + sub + i * ROWS;
+        const long long at = p.in_order ? (long long)t * TILE + in_tile : (long long)in_tile * p.tiles + t;
+        long long row = mine && at < n_in ? (p.rows ? (long long)p.rows[at] : at) : -1;
         if (row >= p.n_src) row = -1;
         src[i] = row;
     }
@@ -311,8 +331,11 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
             if (hg) nh = INF;
             if (src[i] < 0 || !(x < INF)) nh = p.absent;         // no row, or one whose squared norm is not a finite float32
             p.negh[at] = nh;
+            if (p.negh_best) p.negh_best[at] = nh == INF ? p.absent : nh;
+            if (hg && src[i] >= 0) p.sc->huge = 1u;
             if (p.out_colour) p.out_colour[at] = src[i] >= 0 && p.colour ? p.colour[src[i]] : -1;
             if (p.best) p.best[at] = 0u;
+            if (p.best_at) p.best_at[at] = 0ull;
             if (p.count) p.count[at] = 0;
             if (src[i] >= 0) {
                 if (p.hn) p.hn[src[i]] = p.hn_scale * x;
@@ -333,13 +356,15 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
 bool near_supported(int d) { return d >= 1; }
 
 hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
-                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo)
+                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo, const int32_t* n_dev)
 {
+    if (n_dev && !out.in_order) return hipErrorInvalidValue;
     NearMake p{};
     p.X = X; p.rows = rows; p.colour = colour; p.shift = b.shift; p.sc = b.scale;
     p.frag = out.frag; p.negh = out.negh; p.out_colour = out.colour; p.hn = hn; p.nonfinite = nonfinite;
     p.n_src = n_src; p.n = n; p.d = d; p.tiles = out.tiles; p.steps = near_steps(d); p.h_of_n = 0.5f - 0.5f * near_nu(p.steps) - near_e(p.steps);
-    p.best = out.best; p.count = out.count;
+    p.best = out.best; p.count = out.count; p.best_at = out.best_at;
+    p.negh_best = out.negh_best; p.in_order = out.in_order; p.n_dev = n_dev;
     p.absent = out.finite_padding ? -1e38f : -INF;
     p.todo = b.todo; p.todo_words = clear_todo ? 2 + 2 * b.todo_panels : 0;
     p.hn_scale = 0.5f * (1.0f - (float)(d + 8) * 1.1920928955078125e-07f);         // as launch_half_norms
@@ -363,18 +388,22 @@ struct NearSweep {
     // item = panel * nseg + seg; seg takes tiles seg, seg + nseg, ... of a list of `used` candidate tiles: every
     // stride-th one (skip = 0), or all but those (skip = 1)
     int nseg, stride, used, skip;
+    // queries counted on the device (n_dev, over all batches): the panels that exist share `slots` workgroups in at most
+    // most_seg segments each
+    const int32_t* n_dev; int slots, most_seg;
     int nsub;                          // buffers per query: the lanes that hold its values, over all segments
     int kk;                            // candidates a query needs (itself included where it meets itself)
-    const float* bound;                // emit: [queries of the batch]
+    const float* bound;                // emit, nearest (or nullptr): [queries of the batch]
     float* maxima; int parts, groups;  // maxima: [nseg * parts][queries of the batch][groups], groups 32 or 8
     uint2* entries; int32_t* counts; int capl;      // emit: [queries of the batch][2 nseg][capl], [queries][2 nseg]
                                                     // nearest: [queries of the batch][capl], counts by position
-    unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position
+    unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position; block: likewise, the
+                                       // position of the first of the 16 values of a lane in a block of 32 candidates
     uint32_t* best;                    // nearest: largest product value of a query by position (ordered bits)
     int nq_batch;
 };
 
-enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_BEST = 2, NEAR_NEAREST = 3, NEAR_ARG = 4 };
+enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_BEST = 2, NEAR_NEAREST = 3, NEAR_ARG = 4, NEAR_BLOCK = 5 };
 
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
@@ -476,7 +505,8 @@ struct NearLane {
             const bool ok = live && fabsf(nh) < INF;
             bound[qb] = NEVER;
             if (MODE == NEAR_EMIT && ok) bound[qb] = p.bound[lq[qb]];
-            if (MODE == NEAR_NEAREST && ok) {
+            if (MODE == NEAR_NEAREST && ok && p.bound) bound[qb] = p.bound[lq[qb]];
+            else if (MODE == NEAR_NEAREST && ok) {
                 const unsigned int best = p.best[q_at[qb]];
                 // (none found: nothing is admissible, or values beyond float16 hide it; the latter end up with the list kernels)
                 bound[qb] = best != 0u ? fmaxf(LOWEST, near_bound_from(from_ordered(best), h[qb], args)) : LOWEST;
@@ -524,6 +554,22 @@ struct NearLane {
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
                 for (int r = 0; r < 16; ++r) m1[qb] = max3(m1[qb], acc[qb][0][r], acc[qb][1][r]);
+            return;
+        }
+        if (MODE == NEAR_BLOCK) {
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb) {
+                    const v16f& v = acc[qb][cb];
+                    float mx = max3(v[0], v[1], v[2]);
+#pragma unroll
+                    for (int r = 3; r < 15; r += 2) mx = max3(mx, v[r], v[r + 1]);
+                    mx = fmaxf(mx, v[15]);
+                    const bool up = mx > m1[qb];
+                    m1_at[qb] = up ? pos0 + 32 * cb : m1_at[qb];
+                    m1[qb] = up ? mx : m1[qb];
+                }
             return;
         }
         if (MODE == NEAR_ARG) {
@@ -630,6 +676,15 @@ struct NearLane {
                 const float v = fmaxf(m1[qb], __shfl_xor(m1[qb], 32));
                 if (live && lhalf == 0 && v > -INF && v < INF) atomicMax(p.best + q_at[qb], ordered_bits(v));
             }
+            if (MODE == NEAR_BLOCK) {
+                const float v = __shfl_xor(m1[qb], 32);
+                const int at = __shfl_xor(m1_at[qb], 32);
+                const bool other = v > m1[qb];
+                const float m = other ? v : m1[qb];
+                const int pos = other ? at + 4 : m1_at[qb];                  // (lhalf 0 writes)
+                if (live && lhalf == 0 && m > -INF && m < INF)
+                    atomicMax(p.best_at + q_at[qb], ((unsigned long long)ordered_bits(m) << 32) | (unsigned int)pos);
+            }
             if (MODE == NEAR_ARG && live && m1_at[qb] >= 0 && fabsf(m1[qb]) < 1e37f) {
                 const int i = (int)(__float_as_uint(m1[qb]) & 31u), r = i & 15;
                 const int pos = m1_at[qb] + (i >> 4) * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
@@ -650,9 +705,31 @@ __device__ inline void near_lds_load(const void* g, void* l, bool quad)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 4, 0, 0);
 }
 
-__device__ inline int near_tile_at(const NearSweep& p, int seg, int i)
+// The share of a workgroup: which panel, which segment of how many, and where the query tiles end.
+struct NearShare { int panel, seg, nseg, q_tile1; bool any; };
+__device__ inline NearShare near_share(const NearSweep& p, int item, int panel_tiles, int units)
 {
-    const int j = seg + i * p.nseg;
+    NearShare r{0, 0, p.nseg, p.q_tile1, true};
+    if (p.n_dev) {
+        int n = *p.n_dev - p.q_tile0 * TILE;
+        const int most = (p.q_tile1 - p.q_tile0) * TILE;
+        n = n < 0 ? 0 : (n > most ? most : n);
+        r.q_tile1 = p.q_tile0 + (n + TILE - 1) / TILE;
+        const int panels = (r.q_tile1 - p.q_tile0 + panel_tiles - 1) / panel_tiles;
+        int k = panels > 0 ? p.slots / panels : 1;
+        k = k > p.most_seg ? p.most_seg : k;
+        k = k > units ? units : k;
+        r.nseg = k < 1 ? 1 : k;
+        r.any = item < panels * r.nseg;
+    }
+    r.panel = item / r.nseg;
+    r.seg = item - r.panel * r.nseg;
+    return r;
+}
+
+__device__ inline int near_tile_at(const NearSweep& p, int seg, int nseg, int i)
+{
+    const int j = seg + i * nseg;
     return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride;
 }
 
@@ -677,9 +754,11 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6;
-    const int panel = blockIdx.x / p.nseg, seg = blockIdx.x - panel * p.nseg;
-    const int qtile = p.q_tile0 + panel * (waves >> 1) + (wave >> 1);
-    const bool live = qtile < p.q_tile1;                 // (whole wavefronts)
+    const NearShare share = near_share(p, blockIdx.x, waves >> 1, p.used);
+    if (!share.any) return;
+    const int seg = share.seg, nseg = share.nseg;
+    const int qtile = p.q_tile0 + share.panel * (waves >> 1) + (wave >> 1);
+    const bool live = qtile < share.q_tile1;             // (whole wavefronts)
     const int qblk = (wave & 1) * 2;
 
     NearLane<MODE, COLOURED> mine;
@@ -694,9 +773,9 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
                 qf[qb][ks] = *reinterpret_cast<const v8h*>(p.qfrag + (qt * KS + ks) * FRAG_STEP + (qblk + qb) * 1024 + lane * 16);
     }
 
-    const int ntiles = seg < p.used ? (p.used - seg + p.nseg - 1) / p.nseg : 0;
+    const int ntiles = seg < p.used ? (p.used - seg + nseg - 1) / nseg : 0;
     auto stage = [&](int i) {
-        const size_t t = near_tile_at(p, seg, i);
+        const size_t t = near_tile_at(p, seg, nseg, i);
         unsigned char* dst = near_smem + (i & 1) * BUF;
         const unsigned char* src = p.cfrag + t * (KS * FRAG_STEP);
         for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
@@ -712,7 +791,7 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
         near_lds_ready();
         if (i + 1 < ntiles) stage(i + 1);
         const unsigned char* tb = near_smem + (i & 1) * BUF;
-        const int pos0 = near_tile_at(p, seg, i) * TILE;
+        const int pos0 = near_tile_at(p, seg, nseg, i) * TILE;
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             v16f acc[2][2];
@@ -773,15 +852,21 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qg = wave >> 1, cg = wave & 1;                            // 64 queries, 128 candidates of the 256 x 256
+    const int npairs = (p.used + 1) / 2;                                // pairs of listed tiles
     int item = blockIdx.x;
     {
-        const int per = gridDim.x >> 3;                                 // workgroups b, b + 8, ... share an XCD
+        NearShare all = near_share(p, 0, 2, npairs);
+        if (!all.any) return;
+        const int items = (all.q_tile1 - p.q_tile0 + 1) / 2 * all.nseg;
+        const int per = items >> 3;                                     // workgroups b, b + 8, ... share an XCD
+        if (item >= items) return;
         if (item < per * 8) item = (item & 7) * per + (item >> 3);
     }
-    const int panel = item / p.nseg, seg = item - panel * p.nseg;
-    const int qtile0 = p.q_tile0 + panel * 2;
+    const NearShare share = near_share(p, item, 2, npairs);
+    const int seg = share.seg, nseg = share.nseg, q_tile1 = share.q_tile1;
+    const int qtile0 = p.q_tile0 + share.panel * 2;
     const int qtile = qtile0 + (qg >> 1);
-    const bool live = qtile < p.q_tile1;
+    const bool live = qtile < q_tile1;
     const int qblk = (qg & 1) * 2;
     const int sub = (2 * seg + cg) * 2 + lhalf;
 
@@ -789,20 +874,19 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     mine.start(p, qtile, qblk, l32, sub, live);
 
     const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
-    const int npairs = (p.used + 1) / 2;                                // pairs of listed tiles
-    const int nmine = seg < npairs ? (npairs - seg + p.nseg - 1) / p.nseg : 0;
+    const int nmine = seg < npairs ? (npairs - seg + nseg - 1) / nseg : 0;
     auto listed = [&](int j) -> int { return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride; };
     const int total = nmine * nchunks;
     // the loads of step `at` (pair, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the norms with chunk 0
     auto stage = [&](int i, int chunk, int at) {
         unsigned char* dst = near_smem + (at & 1) * WIDE_BUF;
-        const int j0 = 2 * (seg + i * p.nseg);
+        const int j0 = 2 * (seg + i * nseg);
 #pragma unroll
         for (int x = 0; x < 8; ++x) {
             const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block]
             const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
             size_t t;
-            if (side == 0) t = qtile0 + tile < p.q_tile1 ? qtile0 + tile : qtile0;
+            if (side == 0) t = qtile0 + tile < q_tile1 ? qtile0 + tile : qtile0;
             else t = listed(j0 + tile < p.used ? j0 + tile : j0);
             const unsigned char* base = side == 0 ? p.qfrag : p.cfrag;
             near_lds_load(base + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16, dst + piece * 1024, true);
@@ -821,7 +905,7 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     for (int i = 0; i < nmine; ++i) {
         const unsigned char* nb = near_smem + 2 * WIDE_BUF + (i & 1) * 2048;
         v16f acc[2][2][2];                                              // [pair of candidate blocks][query block][candidate block]
-        const bool half_pair = 2 * (seg + i * p.nseg) + cg >= p.used;   // the second tile of the last pair may be missing
+        const bool half_pair = 2 * (seg + i * nseg) + cg >= p.used;   // the second tile of the last pair may be missing
         auto step = [&]() {
             const unsigned char* qs = near_smem + (at & 1) * WIDE_BUF + (qg >> 1) * (WIDE_STEPS * FRAG_STEP) + qblk * 1024 + lane * 16;
             const unsigned char* cs = near_smem + (at & 1) * WIDE_BUF + WIDE_HALF + cg * (WIDE_STEPS * FRAG_STEP) + lane * 16;
@@ -869,7 +953,7 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
             }
             step();
         }
-        const int j = 2 * (seg + i * p.nseg) + cg;
+        const int j = 2 * (seg + i * nseg) + cg;
         const int pos0 = listed(j < p.used ? j : 0) * TILE;
         if (!half_pair) {
             mine.take(p, acc[0], pos0, nb + 1024 + cg * 512, lhalf);
@@ -931,6 +1015,11 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
 }
 
 // ---------------------------------------------------------------------------------------------- selection
+__device__ inline long long near_row(int pos, int tiles, int in_order)
+{
+    return in_order ? (long long)pos : (long long)(pos & (TILE - 1)) * tiles + (pos >> 7);
+}
+
 struct NearSelect {
     const uint2* entries; const int32_t* counts; int nsub, capl, nq_batch, q0, by_position;
     const float* qnegh; const NearScale* sc; float e, nu; int steps;
@@ -940,6 +1029,9 @@ struct NearSelect {
     int32_t* todo; int32_t* todo_mark;
     int merge;                       // the output rows already hold the list of earlier candidates
     float* next_bound;               // optional: the bound the list implies, for the candidates still to come
+    const int32_t* n_dev;            // optional: the first *n_dev queries only
+    const int32_t* slot;             // optional: where the answers of query i go
+    int q_in_order, c_in_order;
 };
 
 template <bool VEC4>
@@ -962,8 +1054,40 @@ __device__ inline float near_quad_sqdist(v4f a, v4f b, float s)
     return s;
 }
 
-// One wavefront per query.  The exact distance adds in the order of group8_sqdist (sweep_kernels.hip): slabs of 64
-// features, lane g of eight adds features 4g.. and 4(g + 8).. of every slab into two sums, xor butterfly 1, 2, 4.
+// The exact distance of row xa to row xb by eight lanes, in the order of group8_sqdist (sweep_kernels.hip): slabs of 64
+// features, lane g of eight adds features 4g.. and 4(g + 8).. of every slab into two sums, xor butterfly 1, 2, 4.  q: what
+// lane g adds of the first 128 features of xa.
+template <bool VEC4>
+__device__ inline float near_exact(const v4f (&q)[4], const float* __restrict__ xa, const float* __restrict__ xb, int d, int g)
+{
+    float s0 = 0.f, s1 = 0.f;
+    {
+        const v4f b00 = near_quad<VEC4>(xb, 4 * g, d), b10 = near_quad<VEC4>(xb, 4 * g + 32, d);
+        const v4f b01 = near_quad<VEC4>(xb, 4 * g + 64, d), b11 = near_quad<VEC4>(xb, 4 * g + 96, d);
+        s0 = near_quad_sqdist(q[0], b00, s0); s0 = near_quad_sqdist(q[2], b01, s0);
+        s1 = near_quad_sqdist(q[1], b10, s1); s1 = near_quad_sqdist(q[3], b11, s1);
+    }
+    for (int base = 128; base < d; base += 128) {
+        const int t0 = base + 4 * g;
+        const v4f a00 = near_quad<VEC4>(xa, t0, d), b00 = near_quad<VEC4>(xb, t0, d);
+        const v4f a10 = near_quad<VEC4>(xa, t0 + 32, d), b10 = near_quad<VEC4>(xb, t0 + 32, d);
+        const v4f a01 = near_quad<VEC4>(xa, t0 + 64, d), b01 = near_quad<VEC4>(xb, t0 + 64, d);
+        const v4f a11 = near_quad<VEC4>(xa, t0 + 96, d), b11 = near_quad<VEC4>(xb, t0 + 96, d);
+        s0 = near_quad_sqdist(a00, b00, s0); s0 = near_quad_sqdist(a01, b01, s0);
+        s1 = near_quad_sqdist(a10, b10, s1); s1 = near_quad_sqdist(a11, b11, s1);
+    }
+    s0 += __shfl_xor(s0, 1); s0 += __shfl_xor(s0, 2); s0 += __shfl_xor(s0, 4);
+    s1 += __shfl_xor(s1, 1); s1 += __shfl_xor(s1, 2); s1 += __shfl_xor(s1, 4);
+    return s0 + s1;
+}
+template <bool VEC4>
+__device__ inline void near_first_quads(v4f (&q)[4], const float* __restrict__ xa, int d, int g)
+{
+#pragma unroll
+    for (int j = 0; j < 4; ++j) q[j] = near_quad<VEC4>(xa, 4 * g + 32 * j, d);
+}
+
+// One wavefront per query.
 template <bool VEC4>
 __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
 {
@@ -973,9 +1097,10 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     if (lq >= p.nq_batch) return;
     unsigned long long* keys = keys_[w];
     const int qpos = p.q0 + lq;
-    const long long qi = (long long)(qpos & (TILE - 1)) * p.q_tiles + (qpos >> 7);
-    if (qi >= p.nq) return;                                     // padding of the last tiles
-    const long long row = p.q_rows ? (long long)p.q_rows[qi] : qi;
+    const long long qn = near_row(qpos, p.q_tiles, p.q_in_order);
+    if (qn >= p.nq || (p.n_dev && qn >= *p.n_dev)) return;      // padding of the last tiles
+    const long long row = p.q_rows ? (long long)p.q_rows[qn] : qn;
+    const long long qi = p.slot ? (long long)p.slot[qn] : qn;
     const float nh = p.qnegh[qpos];
     if (row < 0 || row >= p.nq_rows || nh == -INF) {            // not a row, or not a finite one
         for (int j = lane; j < p.k; j += 64) { p.out_idx[qi * p.k + j] = -1; p.out_dist[qi * p.k + j] = INF; }
@@ -1031,7 +1156,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     for (int i = 0; i < n; i += 64) {
         unsigned long long e = i + lane < n ? keys[i + lane] : 0ull;
         const int pos = (int)(e >> 32);
-        const long long cand = (long long)(pos & (TILE - 1)) * p.c_tiles + (pos >> 7);
+        const long long cand = near_row(pos, p.c_tiles, p.c_in_order);
         const bool keep = i + lane < n && __uint_as_float((unsigned int)e) >= bound && cand < p.nc && !(p.exclude_self && cand == row);
         const unsigned long long mask = __ballot(keep);
         const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
@@ -1043,31 +1168,12 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     // exact distances, eight pairs at a time
     const int grp = lane >> 3, g = lane & 7;
     const float* xa = p.Xq + (size_t)row * p.d;
-    const v4f q00 = near_quad<VEC4>(xa, 4 * g, p.d), q10 = near_quad<VEC4>(xa, 4 * g + 32, p.d);
-    const v4f q01 = near_quad<VEC4>(xa, 4 * g + 64, p.d), q11 = near_quad<VEC4>(xa, 4 * g + 96, p.d);
+    v4f qa[4];
+    near_first_quads<VEC4>(qa, xa, p.d, g);
     for (int i = 0; i < left; i += 8) {
         const bool valid = i + grp < left;
         const unsigned int cand = (unsigned int)keys[valid ? i + grp : i];
-        const float* xb = p.Xc + (size_t)cand * p.d;
-        float s0 = 0.f, s1 = 0.f;
-        {
-            const v4f b00 = near_quad<VEC4>(xb, 4 * g, p.d), b10 = near_quad<VEC4>(xb, 4 * g + 32, p.d);
-            const v4f b01 = near_quad<VEC4>(xb, 4 * g + 64, p.d), b11 = near_quad<VEC4>(xb, 4 * g + 96, p.d);
-            s0 = near_quad_sqdist(q00, b00, s0); s0 = near_quad_sqdist(q01, b01, s0);
-            s1 = near_quad_sqdist(q10, b10, s1); s1 = near_quad_sqdist(q11, b11, s1);
-        }
-        for (int base = 128; base < p.d; base += 128) {
-            const int t0 = base + 4 * g;
-            const v4f a00 = near_quad<VEC4>(xa, t0, p.d), b00 = near_quad<VEC4>(xb, t0, p.d);
-            const v4f a10 = near_quad<VEC4>(xa, t0 + 32, p.d), b10 = near_quad<VEC4>(xb, t0 + 32, p.d);
-            const v4f a01 = near_quad<VEC4>(xa, t0 + 64, p.d), b01 = near_quad<VEC4>(xb, t0 + 64, p.d);
-            const v4f a11 = near_quad<VEC4>(xa, t0 + 96, p.d), b11 = near_quad<VEC4>(xb, t0 + 96, p.d);
-            s0 = near_quad_sqdist(a00, b00, s0); s0 = near_quad_sqdist(a01, b01, s0);
-            s1 = near_quad_sqdist(a10, b10, s1); s1 = near_quad_sqdist(a11, b11, s1);
-        }
-        s0 += __shfl_xor(s0, 1); s0 += __shfl_xor(s0, 2); s0 += __shfl_xor(s0, 4);
-        s1 += __shfl_xor(s1, 1); s1 += __shfl_xor(s1, 2); s1 += __shfl_xor(s1, 4);
-        const float dist = s0 + s1;
+        const float dist = near_exact<VEC4>(qa, xa, p.Xc + (size_t)cand * p.d, p.d, g);
         __builtin_amdgcn_wave_barrier();
         if (valid && g == 0) keys[i + grp] = ((unsigned long long)__float_as_uint(dist) << 32) | cand;
         __builtin_amdgcn_wave_barrier();
@@ -1202,7 +1308,8 @@ static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s
     const bool wide = p.steps > REG_STEPS;
     const int per_panel = wide ? 2 : waves / 2;
     const int panels = (p.q_tile1 - p.q_tile0 + per_panel - 1) / per_panel;
-    const dim3 grid((unsigned)(panels * p.nseg)), block((unsigned)(64 * waves));
+    // (queries counted on the device: as many workgroups as any count can use)
+    const dim3 grid((unsigned)(p.n_dev ? (panels > p.slots ? panels : p.slots) : panels * p.nseg)), block((unsigned)(64 * waves));
     const size_t lds = wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024);
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1245,6 +1352,7 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
     sel.q_tiles = q.tiles; sel.c_tiles = c.tiles; sel.exclude_self = a.exclude_self;
     sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
     sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    sel.q_in_order = q.in_order; sel.c_in_order = c.in_order;
     for (int t0 = 0; t0 < q.tiles; t0 += plan.batch_tiles) {
         const int t1 = t0 + plan.batch_tiles < q.tiles ? t0 + plan.batch_tiles : q.tiles;
         const int nqb = (t1 - t0) * TILE;
@@ -1265,8 +1373,10 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
             p.entries = reinterpret_cast<uint2*>(take((size_t)nqb * plan.capl * 8));
             p.counts = q.count;
             p.nseg = plan.nseg; p.stride = 1; p.skip = 0; p.used = c.tiles;
+            if (c.negh_best) p.cnegh = c.negh_best;
             e = a.coloured ? near_launch_sweep<NEAR_BEST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_BEST, false>(p, plan.waves, s);
             if (e != hipSuccess) return e;
+            p.cnegh = c.negh;
             e = a.coloured ? near_launch_sweep<NEAR_NEAREST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_NEAREST, false>(p, plan.waves, s);
             if (e != hipSuccess) return e;
             sel.nsub = 1; sel.by_position = 1;
@@ -1308,18 +1418,161 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
     return hipSuccess;
 }
 
+// ---------------------------------------------------------------------------------------------- connection rounds
+struct NearRange {
+    const unsigned long long* best_at; const float* negh; const int32_t* qcolour; const NearScale* sc; float e, nu; int steps, d;
+    const float* X; const int32_t* colour;
+    int n, n_rows; const int32_t* rows; int c_tiles, c_in_order;
+    uint32_t* threshold;
+    int32_t* out_idx; float *out_dist, *out_low; int32_t* evaluated;
+    int32_t *rows_left, *slot_left, *count_left; float* bound_left;
+};
+
+// One wavefront per query: of the 16 candidates one of which showed the largest product value, the nearest of another
+// colour, exactly.  An edge of the query's component, which lowers the component's threshold.
+template <bool VEC4>
+__global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
+{
+    const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (q >= p.n) return;
+    const unsigned long long best = p.best_at[q];
+    const int c = p.qcolour[q], row = p.rows[q];
+    unsigned long long key = ~0ull;
+    if (best != 0ull && fabsf(p.negh[q]) < INF && (unsigned int)c < (unsigned int)p.n_rows && (unsigned int)row < (unsigned int)p.n_rows) {
+        const int grp = lane >> 3, g = lane & 7;
+        const float* xa = p.X + (size_t)row * p.d;
+        v4f qa[4];
+        near_first_quads<VEC4>(qa, xa, p.d, g);
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int j = half * 8 + grp;
+            const long long cand = near_row((int)(unsigned int)best + 8 * (j >> 2) + (j & 3), p.c_tiles, p.c_in_order);
+            const bool real = cand >= 0 && cand < p.n_rows;
+            const bool fine = real && p.colour[real ? cand : 0] != c;
+            const float dist = near_exact<VEC4>(qa, xa, p.X + (size_t)(fine ? cand : row) * p.d, p.d, g);
+            const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
+            if (fine && dist < INF && k < key) key = k;
+        }
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1) {
+            const unsigned long long other = __shfl_xor(key, o);
+            key = other < key ? other : key;
+        }
+    }
+    if (lane == 0) {
+        p.out_idx[q] = key == ~0ull ? -1 : (int32_t)(unsigned int)key;
+        p.out_dist[q] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
+        if (key != ~0ull) min_into(&p.threshold[c], (uint32_t)(key >> 32));
+    }
+}
+
+// The queries whose nearest row of another colour may be as near as the threshold go on to the search.
+__global__ void __launch_bounds__(256) near_split_kernel(NearRange p)
+{
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    bool left = false;
+    float bound = LOWEST;
+    int row = -1;
+    if (q < p.n) {
+        const unsigned int best = (unsigned int)(p.best_at[q] >> 32);
+        const float nh = p.negh[q], h = -nh;
+        const int c = p.qcolour[q];
+        row = p.rows[q];
+        float lower = 0.f;
+        if (nh == -INF || c < 0 || c >= p.n_rows) lower = INF;          // no row
+        else if (nh == INF) left = true;                                // (ends up with the list kernels)
+        else {
+            const NearBoundArgs a = near_args(p.sc, p.steps, p.d, p.e, p.nu);
+            const float f = __uint_as_float(p.threshold[c]), f2 = f * p.sc->scale * p.sc->scale;
+            if (f2 < INF) bound = fmaxf(bound, near_bound_at(f2, h, a));
+            // nothing found: no other colour among the rows that float16 holds
+            if (p.sc->huge == 0u) lower = best != 0u ? near_lower_from(from_ordered(best), h, a) / p.sc->scale / p.sc->scale : INF;
+            left = lower <= f && lower < INF;
+        }
+        p.out_low[q] = lower;
+        if (!left && p.evaluated) p.evaluated[q] = 0;
+    }
+    const int at = block_append<256>(left, p.count_left);
+    if (left && at < p.n) { p.rows_left[at] = row; p.slot_left[at] = q; p.bound_left[at] = bound; }
+}
+
+// Connection rounds.  One pass over all candidates leaves per query the largest product value and the 16 candidates it came
+// from.  Bound by that pass: the search that follows is left with a query or two per component (10 of 250 000), where every
+// query used to go through it.  250k x 784, ten components: 346 -> 240 ms per call (a pass takes 99 ms); 100k x 64: 11.6 ->
+// 9.9 ms.  Without the exact edge of every query (only an interval for its distance), a component had no threshold in the
+// next round and queried all its rows again: 324 ms.
+hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
+{
+    if (!q.in_order || !q.colour || !c.colour || !q.best_at || !q.count || !c.negh_best || (a.n + 127) / 128 > b.todo_panels) return hipErrorInvalidValue;
+    hipError_t e = near_make(a.X, a.n_rows, a.d, a.rows, a.n, a.colour, b, q, nullptr, nullptr, s, true);
+    if (e != hipSuccess) return e;
+    NearPlan plan = near_plan(a.n, c.rows, a.d, 1, b.batch_bytes);
+    if (plan.batch_tiles < 1) return hipErrorInvalidValue;
+    NearSweep p{};
+    p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour; p.q_tile0 = 0; p.q_tile1 = q.tiles;
+    p.cfrag = c.frag; p.cnegh = c.negh_best; p.ccolour = c.colour; p.c_tiles = c.tiles;
+    p.sc = b.scale; p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
+    p.nseg = plan.nseg; p.stride = 1; p.used = c.tiles; p.kk = 1;
+    p.best_at = q.best_at;
+    e = near_launch_sweep<NEAR_BLOCK, true>(p, plan.waves, s);
+    if (e != hipSuccess) return e;
+    NearRange r{};
+    r.X = a.X; r.colour = a.colour; r.c_tiles = c.tiles; r.c_in_order = c.in_order;
+    r.best_at = q.best_at; r.negh = q.negh; r.qcolour = q.colour; r.sc = b.scale; r.e = p.e; r.nu = p.nu; r.steps = p.steps; r.d = a.d;
+    r.n = a.n; r.n_rows = a.n_rows; r.rows = a.rows; r.threshold = a.threshold;
+    r.out_idx = a.out_idx; r.out_dist = a.out_dist; r.out_low = a.out_low; r.evaluated = a.evaluated;
+    r.rows_left = a.rows_left; r.slot_left = a.slot_left; r.bound_left = a.bound_left; r.count_left = b.todo + 1;
+    const bool vec4 = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
+    if (vec4) hipLaunchKernelGGL((near_edge_kernel<true>), dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, s, r);
+    else hipLaunchKernelGGL((near_edge_kernel<false>), dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, s, r);
+    hipLaunchKernelGGL(near_split_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, r);
+    // the copy of the queries now holds those that are left
+    e = near_make(a.X, a.n_rows, a.d, a.rows_left, a.n, a.colour, b, q, nullptr, nullptr, s, false, r.count_left);
+    if (e != hipSuccess) return e;
+    p.cnegh = c.negh;
+    p.n_dev = r.count_left; p.most_seg = 64;
+    // few are left: workgroups of two wavefronts (of one kind beyond 128 columns) waste least on a panel that is not full
+    const bool wide = p.steps > REG_STEPS;
+    const int waves = wide ? plan.waves : (plan.waves > 2 ? plan.waves / 2 : 2);
+    p.slots = (waves == 8 ? 1 : 2) * near_cus();
+    p.counts = q.count; p.capl = plan.capl;
+    NearSelect sel{};
+    sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
+    sel.Xq = sel.Xc = a.X; sel.q_rows = a.rows_left; sel.slot = a.slot_left; sel.n_dev = r.count_left;
+    sel.d = a.d; sel.k = sel.kk = 1; sel.nq = a.n; sel.nq_rows = sel.nc = a.n_rows;
+    sel.q_tiles = q.tiles; sel.c_tiles = c.tiles; sel.q_in_order = 1; sel.c_in_order = c.in_order;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    sel.capl = plan.capl; sel.nsub = 1; sel.by_position = 1; sel.counts = q.count;
+    p.entries = reinterpret_cast<uint2*>(b.batch);
+    sel.entries = p.entries;
+    for (int t0 = 0; t0 < q.tiles; t0 += plan.batch_tiles) {
+        p.q_tile0 = t0; p.q_tile1 = t0 + plan.batch_tiles < q.tiles ? t0 + plan.batch_tiles : q.tiles;
+        const int nqb = (p.q_tile1 - t0) * TILE;
+        p.nq_batch = sel.nq_batch = nqb; sel.q0 = t0 * TILE;
+        p.bound = a.bound_left + (size_t)t0 * TILE;
+        e = near_launch_sweep<NEAR_NEAREST, true>(p, waves, s);
+        if (e != hipSuccess) return e;
+        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
+        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---------------------------------------------------------------------------------------------- colours, assignment
-__global__ void __launch_bounds__(256) near_colours_kernel(const int32_t* __restrict__ colour, int n, int tiles, int32_t* __restrict__ out)
+__global__ void __launch_bounds__(256) near_colours_kernel(const int32_t* __restrict__ colour, int n, int tiles, int in_order, int32_t* __restrict__ out)
 {
     const int p = blockIdx.x * 256 + threadIdx.x;
     if (p >= tiles * TILE) return;
-    const long long row = (long long)(p & (TILE - 1)) * tiles + (p >> 7);
+    const long long row = near_row(p, tiles, in_order);
     out[p] = row < n ? colour[row] : -1;
 }
 
 hipError_t near_colours(const NearCopy& c, const int32_t* colour, hipStream_t s)
 {
-    hipLaunchKernelGGL(near_colours_kernel, dim3((unsigned)((c.tiles + 1) / 2)), dim3(256), 0, s, colour, c.rows, c.tiles, c.colour);
+    hipLaunchKernelGGL(near_colours_kernel, dim3((unsigned)((c.tiles + 1) / 2)), dim3(256), 0, s, colour, c.rows, c.tiles, c.in_order ? 1 : 0, c.colour);
     return hipGetLastError();
 }
 

@@ -531,15 +531,18 @@ struct NearWs {
             x.rows = (int)n; x.tiles = slhc::near_tiles(n);
             x.frag = w.take<unsigned char>(slhc::near_frag_bytes(n, d));
             x.negh = w.take<float>((size_t)x.tiles * 128);
+            x.negh_best = kk == 1 || coloured ? w.take<float>((size_t)x.tiles * 128) : nullptr;
             x.colour = coloured ? w.take<int32_t>((size_t)x.tiles * 128) : nullptr;
             x.best = w.take<uint32_t>((size_t)x.tiles * 128);
             x.count = w.take<int32_t>((size_t)x.tiles * 128);
+            x.best_at = nullptr;
         };
         b.scale = w.take<slhc::NearScale>(1);
         b.shift = w.take<float>((size_t)d + 8);
         b.partial = w.take<float>(slhc::near_stats_scratch_floats(d));
         copy(c, nc);
         if (nq > 0) copy(q, nq); else q = c;
+        if (nq > 0 && coloured) q.best_at = w.take<unsigned long long>((size_t)q.tiles * 128);
         const int64_t queries = nq > 0 ? nq : nc;
         b.todo_panels = (queries + 127) / 128;
         b.todo = w.take<int32_t>((size_t)(2 + 2 * b.todo_panels));
@@ -679,7 +682,7 @@ struct SlhcWs {
     void* knn_ws;
     int32_t* nbr_idx; float* nbr_dist;
     int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *qlist, *q_idx, *counters, *e_lo, *e_hi;
-    float *ext_dist, *cand_w, *q_dist, *e_w;
+    float *ext_dist, *ext_low, *cand_w, *q_dist, *q_low, *e_w;
     uint32_t *best_w, *vals_a, *vals_b;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
@@ -695,7 +698,7 @@ struct SlhcWs {
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); qlist = c.take<int32_t>(n);
         q_idx = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
-        ext_dist = c.take<float>(n); cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
+        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); q_low = c.take<float>(n); cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
@@ -1513,7 +1516,7 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
 
 struct CsrWs {
     int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *counters, *e_lo, *e_hi;
-    float *ext_dist, *cand_w, *e_w;
+    float *ext_dist, *ext_low, *cand_w, *e_w;
     uint32_t *best_w, *vals_a, *vals_b;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
@@ -1525,7 +1528,7 @@ struct CsrWs {
         colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
-        ext_dist = c.take<float>(n); cand_w = c.take<float>(n); e_w = c.take<float>(n);
+        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); cand_w = c.take<float>(n); e_w = c.take<float>(n);
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
@@ -1569,7 +1572,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::ForestState f{};
         f.N = (int)V; f.k = 1;
-        f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist;
+        f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist; f.ext_low = ws.ext_low;
         f.cand_w = ws.cand_w; f.cand_u = ws.cand_u; f.best_w = ws.best_w; f.best_e = ws.best_e;
         f.hook = ws.hook; f.qlist = ws.ptr; f.counters = ws.counters;
         f.e_lo = ws.e_lo; f.e_hi = ws.e_hi; f.e_w = ws.e_w;
@@ -1875,7 +1878,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     slhc::ForestState f{};
     f.N = (int)N; f.k = k;
     f.nbr_idx = ws.nbr_idx; f.nbr_dist = ws.nbr_dist;
-    f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist;
+    f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist; f.ext_low = ws.ext_low;
     f.cand_w = ws.cand_w; f.cand_u = ws.cand_u; f.best_w = ws.best_w; f.best_e = ws.best_e;
     f.hook = ws.hook; f.qlist = ws.qlist; f.counters = ws.counters;
     f.e_lo = ws.e_lo; f.e_hi = ws.e_hi; f.e_w = ws.e_w;
@@ -2064,6 +2067,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if (round_pruned) { HIP_TRY(hipMemsetAsync(study_steps, 0, (size_t)study_panels * 8, s)); p.panel_steps = study_steps; }
 #endif
                 if (timed) HIP_TRY(hipEventRecord(ev_conn.a, s));
+                uint32_t* thresholds = round_pruned ? ws.vals_a : nullptr;
                 if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;
                     if (!kws.near_ready) {
@@ -2072,16 +2076,18 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                         kws.near_ready = true;
                     }
                     slhc::NearCopy q = near.q;
-                    q.rows = n; q.tiles = slhc::near_tiles(n);
+                    q.rows = n; q.tiles = slhc::near_tiles(n); q.in_order = true;
                     HIP_TRY(slhc::near_colours(near.c, ws.colour, s));
-                    HIP_TRY(slhc::near_make(X, (int)N, d, rows, n, ws.colour, near.b, q, nullptr, nullptr, s, true));
-                    slhc::NearProblem a{};
-                    a.Xq = a.Xc = X; a.d = d; a.k = 1;
-                    a.q_rows = rows; a.nq = n; a.nq_rows = a.nc = (int)N;
-                    a.coloured = 1;
-                    a.out_idx = ws.q_idx; a.out_dist = ws.q_dist;
-                    a.evaluated = reinterpret_cast<int32_t*>(ws.vals_b);          // free until the edge sort
-                    HIP_TRY(slhc::near_search(a, q, near.c, near.b, s));
+                    // (the arrays of the edge sort and of the thresholds are free until then)
+                    HIP_TRY(hipMemcpyAsync(ws.vals_a, ws.best_w, (size_t)N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+                    slhc::NearLink a{};
+                    a.X = X; a.d = d; a.n_rows = (int)N; a.rows = rows; a.n = n; a.colour = ws.colour;
+                    a.threshold = ws.vals_a;
+                    a.out_idx = ws.q_idx; a.out_dist = ws.q_dist; a.out_low = ws.q_low; a.evaluated = reinterpret_cast<int32_t*>(ws.vals_b);
+                    a.rows_left = reinterpret_cast<int32_t*>(ws.keys_a); a.slot_left = a.rows_left + N;
+                    a.bound_left = reinterpret_cast<float*>(ws.keys_b);
+                    HIP_TRY(slhc::near_link(a, q, near.c, near.b, s));
+                    thresholds = ws.vals_a;
                     hipLaunchKernelGGL(k_sum_words, dim3(16), dim3(256), 0, s, reinterpret_cast<const int32_t*>(ws.vals_b), n, kws.counters + 1);
                     HIP_TRY(hipGetLastError());
                     near_tile_steps += (unsigned long long)((n + 127) / 128) * tiles_1d;
@@ -2093,7 +2099,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 // in pruned rounds only)
                 HIP_TRY(slhc::launch_segmented_cross_1nn(p, round_pruned ? ws.keys_b : ws.keys_a, s));
                 if (timed) HIP_TRY(hipEventRecord(ev_conn.b, s));
-                HIP_TRY(slhc::forest_apply_queries(f, rows, ws.q_idx, ws.q_dist, n, round_pruned ? ws.vals_a : nullptr, s));
+                HIP_TRY(slhc::forest_apply_queries(f, rows, ws.q_idx, ws.q_dist, thresholds && !round_pruned ? ws.q_low : nullptr, n, thresholds, s));
                 // (every-tile rounds leave the check to the next reading of the counters)
                 h_cnt[7] = 0;
                 if (round_pruned) HIP_TRY(mail.fetch(ws.counters + 3, 1, h_cnt + 7));
@@ -2189,8 +2195,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
             }
             if (log.on) {
                 HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
-                log.mark("round %d: %d components, %d of %d listed rows queried, sweeps %.2f ms, %llu tile steps so far",
-                         st.boruvka_rounds, (int)(N - edges), queried, nq, ms_round_kernels, h_surv[3]);
+                int32_t left[2] = {0, queried};
+                if (!round_pruned && near_wanted(kws.near, flags)) HIP_TRY(mail.fetch(kws.near.b.todo, 2, left));
+                log.mark("round %d: %d components, %d of %d listed rows queried, %d searched, %d panels by lists, sweeps %.2f ms, %llu tile steps so far",
+                         st.boruvka_rounds, (int)(N - edges), queried, nq, left[1], left[0], ms_round_kernels, h_surv[3]);
             }
         }
         if (small_forest) { HIP_TRY(slhc::forest_small(f, false, s)); continue; }

@@ -100,3 +100,28 @@ def test_nearest_row_of_another_colour(lib, N, d, m, colours):
     oi, od = oracle.cross_1nn(X, colour, rows[take].astype(np.int64))
     assert np.allclose(gd[take], od, rtol=1e-5)
     assert (gi[take] == oi).mean() >= 0.99
+
+
+# connection rounds: components far apart, rows equally far from hundreds (a lattice; copies of rows), values beyond float16;
+# few and many columns, one-workgroup forests and others
+@pytest.mark.parametrize("kind", ["clusters", "lattice", "copies", "one_far_row", "all_far"])
+@pytest.mark.parametrize("N,d", [(300, 3), (5000, 64), (13_000, 24), (4000, 129), (3000, 300), (20_000, 128)])
+def test_trees_by_components(lib, kind, N, d):
+    print(f"half-precision trees, {kind}, N={N} d={d}", flush=True)
+    rng = np.random.default_rng(N + d)
+    if kind == "lattice":
+        X = rng.integers(0, 3, size=(N, d)) + 1000.0 * (rng.integers(0, 5, N) > 2)[:, None]
+    else:
+        X = 50.0 * rng.standard_normal((7, d))[rng.integers(0, 7, N)] + rng.standard_normal((N, d))
+        if kind == "copies":
+            X = X[rng.integers(0, N // 20 + 2, N)]
+        if kind == "one_far_row":
+            X[N // 3] *= 1e5
+        if kind == "all_far":
+            X *= 10.0 ** rng.uniform(0, 5, size=(N, 1))
+    Xd = torch.from_numpy(X.astype(np.float32)).cuda()
+    want = lib.slhc(Xd, 4, prune=False, fp32_filter=True)
+    got = lib.slhc(Xd, 4, prune=False)
+    torch.cuda.synchronize()
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
