@@ -70,7 +70,7 @@ hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32
 // half norms by row and the flag of launch_half_norms; colour (optional): by row
 hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
                      const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo = false,
-                     const int32_t* n_dev = nullptr);
+                     const int32_t* n_dev = nullptr, const int32_t* shift_row = nullptr);
 // the colours of the rows of `c` into c.colour
 hipError_t near_colours(const NearCopy& c, const int32_t* colour, hipStream_t s);
 // For every row of q the row of c with the (nearly) largest product value, i.e. a nearest row up to the rounding of the
@@ -87,9 +87,32 @@ struct NearLink {
     const int32_t* colour;                 // [n_rows]
     uint32_t* threshold;                   // [n_rows] by colour, float bits: known outgoing edges, lowered here
     int32_t* out_idx; float *out_dist, *out_low; int32_t* evaluated;     // [n]; out_low: the lower ends
-    int32_t *rows_left, *slot_left; float* bound_left;         // [n] scratch
+    int32_t *rows_left, *slot_left; float* reach_left;         // [n] scratch
+    // near_link_ordered: the queries' ascending positions in the order, and more scratch
+    const int32_t* qpos;
+    int32_t *pos_left, *counts_left, *edge_at; unsigned long long* best_at; uint32_t* threshold0;
 };
 hipError_t near_link(const NearLink& p, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s);
+// Searches in a row order whose tiles have bounding balls: a tile meets the tiles only that may hold what it looks for.
+// Two float16 copies in that order: `local` relative to the centre of every tile's region (a run of tiles close together), for the
+// pairs of one region, and `all` for the other pairs.
+struct NearOrder {
+    const float* gap; int tiles;           // lower bounds of the squared distances between the rows of two tiles
+    const int32_t* perm; int rows;         // row of X behind a position (-1: none), positions in use
+    const int32_t* region;                 // [tiles], -1: too short for its pairs to matter
+    NearCopy all, local; NearScale* local_scale;
+    float* ratios;                         // near_make_ordered: scale of `local` over that of `all`; squared norms of the rows as they
+                                           // are over those relative to the common shift
+    const int32_t* tile_colour;            // near_link_ordered: the colour all rows of a tile share, -1 where they differ
+    unsigned long long* tile_steps;        // pairs of tiles multiplied are added here
+};
+// (tile_first: the tile whose centre a tile of the local copy is relative to, -1 where region is)
+hipError_t near_make_ordered(const float* X, int n_src, int d, const NearOrder& o, const float* tile_c, const float* tile_r,
+                             const int32_t* tile_first, const float* hn, const NearBuffers& b, hipStream_t s);
+size_t near_ordered_batch_bytes(long long rows, int kk);
+size_t near_linked_batch_bytes(long long rows);
+hipError_t near_search_ordered(const NearProblem& p, const NearOrder& o, const NearBuffers& b, hipStream_t s);
+hipError_t near_link_ordered(const NearLink& p, const NearOrder& o, const NearBuffers& b, hipStream_t s);
 hipError_t near_search(const NearProblem& p, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s);
 
 }  // namespace slhc

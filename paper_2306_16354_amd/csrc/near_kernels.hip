@@ -232,6 +232,7 @@ hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32
 // ---------------------------------------------------------------------------------------------- the float16 copy
 struct NearMake {
     const float* X; const int32_t* rows; const int32_t* colour; const float* shift; NearScale* sc;
+    const int32_t* shift_row;            // optional: tile t is taken relative to row shift_row[t] of `shift` (-1: is left empty)
     unsigned char* frag; float *negh, *negh_best; int32_t* out_colour; float* hn; unsigned int* nonfinite;
     int n_src, n, d, tiles, steps, in_order; float h_of_n, hn_scale, absent;
     const int32_t* n_dev;
@@ -256,6 +257,8 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     const int part = tid % LPR, sub = tid / LPR;
     const bool mine = sub < 32;
     const float scale = p.sc->scale;
+    const float* __restrict__ shift = p.shift_row ? p.shift + (size_t)(p.shift_row[t] < 0 ? 0 : p.shift_row[t]) * p.d : p.shift;
+    const bool empty = p.shift_row && p.shift_row[t] < 0;
     if (tid == 0) eps_max = 0u;
     for (long long i = (long long)blockIdx.x * 256 + tid; i < p.todo_words; i += (long long)gridDim.x * 256) p.todo[i] = 0;
     float nn[PASSES], rr[PASSES], xx[PASSES];
@@ -266,7 +269,7 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
         nn[i] = rr[i] = xx[i] = 0.f; huge[i] = false;
         const int in_tile = blk * 32 + sub + i * ROWS;
         const long long at = p.in_order ? (long long)t * TILE + in_tile : (long long)in_tile * p.tiles + t;
-        long long row = mine && at < n_in ? (p.rows ? (long long)p.rows[at] : at) : -1;
+        long long row = mine && at < n_in && !empty ? (p.rows ? (long long)p.rows[at] : at) : -1;
         if (row >= p.n_src) row = -1;
         src[i] = row;
     }
@@ -276,7 +279,7 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
             const int col = 16 * s0 + 8 * oct;
             float m[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m[e] = col + e < p.d ? p.shift[col + e] : 0.f;
+            for (int e = 0; e < 8; ++e) m[e] = col + e < p.d ? shift[col + e] : 0.f;
 #pragma unroll
             for (int i = 0; i < PASSES; ++i) {
                 const int r = sub + i * ROWS;
@@ -335,7 +338,7 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
             if (hg && src[i] >= 0) p.sc->huge = 1u;
             if (p.out_colour) p.out_colour[at] = src[i] >= 0 && p.colour ? p.colour[src[i]] : -1;
             if (p.best) p.best[at] = 0u;
-            if (p.best_at) p.best_at[at] = 0ull;
+            if (p.best_at) p.best_at[at] = ~0ull;
             if (p.count) p.count[at] = 0;
             if (src[i] >= 0) {
                 if (p.hn) p.hn[src[i]] = p.hn_scale * x;
@@ -356,13 +359,15 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
 bool near_supported(int d) { return d >= 1; }
 
 hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
-                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo, const int32_t* n_dev)
+                     const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo, const int32_t* n_dev,
+                     const int32_t* shift_row)
 {
     if (n_dev && !out.in_order) return hipErrorInvalidValue;
     NearMake p{};
     p.X = X; p.rows = rows; p.colour = colour; p.shift = b.shift; p.sc = b.scale;
     p.frag = out.frag; p.negh = out.negh; p.out_colour = out.colour; p.hn = hn; p.nonfinite = nonfinite;
     p.n_src = n_src; p.n = n; p.d = d; p.tiles = out.tiles; p.steps = near_steps(d); p.h_of_n = 0.5f - 0.5f * near_nu(p.steps) - near_e(p.steps);
+    p.shift_row = shift_row;
     p.best = out.best; p.count = out.count; p.best_at = out.best_at;
     p.negh_best = out.negh_best; p.in_order = out.in_order; p.n_dev = n_dev;
     p.absent = out.finite_padding ? -1e38f : -INF;
@@ -391,14 +396,26 @@ struct NearSweep {
     // queries counted on the device (n_dev, over all batches): the panels that exist share `slots` workgroups in at most
     // most_seg segments each
     const int32_t* n_dev; int slots, most_seg;
+    // listed: the candidate tiles of every panel, list_len of them; list_step: every how-manieth is taken (0: none)
+    const unsigned short* list; const int32_t* list_len; const int32_t* list_step; int list_stride;
+    // block, nearest: the lists are cut into items of ITEM_TILES tiles, panel i has those from items[i] to items[i + 1]
+    const int32_t* items; int panels;
     int nsub;                          // buffers per query: the lanes that hold its values, over all segments
     int kk;                            // candidates a query needs (itself included where it meets itself)
     const float* bound;                // emit, nearest (or nullptr): [queries of the batch]
+    const float* reach;                // instead of bound: squared distances (rows as they are) that matter, by query; < 0: none
+    // queries by position in an order (nullptr: query i is position i), n_q of them unless counted on the device
+    const int32_t* qpos; int n_q;
+    // Searches in a row order with two copies: `local` (side 1) holds every tile relative to its region and serves the pairs
+    // inside one region, the other copy (side 2) all others.  region[tile] < 0: no region.  Entries of side 2 carry `mark`.
+    const int32_t* region; int side; unsigned int mark;
+    int append;                        // emit: the buffers hold the entries of an earlier launch, whose values do not compare
     float* maxima; int parts, groups;  // maxima: [nseg * parts][queries of the batch][groups], groups 32 or 8
     uint2* entries; int32_t* counts; int capl;      // emit: [queries of the batch][2 nseg][capl], [queries][2 nseg]
                                                     // nearest: [queries of the batch][capl], counts by position
-    unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position; block: likewise, the
-                                       // position of the first of the 16 values of a lane in a block of 32 candidates
+    unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position; block: (distance below
+                                       // which there is no candidate, position of the first of the 16 values of a lane in a block
+                                       // of 32 candidates the nearest of which is about there)
     uint32_t* best;                    // nearest: largest product value of a query by position (ordered bits)
     int nq_batch;
 };
@@ -488,33 +505,48 @@ struct NearLane {
     float m[2][16], m1[2];
     int m1_at[2];
     NearBoundArgs args;
-    int q_at[2];                            // position of the query, and its number in the batch
+    int q_at[2];                            // number of the query, and that in the batch
     int lq[2];
+    int q_pos[2], reg[2];                   // its position in the copy, and region
+    bool valid[2];
 
     // queries of block `qblk` and the next one of tile `qtile`; `sub`: the buffer of this lane among the p.nsub of a query
     __device__ inline void start(const NearSweep& p, int qtile, int qblk, int l32, int sub, bool live)
     {
-        if (MODE == NEAR_EMIT || MODE == NEAR_NEAREST) args = near_args(p.sc, p.steps, p.d, p.e, p.nu);
+        if (MODE == NEAR_EMIT || MODE == NEAR_NEAREST || MODE == NEAR_BLOCK) args = near_args(p.sc, p.steps, p.d, p.e, p.nu);
         const int qt = live ? qtile : p.q_tile0;
+        const int n_q = p.n_dev ? *p.n_dev : p.n_q;
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
             q_at[qb] = qt * TILE + (qblk + qb) * 32 + l32;
             lq[qb] = q_at[qb] - p.q_tile0 * TILE;
-            const float nh = p.qnegh[q_at[qb]];
+            valid[qb] = live && (!p.qpos || q_at[qb] < n_q);
+            q_pos[qb] = !p.qpos ? q_at[qb] : valid[qb] ? p.qpos[q_at[qb]] : 0;
+            reg[qb] = p.region ? p.region[q_pos[qb] >> 7] : -1;
+            const float nh = p.qnegh[q_pos[qb]];
             h[qb] = -nh;
-            const bool ok = live && fabsf(nh) < INF;
+            const bool ok = valid[qb] && fabsf(nh) < INF;
             bound[qb] = NEVER;
-            if (MODE == NEAR_EMIT && ok) bound[qb] = p.bound[lq[qb]];
-            if (MODE == NEAR_NEAREST && ok && p.bound) bound[qb] = p.bound[lq[qb]];
+            if ((MODE == NEAR_EMIT || MODE == NEAR_NEAREST) && p.reach) {
+                const float r = ok ? p.reach[MODE == NEAR_EMIT ? lq[qb] : q_at[qb]] : -1.f, t2 = r * p.sc->scale * p.sc->scale;
+                if (r >= 0.f) bound[qb] = t2 < INF ? fmaxf(LOWEST, near_bound_at(t2, h[qb], args)) : LOWEST;
+            } else if (MODE == NEAR_EMIT && ok) bound[qb] = p.bound[lq[qb]];
+            else if (MODE == NEAR_NEAREST && ok && p.bound) bound[qb] = p.bound[lq[qb]];
             else if (MODE == NEAR_NEAREST && ok) {
                 const unsigned int best = p.best[q_at[qb]];
                 // (none found: nothing is admissible, or values beyond float16 hide it; the latter end up with the list kernels)
                 bound[qb] = best != 0u ? fmaxf(LOWEST, near_bound_from(from_ordered(best), h[qb], args)) : LOWEST;
             }
-            if (COLOURED) qcol[qb] = p.qcolour[q_at[qb]];
+            if (COLOURED) qcol[qb] = p.qcolour[q_pos[qb]];
             if (MODE == NEAR_EMIT) {
                 off[qb] = ((unsigned int)lq[qb] * (unsigned int)p.nsub + (unsigned int)sub) * (unsigned int)p.capl * 8u;
                 roomy[qb] = off[qb] + (unsigned int)(p.capl - 32) * 8u;
+                if (p.append && live) {
+                    const int have = p.counts[(size_t)lq[qb] * p.nsub + sub];
+                    if (have > p.capl - 32) {                // (given up, or no room for what one step may find)
+                        off[qb] = 0u; roomy[qb] = 0xffffffffu; bound[qb] = NEVER;
+                    } else off[qb] += (unsigned int)have * 8u;
+                }
             }
             m1[qb] = -INF;
             m1_at[qb] = -1;
@@ -527,8 +559,11 @@ struct NearLane {
 
     // acc[query block][candidate block]: value r of a lane belongs to candidate 8 (r / 4) + 4 lhalf + r % 4 of its block;
     // pos0: position of the first of the 64 candidates, col: their colours (LDS)
-    __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf)
+    // ok: whether the lane's queries and the candidates' tile are of the side in hand
+    __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf,
+                                                               bool ok0 = true, bool ok1 = true)
     {
+        const bool ok[2] = {ok0, ok1};
         const int lane = threadIdx.x & 63;
         if (COLOURED) {
 #pragma unroll
@@ -566,7 +601,7 @@ struct NearLane {
 #pragma unroll
                     for (int r = 3; r < 15; r += 2) mx = max3(mx, v[r], v[r + 1]);
                     mx = fmaxf(mx, v[15]);
-                    const bool up = mx > m1[qb];
+                    const bool up = mx > m1[qb] && ok[qb];
                     m1_at[qb] = up ? pos0 + 32 * cb : m1_at[qb];
                     m1[qb] = up ? mx : m1[qb];
                 }
@@ -603,23 +638,23 @@ struct NearLane {
                 if ((g & 3) < 2) g8[g] = max3(g8[g], v[r + 3], v[r + 4]);
             }
             const float mx = fmaxf(max3(max3(g8[0], g8[1], g8[2]), max3(g8[3], g8[4], g8[5]), g8[6]), g8[7]);
-            if (!__any(mx >= bound[qb])) continue;
+            if (!__any(mx >= bound[qb] && ok[qb])) continue;
 #pragma unroll
             for (int g = 0; g < 8; ++g) {
-                if (__any(g8[g] >= bound[qb])) {
+                if (__any(g8[g] >= bound[qb] && ok[qb])) {
 #pragma unroll
                     for (int r = from[g & 3]; r < from[(g & 3) + 1]; ++r) {
                         const float v = acc[qb][g >> 2][r];
-                        if (__any(v >= bound[qb]) && v >= bound[qb]) {
-                            const int pos = pos0 + (g >> 2) * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
+                        if (__any(v >= bound[qb]) && v >= bound[qb] && ok[qb]) {
+                            const unsigned int pos = p.mark | (unsigned int)pos0 + (g >> 2) * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3);
                             if (MODE == NEAR_EMIT) {
                                 *reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.entries) + off[qb]) =
-                                    make_uint2(__float_as_uint(v), (unsigned int)pos);
+                                    make_uint2(__float_as_uint(v), pos);
                                 off[qb] += 8u;
                             } else {
                                 // (a handful per query over all workgroups)
                                 const int at = atomicAdd(p.counts + q_at[qb], 1);
-                                if (at < p.capl) p.entries[(size_t)lq[qb] * p.capl + at] = make_uint2(__float_as_uint(v), (unsigned int)pos);
+                                if (at < p.capl) p.entries[(size_t)lq[qb] * p.capl + at] = make_uint2(__float_as_uint(v), pos);
                             }
                         }
                     }
@@ -634,7 +669,7 @@ struct NearLane {
                 const unsigned int start = (unsigned int)__builtin_amdgcn_readlane((int)roomy[qb], who) - (unsigned int)(p.capl - 32) * 8u;
                 int n = (int)(((unsigned int)__builtin_amdgcn_readlane((int)off[qb], who) - start) >> 3);
                 const float hw = __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(h[qb]), who));
-                const float nb = near_refine(reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.entries) + start), &n, p.kk, hw, args);
+                const float nb = p.append ? LOWEST : near_refine(reinterpret_cast<uint2*>(reinterpret_cast<unsigned char*>(p.entries) + start), &n, p.kk, hw, args);
                 if (lane == who) {
                     off[qb] = start + (unsigned int)n * 8u;
                     bound[qb] = fmaxf(bound[qb], nb);
@@ -682,8 +717,11 @@ struct NearLane {
                 const bool other = v > m1[qb];
                 const float m = other ? v : m1[qb];
                 const int pos = other ? at + 4 : m1_at[qb];                  // (lhalf 0 writes)
-                if (live && lhalf == 0 && m > -INF && m < INF)
-                    atomicMax(p.best_at + q_at[qb], ((unsigned long long)ordered_bits(m) << 32) | (unsigned int)pos);
+                // (two copies may hold the query, and their product values do not compare: distances do)
+                if (valid[qb] && fabsf(h[qb]) < INF && lhalf == 0 && m > -INF && m < INF) {
+                    const float low = near_lower_from(m, h[qb], args) / p.sc->scale / p.sc->scale;
+                    atomicMin(p.best_at + q_at[qb], ((unsigned long long)__float_as_uint(low) << 32) | (unsigned int)pos);
+                }
             }
             if (MODE == NEAR_ARG && live && m1_at[qb] >= 0 && fabsf(m1[qb]) < 1e37f) {
                 const int i = (int)(__float_as_uint(m1[qb]) & 31u), r = i & 15;
@@ -742,11 +780,13 @@ __device__ inline void near_lds_ready()
     asm volatile("" ::: "memory");
 }
 
+constexpr int ITEM_TILES = 64;
+
 // Up to 128 columns: a wavefront keeps the fragments of its 64 queries (two blocks of 32) in registers and passes over
 // the candidate tiles, which the workgroup's wavefronts bring into LDS together (double buffered, one barrier per
 // tile).  A lane's 16 values of a 32 x 32 block belong to one query, so bounds and counts are registers.
 // Fragment order in memory makes every load and every LDS read consecutive over the lanes.
-template <int KS, int MODE, bool COLOURED>
+template <int KS, int MODE, bool COLOURED, bool LISTED>
 __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
 {
     extern __shared__ __align__(16) unsigned char near_smem[];
@@ -754,8 +794,31 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6;
-    const NearShare share = near_share(p, blockIdx.x, waves >> 1, p.used);
+    // Lists differ in length by orders of magnitude, so searches without buffers of their own per share hand them out in
+    // equal items; the grid passes over the items.
+    constexpr bool ITEMS = LISTED && (MODE == NEAR_BLOCK || MODE == NEAR_NEAREST);
+    const int n_items = ITEMS ? p.items[p.panels] : 0;
+    for (int item = blockIdx.x; !ITEMS || item < n_items; item += gridDim.x) {
+    NearShare share{0, 0, 1, p.q_tile1, true};
+    int item_from = 0;
+    if (ITEMS) {
+        int lo = 0, hi = p.panels;                       // items[lo] <= item < items[hi]
+        while (hi - lo > 1) {
+            const int mid = (lo + hi) >> 1;
+            if (p.items[mid] <= item) lo = mid; else hi = mid;
+        }
+        share.panel = lo;
+        item_from = (item - p.items[lo]) * ITEM_TILES;
+    } else share = near_share(p, item, waves >> 1, p.used);
     if (!share.any) return;
+    const unsigned short* __restrict__ list = LISTED ? p.list + (size_t)share.panel * p.list_stride + item_from : nullptr;
+    const int list_step = LISTED && p.list_step ? p.list_step[share.panel] : 1;
+    if (list_step == 0) return;
+    int used = p.used;
+    if (LISTED) {
+        used = (p.list_len[share.panel] - item_from + list_step - 1) / list_step;
+        if (ITEMS && used > ITEM_TILES) used = ITEM_TILES;
+    }
     const int seg = share.seg, nseg = share.nseg;
     const int qtile = p.q_tile0 + share.panel * (waves >> 1) + (wave >> 1);
     const bool live = qtile < share.q_tile1;             // (whole wavefronts)
@@ -765,17 +828,31 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     mine.start(p, qtile, qblk, l32, 2 * seg + lhalf, live);
     v8h qf[2][KS];
     {
-        const size_t qt = live ? qtile : p.q_tile0;
 #pragma unroll
-        for (int qb = 0; qb < 2; ++qb)
+        for (int qb = 0; qb < 2; ++qb) {
+            const int at = mine.q_pos[qb];                  // consecutive, or wherever the queries are
+            const unsigned char* src = p.qfrag + (size_t)(at >> 7) * (KS * FRAG_STEP) + ((at >> 5) & 3) * 1024 + (lhalf * 32 + (at & 31)) * 16;
 #pragma unroll
-            for (int ks = 0; ks < KS; ++ks)
-                qf[qb][ks] = *reinterpret_cast<const v8h*>(p.qfrag + (qt * KS + ks) * FRAG_STEP + (qblk + qb) * 1024 + lane * 16);
+            for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const v8h*>(src + ks * FRAG_STEP);
+        }
     }
+    // first bounds come from the one copy that holds all of a query's region
+    const int first_reg = LISTED && MODE == NEAR_MAXIMA && p.side ? __builtin_amdgcn_readfirstlane(mine.reg[0]) : 0;
+    const bool mine_here = !(LISTED && MODE == NEAR_MAXIMA && p.side) || (p.side == 1) == (first_reg >= 0);
 
-    const int ntiles = seg < p.used ? (p.used - seg + nseg - 1) / nseg : 0;
-    auto stage = [&](int i) {
-        const size_t t = near_tile_at(p, seg, nseg, i);
+    const int ntiles = seg < used ? (used - seg + nseg - 1) / nseg : 0;
+    // (called for i = 0, 1, ...: a lane holds one of 64 entries of the list)
+    int listed = 0;
+    auto tile_at = [&](int i) -> int {
+        if (!LISTED) return near_tile_at(p, seg, nseg, i);
+        if ((i & 63) == 0) {
+            const int j = seg + (i + lane) * nseg;
+            listed = j < used ? (int)list[j * list_step] : 0;
+        }
+        return __builtin_amdgcn_readlane(listed, i & 63);
+    };
+    auto stage = [&](int i, int tile) {
+        const size_t t = tile;
         unsigned char* dst = near_smem + (i & 1) * BUF;
         const unsigned char* src = p.cfrag + t * (KS * FRAG_STEP);
         for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
@@ -784,14 +861,25 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
             near_lds_load(g, dst + KS * FRAG_STEP + j * 256, false);
         }
     };
-    if (ntiles > 0) stage(0);
+    int next = ntiles > 0 ? tile_at(0) : 0;
+    if (ntiles > 0) stage(0, next);
     const int per_part = MODE == NEAR_MAXIMA ? (ntiles + p.parts - 1) / p.parts : 0;
     int part = 0, part_end = per_part;
     for (int i = 0; i < ntiles; ++i) {
         near_lds_ready();
-        if (i + 1 < ntiles) stage(i + 1);
+        const int pos0 = next * TILE;
+        if (i + 1 < ntiles) {
+            next = tile_at(i + 1);
+            stage(i + 1, next);
+        }
         const unsigned char* tb = near_smem + (i & 1) * BUF;
-        const int pos0 = near_tile_at(p, seg, nseg, i) * TILE;
+        bool ok0 = true, ok1 = true;
+        if (LISTED && p.side) {
+            const int tile_reg = p.region[pos0 >> 7];
+            ok0 = (tile_reg >= 0 && tile_reg == mine.reg[0]) == (p.side == 1);
+            ok1 = (tile_reg >= 0 && tile_reg == mine.reg[1]) == (p.side == 1);
+        }
+        if (!LISTED || (mine_here && __any(ok0 || ok1)))
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             v16f acc[2][2];
@@ -824,17 +912,22 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
                     for (int qb = 0; qb < 2; ++qb)
                         acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
             }
-            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf);
+            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1);
         }
         if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == ntiles)) {
-            mine.flush(p, seg * p.parts + part, lhalf, live);
+            mine.flush(p, seg * p.parts + part, lhalf, live && mine_here);
             ++part;
             part_end += per_part;
         }
     }
     if (MODE == NEAR_MAXIMA)
-        for (; part < p.parts; ++part) mine.flush(p, seg * p.parts + part, lhalf, live);
+        for (; part < p.parts; ++part) mine.flush(p, seg * p.parts + part, lhalf, live && mine_here);
     mine.finish(p, 2 * seg + lhalf, lhalf, live);
+    if (!ITEMS) break;
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();                        // the buffers in LDS are free again
+    asm volatile("" ::: "memory");
+    }
 }
 
 // Beyond 128 columns: 256 queries x 256 candidates per workgroup, both streamed through LDS 64 columns at a time
@@ -971,13 +1064,19 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
 }
 
 // One wavefront per query: (nearly) the kk-th largest of its group maxima, and the bound that follows.
+// reach (optional): an upper end of the squared distance of the kk-th nearest row.  step (optional): a second set of maxima,
+// made where the step of the query's panel is not 0; the better of the two bounds stays (one candidate may be in both sets).
 __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restrict__ maxima, int parts, int log_groups, int nq_batch, int q0, int kk,
                                                           const float* __restrict__ qnegh, const NearScale* __restrict__ sc, float e,
-                                                          float nu, int steps, int d, float* __restrict__ bound)
+                                                          float nu, int steps, int d, float* __restrict__ bound, float* __restrict__ reach,
+                                                          const int32_t* __restrict__ step, int panel_queries,
+                                                          const int32_t* __restrict__ region, const float* __restrict__ negh_local,
+                                                          const NearScale* __restrict__ sc_local)
 {
     const int lane = threadIdx.x & 63;
     const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
     if (lq >= nq_batch) return;
+    if (step && (step[lq / panel_queries] == 0 || region[(q0 + lq) >> 7] < 0)) return;
     const int n = parts << log_groups;               // at most 1024
     float v[16];
 #pragma unroll
@@ -1008,13 +1107,22 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
             if (reach >= kk) lo = mid; else hi = mid;
         }
     if (lane == 0) {
+        if (region && region[(q0 + lq) >> 7] >= 0) { qnegh = negh_local; sc = sc_local; }
         const float nh = qnegh[q0 + lq];
         const NearBoundArgs a = near_args(sc, steps, d, e, nu);
-        bound[lq] = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
+        const float made = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
+        bound[lq] = step ? fmaxf(bound[lq], made) : made;
+        if (reach) {
+            const float t = have < kk ? INF : near_distance_from(lo, -nh, a) / sc->scale;          // (a power of two)
+            // (no row, or none that is finite: reaches nothing; values beyond float16: left to the list kernels)
+            const float r = fabsf(nh) < INF ? (t * t * (1.f + a.gamma) + (float)d * 2.350988701644575e-38f) * (1.f + 1e-6f) : -1.f;
+            reach[lq] = step ? fminf(reach[lq], r) : r;
+        }
     }
 }
 
 // ---------------------------------------------------------------------------------------------- selection
+constexpr unsigned int MARK = 0x80000000u;
 __device__ inline long long near_row(int pos, int tiles, int in_order)
 {
     return in_order ? (long long)pos : (long long)(pos & (TILE - 1)) * tiles + (pos >> 7);
@@ -1032,6 +1140,11 @@ struct NearSelect {
     const int32_t* n_dev;            // optional: the first *n_dev queries only
     const int32_t* slot;             // optional: where the answers of query i go
     int q_in_order, c_in_order;
+    const int32_t* c_ids; int n_ids; // optional: candidates are positions of an order, c_ids[position] their row (-1: none)
+    const int32_t* ids;              // optional: so are the queries
+    const int32_t* qpos;             // optional: query i is this position of the copies
+    // optional, of an order with two copies (see NearSweep): entries without MARK come from the local one
+    const int32_t* region; const float* negh_local; const NearScale* sc_local;
 };
 
 template <bool VEC4>
@@ -1099,9 +1212,11 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     const int qpos = p.q0 + lq;
     const long long qn = near_row(qpos, p.q_tiles, p.q_in_order);
     if (qn >= p.nq || (p.n_dev && qn >= *p.n_dev)) return;      // padding of the last tiles
-    const long long row = p.q_rows ? (long long)p.q_rows[qn] : qn;
-    const long long qi = p.slot ? (long long)p.slot[qn] : qn;
-    const float nh = p.qnegh[qpos];
+    const long long row = p.ids ? (long long)p.ids[qn] : p.q_rows ? (long long)p.q_rows[qn] : qn;
+    if (p.ids && row < 0) return;                               // a position without a row
+    const long long qi = p.ids ? row : p.slot ? (long long)p.slot[qn] : qn;
+    const int qcopy = p.qpos ? p.qpos[qn] : qpos;
+    const float nh = p.qnegh[qcopy];
     if (row < 0 || row >= p.nq_rows || nh == -INF) {            // not a row, or not a finite one
         for (int j = lane; j < p.k; j += 64) { p.out_idx[qi * p.k + j] = -1; p.out_dist[qi * p.k + j] = INF; }
         if (p.evaluated && lane == 0) p.evaluated[qi] = 0;
@@ -1110,7 +1225,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     // gather the entries of all buffers: counts side by side over the lanes, running totals, then every lane looks up
     // the buffer its entry lies in
     int n = 0;
-    bool lost = nh == INF;
+    bool lost = nh == INF || (p.region && p.negh_local[qcopy] == INF);
     {
         const int mine = lane < p.nsub ? p.counts[p.by_position ? (size_t)qpos : (size_t)lq * p.nsub + lane] : 0;
         lost = lost || __any(mine > p.capl);
@@ -1136,7 +1251,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     }
     if (lost) {
         if (lane == 0) {
-            const int panel = (int)(qi >> 7);
+            const int panel = (int)((p.c_ids ? qcopy : qi) >> 7);
             if (atomicExch(p.todo_mark + panel, 1) == 0) p.todo[2 + atomicAdd(p.todo, 1)] = panel;
             if (p.next_bound) p.next_bound[lq] = NEVER;
             if (p.evaluated) p.evaluated[qi] = 0;
@@ -1145,9 +1260,29 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     }
     __builtin_amdgcn_wave_barrier();
     // a tighter bound from (nearly) the kk-th largest product value emitted
-    float bound = LOWEST;
+    float bound = LOWEST, bound_local = LOWEST;
     const NearBoundArgs args = near_args(p.sc, p.steps, p.d, p.e, p.nu);
-    if (n > p.kk + 4) {
+    if (p.region) {
+        // product values of the two copies do not compare: the bound comes from those of one
+        const unsigned int first = p.region[qcopy >> 7] >= 0 ? 0u : MARK;
+        const float nl = p.negh_local[qcopy];
+        const NearBoundArgs al = near_args(p.sc_local, p.steps, p.d, p.e, p.nu);
+        if (n > p.kk + 4) {
+            const float kth = near_kth(n, p.kk, [&](int i) {
+                const unsigned long long e = i + lane < n ? keys[i + lane] : 0ull;
+                return i + lane < n && ((unsigned int)(e >> 32) & MARK) == first ? __uint_as_float((unsigned int)e) : -INF;
+            });
+            if (kth != LOWEST) {
+                const NearScale* sc = first ? p.sc : p.sc_local;
+                const float t = near_distance_from(kth, first ? -nh : -nl, first ? args : al) / sc->scale;
+                const float t2 = (t * t * (1.f + args.gamma) + (float)p.d * 2.350988701644575e-38f) * (1.f + 1e-6f);
+                if (t2 < INF) {
+                    bound = fmaxf(LOWEST, near_bound_at(t2 * p.sc->scale * p.sc->scale, -nh, args));
+                    if (fabsf(nl) < INF) bound_local = fmaxf(LOWEST, near_bound_at(t2 * p.sc_local->scale * p.sc_local->scale, -nl, al));
+                }
+            }
+        }
+    } else if (n > p.kk + 4) {
         const float kth = near_kth(n, p.kk, [&](int i) { return i + lane < n ? __uint_as_float((unsigned int)keys[i + lane]) : -INF; });
         if (kth != LOWEST) bound = near_bound_from(kth, -nh, args);
     }
@@ -1155,9 +1290,11 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     int left = 0;
     for (int i = 0; i < n; i += 64) {
         unsigned long long e = i + lane < n ? keys[i + lane] : 0ull;
-        const int pos = (int)(e >> 32);
-        const long long cand = near_row(pos, p.c_tiles, p.c_in_order);
-        const bool keep = i + lane < n && __uint_as_float((unsigned int)e) >= bound && cand < p.nc && !(p.exclude_self && cand == row);
+        const int pos = (int)((unsigned int)(e >> 32) & ~MARK);
+        const float least = p.region && !((unsigned int)(e >> 32) & MARK) ? bound_local : bound;
+        long long cand = near_row(pos, p.c_tiles, p.c_in_order);
+        if (p.c_ids) cand = i + lane < n && cand < p.n_ids ? (long long)p.c_ids[cand] : -1;
+        const bool keep = i + lane < n && cand >= 0 && __uint_as_float((unsigned int)e) >= least && cand < p.nc && !(p.exclude_self && cand == row);
         const unsigned long long mask = __ballot(keep);
         const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
         __builtin_amdgcn_wave_barrier();
@@ -1302,14 +1439,14 @@ size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk)
     return p.per_tile * (size_t)(p.panel_tiles < most ? p.panel_tiles : most) + 8192;
 }
 
-template <int MODE, bool COLOURED>
+template <int MODE, bool COLOURED, bool LISTED = false>
 static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s)
 {
     const bool wide = p.steps > REG_STEPS;
     const int per_panel = wide ? 2 : waves / 2;
     const int panels = (p.q_tile1 - p.q_tile0 + per_panel - 1) / per_panel;
     // (queries counted on the device: as many workgroups as any count can use)
-    const dim3 grid((unsigned)(p.n_dev ? (panels > p.slots ? panels : p.slots) : panels * p.nseg)), block((unsigned)(64 * waves));
+    const dim3 grid((unsigned)(LISTED && (MODE == NEAR_BLOCK || MODE == NEAR_NEAREST) ? (waves == 8 ? 1 : 2) * near_cus() : p.n_dev ? (panels > p.slots ? panels : p.slots) : panels * p.nseg)), block((unsigned)(64 * waves));
     const size_t lds = wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024);
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1317,16 +1454,20 @@ static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s
         hipLaunchKernelGGL(kernel, grid, block, lds, s, p);
         return hipGetLastError();
     };
-    if (wide) return run(&near_wide_kernel<MODE, COLOURED>);
+    if constexpr (LISTED) {
+        if (wide || !p.list || !p.list_len) return hipErrorInvalidValue;
+    } else {
+        if (wide) return run(&near_wide_kernel<MODE, COLOURED>);
+    }
     switch (p.steps) {
-        case 1: return run(&near_sweep_kernel<1, MODE, COLOURED>);
-        case 2: return run(&near_sweep_kernel<2, MODE, COLOURED>);
-        case 3: return run(&near_sweep_kernel<3, MODE, COLOURED>);
-        case 4: return run(&near_sweep_kernel<4, MODE, COLOURED>);
-        case 5: return run(&near_sweep_kernel<5, MODE, COLOURED>);
-        case 6: return run(&near_sweep_kernel<6, MODE, COLOURED>);
-        case 7: return run(&near_sweep_kernel<7, MODE, COLOURED>);
-        case 8: return run(&near_sweep_kernel<8, MODE, COLOURED>);
+        case 1: return run(&near_sweep_kernel<1, MODE, COLOURED, LISTED>);
+        case 2: return run(&near_sweep_kernel<2, MODE, COLOURED, LISTED>);
+        case 3: return run(&near_sweep_kernel<3, MODE, COLOURED, LISTED>);
+        case 4: return run(&near_sweep_kernel<4, MODE, COLOURED, LISTED>);
+        case 5: return run(&near_sweep_kernel<5, MODE, COLOURED, LISTED>);
+        case 6: return run(&near_sweep_kernel<6, MODE, COLOURED, LISTED>);
+        case 7: return run(&near_sweep_kernel<7, MODE, COLOURED, LISTED>);
+        case 8: return run(&near_sweep_kernel<8, MODE, COLOURED, LISTED>);
         default: return hipErrorInvalidValue;
     }
 }
@@ -1396,7 +1537,8 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
             if (e != hipSuccess) return e;
         }
         hipLaunchKernelGGL(near_bounds_kernel, per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
-                           plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound);
+                           plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound, static_cast<float*>(nullptr), static_cast<const int32_t*>(nullptr), 1,
+                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr));
         p.nseg = plan.nseg; p.nsub = plan.nsub;
         sel.nsub = plan.nsub; sel.by_position = 0; sel.merge = 0; sel.next_bound = nullptr;
         if (plan.stages == 2) {
@@ -1418,27 +1560,497 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
     return hipSuccess;
 }
 
+// ---------------------------------------------------------------------------------------------- searches in a row order
+// Lists of candidate tiles per panel of queries.  One workgroup per panel: the distinct tiles its queries lie in, each with
+// the largest reach and the range of colours among its queries, go to LDS, and every candidate tile is tried against them.
+// Bound by reading the rows of the table of tile pairs once: 1M x 128 (8264 tiles) 85 us per list of all panels.
+enum { LIST_LOCAL = 1, LIST_CROSS = 2 };        // pairs inside a region; all others
+struct NearList {
+    const float* gap; int T;
+    const int32_t* region; int what;
+    float* reach;                          // by query of the batch (set to -1 where the query is left to the list kernels), or
+    const int32_t* colour; const uint32_t* threshold; int n_rows;      // (colour by position) the query's component's threshold
+    const int32_t* tile_colour;            // (with colour) tiles all of whose rows have the queries' one colour are left out
+    const int32_t* pos; int n_pos;         // position of query i in the order (nullptr: query i), positions there are
+    int q0, nq, panel_queries;
+    const int32_t* n_dev;                  // optional: queries there are, over all batches
+    const unsigned short* from; const int32_t* from_len;               // optional: only the tiles of an earlier list
+    unsigned short* list; int32_t* list_len; int32_t* list_step; int list_stride;
+    double cost;                           // list_step: a pass over one tile in units of an emitted entry
+    int kk;
+    unsigned long long* tile_steps;
+    // optional: a query tile that would need more than `most` candidate tiles is left to the list kernels instead
+    int most; int32_t *todo, *todo_mark;
+};
+constexpr int LIST_QUERIES = 512;          // per panel at most
+
+struct NearSegments {
+    int tile[LIST_QUERIES], lo[LIST_QUERIES], hi[LIST_QUERIES], reg[LIST_QUERIES];
+    unsigned int reach[LIST_QUERIES];
+    int heads[8], count;
+};
+// Returns the number of distinct tiles (runs of them) of the panel's `mine` queries; a barrier at the end.
+__device__ inline int near_segments(const NearList& p, NearSegments& g, int base, int mine)
+{
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    if (tid == 0) g.count = 0;
+    for (int i = tid; i < mine; i += 256) { g.lo[i] = 0x7fffffff; g.hi[i] = -1; g.reach[i] = 0u; }
+    auto pos_of = [&](int i) -> int { return p.pos ? p.pos[p.q0 + base + i] : p.q0 + base + i; };
+    int at_pos[2];
+    bool head[2];
+    unsigned long long heads[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = tid + 256 * r;
+        at_pos[r] = i < mine ? pos_of(i) : -1;
+        head[r] = i < mine && (i == 0 || (pos_of(i - 1) >> 7) != (at_pos[r] >> 7));
+        heads[r] = __ballot(head[r]);
+        if (lane == 0) g.heads[r * 4 + wave] = __popcll(heads[r]);
+    }
+    __syncthreads();
+    int nseg = 0;
+    for (int w = 0; w < 8; ++w) nseg += g.heads[w];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = tid + 256 * r;
+        if (i < mine) {
+            int at = -1;
+            for (int w = 0; w < r * 4 + wave; ++w) at += g.heads[w];
+            at += __popcll(heads[r] & (~0ull >> (63 - lane)));
+            const int t = at_pos[r] >> 7;
+            const bool fine = at_pos[r] >= 0 && at_pos[r] < p.n_pos;
+            if (head[r]) { g.tile[at] = fine ? t : -1; g.reg[at] = fine ? p.region[t] : -1; }
+            float reach = -1.f;
+            if (!fine) {}
+            else if (p.colour) {
+                const int c = p.colour[at_pos[r]];
+                if ((unsigned int)c < (unsigned int)p.n_rows) {
+                    reach = __uint_as_float(p.threshold[c]);
+                    atomicMin(&g.lo[at], c); atomicMax(&g.hi[at], c);
+                }
+            } else reach = p.reach[base + i];
+            // (what a bound on a table entry's rounding can hide; 0 is left for a tile none of whose queries needs anything)
+            if (reach >= 0.f) atomicMax(&g.reach[at], __float_as_uint(fmaxf(reach * (1.f + 1e-5f), 1e-37f)));
+        }
+    }
+    __syncthreads();
+    return nseg;
+}
+
+__global__ void __launch_bounds__(256) near_list_kernel(NearList p)
+{
+    __shared__ NearSegments g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int panel = blockIdx.x;
+    int nq = p.nq;
+    if (p.n_dev) { const int n = *p.n_dev - p.q0; nq = n < nq ? n : nq; }
+    const int base = panel * p.panel_queries;
+    if (base >= nq) {
+        if (tid == 0 && gridDim.y == 1) { p.list_len[panel] = 0; if (p.list_step) p.list_step[panel] = 0; }
+        return;
+    }
+    const int mine = nq - base < p.panel_queries ? nq - base : p.panel_queries;
+    const int nseg = near_segments(p, g, base, mine);
+    if (p.what == LIST_LOCAL) {
+        bool any = false;
+        for (int seg = 0; seg < nseg; ++seg) any = any || g.reg[seg] >= 0;
+        if (!any) {
+            if (tid == 0 && gridDim.y == 1) { p.list_len[panel] = 0; if (p.list_step) p.list_step[panel] = 0; }
+            return;
+        }
+    }
+    unsigned short* list = p.list + (size_t)panel * p.list_stride;
+    const unsigned short* from = p.from ? p.from + (size_t)panel * p.list_stride : nullptr;
+    const int n = from ? p.from_len[panel] : p.T;
+    auto needs = [&](int seg, int t, int tc, int tr) -> bool {
+        const unsigned int r = g.reach[seg];
+        const int st = g.tile[seg], sr = g.reg[seg];
+        if (r == 0u || st < 0 || (tc >= 0 && g.lo[seg] == tc && g.hi[seg] == tc)) return false;
+        if ((sr >= 0 && sr == tr) != (p.what == LIST_LOCAL)) return false;
+        return p.gap[(size_t)st * p.T + t] <= __uint_as_float(r);      // (NaN: no)
+    };
+    // (panels of few queries per tile have many tiles: several workgroups share the candidates of one, see gridDim.y)
+    const bool shared = gridDim.y > 1;
+    int32_t* counter = shared ? p.list_len + panel : &g.count;
+    auto scan = [&]() {
+        for (int i0 = (blockIdx.y * 4 + wave) * 64; i0 < n; i0 += 256 * gridDim.y) {
+            const int i = i0 + lane;
+            const int t = i < n ? (from ? (int)from[i] : i) : -1;
+            bool keep = false;
+            const bool fine = t >= 0 && t < p.T;
+            const int tc = fine && p.colour ? p.tile_colour[t] : -1, tr = fine ? p.region[t] : -1;
+            for (int s0 = 0; s0 < nseg && __any(fine && !keep); s0 += 4) {
+                bool k4[4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) k4[e] = fine && s0 + e < nseg && needs(s0 + e, t, tc, tr);      // (loads side by side)
+                keep = keep || k4[0] || k4[1] || k4[2] || k4[3];
+            }
+            const unsigned long long m = __ballot(keep);
+            int at = 0;
+            if (lane == 0 && m) at = atomicAdd(counter, __popcll(m));
+            at = __shfl(at, 0);
+            if (keep) list[at + __popcll(m & (lane ? ~0ull >> (64 - lane) : 0ull))] = (unsigned short)t;
+        }
+        __syncthreads();
+    };
+    scan();
+    if (p.most > 0 && g.count > p.most) {
+        // which of the panel's tiles want that many (there are few such tiles: rows with fewer near rows than they ask for)
+        __syncthreads();
+        for (int seg = wave; seg < nseg; seg += 4) {
+            int wants = 0;
+            for (int t = lane; t < p.T; t += 64) wants += needs(seg, t, p.colour ? p.tile_colour[t] : -1, p.region[t]) ? 1 : 0;
+#pragma unroll
+            for (int o = 32; o > 0; o >>= 1) wants += __shfl_xor(wants, o);
+            if (lane == 0 && wants > p.most) {
+                g.reach[seg] = 0u;
+                const int st = g.tile[seg];
+                if (atomicExch(p.todo_mark + st, 1) == 0) p.todo[2 + atomicAdd(p.todo, 1)] = st;
+            }
+        }
+        if (tid == 0) g.count = 0;
+        __syncthreads();
+        for (int i = tid; i < mine; i += 256) {
+            const int t = (p.q0 + base + i) >> 7;               // (queries in order)
+            for (int seg = 0; seg < nseg; ++seg)
+                if (g.tile[seg] == t && g.reach[seg] == 0u) p.reach[base + i] = -1.f;
+        }
+        scan();
+    }
+    if (tid == 0 && !shared) {
+        const int count = g.count;
+        p.list_len[panel] = count;
+        if (p.list_step) {
+            // as in near_plan: sample one tile in `step`, step^2 = pass over all / entries per step; at least 16 tiles.  A list
+            // not much longer than the window has nothing to gain.
+            int step = (int)(__builtin_sqrt((double)count * p.cost / p.kk) + 0.5);
+            if (step > count / 16) step = count / 16;
+            if (step > 5) step = 5;
+            p.list_step[panel] = count < 24 ? 0 : (step < 1 ? 1 : step);
+        }
+        if (p.tile_steps && count) atomicAdd(p.tile_steps, (unsigned long long)((mine + TILE - 1) / TILE) * count);
+    }
+}
+
+// Some of the nearest tiles with rows of other colours, for a first edge out of every component: of up to eight of the panel's
+// tiles, the nearest in each of four interleaved quarters of all tiles.
+constexpr int FIRST_TILES = 32;
+static int near_list_stride(int T) { return T > FIRST_TILES ? T : FIRST_TILES; }
+__global__ void __launch_bounds__(256) near_first_kernel(NearList p)
+{
+    __shared__ NearSegments g;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int panel = blockIdx.x, base = panel * p.panel_queries;
+    const int mine = p.nq - base < p.panel_queries ? p.nq - base : p.panel_queries;
+    if (mine <= 0) { if (tid == 0) p.list_len[panel] = 0; return; }
+    const int nseg = near_segments(p, g, base, mine);
+    unsigned short* list = p.list + (size_t)panel * p.list_stride;
+    const int picks = nseg < 8 ? nseg : 8;
+    for (int i = 0; i < picks; ++i) {
+        const int s = (int)((long long)i * nseg / picks);
+        const int st = g.tile[s];
+        unsigned long long best = ~0ull;
+        if (st >= 0)
+            for (int t = tid; t < p.T; t += 256) {
+                const int tc = p.tile_colour[t];
+                if (tc >= 0 && g.lo[s] == tc && g.hi[s] == tc) continue;
+                const float gap = p.gap[(size_t)st * p.T + t];
+                if (!(gap >= 0.f)) continue;
+                const unsigned int off = (unsigned int)(t > st ? t - st : st - t);
+                const unsigned long long key = ((unsigned long long)__float_as_uint(gap) << 32) | (off << 16) | (unsigned int)t;
+                best = key < best ? key : best;
+            }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long other = __shfl_xor(best, o);
+            best = other < best ? other : best;
+        }
+        if (lane == 0 && best != ~0ull) list[atomicAdd(&g.count, 1)] = (unsigned short)(best & 0xffffu);
+    }
+    (void)wave;
+    __syncthreads();
+    if (tid == 0) p.list_len[panel] = g.count;
+}
+
+// The tiles around each of a panel's own ones: what the first bounds come from.
+__global__ void __launch_bounds__(64) near_window_kernel(int tile0, int panel_tiles, int last_tile, int T, int around, unsigned short* __restrict__ list,
+                                                         int32_t* __restrict__ list_len, int list_stride, int panels)
+{
+    const int panel = blockIdx.x * 64 + threadIdx.x;
+    if (panel >= panels) return;
+    const int a = tile0 + panel * panel_tiles, e = a + panel_tiles < last_tile ? a + panel_tiles : last_tile;
+    int lo = a - around, hi = e + around;
+    lo = lo < 0 ? 0 : lo;
+    hi = hi > T ? T : hi;
+    for (int t = lo; t < hi; ++t) list[(size_t)panel * list_stride + (t - lo)] = (unsigned short)t;
+    list_len[panel] = hi - lo;
+}
+
+// items[i]: items of the panels before i; tile_steps (optional): tiles multiplied, by the panels' query tiles.
+__global__ void __launch_bounds__(1024) near_items_kernel(const int32_t* __restrict__ len, int panels, int32_t* __restrict__ items,
+                                                          int panel_queries, int nq, unsigned long long* __restrict__ tile_steps)
+{
+    __shared__ int sum[1024];
+    const int tid = threadIdx.x, per = (panels + 1023) / 1024;
+    const int a = tid * per < panels ? tid * per : panels, e = a + per < panels ? a + per : panels;
+    int c = 0;
+    unsigned long long steps = 0;
+    for (int i = a; i < e; ++i) {
+        c += (len[i] + ITEM_TILES - 1) / ITEM_TILES;
+        const int q = nq - i * panel_queries < panel_queries ? nq - i * panel_queries : panel_queries;
+        steps += (unsigned long long)((q + TILE - 1) / TILE) * len[i];
+    }
+    sum[tid] = c;
+    __syncthreads();
+    for (int o = 1; o < 1024; o <<= 1) {
+        const int v = tid >= o ? sum[tid - o] : 0;
+        __syncthreads();
+        sum[tid] += v;
+        __syncthreads();
+    }
+    int at = sum[tid] - c;
+    for (int i = a; i < e; ++i) { items[i] = at; at += (len[i] + ITEM_TILES - 1) / ITEM_TILES; }
+    if (tid == 1023) items[panels] = sum[1023];
+    if (tile_steps && steps) atomicAdd(tile_steps, steps);
+}
+
+__global__ void __launch_bounds__(256) near_todo_clear_kernel(int32_t* __restrict__ todo, long long words)
+{
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < words; i += (long long)gridDim.x * 256) todo[i] = 0;
+}
+
+// The scale of the copy by regions: the median tile's radius near 2^7 (see near_shift_kernel).
+__global__ void __launch_bounds__(64) near_local_scale_kernel(const float* __restrict__ tile_r, const int32_t* __restrict__ region, int T, NearScale* __restrict__ sc,
+                                                              const NearScale* __restrict__ sc_all, const float* __restrict__ negh, int rows,
+                                                              const float* __restrict__ hn, const int32_t* __restrict__ perm, float* __restrict__ ratio)
+{
+    // the 64 lanes' shares of the tiles, one local tile of each
+    const int lane = threadIdx.x;
+    float r = -1.f;
+    for (int t = (int)((long long)lane * T / 64); t < (int)((long long)(lane + 1) * T / 64) && !(r > 0.f); ++t)
+        if (region[t] >= 0) r = tile_r[t];
+    // squared norms of a sample of rows as they are, over those relative to the common shift
+    float as_is = 0.f, shifted = 0.f;
+    for (int j = 0; j < 16; ++j) {
+        const int at = (int)((long long)(lane * 16 + j) * rows / 1024);
+        const float x = perm[at] >= 0 ? hn[perm[at]] : 0.f, y = -negh[at];
+        if (x < INF && y < INF) { as_is += x; shifted += y / sc_all->scale / sc_all->scale; }
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { as_is += __shfl_xor(as_is, o); shifted += __shfl_xor(shifted, o); }
+    if (lane == 0) ratio[1] = as_is / fmaxf(shifted, 1e-30f);
+    const float m = near_median64(r, r > 0.f && r < INF, lane);
+    if (lane == 0) {
+        int e = 0;
+        if (m > 0.f && m < INF) (void)frexpf(m, &e);
+        int up = 7 - e;
+        up = up < -100 ? -100 : (up > 100 ? 100 : up);
+        sc->scale = ldexpf(1.f, up);
+        ratio[0] = sc->scale / sc_all->scale;
+        sc->eps_bits = 0u;
+        sc->huge = 0u;
+    }
+}
+
+hipError_t near_make_ordered(const float* X, int n_src, int d, const NearOrder& o, const float* tile_c, const float* tile_r,
+                             const int32_t* tile_first, const float* hn, const NearBuffers& b, hipStream_t s)
+{
+    hipError_t e = near_make(X, n_src, d, o.perm, o.rows, nullptr, b, o.all, nullptr, nullptr, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(near_local_scale_kernel, dim3(1), dim3(64), 0, s, tile_r, o.region, o.tiles, o.local_scale, b.scale, o.all.negh, o.rows, hn, o.perm, o.ratios);
+    NearBuffers bl = b;
+    bl.scale = o.local_scale;
+    bl.shift = const_cast<float*>(tile_c);
+    return near_make(X, n_src, d, o.perm, o.rows, nullptr, bl, o.local, nullptr, nullptr, s, false, nullptr, tile_first);
+}
+
+// Tiles of other regions that a tile meets at most.  Rows with fewer rows of their own cluster than neighbours asked for reach
+// through a cluster's worth of them, with bounds that one pass cannot tighten; their tiles (a handful) are left to the list
+// kernels, which look outwards from the nearest.  1M x 128: with 256 instead, one workgroup each keeps nine launches for 3.5 ms.
+constexpr int CROSS_MOST = 64;
+struct NearOrderedPlan { int waves, panel_tiles, window, nseg, nsub, capl, max_seg, max_parts, sets; size_t per_tile; };
+constexpr int ORDERED_AROUND = 2;          // tiles before and after a panel's own
+static NearOrderedPlan near_ordered_plan(int T, int kk)
+{
+    NearOrderedPlan p{};
+    // workgroups of eight wavefronts share what they stage among 512 queries; smaller ones where there are too few panels
+    p.waves = T >= 1024 ? 8 : (T >= 256 ? 4 : 2);
+    p.panel_tiles = p.waves / 2;
+    p.window = p.panel_tiles + 2 * ORDERED_AROUND;
+    p.nseg = 4;                            // (panels differ in their lists: four shares of each even that out)
+    p.nsub = 2 * p.nseg;
+    p.capl = 128;
+    p.max_seg = 4;
+    p.max_parts = (6 * kk + GROUPS * p.max_seg - 1) / (GROUPS * p.max_seg);
+    if (p.max_parts > 4) p.max_parts = 4;
+    p.sets = p.window > p.max_seg * p.max_parts ? p.window : p.max_seg * p.max_parts;
+    p.per_tile = (size_t)TILE * (8 + (size_t)p.sets * GROUPS * 4 + (size_t)p.nsub * (4 + 8 * (size_t)p.capl)) + 3 * ((size_t)T * 2 + 1024) / (size_t)p.panel_tiles + 64;
+    return p;
+}
+
+size_t near_ordered_batch_bytes(long long rows, int kk)
+{
+    const int T = near_tiles(rows);
+    const NearOrderedPlan p = near_ordered_plan(T, kk);
+    const int most = T < 1024 ? T : 1024;
+    return p.per_tile * (size_t)(most < p.panel_tiles ? p.panel_tiles : most) + 16384;
+}
+
+static bool near_order_ok(const NearOrder& o, int d)
+{
+    return o.gap && o.perm && o.region && o.all.in_order && o.local.in_order && o.all.tiles == o.tiles && o.local.tiles == o.tiles &&
+           o.tiles >= 1 && o.tiles <= 65535 && o.rows <= o.tiles * TILE && near_steps(d) <= REG_STEPS;
+}
+
+// one side of a sweep over lists
+static void near_side(NearSweep& p, const NearOrder& o, const NearBuffers& b, int side, const unsigned short* list, const int32_t* len,
+                      const int32_t* step, bool best)
+{
+    const NearCopy& c = side == 1 ? o.local : o.all;
+    p.qfrag = p.cfrag = c.frag;
+    p.qnegh = c.negh; p.cnegh = best ? c.negh_best : c.negh;
+    p.sc = side == 1 ? o.local_scale : b.scale;
+    p.region = o.region; p.side = side; p.mark = side == 1 ? 0u : MARK;
+    p.list = list; p.list_len = len; p.list_step = step; p.list_stride = near_list_stride(o.tiles);
+}
+
+// k-NN.  What bounds it: the products of the pairs of tiles on the lists (about 1.3 PFLOP/s) and the exact evaluation of what is
+// emitted.  Bounds come from the tiles around a panel first; the tiles within them are listed and, where these are many, every
+// few of them tighten the bounds before the rest is multiplied.  The copy by regions keeps a cluster's distance from the
+// other clusters out of the rounding: without it, 1M x 128 (k = 32) passes several times as many candidates and a third of the
+// panels overflow.  1M x 128: 68 ms with the list kernels, 32 ms; 100k x 64: 2.1 -> 0.8 ms.
+hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const NearBuffers& b, hipStream_t s)
+{
+    const int kk = a.k + 1, T = o.tiles;
+    const NearOrderedPlan plan = near_ordered_plan(T, kk);
+    if (!near_order_ok(o, a.d) || T > b.todo_panels || b.batch_bytes < 16384) return hipErrorInvalidValue;
+    long long bt = (long long)((b.batch_bytes - 16384) / plan.per_tile) / plan.panel_tiles * plan.panel_tiles;
+    if (bt < 1) return hipErrorInvalidValue;
+    if (bt > 1024) bt = 1024;              // (byte offsets of 32 bits into the entries)
+    if (bt > T) bt = T;
+    NearSweep p{};
+    p.c_tiles = T;
+    p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
+    p.kk = kk; p.stride = 1; p.used = T;
+    NearSelect sel{};
+    sel.qnegh = o.all.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
+    sel.region = o.region; sel.negh_local = o.local.negh; sel.sc_local = o.local_scale;
+    sel.Xq = sel.Xc = a.Xq; sel.ids = sel.c_ids = o.perm; sel.n_ids = o.rows;
+    sel.d = a.d; sel.k = a.k; sel.kk = kk; sel.nq = o.rows; sel.nq_rows = sel.nc = a.nc;
+    sel.q_tiles = sel.c_tiles = T; sel.q_in_order = sel.c_in_order = 1; sel.exclude_self = 1;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    const bool vec4 = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.Xq) & 15) == 0;
+    for (int t0 = 0; t0 < T; t0 += (int)bt) {
+        const int t1 = t0 + bt < T ? t0 + (int)bt : T;
+        const int nqb = (t1 - t0) * TILE, panels = (t1 - t0 + plan.panel_tiles - 1) / plan.panel_tiles;
+        const dim3 per_query((unsigned)((nqb + 3) / 4)), per_panel((unsigned)panels);
+        unsigned char* at = b.batch;
+        auto take = [&](size_t bytes) { unsigned char* r = at; at += (bytes + 255) / 256 * 256; return r; };
+        float* bound = reinterpret_cast<float*>(take((size_t)nqb * 4));
+        float* reach = reinterpret_cast<float*>(take((size_t)nqb * 4));
+        float* maxima = reinterpret_cast<float*>(take((size_t)nqb * plan.sets * GROUPS * 4));
+        int32_t* counts = reinterpret_cast<int32_t*>(take((size_t)nqb * plan.nsub * 4));
+        uint2* entries = reinterpret_cast<uint2*>(take((size_t)nqb * plan.nsub * plan.capl * 8));
+        unsigned short* list[3];
+        int32_t *len[3], *step[2];
+        for (int i = 0; i < 3; ++i) list[i] = reinterpret_cast<unsigned short*>(take((size_t)panels * near_list_stride(T) * 2));
+        for (int i = 0; i < 3; ++i) len[i] = reinterpret_cast<int32_t*>(take((size_t)panels * 4));
+        for (int i = 0; i < 2; ++i) step[i] = reinterpret_cast<int32_t*>(take((size_t)panels * 4));
+        p.q_tile0 = t0; p.q_tile1 = t1; p.nq_batch = nqb;
+        p.maxima = maxima; p.groups = GROUPS; p.capl = plan.capl; p.append = 0;
+        sel.nq_batch = nqb; sel.q0 = t0 * TILE;
+        auto bounds = [&](int sets, const int32_t* steps_of) {
+            hipLaunchKernelGGL(near_bounds_kernel, per_query, dim3(256), 0, s, maxima, sets, 5, nqb, t0 * TILE, kk, o.all.negh, b.scale, p.e, p.nu,
+                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale);
+        };
+        NearList l{};
+        l.gap = o.gap; l.T = T; l.region = o.region; l.reach = reach; l.n_pos = T * TILE; l.q0 = t0 * TILE; l.nq = nqb;
+        l.panel_queries = plan.panel_tiles * TILE;
+        l.list_stride = near_list_stride(T); l.kk = kk;
+        l.cost = 16.0 * p.steps * 1.28e-5 * TILE;
+        auto make_list = [&](int what, int from, int to, int32_t* step_to) {
+            l.what = what; l.from = from >= 0 ? list[from] : nullptr; l.from_len = from >= 0 ? len[from] : nullptr;
+            l.list = list[to]; l.list_len = len[to]; l.list_step = step_to;
+            hipLaunchKernelGGL(near_list_kernel, per_panel, dim3(256), 0, s, l);
+        };
+        hipError_t e = hipSuccess;
+        // 1. the tiles around every panel: first bounds (of each query in the copy that holds its region, or in the other)
+        hipLaunchKernelGGL(near_window_kernel, dim3((unsigned)((panels + 63) / 64)), dim3(64), 0, s, t0, plan.panel_tiles, t1, T, ORDERED_AROUND,
+                           list[2], len[2], near_list_stride(T), panels);
+        p.nseg = 1; p.parts = plan.window;
+        for (int side = 1; side <= 2 && e == hipSuccess; ++side) {
+            near_side(p, o, b, side, list[2], len[2], nullptr, false);
+            e = near_launch_sweep<NEAR_MAXIMA, false, true>(p, plan.waves, s);
+        }
+        if (e != hipSuccess) return e;
+        bounds(plan.window, nullptr);
+        // 2. the tiles within them, and where these are many, better bounds from a sample of them
+        make_list(LIST_LOCAL, -1, 0, step[0]);
+        p.nseg = plan.max_seg; p.parts = plan.max_parts;
+        near_side(p, o, b, 1, list[0], len[0], step[0], false);
+        e = near_launch_sweep<NEAR_MAXIMA, false, true>(p, plan.waves, s);
+        if (e != hipSuccess) return e;
+        bounds(plan.max_seg * plan.max_parts, step[0]);
+        // 3. emit and select
+        l.tile_steps = o.tile_steps;
+        make_list(LIST_LOCAL, 0, 2, nullptr);
+        l.most = CROSS_MOST; l.todo = b.todo; l.todo_mark = b.todo_mark;
+        make_list(LIST_CROSS, -1, 1, nullptr);
+        p.reach = reach; p.counts = counts; p.entries = entries; p.nsub = plan.nsub;
+        p.nseg = plan.nseg;
+        near_side(p, o, b, 1, list[2], len[2], nullptr, false);
+        e = near_launch_sweep<NEAR_EMIT, false, true>(p, plan.waves, s);
+        if (e != hipSuccess) return e;
+        p.append = 1;
+        near_side(p, o, b, 2, list[1], len[1], nullptr, false);
+        e = near_launch_sweep<NEAR_EMIT, false, true>(p, plan.waves, s);
+        if (e != hipSuccess) return e;
+        p.reach = nullptr;
+        sel.entries = entries; sel.counts = counts; sel.nsub = plan.nsub; sel.capl = plan.capl;
+        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
+        else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
 // ---------------------------------------------------------------------------------------------- connection rounds
 struct NearRange {
-    const unsigned long long* best_at; const float* negh; const int32_t* qcolour; const NearScale* sc; float e, nu; int steps, d;
-    const float* X; const int32_t* colour;
-    int n, n_rows; const int32_t* rows; int c_tiles, c_in_order;
-    uint32_t* threshold;
+    unsigned long long* best_at; const float *negh, *negh_local; const NearScale *sc, *sc_local;
+    const float* X; const int32_t* colour; int d;
+    int n, n_rows; const int32_t* rows; const int32_t* qpos; int c_tiles, c_in_order; const int32_t* c_ids; int n_ids;
+    uint32_t* threshold; const uint32_t* threshold0;
+    int32_t* edge_at;
     int32_t* out_idx; float *out_dist, *out_low; int32_t* evaluated;
-    int32_t *rows_left, *slot_left, *count_left; float* bound_left;
+    int32_t *rows_left, *slot_left, *pos_left, *counts_left, *count_left; float* reach_left;
 };
 
-// One wavefront per query: of the 16 candidates one of which showed the largest product value, the nearest of another
-// colour, exactly.  An edge of the query's component, which lowers the component's threshold.
+__global__ void __launch_bounds__(256) near_range_clear_kernel(NearRange p)
+{
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= p.n) return;
+    p.best_at[q] = ~0ull;
+    p.edge_at[q] = -1;
+    p.out_idx[q] = -1;
+    p.out_dist[q] = INF;
+}
+
+// One wavefront per query: of the 16 candidates about the nearest of which is in best_at, the nearest of another colour,
+// exactly.  An edge of the query's component, which lowers the component's threshold.
 template <bool VEC4>
 __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
     if (q >= p.n) return;
     const unsigned long long best = p.best_at[q];
-    const int c = p.qcolour[q], row = p.rows[q];
+    const int row = p.rows[q];
+    if (p.edge_at && (best == ~0ull || p.edge_at[q] == (int)(unsigned int)best)) return;      // as before
+    const bool fine_row = (unsigned int)row < (unsigned int)p.n_rows;
+    const int c = fine_row ? p.colour[row] : -1;
     unsigned long long key = ~0ull;
-    if (best != 0ull && fabsf(p.negh[q]) < INF && (unsigned int)c < (unsigned int)p.n_rows && (unsigned int)row < (unsigned int)p.n_rows) {
+    if (best != ~0ull && (unsigned int)c < (unsigned int)p.n_rows) {
         const int grp = lane >> 3, g = lane & 7;
         const float* xa = p.X + (size_t)row * p.d;
         v4f qa[4];
@@ -1446,7 +2058,8 @@ __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const int j = half * 8 + grp;
-            const long long cand = near_row((int)(unsigned int)best + 8 * (j >> 2) + (j & 3), p.c_tiles, p.c_in_order);
+            long long cand = near_row((int)(unsigned int)best + 8 * (j >> 2) + (j & 3), p.c_tiles, p.c_in_order);
+            if (p.c_ids) cand = cand < p.n_ids ? (long long)p.c_ids[cand] : -1;
             const bool real = cand >= 0 && cand < p.n_rows;
             const bool fine = real && p.colour[real ? cand : 0] != c;
             const float dist = near_exact<VEC4>(qa, xa, p.X + (size_t)(fine ? cand : row) * p.d, p.d, g);
@@ -1460,6 +2073,11 @@ __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
         }
     }
     if (lane == 0) {
+        if (p.edge_at) {
+            p.edge_at[q] = (int)(unsigned int)best;
+            // (an edge found earlier may be the shorter one all the same)
+            if (key == ~0ull || !(__uint_as_float((unsigned int)(key >> 32)) < p.out_dist[q])) return;
+        }
         p.out_idx[q] = key == ~0ull ? -1 : (int32_t)(unsigned int)key;
         p.out_dist[q] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
         if (key != ~0ull) min_into(&p.threshold[c], (uint32_t)(key >> 32));
@@ -1471,36 +2089,48 @@ __global__ void __launch_bounds__(256) near_split_kernel(NearRange p)
 {
     const int q = blockIdx.x * 256 + threadIdx.x;
     bool left = false;
-    float bound = LOWEST;
-    int row = -1;
+    float reach = INF;
+    int row = -1, pos = 0;
     if (q < p.n) {
-        const unsigned int best = (unsigned int)(p.best_at[q] >> 32);
-        const float nh = p.negh[q], h = -nh;
-        const int c = p.qcolour[q];
+        pos = p.qpos ? p.qpos[q] : q;
+        const float nh = p.negh[pos];
         row = p.rows[q];
+        const int c = (unsigned int)row < (unsigned int)p.n_rows ? p.colour[row] : -1;
         float lower = 0.f;
         if (nh == -INF || c < 0 || c >= p.n_rows) lower = INF;          // no row
-        else if (nh == INF) left = true;                                // (ends up with the list kernels)
+        else if (nh == INF || (p.negh_local && p.negh_local[pos] == INF)) left = true;      // (ends up with the list kernels)
         else {
-            const NearBoundArgs a = near_args(p.sc, p.steps, p.d, p.e, p.nu);
-            const float f = __uint_as_float(p.threshold[c]), f2 = f * p.sc->scale * p.sc->scale;
-            if (f2 < INF) bound = fmaxf(bound, near_bound_at(f2, h, a));
+            reach = __uint_as_float(p.threshold[c]);
             // nothing found: no other colour among the rows that float16 holds
-            if (p.sc->huge == 0u) lower = best != 0u ? near_lower_from(from_ordered(best), h, a) / p.sc->scale / p.sc->scale : INF;
-            left = lower <= f && lower < INF;
+            if (p.sc->huge == 0u && (!p.sc_local || p.sc_local->huge == 0u)) {
+                const unsigned long long best = p.best_at[q];
+                lower = best == ~0ull ? INF : __uint_as_float((unsigned int)(best >> 32));
+            }
+            left = lower <= reach && lower < INF;
+            // (the tiles left out hold only rows beyond the threshold they were left out by, which is not below `reach`)
+            if (p.threshold0) lower = fminf(lower, __uint_as_float(p.threshold0[c]));
         }
         p.out_low[q] = lower;
         if (!left && p.evaluated) p.evaluated[q] = 0;
     }
     const int at = block_append<256>(left, p.count_left);
-    if (left && at < p.n) { p.rows_left[at] = row; p.slot_left[at] = q; p.bound_left[at] = bound; }
+    if (left && at < p.n) {
+        p.rows_left[at] = row; p.slot_left[at] = q; p.reach_left[at] = reach;
+        if (p.pos_left) { p.pos_left[at] = pos; p.counts_left[at] = 0; }
+    }
 }
 
-// Connection rounds.  One pass over all candidates leaves per query the largest product value and the 16 candidates it came
-// from.  Bound by that pass: the search that follows is left with a query or two per component (10 of 250 000), where every
-// query used to go through it.  250k x 784, ten components: 346 -> 240 ms per call (a pass takes 99 ms); 100k x 64: 11.6 ->
-// 9.9 ms.  Without the exact edge of every query (only an interval for its distance), a component had no threshold in the
-// next round and queried all its rows again: 324 ms.
+static void near_edges(const NearRange& r, bool vec4, hipStream_t s)
+{
+    if (vec4) hipLaunchKernelGGL((near_edge_kernel<true>), dim3((unsigned)((r.n + 3) / 4)), dim3(256), 0, s, r);
+    else hipLaunchKernelGGL((near_edge_kernel<false>), dim3((unsigned)((r.n + 3) / 4)), dim3(256), 0, s, r);
+}
+
+// Connection rounds.  One pass over all candidates leaves per query the distance below which there is none and the 16
+// candidates about the nearest.  Bound by that pass: the search that follows is left with a query or two per component (10 of
+// 250 000), where every query used to go through it.  250k x 784, ten components: 346 -> 240 ms per call (a pass takes
+// 99 ms); 100k x 64: 11.6 -> 9.9 ms.  Without the exact edge of every query (only an interval for its distance), a component
+// had no threshold in the next round and queried all its rows again: 324 ms.
 hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
 {
     if (!q.in_order || !q.colour || !c.colour || !q.best_at || !q.count || !c.negh_best || (a.n + 127) / 128 > b.todo_panels) return hipErrorInvalidValue;
@@ -1517,14 +2147,13 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
     e = near_launch_sweep<NEAR_BLOCK, true>(p, plan.waves, s);
     if (e != hipSuccess) return e;
     NearRange r{};
-    r.X = a.X; r.colour = a.colour; r.c_tiles = c.tiles; r.c_in_order = c.in_order;
-    r.best_at = q.best_at; r.negh = q.negh; r.qcolour = q.colour; r.sc = b.scale; r.e = p.e; r.nu = p.nu; r.steps = p.steps; r.d = a.d;
+    r.X = a.X; r.colour = a.colour; r.c_tiles = c.tiles; r.c_in_order = c.in_order; r.d = a.d;
+    r.best_at = q.best_at; r.negh = q.negh; r.sc = b.scale;
     r.n = a.n; r.n_rows = a.n_rows; r.rows = a.rows; r.threshold = a.threshold;
     r.out_idx = a.out_idx; r.out_dist = a.out_dist; r.out_low = a.out_low; r.evaluated = a.evaluated;
-    r.rows_left = a.rows_left; r.slot_left = a.slot_left; r.bound_left = a.bound_left; r.count_left = b.todo + 1;
+    r.rows_left = a.rows_left; r.slot_left = a.slot_left; r.reach_left = a.reach_left; r.count_left = b.todo + 1;
     const bool vec4 = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
-    if (vec4) hipLaunchKernelGGL((near_edge_kernel<true>), dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, s, r);
-    else hipLaunchKernelGGL((near_edge_kernel<false>), dim3((unsigned)((a.n + 3) / 4)), dim3(256), 0, s, r);
+    near_edges(r, vec4, s);
     hipLaunchKernelGGL(near_split_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, r);
     // the copy of the queries now holds those that are left
     e = near_make(a.X, a.n_rows, a.d, a.rows_left, a.n, a.colour, b, q, nullptr, nullptr, s, false, r.count_left);
@@ -1536,6 +2165,7 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
     const int waves = wide ? plan.waves : (plan.waves > 2 ? plan.waves / 2 : 2);
     p.slots = (waves == 8 ? 1 : 2) * near_cus();
     p.counts = q.count; p.capl = plan.capl;
+    p.reach = a.reach_left;
     NearSelect sel{};
     sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
     sel.Xq = sel.Xc = a.X; sel.q_rows = a.rows_left; sel.slot = a.slot_left; sel.n_dev = r.count_left;
@@ -1550,11 +2180,142 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
         p.q_tile0 = t0; p.q_tile1 = t0 + plan.batch_tiles < q.tiles ? t0 + plan.batch_tiles : q.tiles;
         const int nqb = (p.q_tile1 - t0) * TILE;
         p.nq_batch = sel.nq_batch = nqb; sel.q0 = t0 * TILE;
-        p.bound = a.bound_left + (size_t)t0 * TILE;
         e = near_launch_sweep<NEAR_NEAREST, true>(p, waves, s);
         if (e != hipSuccess) return e;
         if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
         else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
+        e = hipGetLastError();
+        if (e != hipSuccess) return e;
+    }
+    return hipSuccess;
+}
+
+size_t near_linked_batch_bytes(long long rows)
+{
+    const size_t T = (size_t)near_tiles(rows);
+    return 256 * 2 * (T * 2 + 256) + (size_t)128 * 128 * 256 * 8 + 65536;
+}
+
+// The same in a row order: the queries (rows, qpos: ascending positions) meet the tiles only whose distance does not exceed their
+// component's threshold, which a pass over a few of the nearest tiles of other colours sets first.  Bound by the products of
+// the listed pairs (half of the time) and the lists.  1M x 128, five rounds of 1.3 million queries: 50 ms with the list kernels
+// (128 queries share what they stage, three products), 21 ms; with lists in equal shares per panel instead of equal items 36 ms.
+hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBuffers& b, hipStream_t s)
+{
+    const int T = o.tiles;
+    if (!near_order_ok(o, a.d) || !a.qpos || T > b.todo_panels || b.batch_bytes < near_linked_batch_bytes(o.rows) || !o.all.colour || !o.tile_colour)
+        return hipErrorInvalidValue;
+    // panels of 512 queries share what they stage; smaller ones where there are too few of them
+    const int waves = a.n >= 131072 ? 8 : 4, panel_queries = 64 * waves;
+    const size_t per_panel = 2 * ((size_t)near_list_stride(T) * 2 + 64);       // two lists, their lengths and items
+    long long batch_panels = (long long)((b.batch_bytes - 16384) / per_panel);
+    if (batch_panels > 8192) batch_panels = 8192;
+    NearSweep p{};
+    p.qcolour = p.ccolour = o.all.colour; p.c_tiles = T;
+    p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
+    p.stride = 1; p.used = T; p.kk = 1;
+    p.qpos = a.qpos; p.n_q = a.n; p.best_at = a.best_at;
+    NearRange r{};
+    r.X = a.X; r.colour = a.colour; r.c_tiles = T; r.c_in_order = 1; r.c_ids = o.perm; r.n_ids = o.rows; r.d = a.d;
+    r.best_at = a.best_at; r.negh = o.all.negh; r.negh_local = o.local.negh; r.sc = b.scale; r.sc_local = o.local_scale;
+    r.n = a.n; r.n_rows = a.n_rows; r.rows = a.rows; r.qpos = a.qpos; r.threshold = a.threshold;
+    r.edge_at = a.edge_at;
+    r.out_idx = a.out_idx; r.out_dist = a.out_dist; r.out_low = a.out_low; r.evaluated = a.evaluated;
+    r.rows_left = a.rows_left; r.slot_left = a.slot_left; r.pos_left = a.pos_left; r.counts_left = a.counts_left; r.reach_left = a.reach_left;
+    r.count_left = b.todo + 1;
+    const bool vec4 = a.d % 4 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15) == 0;
+    const dim3 per_row((unsigned)((a.n + 255) / 256));
+    hipLaunchKernelGGL(near_range_clear_kernel, per_row, dim3(256), 0, s, r);
+    hipLaunchKernelGGL(near_todo_clear_kernel, dim3(64), dim3(256), 0, s, b.todo, 2 + 2 * b.todo_panels);
+    NearList l{};
+    l.gap = o.gap; l.T = T; l.region = o.region; l.colour = o.all.colour; l.threshold = a.threshold; l.n_rows = a.n_rows; l.tile_colour = o.tile_colour;
+    l.pos = a.qpos; l.n_pos = o.rows; l.list_stride = near_list_stride(T);
+    hipError_t e = hipSuccess;
+    for (int pass = 0; pass < 2; ++pass) {
+        for (long long q0 = 0; q0 < a.n; q0 += batch_panels * panel_queries) {
+            const int nq = (int)(a.n - q0 < batch_panels * panel_queries ? a.n - q0 : batch_panels * panel_queries);
+            const int panels = (nq + panel_queries - 1) / panel_queries;
+            unsigned char* at = b.batch;
+            auto take = [&](size_t bytes) { unsigned char* x = at; at += (bytes + 255) / 256 * 256; return x; };
+            unsigned short *list[2];
+            int32_t *len[2], *items[2];
+            for (int i = 0; i < 2; ++i) list[i] = reinterpret_cast<unsigned short*>(take((size_t)panels * near_list_stride(T) * 2));
+            for (int i = 0; i < 2; ++i) len[i] = reinterpret_cast<int32_t*>(take((size_t)panels * 4));
+            for (int i = 0; i < 2; ++i) items[i] = reinterpret_cast<int32_t*>(take((size_t)(panels + 1) * 4));
+            l.q0 = (int)q0; l.nq = nq; l.panel_queries = panel_queries;
+            for (int i = 0; i <= pass; ++i) {
+                l.what = i ? LIST_CROSS : LIST_LOCAL; l.list = list[i]; l.list_len = len[i];
+                if (pass) hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels), dim3(256), 0, s, l);
+                else hipLaunchKernelGGL(near_first_kernel, dim3((unsigned)panels), dim3(256), 0, s, l);
+                hipLaunchKernelGGL(near_items_kernel, dim3(1), dim3(1024), 0, s, len[i], panels, items[i], panel_queries, nq,
+                                   pass ? o.tile_steps : nullptr);
+            }
+            p.q_tile0 = (int)(q0 / TILE); p.q_tile1 = (int)((q0 + nq + TILE - 1) / TILE); p.nq_batch = nq;
+            p.panels = panels; p.nseg = 1;
+            for (int side = 1; side <= 2; ++side) {
+                near_side(p, o, b, side, list[pass ? side - 1 : 0], len[pass ? side - 1 : 0], nullptr, true);
+                p.items = items[pass ? side - 1 : 0];
+                e = near_launch_sweep<NEAR_BLOCK, true, true>(p, waves, s);
+                if (e != hipSuccess) return e;
+            }
+        }
+        near_edges(r, vec4, s);
+        if (!pass) {
+            // the thresholds that the lists are made by
+            e = hipMemcpyAsync(a.threshold0, a.threshold, (size_t)a.n_rows * 4, hipMemcpyDeviceToDevice, s);
+            if (e != hipSuccess) return e;
+        }
+    }
+    r.threshold0 = a.threshold0;
+    hipLaunchKernelGGL(near_split_kernel, per_row, dim3(256), 0, s, r);
+    // the few that are left
+    constexpr int capl = 256, left_waves = 4, left_queries = 256, left_slices = 16;
+    l.pos = a.pos_left; l.n_dev = r.count_left; l.panel_queries = left_queries;
+    p.qpos = a.pos_left; p.n_dev = r.count_left;
+    p.counts = a.counts_left; p.capl = capl; p.reach = a.reach_left;
+    NearSelect sel{};
+    sel.qnegh = o.all.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
+    sel.region = o.region; sel.negh_local = o.local.negh; sel.sc_local = o.local_scale;
+    sel.Xq = sel.Xc = a.X; sel.q_rows = a.rows_left; sel.slot = a.slot_left; sel.n_dev = r.count_left; sel.qpos = a.pos_left;
+    sel.c_ids = o.perm; sel.n_ids = o.rows;
+    sel.d = a.d; sel.k = sel.kk = 1; sel.nq = a.n; sel.nq_rows = sel.nc = a.n_rows;
+    sel.q_tiles = sel.c_tiles = T; sel.q_in_order = sel.c_in_order = 1;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    sel.capl = capl; sel.nsub = 1; sel.by_position = 1; sel.counts = a.counts_left;
+    const size_t per_left = per_panel + (size_t)left_queries * capl * 8;
+    long long left_panels = (long long)((b.batch_bytes - 16384) / per_left);
+    if (left_panels > 8192) left_panels = 8192;
+    for (long long q0 = 0; q0 < a.n; q0 += left_panels * left_queries) {
+        const int nq = (int)(a.n - q0 < left_panels * left_queries ? a.n - q0 : left_panels * left_queries);
+        const int panels = (nq + left_queries - 1) / left_queries;
+        unsigned char* at = b.batch;
+        auto take = [&](size_t bytes) { unsigned char* x = at; at += (bytes + 255) / 256 * 256; return x; };
+        unsigned short *list[2];
+        int32_t *len[2], *items[2];
+        for (int i = 0; i < 2; ++i) list[i] = reinterpret_cast<unsigned short*>(take((size_t)panels * near_list_stride(T) * 2));
+        for (int i = 0; i < 2; ++i) len[i] = reinterpret_cast<int32_t*>(take((size_t)panels * 4));
+        for (int i = 0; i < 2; ++i) items[i] = reinterpret_cast<int32_t*>(take((size_t)(panels + 1) * 4));
+        p.entries = reinterpret_cast<uint2*>(take((size_t)panels * left_queries * capl * 8));
+        l.q0 = (int)q0; l.nq = nq;
+        hipLaunchKernelGGL(near_todo_clear_kernel, dim3(8), dim3(256), 0, s, len[0], (long long)(reinterpret_cast<unsigned char*>(items[0]) - reinterpret_cast<unsigned char*>(len[0])) / 4);
+        for (int i = 0; i < 2; ++i) {
+            l.what = i ? LIST_CROSS : LIST_LOCAL; l.list = list[i]; l.list_len = len[i];
+            hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels, left_slices), dim3(256), 0, s, l);
+            hipLaunchKernelGGL(near_items_kernel, dim3(1), dim3(1024), 0, s, len[i], panels, items[i], left_queries, nq, static_cast<unsigned long long*>(nullptr));
+        }
+        p.panels = panels;
+        p.q_tile0 = (int)(q0 / TILE); p.q_tile1 = p.q_tile0 + panels * (left_queries / TILE); p.nq_batch = nq;
+        for (int side = 1; side <= 2; ++side) {
+            near_side(p, o, b, side, list[side - 1], len[side - 1], nullptr, false);
+            p.items = items[side - 1];
+            e = near_launch_sweep<NEAR_NEAREST, true, true>(p, left_waves, s);
+            if (e != hipSuccess) return e;
+        }
+        sel.entries = p.entries;
+        sel.nq_batch = panels * left_queries; sel.q0 = (int)q0;
+        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
+        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }

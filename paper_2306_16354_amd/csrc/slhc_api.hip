@@ -218,6 +218,74 @@ __global__ void __launch_bounds__(256) k_region_last(const int32_t* __restrict__
         for (; u <= t; ++u) last[u] = t;
     }
 }
+// local[t], centre[t] = the tile's region and that one's first tile where it is at least REGION_TILES long, else -1; *pairs += the tiles of t's region
+constexpr int REGION_TILES = 8;
+__global__ void __launch_bounds__(256) k_region_local(const int32_t* __restrict__ region, const int32_t* __restrict__ first,
+                                                      const int32_t* __restrict__ last, int T, int32_t* __restrict__ local,
+                                                      int32_t* __restrict__ centre, unsigned long long* __restrict__ pairs)
+{
+    const int t = blockIdx.x * 256 + threadIdx.x;
+    int len = 0;
+    if (t < T) {
+        len = last[t] - first[t] + 1;
+        local[t] = len >= REGION_TILES ? region[t] : -1;
+        centre[t] = len >= REGION_TILES ? first[t] : -1;
+    }
+    unsigned long long sum = (unsigned long long)(len > 0 ? len : 0);
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) sum += __shfl_xor(sum, o);
+    if ((threadIdx.x & 63) == 0 && sum) atomicAdd(pairs, sum);
+}
+
+// The listed rows in the order of their positions: slot[position] >= 0 marks them; one wavefront per tile of 128 positions.
+__global__ void __launch_bounds__(256) k_slot_counts(const int32_t* __restrict__ slot, int n, int T, int32_t* __restrict__ count)
+{
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (t >= T) return;
+    int c = 0;
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int p = t * 128 + h * 64 + lane;
+        c += __popcll(__ballot(p < n && slot[p] >= 0));
+    }
+    if (lane == 0) count[t] = c;
+}
+__global__ void __launch_bounds__(1024) k_slot_offsets(int32_t* __restrict__ count, int T)
+{
+    __shared__ int sum[1024];
+    const int tid = threadIdx.x, per = (T + 1023) / 1024;
+    const int t0 = tid * per < T ? tid * per : T, t1 = t0 + per < T ? t0 + per : T;
+    int c = 0;
+    for (int t = t0; t < t1; ++t) c += count[t];
+    sum[tid] = c;
+    __syncthreads();
+    for (int off = 1; off < 1024; off <<= 1) {
+        const int v = tid >= off ? sum[tid - off] : 0;
+        __syncthreads();
+        sum[tid] += v;
+        __syncthreads();
+    }
+    int at = sum[tid] - c;
+    for (int t = t0; t < t1; ++t) { const int v = count[t]; count[t] = at; at += v; }
+}
+__global__ void __launch_bounds__(256) k_slot_rows(int32_t* __restrict__ slot, const int32_t* __restrict__ perm, int n, int T,
+                                                   const int32_t* __restrict__ offset, int m, int32_t* __restrict__ rows,
+                                                   int32_t* __restrict__ pos)
+{
+    const int t = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (t >= T) return;
+    int at = offset[t];
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+        const int p = t * 128 + h * 64 + lane;
+        const bool marked = p < n && slot[p] >= 0;
+        const unsigned long long mask = __ballot(marked);
+        const int i = at + __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)mask, 0u));
+        if (marked && i < m) { rows[i] = perm[p]; pos[i] = p; slot[p] = i; }
+        at += __popcll(mask);
+    }
+}
+
 // out[row] = the smallest lower bound in row `row` of the table of tile pairs among the tiles of other regions
 // (+inf: none; NaN entries mark tiles that are never needed)
 __global__ void __launch_bounds__(256) k_region_other_min(const float* __restrict__ tile_gap, const int32_t* __restrict__ region,
@@ -523,7 +591,8 @@ struct NearWs {
     slhc::NearBuffers b{};
     bool ok = false;
     // `most`: where the workspace ends (0: no limit); the batch takes what is left of it
-    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = 0)
+    // `ordered`: rows of a padded row order that is searched too (0: none)
+    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = 0, int64_t ordered = 0)
     {
         ok = slhc::near_supported(d);
         if (!ok) return;
@@ -544,10 +613,11 @@ struct NearWs {
         if (nq > 0) copy(q, nq); else q = c;
         if (nq > 0 && coloured) q.best_at = w.take<unsigned long long>((size_t)q.tiles * 128);
         const int64_t queries = nq > 0 ? nq : nc;
-        b.todo_panels = (queries + 127) / 128;
+        b.todo_panels = (std::max(queries, ordered) + 127) / 128;
         b.todo = w.take<int32_t>((size_t)(2 + 2 * b.todo_panels));
         b.todo_mark = b.todo + 2 + b.todo_panels;
         b.batch_bytes = slhc::near_batch_bytes(queries, nc, d, kk);
+        if (ordered) b.batch_bytes = std::max({b.batch_bytes, slhc::near_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
         if (most && w.off + b.batch_bytes > most) b.batch_bytes = most > w.off ? most - w.off : 0;
         if (b.batch_bytes < slhc::near_least_batch_bytes(queries, nc, d, kk)) { ok = false; return; }
         b.batch = w.take<unsigned char>(b.batch_bytes);
@@ -561,12 +631,15 @@ struct OrderWs {
     // a second split copy, every tile relative to the centre of the first tile of its region, with its half norms;
     // region number, first tile and boundary flag per tile (see run_knn; nullptr: the pruned sweeps keep float32 products)
     float *Xs_local, *hs_local, *region_other_min;
-    int32_t *tile_region, *tile_first, *tile_last, *tile_boundary;
+    int32_t *tile_region, *tile_first, *tile_last, *tile_boundary, *tile_local;
     int32_t *pid, *perm, *inv, *colour_s, *qslot, *tile_colour, *tile_list, *counts, *rank, *shift, *far_count;
     int32_t *n_src, *n_dst;
     uint32_t *tmp_a, *tmp_b, *tmp_c;
-    slhc::NearCopy near_p{};          // float16 copy of the pivots, and scratch of the assignment
+    slhc::NearCopy near_all{}, near_local{};      // float16 copies of the rows in this order (see NearOrder)
+    slhc::NearScale* local_scale;
+    slhc::NearCopy near_p{};          // that of the pivots, and scratch of the assignment
     unsigned long long* best_at;
+    int32_t* near_colour;
     void* sort_temp; size_t sort_temp_bytes;
     void* nested_ws; size_t nested_bytes;
     int P1, Pmax, Tmax;
@@ -587,13 +660,13 @@ struct OrderWs {
         Xs = c.take<float>(nm * d); hs = c.take<float>(nm);
         Xs_split = nullptr; hs_split = nullptr;
         if (split_products_ok(d)) { Xs_split = c.take<float>(nm * d); hs_split = c.take<float>(nm); }
-        Xs_local = nullptr; hs_local = nullptr; region_other_min = nullptr; tile_region = nullptr; tile_first = nullptr; tile_last = nullptr; tile_boundary = nullptr;
+        Xs_local = nullptr; hs_local = nullptr; region_other_min = nullptr;
+        tile_region = c.take<int32_t>((size_t)Tmax); tile_first = c.take<int32_t>((size_t)Tmax);
+        tile_last = c.take<int32_t>((size_t)Tmax);
+        tile_boundary = c.take<int32_t>((size_t)Tmax); tile_local = c.take<int32_t>((size_t)Tmax);
         if (split_products_ok(d) && d <= 128) {
             Xs_local = c.take<float>(nm * d); hs_local = c.take<float>(nm);
-            tile_region = c.take<int32_t>((size_t)Tmax); tile_first = c.take<int32_t>((size_t)Tmax);
-            tile_last = c.take<int32_t>((size_t)Tmax);
             region_other_min = c.take<float>((size_t)Tmax);
-            tile_boundary = c.take<int32_t>((size_t)Tmax);
         }
         tile_c = c.take<float>((size_t)Tmax * d); tile_r = c.take<float>((size_t)Tmax);
         int grid = slhc::sweep_grid_limit();
@@ -604,6 +677,13 @@ struct OrderWs {
         pid = c.take<int32_t>(n); perm = c.take<int32_t>(nm); inv = c.take<int32_t>(n); colour_s = c.take<int32_t>(nm);
         qslot = c.take<int32_t>(nm); tile_colour = c.take<int32_t>((size_t)Tmax); tile_list = c.take<int32_t>((size_t)Tmax);
         counts = c.take<int32_t>(pm); rank = c.take<int32_t>(pm); shift = c.take<int32_t>(pm); far_count = c.take<int32_t>(64);
+        for (slhc::NearCopy* x : {&near_all, &near_local}) {
+            x->in_order = true;
+            x->frag = c.take<unsigned char>(slhc::near_frag_bytes(Nmax, d));
+            x->negh = c.take<float>((size_t)Tmax * 128); x->negh_best = c.take<float>((size_t)Tmax * 128);
+        }
+        near_colour = c.take<int32_t>((size_t)Tmax * 128);
+        local_scale = c.take<slhc::NearScale>(1);
         near_p.tiles = slhc::near_tiles(Pmax);
         near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
         near_p.negh = c.take<float>((size_t)near_p.tiles * 128);
@@ -639,6 +719,8 @@ struct KnnWs {
     NearWs near;                     // every-tile sweeps in half precision
     bool near_done = false;          // ... made the lists of this call
     bool near_ready = false;         // the float16 copy of X is made
+    bool near_order_ready = false;   // those of the row order are
+    bool regions_ready = false;
     bool split_ready = false;        // filled in this call
     bool order_split_ready = false;  // likewise the split copy of the reordered rows
     bool offset_heavy = false;       // the rows' norms are mostly a common offset (see run_knn): split products everywhere
@@ -673,7 +755,7 @@ struct KnnWs {
         has_order = with_order && prunable(N, d);
         if (has_order) order.carve(c, N, d);
         // (the queries' copy and the colours serve the every-tile connection sweeps)
-        if (k > 0) near.carve(c, N, N, d, k + 1, true);
+        if (k > 0) near.carve(c, N, N, d, k + 1, true, 0, has_order ? order.Nmax : 0);
         bytes = c.off;
     }
 };
@@ -993,6 +1075,47 @@ int run_knn_near(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_i
     return SLHC_OK;
 }
 
+slhc::NearOrder near_order_of(const OrderWs& o)
+{
+    slhc::NearOrder n{};
+    n.gap = o.tile_gap; n.tiles = (o.Ns + 127) / 128; n.perm = o.perm; n.rows = o.Ns;
+    n.region = o.tile_local; n.all = o.near_all; n.local = o.near_local; n.local_scale = o.local_scale;
+    n.all.tiles = n.local.tiles = n.tiles; n.all.rows = n.local.rows = o.Ns;
+    n.tile_colour = o.tile_colour;
+    return n;
+}
+// Pruned k-NN searches go to the half-precision engine where a tile's region holds this many tiles on average: below it (clusters
+// of a tile or two) a panel of 512 queries and the tiles around it are mostly pairs that nobody needs.  2M x 32 in clusters of
+// 100 rows: list kernels 4.7 ms, 22 ms; 100k x 64 in clusters of 2000 (16 tiles): 2.1 ms, 0.8 ms.
+constexpr unsigned long long NEAR_REGION_TILES = 12;
+// Connection rounds go there too unless the clusters are tight against their distances: a row of another cluster is then known
+// up to a few 1e-4 of the spread of all rows, and where that is as much as a cluster's radius every row of a component may be the
+// one that is nearest (2M x 32 in clusters of 100 rows, a thousand radii apart: all rows are left to be searched, 57 ms of
+// rounds against the list kernels' 30).  The spread is about 0.6 sqrt(d) times the largest deviation of a column, so the line is
+// drawn where the rounding of two rows reaches a quarter of the radius.
+constexpr float NEAR_LINK_SPREAD = 360.f;
+
+// Pruned searches by the half-precision engine, where the table of tile pairs exists; the flags that ask for a form of the
+// list kernels' sweeps get those.
+bool near_ordered(const KnnWs& ws, uint32_t flags)
+{
+    return near_wanted(ws.near, flags) && ws.has_order && ws.order.tile_gap &&
+           !(flags & (SLHC_NO_TILE_TABLE | SLHC_ONE_SHIFT | SLHC_SPLIT_ROUNDS | SLHC_SPLIT_SCANS));
+}
+
+// The regions of the row order: tiles are cut where consecutive centres part (see run_knn).
+int make_regions(const OrderWs& o, int32_t d, hipStream_t stream)
+{
+    const int T = (o.Ns + 127) / 128;
+    hipLaunchKernelGGL(k_region_boundaries, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, stream, o.tile_c, o.tile_r, T, d,
+                       o.tile_boundary);
+    hipLaunchKernelGGL(k_region_scan, dim3(1), dim3(1024), 0, stream, o.tile_boundary, T, o.tile_region, o.tile_first);
+    hipLaunchKernelGGL(k_region_last, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, stream, o.tile_boundary, o.tile_first, T,
+                       o.tile_last);
+    HIP_TRY(hipGetLastError());
+    return SLHC_OK;
+}
+
 int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist,
             KnnWs& ws, hipStream_t stream, uint32_t flags, bool* pruned_out = nullptr,
             EventPair* ev_norm = nullptr, EventPair* ev_order = nullptr, EventPair* ev_sweep = nullptr)
@@ -1017,30 +1140,35 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
     if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->b, stream));
     const bool prune = (flags & SLHC_PRUNE) && ws.has_order;
     if (pruned_out) *pruned_out = prune;
+    const bool split = prune && ws.Xsplit && ws.hn_split && !(flags & SLHC_FP32_FILTER);
+    // X in split halves: for the list kernels' sweeps
+    auto make_split = [&]() -> int {
+        const int rs = make_split_copy(X, N, d, ws, stream);
+        if (rs != SLHC_OK) return rs;
+        if (!split_products_pruned_ok(d)) {
+            // Below 64 features the pruned sweeps multiply in float32, on the rows as they are: fine unless the
+            // rows share an offset far larger than their distances, which then fills the filter's slack and
+            // lets every pair of a tile through.  The split copy is taken relative to the column means; when
+            // that shrinks the norms eightfold or more, the pruned sweeps multiply it too.
+            Mailbox mail(stream);
+            HIP_TRY(mail.open());
+            float h_sums[2];
+            hipLaunchKernelGGL(k_sample_sums, dim3(1), dim3(256), 0, stream, ws.hn, ws.hn_split, (int)N, ws.shift_scratch);
+            HIP_TRY(hipGetLastError());
+            HIP_TRY(mail.fetch(ws.shift_scratch, 2, h_sums));
+            mail.box.idle();
+            ws.offset_heavy = h_sums[0] >= 8.f * h_sums[1];          // false when either sum is NaN
+        }
+    
+        return SLHC_OK;
+    };
     if (ev_order) HIP_TRY(hipEventRecord(ev_order->a, stream));
     if (prune) {
-        const bool split = ws.Xsplit && ws.hn_split && !(flags & SLHC_FP32_FILTER);
-        if (split) {        // X in split halves: for the nearest-pivot sweep here and for every-tile sweeps later
-            const int rs = make_split_copy(X, N, d, ws, stream);
-            if (rs != SLHC_OK) return rs;
-            if (!split_products_pruned_ok(d)) {
-                // Below 64 features the pruned sweeps multiply in float32, on the rows as they are: fine unless the
-                // rows share an offset far larger than their distances, which then fills the filter's slack and
-                // lets every pair of a tile through.  The split copy is taken relative to the column means; when
-                // that shrinks the norms eightfold or more, the pruned sweeps multiply it too.
-                Mailbox mail(stream);
-                HIP_TRY(mail.open());
-                float h_sums[2];
-                hipLaunchKernelGGL(k_sample_sums, dim3(1), dim3(256), 0, stream, ws.hn, ws.hn_split, (int)N, ws.shift_scratch);
-                HIP_TRY(hipGetLastError());
-                HIP_TRY(mail.fetch(ws.shift_scratch, 2, h_sums));
-                mail.box.idle();
-                ws.offset_heavy = h_sums[0] >= 8.f * h_sums[1];          // false when either sum is NaN
-            }
-        }
+        const int rc0 = split && !near_ordered(ws, flags) ? make_split() : SLHC_OK;
+        if (rc0 != SLHC_OK) return rc0;
         const int rc = build_order(X, N, d, ws.hn, reinterpret_cast<const unsigned int*>(ws.counters + 4), ws.order, stream,
                                    ws.near_ready ? &ws.near : nullptr,
-                                   split ? ws.Xsplit : nullptr, split ? ws.hn_split : nullptr, split ? ws.shift : nullptr);
+                                   ws.split_ready ? ws.Xsplit : nullptr, ws.split_ready ? ws.hn_split : nullptr, ws.split_ready ? ws.shift : nullptr);
         if (rc != SLHC_OK) return rc;
     }
     if (ev_order) HIP_TRY(hipEventRecord(ev_order->b, stream));
@@ -1051,10 +1179,38 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
     p.exclude_self = 1;
     p.survivors = ws.counters;
     p.tiles_done = ws.counters + 2;
+    bool by_near = false, by_lists = true;
+    if (prune && near_ordered(ws, flags)) {
+        const OrderWs& o = ws.order;
+        const int T = (o.Ns + 127) / 128;
+        const int rr = make_regions(o, d, stream);
+        if (rr != SLHC_OK) return rr;
+        ws.regions_ready = true;
+        hipLaunchKernelGGL(k_region_local, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, stream, o.tile_region, o.tile_first, o.tile_last, T,
+                           o.tile_local, o.tile_boundary, ws.counters + 10);       // (the boundaries are used up)
+        HIP_TRY(hipGetLastError());
+        Mailbox mail(stream);
+        HIP_TRY(mail.open());
+        unsigned long long pairs = 0;
+        HIP_TRY(mail.fetch(ws.counters + 10, 2, &pairs));
+        by_near = pairs >= NEAR_REGION_TILES * (unsigned long long)T;
+        float ratio[2] = {0.f, 0.f};
+        if (by_near) {
+            slhc::NearOrder n = near_order_of(o);
+            n.ratios = reinterpret_cast<float*>(ws.counters + 11);
+            HIP_TRY(slhc::near_make_ordered(X, (int)N, d, n, o.tile_c, o.tile_r, o.tile_boundary, ws.hn, ws.near.b, stream));
+            HIP_TRY(mail.fetch(ws.counters + 11, 2, ratio));
+            ws.near_order_ready = ratio[0] * sqrtf((float)d) <= NEAR_LINK_SPREAD;
+        }
+        mail.box.idle();
+        // (an offset that most of the norms are: the panels left to the list kernels need the split copy)
+        by_lists = !ws.near_order_ready || ratio[1] >= 8.f;
+        if (split && by_lists) { const int rs = make_split(); if (rs != SLHC_OK) return rs; }
+    }
     if (prune) {
         const OrderWs& o = ws.order;
         p.Xq = p.Xc = o.Xs; p.hq = p.hc = o.hs; p.NQ = p.NC = o.Ns;
-        if (o.Xs_split && ws.hn_split && (split_products_pruned_ok(d) || ws.offset_heavy || (o.Xs_local && !(flags & SLHC_ONE_SHIFT))) &&
+        if (by_lists && o.Xs_split && ws.hn_split && (split_products_pruned_ok(d) || ws.offset_heavy || (o.Xs_local && !(flags & SLHC_ONE_SHIFT))) &&
             !(flags & SLHC_FP32_FILTER)) {
             // the reordered copy in split halves too; its half norms are those of the rows (padding: +inf)
             HIP_TRY(slhc::launch_split_bf16(o.Xs, o.Ns, d, o.Xs_split, stream, ws.shift));
@@ -1094,6 +1250,29 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         p.phase_cycles = ws.counters + 16;
 #endif
     }
+    if (by_near) {
+        const OrderWs& o = ws.order;
+        slhc::NearProblem a{};
+        a.Xq = a.Xc = X; a.d = d; a.k = k;
+        a.nq = a.nq_rows = a.nc = (int)N;
+        a.exclude_self = 1;
+        a.out_idx = nbr_idx; a.out_dist = nbr_dist;
+        a.evaluated = ev_sweep ? reinterpret_cast<int32_t*>(ws.near.q.best) : nullptr;      // (free until the connection rounds)
+        slhc::NearOrder n = near_order_of(o);
+        n.tile_steps = ws.counters + 2;
+        HIP_TRY(slhc::near_search_ordered(a, n, ws.near.b, stream));
+        ws.near_done = true;
+        if (!ws.offset_heavy) { p.Xq_split = p.Xc_split = nullptr; p.hq_split = p.hc_split = nullptr; }
+        p.todo = ws.near.b.todo;            // the panels it could not finish
+        p.tiles_done = nullptr;
+        HIP_TRY(slhc::launch_knn_sweep(p, stream));
+        if (ev_sweep) {
+            HIP_TRY(hipEventRecord(ev_sweep->b, stream));
+            hipLaunchKernelGGL(k_sum_words, dim3(64), dim3(256), 0, stream, a.evaluated, (int)N, ws.counters);
+            HIP_TRY(hipGetLastError());
+        }
+        return SLHC_OK;
+    }
     if (prune && ws.order_split_ready && ws.order.Xs_local && !(flags & SLHC_ONE_SHIFT)) {
         // Two launches (see SweepParams::region_mode).  The rows of a cluster share their centre as an offset that
         // the common shift does not remove, and the filter's slack is a fraction of the squared norms: 1M x 128
@@ -1104,12 +1283,7 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         // second launch starts from those lists and visits the other tiles with the common shift.
         const OrderWs& o = ws.order;
         const int T = (o.Ns + 127) / 128;
-        hipLaunchKernelGGL(k_region_boundaries, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, stream, o.tile_c, o.tile_r, T, d,
-                           o.tile_boundary);
-        hipLaunchKernelGGL(k_region_scan, dim3(1), dim3(1024), 0, stream, o.tile_boundary, T, o.tile_region, o.tile_first);
-        hipLaunchKernelGGL(k_region_last, dim3((unsigned)((T + 255) / 256)), dim3(256), 0, stream, o.tile_boundary, o.tile_first, T,
-                           o.tile_last);
-        HIP_TRY(hipGetLastError());
+        if (!ws.regions_ready) { const int rr = make_regions(o, d, stream); if (rr != SLHC_OK) return rr; }
         HIP_TRY(slhc::launch_split_bf16(o.Xs, o.Ns, d, o.Xs_local, stream, o.tile_c, o.tile_first));
         HIP_TRY(slhc::launch_half_norms(o.Xs, o.Ns, d, o.hs_local, stream, nullptr, true, o.tile_c, o.tile_first));
         hipLaunchKernelGGL(k_mask_padding, dim3((unsigned)((o.Ns + 255) / 256)), dim3(256), 0, stream, o.perm, o.Ns, o.hs_local);
@@ -1854,7 +2028,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     if ((h_surv[4] & 0xffffffffull) != 0) { set_err("a row of X is not finite (NaN, infinity, or a squared norm beyond float32)"); return SLHC_NONFINITE; }
     st.knn_filter_survivors = (int64_t)h_surv[0];
     const unsigned long long tiles_all = (unsigned long long)((N + 127) / 128) * (unsigned long long)((N + 127) / 128);
-    st.knn_tile_steps = (int64_t)(kws.near_done ? tiles_all : h_surv[2]);
+    st.knn_tile_steps = (int64_t)(kws.near_done && !pruned ? tiles_all : h_surv[2]);
 #ifdef SLHC_STUDY_PANEL_STEPS
     if (pruned) {
         const int T_ = (kws.order.Ns + 127) / 128;
@@ -1977,7 +2151,12 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
             if (first_connect) { st.components_after_knn = (int32_t)(N - edges); first_connect = false; }
             ++st.connect_rounds;
             const bool round_pruned = pruned && connect_pruned;
-            if (round_pruned) {
+            const bool round_ordered = round_pruned && kws.near_order_ready;       // pruned by the half-precision engine
+            if (round_ordered) {
+                const OrderWs& o = kws.order;
+                HIP_TRY(slhc::order_gather_i32(ws.colour, o.perm, o.Ns, (int)N, -1, o.near_colour, s));
+                HIP_TRY(slhc::order_tile_colours(o.near_colour, o.Ns, o.tile_colour, s));
+            } else if (round_pruned) {
                 // colours in the reordered copy and one colour summary per tile
                 const OrderWs& o = kws.order;
                 HIP_TRY(slhc::order_gather_i32(ws.colour, o.perm, o.Ns, (int)N, -1, o.colour_s, s));
@@ -2001,6 +2180,25 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     const OrderWs& o = kws.order;
                     HIP_TRY(slhc::order_fill_i32(o.qslot, o.Ns, -1, s));
                     HIP_TRY(slhc::order_scatter_slots(o.inv, rows, n, (int)N, o.Ns, o.qslot, s));
+                    p.Xq = p.Xc = o.Xs; p.hq = p.hc = o.hs; p.NQ = p.NC = o.Ns;
+                    p.qslot = o.qslot;
+                    p.c_id = o.perm;
+                    p.tile_c = o.tile_c; p.tile_r = o.tile_r; p.gap_ws = o.gap_ws;
+                    p.tile_gap = (flags & SLHC_NO_TILE_TABLE) ? nullptr : o.tile_gap;
+                    p.tile_colour = o.tile_colour;
+                    p.comp_count = (int)N;
+                    p.panel_counter = reinterpret_cast<unsigned int*>(kws.counters + 8);
+                    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, p.panel_counter, 1);
+                    HIP_TRY(hipGetLastError());
+                    // what the forest already knows of every component's lightest edge; lowered by the search (vals_a is free
+                    // until the edge sort)
+                    HIP_TRY(hipMemcpyAsync(ws.vals_a, ws.best_w, (size_t)N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
+                    p.comp_best = ws.vals_a;
+                }
+                if (round_ordered) {
+                    p.qcolour = p.ccolour = kws.order.near_colour;
+                } else if (round_pruned) {
+                    const OrderWs& o = kws.order;
                     // A launch with few panels is as long as its longest panel, and a panel whose queries admit
                     // thousands of tiles outlasts the others several times over: with fewer non-empty panels
                     // than SPLIT_ITEMS_TARGET, every panel's scan is split into parts (see the kernel).
@@ -2018,32 +2216,19 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     if (flags & SLHC_SPLIT_SCANS) p.segments = 5;
                     if (h_cnt[6] < 0 || h_cnt[6] > (o.Ns + 127) / 128) { set_err("bad count of queried tiles %d", h_cnt[6]); return SLHC_INTERNAL; }
                     p.panel_list = o.tile_list; p.panel_list_n = h_cnt[6];
-                    p.Xq = p.Xc = o.Xs; p.hq = p.hc = o.hs; p.NQ = p.NC = o.Ns;
                     if (kws.order_split_connect) { p.Xq_split = p.Xc_split = o.Xs_split; p.hq_split = p.hc_split = o.hs_split; }
                     p.qcolour = p.ccolour = o.colour_s;
-                    p.qslot = o.qslot;
-                    p.c_id = o.perm;
-                    p.tile_c = o.tile_c; p.tile_r = o.tile_r; p.gap_ws = o.gap_ws;
-                    p.tile_gap = (flags & SLHC_NO_TILE_TABLE) ? nullptr : o.tile_gap;
-                    p.tile_colour = o.tile_colour;
-                    // thresholds shared by the queries of a component: what the forest already knows (a
-                    // working copy that the sweep lowers further as its queries find lighter edges;
-                    // vals_a is free until the edge sort)
-                    HIP_TRY(hipMemcpyAsync(ws.vals_a, ws.best_w, (size_t)N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
-                    p.comp_best = ws.vals_a;
+                    // thresholds shared by the queries of a component, in a working copy that the sweep lowers further as
+                    // its queries find lighter edges
 #ifndef SLHC_STUDY_NO_LOWERING
                     p.comp_best_lower = ws.vals_a;      // lowered in place; forest_apply_queries reads the final values
                     p.comp_lower_factor = LOWER_FACTOR;
                     p.comp_size = reinterpret_cast<const int32_t*>(ws.vals_b);
                     p.comp_lower_min_size = LOWER_MIN_ROWS;
 #endif
-                    p.comp_count = (int)N;
-                    p.panel_counter = reinterpret_cast<unsigned int*>(kws.counters + 8);
 #ifdef SLHC_PHASE_TIMERS
                     p.phase_cycles = kws.counters + 24;
 #endif
-                    hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, p.panel_counter, 1);
-                    HIP_TRY(hipGetLastError());
                 } else {
                     p.Xq = p.Xc = X; p.hq = p.hc = kws.hn; p.NQ = p.NC = (int)N;
                     p.qcolour = p.ccolour = ws.colour;
@@ -2068,7 +2253,34 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
 #endif
                 if (timed) HIP_TRY(hipEventRecord(ev_conn.a, s));
                 uint32_t* thresholds = round_pruned ? ws.vals_a : nullptr;
-                if (!round_pruned && near_wanted(kws.near, flags)) {
+                if (round_ordered) {
+                    const OrderWs& o = kws.order;
+                    const int T = (o.Ns + 127) / 128;
+                    // the listed rows by position (tmp_a .. tmp_c are free since the order was made)
+                    int32_t* sorted = const_cast<int32_t*>(rows);
+                    int32_t* pos = reinterpret_cast<int32_t*>(o.tmp_b);
+                    hipLaunchKernelGGL(k_slot_counts, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s, o.qslot, o.Ns, T, o.tile_list);
+                    hipLaunchKernelGGL(k_slot_offsets, dim3(1), dim3(1024), 0, s, o.tile_list, T);
+                    hipLaunchKernelGGL(k_slot_rows, dim3((unsigned)((T + 3) / 4)), dim3(256), 0, s, o.qslot, o.perm, o.Ns, T, o.tile_list, n, sorted, pos);
+                    HIP_TRY(hipGetLastError());
+                    slhc::NearOrder order = near_order_of(o);
+                    order.all.colour = o.near_colour;
+                    order.tile_steps = kws.counters + 3;
+                    slhc::NearLink a{};
+                    a.X = X; a.d = d; a.n_rows = (int)N; a.rows = sorted; a.n = n; a.colour = ws.colour;
+                    a.threshold = ws.vals_a;
+                    a.out_idx = ws.q_idx; a.out_dist = ws.q_dist; a.out_low = ws.q_low; a.evaluated = reinterpret_cast<int32_t*>(ws.vals_b);
+                    a.rows_left = reinterpret_cast<int32_t*>(ws.keys_a); a.slot_left = a.rows_left + N;
+                    a.reach_left = reinterpret_cast<float*>(ws.keys_b);
+                    a.qpos = pos; a.pos_left = reinterpret_cast<int32_t*>(o.tmp_c); a.counts_left = kws.near.q.count;
+                    a.edge_at = reinterpret_cast<int32_t*>(kws.near.q.best); a.best_at = o.best_at; a.threshold0 = o.tmp_a;
+                    HIP_TRY(slhc::near_link_ordered(a, order, kws.near.b, s));
+                    hipLaunchKernelGGL(k_sum_words, dim3(16), dim3(256), 0, s, reinterpret_cast<const int32_t*>(ws.vals_b), n, kws.counters + 1);
+                    HIP_TRY(hipGetLastError());
+                    p.todo = kws.near.b.todo;
+                    p.tiles_done = nullptr;
+                    HIP_TRY(slhc::launch_cross_1nn_sweep(p, s));
+                } else if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;
                     if (!kws.near_ready) {
                         HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, nullptr, 0, s));
@@ -2085,7 +2297,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     a.threshold = ws.vals_a;
                     a.out_idx = ws.q_idx; a.out_dist = ws.q_dist; a.out_low = ws.q_low; a.evaluated = reinterpret_cast<int32_t*>(ws.vals_b);
                     a.rows_left = reinterpret_cast<int32_t*>(ws.keys_a); a.slot_left = a.rows_left + N;
-                    a.bound_left = reinterpret_cast<float*>(ws.keys_b);
+                    a.reach_left = reinterpret_cast<float*>(ws.keys_b);
                     HIP_TRY(slhc::near_link(a, q, near.c, near.b, s));
                     thresholds = ws.vals_a;
                     hipLaunchKernelGGL(k_sum_words, dim3(16), dim3(256), 0, s, reinterpret_cast<const int32_t*>(ws.vals_b), n, kws.counters + 1);
@@ -2099,10 +2311,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 // in pruned rounds only)
                 HIP_TRY(slhc::launch_segmented_cross_1nn(p, round_pruned ? ws.keys_b : ws.keys_a, s));
                 if (timed) HIP_TRY(hipEventRecord(ev_conn.b, s));
-                HIP_TRY(slhc::forest_apply_queries(f, rows, ws.q_idx, ws.q_dist, thresholds && !round_pruned ? ws.q_low : nullptr, n, thresholds, s));
+                HIP_TRY(slhc::forest_apply_queries(f, rows, ws.q_idx, ws.q_dist, thresholds && (round_ordered || !round_pruned) ? ws.q_low : nullptr, n, thresholds, s));
                 // (every-tile rounds leave the check to the next reading of the counters)
                 h_cnt[7] = 0;
-                if (round_pruned) HIP_TRY(mail.fetch(ws.counters + 3, 1, h_cnt + 7));
+                if (round_pruned && !round_ordered) HIP_TRY(mail.fetch(ws.counters + 3, 1, h_cnt + 7));
                 if (h_cnt[7] == 14) {
                     // an answer inside the query's own component: say what the sweep was given
                     HIP_TRY(hipMemcpy(h_cnt + 8, ws.counters + 16, 7 * sizeof(int32_t), hipMemcpyDeviceToHost));
@@ -2146,7 +2358,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                                          ? nq >= 256
                                          : ((int64_t)nq * 2 >= N && (int64_t)nq >= TWO_PHASE_MIN_ROWS &&
                                             prev_steps_per_panel >= TWO_PHASE_MIN_STEPS);
-            if (round_pruned && split_round) {
+            if (round_pruned && !round_ordered && split_round) {
                 // Two phases, for a round that queries most rows while the thresholds the forest has
                 // are loose (the last pruned round multiplied hundreds of tiles per panel).  The rows
                 // of every 16th panel go first; what they find lowers their components' best
@@ -2196,7 +2408,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
             if (log.on) {
                 HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
                 int32_t left[2] = {0, queried};
-                if (!round_pruned && near_wanted(kws.near, flags)) HIP_TRY(mail.fetch(kws.near.b.todo, 2, left));
+                if (round_ordered || (!round_pruned && near_wanted(kws.near, flags))) HIP_TRY(mail.fetch(kws.near.b.todo, 2, left));
                 log.mark("round %d: %d components, %d of %d listed rows queried, %d searched, %d panels by lists, sweeps %.2f ms, %llu tile steps so far",
                          st.boruvka_rounds, (int)(N - edges), queried, nq, left[1], left[0], ms_round_kernels, h_surv[3]);
             }

@@ -1033,7 +1033,7 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
     constexpr bool CAN_CARRY = !PRUNE;
     constexpr bool REGIONS = PRUNE && !MASKED;          // p.region_mode applies
     const int ncarry = (CAN_CARRY && p.carry_ranges > 1 && p.carry_ws != nullptr) ? p.carry_ranges : 1;
-    const bool todo_panels = !PRUNE && p.todo != nullptr;
+    const bool todo_panels = p.todo != nullptr;
     const int nitems = todo_panels ? (p.todo[0] < npanels ? p.todo[0] : npanels)
                      : ncarry > 1 ? npanels * ncarry : (listed_panels ? p.panel_list_n : npanels) * nparts;
     unsigned int* hand_out = ncarry > 1 ? p.carry_ws : (PRUNE ? p.panel_counter : nullptr);
@@ -1050,7 +1050,7 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
         const int crange = ncarry > 1 ? item / npanels : 0;
         const int panel_at = ncarry > 1 ? item - crange * npanels : (nparts > 1 ? item / nparts : item);
         const int part = (ncarry == 1 && nparts > 1) ? item - panel_at * nparts : 0;
-        const int panel = listed_panels ? p.panel_list[panel_at] : todo_panels ? p.todo[2 + panel_at] : panel_at;
+        const int panel = todo_panels ? p.todo[2 + panel_at] : listed_panels ? p.panel_list[panel_at] : panel_at;
         if ((unsigned int)panel >= (unsigned int)npanels) continue;          // never trust a list entry as an index
 #ifdef SLHC_STUDY_PANEL_STEPS
         const long long study_t0 = clock64();
@@ -2329,7 +2329,7 @@ static hipError_t launch_sweep_t(const SweepParams& p_in, hipStream_t stream)
     // candidate segments: the streaming kernel (no pruning); parts of a pruned scan: cross 1-NN with a slot map
     const bool ranges = !MASKED && p.k > 1 && p.segments > 1 && p.part_idx && p.part_dist && !p.tile_c;     // k-NN in candidate ranges
     if (p.segments > 1 && !ranges && (!p.out_key || p.k != 1 || (p.tile_c && !(MASKED && p.qslot)))) return hipErrorInvalidValue;
-    if (p.todo && (p.tile_c || p.segments > 1 || p.qslot)) return hipErrorInvalidValue;
+    if (p.todo && p.segments > 1) return hipErrorInvalidValue;
     if (p.todo) p.carry_ws = nullptr;
     const bool listed = MASKED && aligned && p.tile_c && p.panel_list;
     if (listed && p.panel_list_n < 1) return hipSuccess;

@@ -125,3 +125,27 @@ def test_trees_by_components(lib, kind, N, d):
     torch.cuda.synchronize()
     for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
         assert torch.equal(want[key], got[key]), key
+
+
+# searches in the row order: panels of two, four and eight wavefronts (tiles from 256 and from 1024 on), clusters of more and of
+# fewer rows than neighbours asked for, on both sides of the shortest region, one cluster, and clusters far apart for their size
+@pytest.mark.parametrize("N,d,k,rows,spread", [
+    (700, 4, 3, 700, 8), (5000, 128, 16, 20, 8), (20_000, 40, 31, 900, 8), (33_000, 100, 64, 1100, 40), (34_000, 12, 5, 8000, 8),
+    (60_000, 64, 12, 2500, 5000), (110_000, 8, 20, 110_000, 0), (133_000, 20, 15, 9000, 8), (140_000, 128, 8, 30_000, 30),
+])
+def test_lists_and_trees_in_the_row_order(lib, N, d, k, rows, spread):
+    print(f"half-precision row order N={N} d={d} k={k} rows={rows} spread={spread}", flush=True)
+    rng = np.random.default_rng(N + d)
+    centres = rng.uniform(-spread, spread, size=(max(1, N // rows), d))
+    X = centres[rng.integers(0, len(centres), N)] + rng.standard_normal((N, d))
+    X[: N // 50] = X[rng.integers(0, N, N // 50)] * (1.0 + 1e-3 * (rows > 5000))
+    X[:3] = 40.0 * spread + rng.standard_normal((3, d))                       # fewer rows than neighbours, far from all others
+    Xd = torch.from_numpy(X.astype(np.float32)).cuda()
+    a, b = lib.knn_graph(Xd, k), lib.knn_graph(Xd, k, prune=True)
+    torch.cuda.synchronize()
+    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    want, got = lib.slhc(Xd, min(k, 16), prune=False), lib.slhc(Xd, min(k, 16), prune=True)
+    torch.cuda.synchronize()
+    assert got["stats"]["pruned"] == 1
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
