@@ -23,9 +23,10 @@ struct NearCopy {
     float* negh;               // [tiles * 128] minus the half norm; -inf: no such row, +inf: values beyond float16
     float* negh_best;          // [tiles * 128] or nullptr: the same with -inf for the latter (candidates of 1-NN searches)
     int32_t* colour;           // [tiles * 128] or nullptr
-    uint32_t* best;            // [tiles * 128] or nullptr: scratch of 1-NN searches for these rows as queries,
-    int32_t* count;            // and the same; near_make clears all
-    unsigned long long* best_at;    // likewise: largest product value and where (near_link)
+    // scratch of 1-NN searches for these rows as queries, or nullptr
+    int32_t* left;             // [4 * tiles * 128]
+    int32_t* count;            // [tiles * 128], cleared by near_make
+    unsigned long long* best_at;    // [tiles * 128], set to ~0 by near_make (near_link)
     bool finite_padding;       // -1e38 instead of -inf (near_assign)
     bool in_order;
     int rows, tiles;

@@ -236,7 +236,7 @@ struct NearMake {
     unsigned char* frag; float *negh, *negh_best; int32_t* out_colour; float* hn; unsigned int* nonfinite;
     int n_src, n, d, tiles, steps, in_order; float h_of_n, hn_scale, absent;
     const int32_t* n_dev;
-    uint32_t* best; int32_t* count; unsigned long long* best_at;
+    int32_t* count; unsigned long long* best_at;
     int32_t* todo; long long todo_words;
 };
 
@@ -337,7 +337,6 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
             if (p.negh_best) p.negh_best[at] = nh == INF ? p.absent : nh;
             if (hg && src[i] >= 0) p.sc->huge = 1u;
             if (p.out_colour) p.out_colour[at] = src[i] >= 0 && p.colour ? p.colour[src[i]] : -1;
-            if (p.best) p.best[at] = 0u;
             if (p.best_at) p.best_at[at] = ~0ull;
             if (p.count) p.count[at] = 0;
             if (src[i] >= 0) {
@@ -368,7 +367,7 @@ hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int 
     p.frag = out.frag; p.negh = out.negh; p.out_colour = out.colour; p.hn = hn; p.nonfinite = nonfinite;
     p.n_src = n_src; p.n = n; p.d = d; p.tiles = out.tiles; p.steps = near_steps(d); p.h_of_n = 0.5f - 0.5f * near_nu(p.steps) - near_e(p.steps);
     p.shift_row = shift_row;
-    p.best = out.best; p.count = out.count; p.best_at = out.best_at;
+    p.count = out.count; p.best_at = out.best_at;
     p.negh_best = out.negh_best; p.in_order = out.in_order; p.n_dev = n_dev;
     p.absent = out.finite_padding ? -1e38f : -INF;
     p.todo = b.todo; p.todo_words = clear_todo ? 2 + 2 * b.todo_panels : 0;
@@ -416,11 +415,12 @@ struct NearSweep {
     unsigned long long* best_at;       // arg: (largest product value, candidate position) by query position; block: (distance below
                                        // which there is no candidate, position of the first of the 16 values of a lane in a block
                                        // of 32 candidates the nearest of which is about there)
-    uint32_t* best;                    // nearest: largest product value of a query by position (ordered bits)
+    uint4* top;                        // top: [queries of the batch][nsub] (largest product value of a lane, position of the first of
+                                       // the 16 values it is among, largest outside these 16)
     int nq_batch;
 };
 
-enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_BEST = 2, NEAR_NEAREST = 3, NEAR_ARG = 4, NEAR_BLOCK = 5 };
+enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_TOP = 2, NEAR_NEAREST = 3, NEAR_ARG = 4, NEAR_BLOCK = 5 };
 
 __device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
 
@@ -434,11 +434,6 @@ __device__ inline unsigned int ordered_bits(float x)
     const unsigned int b = __float_as_uint(x);
     return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
 }
-__device__ inline float from_ordered(unsigned int o)
-{
-    return __uint_as_float((o & 0x80000000u) ? (o & 0x7fffffffu) : ~o);
-}
-
 // A value that at least kk of the wavefront's values v(i), i < n, reach, and not many more: bisection between the
 // smallest and the largest of them.  Values that are not finite do not count.  Returns LOWEST when fewer than kk are.
 constexpr int BISECT = 13;
@@ -502,7 +497,7 @@ struct NearLane {
     float h[2], bound[2];
     int qcol[2];
     unsigned int off[2], roomy[2];          // byte offsets into the entries: next free, last with room for 32
-    float m[2][16], m1[2];
+    float m[2][16], m1[2], m2[2];
     int m1_at[2];
     NearBoundArgs args;
     int q_at[2];                            // number of the query, and that in the batch
@@ -531,12 +526,6 @@ struct NearLane {
                 const float r = ok ? p.reach[MODE == NEAR_EMIT ? lq[qb] : q_at[qb]] : -1.f, t2 = r * p.sc->scale * p.sc->scale;
                 if (r >= 0.f) bound[qb] = t2 < INF ? fmaxf(LOWEST, near_bound_at(t2, h[qb], args)) : LOWEST;
             } else if (MODE == NEAR_EMIT && ok) bound[qb] = p.bound[lq[qb]];
-            else if (MODE == NEAR_NEAREST && ok && p.bound) bound[qb] = p.bound[lq[qb]];
-            else if (MODE == NEAR_NEAREST && ok) {
-                const unsigned int best = p.best[q_at[qb]];
-                // (none found: nothing is admissible, or values beyond float16 hide it; the latter end up with the list kernels)
-                bound[qb] = best != 0u ? fmaxf(LOWEST, near_bound_from(from_ordered(best), h[qb], args)) : LOWEST;
-            }
             if (COLOURED) qcol[qb] = p.qcolour[q_pos[qb]];
             if (MODE == NEAR_EMIT) {
                 off[qb] = ((unsigned int)lq[qb] * (unsigned int)p.nsub + (unsigned int)sub) * (unsigned int)p.capl * 8u;
@@ -548,7 +537,7 @@ struct NearLane {
                     } else off[qb] += (unsigned int)have * 8u;
                 }
             }
-            m1[qb] = -INF;
+            m1[qb] = m2[qb] = -INF;
             m1_at[qb] = -1;
             if (MODE == NEAR_MAXIMA) {
 #pragma unroll
@@ -584,14 +573,7 @@ struct NearLane {
                 for (int r = 0; r < 16; ++r) m[qb][r] = max3(m[qb][r], acc[qb][0][r], acc[qb][1][r]);
             return;
         }
-        if (MODE == NEAR_BEST) {
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) m1[qb] = max3(m1[qb], acc[qb][0][r], acc[qb][1][r]);
-            return;
-        }
-        if (MODE == NEAR_BLOCK) {
+        if (MODE == NEAR_BLOCK || MODE == NEAR_TOP) {
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
@@ -603,6 +585,7 @@ struct NearLane {
                     mx = fmaxf(mx, v[15]);
                     const bool up = mx > m1[qb] && ok[qb];
                     m1_at[qb] = up ? pos0 + 32 * cb : m1_at[qb];
+                    if (MODE == NEAR_TOP) m2[qb] = fmaxf(m2[qb], fminf(m1[qb], mx));
                     m1[qb] = up ? mx : m1[qb];
                 }
             return;
@@ -707,10 +690,8 @@ struct NearLane {
     {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb) {
-            if (MODE == NEAR_BEST) {
-                const float v = fmaxf(m1[qb], __shfl_xor(m1[qb], 32));
-                if (live && lhalf == 0 && v > -INF && v < INF) atomicMax(p.best + q_at[qb], ordered_bits(v));
-            }
+            if (MODE == NEAR_TOP && live)
+                p.top[(size_t)lq[qb] * p.nsub + sub] = make_uint4(__float_as_uint(m1[qb]), (unsigned int)(m1_at[qb] + 4 * lhalf), __float_as_uint(m2[qb]), 0u);
             if (MODE == NEAR_BLOCK) {
                 const float v = __shfl_xor(m1[qb], 32);
                 const int at = __shfl_xor(m1_at[qb], 32);
@@ -970,6 +951,17 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     const int nmine = seg < npairs ? (npairs - seg + nseg - 1) / nseg : 0;
     auto listed = [&](int j) -> int { return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride; };
     const int total = nmine * nchunks;
+    // positions of the queries whose pieces this wavefront brings in (wavefronts 0 to 3, one tile each for two)
+    int q_src[4] = {0, 0, 0, 0};
+    if (wave < 4) {
+        const int n_q = p.n_dev ? *p.n_dev : p.n_q;
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) {
+            const int t = qtile0 + (wave >> 1) < q_tile1 ? qtile0 + (wave >> 1) : qtile0;
+            const int i = t * TILE + blk * 32 + l32;
+            q_src[blk] = !p.qpos ? i : i < n_q ? p.qpos[i] : 0;
+        }
+    }
     // the loads of step `at` (pair, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the norms with chunk 0
     auto stage = [&](int i, int chunk, int at) {
         unsigned char* dst = near_smem + (at & 1) * WIDE_BUF;
@@ -978,11 +970,15 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
         for (int x = 0; x < 8; ++x) {
             const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block]
             const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
-            size_t t;
-            if (side == 0) t = qtile0 + tile < q_tile1 ? qtile0 + tile : qtile0;
-            else t = listed(j0 + tile < p.used ? j0 + tile : j0);
-            const unsigned char* base = side == 0 ? p.qfrag : p.cfrag;
-            near_lds_load(base + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16, dst + piece * 1024, true);
+            const unsigned char* src;
+            if (side == 0) {
+                const int at_q = q_src[blk];
+                src = p.qfrag + ((size_t)(at_q >> 7) * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + ((at_q >> 5) & 3) * 1024 + (lhalf * 32 + (at_q & 31)) * 16;
+            } else {
+                const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
+                src = p.cfrag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16;
+            }
+            near_lds_load(src, dst + piece * 1024, true);
         }
         if (chunk == 0 && wave < (COLOURED ? 8 : 4)) {
             const int tile = (wave >> 1) & 1, half = wave & 1;
@@ -1346,6 +1342,11 @@ __global__ void __launch_bounds__(256) near_clear_kernel(unsigned long long* a, 
     if (i < n) a[i] = 0ull;
 }
 
+__global__ void __launch_bounds__(256) near_todo_clear_kernel(int32_t* __restrict__ todo, long long words)
+{
+    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < words; i += (long long)gridDim.x * 256) todo[i] = 0;
+}
+
 struct NearPlan {
     int waves, panel_tiles;             // wavefronts per workgroup, query tiles per panel
     int nseg, nsub, capl;               // emit
@@ -1472,19 +1473,169 @@ static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s
     }
 }
 
+// ---------------------------------------------------------------------------------------------- nearest rows
+// A 1-NN search keeps, per lane, the 16 candidates with the largest product value and what the others reach at most; so one
+// pass settles all queries except those that have a second near candidate in the same lane (1 in a hundred or so), which
+// are searched for on their own.  Bound by that pass.  1k x 100k x 128: 129 -> 115 us; 10k x 100k x 64 by colours: 390 -> 261 us
+// (two passes, the second emitting what the first one's best value leaves).
+struct NearTop {
+    const uint4* top; int nsub, nq_batch, q0;
+    const float* qnegh; const int32_t *qcolour, *ccolour; const NearScale* sc; float e, nu; int steps;
+    const float* Xq; const float* Xc; const int32_t* q_rows;
+    int d, nq, nq_rows, nc, q_tiles, c_tiles, q_in_order, c_in_order;
+    int32_t* out_idx; float* out_dist; int32_t* evaluated;
+    int32_t *rows_left, *slot_left, *pos_left, *counts_left, *count_left; float* reach_left;
+    int32_t* todo; int32_t* todo_mark;
+};
+
+template <bool VEC4>
+__global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
+{
+    const int lane = threadIdx.x & 63;
+    const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
+    if (lq >= p.nq_batch) return;
+    const int qpos = p.q0 + lq;
+    const long long qi = near_row(qpos, p.q_tiles, p.q_in_order);
+    if (qi >= p.nq) return;
+    const long long row = p.q_rows ? (long long)p.q_rows[qi] : qi;
+    const float nh = p.qnegh[qpos];
+    if (row < 0 || row >= p.nq_rows || nh == -INF) {
+        if (lane == 0) { p.out_idx[qi] = -1; p.out_dist[qi] = INF; if (p.evaluated) p.evaluated[qi] = 0; }
+        return;
+    }
+    if (nh == INF) {                                            // values beyond float16: the list kernels
+        if (lane == 0) {
+            const int panel = (int)(qi >> 7);
+            if (atomicExch(p.todo_mark + panel, 1) == 0) p.todo[2 + atomicAdd(p.todo, 1)] = panel;
+            if (p.evaluated) p.evaluated[qi] = 0;
+        }
+        return;
+    }
+    float m1[2], m2[2];
+    int at[2];
+    bool pending[2];
+#pragma unroll
+    for (int r = 0; r < 2; ++r) {
+        const int i = lane + 64 * r;
+        uint4 t = make_uint4(__float_as_uint(-INF), 0u, __float_as_uint(-INF), 0u);
+        if (i < p.nsub) t = p.top[(size_t)lq * p.nsub + i];
+        m1[r] = __uint_as_float(t.x); at[r] = (int)t.y; m2[r] = __uint_as_float(t.z);
+        pending[r] = m1[r] > -INF;
+    }
+    const NearBoundArgs a = near_args(p.sc, p.steps, p.d, p.e, p.nu);
+    const float* xa = p.Xq + (size_t)row * p.d;
+    const int grp = lane >> 3, g = lane & 7;
+    v4f qa[4];
+    near_first_quads<VEC4>(qa, xa, p.d, g);
+    const int qcol = p.qcolour ? p.qcolour[qpos] : 0;
+    unsigned long long key = ~0ull;
+    float bound = LOWEST;
+    int evaluated = 0;
+    for (int turn = 0; turn < 128; ++turn) {
+        // the lane with the largest value that may still hide the nearest
+        const float mine = fmaxf(pending[0] ? m1[0] : -INF, pending[1] ? m1[1] : -INF);
+        float mx = mine;
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        if (!(mx > -INF) || mx < bound) break;
+        const int who = __builtin_ctzll(__ballot(mine == mx));
+        const bool second = !(pending[0] && m1[0] == mx);
+        const int base = __builtin_amdgcn_readlane(second ? at[1] : at[0], who);
+        if (lane == who) pending[second ? 1 : 0] = false;
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const int j = half * 8 + grp;
+            const int pos = base + 8 * (j >> 2) + (j & 3);
+            const long long cand = near_row(pos, p.c_tiles, p.c_in_order);
+            const bool fine = cand >= 0 && cand < p.nc && !(p.qcolour && p.ccolour[pos] == qcol);
+            const float dist = near_exact<VEC4>(qa, xa, p.Xc + (size_t)(fine ? cand : 0) * p.d, p.d, g);
+            const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
+            if (fine && dist < INF && k < key) key = k;
+        }
+#pragma unroll
+        for (int o = 8; o < 64; o <<= 1) {
+            const unsigned long long other = __shfl_xor(key, o);
+            key = other < key ? other : key;
+        }
+        evaluated += 16;
+        if (key != ~0ull) bound = fmaxf(LOWEST, near_bound_at(__uint_as_float((unsigned int)(key >> 32)) * p.sc->scale * p.sc->scale, -nh, a));
+    }
+    const bool open = __any(m2[0] >= bound && m2[0] > -INF) || __any(m2[1] >= bound && m2[1] > -INF) || p.sc->huge != 0u;
+    if (lane == 0) {
+        p.out_idx[qi] = key == ~0ull ? -1 : (int32_t)(unsigned int)key;
+        p.out_dist[qi] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
+        if (p.evaluated) p.evaluated[qi] = evaluated;
+        if (open) {
+            const int i = atomicAdd(p.count_left, 1);
+            p.rows_left[i] = (int32_t)row; p.slot_left[i] = (int32_t)qi; p.pos_left[i] = qpos; p.counts_left[i] = 0;
+            p.reach_left[i] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
+        }
+    }
+}
+
+// the query tiles from t0 on, nqb queries; `p` prepared for the copies
+static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, const NearPlan& plan,
+                               NearSweep p, bool vec4, int t0, int nqb, hipStream_t s)
+{
+    const bool wide = p.steps > REG_STEPS;
+    const int lanes = wide ? 4 : 2, tiles = nqb / TILE;
+    const size_t n = (size_t)q.tiles * TILE;
+    p.nseg = plan.nseg * lanes > 128 ? 128 / lanes : plan.nseg;
+    p.nsub = lanes * p.nseg; p.stride = 1; p.skip = 0; p.used = c.tiles;
+    p.top = reinterpret_cast<uint4*>(b.batch);
+    p.cnegh = c.negh_best;
+    hipError_t e = a.coloured ? near_launch_sweep<NEAR_TOP, true>(p, plan.waves, s) : near_launch_sweep<NEAR_TOP, false>(p, plan.waves, s);
+    if (e != hipSuccess) return e;
+    if (t0 > 0) hipLaunchKernelGGL(near_todo_clear_kernel, dim3(1), dim3(256), 0, s, b.todo + 1, 1);
+    NearTop t{};
+    t.top = p.top; t.nsub = p.nsub; t.nq_batch = nqb; t.q0 = t0 * TILE;
+    t.qnegh = q.negh; t.qcolour = a.coloured ? q.colour : nullptr; t.ccolour = c.colour;
+    t.sc = b.scale; t.e = p.e; t.nu = p.nu; t.steps = p.steps;
+    t.Xq = a.Xq; t.Xc = a.Xc; t.q_rows = a.q_rows;
+    t.d = a.d; t.nq = a.nq; t.nq_rows = a.nq_rows; t.nc = a.nc;
+    t.q_tiles = q.tiles; t.c_tiles = c.tiles; t.q_in_order = q.in_order; t.c_in_order = c.in_order;
+    t.out_idx = a.out_idx; t.out_dist = a.out_dist; t.evaluated = a.evaluated;
+    t.rows_left = q.left; t.slot_left = q.left + n; t.pos_left = q.left + 2 * n; t.reach_left = reinterpret_cast<float*>(q.left + 3 * n);
+    t.counts_left = q.count; t.count_left = b.todo + 1;
+    t.todo = b.todo; t.todo_mark = b.todo_mark;
+    const dim3 per_query((unsigned)((nqb + 3) / 4));
+    if (vec4) hipLaunchKernelGGL((near_top_kernel<true>), per_query, dim3(256), 0, s, t);
+    else hipLaunchKernelGGL((near_top_kernel<false>), per_query, dim3(256), 0, s, t);
+    // those with more than one near candidate in a lane
+    const int waves = wide ? plan.waves : (plan.waves > 2 ? plan.waves / 2 : 2);
+    p.cnegh = c.negh;
+    p.q_tile0 = 0; p.q_tile1 = tiles;
+    p.qpos = t.pos_left; p.n_dev = t.count_left; p.slots = (waves == 8 ? 1 : 2) * near_cus(); p.most_seg = p.slots;
+    p.reach = t.reach_left; p.counts = t.counts_left; p.capl = plan.capl;
+    p.entries = reinterpret_cast<uint2*>(b.batch);
+    e = a.coloured ? near_launch_sweep<NEAR_NEAREST, true>(p, waves, s) : near_launch_sweep<NEAR_NEAREST, false>(p, waves, s);
+    if (e != hipSuccess) return e;
+    NearSelect sel{};
+    sel.entries = p.entries; sel.counts = p.counts; sel.nsub = 1; sel.by_position = 1; sel.capl = plan.capl;
+    sel.nq_batch = nqb; sel.q0 = 0;
+    sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
+    sel.Xq = a.Xq; sel.Xc = a.Xc; sel.q_rows = t.rows_left; sel.slot = t.slot_left; sel.qpos = t.pos_left; sel.n_dev = t.count_left;
+    sel.d = a.d; sel.k = sel.kk = 1; sel.nq = nqb; sel.nq_rows = a.nq_rows; sel.nc = a.nc;
+    sel.q_tiles = q.tiles; sel.c_tiles = c.tiles; sel.q_in_order = 1; sel.c_in_order = c.in_order;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
+    else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+    return hipGetLastError();
+}
+
 hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
 {
     const int kk = a.k + (a.exclude_self ? 1 : 0);
     const NearPlan plan = near_plan(a.nq, a.nc, a.d, kk, b.batch_bytes);
     if (plan.batch_tiles < 1 || (a.nq + 127) / 128 > b.todo_panels || (a.coloured && (kk != 1 || !q.colour || !c.colour)) ||
-        (kk == 1 && (!q.best || !q.count)))
+        (kk == 1 && (!q.left || !q.count || !c.negh_best)))
         return hipErrorInvalidValue;
     NearSweep p{};
     p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour;
     p.cfrag = c.frag; p.cnegh = c.negh; p.ccolour = c.colour; p.c_tiles = c.tiles;
     p.sc = b.scale; p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
     p.kk = kk;
-    p.best = q.best;
     const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
     NearSelect sel{};
     sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
@@ -1511,17 +1662,7 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
         };
         hipError_t e = hipSuccess;
         if (kk == 1) {
-            p.entries = reinterpret_cast<uint2*>(take((size_t)nqb * plan.capl * 8));
-            p.counts = q.count;
-            p.nseg = plan.nseg; p.stride = 1; p.skip = 0; p.used = c.tiles;
-            if (c.negh_best) p.cnegh = c.negh_best;
-            e = a.coloured ? near_launch_sweep<NEAR_BEST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_BEST, false>(p, plan.waves, s);
-            if (e != hipSuccess) return e;
-            p.cnegh = c.negh;
-            e = a.coloured ? near_launch_sweep<NEAR_NEAREST, true>(p, plan.waves, s) : near_launch_sweep<NEAR_NEAREST, false>(p, plan.waves, s);
-            if (e != hipSuccess) return e;
-            sel.nsub = 1; sel.by_position = 1;
-            e = select();
+            e = near_nearest(a, q, c, b, plan, p, vec4, t0, nqb, s);
             if (e != hipSuccess) return e;
             continue;
         }
@@ -1812,11 +1953,6 @@ __global__ void __launch_bounds__(1024) near_items_kernel(const int32_t* __restr
     for (int i = a; i < e; ++i) { items[i] = at; at += (len[i] + ITEM_TILES - 1) / ITEM_TILES; }
     if (tid == 1023) items[panels] = sum[1023];
     if (tile_steps && steps) atomicAdd(tile_steps, steps);
-}
-
-__global__ void __launch_bounds__(256) near_todo_clear_kernel(int32_t* __restrict__ todo, long long words)
-{
-    for (long long i = (long long)blockIdx.x * 256 + threadIdx.x; i < words; i += (long long)gridDim.x * 256) todo[i] = 0;
 }
 
 // The scale of the copy by regions: the median tile's radius near 2^7 (see near_shift_kernel).
@@ -2159,11 +2295,11 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
     e = near_make(a.X, a.n_rows, a.d, a.rows_left, a.n, a.colour, b, q, nullptr, nullptr, s, false, r.count_left);
     if (e != hipSuccess) return e;
     p.cnegh = c.negh;
-    p.n_dev = r.count_left; p.most_seg = 64;
+    p.n_dev = r.count_left;
     // few are left: workgroups of two wavefronts (of one kind beyond 128 columns) waste least on a panel that is not full
     const bool wide = p.steps > REG_STEPS;
     const int waves = wide ? plan.waves : (plan.waves > 2 ? plan.waves / 2 : 2);
-    p.slots = (waves == 8 ? 1 : 2) * near_cus();
+    p.slots = p.most_seg = (waves == 8 ? 1 : 2) * near_cus();
     p.counts = q.count; p.capl = plan.capl;
     p.reach = a.reach_left;
     NearSelect sel{};

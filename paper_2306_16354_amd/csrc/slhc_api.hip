@@ -602,7 +602,7 @@ struct NearWs {
             x.negh = w.take<float>((size_t)x.tiles * 128);
             x.negh_best = kk == 1 || coloured ? w.take<float>((size_t)x.tiles * 128) : nullptr;
             x.colour = coloured ? w.take<int32_t>((size_t)x.tiles * 128) : nullptr;
-            x.best = w.take<uint32_t>((size_t)x.tiles * 128);
+            x.left = w.take<int32_t>((size_t)x.tiles * 128 * (kk == 1 ? 4 : 1));      // (one part serves k-NN searches as scratch)
             x.count = w.take<int32_t>((size_t)x.tiles * 128);
             x.best_at = nullptr;
         };
@@ -1257,7 +1257,7 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         a.nq = a.nq_rows = a.nc = (int)N;
         a.exclude_self = 1;
         a.out_idx = nbr_idx; a.out_dist = nbr_dist;
-        a.evaluated = ev_sweep ? reinterpret_cast<int32_t*>(ws.near.q.best) : nullptr;      // (free until the connection rounds)
+        a.evaluated = ev_sweep ? ws.near.q.left : nullptr;      // (free until the connection rounds)
         slhc::NearOrder n = near_order_of(o);
         n.tile_steps = ws.counters + 2;
         HIP_TRY(slhc::near_search_ordered(a, n, ws.near.b, stream));
@@ -2273,7 +2273,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     a.rows_left = reinterpret_cast<int32_t*>(ws.keys_a); a.slot_left = a.rows_left + N;
                     a.reach_left = reinterpret_cast<float*>(ws.keys_b);
                     a.qpos = pos; a.pos_left = reinterpret_cast<int32_t*>(o.tmp_c); a.counts_left = kws.near.q.count;
-                    a.edge_at = reinterpret_cast<int32_t*>(kws.near.q.best); a.best_at = o.best_at; a.threshold0 = o.tmp_a;
+                    a.edge_at = kws.near.q.left; a.best_at = o.best_at; a.threshold0 = o.tmp_a;
                     HIP_TRY(slhc::near_link_ordered(a, order, kws.near.b, s));
                     hipLaunchKernelGGL(k_sum_words, dim3(16), dim3(256), 0, s, reinterpret_cast<const int32_t*>(ws.vals_b), n, kws.counters + 1);
                     HIP_TRY(hipGetLastError());
