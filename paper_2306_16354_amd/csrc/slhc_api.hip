@@ -2403,7 +2403,8 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if (used_panels_round > 0) steps_per_used_panel = (double)steps / (double)used_panels_round;
                 used_panels_round = 0;
                 const unsigned long long every = (unsigned long long)((nq + 127) / 128) * (unsigned long long)((N + 127) / 128);
-                if ((int64_t)nq * 8 >= N && steps * 3 > every) connect_pruned = false;
+                // (tiles that only leave out a component's own already cost less, for lists, than they save)
+                if ((int64_t)nq * 8 >= N && (round_ordered ? steps * 10 > every * 9 : steps * 3 > every)) connect_pruned = false;
             }
             if (log.on) {
                 HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
