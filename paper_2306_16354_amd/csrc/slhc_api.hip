@@ -21,6 +21,7 @@
 #include "cluster_kernels.h"
 #include "forest_kernels.h"
 #include "near_kernels.h"
+#include "direct_kernels.h"
 #include "order_kernels.h"
 #include "sweep_kernels.h"
 
@@ -1662,6 +1663,11 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
         if (m == 0) return SLHC_OK;
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::SweepParams p{};
+        if (near.ok && slhc::direct_1nn_wanted(m, N, d)) {
+            HIP_TRY(slhc::direct_1nn(X, (int)m, (int)N, rows, X, (int)N, d, colour, out_idx, out_dist,
+                                     reinterpret_cast<unsigned long long*>(near.b.batch), s));
+            return SLHC_OK;
+        }
         if (near.ok) {
             HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, reinterpret_cast<uint32_t*>(counters), 64, s));
             HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, colour, near.b, near.c, hn, nullptr, s));
@@ -1871,6 +1877,10 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::SweepParams p{};
+        if (near.ok && slhc::direct_1nn_wanted(m, n, d)) {
+            HIP_TRY(slhc::direct_1nn(Q, (int)m, (int)m, nullptr, Y, (int)n, d, nullptr, out_idx, out_dist, keys, s));
+            return SLHC_OK;
+        }
         if (near.ok) {
             HIP_TRY(slhc::near_stats(Y, (int)n, d, near.b, nullptr, 0, s));
             HIP_TRY(slhc::near_make(Y, (int)n, d, nullptr, (int)n, nullptr, near.b, near.c, hy, nullptr, s));

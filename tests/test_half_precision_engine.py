@@ -149,3 +149,32 @@ def test_lists_and_trees_in_the_row_order(lib, N, d, k, rows, spread):
     assert got["stats"]["pruned"] == 1
     for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
         assert torch.equal(want[key], got[key]), key
+
+
+# searches small enough to evaluate every pair: parts of a wavefront's queries, of a step of 64 candidates and of a slab of 64
+# features, one and many shares of the candidates, rows that are not finite or close to it, rows outside the matrix
+@pytest.mark.parametrize("m,n,d", [(1, 1, 1), (7, 63, 4), (9, 65, 31), (64, 1000, 64), (65, 1025, 65), (3, 30_000, 130), (2000, 700, 12)])
+def test_small_nearest_row_searches(lib, m, n, d):
+    print(f"small 1-NN m={m} n={n} d={d}", flush=True)
+    rng = np.random.default_rng(m + n + d)
+    Q, Y = rng.standard_normal((m, d)).astype(np.float32), rng.standard_normal((n, d)).astype(np.float32)
+    Y[n // 3] = Y[n // 2] = Q[m // 2]
+    if n > 100:
+        Y[5] = np.nan
+        Y[6] = 3e19
+        Q[0] = 1e19 if m > 5 else Q[0]
+    gi, gd = lib.fused_1nn(torch.from_numpy(Q).cuda(), torch.from_numpy(Y).cuda())
+    colour = np.r_[np.zeros(m, np.int32), np.ones(n, np.int32)]
+    both = torch.from_numpy(np.concatenate([Q, Y])).cuda()
+    rows = torch.tensor(list(range(m)) + [-1, m + n], dtype=torch.int32, device="cuda")
+    ci, cd = lib.cross_1nn(both, torch.from_numpy(colour).cuda(), rows)
+    torch.cuda.synchronize()
+    assert ci[m:].tolist() == [-1, -1] and torch.isinf(cd[m:]).all()
+    assert torch.equal(ci[:m], torch.where(gi >= 0, gi + m, gi)) and torch.equal(cd[:m], gd)
+    fine = np.flatnonzero(np.isfinite(Y).all(1) & (np.abs(Y).max(1) < 1e19))
+    D = ((Q[:, None, :].astype(np.float64) - Y[None, fine, :]) ** 2).sum(2) if m * len(fine) * d < 5e7 else None
+    if D is not None:
+        take = np.arange(1 if n > 100 and m > 5 else 0, m)
+        assert np.allclose(gd.cpu().numpy()[take], D.min(1)[take], rtol=1e-5, atol=1e-30)
+        exact = gi.cpu().numpy()[take] == fine[D.argmin(1)[take]]
+        assert exact.mean() >= 0.99
