@@ -56,7 +56,7 @@ typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
 #define SLHC_SEGMENT_HANDICAP 1.18   // see sweep_segments_for
 #endif
 #ifndef SLHC_SCAN_AHEAD_1NN
-#define SLHC_SCAN_AHEAD_1NN 4   // the same in the connection sweeps (8 and 16 measured: no gain at 2M x 32, 1-5 % slower at 1M x 128)
+#define SLHC_SCAN_AHEAD_1NN 4   // the same in the connection sweeps, for each of the four wavefronts that share a scan (see next_scan)
 #endif
 #ifndef SLHC_SCAN_AHEAD
 #define SLHC_SCAN_AHEAD 4      // groups of 64 scan positions whose lower bounds a pruned sweep reads at once (see next_scan)
@@ -1002,6 +1002,8 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
     unsigned long long ph_t = clock64();
 #endif
 
+    __shared__ int scan_hit[8];           // connection sweeps: first hits of the wavefronts' shares of a scan, two turns
+    int scan_parity = 0;
     int* next_panel = reinterpret_cast<int*>(L.wmax + 8);      // LDS word after the wmax slots
     unsigned int* panel_thr_bits = reinterpret_cast<unsigned int*>(L.wmax + 9);   // see the panel prologue
     // Pruned cross 1-NN sweeps with a slot map may split every panel's scan into p.segments work items (item =
@@ -1214,11 +1216,13 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
         // p.region_mode 1: only the candidate tiles of the panel's own region are of use; 2: only the others
         const int region_mode = (REGIONS && p.tile_region != nullptr && panel < ntiles) ? p.region_mode : 0;
         const int my_region = region_mode ? p.tile_region[panel] : 0;
-        auto gap_of = [&](int t) -> float {
+        auto gap_distance = [&](int t) -> float {
             float g = gap[t];
-            if (own_colour_test && p.tile_colour[t] == panel_colour) g = __builtin_nanf("");
             if (REGIONS && region_mode && ((p.tile_region[t] == my_region) != (region_mode == 1))) g = __builtin_nanf("");
             return g;
+        };
+        auto gap_of = [&](int t) -> float {
+            return own_colour_test && p.tile_colour[t] == panel_colour ? __builtin_nanf("") : gap_distance(t);
         };
         PHASE_MARK(1);
 
@@ -1281,8 +1285,8 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
 
         // Order in which the candidate tiles are visited.  Every-tile sweeps: 0, 1, 2, ...  Pruned
         // sweeps start at the tile the panel's own rows sit in (a self-join in the same row order
-        // visits that tile before the scan starts) and move outwards on both sides in turn: c+1, c-1,
-        // c+2, c-2, ... and on along the longer side once the shorter one is used up.  In a spatially
+        // visits that tile before the scan starts) and move outwards on both sides in turn, 32 tiles at a time,
+        // and on along the longer side once the shorter one is used up.  In a spatially
         // coherent order the nearest rows sit in the neighbouring tiles on either side, so the
         // thresholds tighten early and the gap test skips more of what follows.
         // `scan` indices count positions in that order; every lane of every wavefront evaluates
@@ -1305,7 +1309,11 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
             const int left = panel - p.tile_first[panel], right = p.tile_last[panel] - panel;
             const int reach = left > right ? left : right;
             const int to_r = ntiles - 1 - centre, to_l = centre;
-            const int within = (reach < to_l ? reach : to_l) + (reach < to_r ? reach : to_r) + (own_tile >= 0 ? 0 : 1);
+            int within = (reach < to_l ? reach : to_l) + (reach < to_r ? reach : to_r);
+            // (the scan takes 32 tiles of either side in turn, see scan_tile)
+            const int blocks = (to_l < to_r ? to_l : to_r) / 32;
+            if (reach <= blocks * 32) within = (reach + 31) / 32 * 64;
+            within += own_tile >= 0 ? 0 : 1;
             if (reach >= 0 && within < nscan_all) nscan_all = within;
         }
         // positions of this work item: part, part + nparts, ... of the panel's scan order
@@ -1317,10 +1325,17 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
                         : nparts > 1 ? (nscan_all > part ? (nscan_all - part + nparts - 1) / nparts : 0) : nscan_all;
         const int side_r = ntiles - 1 - centre, side_l = centre;
         const int side_min = side_r < side_l ? side_r : side_l;
+        const int side_blocks = side_min / 32 * 64;
         auto scan_tile = [&](int i) -> int {                   // 0 <= i < nscan
             if (!prune) return i + range_begin;
             if (nparts > 1) i = i * nparts + part;
             if (with_centre) { if (i == 0) return centre; --i; }
+            // 32 tiles on one side, then 32 on the other: what a wavefront reads of the bounds' row at once lies in two runs
+            // (one tile on either side in turn, every four lanes read two lines, four times over in four wavefronts)
+            if (i < side_blocks) {
+                const int j = (i >> 6) * 32 + (i & 31) + 1;
+                return (i & 32) ? centre - j : centre + j;
+            }
             if (i < 2 * side_min) { const int j = (i >> 1) + 1; return (i & 1) ? centre - j : centre + j; }
             const int r = i - 2 * side_min;
             return side_r > side_l ? centre + side_min + 1 + r : centre - side_min - 1 - r;
@@ -1328,24 +1343,46 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
         auto tile_of = [&](int i) -> int { return i >= nscan ? ntiles : scan_tile(i); };
         // (SCAN_AHEAD groups of 64 positions are read at once: one group at a time the scan is a chain of dependent
         // loads, a microsecond each, and a panel that multiplies two tiles of 20 000 spends its time there)
+        constexpr bool SHARED_SCAN = PRUNE && MASKED;
         constexpr int SCAN_AHEAD = MASKED ? SLHC_SCAN_AHEAD_1NN : SLHC_SCAN_AHEAD;
         auto next_scan = [&](int i, float thr_max) -> int {
             if (!prune) return i;
             while (i < nscan) {
+                // connection sweeps, whose panels read thousands of bounds for the tiles they multiply, share the positions out
+                // among the wavefronts (all of them come here together, see thr_c0):
+                // 2M x 32, 20 000 bounds for 15 tiles, 24.4 -> 18.4 ms of connection sweeps (30 ms before scan_tile's runs of 32)
+                const int i_from = i;
+                if (SHARED_SCAN) i += wave * 64 * SCAN_AHEAD;
+                int found = 0x7fffffff;
                 // (all the votes are taken before the first is looked at: a vote cannot move into a branch, so
                 // the loads behind it cannot either)
                 float g[SCAN_AHEAD];
+                int t[SCAN_AHEAD];
 #pragma unroll
                 for (int u = 0; u < SCAN_AHEAD; ++u) {
                     const int ii = i + 64 * u + lane;
-                    g[u] = ii < nscan ? gap_of(scan_tile(ii)) : __builtin_nanf("");
+                    t[u] = ii < nscan ? scan_tile(ii) : -1;
+                    g[u] = t[u] >= 0 ? gap_distance(t[u]) : __builtin_nanf("");
                 }
                 unsigned long long mask[SCAN_AHEAD];
 #pragma unroll
                 for (int u = 0; u < SCAN_AHEAD; ++u) mask[u] = __ballot(g[u] <= thr_max);          // false for NaN
+                // (colours only of the few tiles that are near enough)
 #pragma unroll
-                for (int u = 0; u < SCAN_AHEAD; ++u)
-                    if (mask[u]) return i + 64 * u + __builtin_ctzll(mask[u]);
+                for (int u = 0; u < SCAN_AHEAD; ++u) {
+                    if (mask[u] && own_colour_test) mask[u] = __ballot(g[u] <= thr_max && p.tile_colour[t[u]] != panel_colour);
+                    if (mask[u] && found == 0x7fffffff) found = i + 64 * u + __builtin_ctzll(mask[u]);
+                }
+                if (SHARED_SCAN) {
+                    if (lane == 0) scan_hit[scan_parity * 4 + wave] = found;
+                    __syncthreads();
+                    const int* hit = scan_hit + scan_parity * 4;
+                    scan_parity ^= 1;
+                    const int a = hit[0] < hit[1] ? hit[0] : hit[1], b = hit[2] < hit[3] ? hit[2] : hit[3];
+                    found = a < b ? a : b;
+                    i = i_from + 3 * 64 * SCAN_AHEAD;
+                }
+                if (found != 0x7fffffff) return found;
                 i += 64 * SCAN_AHEAD;
             }
             return nscan;
