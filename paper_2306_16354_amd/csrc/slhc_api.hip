@@ -2360,7 +2360,8 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     for (int r = 0; r < 12; ++r) { const int i = order_[(size_t)r]; std::fprintf(stderr, "[study]   panel %d: steps %d kcycles %d\n", i, hs[(size_t)i], hs[(size_t)study_panels + i]); }
                 }
 #endif
-                if (timed && round_pruned) ms_round_kernels += ev_conn.ms();
+                // (the list kernels' pruned sweeps have been waited for above; others are timed when later counters arrive)
+                if (timed && round_pruned && !round_ordered) ms_round_kernels += ev_conn.ms();
                 return SLHC_OK;
             };
             int queried = nq;
@@ -2398,8 +2399,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 if (rc != SLHC_OK) return rc;
             }
             st.connect_query_rows += queried;
-            if (round_pruned) HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
-            else conn_pending = timed;          // one sweep: its time is read when the next counters have arrived
+            if (round_pruned) {
+                HIP_TRY(mail.fetch(kws.counters, 8, h_surv));
+                if (timed && round_ordered) ms_round_kernels += ev_conn.ms();          // (one sweep, over by now)
+            } else conn_pending = timed;        // one sweep: its time is read when the next counters have arrived
             st.ms_connect_kernels += ms_round_kernels;
             if (round_pruned) ms_connect += now_ms() - tc0;
             if (round_pruned) {
