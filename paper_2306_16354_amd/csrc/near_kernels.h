@@ -21,7 +21,7 @@ struct NearScale {
 struct NearCopy {
     unsigned char* frag;       // [tiles][steps of 16 columns][4 blocks of 32 rows][64 lanes][16 bytes]
     float* negh;               // [tiles * 128] minus the half norm; -inf: no such row, +inf: values beyond float16
-    float* negh_best;          // [tiles * 128] or nullptr: the same with -inf for the latter (candidates of 1-NN searches)
+    float* negh_best;          // [tiles * 128] or nullptr: the same with -inf for the latter (candidates of 1-NN searches and near_assign)
     int32_t* colour;           // [tiles * 128] or nullptr
     // scratch of 1-NN searches for these rows as queries, or nullptr
     int32_t* left;             // [4 * tiles * 128]

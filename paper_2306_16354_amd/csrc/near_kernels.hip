@@ -2505,12 +2505,12 @@ __global__ void __launch_bounds__(256) near_unpack_kernel(const unsigned long lo
 hipError_t near_assign(const NearCopy& q, const NearCopy& c, const float* Xq, const int32_t* q_rows, const float* Xc, int d,
                        const NearBuffers& b, unsigned long long* best_at, int32_t* out_idx, float* out_dist, hipStream_t s)
 {
-    if (!c.finite_padding) return hipErrorInvalidValue;
-
+    if (!c.finite_padding || !c.negh_best) return hipErrorInvalidValue;
     NearPlan plan = near_plan(q.rows, c.rows, d, 1, (size_t)1 << 62);
     NearSweep p{};
     p.qfrag = q.frag; p.qnegh = q.negh; p.q_tile0 = 0; p.q_tile1 = q.tiles;
-    p.cfrag = c.frag; p.cnegh = c.negh; p.c_tiles = c.tiles;
+    // (without values beyond float16: their +inf would hide every other candidate of its lane)
+    p.cfrag = c.frag; p.cnegh = c.negh_best; p.c_tiles = c.tiles;
     p.sc = b.scale; p.d = d; p.steps = near_steps(d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
     p.nseg = plan.nseg; p.stride = 1; p.used = c.tiles; p.kk = 1;
     p.best_at = best_at;

@@ -687,7 +687,7 @@ struct OrderWs {
         local_scale = c.take<slhc::NearScale>(1);
         near_p.tiles = slhc::near_tiles(Pmax);
         near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
-        near_p.negh = c.take<float>((size_t)near_p.tiles * 128);
+        near_p.negh = c.take<float>((size_t)near_p.tiles * 128); near_p.negh_best = c.take<float>((size_t)near_p.tiles * 128);
         best_at = c.take<unsigned long long>((size_t)slhc::near_tiles(N) * 128);
         tmp_a = c.take<uint32_t>(n); tmp_b = c.take<uint32_t>(n); tmp_c = c.take<uint32_t>(n);
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
