@@ -111,6 +111,7 @@ struct NearOrder {
 hipError_t near_make_ordered(const float* X, int n_src, int d, const NearOrder& o, const float* tile_c, const float* tile_r,
                              const int32_t* tile_first, const float* hn, const NearBuffers& b, hipStream_t s);
 size_t near_ordered_batch_bytes(long long rows, int kk);
+size_t near_least_ordered_batch_bytes(long long rows, int kk);
 size_t near_linked_batch_bytes(long long rows);
 hipError_t near_search_ordered(const NearProblem& p, const NearOrder& o, const NearBuffers& b, hipStream_t s);
 hipError_t near_link_ordered(const NearLink& p, const NearOrder& o, const NearBuffers& b, hipStream_t s);

@@ -2032,6 +2032,12 @@ size_t near_ordered_batch_bytes(long long rows, int kk)
     return p.per_tile * (size_t)(most < p.panel_tiles ? p.panel_tiles : most) + 16384;
 }
 
+size_t near_least_ordered_batch_bytes(long long rows, int kk)
+{
+    const NearOrderedPlan p = near_ordered_plan(near_tiles(rows), kk);
+    return p.per_tile * (size_t)p.panel_tiles + 16384;
+}
+
 static bool near_order_ok(const NearOrder& o, int d)
 {
     return o.gap && o.perm && o.region && o.all.in_order && o.local.in_order && o.all.tiles == o.tiles && o.local.tiles == o.tiles &&

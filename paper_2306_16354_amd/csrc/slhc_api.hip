@@ -575,6 +575,7 @@ int first_level_pivots(int64_t N) { return (int)((N + SLHC_PIVOT_STRIDE - 1) / S
 // boundary; padding is limited to N/2 rows.
 int64_t padded_rows_limit(int64_t N) { return N + N / 2 + 256; }
 
+constexpr size_t NO_LIMIT = ~(size_t)0;      // of a workspace
 size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order);
 
 // tile products from split bfloat16 halves: whole chunks of 32 columns up to 128 features (the
@@ -591,12 +592,12 @@ struct NearWs {
     slhc::NearCopy c{}, q{};
     slhc::NearBuffers b{};
     bool ok = false;
-    // `most`: where the workspace ends (0: no limit); the batch takes what is left of it
+    // `most`: where the workspace ends; the batch takes what is left of it, and where that is too little there is no engine
+    // and nothing of it in the layout (ok stays false)
     // `ordered`: rows of a padded row order that is searched too (0: none)
-    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = 0, int64_t ordered = 0)
+    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = NO_LIMIT, int64_t ordered = 0)
     {
-        ok = slhc::near_supported(d);
-        if (!ok) return;
+        const size_t begin = w.off;
         auto copy = [&](slhc::NearCopy& x, int64_t n) {
             x.rows = (int)n; x.tiles = slhc::near_tiles(n);
             x.frag = w.take<unsigned char>(slhc::near_frag_bytes(n, d));
@@ -618,10 +619,20 @@ struct NearWs {
         b.todo = w.take<int32_t>((size_t)(2 + 2 * b.todo_panels));
         b.todo_mark = b.todo + 2 + b.todo_panels;
         b.batch_bytes = slhc::near_batch_bytes(queries, nc, d, kk);
-        if (ordered) b.batch_bytes = std::max({b.batch_bytes, slhc::near_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
-        if (most && w.off + b.batch_bytes > most) b.batch_bytes = most > w.off ? most - w.off : 0;
-        if (b.batch_bytes < slhc::near_least_batch_bytes(queries, nc, d, kk)) { ok = false; return; }
+        size_t least = slhc::near_least_batch_bytes(queries, nc, d, kk);
+        if (ordered) {
+            b.batch_bytes = std::max({b.batch_bytes, slhc::near_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
+            least = std::max({least, slhc::near_least_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
+        }
+        const size_t room = most > w.off ? (most - w.off) / ALIGN * ALIGN : 0;
+        if (b.batch_bytes > room) b.batch_bytes = room;
+        if (b.batch_bytes < least) {
+            *this = NearWs{};
+            w.off = begin;
+            return;
+        }
         b.batch = w.take<unsigned char>(b.batch_bytes);
+        ok = true;
     }
 };
 
@@ -642,13 +653,13 @@ struct OrderWs {
     unsigned long long* best_at;
     int32_t* near_colour;
     void* sort_temp; size_t sort_temp_bytes;
-    void* nested_ws; size_t nested_bytes;
+    void* nested_ws; size_t nested_bytes;      // of the clustering of the pivots, which keeps within it
     int P1, Pmax, Tmax;
     int64_t Nmax;
     int P = 0;        // pivots in use          (set by build_order)
     int Ns = 0;       // rows of the padded copy (set by build_order)
     static constexpr int SAMPLE = 4096;
-    void carve(Carver& c, int64_t N, int32_t d)
+    void carve(Carver& c, int64_t N, int32_t d, bool with_near)
     {
         const size_t n = (size_t)N;
         P1 = first_level_pivots(N);
@@ -678,17 +689,19 @@ struct OrderWs {
         pid = c.take<int32_t>(n); perm = c.take<int32_t>(nm); inv = c.take<int32_t>(n); colour_s = c.take<int32_t>(nm);
         qslot = c.take<int32_t>(nm); tile_colour = c.take<int32_t>((size_t)Tmax); tile_list = c.take<int32_t>((size_t)Tmax);
         counts = c.take<int32_t>(pm); rank = c.take<int32_t>(pm); shift = c.take<int32_t>(pm); far_count = c.take<int32_t>(64);
-        for (slhc::NearCopy* x : {&near_all, &near_local}) {
-            x->in_order = true;
-            x->frag = c.take<unsigned char>(slhc::near_frag_bytes(Nmax, d));
-            x->negh = c.take<float>((size_t)Tmax * 128); x->negh_best = c.take<float>((size_t)Tmax * 128);
+        if (with_near) {
+            for (slhc::NearCopy* x : {&near_all, &near_local}) {
+                x->in_order = true;
+                x->frag = c.take<unsigned char>(slhc::near_frag_bytes(Nmax, d));
+                x->negh = c.take<float>((size_t)Tmax * 128); x->negh_best = c.take<float>((size_t)Tmax * 128);
+            }
+            near_colour = c.take<int32_t>((size_t)Tmax * 128);
+            local_scale = c.take<slhc::NearScale>(1);
+            near_p.tiles = slhc::near_tiles(Pmax);
+            near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
+            near_p.negh = c.take<float>((size_t)near_p.tiles * 128); near_p.negh_best = c.take<float>((size_t)near_p.tiles * 128);
+            best_at = c.take<unsigned long long>((size_t)slhc::near_tiles(N) * 128);
         }
-        near_colour = c.take<int32_t>((size_t)Tmax * 128);
-        local_scale = c.take<slhc::NearScale>(1);
-        near_p.tiles = slhc::near_tiles(Pmax);
-        near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
-        near_p.negh = c.take<float>((size_t)near_p.tiles * 128); near_p.negh_best = c.take<float>((size_t)near_p.tiles * 128);
-        best_at = c.take<unsigned long long>((size_t)slhc::near_tiles(N) * 128);
         tmp_a = c.take<uint32_t>(n); tmp_b = c.take<uint32_t>(n); tmp_c = c.take<uint32_t>(n);
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
@@ -727,9 +740,18 @@ struct KnnWs {
     bool offset_heavy = false;       // the rows' norms are mostly a common offset (see run_knn): split products everywhere
     bool order_split_connect = false;   // the pruned connection sweeps multiply the split copy of the reordered rows too
     size_t bytes;
-    KnnWs(void* ws, int64_t N, int32_t d, bool with_order, int32_t k = 0)
+    // `most`: bytes there are.  Too few for the half-precision engine: the layout without it (whose `bytes` may exceed them too).
+    KnnWs(void* ws, int64_t N, int32_t d, bool with_order, int32_t k = 0, size_t most = NO_LIMIT)
+    {
+        lay_out(ws, N, d, with_order, k, k > 0, most);
+        if (k > 0 && !near.ok) lay_out(ws, N, d, with_order, k, false, most);
+    }
+private:
+    void lay_out(void* ws, int64_t N, int32_t d, bool with_order, int32_t k, bool with_near, size_t most)
     {
         Carver c(ws);
+        order = OrderWs();
+        near = NearWs();
         counters = c.take<unsigned long long>(32);
         hn = c.take<float>((size_t)N);
         part_idx = nullptr; part_dist = nullptr; part_rows = 0;
@@ -754,9 +776,9 @@ struct KnnWs {
         carry_ws_words = 2 + (long long)((N + 127) / 128);
         carry_ws = c.take<unsigned int>((size_t)carry_ws_words);
         has_order = with_order && prunable(N, d);
-        if (has_order) order.carve(c, N, d);
+        if (has_order) order.carve(c, N, d, with_near);
         // (the queries' copy and the colours serve the every-tile connection sweeps)
-        if (k > 0) near.carve(c, N, N, d, k + 1, true, 0, has_order ? order.Nmax : 0);
+        if (with_near) near.carve(c, N, N, d, k + 1, true, most, has_order ? order.Nmax : 0);
         bytes = c.off;
     }
 };
@@ -770,11 +792,21 @@ struct SlhcWs {
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
     size_t bytes;
-    SlhcWs(void* ws, int64_t N, int32_t d, int32_t k, bool with_order)
+    size_t knn_most = NO_LIMIT;      // bytes there are for knn_ws (see KnnWs)
+    SlhcWs(void* ws, int64_t N, int32_t d, int32_t k, bool with_order, size_t most = NO_LIMIT)
+    {
+        if (most != NO_LIMIT) {
+            lay_out(nullptr, N, k, 0);                   // what everything else takes
+            knn_most = most > bytes ? most - bytes : 0;
+        }
+        lay_out(ws, N, k, KnnWs(nullptr, N, d, with_order, k, knn_most).bytes);
+    }
+private:
+    void lay_out(void* ws, int64_t N, int32_t k, size_t knn_bytes)
     {
         Carver c(ws);
         const size_t n = (size_t)N;
-        knn_ws = c.take<unsigned char>(KnnWs(nullptr, N, d, with_order, k).bytes);
+        knn_ws = c.take<unsigned char>(knn_bytes);
         nbr_idx = c.take<int32_t>(n * k);
         nbr_dist = c.take<float>(n * k);
         colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);
@@ -794,7 +826,7 @@ struct SlhcWs {
 size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order) { return SlhcWs(nullptr, N, d, k, with_order).bytes; }
 
 int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, int32_t* mst_dst, float* mst_w,
-             int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace,
+             int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace, size_t workspace_bytes,
              hipStream_t s, uint32_t flags, bool with_order);
 
 int bits_for(long long n) { int b = 1; while (b < 32 && (1LL << b) < n) ++b; return b; }
@@ -959,7 +991,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     if (P >= 2) {
         const int32_t kp = P - 1 < NESTED_K ? P - 1 : NESTED_K;
         rc = run_slhc(o.Xp, P, d, kp, o.n_src, o.n_dst, o.n_w, nullptr, nullptr, nullptr, nullptr,
-                      o.nested_ws, s, 0u, false);
+                      o.nested_ws, o.nested_bytes, s, 0u, false);
         if (rc != SLHC_OK) return rc;
         const size_t E = (size_t)(P - 1);
         HIP_TRY(hipMemcpyAsync(h_src, o.n_src, E * 4, hipMemcpyDeviceToHost, s));
@@ -1991,7 +2023,7 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
             X = static_cast<const float*>(workspace);
         }
         return run_slhc(X, N, dw, k, mst_src, mst_dst, mst_w, children, heights, sizes, stats,
-                        static_cast<unsigned char*>(workspace) + head, static_cast<hipStream_t>(stream), flags, true);
+                        static_cast<unsigned char*>(workspace) + head, workspace_bytes - head, static_cast<hipStream_t>(stream), flags, true);
     });
 }
 
@@ -2002,11 +2034,12 @@ namespace {
 // The whole pipeline on validated arguments.  `with_order` selects the workspace layout (the
 // nested call that clusters the pivots of the row order runs without one).
 int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, int32_t* mst_dst, float* mst_w,
-             int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace,
+             int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace, size_t workspace_bytes,
              hipStream_t s, uint32_t flags, bool with_order)
 {
     int rc = SLHC_OK;
-    SlhcWs ws(workspace, N, d, k, with_order);
+    SlhcWs ws(workspace, N, d, k, with_order, workspace_bytes);
+    if (ws.bytes > workspace_bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, ws.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
     slhc_stats st;
     std::memset(&st, 0, sizeof(st));
     const double t_begin = now_ms();
@@ -2022,7 +2055,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         HIP_TRY(ev_conn.create());
     }
     bool pruned = false;
-    KnnWs kws(ws.knn_ws, N, d, with_order, k);   // half norms and row order are reused by the connection sweeps
+    KnnWs kws(ws.knn_ws, N, d, with_order, k, ws.knn_most);      // half norms and row order are reused by the connection sweeps
     rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, timed ? &ev_norm : nullptr, timed ? &ev_order : nullptr,
                  timed ? &ev_knn : nullptr);
     if (rc != SLHC_OK) return rc;
