@@ -19,8 +19,17 @@
  *     non-finite norm is never reported as anybody's neighbour, and the entries of its own result
  *     are unspecified except that every index written is -1 or a valid row.
  *   - `stream` is a hipStream_t passed as void* (NULL = the default stream).
- *   - `workspace` is DEVICE scratch of at least the size the matching *_workspace_bytes call
- *     reports, 256-byte aligned; its contents on entry are ignored and on exit unspecified.
+ *   - `workspace` is DEVICE scratch, 256-byte aligned; its contents on entry are ignored and on exit
+ *     unspecified.  The matching *_workspace_bytes call reports the size with which a call is fastest.
+ *     The k-NN, 1-NN and clustering entry points also take less: the half-precision engine (which keeps
+ *     float16 copies of the rows and about 1.2 MiB of scratch per 128 queries of a batch, 1024 x 128
+ *     queries at most) then works in smaller batches, and where it does not fit the list kernels run,
+ *     which need none of that.  Same outputs, bit for bit.  SLHC_WORKSPACE_TOO_SMALL is returned below
+ *     that, and its message names the least there must be.  Reported and least, in MB:
+ *       slhc_slhc       100 000 x 64, k = 32: 1470 and 193    1 000 000 x 128, k = 32: 6180 and 3850
+ *                       250 000 x 784, k = 16: 2850 and 858   100 000 000 x 8, k = 8: 41 400 and 28 500
+ *       slhc_fused_1nn  1000 queries, 100 000 x 128: 29 and 0.42    10 queries, 2 000 000 x 64: 280 and 8
+ *       slhc_cross_1nn  10 000 of 100 000 x 64: 37 and 0.41         10 of 1 000 000 x 64: 144 and 4
  *   - Every function returns an slhc_status.  No C++ exception crosses the boundary (a failed
  *     host allocation becomes SLHC_HOST_MEMORY).  On any status other than SLHC_OK the outputs are
  *     unspecified.  slhc_last_error() gives a thread-local detail string for the last failing call

@@ -576,7 +576,8 @@ int first_level_pivots(int64_t N) { return (int)((N + SLHC_PIVOT_STRIDE - 1) / S
 int64_t padded_rows_limit(int64_t N) { return N + N / 2 + 256; }
 
 constexpr size_t NO_LIMIT = ~(size_t)0;      // of a workspace
-size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order);
+// (with_near = false: without the half-precision engine)
+size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order, bool with_near);
 
 // tile products from split bfloat16 halves: whole chunks of 32 columns up to 128 features (the
 // register-resident-query kernel); beyond 128 features the streaming kernel takes any multiple of 4 columns,
@@ -595,25 +596,34 @@ struct NearWs {
     // `most`: where the workspace ends; the batch takes what is left of it, and where that is too little there is no engine
     // and nothing of it in the layout (ok stays false)
     // `ordered`: rows of a padded row order that is searched too (0: none)
-    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = NO_LIMIT, int64_t ordered = 0)
+    // `lent`: memory for the copy of the queries that the layout has anyway
+    void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = NO_LIMIT, int64_t ordered = 0,
+               const slhc::NearCopy* lent = nullptr)
     {
         const size_t begin = w.off;
-        auto copy = [&](slhc::NearCopy& x, int64_t n) {
+        auto copy = [&](slhc::NearCopy& x, int64_t n, bool queries) {
             x.rows = (int)n; x.tiles = slhc::near_tiles(n);
             x.frag = w.take<unsigned char>(slhc::near_frag_bytes(n, d));
             x.negh = w.take<float>((size_t)x.tiles * 128);
             x.negh_best = kk == 1 || coloured ? w.take<float>((size_t)x.tiles * 128) : nullptr;
             x.colour = coloured ? w.take<int32_t>((size_t)x.tiles * 128) : nullptr;
+            x.left = nullptr; x.count = nullptr; x.best_at = nullptr;
+            if (!queries) return;
             x.left = w.take<int32_t>((size_t)x.tiles * 128 * (kk == 1 ? 4 : 1));      // (one part serves k-NN searches as scratch)
             x.count = w.take<int32_t>((size_t)x.tiles * 128);
-            x.best_at = nullptr;
+            if (coloured) x.best_at = w.take<unsigned long long>((size_t)x.tiles * 128);
         };
         b.scale = w.take<slhc::NearScale>(1);
         b.shift = w.take<float>((size_t)d + 8);
         b.partial = w.take<float>(slhc::near_stats_scratch_floats(d));
-        copy(c, nc);
-        if (nq > 0) copy(q, nq); else q = c;
-        if (nq > 0 && coloured) q.best_at = w.take<unsigned long long>((size_t)q.tiles * 128);
+        copy(c, nc, false);
+        if (lent) {
+            q = *lent;
+            q.rows = (int)nq; q.tiles = slhc::near_tiles(nq);
+            q.left = w.take<int32_t>((size_t)q.tiles * 128);
+            q.count = w.take<int32_t>((size_t)q.tiles * 128);
+        } else if (nq > 0) copy(q, nq, true);
+        else q = c;                                         // (k-NN: no scratch per query)
         const int64_t queries = nq > 0 ? nq : nc;
         b.todo_panels = (std::max(queries, ordered) + 127) / 128;
         b.todo = w.take<int32_t>((size_t)(2 + 2 * b.todo_panels));
@@ -652,6 +662,7 @@ struct OrderWs {
     slhc::NearCopy near_p{};          // that of the pivots, and scratch of the assignment
     unsigned long long* best_at;
     int32_t* near_colour;
+    bool near_searched;               // near_all, near_local, near_colour and local_scale exist
     void* sort_temp; size_t sort_temp_bytes;
     void* nested_ws; size_t nested_bytes;      // of the clustering of the pivots, which keeps within it
     int P1, Pmax, Tmax;
@@ -669,27 +680,16 @@ struct OrderWs {
         const size_t nm = (size_t)Nmax, pm = (size_t)Pmax;
         Xp = c.take<float>(pm * d); hp = c.take<float>(pm);
         pdist = c.take<float>(n); sample = c.take<float>(SAMPLE);
+        // The copies in the row order are made when the pivots' clustering is over, whose workspace takes the same place.
+        const size_t copies_begin = c.off;
         Xs = c.take<float>(nm * d); hs = c.take<float>(nm);
         Xs_split = nullptr; hs_split = nullptr;
         if (split_products_ok(d)) { Xs_split = c.take<float>(nm * d); hs_split = c.take<float>(nm); }
         Xs_local = nullptr; hs_local = nullptr; region_other_min = nullptr;
-        tile_region = c.take<int32_t>((size_t)Tmax); tile_first = c.take<int32_t>((size_t)Tmax);
-        tile_last = c.take<int32_t>((size_t)Tmax);
-        tile_boundary = c.take<int32_t>((size_t)Tmax); tile_local = c.take<int32_t>((size_t)Tmax);
-        if (split_products_ok(d) && d <= 128) {
-            Xs_local = c.take<float>(nm * d); hs_local = c.take<float>(nm);
-            region_other_min = c.take<float>((size_t)Tmax);
-        }
-        tile_c = c.take<float>((size_t)Tmax * d); tile_r = c.take<float>((size_t)Tmax);
-        int grid = slhc::sweep_grid_limit();
-        if (grid < 1) grid = 512;
-        gap_ws = c.take<float>((size_t)grid * Tmax);
-        // lower bounds between all pairs of tiles (order_tile_gaps), as long as the table stays moderate
-        tile_gap = Tmax <= TILE_GAP_MAX_TILES ? c.take<float>((size_t)Tmax * Tmax) : nullptr;
-        pid = c.take<int32_t>(n); perm = c.take<int32_t>(nm); inv = c.take<int32_t>(n); colour_s = c.take<int32_t>(nm);
-        qslot = c.take<int32_t>(nm); tile_colour = c.take<int32_t>((size_t)Tmax); tile_list = c.take<int32_t>((size_t)Tmax);
-        counts = c.take<int32_t>(pm); rank = c.take<int32_t>(pm); shift = c.take<int32_t>(pm); far_count = c.take<int32_t>(64);
-        if (with_near) {
+        if (split_products_ok(d) && d <= 128) { Xs_local = c.take<float>(nm * d); hs_local = c.take<float>(nm); }
+        // searches of the half-precision engine in this order need the table of tile pairs
+        near_searched = with_near && Tmax <= TILE_GAP_MAX_TILES;
+        if (near_searched) {
             for (slhc::NearCopy* x : {&near_all, &near_local}) {
                 x->in_order = true;
                 x->frag = c.take<unsigned char>(slhc::near_frag_bytes(Nmax, d));
@@ -697,6 +697,29 @@ struct OrderWs {
             }
             near_colour = c.take<int32_t>((size_t)Tmax * 128);
             local_scale = c.take<slhc::NearScale>(1);
+        }
+        int grid = slhc::sweep_grid_limit();
+        if (grid < 1) grid = 512;
+        {
+            const int32_t kp = Pmax - 1 < NESTED_K ? Pmax - 1 : NESTED_K;
+            // (the clustering runs on the pivots in use, fewer than Pmax: a k-NN sweep of few panels then also wants
+            // its scratch for candidate ranges, which the layout for Pmax rows may not contain)
+            nested_bytes = slhc_ws_bytes(Pmax, d, kp, false, with_near) + (size_t)grid * 128 * (size_t)kp * 8 + 1024;
+            nested_ws = c.base ? c.base + copies_begin : nullptr;
+            if (c.off < copies_begin + up(nested_bytes)) c.off = copies_begin + up(nested_bytes);
+        }
+        tile_region = c.take<int32_t>((size_t)Tmax); tile_first = c.take<int32_t>((size_t)Tmax);
+        tile_last = c.take<int32_t>((size_t)Tmax);
+        tile_boundary = c.take<int32_t>((size_t)Tmax); tile_local = c.take<int32_t>((size_t)Tmax);
+        if (Xs_local) region_other_min = c.take<float>((size_t)Tmax);
+        tile_c = c.take<float>((size_t)Tmax * d); tile_r = c.take<float>((size_t)Tmax);
+        gap_ws = c.take<float>((size_t)grid * Tmax);
+        // lower bounds between all pairs of tiles (order_tile_gaps), as long as the table stays moderate
+        tile_gap = Tmax <= TILE_GAP_MAX_TILES ? c.take<float>((size_t)Tmax * Tmax) : nullptr;
+        pid = c.take<int32_t>(n); perm = c.take<int32_t>(nm); inv = c.take<int32_t>(n); colour_s = c.take<int32_t>(nm);
+        qslot = c.take<int32_t>(nm); tile_colour = c.take<int32_t>((size_t)Tmax); tile_list = c.take<int32_t>((size_t)Tmax);
+        counts = c.take<int32_t>(pm); rank = c.take<int32_t>(pm); shift = c.take<int32_t>(pm); far_count = c.take<int32_t>(64);
+        if (with_near) {
             near_p.tiles = slhc::near_tiles(Pmax);
             near_p.frag = c.take<unsigned char>(slhc::near_frag_bytes(Pmax, d));
             near_p.negh = c.take<float>((size_t)near_p.tiles * 128); near_p.negh_best = c.take<float>((size_t)near_p.tiles * 128);
@@ -706,11 +729,15 @@ struct OrderWs {
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
         n_src = c.take<int32_t>(pm); n_dst = c.take<int32_t>(pm); n_w = c.take<float>(pm);
-        const int32_t kp = Pmax - 1 < NESTED_K ? Pmax - 1 : NESTED_K;
-        // (the clustering runs on the pivots in use, fewer than Pmax: a k-NN sweep of few panels then also wants
-        // its scratch for candidate ranges, which the layout for Pmax rows may not contain)
-        nested_bytes = slhc_ws_bytes(Pmax, d, kp, false) + (size_t)grid * 128 * (size_t)kp * 8 + 1024;
-        nested_ws = c.take<unsigned char>(nested_bytes);
+    }
+    // Memory of a copy of listed rows: that of the copy in this order, which is made later and no longer used when the
+    // connection rounds come to make one.
+    slhc::NearCopy lent_copy() const
+    {
+        slhc::NearCopy q{};
+        q.frag = near_all.frag; q.negh = near_all.negh; q.negh_best = near_all.negh_best;
+        q.colour = near_colour; q.best_at = best_at;
+        return q;
     }
 };
 
@@ -740,14 +767,15 @@ struct KnnWs {
     bool offset_heavy = false;       // the rows' norms are mostly a common offset (see run_knn): split products everywhere
     bool order_split_connect = false;   // the pruned connection sweeps multiply the split copy of the reordered rows too
     size_t bytes;
+    // `connect`: for connection rounds too.
     // `most`: bytes there are.  Too few for the half-precision engine: the layout without it (whose `bytes` may exceed them too).
-    KnnWs(void* ws, int64_t N, int32_t d, bool with_order, int32_t k = 0, size_t most = NO_LIMIT)
+    KnnWs(void* ws, int64_t N, int32_t d, bool with_order, int32_t k, bool connect, size_t most = NO_LIMIT)
     {
-        lay_out(ws, N, d, with_order, k, k > 0, most);
-        if (k > 0 && !near.ok) lay_out(ws, N, d, with_order, k, false, most);
+        lay_out(ws, N, d, with_order, k, connect, k > 0, most);
+        if (k > 0 && !near.ok) lay_out(ws, N, d, with_order, k, connect, false, most);
     }
 private:
-    void lay_out(void* ws, int64_t N, int32_t d, bool with_order, int32_t k, bool with_near, size_t most)
+    void lay_out(void* ws, int64_t N, int32_t d, bool with_order, int32_t k, bool connect, bool with_near, size_t most)
     {
         Carver c(ws);
         order = OrderWs();
@@ -777,8 +805,12 @@ private:
         carry_ws = c.take<unsigned int>((size_t)carry_ws_words);
         has_order = with_order && prunable(N, d);
         if (has_order) order.carve(c, N, d, with_near);
-        // (the queries' copy and the colours serve the every-tile connection sweeps)
-        if (with_near) near.carve(c, N, N, d, k + 1, true, most, has_order ? order.Nmax : 0);
+        // (the queries' copy serves the making of the row order and, as the colours, the every-tile connection sweeps)
+        if (with_near) {
+            const bool searched = has_order && order.near_searched;
+            const slhc::NearCopy lent = searched ? order.lent_copy() : slhc::NearCopy{};
+            near.carve(c, N, connect || has_order ? N : 0, d, k + 1, connect, most, searched ? order.Nmax : 0, searched ? &lent : nullptr);
+        }
         bytes = c.off;
     }
 };
@@ -796,13 +828,14 @@ struct SlhcWs {
     SlhcWs(void* ws, int64_t N, int32_t d, int32_t k, bool with_order, size_t most = NO_LIMIT)
     {
         if (most != NO_LIMIT) {
-            lay_out(nullptr, N, k, 0);                   // what everything else takes
+            lay_out(nullptr, N, k, 0, true);             // what everything else takes
             knn_most = most > bytes ? most - bytes : 0;
         }
-        lay_out(ws, N, k, KnnWs(nullptr, N, d, with_order, k, knn_most).bytes);
+        const KnnWs knn(nullptr, N, d, with_order, k, true, knn_most);
+        lay_out(ws, N, k, knn.bytes, knn.near.ok);
     }
 private:
-    void lay_out(void* ws, int64_t N, int32_t k, size_t knn_bytes)
+    void lay_out(void* ws, int64_t N, int32_t k, size_t knn_bytes, bool with_near)
     {
         Carver c(ws);
         const size_t n = (size_t)N;
@@ -813,7 +846,7 @@ private:
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); qlist = c.take<int32_t>(n);
         q_idx = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
-        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); q_low = c.take<float>(n); cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
+        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); q_low = with_near ? c.take<float>(n) : nullptr; cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
@@ -823,7 +856,7 @@ private:
     }
 };
 
-size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order) { return SlhcWs(nullptr, N, d, k, with_order).bytes; }
+size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order, bool with_near) { return SlhcWs(nullptr, N, d, k, with_order, with_near ? NO_LIMIT : 0).bytes; }
 
 int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, int32_t* mst_dst, float* mst_w,
              int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace, size_t workspace_bytes,
@@ -1506,7 +1539,7 @@ int slhc_knn_workspace_bytes(int64_t N, int32_t d, int32_t k, size_t* bytes)
         if (!bytes) { set_err("bytes is NULL"); return SLHC_INVALID_ARG; }
         const int rc = check_shape(N, d, k, true);
         if (rc != SLHC_OK) return rc;
-        *bytes = padded_copy_bytes(N, d) + KnnWs(nullptr, N, working_columns(N, d), true, k).bytes;
+        *bytes = padded_copy_bytes(N, d) + KnnWs(nullptr, N, working_columns(N, d), true, k, false).bytes;
         return SLHC_OK;
     });
 }
@@ -1520,7 +1553,7 @@ int slhc_knn_graph_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t*
         if (rc != SLHC_OK) return rc;
         const int32_t dw = working_columns(N, d);
         const size_t head = padded_copy_bytes(N, d);
-        KnnWs ws(static_cast<unsigned char*>(workspace) + head, N, dw, true, k);
+        KnnWs ws(static_cast<unsigned char*>(workspace) + head, N, dw, true, k, false, workspace_bytes > head ? workspace_bytes - head : 0);
         if (workspace_bytes < head + ws.bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, head + ws.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
         const bool prune = (flags & SLHC_PRUNE) && ws.has_order;
         if (!prune && near_wanted(ws.near, flags))          // (reads the rows as they are)
@@ -1567,7 +1600,7 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k, int32
             if (near.ok && c.off <= STATIC_SCRATCH_BYTES)
                 return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream));
         }
-        KnnWs ws(ptr, N, d, false);                 // counters (cleared by run_knn) + half norms (all N written)
+        KnnWs ws(ptr, N, d, false, 0, false);       // counters (cleared by run_knn) + half norms (all N written)
         if (ws.bytes > STATIC_SCRATCH_BYTES) { set_err("scratch layout %zu > %zu bytes", ws.bytes, STATIC_SCRATCH_BYTES); return SLHC_INTERNAL; }
         return run_knn(X, N, d, k, nbr_idx, nbr_dist, ws, static_cast<hipStream_t>(stream), 0u);
     });
@@ -1652,16 +1685,25 @@ int slhc_probe_panel_loop(int32_t steps, double* tflops, void* workspace, size_t
     });
 }
 
-static void cross_1nn_carve(Carver& c, int64_t N, int32_t d, int64_t m, unsigned long long** counters, float** hn, NearWs* near)
-{
-    unsigned long long* w = c.take<unsigned long long>(32);
-    float* h = c.take<float>((size_t)N);
-    NearWs local;
-    NearWs& n = near ? *near : local;
-    if (m > 0) n.carve(c, N, m, d, 1, true);
-    if (counters) *counters = w;
-    if (hn) *hn = h;
-}
+// Scratch of slhc_cross_1nn, `most` bytes of it.  A search that evaluates every pair needs a word per query besides, one of the
+// half-precision engine its copies; the list kernels, which run where neither fits, need nothing else.
+struct CrossWs {
+    unsigned long long* counters;
+    float* hn;
+    unsigned long long* keys = nullptr;
+    NearWs near;
+    size_t bytes;
+    CrossWs(void* ws, int64_t N, int32_t d, int64_t m, size_t most = NO_LIMIT)
+    {
+        Carver c(ws);
+        counters = c.take<unsigned long long>(32);
+        hn = c.take<float>((size_t)N);
+        if (m > 0 && slhc::direct_1nn_wanted(m, N, d)) {
+            if (most > c.off && up((size_t)m * 8) <= most - c.off) keys = c.take<unsigned long long>((size_t)m);
+        } else if (m > 0) near.carve(c, N, m, d, 1, true, most);
+        bytes = c.off;
+    }
+};
 
 int slhc_cross_1nn_workspace_bytes(int64_t N, int32_t d, int64_t m, size_t* bytes)
 {
@@ -1670,9 +1712,7 @@ int slhc_cross_1nn_workspace_bytes(int64_t N, int32_t d, int64_t m, size_t* byte
         const int rc = check_shape(N, d, 1, false);
         if (rc != SLHC_OK) return rc;
         if (m < 0 || m > 2147483647LL) { set_err("bad m"); return SLHC_INVALID_ARG; }
-        Carver c(nullptr);
-        cross_1nn_carve(c, N, d, m, nullptr, nullptr, nullptr);
-        *bytes = c.off;
+        *bytes = CrossWs(nullptr, N, d, m).bytes;
         return SLHC_OK;
     });
 }
@@ -1686,31 +1726,31 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
         const int rc = check_shape(N, d, 1, false);
         if (rc != SLHC_OK) return rc;
         if (m < 0 || m > 2147483647LL || (!rows && m > N)) { set_err("bad m=%lld", (long long)m); return SLHC_INVALID_ARG; }
-        Carver c(workspace);
-        unsigned long long* counters = nullptr;
-        float* hn = nullptr;
-        NearWs near;
-        cross_1nn_carve(c, N, d, m, &counters, &hn, &near);
-        if (workspace_bytes < c.off) { set_err("workspace %zu < %zu bytes", workspace_bytes, c.off); return SLHC_WORKSPACE_TOO_SMALL; }
+        const CrossWs ws(workspace, N, d, m, workspace_bytes);
+        const NearWs& near = ws.near;
+        unsigned long long* counters = ws.counters;
+        float* hn = ws.hn;
+        if (workspace_bytes < ws.bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, ws.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
         if (m == 0) return SLHC_OK;
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::SweepParams p{};
-        if (near.ok && slhc::direct_1nn_wanted(m, N, d)) {
-            HIP_TRY(slhc::direct_1nn(X, (int)m, (int)N, rows, X, (int)N, d, colour, out_idx, out_dist,
-                                     reinterpret_cast<unsigned long long*>(near.b.batch), s));
+        if (ws.keys) {
+            HIP_TRY(slhc::direct_1nn(X, (int)m, (int)N, rows, X, (int)N, d, colour, out_idx, out_dist, ws.keys, s));
             return SLHC_OK;
         }
         if (near.ok) {
             HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, reinterpret_cast<uint32_t*>(counters), 64, s));
-            HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, colour, near.b, near.c, hn, nullptr, s));
             const bool all = !rows && m == N;            // queries are the candidates
+            slhc::NearCopy c = near.c;
+            if (all) { c.left = near.q.left; c.count = near.q.count; }
+            HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, colour, near.b, c, hn, nullptr, s));
             if (!all) HIP_TRY(slhc::near_make(X, (int)N, d, rows, (int)m, colour, near.b, near.q, nullptr, nullptr, s));
             slhc::NearProblem a{};
             a.Xq = a.Xc = X; a.d = d; a.k = 1;
             a.q_rows = rows; a.nq = (int)m; a.nq_rows = a.nc = (int)N;
             a.coloured = 1;
             a.out_idx = out_idx; a.out_dist = out_dist;
-            HIP_TRY(slhc::near_search(a, all ? near.c : near.q, near.c, near.b, s));
+            HIP_TRY(slhc::near_search(a, all ? c : near.q, c, near.b, s));
             p.todo = near.b.todo;
         } else {
             hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(counters), 64);
@@ -1873,13 +1913,16 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
     });
 }
 
-static size_t fused_1nn_layout(void* ws, int64_t m, int64_t n, int32_t d, float** hq, float** hy, unsigned long long** keys, NearWs* near)
+// (a search that evaluates every pair, and the list kernels, which run where the half-precision engine does not fit, need no more
+// than the words per row)
+static size_t fused_1nn_layout(void* ws, int64_t m, int64_t n, int32_t d, float** hq, float** hy, unsigned long long** keys, NearWs* near,
+                               size_t most = NO_LIMIT)
 {
     Carver c(ws);
     *hq = c.take<float>((size_t)m);
     *hy = c.take<float>((size_t)n);
     *keys = c.take<unsigned long long>((size_t)m);
-    near->carve(c, n, m, d, 1, false);
+    if (!slhc::direct_1nn_wanted(m, n, d)) near->carve(c, n, m, d, 1, false, most);
     return c.off;
 }
 
@@ -1905,11 +1948,11 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
         if (m * (int64_t)d > 2147483647LL || n * (int64_t)d > 2147483647LL) { set_err("m*d or n*d exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
         float *hq, *hy; unsigned long long* keys;
         NearWs near;
-        const size_t need = fused_1nn_layout(workspace, m, n, d, &hq, &hy, &keys, &near);
+        const size_t need = fused_1nn_layout(workspace, m, n, d, &hq, &hy, &keys, &near, workspace_bytes);
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::SweepParams p{};
-        if (near.ok && slhc::direct_1nn_wanted(m, n, d)) {
+        if (slhc::direct_1nn_wanted(m, n, d)) {
             HIP_TRY(slhc::direct_1nn(Q, (int)m, (int)m, nullptr, Y, (int)n, d, nullptr, out_idx, out_dist, keys, s));
             return SLHC_OK;
         }
@@ -2015,7 +2058,7 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
         if (rc != SLHC_OK) return rc;
         const int32_t dw = working_columns(N, d);
         const size_t head = padded_copy_bytes(N, d);
-        const size_t need = head + slhc_ws_bytes(N, dw, k, true);
+        const size_t need = head + SlhcWs(nullptr, N, dw, k, true, workspace_bytes > head ? workspace_bytes - head : 0).bytes;
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         if (dw != d) {
             const int rp = pad_columns(X, N, d, dw, static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
@@ -2055,7 +2098,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         HIP_TRY(ev_conn.create());
     }
     bool pruned = false;
-    KnnWs kws(ws.knn_ws, N, d, with_order, k, ws.knn_most);      // half norms and row order are reused by the connection sweeps
+    KnnWs kws(ws.knn_ws, N, d, with_order, k, true, ws.knn_most);      // half norms and row order are reused by the connection sweeps
     rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, timed ? &ev_norm : nullptr, timed ? &ev_order : nullptr,
                  timed ? &ev_knn : nullptr);
     if (rc != SLHC_OK) return rc;
@@ -2332,6 +2375,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     }
                     slhc::NearCopy q = near.q;
                     q.rows = n; q.tiles = slhc::near_tiles(n); q.in_order = true;
+                    kws.near_order_ready = false;           // (in whose memory the copy of the queries may lie)
                     HIP_TRY(slhc::near_colours(near.c, ws.colour, s));
                     // (the arrays of the edge sort and of the thresholds are free until then)
                     HIP_TRY(hipMemcpyAsync(ws.vals_a, ws.best_w, (size_t)N * sizeof(uint32_t), hipMemcpyDeviceToDevice, s));
