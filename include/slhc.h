@@ -188,10 +188,10 @@ int slhc_knn_graph_opt(const float* X, int64_t N, int32_t d, int32_t k,
  * slhc_knn_graph for callers that cannot allocate and have no workspace to pass: code under HIP
  * graph capture, tight serving loops, harnesses that forbid hipMalloc.  Same kernels and the same
  * result as slhc_knn_graph, bit for bit; the scratch they need is a fixed device array inside the library of 128 MiB,
- * which every GPU the library runs on holds until the process ends.  It holds the float16 copy of about 300 000 rows of
+ * which every GPU this entry point is called on holds from its first call there until the process ends.  It holds the float16 copy of about 300 000 rows of
  * 128 features; larger inputs go through the float32-product list kernels (same result, slower).  The call allocates
  * and frees nothing, on the device or on the host (its first call on a device looks up the
- * array's address).  N > SLHC_STATIC_MAX_ROWS is rejected with SLHC_UNSUPPORTED.
+ * array's address, at which the runtime makes room for the array; that call may be captured too).  N > SLHC_STATIC_MAX_ROWS is rejected with SLHC_UNSUPPORTED.
  * All calls on one GPU share that array: two calls that overlap in time on one GPU (different
  * streams or threads) race; calls in order on one stream are safe.  Asynchronous on `stream`.
  * The counters are cleared by a kernel, not a memset node, so the call may be captured.

@@ -23,6 +23,7 @@
 #include "near_kernels.h"
 #include "direct_kernels.h"
 #include "order_kernels.h"
+#include "static_scratch.h"
 #include "sweep_kernels.h"
 
 namespace {
@@ -1481,19 +1482,14 @@ int host_threads()
     return t < 1 ? 1 : (t > 16 ? 16 : t);
 }
 
-// ---- scratch of slhc_knn_graph_static: the workspace of the every-tile k-NN path as a fixed device array.  At
-// 128 MiB it holds the float16 copy and the buffers of the half-precision engine up to about 300 000 x 128; larger
-// inputs (to SLHC_STATIC_MAX_ROWS rows) go through the list kernels, which need one half norm per row only.  Every GPU the
-// library runs on holds its own copy at its own address until the process ends; host code never
-// uses the array's name as an address, only what hipGetSymbolAddress returns for the current device.
-constexpr size_t STATIC_SCRATCH_BYTES = (size_t)128 << 20;
-static __device__ __align__(256) unsigned char scratch[STATIC_SCRATCH_BYTES];
-
+// ---- scratch of slhc_knn_graph_static: the workspace of the every-tile k-NN path as a fixed device array
+// (static_scratch.hip).  Every GPU that entry point runs on holds its own copy at its own address until the process ends.
+using slhc::STATIC_SCRATCH_BYTES;
 constexpr int MAX_DEVICES = 64;
 std::mutex g_scratch_mutex;
 void* g_scratch_ptr[MAX_DEVICES] = {};
 
-// Device address of `scratch` on the current device (looked up once per device).
+// Device address of that array on the current device (looked up once per device).
 int static_scratch(void** out)
 {
     int dev = -1;
@@ -1502,7 +1498,7 @@ int static_scratch(void** out)
     std::lock_guard<std::mutex> lock(g_scratch_mutex);
     if (!g_scratch_ptr[dev]) {
         void* ptr = nullptr;
-        HIP_TRY(hipGetSymbolAddress(&ptr, HIP_SYMBOL(scratch)));
+        HIP_TRY(slhc::static_scratch_address(&ptr));
         if (!ptr) { set_err("hipGetSymbolAddress returned a null address"); return SLHC_HIP_ERROR; }
         g_scratch_ptr[dev] = ptr;
     }

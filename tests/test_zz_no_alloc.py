@@ -54,3 +54,62 @@ def test_static_scratch_rejects_oversize():
     assert lib.slhc_knn_graph_static(ptr, N, 4, 2, ptr, ptr, None) == 2
     assert b"SLHC_STATIC_MAX_ROWS" in lib.slhc_last_error()
     assert lib.slhc_knn_graph_static(None, 100, 4, 2, ptr, ptr, None) == 1
+
+
+def test_static_scratch_is_held_from_its_first_call_on():
+    """A program that never calls the entry point does not hold its array (in a process of its own, which calls everything else
+    first)."""
+    first, second = map(int, child("""
+import torch, paper_2306_16354_amd as slhc
+X = torch.randn(30_000, 16, device="cuda")
+idx, dist = slhc.knn_graph(X, 4)
+slhc.knn_graph(X, 4, prune=True, fp32_filter=True)
+out = slhc.slhc(X, 4)
+slhc.flat_clusters(out["children"], 5)
+slhc.fused_1nn(X[:100], X)
+slhc.cross_1nn(X, torch.arange(30_000, dtype=torch.int32, device="cuda") % 3)
+torch.cuda.synchronize()
+free = [torch.cuda.mem_get_info()[0]]
+for _ in range(2):
+    slhc.knn_graph_static(X, 4, (idx, dist))
+    torch.cuda.synchronize()
+    free.append(torch.cuda.mem_get_info()[0])
+print(free[0] - free[1], free[1] - free[2])
+""").split())
+    print(f"first call takes {first} bytes, second {second}", flush=True)
+    assert 120 << 20 <= first <= 200 << 20 and second == 0
+
+
+def test_first_static_call_in_a_capture():
+    """The call that brings the array in may be a captured one; replays follow the input, with other work in between."""
+    assert child("""
+import torch, paper_2306_16354_amd as slhc
+X = torch.randn(3000, 16, device="cuda")
+slhc.knn_graph(X, 4)
+idx = torch.empty((3000, 4), dtype=torch.int32, device="cuda")
+dist = torch.empty((3000, 4), device="cuda")
+torch.cuda.synchronize()
+graph = torch.cuda.CUDAGraph()
+with torch.cuda.graph(graph):
+    slhc.knn_graph_static(X, 4, (idx, dist))
+for replay in range(4):
+    X.copy_(torch.randn_like(X))
+    idx.fill_(-7)
+    graph.replay()
+    torch.cuda.synchronize()
+    want = slhc.knn_graph(X, 4)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], idx) and torch.equal(want[1], dist), replay
+print("same")
+""").split() == ["same"]
+
+
+def child(code):
+    """What a Python process of its own prints."""
+    import os
+    import subprocess
+    import sys
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    run = subprocess.run([sys.executable, "-c", code], cwd=root, capture_output=True, text=True, timeout=100)
+    assert run.returncode == 0, run.stderr
+    return run.stdout
