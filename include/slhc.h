@@ -212,8 +212,10 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k,
  */
 int slhc_probe_fp32_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
 /* The same for v_mfma_f32_32x32x16_bf16, the multiply of the sweeps that form their tile products from split
- * bfloat16 halves (SLHC_FP32_FILTER describes them); same arguments. */
+ * bfloat16 halves (SLHC_FP32_FILTER describes them), and for v_mfma_f32_32x32x16_f16, that of the half-precision
+ * engine; same arguments. */
 int slhc_probe_bf16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
+int slhc_probe_f16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
 /*
  * Checking aid for the filter slack of those sweeps (paper Sec. 3.1.1: the tile contraction; how far its value may
  * be off decides which pairs must be re-evaluated): one v_mfma_f32_32x32x16_bf16 per trial on the caller's values,
@@ -223,6 +225,9 @@ int slhc_probe_bf16_mfma(double* tflops, void* workspace, size_t workspace_bytes
  * on `stream`; 0 <= trials <= 2^24.
  */
 int slhc_probe_bf16_mfma_values(const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream);
+/* The same for v_mfma_f32_32x32x16_f16, on values that float16 holds: the half-precision engine discards a pair only if
+ * its product value misses a bound by more than this instruction can be off. */
+int slhc_probe_f16_mfma_values(const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream);
 
 /*
  * Measurement aid like slhc_probe_fp32_mfma, for the panel loop of the sweeps (paper Sec. 3.1.1, the

@@ -66,10 +66,11 @@ def load_library():
     lib.slhc_knn_graph_static.restype = ctypes.c_int
     lib.slhc_probe_fp32_mfma.argtypes = [ctypes.POINTER(ctypes.c_double), vp, sz, vp]
     lib.slhc_probe_fp32_mfma.restype = ctypes.c_int
-    lib.slhc_probe_bf16_mfma.argtypes = [ctypes.POINTER(ctypes.c_double), vp, sz, vp]
-    lib.slhc_probe_bf16_mfma.restype = ctypes.c_int
-    lib.slhc_probe_bf16_mfma_values.argtypes = [vp, vp, vp, vp, ctypes.c_int32, vp]
-    lib.slhc_probe_bf16_mfma_values.restype = ctypes.c_int
+    for kind in ("bf16", "f16"):
+        rate, values = getattr(lib, f"slhc_probe_{kind}_mfma"), getattr(lib, f"slhc_probe_{kind}_mfma_values")
+        rate.argtypes = [ctypes.POINTER(ctypes.c_double), vp, sz, vp]
+        values.argtypes = [vp, vp, vp, vp, ctypes.c_int32, vp]
+        rate.restype = values.restype = ctypes.c_int
     lib.slhc_probe_panel_loop.argtypes = [i32, ctypes.POINTER(ctypes.c_double), vp, sz, vp]
     lib.slhc_probe_panel_loop.restype = ctypes.c_int
     lib.slhc_cross_1nn_workspace_bytes.argtypes = [i64, i32, i64, ctypes.POINTER(sz)]
@@ -167,29 +168,44 @@ def knn_graph_static(X, k, out):
     return idx, dist
 
 
-def probe_bf16_mfma_values(A, B, C):
-    """slhc_probe_bf16_mfma_values: D[t] = C[t] + sum_k A[t, k] B[t, k] by one bf16 MFMA per row (A, B [T, 16], C [T])."""
+def _probe_values(entry, A, B, C):
     A, B, C = A.contiguous(), B.contiguous(), C.contiguous()
     assert A.dtype == B.dtype == C.dtype == torch.float32 and A.shape == B.shape and A.shape[1] == 16 and C.numel() == A.shape[0]
     D = torch.empty_like(C)
-    _check(load_library().slhc_probe_bf16_mfma_values(A.data_ptr(), B.data_ptr(), C.data_ptr(), D.data_ptr(), A.shape[0], _stream()))
+    _check(entry(A.data_ptr(), B.data_ptr(), C.data_ptr(), D.data_ptr(), A.shape[0], _stream()))
     return D
+
+
+def _probe_rate(entry, device):
+    ws = _workspace(256, device)
+    out = ctypes.c_double(0.0)
+    _check(entry(ctypes.byref(out), ws.data_ptr(), ws.numel(), _stream()))
+    return out.value
+
+
+def probe_bf16_mfma_values(A, B, C):
+    """slhc_probe_bf16_mfma_values: D[t] = C[t] + sum_k A[t, k] B[t, k] by one bf16 MFMA per row (A, B [T, 16], C [T])."""
+    return _probe_values(load_library().slhc_probe_bf16_mfma_values, A, B, C)
+
+
+def probe_f16_mfma_values(A, B, C):
+    """slhc_probe_f16_mfma_values: the same by one float16 MFMA per row."""
+    return _probe_values(load_library().slhc_probe_f16_mfma_values, A, B, C)
 
 
 def probe_bf16_mfma(device="cuda"):
     """slhc_probe_bf16_mfma: TFLOP/s a register-only v_mfma_f32_32x32x16_bf16 loop sustains on the current device."""
-    ws = _workspace(256, device)
-    out = ctypes.c_double(0.0)
-    _check(load_library().slhc_probe_bf16_mfma(ctypes.byref(out), ws.data_ptr(), ws.numel(), _stream()))
-    return out.value
+    return _probe_rate(load_library().slhc_probe_bf16_mfma, device)
+
+
+def probe_f16_mfma(device="cuda"):
+    """slhc_probe_f16_mfma: the same for v_mfma_f32_32x32x16_f16."""
+    return _probe_rate(load_library().slhc_probe_f16_mfma, device)
 
 
 def probe_fp32_mfma(device="cuda"):
     """slhc_probe_fp32_mfma: TFLOP/s a register-only fp32 MFMA loop sustains on the current device."""
-    ws = _workspace(256, device)
-    out = ctypes.c_double(0.0)
-    _check(load_library().slhc_probe_fp32_mfma(ctypes.byref(out), ws.data_ptr(), ws.numel(), _stream()))
-    return out.value
+    return _probe_rate(load_library().slhc_probe_fp32_mfma, device)
 
 
 def probe_panel_loop(steps, workspace):

@@ -46,7 +46,8 @@ constexpr float LOWEST = -3.4028234663852886e38f;      // a bound every product 
 
 // What the arithmetic on the rounded rows can be off by.  An instruction aligns its 16 products and the accumulator
 // to the largest magnitude, one bit below its last place, cuts the rest off, adds and rounds: at most 18 units of
-// 2^-24 of that magnitude.  The accumulator starts at minus half the candidate's squared norm, so no partial sum
+// 2^-24 of that magnitude (6.0 measured at most, over 3 million sums against 64 bits: test_f16_mfma_error_stays_within_the_budget).
+// The accumulator starts at minus half the candidate's squared norm, so no partial sum
 // exceeds n_c / 2 + |x_q||x_c| <= n_c + n_q / 2, and after `steps` instructions the value is off by at most
 // e (n_c + n_q / 2), e = 9 steps 2^-23.  nu: the relative error of a squared norm (8 ceil(steps / 8) + 8 rounded
 // additions).  The stored half norms are lowered by what belongs to the candidate: a value `acc` is never below the

@@ -1623,35 +1623,51 @@ int slhc_probe_fp32_mfma(double* tflops, void* workspace, size_t workspace_bytes
     });
 }
 
+static int probe_16bit_mfma(bool half, double* tflops, void* workspace, size_t workspace_bytes, void* stream)
+{
+    if (!tflops || !workspace) { set_err("NULL pointer argument"); return SLHC_INVALID_ARG; }
+    if (workspace_bytes < 256) { set_err("workspace %zu < 256 bytes", workspace_bytes); return SLHC_WORKSPACE_TOO_SMALL; }
+    hipStream_t s = static_cast<hipStream_t>(stream);
+    EventPair ev;
+    HIP_TRY(ev.create());
+    double flop = 0.0;
+    HIP_TRY(slhc::launch_mfma_16bit_probe(half, 2000, static_cast<float*>(workspace), s, &flop));      // warm-up: clocks settle
+    HIP_TRY(hipEventRecord(ev.a, s));
+    HIP_TRY(slhc::launch_mfma_16bit_probe(half, 80000, static_cast<float*>(workspace), s, &flop));     // ~40 ms
+    HIP_TRY(hipEventRecord(ev.b, s));
+    HIP_TRY(hipStreamSynchronize(s));
+    const float ms = ev.ms();
+    if (!(ms > 0.f)) { set_err("probe timing failed"); return SLHC_HIP_ERROR; }
+    *tflops = flop / (ms * 1e-3) / 1e12;
+    return SLHC_OK;
+}
+
 int slhc_probe_bf16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream)
 {
-    return guarded([&]() -> int {
-        if (!tflops || !workspace) { set_err("NULL pointer argument"); return SLHC_INVALID_ARG; }
-        if (workspace_bytes < 256) { set_err("workspace %zu < 256 bytes", workspace_bytes); return SLHC_WORKSPACE_TOO_SMALL; }
-        hipStream_t s = static_cast<hipStream_t>(stream);
-        EventPair ev;
-        HIP_TRY(ev.create());
-        double flop = 0.0;
-        HIP_TRY(slhc::launch_mfma_bf16_probe(2000, static_cast<float*>(workspace), s, &flop));     // warm-up: clocks settle
-        HIP_TRY(hipEventRecord(ev.a, s));
-        HIP_TRY(slhc::launch_mfma_bf16_probe(80000, static_cast<float*>(workspace), s, &flop));    // ~40 ms
-        HIP_TRY(hipEventRecord(ev.b, s));
-        HIP_TRY(hipStreamSynchronize(s));
-        const float ms = ev.ms();
-        if (!(ms > 0.f)) { set_err("probe timing failed"); return SLHC_HIP_ERROR; }
-        *tflops = flop / (ms * 1e-3) / 1e12;
-        return SLHC_OK;
-    });
+    return guarded([&]() -> int { return probe_16bit_mfma(false, tflops, workspace, workspace_bytes, stream); });
+}
+
+int slhc_probe_f16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream)
+{
+    return guarded([&]() -> int { return probe_16bit_mfma(true, tflops, workspace, workspace_bytes, stream); });
+}
+
+static int probe_16bit_values(bool half, const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream)
+{
+    if (!A || !B || !C || !D) { set_err("NULL pointer argument"); return SLHC_INVALID_ARG; }
+    if (trials < 0 || trials > (1 << 24)) { set_err("trials must be 0..2^24 (trials=%d)", trials); return SLHC_INVALID_ARG; }
+    HIP_TRY(slhc::launch_mfma_16bit_values(half, A, B, C, D, trials, static_cast<hipStream_t>(stream)));
+    return SLHC_OK;
 }
 
 int slhc_probe_bf16_mfma_values(const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream)
 {
-    return guarded([&]() -> int {
-        if (!A || !B || !C || !D) { set_err("NULL pointer argument"); return SLHC_INVALID_ARG; }
-        if (trials < 0 || trials > (1 << 24)) { set_err("trials must be 0..2^24 (trials=%d)", trials); return SLHC_INVALID_ARG; }
-        HIP_TRY(slhc::launch_mfma_bf16_values(A, B, C, D, trials, static_cast<hipStream_t>(stream)));
-        return SLHC_OK;
-    });
+    return guarded([&]() -> int { return probe_16bit_values(false, A, B, C, D, trials, stream); });
+}
+
+int slhc_probe_f16_mfma_values(const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream)
+{
+    return guarded([&]() -> int { return probe_16bit_values(true, A, B, C, D, trials, stream); });
 }
 
 int slhc_probe_panel_loop(int32_t steps, double* tflops, void* workspace, size_t workspace_bytes, void* stream)

@@ -41,6 +41,7 @@ namespace slhc {
 typedef float v16f __attribute__((ext_vector_type(16)));
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef __bf16 v8bf __attribute__((ext_vector_type(8)));
+typedef _Float16 v8hf __attribute__((ext_vector_type(8)));
 
 #ifndef SLHC_SPLIT_MIN_CHUNKS
 #define SLHC_SPLIT_MIN_CHUNKS 1   // every-tile sweeps: split bfloat16 products from this many chunks of 32 columns on
@@ -1937,22 +1938,27 @@ __global__ void __launch_bounds__(WG_THREADS, 2) mfma_probe_kernel(int iters, fl
     if (total == 123456.789f) sink[0] = total;          // keeps the chain alive; practically never taken
 }
 
-// The same for the multiply of the split-product sweeps, v_mfma_f32_32x32x16_bf16.
-__global__ void __launch_bounds__(WG_THREADS, 2) mfma_bf16_probe_kernel(int iters, float seed, float* __restrict__ sink)
+// The multiplies of the split-product sweeps, v_mfma_f32_32x32x16_bf16, and of the half-precision engine, v_mfma_f32_32x32x16_f16.
+__device__ inline v16f probe_mfma(v8bf a, v8bf b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, c, 0, 0, 0); }
+__device__ inline v16f probe_mfma(v8hf a, v8hf b, v16f c) { return __builtin_amdgcn_mfma_f32_32x32x16_f16(a, b, c, 0, 0, 0); }
+
+// The same for those.
+template <typename V, typename E>
+__global__ void __launch_bounds__(WG_THREADS, 2) mfma_16bit_probe_kernel(int iters, float seed, float* __restrict__ sink)
 {
     v16f acc[4];
 #pragma unroll
     for (int b = 0; b < 4; ++b)
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
-    v8bf a, c;
+    V a, c;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) { a[e] = (__bf16)(seed + (float)((threadIdx.x + e) & 7) * 0.125f); c[e] = (__bf16)(seed * 0.5f); }
+    for (int e = 0; e < 8; ++e) { a[e] = (E)(seed + (float)((threadIdx.x + e) & 7) * 0.125f); c[e] = (E)(seed * 0.5f); }
     for (int it = 0; it < iters; ++it) {
 #pragma unroll
         for (int u = 0; u < 4; ++u) {
 #pragma unroll
-            for (int b = 0; b < 4; ++b) acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, c, acc[b], 0, 0, 0);
+            for (int b = 0; b < 4; ++b) acc[b] = probe_mfma(a, c, acc[b]);
         }
     }
     float total = 0.f;
@@ -1963,41 +1969,44 @@ __global__ void __launch_bounds__(WG_THREADS, 2) mfma_bf16_probe_kernel(int iter
     if (total == 123456.789f) sink[0] = total;
 }
 
-// One v_mfma_f32_32x32x16_bf16 per trial on caller-given values: D[t] = C[t] + sum_k A[t][k] B[t][k], k < 16, the
-// values rounded to bfloat16 first (pass bfloat16-representable ones).  For checking the rounding behaviour that
-// split_slack_coefficient relies on against an exact sum computed elsewhere.
-__global__ void __launch_bounds__(64) mfma_bf16_values_kernel(const float* __restrict__ A, const float* __restrict__ B,
-                                                              const float* __restrict__ C, float* __restrict__ D, int trials)
+// One such multiply per trial on caller-given values: D[t] = C[t] + sum_k A[t][k] B[t][k], k < 16, the values rounded to 16 bits
+// first (pass ones that those hold).  For checking the rounding behaviour that split_slack_coefficient and near_e
+// (near_kernels.hip) rely on against an exact sum computed elsewhere.
+template <typename V, typename E>
+__global__ void __launch_bounds__(64) mfma_16bit_values_kernel(const float* __restrict__ A, const float* __restrict__ B,
+                                                               const float* __restrict__ C, float* __restrict__ D, int trials)
 {
     const int t = blockIdx.x, lane = threadIdx.x;
     if (t >= trials) return;
-    v8bf a, b;
+    V a, b;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-        a[e] = (__bf16)A[(size_t)t * 16 + 8 * (lane >> 5) + e];
-        b[e] = (__bf16)B[(size_t)t * 16 + 8 * (lane >> 5) + e];
+        a[e] = (E)A[(size_t)t * 16 + 8 * (lane >> 5) + e];
+        b[e] = (E)B[(size_t)t * 16 + 8 * (lane >> 5) + e];
     }
     v16f acc;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = C[t];
-    acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, acc, 0, 0, 0);
+    acc = probe_mfma(a, b, acc);
     if (lane == 0) D[t] = acc[0];
 }
 
-hipError_t launch_mfma_bf16_values(const float* A, const float* B, const float* C, float* D, int trials, hipStream_t stream)
+hipError_t launch_mfma_16bit_values(bool half, const float* A, const float* B, const float* C, float* D, int trials, hipStream_t stream)
 {
     if (trials < 1) return hipSuccess;
-    hipLaunchKernelGGL(mfma_bf16_values_kernel, dim3(trials), dim3(64), 0, stream, A, B, C, D, trials);
+    if (half) hipLaunchKernelGGL((mfma_16bit_values_kernel<v8hf, _Float16>), dim3(trials), dim3(64), 0, stream, A, B, C, D, trials);
+    else hipLaunchKernelGGL((mfma_16bit_values_kernel<v8bf, __bf16>), dim3(trials), dim3(64), 0, stream, A, B, C, D, trials);
     return hipGetLastError();
 }
 
-hipError_t launch_mfma_bf16_probe(int iters, float* sink, hipStream_t stream, double* flop)
+hipError_t launch_mfma_16bit_probe(bool half, int iters, float* sink, hipStream_t stream, double* flop)
 {
     int cus = 0;
     hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;
     const int grid = 2 * cus;
-    hipLaunchKernelGGL(mfma_bf16_probe_kernel, dim3(grid), dim3(WG_THREADS), 0, stream, iters, 1.0f, sink);
+    if (half) hipLaunchKernelGGL((mfma_16bit_probe_kernel<v8hf, _Float16>), dim3(grid), dim3(WG_THREADS), 0, stream, iters, 1.0f, sink);
+    else hipLaunchKernelGGL((mfma_16bit_probe_kernel<v8bf, __bf16>), dim3(grid), dim3(WG_THREADS), 0, stream, iters, 1.0f, sink);
     *flop = (double)grid * (WG_THREADS / 64) * (double)iters * 16.0 * (2.0 * 32 * 32 * 16);
     return hipGetLastError();
 }
@@ -2142,7 +2151,7 @@ hipError_t launch_loop_probe(int steps, int iters, const float* stream_rows, int
                              double* flop)
 {
     if (steps <= 0) return launch_mfma_probe(iters * 4, sink, stream, flop);     // 16 multiplies per iteration there
-    if (steps == 8) return launch_mfma_bf16_probe(iters * 2, sink, stream, flop);
+    if (steps == 8) return launch_mfma_16bit_probe(false, iters * 2, sink, stream, flop);
     int cus = 0;
     hipError_t e = device_cus(&cus);
     if (e != hipSuccess) return e;

@@ -178,3 +178,45 @@ def test_small_nearest_row_searches(lib, m, n, d):
         assert np.allclose(gd.cpu().numpy()[take], D.min(1)[take], rtol=1e-5, atol=1e-30)
         exact = gi.cpu().numpy()[take] == fine[D.argmin(1)[take]]
         assert exact.mean() >= 0.99
+
+
+def test_f16_mfma_error_stays_within_the_budget(lib):
+    """near_e budgets 9 x 2^-23 (18 x 2^-24) of the largest partial sum per v_mfma_f32_32x32x16_f16, and everything the engine
+    discards rests on that: one unit of 2^-24 for each of 16 products and the accumulator that are aligned to the largest term
+    and cut off, one for the rounding of the sum.  Checked against exact float64 sums, relative to the largest of the 17 terms
+    (which no partial sum of the sweeps' values exceeds): the error must stay below half the budget.  Values as the copies hold
+    them (2^-14 and above, or 0; products down to 2^-28 and up to 2^24), of equal and of widely different magnitude, of one sign
+    and of both, the accumulator far above, at and far below the products; and one large product beside fifteen small ones."""
+    g = torch.Generator().manual_seed(78)
+    T = 1 << 18
+    worst = 0.0
+    for spread in (0, 2, 4, 10, 18, 26):
+        for sign in ("plus", "both"):
+            def draw(shape):
+                v = (1.0 + torch.rand(shape, generator=g)) * torch.exp2(12.0 - torch.randint(0, spread + 1, shape, generator=g).float())
+                v = v.to(torch.float16).float()
+                assert v.min() >= 2.0 ** -14
+                if sign == "both":
+                    v = torch.where(torch.rand(shape, generator=g) < 0.5, -v, v)
+                return torch.where(torch.rand(shape, generator=g) < 0.05, torch.zeros(()), v)
+            A, B = draw((T, 16)), draw((T, 16))
+            C = (1.0 + torch.rand((T,), generator=g)) * torch.exp2(torch.randint(-8, 33, (T,), generator=g).float())
+            C = torch.where(torch.arange(T) % 7 == 0, torch.zeros(()), -C if sign == "both" else C)
+            D = lib.probe_f16_mfma_values(A.cuda(), B.cuda(), C.cuda()).cpu().double()
+            prod = A.double() * B.double()                             # 22 bits each: exact
+            exact = C.double() + prod.sum(dim=1)
+            largest = torch.maximum(torch.maximum(C.double().abs(), prod.abs().max(dim=1).values), exact.abs())
+            fine = largest > 0
+            rel = ((D - exact).abs()[fine] / (largest[fine] * 2.0 ** -24)).max().item()
+            print(f"f16 MFMA, exponent spread {spread}, {sign}: worst error {rel:.3f} x 2^-24 of the largest", flush=True)
+            worst = max(worst, rel)
+    for small in (2.0 ** -24, 2.0 ** -25, 2.0 ** -26):
+        A = torch.full((1, 16), 2.0 ** -12)
+        B = torch.full((1, 16), small * 2.0 ** 12)
+        A[0, 0] = B[0, 0] = 1.0
+        assert B.min() >= 2.0 ** -14
+        D = lib.probe_f16_mfma_values(A.cuda(), B.cuda(), torch.zeros(1).cuda()).cpu().double().item()
+        err = abs(D - (1.0 + 15 * small)) / 2.0 ** -24
+        print(f"one product of 1 and fifteen of {small:.3g}: off by {err:.3f} x 2^-24", flush=True)
+        worst = max(worst, err)
+    assert worst <= 9.0
