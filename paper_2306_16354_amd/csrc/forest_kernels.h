@@ -34,7 +34,6 @@ struct ForestState {
 };
 
 hipError_t forest_init(const ForestState& f, hipStream_t s);
-hipError_t forest_round_reset(const ForestState& f, hipStream_t s);
 hipError_t forest_scan_lists(const ForestState& f, hipStream_t s);
 hipError_t forest_classify(const ForestState& f, hipStream_t s);
 // qrows[q] is the vertex query q was made for (f.qlist, or a reordered copy of it).  `thresholds`

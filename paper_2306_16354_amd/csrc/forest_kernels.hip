@@ -64,15 +64,6 @@ __global__ void __launch_bounds__(TB) k_forest_init(ForestState f)
     f.best_e[v] = ~0ull;
 }
 
-__global__ void __launch_bounds__(TB) k_round_reset(ForestState f)
-{
-    const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N) return;
-    f.best_w[v] = INF_BITS;
-    f.best_e[v] = ~0ull;
-    if (v == 0) f.counters[0] = 0;
-}
-
 // G lanes per vertex walk its list from ptr[v] on, G entries at a time, until an entry of another colour
 // turns up: the lists are ascending, so that entry is the vertex's lightest listed outgoing edge.  Most
 // vertices find it in their first step (in the first round entry 0 always is foreign), and ptr only moves
@@ -636,7 +627,6 @@ __global__ void __launch_bounds__(TB) k_csr_scan(const int32_t* __restrict__ off
     } while (0)
 
 hipError_t forest_init(const ForestState& f, hipStream_t s) { LAUNCH1(k_forest_init, f.N, s, f); }
-hipError_t forest_round_reset(const ForestState& f, hipStream_t s) { LAUNCH1(k_round_reset, f.N, s, f); }
 
 hipError_t forest_scan_lists(const ForestState& f, hipStream_t s)
 {

@@ -12,7 +12,6 @@ struct NearScale {
     float scale;
     unsigned int eps_bits;
     unsigned int huge;         // not 0: some row has values beyond float16
-    float spare;
 };
 
 // The rows of a matrix rounded to float16, in tiles of 128 in the order the matrix instruction reads them.
@@ -62,7 +61,6 @@ size_t near_stats_scratch_floats(int d);
 // (kk: k, plus one where a query meets itself)
 size_t near_batch_bytes(long long nq, long long nc, int d, int kk);       // what NearBuffers::batch wants (less also works, down to one panel)
 size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk);
-bool near_supported(int d);
 
 // (clears `clear` [clear_words], optional, on the way)
 hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s);

@@ -356,8 +356,6 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     }
 }
 
-bool near_supported(int d) { return d >= 1; }
-
 hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int n, const int32_t* colour, const NearBuffers& b,
                      const NearCopy& out, float* hn, unsigned int* nonfinite, hipStream_t s, bool clear_todo, const int32_t* n_dev,
                      const int32_t* shift_row)
@@ -1881,7 +1879,7 @@ static int near_list_stride(int T) { return T > FIRST_TILES ? T : FIRST_TILES; }
 __global__ void __launch_bounds__(256) near_first_kernel(NearList p)
 {
     __shared__ NearSegments g;
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int tid = threadIdx.x, lane = tid & 63;
     const int panel = blockIdx.x, base = panel * p.panel_queries;
     const int mine = p.nq - base < p.panel_queries ? p.nq - base : p.panel_queries;
     if (mine <= 0) { if (tid == 0) p.list_len[panel] = 0; return; }
@@ -1909,7 +1907,6 @@ __global__ void __launch_bounds__(256) near_first_kernel(NearList p)
         }
         if (lane == 0 && best != ~0ull) list[atomicAdd(&g.count, 1)] = (unsigned short)(best & 0xffffu);
     }
-    (void)wave;
     __syncthreads();
     if (tid == 0) p.list_len[panel] = g.count;
 }

@@ -10,7 +10,6 @@ namespace slhc {
 hipError_t order_iota(int32_t* a, int n, hipStream_t s);
 // Xp[j] = X[row_j], hp[j] = h[row_j] with row_j = floor(j * N / P): P evenly spaced rows
 hipError_t order_pick_rows(const float* X, const float* h, int N, int d, int P, float* Xp, float* hp, hipStream_t s);
-hipError_t order_gather_rows(const float* X, const int32_t* perm, int N, int d, float* Xs, hipStream_t s);
 // out[i] = a[idx[i]] for i < n; `fallback` where the index is outside [0, limit)
 hipError_t order_gather_f32(const float* a, const int32_t* idx, int n, int limit, float fallback, float* out,
                             hipStream_t s);
@@ -23,7 +22,6 @@ hipError_t order_mark_far(const float* dist, int n, float tau, uint32_t* key, in
 // Xp[j] = X[list[floor(j * m / P)]], hp[j] = h[...]: P evenly spaced rows of a row list of length m
 hipError_t order_pick_listed_rows(const float* X, const float* h, const uint32_t* list, int m, int N, int d, int P,
                                   float* Xp, float* hp, hipStream_t s);
-hipError_t order_invert(const int32_t* perm, int n, int32_t* inv, hipStream_t s);
 hipError_t order_fill_i32(int32_t* a, int n, int32_t value, hipStream_t s);
 // counts[pid[i]] += 1 (counts zeroed by the caller)
 hipError_t order_histogram(const int32_t* pid, int n, int bins, int32_t* counts, hipStream_t s);

@@ -15,18 +15,15 @@ __global__ void __launch_bounds__(TB) k_iota(int32_t* a, int n)
     if (i < n) a[i] = i;
 }
 
-// one thread per output float4 (or float when d is not a multiple of 4)
+// P evenly spaced rows; one thread per output float4 (or float when d is not a multiple of 4)
 template <bool VEC4>
-__global__ void __launch_bounds__(TB) k_gather_rows(const float* __restrict__ X, const int32_t* __restrict__ perm,
-                                                    int N, int d, int P, float* __restrict__ Xs)
+__global__ void __launch_bounds__(TB) k_gather_rows(const float* __restrict__ X, int N, int d, int P, float* __restrict__ Xs)
 {
     const int per_row = VEC4 ? d / 4 : d;
     const long long i = (long long)blockIdx.x * TB + threadIdx.x;
-    const long long total = (long long)(perm ? N : P) * per_row;
-    if (i >= total) return;
+    if (i >= (long long)P * per_row) return;
     const int r = (int)(i / per_row), c = (int)(i % per_row);
-    const int src = perm ? perm[r] : (int)((long long)r * N / P);
-    if ((unsigned int)src >= (unsigned int)N) return;
+    const int src = (int)((long long)r * N / P);
     if (VEC4) reinterpret_cast<float4*>(Xs)[i] = reinterpret_cast<const float4*>(X + (size_t)src * d)[c];
     else Xs[i] = X[(size_t)src * d + c];
 }
@@ -73,14 +70,6 @@ __global__ void __launch_bounds__(TB) k_pick_listed(const float* __restrict__ X,
     if (VEC4) reinterpret_cast<float4*>(Xp)[i] = reinterpret_cast<const float4*>(X + (size_t)src * d)[c];
     else Xp[i] = X[(size_t)src * d + c];
     if (c == 0) hp[r] = h[src];
-}
-
-__global__ void __launch_bounds__(TB) k_invert(const int32_t* __restrict__ perm, int n, int32_t* __restrict__ inv)
-{
-    const int i = blockIdx.x * TB + threadIdx.x;
-    if (i >= n) return;
-    const int j = perm[i];
-    if ((unsigned int)j < (unsigned int)n) inv[j] = i;
 }
 
 __global__ void __launch_bounds__(TB) k_fill_i32(int32_t* a, int n, int32_t v)
@@ -295,21 +284,12 @@ hipError_t order_iota(int32_t* a, int n, hipStream_t s)
 hipError_t order_pick_rows(const float* X, const float* h, int N, int d, int P, float* Xp, float* hp, hipStream_t s)
 {
     if (vec4_ok(X, Xp, d))
-        hipLaunchKernelGGL(k_gather_rows<true>, dim3(blocks_for((long long)P * (d / 4))), dim3(TB), 0, s, X, (const int32_t*)nullptr, N, d, P, Xp);
+        hipLaunchKernelGGL(k_gather_rows<true>, dim3(blocks_for((long long)P * (d / 4))), dim3(TB), 0, s, X, N, d, P, Xp);
     else
-        hipLaunchKernelGGL(k_gather_rows<false>, dim3(blocks_for((long long)P * d)), dim3(TB), 0, s, X, (const int32_t*)nullptr, N, d, P, Xp);
+        hipLaunchKernelGGL(k_gather_rows<false>, dim3(blocks_for((long long)P * d)), dim3(TB), 0, s, X, N, d, P, Xp);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_pick_f32, dim3(blocks_for(P)), dim3(TB), 0, s, h, N, P, hp);
-    return hipGetLastError();
-}
-
-hipError_t order_gather_rows(const float* X, const int32_t* perm, int N, int d, float* Xs, hipStream_t s)
-{
-    if (vec4_ok(X, Xs, d))
-        hipLaunchKernelGGL(k_gather_rows<true>, dim3(blocks_for((long long)N * (d / 4))), dim3(TB), 0, s, X, perm, N, d, N, Xs);
-    else
-        hipLaunchKernelGGL(k_gather_rows<false>, dim3(blocks_for((long long)N * d)), dim3(TB), 0, s, X, perm, N, d, N, Xs);
     return hipGetLastError();
 }
 
@@ -346,12 +326,6 @@ hipError_t order_pick_listed_rows(const float* X, const float* h, const uint32_t
         hipLaunchKernelGGL(k_pick_listed<true>, dim3(blocks_for((long long)P * (d / 4))), dim3(TB), 0, s, X, h, list, m, N, d, P, Xp, hp);
     else
         hipLaunchKernelGGL(k_pick_listed<false>, dim3(blocks_for((long long)P * d)), dim3(TB), 0, s, X, h, list, m, N, d, P, Xp, hp);
-    return hipGetLastError();
-}
-
-hipError_t order_invert(const int32_t* perm, int n, int32_t* inv, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_invert, dim3(blocks_for(n)), dim3(TB), 0, s, perm, n, inv);
     return hipGetLastError();
 }
 

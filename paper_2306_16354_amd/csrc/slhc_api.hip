@@ -1998,7 +1998,7 @@ static int flat_clusters_layout(void* ws, int64_t N, int32_t** above, int32_t** 
     Carver c(ws);
     const size_t nodes = 2 * (size_t)N;
     *above = c.take<int32_t>(nodes);
-    (void)c.take<int32_t>(nodes);          // (unused; the size that callers know)
+    (void)c.take<int32_t>(nodes);          // (not used; it keeps the size that is reported what it was)
     *rank = c.take<int32_t>(nodes);
     *temp_bytes = slhc::flat_clusters_scan_temp_bytes((int)N);
     *temp = c.take<unsigned char>(*temp_bytes);
