@@ -199,11 +199,17 @@ __global__ void __launch_bounds__(256) direct_unpack_kernel(const unsigned long 
     out_dist[i] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
 }
 
-// 1000 x 4000 x 30 (288 million operations): 33 us, the engine 51; 32 x 111 642 x 21 (193 million, single floats to load):
-// 73 and 57.  So up to a hundred million.
+// Where every pair is evaluated instead of the engine's search, measured on both sides of the lines (us a call among others, this
+// against the engine).  What the operations cost is one part, what it takes to bring every candidate once to each panel of eight
+// queries, 64 at a time, the other; it grows with the candidates, and with their width where a step is more than one slab.
+//   up to 100 M operations: 1250 x 4000 x 4 22 and 45, 178 x 4000 x 64 24 and 39, 22 x 32 000 x 64 35 and 45, 64 x 50 000 x 8 37 and 43;
+//     the worst of 40 shapes 24 x 8000 x 250 78 and 72, 20 x 100 000 x 6 57 and 50;
+//   up to 200 M: 1136 x 4000 x 16 25 and 45, 694 x 4000 x 30 27 and 47, 173 x 16 000 x 30 32 and 48, 142 x 32 000 x 16 33 and 38; the worst
+//     of 33 shapes up to 65 536 candidates 43 x 64 000 x 30 55 and 49; beyond those 32 x 111 642 x 21 70 and 57, 16 x 300 000 x 16 88 and 85;
+//   300 M: even on the whole (1704 x 4000 x 16 37 and 47, 3750 x 4000 x 4 47 and 50, 360 x 32 000 x 7 45 and 41, 73 x 8000 x 250 94 and 76).
 bool direct_1nn_wanted(long long m, long long nc, int d)
 {
-    return m <= (1LL << 20) && nc <= (1LL << 24) && m * nc * (2LL * d + 12) <= 100000000LL;
+    return m <= (1LL << 20) && nc <= (1LL << 24) && m * nc * (2LL * d + 12) <= (nc <= 65536 ? 200000000LL : 100000000LL);
 }
 
 hipError_t direct_1nn(const float* Xq, int m, int nq_rows, const int32_t* q_rows, const float* Xc, int nc, int d, const int32_t* colour,

@@ -1151,10 +1151,14 @@ slhc::NearOrder near_order_of(const OrderWs& o)
     n.tile_colour = o.tile_colour;
     return n;
 }
-// Pruned k-NN searches go to the half-precision engine where a tile's region holds this many tiles on average: below it (clusters
-// of a tile or two) a panel of 512 queries and the tiles around it are mostly pairs that nobody needs.  2M x 32 in clusters of
-// 100 rows: list kernels 4.7 ms, 22 ms; 100k x 64 in clusters of 2000 (16 tiles): 2.1 ms, 0.8 ms.
-constexpr unsigned long long NEAR_REGION_TILES = 12;
+// Pruned k-NN searches, and with them the connection rounds, go to the half-precision engine where a tile's region holds as many
+// tiles on average as a region must have for a copy relative to its centre (k_region_local).  Without that copy the rounding is a
+// share of the distance from all rows' centre, and in tight clusters (300k x 32, a thousand radii apart) every pair of a tile may
+// be the one that is wanted: of 700 rows (7 tiles) the search takes 14.4 ms and the list kernels 1.5 ms, of 1000 rows (8 tiles)
+// 1.8 and 1.55 ms, of 100 rows 3.3 and 0.8 ms (2M x 32: 22 and 4.7 ms).  Clusters a few radii apart do not need it, and there the
+// search costs little where it does not gain, and the connection rounds gain on both sides of the line: 200k x 64 in clusters of
+// 800 rows 1.4 and 1.7 ms, rounds 7.0 and 17.3 ms; of 120 rows 1.2 and 0.7 ms, rounds 5.9 and 11.6 ms.
+constexpr unsigned long long NEAR_REGION_TILES = REGION_TILES;
 // Connection rounds go there too unless the clusters are tight against their distances: a row of another cluster is then known
 // up to a few 1e-4 of the spread of all rows, and where that is as much as a cluster's radius every row of a component may be the
 // one that is nearest (2M x 32 in clusters of 100 rows, a thousand radii apart: all rows are left to be searched, 57 ms of

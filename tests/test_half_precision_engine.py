@@ -131,7 +131,7 @@ def test_trees_by_components(lib, kind, N, d):
 # fewer rows than neighbours asked for, on both sides of the shortest region, one cluster, and clusters far apart for their size
 @pytest.mark.parametrize("N,d,k,rows,spread", [
     (700, 4, 3, 700, 8), (5000, 128, 16, 20, 8), (20_000, 40, 31, 900, 8), (33_000, 100, 64, 1100, 40), (34_000, 12, 5, 8000, 8),
-    (60_000, 64, 12, 2500, 5000), (110_000, 8, 20, 110_000, 0), (133_000, 20, 15, 9000, 8), (140_000, 128, 8, 30_000, 30),
+    (60_000, 64, 12, 2500, 5000), (64_000, 48, 9, 1000, 3000), (64_000, 48, 9, 850, 8), (110_000, 8, 20, 110_000, 0), (133_000, 20, 15, 9000, 8), (140_000, 128, 8, 30_000, 30),
 ])
 def test_lists_and_trees_in_the_row_order(lib, N, d, k, rows, spread):
     print(f"half-precision row order N={N} d={d} k={k} rows={rows} spread={spread}", flush=True)

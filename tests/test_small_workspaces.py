@@ -131,8 +131,11 @@ def cross(lib, Xd, colour, rows, m):
     return call
 
 
-# all rows, listed rows, and a search small enough to evaluate every pair
-@pytest.mark.parametrize("N,d,m,listed", [(30_000, 64, 30_000, False), (60_000, 33, 5000, True), (20_000, 200, 900, True), (1500, 8, 1400, True)])
+# all rows, listed rows, and searches small enough to evaluate every pair, on both sides of the lines where these end (100 and 200
+# million operations, 65 536 candidates)
+@pytest.mark.parametrize("N,d,m,listed", [(30_000, 64, 30_000, False), (60_000, 33, 5000, True), (20_000, 200, 900, True), (1500, 8, 1400, True),
+                                          (60_000, 14, 82, True), (60_000, 14, 86, True), (65_536, 12, 45, True), (65_537, 12, 45, True),
+                                          (9000, 250, 42, True)])
 def test_nearest_rows_of_another_colour(lib, N, d, m, listed):
     print(f"1-NN by colours in small workspaces N={N} d={d} m={m}", flush=True)
     rng = np.random.default_rng(N)
