@@ -14,6 +14,7 @@
 #include <mutex>
 #include <memory>
 #include <new>
+#include <optional>
 #include <thread>
 #include <vector>
 
@@ -817,42 +818,35 @@ private:
 };
 
 struct SlhcWs {
-    void* knn_ws;
     int32_t* nbr_idx; float* nbr_dist;
     int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *qlist, *q_idx, *counters, *e_lo, *e_hi;
     float *ext_dist, *ext_low, *cand_w, *q_dist, *q_low, *e_w;
     uint32_t *best_w, *vals_a, *vals_b;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
+    std::optional<KnnWs> knn;        // half norms and row order are reused by the connection sweeps
     size_t bytes;
-    size_t knn_most = NO_LIMIT;      // bytes there are for knn_ws (see KnnWs)
     SlhcWs(void* ws, int64_t N, int32_t d, int32_t k, bool with_order, size_t most = NO_LIMIT)
-    {
-        if (most != NO_LIMIT) {
-            lay_out(nullptr, N, k, 0, true);             // what everything else takes
-            knn_most = most > bytes ? most - bytes : 0;
-        }
-        const KnnWs knn(nullptr, N, d, with_order, k, true, knn_most);
-        lay_out(ws, N, k, knn.bytes, knn.near.ok);
-    }
-private:
-    void lay_out(void* ws, int64_t N, int32_t k, size_t knn_bytes, bool with_near)
     {
         Carver c(ws);
         const size_t n = (size_t)N;
-        knn_ws = c.take<unsigned char>(knn_bytes);
         nbr_idx = c.take<int32_t>(n * k);
         nbr_dist = c.take<float>(n * k);
         colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); qlist = c.take<int32_t>(n);
         q_idx = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
-        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); q_low = with_near ? c.take<float>(n) : nullptr; cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
+        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); cand_w = c.take<float>(n); q_dist = c.take<float>(n); e_w = c.take<float>(n);
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
         sort_temp_bytes = std::max(slhc::edge_sort_temp_bytes((int)(N - 1)), slhc::pair_sort_temp_bytes((int)N));   // the second: grouping the dendrogram's edges
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
+        // the k-NN part takes what is left, without the engine's lower ends of the queries' answers
+        const size_t low = up(n * sizeof(float));
+        knn.emplace(c.base ? c.base + c.off : nullptr, N, d, with_order, k, true, most == NO_LIMIT ? most : most > c.off + low ? most - c.off - low : 0);
+        c.off += knn->bytes;
+        q_low = knn->near.ok ? c.take<float>(n) : nullptr;
         bytes = c.off;
     }
 };
@@ -2114,7 +2108,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         HIP_TRY(ev_conn.create());
     }
     bool pruned = false;
-    KnnWs kws(ws.knn_ws, N, d, with_order, k, true, ws.knn_most);      // half norms and row order are reused by the connection sweeps
+    KnnWs& kws = *ws.knn;
     rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, timed ? &ev_norm : nullptr, timed ? &ev_order : nullptr,
                  timed ? &ev_knn : nullptr);
     if (rc != SLHC_OK) return rc;

@@ -16,8 +16,7 @@ static void pivots(int64_t N, int32_t d)
         if (P < 2) continue;
         const int32_t kp = P - 1 < NESTED_K ? P - 1 : NESTED_K;
         const SlhcWs w(nullptr, P, d, kp, false, o.nested_bytes);
-        const KnnWs k(nullptr, P, d, false, kp, w.knn_most);
-        if (w.bytes > o.nested_bytes || !k.near.ok) std::printf("pivots N=%lld d=%d P=%d: %zu of %zu bytes, engine %d\n", (long long)N, d, P, w.bytes, o.nested_bytes, k.near.ok);
+        if (w.bytes > o.nested_bytes || !w.knn->near.ok) std::printf("pivots N=%lld d=%d P=%d: %zu of %zu bytes, engine %d\n", (long long)N, d, P, w.bytes, o.nested_bytes, w.knn->near.ok);
         ++checked;
     }
 }
@@ -58,7 +57,7 @@ int main()
         });
         limits("slhc", x.N, x.d, x.k, [&](size_t most, bool* e) {
             const SlhcWs w(nullptr, x.N, dw, x.k, true, most == NO_LIMIT ? most : most > head ? most - head : 0);
-            *e = KnnWs(nullptr, x.N, dw, true, x.k, true, w.knn_most).near.ok;
+            *e = w.knn->near.ok;
             return head + w.bytes;
         });
     }
