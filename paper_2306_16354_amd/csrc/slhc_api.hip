@@ -713,7 +713,7 @@ struct OrderWs {
         tile_region = c.take<int32_t>((size_t)Tmax); tile_first = c.take<int32_t>((size_t)Tmax);
         tile_last = c.take<int32_t>((size_t)Tmax);
         tile_boundary = c.take<int32_t>((size_t)Tmax); tile_local = c.take<int32_t>((size_t)Tmax);
-        if (Xs_local) region_other_min = c.take<float>((size_t)Tmax);
+        if (split_products_ok(d) && d <= 128) region_other_min = c.take<float>((size_t)Tmax);
         tile_c = c.take<float>((size_t)Tmax * d); tile_r = c.take<float>((size_t)Tmax);
         gap_ws = c.take<float>((size_t)grid * Tmax);
         // lower bounds between all pairs of tiles (order_tile_gaps), as long as the table stays moderate

@@ -21,12 +21,19 @@ static void pivots(int64_t N, int32_t d)
     }
 }
 
-// A layout keeps within the bytes it is given, from the least there can be to what the size functions report; `engine`: whether
-// the half-precision engine is part of it, and at least one panel's worth of batch.
+// A layout keeps within the bytes it is given, from the least there can be to what the size functions report, and takes as many
+// where it is laid out as where it is only measured; `engine`: whether the half-precision engine is part of it, and at least one
+// panel's worth of batch.
 template <typename L>
-static void limits(const char* what, long long a, long long b, long long c, L&& layout)
+static void limits(const char* what, long long a, long long b, long long c, L&& layout_at)
 {
     bool engine = false;
+    auto layout = [&](size_t most, bool* e) {
+        bool e2 = false;
+        const size_t bytes = layout_at(nullptr, most, e), there = layout_at(reinterpret_cast<void*>((size_t)1 << 40), most, &e2);
+        if (bytes != there || *e != e2) std::printf("%s %lld %lld %lld: %zu bytes measured, %zu laid out\n", what, a, b, c, bytes, there);
+        return bytes;
+    };
     const size_t least = layout(0, &engine), full = layout(NO_LIMIT, &engine);
     const bool has_engine = engine;
     auto check = [&](size_t most, bool want) {
@@ -50,29 +57,29 @@ int main()
                           Shape{1000000, 128, 32}, Shape{2000000, 32, 8}, Shape{100000000, 8, 8}}) {
         const int32_t dw = working_columns(x.N, x.d);
         const size_t head = padded_copy_bytes(x.N, x.d);
-        limits("knn", x.N, x.d, x.k, [&](size_t most, bool* e) {
-            const KnnWs w(nullptr, x.N, dw, true, x.k, false, most == NO_LIMIT ? most : most > head ? most - head : 0);
+        limits("knn", x.N, x.d, x.k, [&](void* at, size_t most, bool* e) {
+            const KnnWs w(at, x.N, dw, true, x.k, false, most == NO_LIMIT ? most : most > head ? most - head : 0);
             *e = w.near.ok;
             return head + w.bytes;
         });
-        limits("slhc", x.N, x.d, x.k, [&](size_t most, bool* e) {
-            const SlhcWs w(nullptr, x.N, dw, x.k, true, most == NO_LIMIT ? most : most > head ? most - head : 0);
+        limits("slhc", x.N, x.d, x.k, [&](void* at, size_t most, bool* e) {
+            const SlhcWs w(at, x.N, dw, x.k, true, most == NO_LIMIT ? most : most > head ? most - head : 0);
             *e = w.knn->near.ok;
             return head + w.bytes;
         });
     }
     struct Search { int64_t m, n; int32_t d; };
     for (const Search x : {Search{1, 1, 1}, Search{10, 2000000, 64}, Search{1000, 100000, 128}, Search{1000, 4000, 30}, Search{20000, 500000, 256}, Search{200000, 3000, 20}})
-        limits("fused", x.m, x.n, x.d, [&](size_t most, bool* e) {
+        limits("fused", x.m, x.n, x.d, [&](void* at, size_t most, bool* e) {
             float *hq, *hy; unsigned long long* keys;
             NearWs near;
-            const size_t bytes = fused_1nn_layout(nullptr, x.m, x.n, x.d, &hq, &hy, &keys, &near, most);
+            const size_t bytes = fused_1nn_layout(at, x.m, x.n, x.d, &hq, &hy, &keys, &near, most);
             *e = near.ok;
             return bytes;
         });
     for (const Search x : {Search{0, 100, 4}, Search{1, 2, 1}, Search{10000, 100000, 64}, Search{10, 1000000, 64}, Search{50, 2000, 8}, Search{300000, 300000, 128}})
-        limits("cross", x.n, x.d, x.m, [&](size_t most, bool* e) {
-            const CrossWs w(nullptr, x.n, x.d, x.m, most);
+        limits("cross", x.n, x.d, x.m, [&](void* at, size_t most, bool* e) {
+            const CrossWs w(at, x.n, x.d, x.m, most);
             *e = w.near.ok;
             return w.bytes;
         });
