@@ -9,6 +9,8 @@ import oracle
 import slhc_inputs as gen
 
 torch = pytest.importorskip("torch")
+from workspaces import by_list_kernels, cross_1nn_in  # noqa: E402
+
 pytestmark = pytest.mark.gpu
 
 RTOL_DIST = 1e-5
@@ -74,6 +76,15 @@ def gpu_knn(lib, X, k):
     idx, dist = lib.knn_graph(Xd, k)
     torch.cuda.synchronize()
     return idx.cpu().numpy(), dist.cpu().numpy()
+
+
+def knn_by_list_kernels(lib, Xd, k, **flags):
+    """The k-NN graph without the half-precision engine, which the smallest workspace leaves no room for."""
+    return by_list_kernels(lib, lambda ws: lib.knn_graph(Xd, k, workspace=ws, **flags))
+
+
+def slhc_by_list_kernels(lib, Xd, k, **flags):
+    return by_list_kernels(lib, lambda ws: lib.slhc(Xd, k, workspace=ws, **flags))
 
 
 # ----------------------------------------------------------------------------- k-NN graph
@@ -611,11 +622,11 @@ def test_pruned_random_shapes(lib):
 @pytest.mark.parametrize("N,d,k", [(700, 1, 3), (3000, 7, 5), (5000, 50, 16), (4000, 100, 32), (2100, 127, 64),
                                    (3000, 130, 8), (2500, 301, 16)])
 def test_padded_columns_change_nothing(lib, N, d, k):
-    """slhc_knn_graph and slhc_slhc work on a copy of X with zero columns appended (whole chunks of 32 up to 128
-    features, a multiple of 4 beyond), which opens the register-resident-query kernel, split products and tile
-    pruning to every d.  A zero column adds nothing to a distance, so the lists must equal, bit for bit, those of
-    the entry point that never pads (slhc_knn_graph_static), the pruned path those of the every-tile path, and
-    both the oracle's."""
+    """The list kernels of slhc_knn_graph and slhc_slhc work on a copy of X with zero columns appended (whole chunks of 32 up to
+    128 features, a multiple of 4 beyond), which opens the register-resident-query kernel, split products and tile
+    pruning to every d.  A zero column adds nothing to a distance, so their lists (float32 products, and those of the smallest
+    workspace) must equal, bit for bit, those of the half-precision engine, which reads the rows as they are, with and without
+    a workspace (slhc_knn_graph_static), the pruned path those of the every-tile path, and both the oracle's."""
     rng = np.random.default_rng(N + 7 * d)
     centres = rng.uniform(-15, 15, size=(9, d))
     X = (centres[rng.integers(0, 9, size=N)] + rng.standard_normal((N, d))).astype(np.float32)
@@ -626,6 +637,8 @@ def test_padded_columns_change_nothing(lib, N, d, k):
     i0, d0 = lib.knn_graph(Xd, k)
     torch.cuda.synchronize()
     assert torch.equal(plain[0], i0) and torch.equal(plain[1], d0)
+    for padded in (lib.knn_graph(Xd, k, fp32_filter=True), knn_by_list_kernels(lib, Xd, k)):
+        assert torch.equal(padded[0], i0) and torch.equal(padded[1], d0)
     check_knn(X, k, i0.cpu().numpy(), d0.cpu().numpy(), min_exact=0.999)
     b = _pruned_equals_every_tile(lib, X, k)
     assert b["stats"]["pruned"] == (1 if d <= 128 else 0)
@@ -637,10 +650,11 @@ def test_padded_columns_change_nothing(lib, N, d, k):
 @pytest.mark.parametrize("d", [32, 64, 96, 128, 132, 260, 784])
 def test_split_bf16_filter_loses_nothing(lib, kind, d):
     """From 32 to 128 features (multiples of 32, register-resident queries) and beyond 128 features (multiples of
-    4, streaming kernel, split copy padded to whole chunks) the every-tile sweeps form their tile products from bfloat16 halves
-    (hi*hi + hi*lo + lo*hi) and widen the filter's slack by what that drops.  The filter only decides
-    which pairs are evaluated exactly, so lists and trees must equal those of the float32 products bit for
-    bit, and the oracle's on sampled rows, also where the slack is put to the test: a common offset far
+    4, streaming kernel, split copy padded to whole chunks) the every-tile sweeps of the list kernels (panel order; the
+    smallest workspace) form their tile products from bfloat16 halves (hi*hi + hi*lo + lo*hi) and widen the filter's slack by
+    what that drops; the half-precision engine, which runs otherwise, multiplies float16 copies under a bound of its own.  The
+    filter only decides which pairs are evaluated exactly, so lists and trees of all three must equal those of the float32
+    products bit for bit, and the oracle's on sampled rows, also where the slack is put to the test: a common offset far
     larger than the distances, values that use all 24 bits, rows of very different scale, duplicates, a
     lattice with many exact ties, tiny values."""
     rng = np.random.default_rng(len(kind) * 1000 + d)
@@ -664,15 +678,19 @@ def test_split_bf16_filter_loses_nothing(lib, kind, d):
     print(f"split bf16 filter: {kind} N={N} d={d} k={k}", flush=True)
     a = lib.knn_graph(Xd, k, fp32_filter=True)
     b = lib.knn_graph(Xd, k)
-    torch.cuda.synchronize()
-    assert torch.equal(a[0], b[0]) and torch.equal(a[1], b[1])
+    for c in (b, lib.knn_graph(Xd, k, panel_order=True), knn_by_list_kernels(lib, Xd, k)):
+        torch.cuda.synchronize()
+        assert torch.equal(a[0], c[0]) and torch.equal(a[1], c[1])
     rows = rng.choice(N, size=150, replace=False)
     check_knn(X, k, b[0].cpu().numpy()[rows], b[1].cpu().numpy()[rows], rows=rows,
               min_exact=0.0 if kind in ("duplicates", "lattice") else 0.9)
-    ta = lib.slhc(Xd, min(k, 16), prune=False, fp32_filter=True)
-    tb = lib.slhc(Xd, min(k, 16), prune=False)
-    for name_ in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
-        assert torch.equal(ta[name_], tb[name_]), name_
+    kt = min(k, 16)
+    ta = lib.slhc(Xd, kt, prune=False, fp32_filter=True)
+    assert ta["stats"]["split_products"] == 0
+    for tb in (lib.slhc(Xd, kt, prune=False), lib.slhc(Xd, kt, prune=False, panel_order=True), slhc_by_list_kernels(lib, Xd, kt, prune=False)):
+        assert tb["stats"]["split_products"] == 1
+        for name_ in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+            assert torch.equal(ta[name_], tb[name_]), name_
 
 
 @pytest.mark.parametrize("N,d,k,offset", [(30_000, 20, 8, 1.0e4), (26_000, 3, 4, 3.0e5), (25_000, 64, 16, 1.0e3),
@@ -683,7 +701,8 @@ def test_common_offset_stays_out_of_the_filter(lib, N, d, k, offset):
     towards it; below 64 features, where the pruned sweeps otherwise multiply the rows as they are in float32, they
     switch to the split copy when the means carry most of the norms.  Same lists and trees as with float32
     products and as the oracle on sampled rows, and about as few pairs passed on to the exact evaluation as for
-    the same data without the offset (without the shift: every pair of every multiplied tile)."""
+    the same data without the offset (without the shift: every pair of every multiplied tile).  The copies of the half-precision
+    engine are taken relative to a central value of every column likewise; both are looked at."""
     rng = np.random.default_rng(N + d)
     centres = rng.uniform(-10, 10, size=(30, d))
     base = centres[rng.integers(0, 30, size=N)] + rng.standard_normal((N, d))
@@ -703,20 +722,25 @@ def test_common_offset_stays_out_of_the_filter(lib, N, d, k, offset):
         pruned = lib.slhc(Xd, k, prune=True)
         for n_ in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
             assert torch.equal(every[n_], pruned[n_]), n_
-        per_row[name_] = (every["stats"]["knn_filter_survivors"] / N, pruned["stats"]["knn_filter_survivors"] / N)
-        print(f"  {name_}: pairs passed per row, every tile {per_row[name_][0]:.1f}, pruned {per_row[name_][1]:.1f}", flush=True)
-    assert per_row["offset"][0] <= 3.0 * per_row["plain"][0] + 50
-    assert per_row["offset"][1] <= 3.0 * per_row["plain"][1] + 50
+        lists = [slhc_by_list_kernels(lib, Xd, k, prune=prune) for prune in (False, True)]
+        for out in lists:
+            assert torch.equal(every["children"], out["children"]) and torch.equal(every["mst_w"], out["mst_w"])
+        per_row[name_] = [out["stats"]["knn_filter_survivors"] / N for out in (every, pruned, *lists)]
+        print(f"  {name_}: pairs passed per row, every tile and pruned, engine and list kernels: {per_row[name_]}", flush=True)
+    for offset_, plain_ in zip(per_row["offset"], per_row["plain"]):
+        assert offset_ <= 3.0 * plain_ + 50
 
 
 @pytest.mark.parametrize("kind", ["blobs", "one_cluster", "tiny_clusters", "uniform", "chain"])
 @pytest.mark.parametrize("d", [64, 100, 128])
 def test_pruned_knn_by_regions_is_identical(lib, kind, d):
-    """From 64 to 128 features the pruned k-NN sweep runs as two launches: the tiles of a panel's own region (a run
+    """From 64 to 128 features the pruned k-NN sweep of the list kernels (without the table of tile pairs; the smallest
+    workspace) runs as two launches: the tiles of a panel's own region (a run
     of tiles of the row order whose centres stay close) from a split copy relative to a centre of that region,
     then all other tiles, starting from the lists of the first launch, from the copy relative to the column
-    means.  Only the filter's slack differs, so the lists must equal, bit for bit, those of the single launch
-    (SLHC_ONE_SHIFT), of the every-tile sweep and of the entry point that never reorders or shifts, on data with
+    means.  The half-precision engine, which runs otherwise, has a copy relative to the regions as well.  Only the filter's
+    slack differs, so the lists must equal, bit for bit, those of the single launch
+    (SLHC_ONE_SHIFT), of the every-tile sweep and of the entry point that never reorders, on data with
     one region, with regions of a tile or two, with none to speak of, and with clusters strung along a line so
     that a region's first tile lies far from its last."""
     rng = np.random.default_rng(len(kind) * 100 + d)
@@ -742,22 +766,24 @@ def test_pruned_knn_by_regions_is_identical(lib, kind, d):
     lib.knn_graph_static(Xd, k, plain)
     two = lib.knn_graph(Xd, k, prune=True)
     one = lib.knn_graph(Xd, k, prune=True, one_shift=True)
+    lists = [lib.knn_graph(Xd, k, prune=True, tile_table=False), knn_by_list_kernels(lib, Xd, k, prune=True)]
     torch.cuda.synchronize()
-    assert torch.equal(plain[0], two[0]) and torch.equal(plain[1], two[1])
-    assert torch.equal(plain[0], one[0]) and torch.equal(plain[1], one[1])
-    a = lib.slhc(Xd, min(k, 16), prune=True)
+    for got in (two, one, *lists):
+        assert torch.equal(plain[0], got[0]) and torch.equal(plain[1], got[1])
+    a = slhc_by_list_kernels(lib, Xd, min(k, 16), prune=True)
     b = lib.slhc(Xd, min(k, 16), prune=True, one_shift=True)
     c = lib.slhc(Xd, min(k, 16), prune=False)
+    e = lib.slhc(Xd, min(k, 16), prune=True)
     for name_ in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
-        assert torch.equal(a[name_], b[name_]) and torch.equal(a[name_], c[name_]), name_
+        assert torch.equal(a[name_], b[name_]) and torch.equal(a[name_], c[name_]) and torch.equal(a[name_], e[name_]), name_
     print(f"  pairs passed per row: {a['stats']['knn_filter_survivors'] / N:.1f} by regions, "
           f"{b['stats']['knn_filter_survivors'] / N:.1f} in one launch", flush=True)
 
 
 def test_far_outlier_does_not_drag_the_shift(lib):
-    """The shift of the split copy is a median of means, not a mean: one row at 1e12 among unit-scale rows would move a
-    mean to 3e8 per column and put that into every row's norm, after which every pair passes the filter.  Same
-    lists as the entry point that multiplies the rows as they are, and about as few pairs passed as without the row."""
+    """The shift of the split copy, as that of the float16 copy, is a median of means, not a mean: one row at 1e12 among
+    unit-scale rows would move a mean to 3e8 per column and put that into every row's norm, after which every pair passes the
+    filter.  Same lists with float32 products of the rows as they are, and about as few pairs passed as without the row."""
     rng = np.random.default_rng(77)
     N, d, k = 3000, 40, 6
     base = rng.standard_normal((N, d)).astype(np.float32)
@@ -766,14 +792,14 @@ def test_far_outlier_does_not_drag_the_shift(lib):
     for X in (base, with_outlier):
         Xd = torch.from_numpy(np.ascontiguousarray(X)).cuda()
         n = X.shape[0]
-        plain = (torch.empty((n, k), dtype=torch.int32, device="cuda"), torch.empty((n, k), dtype=torch.float32, device="cuda"))
-        lib.knn_graph_static(Xd, k, plain)
-        got = lib.knn_graph(Xd, k)
-        torch.cuda.synchronize()
-        assert torch.equal(plain[0], got[0]) and torch.equal(plain[1], got[1])
-        per_row.append(lib.slhc(Xd, k, prune=False)["stats"]["knn_filter_survivors"] / n)
-    print(f"  pairs passed per row: {per_row[0]:.1f} without the outlier, {per_row[1]:.1f} with it", flush=True)
-    assert per_row[1] <= 2.0 * per_row[0] + 20
+        plain = lib.knn_graph(Xd, k, fp32_filter=True)
+        for got in (lib.knn_graph(Xd, k), lib.knn_graph(Xd, k, panel_order=True)):
+            torch.cuda.synchronize()
+            assert torch.equal(plain[0], got[0]) and torch.equal(plain[1], got[1])
+        per_row.append([lib.slhc(Xd, k, prune=False, panel_order=p)["stats"]["knn_filter_survivors"] / n for p in (False, True)])
+    print(f"  pairs passed per row, engine and list kernels: {per_row[0]} without the outlier, {per_row[1]} with it", flush=True)
+    for without, with_it in zip(*per_row):
+        assert with_it <= 2.0 * without + 20
 
 
 def test_bf16_mfma_error_stays_within_what_the_slack_allows(lib):
@@ -831,9 +857,9 @@ def test_default_entry_point_prunes_from_its_limit(lib):
 def test_knn_candidate_ranges_equal_unsplit(lib, N, d, k):
     """With fewer query panels than half the workgroup slots the every-tile k-NN sweep (k > 1) splits the
     candidate tiles into up to 16 ranges, one work item per (panel, range), and a merge kernel picks the k
-    smallest of a row's lists (the paper's multi-block row epilogue, App. A, without its mutex).  The lists
-    must equal, bit for bit, those of the entry point that never splits (it has no room for partial lists),
-    and sampled rows must equal the oracle's."""
+    smallest of a row's lists (the paper's multi-block row epilogue, App. A, without its mutex): the list kernels with float32
+    products, with split ones in panel order, and in the smallest workspace.  The lists must equal, bit for bit, those of the
+    half-precision engine, which keeps none per range, with and without a workspace, and sampled rows must equal the oracle's."""
     rng = np.random.default_rng(N + d + k)
     X = rng.standard_normal((N, d)).astype(np.float32)
     X[rng.integers(0, N, size=N // 20)] = X[rng.integers(0, N, size=N // 20)]        # duplicates: ties by index
@@ -843,6 +869,9 @@ def test_knn_candidate_ranges_equal_unsplit(lib, N, d, k):
     lib.knn_graph_static(Xd, k, ref)
     torch.cuda.synchronize()
     assert torch.equal(idx, ref[0]) and torch.equal(dist, ref[1])
+    for got in (lib.knn_graph(Xd, k, fp32_filter=True), lib.knn_graph(Xd, k, panel_order=True), knn_by_list_kernels(lib, Xd, k)):
+        torch.cuda.synchronize()
+        assert torch.equal(got[0], ref[0]) and torch.equal(got[1], ref[1])
     rows = rng.choice(N, size=min(N, 200), replace=False)
     check_knn(X, k, idx.cpu().numpy()[rows], dist.cpu().numpy()[rows], rows=rows, min_exact=0.9)
 
@@ -1034,17 +1063,20 @@ def test_c5_full_size_pruned_equals_every_tile(lib):
 # ----------------------------------------------------------------------------- sweeps range by range
 @pytest.mark.parametrize("N,d,k", [(270_000, 64, 8), (263_000, 32, 5), (300_001, 128, 33), (262_144, 96, 1)])
 def test_range_order_equals_panel_order(lib, N, d, k):
-    """Every-tile k-NN sweeps of at least four panels per workgroup slot hand out their work range by range and
-    carry a panel's lists from range to range through the output arrays; the lists must equal those of the
-    sweep that takes one panel at a time (split and float32 products), and sampled rows must equal the oracle's."""
+    """Every-tile k-NN sweeps of the list kernels of at least four panels per workgroup slot hand out their work range by range
+    and carry a panel's lists from range to range through the output arrays; the lists (split products in the smallest
+    workspace, float32 products) must equal those of the sweep that takes one panel at a time (split and float32 products) and
+    of the half-precision engine, and sampled rows must equal the oracle's."""
     rng = np.random.default_rng(N + d)
     centres = rng.uniform(-20, 20, size=(200, d))
     X = (centres[rng.integers(0, 200, size=N)] + rng.standard_normal((N, d))).astype(np.float32)
     X[rng.integers(0, N, size=500)] = X[rng.integers(0, N, size=500)]          # some exact copies
     Xd = torch.from_numpy(X).cuda()
     print("range order", N, d, k, flush=True)
-    a = lib.knn_graph(Xd, k)
+    a = knn_by_list_kernels(lib, Xd, k)
+    e = lib.knn_graph(Xd, k)
     torch.cuda.synchronize()
+    assert torch.equal(a[0], e[0]) and torch.equal(a[1], e[1])
     for fp32 in (False, True):
         b = lib.knn_graph(Xd, k, panel_order=True, fp32_filter=fp32)
         torch.cuda.synchronize()
@@ -1085,7 +1117,7 @@ def test_headline_full_size_properties(lib):
     torch.cuda.synchronize()
     assert torch.equal(idx, idx_p) and torch.equal(dist, dist_p)
     del idx_p, dist_p
-    print("headline: knn panel by panel, split and float32 products", flush=True)   # (the default goes range by range)
+    print("headline: knn panel by panel by the list kernels, split and float32 products", flush=True)
     for fp32 in (False, True):
         idx_p, dist_p = lib.knn_graph(Xd, k, panel_order=True, fp32_filter=fp32)
         torch.cuda.synchronize()
@@ -1122,8 +1154,7 @@ def test_c2_full_size_tree_against_prim(lib):
 
 
 def test_c4_full_size_properties(lib):
-    """c4 at its full size (250k x 784, k=16), the launch configuration of the streaming sweep kernel
-    with several panels per workgroup: sampled rows of the k-NN graph against the oracle, sampled
+    """c4 at its full size (250k x 784, k=16), the half-precision engine's widest case: sampled rows of the k-NN graph against the oracle, sampled
     reported pairs recomputed, and the tree checked through the properties that hold at any size."""
     X, _, k = gen.make("c4")
     N = X.shape[0]
@@ -1145,13 +1176,14 @@ def test_c4_full_size_properties(lib):
     out = lib.slhc(Xd, k)
     print("stats", out["stats"], flush=True)
     T = (N + 127) // 128
-    assert out["stats"]["knn_tile_steps"] == T * T          # the streaming kernel counts its tile steps too
+    assert out["stats"]["knn_tile_steps"] == T * T          # every pair of tiles is multiplied
     check_tree_properties(X, k, gi, out, rng, n_weights=100_000)
 
 
 # ----------------------------------------------------------------------------- streaming kernel, many panels
-# More than 512 query panels (65 536 rows): every workgroup of the streaming sweep kernel (d > 128 or
-# d % 4 != 0) then loops over several work items.  All list widths of that kernel are instantiated.
+# More than 512 query panels (65 536 rows): every workgroup of the streaming sweep kernel (d > 128; the list kernels' way, which
+# the smallest workspace asks for) then loops over several work items.  All list widths of that kernel are instantiated.  The
+# half-precision engine gives the same lists.
 @pytest.mark.parametrize("N,d,k", [(70_000, 132, 16), (70_000, 132, 33), (66_500, 30, 20), (66_000, 30, 5),
                                    (66_000, 130, 1)])
 def test_streaming_kernel_many_panels(lib, N, d, k):
@@ -1160,6 +1192,8 @@ def test_streaming_kernel_many_panels(lib, N, d, k):
     centres = rng.uniform(-10, 10, size=(40, d))
     X = (centres[rng.integers(0, 40, size=N)] + rng.standard_normal((N, d))).astype(np.float32)
     gi, gd = gpu_knn(lib, X, k)
+    li, ld = knn_by_list_kernels(lib, torch.from_numpy(X).cuda(), k)
+    assert np.array_equal(gi, li.cpu().numpy()) and np.array_equal(gd, ld.cpu().numpy())
     assert gi.min() >= 0 and gi.max() < N
     step = 10_000
     for s0 in range(0, N, step):                      # every reported pair, in float64
@@ -1172,8 +1206,8 @@ def test_streaming_kernel_many_panels(lib, N, d, k):
 
 
 def test_streaming_1nn_many_query_panels(lib):
-    """The k = 1 variants of the streaming kernel with more than 512 query panels: the cross-colour 1-NN
-    over all rows and the two-matrix 1-NN, sampled rows against the oracle."""
+    """The k = 1 variants of the streaming kernel with more than 512 query panels (in the smallest workspace), and the
+    half-precision engine: the cross-colour 1-NN over all rows and the two-matrix 1-NN, sampled rows against the oracle."""
     N, d = 68_000, 132
     rng = np.random.default_rng(5)
     centres = rng.uniform(-10, 10, size=(30, d))
@@ -1181,8 +1215,11 @@ def test_streaming_1nn_many_query_panels(lib):
     X = (centres[lab] + rng.standard_normal((N, d))).astype(np.float32)
     colour = (lab % 7).astype(np.int32)
     print("streaming cross 1-NN, all rows", flush=True)
-    gi, gd = lib.cross_1nn(torch.from_numpy(X).cuda(), torch.from_numpy(colour).cuda())
+    Xd, cd = torch.from_numpy(X).cuda(), torch.from_numpy(colour).cuda()
+    gi, gd = lib.cross_1nn(Xd, cd)
+    li, ld = by_list_kernels(lib, cross_1nn_in(lib, Xd, cd, None, N))
     torch.cuda.synchronize()
+    assert torch.equal(gi, li) and torch.equal(gd, ld)
     gi, gd = gi.cpu().numpy(), gd.cpu().numpy()
     assert gi.min() >= 0 and gi.max() < N and (colour[gi] != colour).all()
     assert close(gd, pair_dist64(X, np.arange(N), gi), RTOL_DIST).all()
@@ -1193,8 +1230,11 @@ def test_streaming_1nn_many_query_panels(lib):
     assert (gi[rows] == oi).mean() >= 0.99
     print("streaming two-matrix 1-NN, 68 000 queries", flush=True)
     Y = (centres[rng.integers(0, 30, size=3000)] + rng.standard_normal((3000, d))).astype(np.float32)
-    fi, fd = lib.fused_1nn(torch.from_numpy(X).cuda(), torch.from_numpy(Y).cuda())
+    Yd = torch.from_numpy(Y).cuda()
+    fi, fd = lib.fused_1nn(Xd, Yd)
+    li, ld = by_list_kernels(lib, lambda ws: lib.fused_1nn(Xd, Yd, workspace=ws))
     torch.cuda.synchronize()
+    assert torch.equal(fi, li) and torch.equal(fd, ld)
     fi, fd = fi.cpu().numpy(), fd.cpu().numpy()
     assert fi.min() >= 0 and fi.max() < 3000
     XY = np.concatenate([X, Y])

@@ -1,7 +1,6 @@
 """Calls whose workspace is smaller than the size functions report: the half-precision engine in smaller batches, and, where it
 does not fit at all, the list kernels.  Same outputs, bit for bit, and the list kernels' against the oracle."""
 import ctypes
-import re
 
 import numpy as np
 import pytest
@@ -9,6 +8,8 @@ import pytest
 import oracle
 
 torch = pytest.importorskip("torch")
+from workspaces import cross_1nn_in, least_bytes, scratch  # noqa: E402
+
 pytestmark = pytest.mark.gpu
 
 TREE = ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes")
@@ -20,20 +21,6 @@ def lib():
     slhc.load_library()
     assert torch.cuda.is_available()
     return slhc
-
-
-def scratch(nbytes):
-    """That many bytes with a guard behind them, which a call must leave alone."""
-    whole = torch.full((nbytes + 4096,), 0x5a, dtype=torch.uint8, device="cuda")
-    return whole[:nbytes], whole[nbytes:]
-
-
-def least_bytes(lib, call):
-    """What the message of a refusal says."""
-    with pytest.raises(lib.SlhcError) as e:
-        call(scratch(256)[0])
-    assert e.value.status == 3
-    return int(re.search(r"workspace \d+ < (\d+) bytes", str(e.value)).group(1))
 
 
 def same_for_all_sizes(lib, call, full, between=(0.1, 0.5)):
@@ -116,21 +103,6 @@ def test_nearest_rows_of_another_matrix(lib, m, n, d):
     assert (idx.cpu().numpy()[take] == oi - m).mean() >= 0.9
 
 
-def cross(lib, Xd, colour, rows, m):
-    N, d = Xd.shape
-
-    def call(ws):
-        idx = torch.empty(m, dtype=torch.int32, device="cuda")
-        dist = torch.empty(m, dtype=torch.float32, device="cuda")
-        rc = lib.load_library().slhc_cross_1nn(Xd.data_ptr(), N, d, colour.data_ptr(), rows.data_ptr() if rows is not None else None, m,
-                                               idx.data_ptr(), dist.data_ptr(), ws.data_ptr(), ws.numel(),
-                                               ctypes.c_void_p(torch.cuda.current_stream().cuda_stream))
-        if rc:
-            raise lib.SlhcError(rc, "", lib.load_library().slhc_last_error().decode())
-        return idx, dist
-    return call
-
-
 # all rows, listed rows, and searches small enough to evaluate every pair, on both sides of the lines where these end (100 and 200
 # million operations, 65 536 candidates)
 @pytest.mark.parametrize("N,d,m,listed", [(30_000, 64, 30_000, False), (60_000, 33, 5000, True), (20_000, 200, 900, True), (1500, 8, 1400, True),
@@ -147,7 +119,7 @@ def test_nearest_rows_of_another_colour(lib, N, d, m, listed):
     Xd, cd = torch.from_numpy(X).cuda(), torch.from_numpy(colour).cuda()
     out = ctypes.c_size_t(0)
     assert lib.load_library().slhc_cross_1nn_workspace_bytes(N, d, m, ctypes.byref(out)) == 0
-    idx, dist = same_for_all_sizes(lib, cross(lib, Xd, cd, torch.from_numpy(rows).cuda() if listed else None, m), out.value)
+    idx, dist = same_for_all_sizes(lib, cross_1nn_in(lib, Xd, cd, torch.from_numpy(rows).cuda() if listed else None, m), out.value)
     idx, dist = idx.cpu().numpy(), dist.cpu().numpy()
     if listed:
         assert idx[3] == idx[7] == -1 and np.isinf(dist[[3, 7]]).all()
@@ -170,4 +142,4 @@ def test_several_batches_of_nearest_row_queries(lib):
     both = torch.cat([Yd, Qd[:200_000]]).contiguous()
     colour = torch.from_numpy(rng.integers(0, 7, n + 200_000).astype(np.int32)).cuda()
     assert lib.load_library().slhc_cross_1nn_workspace_bytes(n + 200_000, d, n + 200_000, ctypes.byref(out)) == 0
-    same_for_all_sizes(lib, cross(lib, both, colour, None, n + 200_000), out.value, ())
+    same_for_all_sizes(lib, cross_1nn_in(lib, both, colour, None, n + 200_000), out.value, ())
