@@ -8,8 +8,8 @@ already resident in HBM.  Prints ONE JSON line:
   value      fused k-NN distance pairs per second = N^2 / (norm kernel + k-NN sweep kernel time),
              kernel times taken with HIP events on the launch stream inside every timed step
   ms_per_step   wall time of the whole step (the end-to-end single-linkage seconds x 1000)
-  roofline   the fused k-NN sweep against the fp32 MFMA peak (2*d FLOP per ordered pair); also against
-             the rate a register-only fp32 MFMA loop sustains in the same run (empirical_peak)
+  roofline   the k-NN search against the MFMA peak of the multiply it runs (2*d FLOP per ordered pair); also against
+             the rate a register-only loop of that multiply sustains in the same run (empirical_peak)
   roofline_connect / roofline_forest   the connection sweeps (MFMA) and the Boruvka rounds (HBM)
   cpu_baseline  the CPU oracle's brute-force k-NN on a bounded sample of query rows, and its dense Prim +
              dendrogram on the small workload and on a scaled-down copy of this one, next to the GPU
@@ -34,7 +34,7 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3      # MI355X published dense fp32 matrix peak
-PEAK_BF16_MFMA_TFLOPS = 2500.0     # MI355X published dense bf16 matrix peak
+PEAK_16BIT_MFMA_TFLOPS = 2500.0    # MI355X published dense bf16 and f16 matrix peak
 PEAK_HBM_GBS = 8000.0
 
 
@@ -97,8 +97,8 @@ def main():
         for rep in range(2):                                                    # second pass reported
             out_rows = [{"steps": st, "what": names[st], "tflops": slhc.probe_panel_loop(st, ws_probe)} for st in range(12)]
         for r in out_rows:
-            r["frac_of_peak"] = r["tflops"] / (PEAK_BF16_MFMA_TFLOPS if r["steps"] >= 8 else PEAK_FP32_MFMA_TFLOPS)
-        print(json.dumps({"loop_study": out_rows, "peak": PEAK_FP32_MFMA_TFLOPS, "peak_bf16": PEAK_BF16_MFMA_TFLOPS}))
+            r["frac_of_peak"] = r["tflops"] / (PEAK_16BIT_MFMA_TFLOPS if r["steps"] >= 8 else PEAK_FP32_MFMA_TFLOPS)
+        print(json.dumps({"loop_study": out_rows, "peak": PEAK_FP32_MFMA_TFLOPS, "peak_bf16": PEAK_16BIT_MFMA_TFLOPS}))
         return
 
     t0 = time.time()
@@ -142,14 +142,16 @@ def main():
         return float(np.mean([s[name] for s in stats]))
 
     empirical_tflops = slhc.probe_fp32_mfma(dev)       # register-only MFMA loop, same process, right after the steps
-    empirical_bf16_tflops = slhc.probe_bf16_mfma(dev)  # the same for v_mfma_f32_32x32x16_bf16
 
-    # Which products the timed sweeps formed: float32 on the fp32 MFMA, or (64 to 128 features, the library's
-    # default) split bfloat16 halves hi*hi + hi*lo + lo*hi on the bf16 MFMA.  Either way every pair that can
-    # enter a list is re-evaluated in float32, so the outputs are the same bits.
-    split = (not args.knn_only and bool(stats[-1].get("split_products", 0))) or \
-            (args.knn_only and ((d % 32 == 0 and 64 <= d <= 128) or (d > 128 and d % 4 == 0)))
-    peak_tflops = PEAK_BF16_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
+    # Which products the timed searches formed: of float16 copies by the half-precision engine (the library's default), of
+    # split bfloat16 halves hi*hi + hi*lo + lo*hi or of float32 values by the list kernels.  Every pair that can enter a list is
+    # evaluated in float32 in each case, so the outputs are the same bits.
+    half = args.knn_only or bool(stats[-1]["half_products"])
+    split = half or bool(stats[-1]["split_products"])
+    products = 3.0 if split and not half else 1.0      # per multiply-add
+    multiply = "v_mfma_f32_32x32x16_f16" if half else "v_mfma_f32_32x32x16_bf16" if split else "v_mfma_f32_32x32x2_f32"
+    empirical_16bit_tflops = slhc.probe_f16_mfma(dev) if half else slhc.probe_bf16_mfma(dev)     # the same for that multiply
+    peak_tflops = PEAK_16BIT_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
     # the float32-product variant of the same sweep, once, outside the timed region (the kernel earlier
     # reports quote)
     fp32_ms = None
@@ -185,8 +187,8 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (tile products from split bf16 halves on the bf16 MFMA, accumulated in f32; every listed pair "
-                 "re-evaluated in f32)" if split else "f32",
+        "dtype": "f32 (tile products of " + ("float16 copies" if half else "split bf16 halves") + ", accumulated in f32, decide which "
+                 "pairs are evaluated; every listed pair evaluated in f32)" if split else "f32",
         "data": "synthetic",
         "config": {
             "workload": f"{args.workload}: N={N} d={d} k={k} squared-L2 "
@@ -198,8 +200,8 @@ def main():
         "slhc_seconds": None if args.knn_only else ms_per_step / 1e3,
         "pct_fp32_mfma_peak": None if split else 100.0 * achieved_tflops / PEAK_FP32_MFMA_TFLOPS,
         "roofline": {
-            "kernel": "sweep_kernel (fused distance tile + filter + top-k)" +
-                      (", products from split bf16 halves" if split else ""),
+            "kernel": "near_sweep_kernel / near_wide_kernel (maxima of a sample, emission), near_bounds_kernel, near_select_kernel" if half
+                      else "sweep_kernel (fused distance tile + filter + top-k)" + (", products from split bf16 halves" if split else ""),
             "bound": "mfma",
             "achieved": achieved_tflops,
             "peak": peak_tflops,
@@ -208,18 +210,17 @@ def main():
             "traffic": None,
             "launch_ms": knn_kernel_ms,
             "algorithmic_flop_per_launch": flops,
-            "executed_mfma_flop_per_launch": 3.0 * flops if split else flops,
-            "frac_executed": (3.0 if split else 1.0) * achieved_tflops / peak_tflops,
-            "note": ("achieved counts the algorithmic 2 d N^2 against the bf16 MFMA peak; the kernel executes three "
-                     "bf16 products per multiply-add (frac_executed) and is bound by LDS operand reads, the "
-                     "candidate stream and the exact re-evaluation of the pairs that pass, not by the MFMA pipe")
-                    if split else "",
-            "empirical_peak": empirical_bf16_tflops if split else empirical_tflops,
-            "frac_of_empirical_peak": achieved_tflops / (empirical_bf16_tflops if split else empirical_tflops),
-            "frac_executed_of_empirical_peak": (3.0 * achieved_tflops / empirical_bf16_tflops) if split
-                                               else achieved_tflops / empirical_tflops,
-            "empirical_peak_note": "TFLOP/s of a register-only loop of the sweep's own multiply ("
-                                   + ("v_mfma_f32_32x32x16_bf16" if split else "v_mfma_f32_32x32x2_f32") +
+            "executed_mfma_flop_per_launch": products * flops,
+            "frac_executed": products * achieved_tflops / peak_tflops,
+            "note": ("achieved counts the algorithmic 2 d N^2; the search executes one float16 product per multiply-add, and those "
+                     "of a sample of the candidates (every fifth tile at most) once more for its bounds, which frac_executed "
+                     "leaves out; launch_ms holds the bounds and the exact evaluation of what is emitted too") if half else
+                    ("achieved counts the algorithmic 2 d N^2 against the bf16 MFMA peak; the kernel executes three "
+                     "bf16 products per multiply-add (frac_executed)") if split else "",
+            "empirical_peak": empirical_16bit_tflops if split else empirical_tflops,
+            "frac_of_empirical_peak": achieved_tflops / (empirical_16bit_tflops if split else empirical_tflops),
+            "frac_executed_of_empirical_peak": products * achieved_tflops / (empirical_16bit_tflops if split else empirical_tflops),
+            "empirical_peak_note": "TFLOP/s of a register-only loop of the search's own multiply (" + multiply +
                                    ", 4 accumulator blocks per wavefront, 8 wavefronts per CU) measured in this run: "
                                    "what the chip sustains at the clocks it holds under MFMA load",
             "empirical_peak_fp32_mfma": empirical_tflops,
@@ -236,7 +237,7 @@ def main():
         # the metric's "% FP32-MFMA peak" belongs to the sweep that multiplies on the fp32 MFMA
         line["pct_fp32_mfma_peak"] = 100.0 * ft / PEAK_FP32_MFMA_TFLOPS
         line["pct_fp32_mfma_peak_note"] = ("of the k-NN sweep with float32 tile products (roofline_fp32_products); the timed "
-                                           "default forms its products from split bf16 halves and is priced in `roofline`")
+                                           "default forms its products in 16 bits and is priced in `roofline`")
     # HBM traffic is not measurable from inside the run; it comes from the committed rocprofv3 counter runs
     # of this same workload (profiles/traffic.json: one entry per kernel, keyed by workload and kernel name,
     # FETCH_SIZE + WRITE_SIZE scaled by what the same counters read for a plain copy of known size)
@@ -256,7 +257,7 @@ def main():
             obj["traffic_unit"] = ent["per"]
             obj["traffic_kernel"] = ent["kernel"]
 
-    attach_traffic(line["roofline"], "knn_sweep_split" if split else "knn_sweep")
+    attach_traffic(line["roofline"], "knn_half" if half else "knn_sweep_split" if split else "knn_sweep")
     if "roofline_fp32_products" in line:
         attach_traffic(line["roofline_fp32_products"], "knn_sweep")
     if not args.knn_only:
@@ -270,11 +271,12 @@ def main():
         cq = float(s0["connect_query_rows"])
         if cq > 0 and mean("ms_connect_kernels") > 0:
             ct = 2.0 * d * cq * N / (mean("ms_connect_kernels") * 1e-3) / 1e12
-            line["roofline_connect"] = {"kernel": "sweep_kernel (cross-component 1-NN)", "bound": "mfma",
+            line["roofline_connect"] = {"kernel": "near_link: one pass per round, a search for the queries that are left" if half
+                                                  else "sweep_kernel (cross-component 1-NN)", "bound": "mfma",
                                         "achieved": ct, "peak": peak_tflops, "unit": "TFLOP/s",
                                         "frac": ct / peak_tflops, "traffic": None,
-                                        "frac_executed": (3.0 if split else 1.0) * ct / peak_tflops}
-            attach_traffic(line["roofline_connect"], "connect_sweeps_split" if split else "connect_sweeps")
+                                        "frac_executed": products * ct / peak_tflops}
+            attach_traffic(line["roofline_connect"], "connect_half" if half else "connect_sweeps_split" if split else "connect_sweeps")
 
     if not args.knn_only:
         # graph / Boruvka stage against the HBM roofline: per round every list entry (4 B index) and the
@@ -324,13 +326,14 @@ def main():
                 "connect_tile_steps": int(ps["connect_tile_steps"]),
                 "order_pivots": int(ps["order_pivots"]),
                 "order_padded_rows": int(ps["order_padded_rows"]),
+                "half_products": int(ps["half_products"]),
                 "mfma_tflops_on_multiplied_tiles":
                     2.0 * d * 128.0 * 128.0 * ps["knn_tile_steps"] / (ps["ms_knn_kernel"] * 1e-3) / 1e12,
                 "stages_ms": {n: float(ps[n]) for n in ("ms_norm_kernel", "ms_order", "ms_knn_kernel", "ms_boruvka",
                                                         "ms_connect", "ms_connect_kernels", "ms_sort",
                                                         "ms_dendrogram", "ms_total")},
             }
-            for role in ("pruned_knn_sweep", "pruned_connect_sweeps"):
+            for role in ("pruned_knn_half", "pruned_connect_half") if ps["half_products"] else ("pruned_knn_sweep", "pruned_connect_sweeps"):
                 ent = traffic_table.get(role)
                 if ent:
                     line["pruned"].setdefault("traffic", {})[role] = {

@@ -98,9 +98,12 @@ typedef struct slhc_stats {
     int64_t connect_tile_steps;      /* same, summed over the connection sweeps                    */
     int32_t pruned;                  /* 1 when tile pruning was active in this call                */
     int32_t order_padded_rows;       /* rows of the reordered copy incl. padding (0 when not pruned) */
-    int32_t split_products;          /* 1 when the k-NN sweep formed its tile products from split bfloat16
-                                        halves (see SLHC_FP32_FILTER), 0 when in float32              */
-    int32_t reserved0;
+    int32_t split_products;          /* 1 when the k-NN search formed tile products from 16-bit values (float16
+                                        copies or split bfloat16 halves, see half_products), 0 when all were in
+                                        float32 (see SLHC_FP32_FILTER)                                */
+    int32_t half_products;           /* 1 when the half-precision engine ran the k-NN search: one product of
+                                        float16 copies per pair; 0: the list kernels' split bfloat16 halves
+                                        (three products per pair) or float32                          */
 } slhc_stats;
 
 /* Option flags of the *_opt entry points. */

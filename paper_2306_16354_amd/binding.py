@@ -29,7 +29,7 @@ class _Stats(ctypes.Structure):
         ("ms_connect_kernels", ctypes.c_float), ("ms_order", ctypes.c_float),
         ("knn_tile_steps", ctypes.c_int64), ("connect_tile_steps", ctypes.c_int64),
         ("pruned", ctypes.c_int32), ("order_padded_rows", ctypes.c_int32),
-        ("split_products", ctypes.c_int32), ("reserved0", ctypes.c_int32),
+        ("split_products", ctypes.c_int32), ("half_products", ctypes.c_int32),
     ]
 
 SLHC_PRUNE = 1
@@ -278,7 +278,7 @@ def slhc(X, k, workspace=None, out=None, prune=True, split_rounds=False, split_s
                                  (SLHC_SPLIT_SCANS if split_scans else 0) | (0 if tile_table else SLHC_NO_TILE_TABLE) |
                                  (SLHC_FP32_FILTER if fp32_filter else 0) | (SLHC_PANEL_ORDER if panel_order else 0) |
                                   (SLHC_ONE_SHIFT if one_shift else 0)))
-    out["stats"] = {name: getattr(st, name) for name, _ in _Stats._fields_ if not name.startswith("reserved")}
+    out["stats"] = {name: getattr(st, name) for name, _ in _Stats._fields_}
     return out
 
 

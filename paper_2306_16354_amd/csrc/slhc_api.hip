@@ -2538,6 +2538,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     st.connect_tile_steps = (int64_t)(h_surv[3] + near_tile_steps);
     st.pruned = pruned ? 1 : 0;
     st.split_products = (kws.split_ready || kws.order_split_ready || kws.near_done) ? 1 : 0;
+    st.half_products = kws.near_done ? 1 : 0;
     if (pruned) { st.order_pivots = kws.order.P; st.order_padded_rows = kws.order.Ns; }
     const double t_forest = now_ms();
     st.ms_connect = (float)ms_connect;

@@ -687,8 +687,9 @@ def test_split_bf16_filter_loses_nothing(lib, kind, d):
     kt = min(k, 16)
     ta = lib.slhc(Xd, kt, prune=False, fp32_filter=True)
     assert ta["stats"]["split_products"] == 0
-    for tb in (lib.slhc(Xd, kt, prune=False), lib.slhc(Xd, kt, prune=False, panel_order=True), slhc_by_list_kernels(lib, Xd, kt, prune=False)):
-        assert tb["stats"]["split_products"] == 1
+    for half, tb in ((1, lib.slhc(Xd, kt, prune=False)), (0, lib.slhc(Xd, kt, prune=False, panel_order=True)),
+                     (0, slhc_by_list_kernels(lib, Xd, kt, prune=False))):
+        assert tb["stats"]["split_products"] == 1 and tb["stats"]["half_products"] == half
         for name_ in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
             assert torch.equal(ta[name_], tb[name_]), name_
 
