@@ -80,7 +80,7 @@ typedef struct slhc_stats {
     int32_t connect_rounds;          /* rounds in which the cross-component 1-NN kernel ran        */
     int32_t components_after_knn;    /* components when the k-NN lists alone could add no edge     */
     int32_t order_pivots;            /* pivots of the row order (0 when not pruned)                */
-    int64_t knn_filter_survivors;    /* pairs that passed the MFMA filter in the k-NN sweep        */
+    int64_t knn_filter_survivors;    /* pairs the k-NN search evaluated exactly (passed the MFMA filter) */
     int64_t connect_query_rows;      /* sum over connection rounds of queried rows                 */
     int64_t connect_filter_survivors;
     float ms_knn;                    /* norms + fused k-NN (host clock, includes the sync)         */
@@ -89,12 +89,12 @@ typedef struct slhc_stats {
     float ms_sort;                   /* edge sort                                                  */
     float ms_dendrogram;             /* device->host copy, host union-find, host->device copy      */
     float ms_total;
-    float ms_norm_kernel;            /* HIP-event time of the half-norm kernel                     */
-    float ms_knn_kernel;             /* HIP-event time of the fused k-NN sweep kernel alone        */
+    float ms_norm_kernel;            /* HIP-event time of the half norms and the float16 copy       */
+    float ms_knn_kernel;             /* HIP-event time of the k-NN search's kernels                */
     float ms_connect_kernels;        /* HIP-event time summed over the cross-component 1-NN sweeps */
     float ms_order;                  /* HIP-event time of building the row order + tile balls     */
     int64_t knn_tile_steps;          /* (query panel, candidate tile) pairs the k-NN sweep multiplied;
-                                        ceil(N/128)^2 when nothing is pruned (either sweep kernel)  */
+                                        ceil(N/128)^2 when nothing is pruned                       */
     int64_t connect_tile_steps;      /* same, summed over the connection sweeps                    */
     int32_t pruned;                  /* 1 when tile pruning was active in this call                */
     int32_t order_padded_rows;       /* rows of the reordered copy incl. padding (0 when not pruned) */
@@ -106,7 +106,9 @@ typedef struct slhc_stats {
                                         (three products per pair) or float32                          */
 } slhc_stats;
 
-/* Option flags of the *_opt entry points. */
+/* Option flags of the *_opt entry points.  By default the half-precision engine searches (tile products of float16 copies
+ * of the rows, bounds from a sample of the candidates, emission, exact evaluation of what is emitted); every flag but
+ * SLHC_PRUNE asks for a form of the list kernels instead, which keep lists of k inside one sweep.  Same outputs, bit for bit. */
 #define SLHC_PRUNE 1u   /* reorder rows spatially and skip (query panel, candidate tile) pairs whose
                            bounding balls prove that no pair can enter a list.  Results are identical
                            to the unpruned sweep; only available for d <= 128 and N >= 512 (ignored
@@ -123,27 +125,26 @@ typedef struct slhc_stats {
                            tiles into 5 work items that exchange what they find, which the library
                            otherwise does (in 2 to 16 parts) only for launches with few panels and
                            long scans.  Same outputs.                                           */
-#define SLHC_NO_TILE_TABLE 8u  /* with SLHC_PRUNE only; a testing aid.  The pruned sweeps compute the lower
+#define SLHC_NO_TILE_TABLE 8u  /* with SLHC_PRUNE only; a testing aid.  The pruned sweeps of the list kernels compute the lower
                            bounds of every query panel against the candidate tiles themselves, as
                            they do for row orders of more than 32768 tiles, instead of reading them
                            from the table of all tile pairs.  Same outputs.                     */
-#define SLHC_FP32_FILTER 16u   /* The sweeps accumulate their tile products in float32 (fp32 MFMA), as the
-                           pruned sweeps always do below 64 features, instead of in split bfloat16 halves
-                           (bf16 MFMA, 16 times the rate), which is the default of slhc_knn_graph* and
-                           slhc_slhc* (these work on a copy of X with zero columns appended: whole chunks of
-                           32 columns up to 128 features, a multiple of 4 beyond; a zero column changes no
-                           bit of any distance).  Only the filter differs: every
-                           pair that may enter a list is re-evaluated in float32 either way, so the
+#define SLHC_FP32_FILTER 16u   /* List kernels that accumulate their tile products in float32 (fp32 MFMA), as their pruned
+                           sweeps always do below 64 features, instead of in split bfloat16 halves (bf16 MFMA, 16
+                           times the rate).  (The list kernels of slhc_knn_graph* and slhc_slhc* work on a copy of X
+                           with zero columns appended: whole chunks of 32 columns up to 128 features, a multiple of 4
+                           beyond; a zero column changes no bit of any distance.)  Only the filter differs: every
+                           pair that may enter a list is evaluated in float32 either way, so the
                            outputs are the same bit for bit.                                     */
 
-#define SLHC_ONE_SHIFT 64u     /* with SLHC_PRUNE only; a testing and tuning aid.  The pruned k-NN sweep otherwise runs
+#define SLHC_ONE_SHIFT 64u     /* with SLHC_PRUNE only; a testing and tuning aid.  The list kernels' pruned k-NN sweep otherwise runs
                            as two launches where its products come from split bfloat16 halves (64 to 128
                            features): the candidate tiles of a row panel's own region (a run of tiles whose
                            centres stay close: a cluster) from a copy taken relative to a centre of that
                            region, which keeps the cluster's position out of the filter's slack, then the
                            other tiles from the copy relative to the column means.  With this flag: one launch,
                            all tiles from the latter copy.  Same outputs.                              */
-#define SLHC_PANEL_ORDER 32u   /* A testing and tuning aid.  Every-tile sweeps of many query panels (from 4 panels
+#define SLHC_PANEL_ORDER 32u   /* A testing and tuning aid.  The list kernels' every-tile sweeps of many query panels (from 4 panels
                            per workgroup slot on, d <= 128) otherwise hand out their work range by range:
                            the candidate tiles are cut into ranges of about 32 MiB, all workgroups sweep the
                            same range at a time (served by the memory-side cache instead of being fetched
@@ -153,7 +154,8 @@ typedef struct slhc_stats {
                            (Going range by range, a work item waits for the item that wrote its panel's
                            lists one range earlier; the wait is bounded, and if it ever ran out the
                            synchronous entry points would return SLHC_INTERNAL.  slhc_knn_graph is
-                           asynchronous and cannot; the condition has never been observed.)            */
+                           asynchronous and cannot; the condition has never been observed.  Without this flag that
+                           order serves calls with SLHC_FP32_FILTER and in small workspaces.)          */
 
 int slhc_abi_version(void);
 const char* slhc_strerror(int status);          /* static string, never NULL */
@@ -164,7 +166,7 @@ const char* slhc_last_error(void);              /* thread-local, never NULL  */
  *
  * For every row i the k rows j != i with the smallest (||x_i - x_j||^2, j), ascending.
  * The distance tile x_i . x_j is computed on the MFMA (from rows rounded to float16 with a bound on what the rounding
- * can do, unless SLHC_FP32_FILTER or SLHC_PANEL_ORDER asks for the list kernels) and only used to discard pairs that
+ * can do, unless a flag asks for the list kernels or the workspace has no room) and only used to discard pairs that
  * cannot enter a row's list; a pair that may enter is re-evaluated as sum_t (x_it - x_jt)^2
  * in fp32, so the reported value of (i,j) equals that of (j,i) bit for bit and duplicates are at
  * exactly 0.  A row is never its own neighbour (excluded by index, not by distance).
@@ -215,7 +217,7 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k,
  */
 int slhc_probe_fp32_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
 /* The same for v_mfma_f32_32x32x16_bf16, the multiply of the sweeps that form their tile products from split
- * bfloat16 halves (SLHC_FP32_FILTER describes them), and for v_mfma_f32_32x32x16_f16, that of the half-precision
+ * bfloat16 halves (list kernels, see SLHC_FP32_FILTER), and for v_mfma_f32_32x32x16_f16, that of the half-precision
  * engine; same arguments. */
 int slhc_probe_bf16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
 int slhc_probe_f16_mfma(double* tflops, void* workspace, size_t workspace_bytes, void* stream);
