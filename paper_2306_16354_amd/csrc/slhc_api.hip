@@ -2048,8 +2048,10 @@ int slhc_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src,
               void* workspace, size_t workspace_bytes, void* stream)
 {
     return guarded([&]() -> int {
-        // below this size the row order costs more than the skipped tiles save (measured on four kinds of data
-        // between 4096 and 65 536 rows: the two paths cross between 24 000 and 32 000 rows)
+        // Below this size the row order costs more than the skipped tiles save.  The line is where the two paths crossed with the list
+        // kernels (four kinds of data between 4096 and 65 536 rows: between 24 000 and 32 000 rows) and part of the interface.  With the
+        // half-precision engine they cross later: 24 576 x 64 1.3 to 1.4 ms with every tile and 3.3 to 4.3 ms in the row order, 65 536 x 64
+        // 3.7 to 4.5 and 5.1 to 7.4 ms; tight clusters 2.5 and 7.2, 12.3 and 10.3 ms.
         return slhc_slhc_opt(X, N, d, k, mst_src, mst_dst, mst_w, children, heights, sizes, stats, workspace,
                              workspace_bytes, stream, N >= SLHC_AUTO_PRUNE_MIN_ROWS ? SLHC_PRUNE : 0u);
     });
