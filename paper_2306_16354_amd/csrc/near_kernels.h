@@ -41,6 +41,7 @@ struct NearBuffers {           // scratch of one call
     float* shift;              // [d]
     float* partial;            // near_stats_scratch_floats(d)
     unsigned char* batch; size_t batch_bytes;     // bounds, group maxima, entries and counts of one batch of queries
+    unsigned char* pairs; size_t pairs_bytes;     // limits and lists of all rows (near_pairs_bytes), possibly the same memory; 0: none
     int32_t* todo;             // [2 + panels of 128 queries]: count, queries left by near_link, panels left to the list kernels
     int32_t* todo_mark;        // [panels]
     long long todo_panels;
@@ -61,6 +62,8 @@ size_t near_stats_scratch_floats(int d);
 // (kk: k, plus one where a query meets itself)
 size_t near_batch_bytes(long long nq, long long nc, int d, int kk);       // what NearBuffers::batch wants (less also works, down to one panel)
 size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk);
+// what NearBuffers::pairs wants for a search of the rows among themselves; 0: such a search does not use it
+size_t near_pairs_bytes(long long n, int d, int kk);
 
 // (clears `clear` [clear_words], optional, on the way)
 hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s);

@@ -21,95 +21,18 @@
 // the results are the same bits.  A query whose candidates do not fit its buffers even after tightening (masses of
 // ties) is left to the list kernels through a device-side list of panels.
 #include <hip/hip_runtime.h>
+#include <cmath>
 #include <stdint.h>
 #include "near_kernels.h"
+#include "near_parts.h"
+#include "pairs_kernels.h"
 #include "wave_ops.h"
 
 namespace slhc {
 
-typedef float v16f __attribute__((ext_vector_type(16)));
-typedef float v4f __attribute__((ext_vector_type(4)));
-typedef _Float16 v8h __attribute__((ext_vector_type(8)));
-typedef int v4i __attribute__((ext_vector_type(4)));
-
-constexpr int TILE = 128;
-constexpr int FRAG_STEP = 4096;            // bytes of a tile per 16 columns
-constexpr int REG_STEPS = 8;               // up to 128 columns the query fragments stay in registers
-constexpr float F16_LIMIT = 60000.f;       // larger values (after scaling) do not fit
-constexpr float F16_FLUSH = 6.103515625e-05f;   // 2^-14: smaller ones are rounded to 0, so no subnormal is ever multiplied
 constexpr int SAMPLE_RUNS = 64, SAMPLE_PER_RUN = 32;
 constexpr int MAX_ENTRIES = 1024;          // entries of one query over all its buffers
 constexpr int GROUPS = 32;                 // group maxima per query and part
-constexpr float INF = __builtin_inff();
-constexpr float LOWEST = -3.4028234663852886e38f;      // a bound every product value of a real row reaches
-#define NEVER __builtin_nanf("")                       // a bound nothing reaches, +inf included
-
-// What the arithmetic on the rounded rows can be off by.  An instruction aligns its 16 products and the accumulator
-// to the largest magnitude, one bit below its last place, cuts the rest off, adds and rounds: at most 18 units of
-// 2^-24 of that magnitude (6.0 measured at most, over 3 million sums against 64 bits: test_f16_mfma_error_stays_within_the_budget).
-// The accumulator starts at minus half the candidate's squared norm, so no partial sum
-// exceeds n_c / 2 + |x_q||x_c| <= n_c + n_q / 2, and after `steps` instructions the value is off by at most
-// e (n_c + n_q / 2), e = 9 steps 2^-23.  nu: the relative error of a squared norm (8 ceil(steps / 8) + 8 rounded
-// additions).  The stored half norms are lowered by what belongs to the candidate: a value `acc` is never below the
-// true one by more than e n_q / 2.
-struct NearBoundArgs { float e, nu, h_of_n, eps, delta, gamma, tiny; };
-static float near_e(int steps) { return 9.f * (float)steps * 1.02f * 1.1920928955078125e-07f; }
-static float near_nu(int steps) { return (float)(8 * ((steps + 7) / 8) + 8) * 5.9604644775390625e-08f; }
-
-// The product value any row within (scaled, squared) distance t2 of the query reaches; h: the query's stored half norm.
-__device__ inline float near_bound_at(float t2, float h, const NearBoundArgs& a)
-{
-    const float n = h / a.h_of_n;
-    const float norm = __builtin_sqrtf(n);
-    // what the exact evaluation's own rounding can hide, and underflow of its squares
-    const float t = __builtin_sqrtf(t2 * (1.f + a.gamma) + a.tiny);
-    const float rho_q = a.eps * norm + a.delta;
-    // a candidate within t of the query has a norm of at most norm + t + both displacements
-    const float rho_c = (a.eps * (norm + t + rho_q) + a.delta) * (1.f + 1e-3f);
-    const float reach = (t + rho_q + rho_c) * (1.f + 1e-6f);
-    return n * (0.5f - 0.5f * a.nu - 0.5f * a.e - 2.4e-7f) - 0.5f * reach * reach * (1.f + 1e-6f);
-}
-// From a product value some candidate shows: an upper bound of that candidate's distance (its squared norm n_c is at
-// most (|x_q| + D)^2 <= 1.25 n_q + 5 D^2), and from it the bound for all candidates that may be as near.
-__device__ inline float near_distance_from(float acc, float h, const NearBoundArgs& a)
-{
-    const float n = h / a.h_of_n;
-    const float norm = __builtin_sqrtf(n);
-    const float of_c = 4.f * a.e + 2.f * a.nu;
-    const float d2 = fmaxf(0.f, n * (1.f + a.nu + a.e + 1.25f * of_c + 4.8e-7f) - 2.f * acc) * (1.f + 6.f * of_c);
-    const float dd = __builtin_sqrtf(d2);
-    const float rho_q = a.eps * norm + a.delta;
-    const float rho_c = (a.eps * (norm + dd) + a.delta) * (1.f + 1e-3f);
-    return (dd + rho_q + rho_c) * (1.f + 1e-6f);
-}
-__device__ inline float near_bound_from(float acc, float h, const NearBoundArgs& a)
-{
-    const float t = near_distance_from(acc, h, a);
-    return near_bound_at(t * t * (1.f + a.gamma), h, a);
-}
-// near_bound_at the other way round: no row whose product value is `acc` at most is within this (scaled, squared) distance.
-__device__ inline float near_lower_from(float acc, float h, const NearBoundArgs& a)
-{
-    const float n = h / a.h_of_n;
-    const float norm = __builtin_sqrtf(n);
-    const float rho_q = a.eps * norm + a.delta;
-    const float reach2 = 2.f * (n * (0.5f - 0.5f * a.nu - 0.5f * a.e - 2.4e-7f) * (1.f - 1e-6f) - acc) * (1.f - 4e-6f);
-    const float reach = __builtin_sqrtf(fmaxf(0.f, reach2)) * (1.f - 4e-6f);
-    const float t = (reach - rho_q - (a.eps * (norm + rho_q) + a.delta) * (1.f + 2e-3f)) / (1.f + a.eps * (1.f + 2e-3f)) * (1.f - 4e-6f);
-    return t > 0.f ? fmaxf(0.f, (t * t * (1.f - 4e-6f) - a.tiny) / (1.f + a.gamma) * (1.f - 4e-6f)) : 0.f;
-}
-
-__device__ inline NearBoundArgs near_args(const NearScale* sc, int steps, int d, float e, float nu)
-{
-    NearBoundArgs a;
-    a.e = e; a.nu = nu;
-    a.h_of_n = 0.5f - 0.5f * nu - e;
-    a.eps = fminf(__uint_as_float(sc->eps_bits), 4.8876e-4f) * (1.f + 1e-3f);      // 2^-11 at most
-    a.delta = F16_FLUSH * __builtin_sqrtf((float)d);
-    a.gamma = (float)(2 * (d + 16)) * 1.1920928955078125e-07f;
-    a.tiny = (float)d * 2.350988701644575e-38f * sc->scale * sc->scale;            // d * 2^-125
-    return a;
-}
 
 // ---------------------------------------------------------------------------------------------- sample of the rows
 // Column means of SAMPLE_RUNS runs of evenly spaced rows, and per run the largest distance of a value from its run's
@@ -421,48 +344,11 @@ struct NearSweep {
 
 enum { NEAR_MAXIMA = 0, NEAR_EMIT = 1, NEAR_TOP = 2, NEAR_NEAREST = 3, NEAR_ARG = 4, NEAR_BLOCK = 5 };
 
-__device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
-
 // entries are written and read back by one wavefront, past its L1
 __device__ inline unsigned long long near_entry_load(const uint2* e)
 {
     return __hip_atomic_load(reinterpret_cast<const unsigned long long*>(e), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
-__device__ inline unsigned int ordered_bits(float x)
-{
-    const unsigned int b = __float_as_uint(x);
-    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
-}
-// A value that at least kk of the wavefront's values v(i), i < n, reach, and not many more: bisection between the
-// smallest and the largest of them.  Values that are not finite do not count.  Returns LOWEST when fewer than kk are.
-constexpr int BISECT = 13;
-template <typename V>
-__device__ inline float near_kth(int n, int kk, V&& value)
-{
-    float lo = INF, hi = -INF;
-    int have = 0;
-    for (int i = 0; i < n; i += 64) {
-        const float x = value(i);
-        const bool fine = fabsf(x) < INF;
-        have += __popcll(__ballot(fine));
-        lo = fine ? fminf(lo, x) : lo;
-        hi = fine ? fmaxf(hi, x) : hi;
-    }
-    if (have < kk) return LOWEST;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
-    for (int it = 0; it < BISECT; ++it) {
-        const float mid = 0.5f * lo + 0.5f * hi;
-        int reach = 0;
-        for (int i = 0; i < n; i += 64) {
-            const float x = value(i);
-            reach += __popcll(__ballot(x >= mid && x < INF));
-        }
-        if (reach >= kk) lo = mid; else hi = mid;
-    }
-    return lo;
-}
-
 // One lane's buffer is about to fill: the whole wavefront reads its n entries, finds the kk-th largest product value
 // (every one of them belongs to a different candidate, so kk candidates reach it) and keeps the entries that may
 // still be among the nearest.  Returns the new bound; *n the number kept.
@@ -715,14 +601,6 @@ struct NearLane {
     }
 };
 
-__device__ inline void near_lds_load(const void* g, void* l, bool quad)
-{
-    if (quad)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
-    else
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 4, 0, 0);
-}
-
 // The share of a workgroup: which panel, which segment of how many, and where the query tiles end.
 struct NearShare { int panel, seg, nseg, q_tile1; bool any; };
 __device__ inline NearShare near_share(const NearSweep& p, int item, int panel_tiles, int units)
@@ -749,15 +627,6 @@ __device__ inline int near_tile_at(const NearSweep& p, int seg, int nseg, int i)
 {
     const int j = seg + i * nseg;
     return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride;
-}
-
-// Waits for this wavefront's loads into LDS, then for the other wavefronts.
-__device__ inline void near_lds_ready()
-{
-    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
 }
 
 constexpr int ITEM_TILES = 64;
@@ -1061,12 +930,13 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
 // One wavefront per query: (nearly) the kk-th largest of its group maxima, and the bound that follows.
 // reach (optional): an upper end of the squared distance of the kk-th nearest row.  step (optional): a second set of maxima,
 // made where the step of the query's panel is not 0; the better of the two bounds stays (one candidate may be in both sets).
+template <bool LIMIT>
 __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restrict__ maxima, int parts, int log_groups, int nq_batch, int q0, int kk,
                                                           const float* __restrict__ qnegh, const NearScale* __restrict__ sc, float e,
                                                           float nu, int steps, int d, float* __restrict__ bound, float* __restrict__ reach,
                                                           const int32_t* __restrict__ step, int panel_queries,
                                                           const int32_t* __restrict__ region, const float* __restrict__ negh_local,
-                                                          const NearScale* __restrict__ sc_local)
+                                                          const NearScale* __restrict__ sc_local, int32_t* __restrict__ limit_counts)
 {
     const int lane = threadIdx.x & 63;
     const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1093,19 +963,25 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
     if (have >= kk)
-        for (int it = 0; it < BISECT; ++it) {
+        for (int it = 0; it < (LIMIT ? BISECT_FAR : BISECT); ++it) {
             const float mid = 0.5f * lo + 0.5f * hi;
             int reach = 0;
 #pragma unroll
             for (int j = 0; j < 16; ++j)
                 if (j * 64 < n) reach += __popcll(__ballot(v[j] >= mid));
             if (reach >= kk) lo = mid; else hi = mid;
+            if (LIMIT && reach == kk) break;
         }
     if (lane == 0) {
         if (region && region[(q0 + lq) >> 7] >= 0) { qnegh = negh_local; sc = sc_local; }
         const float nh = qnegh[q0 + lq];
         const NearBoundArgs a = near_args(sc, steps, d, e, nu);
         const float made = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
+        if (LIMIT) {                    // of a row for pairs_emit; none where there is no row or it goes to the list kernels
+            limit_counts[lq] = 0;
+            bound[lq] = !(fabsf(nh) < INF) ? NEVER : made == LOWEST ? LOWEST : made + nh;
+            return;
+        }
         bound[lq] = step ? fmaxf(bound[lq], made) : made;
         if (reach) {
             const float t = have < kk ? INF : near_distance_from(lo, -nh, a) / sc->scale;          // (a power of two)
@@ -1118,11 +994,6 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
 
 // ---------------------------------------------------------------------------------------------- selection
 constexpr unsigned int MARK = 0x80000000u;
-__device__ inline long long near_row(int pos, int tiles, int in_order)
-{
-    return in_order ? (long long)pos : (long long)(pos & (TILE - 1)) * tiles + (pos >> 7);
-}
-
 struct NearSelect {
     const uint2* entries; const int32_t* counts; int nsub, capl, nq_batch, q0, by_position;
     const float* qnegh; const NearScale* sc; float e, nu; int steps;
@@ -1138,6 +1009,7 @@ struct NearSelect {
     const int32_t* c_ids; int n_ids; // optional: candidates are positions of an order, c_ids[position] their row (-1: none)
     const int32_t* ids;              // optional: so are the queries
     const int32_t* qpos;             // optional: query i is this position of the copies
+    int pair_lists;                  // the entries hold u (pairs_kernels.h) instead of product values
     // optional, of an order with two copies (see NearSweep): entries without MARK come from the local one
     const int32_t* region; const float* negh_local; const NearScale* sc_local;
 };
@@ -1241,7 +1113,10 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
                 if (sub + o <= p.nsub && end <= at) sub += o;
             }
             const int begin = __shfl(upto - mine, sub & 63);
-            if (at < n) keys[at] = e[(size_t)sub * p.capl + (at - begin)];
+            if (at < n) {
+                const unsigned long long x = e[(size_t)sub * p.capl + (at - begin)];
+                keys[at] = p.pair_lists ? (x & 0xffffffff00000000ull) | __float_as_uint(__uint_as_float((unsigned int)x) - nh) : x;
+            }
         }
     }
     if (lost) {
@@ -1363,6 +1238,23 @@ static int near_cus()
     return v;
 }
 
+// A sample of one candidate tile in `stride`, searched in at most `seg` segments.
+static void near_sample(NearPlan& p, int stride, int CT, int kk, bool wide, int seg)
+{
+    p.stride = stride;
+    p.used = (CT + stride - 1) / stride;
+    p.max_seg = seg;
+    const int sets = p.max_seg * (wide ? 2 : 1);         // sets of group maxima per part
+    const int per_seg = ((wide ? (p.used + 1) / 2 : p.used) + p.max_seg - 1) / p.max_seg;
+    // about six groups per neighbour wanted, in 8 or 32 groups per set
+    p.groups = 6 * kk <= 8 * sets ? 8 : GROUPS;
+    int parts = (6 * kk + p.groups * sets - 1) / (p.groups * sets);
+    if (parts > per_seg) parts = per_seg;
+    if (parts * sets > 32) parts = 32 / sets;
+    p.max_parts = parts < 1 ? 1 : parts;
+    p.max_sets = sets * p.max_parts;
+}
+
 static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batch_bytes)
 {
     NearPlan p{};
@@ -1403,18 +1295,7 @@ static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batc
         if (stride > 5) stride = 5;
         if (stride < 1) stride = 1;
         p.stages = stride >= 3 ? 2 : 1;
-        p.stride = stride;
-        p.used = (CT + stride - 1) / stride;
-        p.max_seg = segs(wide ? (p.used + 1) / 2 : p.used, wide ? 8 : 16);
-        const int sets = p.max_seg * (wide ? 2 : 1);     // sets of group maxima per part
-        const int per_seg = ((wide ? (p.used + 1) / 2 : p.used) + p.max_seg - 1) / p.max_seg;
-        // about six groups per neighbour wanted, in 8 or 32 groups per set
-        p.groups = 6 * kk <= 8 * sets ? 8 : GROUPS;
-        int parts = (6 * kk + p.groups * sets - 1) / (p.groups * sets);
-        if (parts > per_seg) parts = per_seg;
-        if (parts * sets > 32) parts = 32 / sets;
-        p.max_parts = parts < 1 ? 1 : parts;
-        p.max_sets = sets * p.max_parts;
+        near_sample(p, stride, CT, kk, wide, segs(wide ? ((CT + stride - 1) / stride + 1) / 2 : (CT + stride - 1) / stride, wide ? 8 : 16));
     }
     p.per_tile = kk == 1 ? (size_t)TILE * 8 * (size_t)p.capl
                          : (size_t)TILE * (4 + (size_t)(p.used ? p.max_sets * p.groups * 4 : 0) + (size_t)p.nsub * (4 + 8 * (size_t)p.capl));
@@ -1623,6 +1504,183 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
     return hipGetLastError();
 }
 
+// ---------------------------------------------------------------------------------------------- rows among themselves
+// A k-NN search whose queries are its candidates multiplies every pair once (pairs_kernels.hip): limits from a sample as before,
+// then the offsets round the circle of blocks in a few bands; between two bands every row's limit is tightened by what its list
+// holds.  A list needs room for what passes before the next tightening: kk * g entries and what rounding adds, if a band has
+// seen g times as many rows at its end as at its beginning (every tile is an even sample of the rows).  Rows whose lists
+// overflow all the same are searched for on their own, with the buffers and the tightening of the sweeps.
+// (Sorting the rows by their nearest of a few hundred pivots first, so that what passes comes together, was tried: limits then come from
+// a row's own surroundings and say nothing about the other rows, a third of the rows overflowed, 1M x 128 took 250 ms
+// without their panels against 200 ms.)
+struct PairPlan {
+    NearPlan sample;
+    int waves, blocks, cap, bands, to[8], nseg[8];
+};
+// Who gains: up to 64 columns a block's comparisons (66 instructions of its wavefront) take as long as its products, and of the rows of a
+// small search every block holds a few that pass.  Each side in us, products once per row and once per pair: 5000 x 40, k = 10: 76 and 65;
+// 10 000 x 64, 20: 151 and 128; 20 000 x 128, 32: 356 and 370; 20 011 x 50, 10: 224 and 237; 120 000 x 64, 32: 4220 and 4780; 250 000 x 33, 40:
+// 13.1 and 13.6 ms; 50 000 x 96, 32: 1700 and 1360; 200 000 x 128, 16: 17.2 and 12.4 ms; 5000 x 200, 10: 146 and 105; 250 000 x 784, 16: 126 and 62 ms.
+// (up to 12 800 rows it is the fewer, longer shares of the candidates that gain)
+static bool pair_search_wanted(int T, int steps)
+{
+    if (T < 32 || T >= (1 << 17)) return false;
+    return steps > REG_STEPS || (T <= 100 ? steps >= 3 : T >= 256 && steps >= 5);
+}
+// from here on rows whose lists overflow are searched for on their own before the list kernels take their panels; below, the five
+// launches cost more (20 us) than a panel or two
+constexpr int PAIR_AGAIN_TILES = 128;
+static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
+{
+    const int T = near_tiles(n), steps = near_steps(d);
+    if (kk < 2 || !pair_search_wanted(T, steps)) return false;
+    PairPlan p{};
+    const bool wide = steps > REG_STEPS;
+    const int cus = near_cus();
+    p.cap = (12 * kk + 63) / 64 * 64;
+    p.cap = p.cap < 256 ? 256 : (p.cap > PAIRS_MOST ? PAIRS_MOST : p.cap);
+    p.waves = 8;
+    while (!wide && p.waves > 2 && (T / (p.waves / 2)) * (T / p.waves) < 2 * cus) p.waves >>= 1;
+    const int bt = wide ? 2 : p.waves / 2, slots = p.waves == 8 ? cus : 2 * cus;
+    p.blocks = (T + bt - 1) / bt;
+    const int half = p.blocks / 2 + 1;
+    // What a sample of one tile in `stride` costs, and one band (0) or a first one of the sample's share and b more that see
+    // g times as much each, in us: the products of the sample (1.1e15 a second), 15 us per band, 0.1 ns per entry, of which
+    // rounding makes twice what is asked for on average.
+    const double all = (double)n * n * 32.0 * (steps < 6 ? 6 : steps) / 1.1e9, entry = 2e-4 * n * kk, most = p.cap / (3.5 * kk);
+    double best = 1e300;
+    int stride = 1, more = 0;
+    for (int s = 1; s <= 16 && s <= T / 16; ++s)
+        for (int b = 0; b <= 7; ++b) {
+            const double g = b > 0 ? pow((double)s, 1.0 / b) : s;
+            if (g > most && s > 1 && b < 7) continue;
+            const double cost = all / s + 15.0 * (b + 1) + entry * (b > 0 ? 1.0 + b * (g - 1.0) : g);
+            if (cost < best) { best = cost; stride = s; more = b; }
+        }
+    const double g = more > 0 ? pow((double)stride, 1.0 / more) : 1.0;
+    double seen = 1.0 / stride;
+    int from = 0;
+    for (p.bands = 0; from < half; ++p.bands, seen *= g) {
+        int to = p.bands == more ? half : (int)(0.5 * (seen * p.blocks + 1.0));
+        to = to < from + 1 ? from + 1 : (to > half ? half : to);
+        const int len = to - from;
+        int seg = (8 * slots + p.blocks - 1) / p.blocks;
+        if (wide && seg < 4) seg = 4;      // (so that an XCD's workgroups share 8 blocks, see the kernel)
+        p.to[p.bands] = to;
+        p.nseg[p.bands] = seg > len ? len : seg;
+        from = to;
+    }
+    p.sample = near_plan(n, n, d, kk, 0);
+    NearPlan& q = p.sample;
+    const int used = (T + stride - 1) / stride, panels = (T + q.panel_tiles - 1) / q.panel_tiles;
+    int seg = (q.waves == 8 ? cus : 2 * cus) / panels;
+    const int units = wide ? (used + 1) / 2 : used, limit = wide ? 8 : 16;
+    seg = seg > limit ? limit : seg;
+    seg = seg > units ? units : seg;
+    near_sample(q, stride, T, kk, wide, seg < 1 ? 1 : seg);
+    *out = p;
+    return true;
+}
+
+size_t near_pairs_bytes(long long n, int d, int kk)
+{
+    PairPlan p;
+    if (!near_pair_plan(n, d, kk, &p)) return 0;
+    return (size_t)near_tiles(n) * TILE * (24 + 8 * (size_t)p.cap) + 4096;
+}
+
+static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, const NearBuffers& b, const PairPlan& plan, bool vec4, hipStream_t s)
+{
+    const int kk = a.k + 1, steps = near_steps(a.d), rows = c.tiles * TILE;
+    const bool wide = steps > REG_STEPS;
+    const float e = near_e(steps), nu = near_nu(steps);
+    unsigned char* at = b.pairs;
+    auto take = [&](size_t bytes) { unsigned char* r = at; at += (bytes + 255) / 256 * 256; return r; };
+    float* limit = reinterpret_cast<float*>(take((size_t)rows * 4));
+    int32_t* counts = reinterpret_cast<int32_t*>(take((size_t)rows * 4));
+    PairsLeft left{};
+    left.row = reinterpret_cast<int32_t*>(take((size_t)rows * 4)); left.pos = reinterpret_cast<int32_t*>(take((size_t)rows * 4));
+    left.counts = reinterpret_cast<int32_t*>(take((size_t)rows * 4)); left.reach = reinterpret_cast<float*>(take((size_t)rows * 4));
+    left.count = b.todo + 1;
+    const size_t lists_bytes = (size_t)rows * (size_t)plan.cap * 8;
+    uint2* entries = reinterpret_cast<uint2*>(take(lists_bytes));
+    NearSweep p{};
+    p.qfrag = p.cfrag = c.frag; p.qnegh = p.cnegh = c.negh; p.c_tiles = c.tiles;
+    p.sc = b.scale; p.d = a.d; p.steps = steps; p.e = e; p.nu = nu; p.kk = kk;
+    const NearPlan& q = plan.sample;
+    p.stride = q.stride; p.used = q.used; p.nseg = q.max_seg; p.parts = q.max_parts; p.groups = q.groups;
+    float* maxima = reinterpret_cast<float*>(entries);              // (the lists are empty yet)
+    const size_t per_tile = (size_t)TILE * q.max_sets * q.groups * 4;
+    long long batch = (long long)(lists_bytes / per_tile) / q.panel_tiles * q.panel_tiles;
+    if (batch < 1) return hipErrorInvalidValue;
+    hipError_t err = hipSuccess;
+    for (int t0 = 0; t0 < c.tiles; t0 += (int)batch) {
+        const int t1 = t0 + batch < c.tiles ? t0 + (int)batch : c.tiles;
+        p.q_tile0 = t0; p.q_tile1 = t1; p.nq_batch = (t1 - t0) * TILE;
+        p.maxima = maxima;
+        err = near_launch_sweep<NEAR_MAXIMA, false>(p, q.waves, s);
+        if (err != hipSuccess) return err;
+        hipLaunchKernelGGL((near_bounds_kernel<true>), dim3((unsigned)(p.nq_batch / 4)), dim3(256), 0, s, maxima, q.max_sets, q.groups == GROUPS ? 5 : 3, p.nq_batch,
+                           t0 * TILE, kk, c.negh, b.scale, e, nu, steps, a.d, limit + (size_t)t0 * TILE, static_cast<float*>(nullptr),
+                           static_cast<const int32_t*>(nullptr), 1, static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr),
+                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE);
+    }
+    NearPairs r{};
+    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks;
+    r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
+    for (int i = 0; i < plan.bands; ++i) {
+        if (i > 0) {
+            err = pairs_tighten(r, kk, b.scale, e, nu, a.d, s);
+            if (err != hipSuccess) return err;
+        }
+        r.from = i > 0 ? plan.to[i - 1] : 0; r.to = plan.to[i]; r.nseg = plan.nseg[i];
+        err = pairs_emit(r, plan.waves, s);
+        if (err != hipSuccess) return err;
+    }
+    const bool again = c.tiles >= PAIR_AGAIN_TILES;
+    if (again) {
+        err = pairs_left(r, kk, b.scale, e, nu, a.d, a.nq, left, s);
+        if (err != hipSuccess) return err;
+    }
+    NearSelect sel{};
+    sel.qnegh = c.negh; sel.sc = b.scale; sel.e = e; sel.nu = nu; sel.steps = steps;
+    sel.Xq = a.Xq; sel.Xc = a.Xc;
+    sel.d = a.d; sel.k = a.k; sel.kk = kk; sel.nq = a.nq; sel.nq_rows = a.nq_rows; sel.nc = a.nc;
+    sel.q_tiles = sel.c_tiles = c.tiles; sel.exclude_self = 1;
+    sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
+    sel.todo = b.todo; sel.todo_mark = b.todo_mark;
+    sel.entries = entries; sel.counts = counts; sel.nsub = 1; sel.by_position = 1; sel.capl = plan.cap; sel.pair_lists = 1;
+    sel.nq_batch = rows; sel.q0 = 0;
+    auto select = [&]() -> hipError_t {
+        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
+        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
+        return hipGetLastError();
+    };
+    err = select();
+    if (err != hipSuccess || !again) return err;
+    // The rows left: any kk of the rows met reach their distance, and lists of 1024 rarely overflow; where one does, its kk-th value
+    // makes the second search short.
+    const int waves = wide ? 8 : 4;
+    r.cap = PAIRS_MOST;
+    p.stride = 1; p.used = c.tiles;
+    p.qpos = left.pos; p.n_dev = left.count; p.slots = (waves == 8 ? 1 : 2) * near_cus(); p.most_seg = p.slots;
+    p.reach = left.reach; p.counts = left.counts; p.capl = PAIRS_MOST; p.entries = entries;
+    sel.q_rows = sel.slot = left.row; sel.qpos = left.pos; sel.n_dev = left.count;
+    sel.q_in_order = 1; sel.counts = left.counts; sel.capl = PAIRS_MOST; sel.pair_lists = 0; sel.nq = rows;
+    const int room = (int)(lists_bytes / ((size_t)TILE * PAIRS_MOST * 8)) / 2 * 2;           // tiles of queries whose lists fit
+    if (room < 2) return hipErrorInvalidValue;
+    for (int t0 = 0; t0 < c.tiles; t0 += room) {
+        p.q_tile0 = t0; p.q_tile1 = t0 + room < c.tiles ? t0 + room : c.tiles;
+        p.nq_batch = sel.nq_batch = (p.q_tile1 - t0) * TILE; sel.q0 = t0 * TILE;
+        err = near_launch_sweep<NEAR_NEAREST, false>(p, waves, s);
+        if (err == hipSuccess) err = pairs_again(r, kk, b.scale, e, nu, a.d, t0 * TILE, p.nq_batch, left, s);
+        if (err == hipSuccess) err = near_launch_sweep<NEAR_NEAREST, false>(p, waves, s);
+        if (err == hipSuccess) err = select();
+        if (err != hipSuccess) return err;
+    }
+    return hipSuccess;
+}
+
 hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
 {
     const int kk = a.k + (a.exclude_self ? 1 : 0);
@@ -1630,12 +1688,16 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
     if (plan.batch_tiles < 1 || (a.nq + 127) / 128 > b.todo_panels || (a.coloured && (kk != 1 || !q.colour || !c.colour)) ||
         (kk == 1 && (!q.left || !q.count || !c.negh_best)))
         return hipErrorInvalidValue;
+    const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
+    PairPlan pairs;
+    if (a.exclude_self && q.frag == c.frag && !c.in_order && b.pairs && near_pair_plan(a.nc, a.d, kk, &pairs) &&
+        b.pairs_bytes >= near_pairs_bytes(a.nc, a.d, kk))
+        return near_search_pairs(a, c, b, pairs, vec4, s);
     NearSweep p{};
     p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour;
     p.cfrag = c.frag; p.cnegh = c.negh; p.ccolour = c.colour; p.c_tiles = c.tiles;
     p.sc = b.scale; p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
     p.kk = kk;
-    const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
     NearSelect sel{};
     sel.qnegh = q.negh; sel.sc = b.scale; sel.e = p.e; sel.nu = p.nu; sel.steps = p.steps;
     sel.Xq = a.Xq; sel.Xc = a.Xc; sel.q_rows = a.q_rows;
@@ -1676,9 +1738,9 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
             e = near_launch_sweep<NEAR_MAXIMA, false>(p, plan.waves, s);
             if (e != hipSuccess) return e;
         }
-        hipLaunchKernelGGL(near_bounds_kernel, per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
+        hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
                            plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound, static_cast<float*>(nullptr), static_cast<const int32_t*>(nullptr), 1,
-                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr));
+                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr), static_cast<int32_t*>(nullptr));
         p.nseg = plan.nseg; p.nsub = plan.nsub;
         sel.nsub = plan.nsub; sel.by_position = 0; sel.merge = 0; sel.next_bound = nullptr;
         if (plan.stages == 2) {
@@ -2101,8 +2163,8 @@ hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const N
         p.maxima = maxima; p.groups = GROUPS; p.capl = plan.capl; p.append = 0;
         sel.nq_batch = nqb; sel.q0 = t0 * TILE;
         auto bounds = [&](int sets, const int32_t* steps_of) {
-            hipLaunchKernelGGL(near_bounds_kernel, per_query, dim3(256), 0, s, maxima, sets, 5, nqb, t0 * TILE, kk, o.all.negh, b.scale, p.e, p.nu,
-                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale);
+            hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, sets, 5, nqb, t0 * TILE, kk, o.all.negh, b.scale, p.e, p.nu,
+                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale, static_cast<int32_t*>(nullptr));
         };
         NearList l{};
         l.gap = o.gap; l.T = T; l.region = o.region; l.reach = reach; l.n_pos = T * TILE; l.q0 = t0 * TILE; l.nq = nqb;
@@ -2266,6 +2328,64 @@ static void near_edges(const NearRange& r, bool vec4, hipStream_t s)
     else hipLaunchKernelGGL((near_edge_kernel<false>), dim3((unsigned)((r.n + 3) / 4)), dim3(256), 0, s, r);
 }
 
+// Where most rows are queries, one pass over all pairs of rows serves both rows of each (pairs_best) and costs half of one over
+// all candidates of every row; rows that ask nothing are served too.
+static bool near_link_by_pairs(const NearLink& a, const NearCopy& c, const NearBuffers& b)
+{
+    return near_steps(a.d) > REG_STEPS && c.rows == a.n_rows && c.tiles >= 32 && 5LL * a.n >= 3LL * a.n_rows && !c.in_order &&
+           b.batch_bytes >= (size_t)c.tiles * TILE * 8;
+}
+__global__ void __launch_bounds__(256) near_pair_best_clear_kernel(unsigned long long* __restrict__ best, int n)
+{
+    const int i = blockIdx.x * 256 + threadIdx.x;
+    if (i < n) best[i] = 0x7f800000ffffffffull;
+}
+// (w, position) by position of the copy of all rows -> (distance below which there is no candidate, position) by query
+__global__ void __launch_bounds__(256) near_pair_best_kernel(const unsigned long long* __restrict__ best, const int32_t* __restrict__ rows, int n, int n_rows,
+                                                             int tiles, const float* __restrict__ negh, const NearScale* __restrict__ sc, float e, float nu,
+                                                             int steps, int d, unsigned long long* __restrict__ best_at)
+{
+    const int q = blockIdx.x * 256 + threadIdx.x;
+    if (q >= n) return;
+    const int row = rows[q];
+    unsigned long long out = ~0ull;
+    if ((unsigned int)row < (unsigned int)n_rows) {
+        const int pos = row % tiles * TILE + row / tiles;               // (see near_row)
+        const unsigned long long key = best[pos];
+        const float w = __uint_as_float((unsigned int)(key >> 32)), h = -negh[pos];
+        if (w < INF && fabsf(h) < INF) {
+            // (w = 0: the value itself was cut off)
+            const NearBoundArgs a = near_args(sc, steps, d, e, nu);
+            const float low = w > 0.f ? near_lower_from(h - w, h, a) / sc->scale / sc->scale : 0.f;
+            out = ((unsigned long long)__float_as_uint(low) << 32) | (unsigned int)key;
+        }
+    }
+    best_at[q] = out;
+}
+static hipError_t near_link_pairs(const NearLink& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
+{
+    NearPairs r{};
+    r.frag = c.frag; r.negh = c.negh_best; r.colour = c.colour; r.tiles = c.tiles; r.steps = near_steps(a.d);
+    r.blocks = (c.tiles + 1) / 2;
+    r.best = reinterpret_cast<unsigned long long*>(b.batch);
+    const int n = c.tiles * TILE, half = r.blocks / 2 + 1, cus = near_cus();
+    hipLaunchKernelGGL(near_pair_best_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, r.best, n);
+    auto shares = [&](int len) { const int seg = (8 * cus + r.blocks - 1) / r.blocks; return seg < 4 ? (len < 4 ? len : 4) : (seg > len ? len : seg); };
+    // every row's own block and a few more first: what they leave keeps nearly all updates of the other rows' words away
+    const int first = half / 32 > 1 ? half / 32 : 1;
+    r.from = 0; r.to = first; r.both = 0; r.nseg = shares(first);
+    hipError_t e = pairs_best(r, s);
+    if (e != hipSuccess) return e;
+    if (half > 1) {
+        r.from = 1; r.to = half; r.both = 1; r.nseg = shares(half - 1);
+        e = pairs_best(r, s);
+        if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(near_pair_best_kernel, dim3((unsigned)((a.n + 255) / 256)), dim3(256), 0, s, r.best, a.rows, a.n, a.n_rows, c.tiles, c.negh_best,
+                       b.scale, near_e(r.steps), near_nu(r.steps), r.steps, a.d, q.best_at);
+    return hipGetLastError();
+}
+
 // Connection rounds.  One pass over all candidates leaves per query the distance below which there is none and the 16
 // candidates about the nearest.  Bound by that pass: the search that follows is left with a query or two per component (10 of
 // 250 000), where every query used to go through it.  250k x 784, ten components: 346 -> 240 ms per call (a pass takes
@@ -2284,7 +2404,8 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
     p.sc = b.scale; p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
     p.nseg = plan.nseg; p.stride = 1; p.used = c.tiles; p.kk = 1;
     p.best_at = q.best_at;
-    e = near_launch_sweep<NEAR_BLOCK, true>(p, plan.waves, s);
+    if (near_link_by_pairs(a, c, b)) e = near_link_pairs(a, q, c, b, s);
+    else e = near_launch_sweep<NEAR_BLOCK, true>(p, plan.waves, s);
     if (e != hipSuccess) return e;
     NearRange r{};
     r.X = a.X; r.colour = a.colour; r.c_tiles = c.tiles; r.c_in_order = c.in_order; r.d = a.d;

@@ -1,0 +1,161 @@
+// Device parts that the passes of the half-precision engine share: bounds between product values and distances, the search for
+// the k-th largest of a wavefront's values, loads into LDS.
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "near_kernels.h"
+
+namespace slhc {
+
+typedef float v16f __attribute__((ext_vector_type(16)));
+typedef float v4f __attribute__((ext_vector_type(4)));
+typedef _Float16 v8h __attribute__((ext_vector_type(8)));
+typedef int v4i __attribute__((ext_vector_type(4)));
+
+constexpr int TILE = 128;
+constexpr int FRAG_STEP = 4096;            // bytes of a tile per 16 columns
+constexpr int REG_STEPS = 8;               // up to 128 columns the query fragments stay in registers
+constexpr float F16_LIMIT = 60000.f;       // larger values (after scaling) do not fit
+constexpr float F16_FLUSH = 6.103515625e-05f;   // 2^-14: smaller ones are rounded to 0, so no subnormal is ever multiplied
+constexpr float INF = __builtin_inff();
+constexpr float LOWEST = -3.4028234663852886e38f;      // a bound every product value of a real row reaches
+#define NEVER __builtin_nanf("")                       // a bound nothing reaches, +inf included
+
+// What the arithmetic on the rounded rows can be off by.  An instruction aligns its 16 products and the accumulator
+// to the largest magnitude, one bit below its last place, cuts the rest off, adds and rounds: at most 18 units of
+// 2^-24 of that magnitude (6.0 measured at most, over 3 million sums against 64 bits: test_f16_mfma_error_stays_within_the_budget).
+// The accumulator starts at minus half the candidate's squared norm n_c.  With a, b the first columns of the query and of the
+// candidate, a . b = (|a|^2 + |b|^2 - |a - b|^2) / 2, so a partial sum lies between -n_c / 2 - D^2 / 2 and n_q / 2 for rows a distance
+// D apart; and all products together have at most the magnitude (n_q + n_c) / 2.  After `steps` instructions the value is off by at most
+//     kappa (steps (max(n_q, n_c) / 2 + D^2 / 2) + (n_q + n_c) / 2),   kappa = 18 2^-24,
+// and since |n_q - n_c| <= D (2 |x_q| + D), by at most e (n_q + n_c) + f (D |x_q| / 2 + 5/4 D^2) with e = kappa (steps / 4 + 1 / 2) and
+// f = kappa steps, for either row in the role of the query: a pair's one product may serve both (pairs_kernels.hip).
+// (Counting every partial sum as n_c + n_q / 2 instead: 1M x 128 in the row order evaluated 46.9 pairs per row exactly instead of 43.8.)
+// nu: the relative error of a squared norm (8 ceil(steps / 8) + 8 rounded additions).  The stored half norms are lowered by what
+// belongs to the candidate: a value `acc` is never below the true one by more than e n_q + f (...).
+struct NearBoundArgs { float e, f, nu, h_of_n, eps, delta, gamma, tiny; };
+static float near_kappa() { return 9.f * 1.02f * 1.1920928955078125e-07f; }
+static float near_e(int steps) { return near_kappa() * (0.25f * (float)steps + 0.5f); }
+static float near_nu(int steps) { return (float)(8 * ((steps + 7) / 8) + 8) * 5.9604644775390625e-08f; }
+
+// The product value any row within (scaled, squared) distance t2 of the query reaches; h: the query's stored half norm.
+// (8 units of 2^-24 of n for the roundings here and of limits and values that have h added or taken off)
+__device__ inline float near_bound_at(float t2, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    // what the exact evaluation's own rounding can hide, and underflow of its squares
+    const float t = __builtin_sqrtf(t2 * (1.f + a.gamma) + a.tiny);
+    const float rho_q = a.eps * norm + a.delta;
+    // a candidate within t of the query has a norm of at most norm + t + both displacements
+    const float rho_c = (a.eps * (norm + t + rho_q) + a.delta) * (1.f + 1e-3f);
+    const float reach = (t + rho_q + rho_c) * (1.f + 1e-6f);
+    return n * (0.5f - 0.5f * a.nu - a.e - 4.8e-7f) - 0.5f * reach * (reach * (1.f + 2e-6f + 2.5f * a.f) + a.f * norm);
+}
+// From a product value some candidate shows: an upper bound of that candidate's distance (its squared norm n_c is at
+// most (|x_q| + D)^2 <= 9/8 n_q + 9 D^2, and D |x_q| at most n_q / 8 + 2 D^2), and from it the bound for all candidates that
+// may be as near.
+__device__ inline float near_distance_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    const float of_c = 4.f * a.e + 2.f * a.nu, of_d = 4.5f * a.f + 9.f * of_c;
+    if (of_d > 0.9f) return INF;                                // (hundreds of thousands of columns)
+    const float d2 = fmaxf(0.f, n * (1.f + a.nu + 2.f * a.e + 1.125f * of_c + 0.125f * a.f + 9.6e-7f) - 2.f * acc) / (1.f - of_d) * (1.f + 1e-6f);
+    const float dd = __builtin_sqrtf(d2);
+    const float rho_q = a.eps * norm + a.delta;
+    const float rho_c = (a.eps * (norm + dd) + a.delta) * (1.f + 1e-3f);
+    return (dd + rho_q + rho_c) * (1.f + 1e-6f);
+}
+__device__ inline float near_bound_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float t = near_distance_from(acc, h, a);
+    return t < INF ? near_bound_at(t * t * (1.f + a.gamma), h, a) : LOWEST;
+}
+// near_bound_at the other way round: no row whose product value is `acc` at most is within this (scaled, squared) distance.
+__device__ inline float near_lower_from(float acc, float h, const NearBoundArgs& a)
+{
+    const float n = h / a.h_of_n;
+    const float norm = __builtin_sqrtf(n);
+    const float rho_q = a.eps * norm + a.delta;
+    const float reach2 = (2.f * (n * (0.5f - 0.5f * a.nu - a.e - 4.8e-7f) * (1.f - 1e-6f) - acc) - 0.125f * a.f * n) / (1.f + 4.5f * a.f) * (1.f - 6e-6f);
+    const float reach = __builtin_sqrtf(fmaxf(0.f, reach2)) * (1.f - 4e-6f);
+    const float t = (reach - rho_q - (a.eps * (norm + rho_q) + a.delta) * (1.f + 2e-3f)) / (1.f + a.eps * (1.f + 2e-3f)) * (1.f - 4e-6f);
+    return t > 0.f ? fmaxf(0.f, (t * t * (1.f - 4e-6f) - a.tiny) / (1.f + a.gamma) * (1.f - 4e-6f)) : 0.f;
+}
+
+__device__ inline NearBoundArgs near_args(const NearScale* sc, int steps, int d, float e, float nu)
+{
+    NearBoundArgs a;
+    a.e = e; a.nu = nu;
+    a.f = 9.f * 1.02f * 1.1920928955078125e-07f * (float)steps;
+    a.h_of_n = 0.5f - 0.5f * nu - e;
+    a.eps = fminf(__uint_as_float(sc->eps_bits), 4.8876e-4f) * (1.f + 1e-3f);      // 2^-11 at most
+    a.delta = F16_FLUSH * __builtin_sqrtf((float)d);
+    a.gamma = (float)(2 * (d + 16)) * 1.1920928955078125e-07f;
+    a.tiny = (float)d * 2.350988701644575e-38f * sc->scale * sc->scale;            // d * 2^-125
+    return a;
+}
+
+__device__ inline float max3(float a, float b, float c) { return fmaxf(fmaxf(a, b), c); }
+
+__device__ inline unsigned int ordered_bits(float x)
+{
+    const unsigned int b = __float_as_uint(x);
+    return (b & 0x80000000u) ? ~b : (b | 0x80000000u);
+}
+// A value that at least kk of the wavefront's values v(i), i < n, reach, and not many more: bisection between the
+// smallest and the largest of them.  Values that are not finite do not count.  Returns LOWEST when fewer than kk are.
+// BISECT_FAR: where the ends may be a thousand times farther apart than the values in question and a list overflows for it (one
+// group of a sample without a row of the query's cluster).
+constexpr int BISECT = 13, BISECT_FAR = 20;
+template <typename V>
+__device__ inline float near_kth(int n, int kk, V&& value)
+{
+    float lo = INF, hi = -INF;
+    int have = 0;
+    for (int i = 0; i < n; i += 64) {
+        const float x = value(i);
+        const bool fine = fabsf(x) < INF;
+        have += __popcll(__ballot(fine));
+        lo = fine ? fminf(lo, x) : lo;
+        hi = fine ? fmaxf(hi, x) : hi;
+    }
+    if (have < kk) return LOWEST;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    for (int it = 0; it < BISECT; ++it) {
+        const float mid = 0.5f * lo + 0.5f * hi;
+        int reach = 0;
+        for (int i = 0; i < n; i += 64) {
+            const float x = value(i);
+            reach += __popcll(__ballot(x >= mid && x < INF));
+        }
+        if (reach >= kk) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
+__device__ inline void near_lds_load(const void* g, void* l, bool quad)
+{
+    if (quad)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 16, 0, 0);
+    else
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void*)g, (__attribute__((address_space(3))) void*)l, 4, 0, 0);
+}
+
+// Waits for this wavefront's loads into LDS, then for the other wavefronts.
+__device__ inline void near_lds_ready()
+{
+    __builtin_amdgcn_s_waitcnt(0x0f70);          // vmcnt(0)
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
+__device__ inline long long near_row(int pos, int tiles, int in_order)
+{
+    return in_order ? (long long)pos : (long long)(pos & (TILE - 1)) * tiles + (pos >> 7);
+}
+
+}  // namespace slhc

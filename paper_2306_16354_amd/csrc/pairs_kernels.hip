@@ -1,0 +1,632 @@
+// Passes over the pairs of ONE float16 copy, each pair of rows multiplied once.
+//
+// The distance of two rows does not depend on which of them asks, so where the queries are the candidates a product serves
+// both.  With h the stored half norms and acc = x_q . x_c - h_c the product value of the sweeps,
+//     u(q, c) = acc - h_q,   about minus half the squared distance,
+// is the same for both, up to rounding (see near_e), and a row's bound on product values becomes a limit on u by taking its own
+// half norm off.  A value is held against the limit of its query, a register, and against that of its candidate, which
+// comes through LDS with the candidate's norm.
+//
+// The copy is cut into blocks of consecutive tiles; block i meets the blocks i, i + 1, ... up to half way round the circle of
+// all blocks, so every pair of blocks meets once, every block has the same number of meetings, and a launch over a range of
+// these offsets has shown every row the same share of all others.
+#include <hip/hip_runtime.h>
+#include <stdint.h>
+#include "near_kernels.h"
+#include "near_parts.h"
+#include "pairs_kernels.h"
+
+namespace slhc {
+
+constexpr int QUEUE = 320;                 // pairs of a wavefront that wait for their slots in the rows' lists
+constexpr int PAIR_TILE_BITS = 17;         // of a tile's number in a queued pair
+
+// Pairs that pass wait in LDS until a wavefront's worth is there; then the limits of both rows are read at one tile, the pairs'
+// slots in the rows' lists are asked for at the next and used at the one after that, so nobody waits for memory.
+struct PairQueue {
+    uint2* at;                             // LDS, QUEUE entries
+    int n;                                 // waiting (the same for all lanes)
+    bool read, asked;                      // 64 pairs at the first and at the second step (the same for all lanes)
+    unsigned int u, code, u2, code2;       // of this lane's at the two steps
+    float q_limit, c_limit;
+    int q_slot, c_slot;
+};
+// A pair: tile and place of the candidate, place of the query among the wavefront's 64; bit 1: it is met in the other order too.
+constexpr unsigned int PAIR_OWN = 2u;
+__device__ inline unsigned int pair_code(int tile, int c, int q, bool own)
+{
+    return ((unsigned int)tile << 15) | ((unsigned int)c << 8) | ((unsigned int)q << 2) | (own ? PAIR_OWN : 0u);
+}
+// q0: position of the wavefront's first query
+__device__ inline int pair_q(unsigned int code, int q0) { return q0 + (int)((code >> 2) & 63u); }
+__device__ inline int pair_c(unsigned int code) { return (int)(code >> 15) * TILE + (int)((code >> 8) & 127u); }
+__device__ inline void pair_entry(const NearPairs& p, int row, int slot, unsigned int u, unsigned int other)
+{
+    if ((unsigned int)slot < (unsigned int)p.cap) p.entries[(size_t)row * (size_t)p.cap + (size_t)slot] = make_uint2(u, other);
+}
+// Every pair under way goes one step further, and where at least `least` wait the next ones set out.
+__device__ inline void pair_turn(PairQueue& w, const NearPairs& p, int q0, int least)
+{
+    const int lane = threadIdx.x & 63;
+    const bool more = w.n >= least && w.n > 0;
+    const int from = w.n > 64 ? w.n - 64 : 0;
+    uint2 e = make_uint2(0u, ~0u);
+    if (more && from + lane < w.n) e = w.at[from + lane];      // (before anything is under way in memory, see pair_push)
+    if (w.asked) {
+        const int q = pair_q(w.code2, q0), c = pair_c(w.code2);
+        pair_entry(p, q, w.q_slot, w.u2, (unsigned int)c);
+        pair_entry(p, c, w.c_slot, w.u2, (unsigned int)q);
+        w.asked = false;
+    }
+    if (w.read) {
+        const float u = __uint_as_float(w.u);
+        w.u2 = w.u; w.code2 = w.code;
+        w.q_slot = w.c_slot = -1;
+        if (u >= w.q_limit) w.q_slot = atomicAdd(p.counts + pair_q(w.code, q0), 1);
+        if (u >= w.c_limit) w.c_slot = atomicAdd(p.counts + pair_c(w.code), 1);
+        w.read = false;
+        w.asked = true;
+    }
+    if (!more) return;
+    w.u = e.x; w.code = e.y;
+    w.q_limit = w.c_limit = NEVER;
+    if (e.y != ~0u) {
+        w.q_limit = p.limit[pair_q(e.y, q0)];
+        if (!(e.y & PAIR_OWN)) w.c_limit = p.limit[pair_c(e.y)];
+    }
+    w.n = from;
+    w.read = true;
+}
+// The queue is empty when this returns.
+__device__ inline void pair_finish(PairQueue& w, const NearPairs& p, int q0)
+{
+#pragma unroll 1
+    while (w.n > 0 || w.read || w.asked) pair_turn(w, p, q0, 1);
+}
+
+// (Past the compiler, which would wait for the tile on its way into LDS before it writes there.  LDS instructions of a wavefront
+// are done in order.)
+__device__ inline void pair_push(uint2* at, unsigned int u, unsigned int code)
+{
+    const unsigned long long e = ((unsigned long long)code << 32) | u;
+    asm volatile("ds_write_b64 %0, %1" ::"v"((unsigned int)(uintptr_t)(__attribute__((address_space(3))) void*)at), "v"(e) : "memory");
+}
+
+// v[r], r < 16 by lane (in bits: from conditions the compiler makes an array in memory)
+__device__ inline float pair_value(const v16f& v, unsigned int r)
+{
+    unsigned int a[16];
+#pragma unroll
+    for (int i = 0; i < 16; ++i) a[i] = __float_as_uint(v[i]);
+#pragma unroll
+    for (int w = 8; w > 0; w >>= 1) {
+        const unsigned int take = 0u - (unsigned int)((r & (unsigned int)w) != 0u);
+#pragma unroll
+        for (int i = 0; i < w; ++i) a[i] = (a[w + i] & take) | (a[i] & ~take);
+    }
+    return __uint_as_float(a[0]);
+}
+
+// One 32 x 32 block of values.  limit: of this lane's 16 candidates; bound: the query's limit plus its half norm h; other: h, or
+// NaN where the block's pairs are met in both orders anyway.  code: of the lane's first candidate.
+// Where rows are few, every block holds something (20 000 x 128, k = 32: two or three pairs, 71 us for products and test and 80 for what
+// follows), so what follows the test has no branch per value (with one per value 90).
+__device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float bound, float h, float other, unsigned int code,
+                                 PairQueue& w, const NearPairs& p, int q0)
+{
+    float f = max3(v[0], v[1], v[2]), t = max3(v[0] - limit[0], v[1] - limit[1], v[2] - limit[2]);
+#pragma unroll
+    for (int r = 3; r < 15; r += 2) {
+        f = max3(f, v[r], v[r + 1]);
+        t = max3(t, v[r] - limit[r], v[r + 1] - limit[r + 1]);
+    }
+    f = fmaxf(f, v[15]);
+    t = fmaxf(t, v[15] - limit[15]);
+    if (!__any(f >= bound || t >= other)) return;
+    unsigned int bits = 0u;                                    // value r: bit 31 - r
+#pragma unroll
+    for (int r = 0; r < 16; ++r) bits = bits + bits + (v[r] >= bound || v[r] - limit[r] >= other ? 1u : 0u);
+    bits <<= 16;
+    unsigned long long m = __ballot(bits != 0u);
+    while (m) {
+        if (w.n > QUEUE - 64) pair_finish(w, p, q0);
+        const unsigned int r = (unsigned int)__clz((int)bits) & 15u;
+        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+        const float x = pair_value(v, r);
+        if (bits != 0u) pair_push(w.at + w.n + pre, __float_as_uint(x - h), code + ((((r & 12u) << 1) | (r & 3u)) << 8));
+        w.n += __popcll(m);
+        bits &= ~(0x80000000u >> r);
+        m = __ballot(bits != 0u);
+    }
+}
+
+// Which blocks a workgroup's block meets: offsets [from, from + len) in an order in which all blocks of one stretch of the circle
+// meet the same block at the same time, so that it is in L2.
+struct PairRange { int block, from, len, j0, j1, turn; };
+__device__ inline PairRange pair_range(const NearPairs& p, int item)
+{
+    PairRange r;
+    r.block = item / p.nseg;
+    const int seg = item - r.block * p.nseg;
+    // half way round an even circle two blocks meet from both sides
+    const int to = 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.block >= p.blocks ? p.to - 1 : p.to;
+    r.from = p.from;
+    r.len = to > p.from ? to - p.from : 0;
+    r.j0 = (int)((long long)r.len * seg / p.nseg);
+    r.j1 = (int)((long long)r.len * (seg + 1) / p.nseg);
+    r.turn = r.len > 0 ? r.len - r.block % r.len : 0;
+    return r;
+}
+__device__ inline int pair_offset(const PairRange& r, int j) { return r.from + (j + r.turn) % r.len; }
+__device__ inline int pair_other(const NearPairs& p, const PairRange& r, int offset)
+{
+    const int c = r.block + offset;
+    return c >= p.blocks ? c - p.blocks : c;
+}
+
+// Up to 128 columns: as near_sweep_kernel, a wavefront keeps the fragments of 64 queries in registers and the candidate tiles pass
+// through LDS (double buffered); a block is the tiles of a workgroup's queries.
+template <int KS>
+__global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
+{
+    extern __shared__ __align__(16) unsigned char pairs_smem[];
+    constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, limits
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int waves = blockDim.x >> 6, bt = waves >> 1;
+    const PairRange range = pair_range(p, blockIdx.x);
+    const int qtile = range.block * bt + (wave >> 1);
+    const bool live = qtile < p.tiles;                   // (whole wavefronts)
+    const int q0 = (live ? qtile : 0) * TILE + (wave & 1) * 64;
+    float h[2], bound[2];
+    v8h qf[2][KS];
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const int at = q0 + qb * 32 + l32;
+        h[qb] = live ? -p.negh[at] : NEVER;
+        bound[qb] = live ? p.limit[at] + h[qb] : NEVER;
+        const unsigned char* src = p.frag + (size_t)(at >> 7) * (KS * FRAG_STEP) + ((at >> 5) & 3) * 1024 + lane * 16;
+#pragma unroll
+        for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const v8h*>(src + ks * FRAG_STEP);
+    }
+    PairQueue w;
+    w.at = reinterpret_cast<uint2*>(pairs_smem + 2 * BUF) + wave * QUEUE;
+    w.n = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
+
+    const int total = (range.j1 - range.j0) * bt;        // tiles to pass over (some may not be there)
+    int step_j = range.j0, step_t = 0;                   // of the tile that is brought in next
+    int next_tile = 0;
+    bool next_own = false;
+    auto advance = [&]() {
+        const int off = pair_offset(range, step_j);
+        next_tile = pair_other(p, range, off) * bt + step_t;
+        next_own = off == 0;
+        if (++step_t == bt) { step_t = 0; ++step_j; }
+    };
+    auto stage = [&](int i, int tile) {
+        const size_t t = tile < p.tiles ? tile : p.tiles - 1;
+        unsigned char* dst = pairs_smem + (i & 1) * BUF;
+        const unsigned char* src = p.frag + t * (KS * FRAG_STEP);
+        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
+        for (int j = wave; j < 4; j += waves) {
+            const float* g = (j < 2 ? p.negh : p.limit) + t * TILE + (j & 1) * 64 + lane;
+            near_lds_load(g, dst + KS * FRAG_STEP + j * 256, false);
+        }
+    };
+    if (total > 0) { advance(); stage(0, next_tile); }
+    for (int i = 0; i < total; ++i) {
+        near_lds_ready();
+        const int tile = next_tile;
+        const bool own = next_own;
+        if (live) pair_turn(w, p, q0, 64);
+        if (i + 1 < total) { advance(); stage(i + 1, next_tile); }
+        if (tile >= p.tiles || !live) continue;
+        const unsigned char* tb = pairs_smem + (i & 1) * BUF;
+        const float other[2] = {own ? NEVER : h[0], own ? NEVER : h[1]};
+#pragma unroll 1
+        for (int half = 0; half < 2; ++half) {
+            v16f acc[2][2];
+            v8h cf[2][2];
+            const unsigned char* hb = tb + half * 2048 + lane * 16;
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(hb + cb * 1024);
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                v16f hv;
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
+                    hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
+                }
+                acc[0][cb] = hv; acc[1][cb] = hv;
+            }
+#pragma unroll
+            for (int ks = 0; ks < KS; ++ks) {
+                // (as in near_sweep_kernel: the next step's reads stay ahead of this step's multiplies)
+                if (ks + 1 < KS) {
+#pragma unroll
+                    for (int cb = 0; cb < 2; ++cb) cf[(ks + 1) & 1][cb] = *reinterpret_cast<const v8h*>(hb + (ks + 1) * FRAG_STEP + cb * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int cb = 0; cb < 2; ++cb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb)
+                        acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
+            }
+#pragma unroll
+            for (int cb = 0; cb < 2; ++cb) {
+                float limit[16];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + 512 + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) limit[4 * g + e] = t4[e];
+                }
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb)
+                    pair_emit(acc[qb][cb], limit, bound[qb], h[qb], other[qb], pair_code(tile, half * 64 + cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0);
+            }
+        }
+    }
+    if (live) pair_finish(w, p, q0);
+}
+
+// Beyond 128 columns: 256 x 256 rows per meeting, both sides streamed through LDS, as near_wide_kernel; a block is two tiles.
+//   BEST = false  pairs within either row's limit go to that row's list
+//   BEST = true   rows of another colour: every row's smallest w = max(0, -u), with the place of the 16 rows about it
+constexpr int WIDE_STEPS = 4;
+constexpr int WIDE_HALF = 2 * WIDE_STEPS * FRAG_STEP;                   // two tiles' steps: 32 KiB
+constexpr int WIDE_BUF = 2 * WIDE_HALF;
+constexpr int WIDE_ROWS = 3072;                                         // half norms, limits or smallest w, colours of 256 rows
+constexpr int WIDE_LDS = 2 * WIDE_BUF + 2 * WIDE_ROWS;
+
+template <bool BEST>
+__global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
+{
+    extern __shared__ __align__(16) unsigned char pairs_smem[];
+    const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int qg = wave >> 1, cg = wave & 1;                            // 64 queries, 128 candidates of the 256 x 256
+    int item = blockIdx.x;
+    {
+        // workgroups b, b + 8, ... share an XCD: they get the shares of neighbouring blocks, whose rows stay in its L2
+        const int items = p.blocks * p.nseg, per = items >> 3;
+        if (item < per * 8) item = (item & 7) * per + (item >> 3);
+    }
+    const PairRange range = pair_range(p, item);
+    const int qtile = range.block * 2 + (qg >> 1);
+    const bool live = qtile < p.tiles;
+    const int qsafe = live ? qtile : range.block * 2;
+    const int q0 = qsafe * TILE + (qg & 1) * 64;
+    float h[2], bound[2], m1[2] = {-INF, -INF};
+    int qcol[2] = {0, 0}, m1_at[2] = {-1, -1};
+#pragma unroll
+    for (int qb = 0; qb < 2; ++qb) {
+        const int at = q0 + qb * 32 + l32;
+        h[qb] = live ? -p.negh[at] : NEVER;
+        bound[qb] = NEVER;
+        if (BEST) qcol[qb] = p.colour[at];
+        else if (live) bound[qb] = p.limit[at] + h[qb];
+    }
+    PairQueue w;
+    w.at = reinterpret_cast<uint2*>(pairs_smem + WIDE_LDS) + wave * QUEUE;
+    w.n = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
+
+    const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
+    const int nmine = range.j1 - range.j0;
+    const int total = nmine * nchunks;
+    auto block_at = [&](int i) { return pair_other(p, range, pair_offset(range, range.j0 + i)); };
+    // the loads of step `at` (meeting, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the rows' words with chunk 0
+    auto stage = [&](int i, int block, int chunk, int at) {
+        unsigned char* dst = pairs_smem + (at & 1) * WIDE_BUF;
+#pragma unroll
+        for (int x = 0; x < 8; ++x) {
+            const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block of 32]
+            const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
+            const int b2 = (side ? block : range.block) * 2;
+            const size_t t = b2 + tile < p.tiles ? b2 + tile : b2;
+            const unsigned char* src = p.frag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16;
+            near_lds_load(src, dst + piece * 1024, true);
+        }
+        if (chunk == 0) {
+            unsigned char* rows = pairs_smem + 2 * WIDE_BUF + (i & 1) * WIDE_ROWS;
+            for (int piece = wave; piece < (BEST ? 12 : 8); piece += 8) {
+                const int what = piece >> 2, tile = (piece >> 1) & 1, half = piece & 1;
+                const size_t t = block * 2 + tile < p.tiles ? block * 2 + tile : block * 2;
+                const size_t r = t * TILE + half * 64 + lane;
+                const void* g = what == 0 ? (const void*)(p.negh + r)
+                              : what == 2 ? (const void*)(p.colour + r)
+                              : BEST ? (const void*)(reinterpret_cast<const uint32_t*>(p.best + r) + 1) : (const void*)(p.limit + r);
+                near_lds_load(g, rows + piece * 256, false);
+            }
+        }
+    };
+    int block = nmine > 0 ? block_at(0) : 0;
+    if (total > 0) stage(0, block, 0, 0);
+    int at = 0;
+    for (int i = 0; i < nmine; ++i) {
+        const unsigned char* rows = pairs_smem + 2 * WIDE_BUF + (i & 1) * WIDE_ROWS;
+        const bool own = block == range.block;
+        const int tile = block * 2 + cg;
+        const int next = i + 1 < nmine ? block_at(i + 1) : block;
+        v16f acc[2][4];                                                 // [query block][candidate block]
+        auto step = [&]() {
+            const unsigned char* qs = pairs_smem + (at & 1) * WIDE_BUF + (qg >> 1) * (WIDE_STEPS * FRAG_STEP) + (qg & 1) * 2048 + lane * 16;
+            const unsigned char* cs = pairs_smem + (at & 1) * WIDE_BUF + WIDE_HALF + cg * (WIDE_STEPS * FRAG_STEP) + lane * 16;
+            v8h qf[2][2], cf[2][4];
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb) qf[0][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
+#pragma unroll
+            for (int st = 0; st < WIDE_STEPS; ++st) {
+                if (st + 1 < WIDE_STEPS) {
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) qf[(st + 1) & 1][qb] = *reinterpret_cast<const v8h*>(qs + (st + 1) * FRAG_STEP + qb * 1024);
+#pragma unroll
+                    for (int cb = 0; cb < 4; ++cb) cf[(st + 1) & 1][cb] = *reinterpret_cast<const v8h*>(cs + (st + 1) * FRAG_STEP + cb * 1024);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+#pragma unroll
+                for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb)
+                        acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st & 1][cb], qf[st & 1][qb], acc[qb][cb], 0, 0, 0);
+            }
+        };
+        near_lds_ready();
+        if (!BEST) { if (live) pair_turn(w, p, q0, 64); }
+        if (at + 1 < total) stage(nchunks > 1 ? i : i + 1, nchunks > 1 ? block : next, nchunks > 1 ? 1 : 0, at + 1);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) {
+            v16f hv;
+#pragma unroll
+            for (int g = 0; g < 4; ++g) {
+                const v4f t4 = *reinterpret_cast<const v4f*>(rows + cg * 512 + (cb * 32 + 8 * g + 4 * lhalf) * 4);
+                hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
+            }
+            acc[0][cb] = hv; acc[1][cb] = hv;
+        }
+        step();
+        ++at;
+        for (int chunk = 1; chunk < nchunks; ++chunk, ++at) {
+            near_lds_ready();
+            if (at + 1 < total) {
+                const bool wrap = chunk + 1 == nchunks;
+                stage(wrap ? i + 1 : i, wrap ? next : block, wrap ? 0 : chunk + 1, at + 1);
+            }
+            step();
+        }
+        if (live && tile < p.tiles) {
+#pragma unroll
+            for (int cb = 0; cb < 4; ++cb) {
+                float limit[16];
+                int col[16];
+#pragma unroll
+                for (int g = 0; g < 4; ++g) {
+                    const unsigned char* word = rows + 1024 + cg * 512 + (cb * 32 + 8 * g + 4 * lhalf) * 4;
+                    const v4f t4 = *reinterpret_cast<const v4f*>(word);
+#pragma unroll
+                    for (int e = 0; e < 4; ++e) limit[4 * g + e] = t4[e];
+                    if (BEST) {
+                        const v4i c4 = *reinterpret_cast<const v4i*>(word + 1024);
+#pragma unroll
+                        for (int e = 0; e < 4; ++e) col[4 * g + e] = c4[e];
+                    }
+                }
+#pragma unroll
+                for (int qb = 0; qb < 2; ++qb) {
+                    if (!BEST) {
+                        pair_emit(acc[qb][cb], limit, bound[qb], h[qb], own ? NEVER : h[qb],
+                                  pair_code(tile, cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0);
+                        continue;
+                    }
+                    v16f& v = acc[qb][cb];
+                    float best = -INF, gain = -INF;
+#pragma unroll
+                    for (int r = 0; r < 16; ++r) {
+                        v[r] = col[r] == qcol[qb] ? -INF : v[r];
+                        best = fmaxf(best, v[r]);
+                        gain = fmaxf(gain, v[r] + limit[r]);
+                    }
+                    const bool up = best > m1[qb];
+                    m1_at[qb] = up ? tile * TILE + cb * 32 + 4 * lhalf : m1_at[qb];
+                    m1[qb] = up ? best : m1[qb];
+                    // (values seen by another workgroup meanwhile only make an update idle)
+                    if (p.both && !own && __any(gain > h[qb])) {
+                        const unsigned int q_at = (unsigned int)(q0 + qb * 32 + (l32 & 4));
+#pragma unroll
+                        for (int r = 0; r < 16; ++r)
+                            if (v[r] + limit[r] > h[qb])
+                                atomicMin(p.best + (size_t)tile * TILE + cb * 32 + 8 * (r >> 2) + 4 * lhalf + (r & 3),
+                                          ((unsigned long long)__float_as_uint(fmaxf(0.f, h[qb] - v[r])) << 32) | q_at);
+                    }
+                }
+            }
+        }
+        block = next;
+    }
+    if (!live) return;
+    if (!BEST) pair_finish(w, p, q0);
+    else {
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb)
+            if (m1_at[qb] >= 0 && fabsf(h[qb]) < INF && fabsf(m1[qb]) < INF)
+                atomicMin(p.best + q0 + qb * 32 + l32, ((unsigned long long)__float_as_uint(fmaxf(0.f, h[qb] - m1[qb])) << 32) | (unsigned int)m1_at[qb]);
+    }
+}
+
+// (Nearly) the kk-th largest of the first n values of a row's list, in `mine`; LOWEST where fewer are finite.
+constexpr int PAIR_WORDS = PAIRS_MOST / 64;
+__device__ inline void pair_list(uint2 (&mine)[PAIR_WORDS], const uint2* __restrict__ list, int n)
+{
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int j = 0; j < PAIR_WORDS; ++j) {
+        mine[j] = make_uint2(__float_as_uint(-INF), 0u);
+        if (j * 64 + lane < n) mine[j] = list[j * 64 + lane];
+    }
+}
+__device__ inline float pair_kth(const uint2 (&mine)[PAIR_WORDS], int n, int kk)
+{
+    float lo = INF, hi = -INF;
+    int have = 0;
+#pragma unroll
+    for (int j = 0; j < PAIR_WORDS; ++j)
+        if (j * 64 < n) {
+            const float x = __uint_as_float(mine[j].x);
+            const bool fine = fabsf(x) < INF;
+            have += __popcll(__ballot(fine));
+            lo = fine ? fminf(lo, x) : lo;
+            hi = fine ? fmaxf(hi, x) : hi;
+        }
+    if (have < kk) return LOWEST;
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    for (int it = 0; it < BISECT_FAR; ++it) {
+        const float mid = 0.5f * lo + 0.5f * hi;
+        int reach = 0;
+#pragma unroll
+        for (int j = 0; j < PAIR_WORDS; ++j)
+            if (j * 64 < n) {
+                const float x = __uint_as_float(mine[j].x);
+                reach += __popcll(__ballot(x >= mid && x < INF));
+            }
+        if (reach >= kk) lo = mid; else hi = mid;
+        if (reach == kk) break;
+    }
+    return lo;
+}
+
+// Between two launches: of what a row's list holds, kk rows reach the kk-th value; what that leaves is kept, and the row's limit
+// follows.  One wavefront per row; bound by reading and writing the lists.
+__global__ void __launch_bounds__(256) pairs_tighten_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d)
+{
+    const int row = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (row >= p.tiles * TILE) return;
+    const int n = p.counts[row];
+    if (n > p.cap) {                                                    // some were lost: nothing more (see pairs_left)
+        if (lane == 0) { p.counts[row] = p.cap + 1; p.limit[row] = NEVER; }
+        return;
+    }
+    const float h = -p.negh[row];
+    if (n <= kk || !(fabsf(h) < INF)) return;
+    uint2* list = p.entries + (size_t)row * (size_t)p.cap;
+    uint2 mine[PAIR_WORDS];
+    pair_list(mine, list, n);
+    const float kth = pair_kth(mine, n, kk);
+    if (kth == LOWEST) return;
+    const NearBoundArgs a = near_args(sc, p.steps, d, e, nu);
+    const float limit = near_bound_from(kth + h, h, a) - h;
+    if (!(limit > p.limit[row])) return;
+    int kept = 0;
+#pragma unroll
+    for (int j = 0; j < PAIR_WORDS; ++j)
+        if (j * 64 < n) {
+            const bool keep = j * 64 + lane < n && __uint_as_float(mine[j].x) >= limit;
+            const unsigned long long m = __ballot(keep);
+            const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+            if (keep) list[kept + pre] = mine[j];
+            kept += __popcll(m);
+        }
+    if (lane == 0) { p.counts[row] = kept; p.limit[row] = limit; }
+}
+
+// an upper end of the squared distance (of the rows as they are) behind a product value
+__device__ inline float pair_reach(float value, float h, const NearBoundArgs& a, const NearScale* sc, int d)
+{
+    const float t = value > LOWEST ? near_distance_from(value, h, a) / sc->scale : INF;
+    return (t * t * (1.f + a.gamma) + (float)d * 2.350988701644575e-38f) * (1.f + 1e-6f);
+}
+__global__ void __launch_bounds__(256) pairs_left_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int n_rows,
+                                                         PairsLeft out)
+{
+    const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (pos >= p.tiles * TILE || p.counts[pos] <= p.cap) return;
+    const float h = -p.negh[pos];
+    const long long row = near_row(pos, p.tiles, 0);
+    if (!(fabsf(h) < INF) || row >= n_rows) return;
+    uint2 mine[PAIR_WORDS];
+    pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
+    const float kth = pair_kth(mine, p.cap, kk);
+    if (lane != 0) return;
+    const int i = atomicAdd(out.count, 1);
+    out.row[i] = (int)row; out.pos[i] = pos; out.counts[i] = 0;
+    out.reach[i] = pair_reach(kth == LOWEST ? LOWEST : kth + h, h, near_args(sc, p.steps, d, e, nu), sc, d);
+    p.counts[pos] = 0;
+}
+__global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int first, int n,
+                                                          PairsLeft left)
+{
+    const int i = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    if (i >= n || first + i >= *left.count) return;
+    const int at = first + i;
+    if (left.counts[at] <= p.cap) {
+        if (lane == 0) left.reach[at] = -1.f;
+        return;
+    }
+    const float h = -p.negh[left.pos[at]];
+    uint2 mine[PAIR_WORDS];
+    pair_list(mine, p.entries + (size_t)i * (size_t)p.cap, p.cap);
+    const float kth = pair_kth(mine, p.cap, kk);
+    if (lane != 0) return;
+    left.counts[at] = 0;
+    left.reach[at] = fminf(left.reach[at], pair_reach(kth, h, near_args(sc, p.steps, d, e, nu), sc, d));
+}
+
+// ---------------------------------------------------------------------------------------------- launches
+hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
+{
+    if (p.tiles < 1 || p.tiles >= (1 << PAIR_TILE_BITS) || p.cap < 1 || p.cap > PAIRS_MOST || p.nseg < 1) return hipErrorInvalidValue;
+    const bool wide = p.steps > REG_STEPS;
+    const int bt = wide ? 2 : waves / 2;
+    if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > p.blocks / 2 + 1) return hipErrorInvalidValue;
+    const dim3 grid((unsigned)(p.blocks * p.nseg)), block((unsigned)(64 * (wide ? 8 : waves)));
+    const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024)) + (size_t)(wide ? 8 : waves) * QUEUE * 8;
+    auto run = [&](auto kernel) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, grid, block, lds, s, p);
+        return hipGetLastError();
+    };
+    if (wide) return run(&pairs_wide_kernel<false>);
+    switch (p.steps) {
+        case 3: return run(&pairs_kernel<3>);
+        case 4: return run(&pairs_kernel<4>);
+        case 5: return run(&pairs_kernel<5>);
+        case 6: return run(&pairs_kernel<6>);
+        case 7: return run(&pairs_kernel<7>);
+        case 8: return run(&pairs_kernel<8>);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t pairs_best(const NearPairs& p, hipStream_t s)
+{
+    if (p.tiles < 1 || p.steps <= REG_STEPS || p.nseg < 1 || p.blocks != (p.tiles + 1) / 2 || p.from < 0 || p.to > p.blocks) return hipErrorInvalidValue;
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pairs_wide_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, WIDE_LDS);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL((pairs_wide_kernel<true>), dim3((unsigned)(p.blocks * p.nseg)), dim3(512), WIDE_LDS, s, p);
+    return hipGetLastError();
+}
+
+hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, hipStream_t s)
+{
+    hipLaunchKernelGGL(pairs_tighten_kernel, dim3((unsigned)(p.tiles * (TILE / 4))), dim3(256), 0, s, p, kk, sc, e, nu, d);
+    return hipGetLastError();
+}
+
+hipError_t pairs_left(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int n_rows, const PairsLeft& out, hipStream_t s)
+{
+    hipLaunchKernelGGL(pairs_left_kernel, dim3((unsigned)(p.tiles * (TILE / 4))), dim3(256), 0, s, p, kk, sc, e, nu, d, n_rows, out);
+    return hipGetLastError();
+}
+
+hipError_t pairs_again(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int first, int n, const PairsLeft& left, hipStream_t s)
+{
+    hipLaunchKernelGGL(pairs_again_kernel, dim3((unsigned)((n + 3) / 4)), dim3(256), 0, s, p, kk, sc, e, nu, d, first, n, left);
+    return hipGetLastError();
+}
+
+}  // namespace slhc

@@ -598,9 +598,9 @@ struct NearWs {
     // `most`: where the workspace ends; the batch takes what is left of it, and where that is too little there is no engine
     // and nothing of it in the layout (ok stays false)
     // `ordered`: rows of a padded row order that is searched too (0: none)
-    // `lent`: memory for the copy of the queries that the layout has anyway
+    // `lent`: memory for the copy of the queries that the layout has anyway; `spare`: for the lists of all rows
     void carve(Carver& w, int64_t nc, int64_t nq, int32_t d, int32_t kk, bool coloured, size_t most = NO_LIMIT, int64_t ordered = 0,
-               const slhc::NearCopy* lent = nullptr)
+               const slhc::NearCopy* lent = nullptr, unsigned char* spare = nullptr, size_t spare_bytes = 0)
     {
         const size_t begin = w.off;
         auto copy = [&](slhc::NearCopy& x, int64_t n, bool queries) {
@@ -636,6 +636,10 @@ struct NearWs {
             b.batch_bytes = std::max({b.batch_bytes, slhc::near_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
             least = std::max({least, slhc::near_least_ordered_batch_bytes(ordered, kk), slhc::near_linked_batch_bytes(ordered)});
         }
+        // The lists of a search that multiplies every pair once: in the batch's memory, in the spare one, or, where neither holds
+        // them, in a batch that may grow to the size of the rows for it.
+        const size_t pairs = slhc::near_pairs_bytes(nc, d, kk);
+        if (pairs > b.batch_bytes && pairs > spare_bytes && pairs <= (size_t)nc * (size_t)d * sizeof(float)) b.batch_bytes = up(pairs);
         const size_t room = most > w.off ? (most - w.off) / ALIGN * ALIGN : 0;
         if (b.batch_bytes > room) b.batch_bytes = room;
         if (b.batch_bytes < least) {
@@ -644,6 +648,8 @@ struct NearWs {
             return;
         }
         b.batch = w.take<unsigned char>(b.batch_bytes);
+        b.pairs = b.batch; b.pairs_bytes = b.batch_bytes;
+        if (pairs > b.batch_bytes) { b.pairs = spare; b.pairs_bytes = spare_bytes; }
         ok = true;
     }
 };
@@ -667,6 +673,7 @@ struct OrderWs {
     bool near_searched;               // near_all, near_local, near_colour and local_scale exist
     void* sort_temp; size_t sort_temp_bytes;
     void* nested_ws; size_t nested_bytes;      // of the clustering of the pivots, which keeps within it
+    unsigned char* spare; size_t spare_bytes;  // what a call that makes no order may use
     int P1, Pmax, Tmax;
     int64_t Nmax;
     int P = 0;        // pivots in use          (set by build_order)
@@ -731,6 +738,8 @@ struct OrderWs {
         sort_temp_bytes = slhc::pair_sort_temp_bytes((int)N);
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
         n_src = c.take<int32_t>(pm); n_dst = c.take<int32_t>(pm); n_w = c.take<float>(pm);
+        spare = c.base ? c.base + copies_begin : nullptr;
+        spare_bytes = c.off - copies_begin;
     }
     // Memory of a copy of listed rows: that of the copy in this order, which is made later and no longer used when the
     // connection rounds come to make one.
@@ -811,7 +820,8 @@ private:
         if (with_near) {
             const bool searched = has_order && order.near_searched;
             const slhc::NearCopy lent = searched ? order.lent_copy() : slhc::NearCopy{};
-            near.carve(c, N, connect || has_order ? N : 0, d, k + 1, connect, most, searched ? order.Nmax : 0, searched ? &lent : nullptr);
+            near.carve(c, N, connect || has_order ? N : 0, d, k + 1, connect, most, searched ? order.Nmax : 0, searched ? &lent : nullptr,
+                       has_order ? order.spare : nullptr, has_order ? order.spare_bytes : 0);
         }
         bytes = c.off;
     }

@@ -1,0 +1,81 @@
+"""Searches that multiply every pair of rows once (pairs_kernels.hip): lists and trees against the float32-product list kernels,
+bit for bit, where blocks, offsets round the circle, bands and lists end."""
+import numpy as np
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2306_16354_amd as slhc
+    slhc.load_library()
+    assert torch.cuda.is_available()
+    return slhc
+
+
+def blobs(N, d, seed, spread=8.0, rows=400):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    centres = (2 * torch.rand((max(2, N // rows), d), generator=g, device="cuda") - 1) * spread
+    label = torch.randint(len(centres), (N,), generator=g, device="cuda")
+    return centres[label] + torch.randn((N, d), generator=g, device="cuda")
+
+
+# the smallest search of its kind and one row less and more; an odd and an even circle of blocks, the last of one to four tiles;
+# every number of 16-column steps; whole and partial chunks beyond 128 columns; lists from 128 entries to 1024; one to several bands
+@pytest.mark.parametrize("N,d,k", [
+    (3968, 33, 8), (3969, 33, 8), (4096, 48, 1), (4097, 49, 64), (4609, 64, 15), (5120, 65, 31), (6001, 81, 7), (7000, 97, 3), (8191, 113, 16),
+    (9000, 128, 33), (9217, 128, 2), (4100, 129, 5), (4353, 192, 64), (5000, 321, 20), (12_545, 784, 9), (30_011, 50, 10), (50_000, 40, 50), (150_000, 64, 24),
+    (70_000, 200, 12), (200_000, 128, 40),
+])
+def test_lists(lib, N, d, k):
+    print(f"pairs once N={N} d={d} k={k}", flush=True)
+    X = blobs(N, d, N + d)
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
+# values beyond float16 on either side of a pair, rows with more ties than a list holds, one row that no other is near, rows in the
+# order of their clusters
+@pytest.mark.parametrize("kind", ["beyond_float16", "ties", "far_row", "sorted", "not_finite"])
+@pytest.mark.parametrize("N,d,k", [(5000, 64, 12), (4500, 160, 12)])
+def test_lists_of_unlike_rows(lib, kind, N, d, k):
+    print(f"pairs once, {kind}, N={N} d={d}", flush=True)
+    X = blobs(N, d, 7)
+    if kind == "beyond_float16":
+        X[::600] *= 1e7
+    elif kind == "ties":
+        X[::3] = X[0]
+    elif kind == "far_row":
+        X[N // 2] += 1e4
+    elif kind == "sorted":
+        X = X[torch.argsort(X[:, 0])].contiguous()
+    elif kind == "not_finite":
+        X[N // 3] = float("nan")
+        X[N // 5, 2] = float("inf")
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
+    if kind == "not_finite":
+        rows = torch.ones(N, dtype=torch.bool, device="cuda")
+        rows[N // 3] = rows[N // 5] = False
+        assert torch.equal(want[0][rows], got[0][rows]) and torch.equal(want[1][rows], got[1][rows])
+        return
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
+# the first connection round asks for most rows; few and many components, copies, a far row
+@pytest.mark.parametrize("kind", ["clusters", "pairs", "copies", "far_row"])
+@pytest.mark.parametrize("N,d", [(4097, 130), (6000, 256), (20_001, 300)])
+def test_trees(lib, kind, N, d):
+    print(f"pairs once, trees, {kind}, N={N} d={d}", flush=True)
+    X = blobs(N, d, N, spread=30.0, rows=N // 8 if kind != "pairs" else 3)
+    if kind == "copies":
+        X = X[torch.arange(N, device="cuda") // 30].contiguous()
+    if kind == "far_row":
+        X[N // 3] *= 1e5
+    want, got = lib.slhc(X, 4, prune=False, fp32_filter=True), lib.slhc(X, 4, prune=False)
+    torch.cuda.synchronize()
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
