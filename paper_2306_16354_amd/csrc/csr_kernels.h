@@ -1,0 +1,45 @@
+// Launch interface of the spanning forest of a CSR graph (csr_kernels.hip).
+#pragma once
+#include <hip/hip_runtime.h>
+#include <stddef.h>
+#include <stdint.h>
+
+namespace slhc {
+
+// words: active vertices and roots of a round, three in turn; the number, from 1 on, of a round whose hooks are not followed to
+// their end; edges; the first failed check
+enum { CSR_ACTIVE = 0, CSR_ROOTS = 3, CSR_CHAINS = 6, CSR_EDGES = 7, CSR_ERROR = 8, CSR_FLAG = 9 };
+struct CsrForest {
+    const int32_t *offsets, *indices; const float* weights; int V, E;
+    int32_t *colour, *hook;                    // [V]
+    int32_t* cand_u; float* cand_w;            // [V] an active vertex's first edge out of its component
+    uint32_t* best_w[2]; unsigned long long* best_e[2];      // [V] by root, of even and odd rounds
+    int32_t *active[2], *roots[2];             // [V] lists, likewise
+    int32_t *e_lo, *e_hi; float* e_w;          // [V - 1]
+    int32_t* words;                            // [64]
+};
+// Round 0: the input check and every vertex's lightest edge.
+hipError_t csr_start(const CsrForest& f, hipStream_t s);
+// Round 1, 2, ... for at most so many active vertices and roots.  On the way host[0 .. 3] get what round - 1 left: active vertices, edges
+// so far, the word of hooks not followed to their end (nothing is done then), the first failed check, each in the low half of a word with
+// `seq` above it.
+constexpr int CSR_TOLD = 4;
+hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s);
+// All rounds from `round` on; host[0] gets the rounds there were in all.  For at most CSR_TAIL active vertices.
+constexpr int CSR_TAIL = 2048;
+hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uint32_t seq, hipStream_t s);
+hipError_t csr_follow_again(const CsrForest& f, int round, int vertices, hipStream_t s);
+hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s);
+
+// Edges by (weight, smaller end, larger end); *flag is set where they have to be sorted by edge_sort instead.
+struct CsrSortScratch {
+    int32_t *count, *offset;                   // [V + 1]
+    int32_t* rank;                             // [E]
+    uint32_t *wbits_a, *wbits_b; unsigned long long *ends_a, *ends_b;        // [E]
+    void* temp; size_t temp_bytes;
+};
+bool csr_sort_fits(int V, int E, size_t temp_bytes);
+hipError_t csr_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w,
+                    int32_t* flag, hipStream_t s);
+
+}  // namespace slhc

@@ -1,0 +1,458 @@
+// Spanning forest of a CSR graph (cuSLINK paper Sec. 3.2, Alg. "MST Algorithm"): the rounds of forest_kernels.hip, same rules and
+// same edges, for a graph whose rows are its neighbour lists.
+//
+// A round only looks at what is left of the graph: the vertices that had an edge out of their component in the round before
+// and the roots of components that had one, both kept as lists.  Components only grow, so a vertex without such an edge never
+// has one again; its colour is complemented, which tells its neighbours, all in its own component, without being kept up to date.
+// (Walking up from stale colours instead: two random reads per entry where one does, 610 us of scans.)
+// What bounds it: random 4-byte reads in the first four rounds (380 us), then the chain of dependent reads and the end of every launch
+// (30 us a round, whatever is left of the graph).  Road-like graph of 1 048 576 vertices and 2.6 million entries: rounds over all
+// vertices 750 us, over the lists 580.
+#include <hip/hip_runtime.h>
+#include <cstring>
+#include <rocprim/rocprim.hpp>
+#include <stdint.h>
+#include "csr_kernels.h"
+#include "wave_ops.h"
+
+namespace slhc {
+
+constexpr uint32_t INF_BITS = 0x7f800000u;
+constexpr int TB = 256, WIDE = 1024;      // (WIDE: kernels that append to a list, one atomic per workgroup)
+constexpr int FOLLOW_STEPS = 64;       // hooks followed in one launch
+static inline int blocks_for(long long n, int threads = TB) { return (int)((n + threads - 1) / threads); }
+static inline int append_blocks(long long n) { const int b = blocks_for(n < 1 ? 1 : n, WIDE); return b > 512 ? 512 : b; }
+
+__device__ inline bool in_range(int i, int n) { return (unsigned int)i < (unsigned int)n; }
+__device__ inline void report(const CsrForest& f, int site) { atomicCAS(f.words + CSR_ERROR, 0, site); }
+// a failed check, or hooks that are not followed to their end yet, leave all rounds enqueued to the host
+__device__ inline bool halted(const CsrForest& f) { return (f.words[CSR_ERROR] | f.words[CSR_CHAINS]) != 0; }
+
+// The edge of v's row out of component c that is first in the order (weight, smaller end, larger end).  One thread per vertex: road-like
+// graphs have two or three edges per vertex (a row with thousands is scanned by one thread: correct, slow).
+template <bool FIRST>
+__device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits)
+{
+    int o0 = f.offsets[v], o1 = f.offsets[v + 1];
+    if (FIRST) {
+        if (o0 < 0 || o1 < o0 || o1 > f.E) report(f, 20);
+        if (v == 0 && o0 != 0) report(f, 21);
+        if (v == f.V - 1 && o1 != f.E) report(f, 22);
+    }
+    o0 = o0 < 0 ? 0 : o0;
+    o1 = o1 > f.E ? f.E : o1;
+    uint32_t best = INF_BITS;
+    unsigned int lo = ~0u, hi = ~0u;
+    int to = -1;
+    // (four entries side by side: their loads wait for memory together)
+    for (int e0 = o0; e0 < o1; e0 += 4) {
+        int u[4], cu[4];
+        float w[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            u[j] = e0 + j < o1 ? f.indices[e0 + j] : -1;
+            w[j] = e0 + j < o1 ? f.weights[e0 + j] : 0.f;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (FIRST) {
+                if (e0 + j < o1 && !in_range(u[j], f.V)) report(f, 23);
+                if (!(w[j] >= 0.f) || w[j] == __builtin_inff()) report(f, 24);
+                cu[j] = u[j];
+            } else cu[j] = in_range(u[j], f.V) ? *reinterpret_cast<volatile int32_t*>(f.colour + u[j]) : -1;
+        }
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            if (!in_range(u[j], f.V) || cu[j] < 0 || cu[j] == c) continue;
+            const uint32_t wb = __float_as_uint(w[j]);
+            const unsigned int l = (unsigned int)(v < u[j] ? v : u[j]), h = (unsigned int)(v < u[j] ? u[j] : v);
+            if (wb < best || (wb == best && (l < lo || (l == lo && h < hi)))) { best = wb; lo = l; hi = h; to = u[j]; }
+        }
+    }
+    *wbits = best;
+    return to;
+}
+
+// Round 0: every vertex is a component.
+__global__ void __launch_bounds__(WIDE) k_csr_first(CsrForest f)
+{
+    for (long long base = (long long)blockIdx.x * WIDE; base < f.V; base += (long long)gridDim.x * WIDE) {
+        const long long v = base + threadIdx.x;
+        int u = -1;
+        uint32_t w = INF_BITS;
+        if (v < f.V) {
+            u = row_edge<true>(f, (int)v, (int)v, &w);
+            const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
+            f.colour[v] = (int)v;
+            f.hook[v] = (int)v;
+            f.cand_u[v] = u;
+            f.cand_w[v] = __uint_as_float(w);
+            f.best_w[0][v] = w;
+            f.best_w[1][v] = INF_BITS;
+            f.best_e[0][v] = u < 0 ? ~0ull : ((unsigned long long)lo << 32) | hi;
+            f.best_e[1][v] = ~0ull;
+        }
+        const int at = block_append<WIDE>(u >= 0, f.words + CSR_ACTIVE + 1);
+        if (u >= 0) f.active[1][at] = (int)v;
+        __syncthreads();
+    }
+}
+
+// Round r: the active vertices' edges, and the weight of every component's lightest.  Also tells the host how the round before
+// ended, in words that carry `seq` each (so no fence has to stand between them and one number for all).
+__global__ void __launch_bounds__(WIDE) k_csr_scan(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
+{
+    if (blockIdx.x == 0 && threadIdx.x < CSR_TOLD) {
+        const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR};
+        __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | (unsigned int)f.words[at[threadIdx.x]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (halted(f)) return;
+    const int n = f.words[CSR_ACTIVE + round % 3];
+    const int32_t* from = f.active[round & 1];
+    int32_t* to = f.active[(round + 1) & 1];
+    uint32_t* best_w = f.best_w[round & 1];
+    for (long long base = (long long)blockIdx.x * WIDE; base < n; base += (long long)gridDim.x * WIDE) {
+        const long long i = base + threadIdx.x;
+        int v = -1, u = -1, c = 0;
+        uint32_t w = INF_BITS;
+        if (i < n) {
+            v = from[i];
+            c = f.colour[v];
+            if (!in_range(c, f.V)) { report(f, 11); c = 0; }
+            else u = row_edge<false>(f, v, c, &w);
+            if (u >= 0) {
+                f.cand_u[v] = u;
+                f.cand_w[v] = __uint_as_float(w);
+            } else f.colour[v] = ~c;
+        }
+        wave_min_into(best_w, c, w, u >= 0);
+        const int at = block_append<WIDE>(u >= 0, f.words + CSR_ACTIVE + (round + 1) % 3);
+        if (u >= 0) to[at] = v;
+        __syncthreads();
+    }
+}
+
+// ... and which of the edges of that weight it is
+__global__ void __launch_bounds__(TB) k_csr_select(CsrForest f, int round)
+{
+    if (halted(f)) return;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        f.words[CSR_ACTIVE + (round + 2) % 3] = 0;
+        f.words[CSR_ROOTS + (round + 2) % 3] = 0;
+    }
+    const int n = f.words[CSR_ACTIVE + (round + 1) % 3];
+    const int32_t* list = f.active[(round + 1) & 1];
+    for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n; i += (long long)gridDim.x * TB) {
+        const int v = list[i], u = f.cand_u[v], c = f.colour[v];
+        if (__float_as_uint(f.cand_w[v]) != f.best_w[round & 1][c]) continue;
+        const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
+        min_into(&f.best_e[round & 1][c], ((unsigned long long)lo << 32) | hi);
+    }
+}
+
+// One thread per root: append the component's edge (once per undirected edge) and hook it to the component at the other end.  Two
+// that chose the same edge keep the smaller root; roots that stay get cleared minima for the next round.
+__global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
+{
+    if (halted(f)) return;
+    const int n = round == 0 ? f.V : f.words[CSR_ROOTS + round % 3];
+    const int32_t* from = f.roots[round & 1];
+    int32_t* to = f.roots[(round + 1) & 1];
+    const uint32_t* best_w = f.best_w[round & 1];
+    const unsigned long long* best_e = f.best_e[round & 1];
+    for (long long base = (long long)blockIdx.x * WIDE; base < n; base += (long long)gridDim.x * WIDE) {
+        const long long i = base + threadIdx.x;
+        bool adds = false, stays = false;
+        int c = 0, lo = 0, hi = 0;
+        uint32_t w = INF_BITS;
+        if (i < n) {
+            c = round == 0 ? (int)i : from[i];
+            w = best_w[c];
+            if (w != INF_BITS) {                                   // (else: a finished tree)
+                const unsigned long long e = best_e[c];
+                lo = (int)(e >> 32); hi = (int)(e & 0xffffffffull);
+                int other = -1;
+                if (!in_range(lo, f.V) || !in_range(hi, f.V)) report(f, 8);
+                else {
+                    const int cl = f.colour[lo], ch = f.colour[hi];        // (both are active)
+                    other = cl == c ? ch : (ch == c ? cl : -1);
+                    if (!in_range(other, f.V) || other == c) { report(f, 9); other = -1; }
+                }
+                if (other >= 0) {
+                    const bool mutual = best_w[other] == w && best_e[other] == e;
+                    adds = !mutual || c < other;
+                    stays = mutual && c < other;
+                    if (!stays) f.hook[c] = other;
+                }
+            }
+        }
+        const int slot = block_append<WIDE>(adds, f.words + CSR_EDGES);
+        if (adds && slot < f.V - 1) { f.e_lo[slot] = lo; f.e_hi[slot] = hi; f.e_w[slot] = __uint_as_float(w); }
+        __syncthreads();
+        const int at = block_append<WIDE>(stays, f.words + CSR_ROOTS + (round + 1) % 3);
+        if (stays) { to[at] = c; f.best_w[(round + 1) & 1][c] = INF_BITS; f.best_e[(round + 1) & 1][c] = ~0ull; }
+        __syncthreads();
+    }
+}
+
+// Active vertex v takes the root at the end of its component's hooks as its colour and shortens the way for the others; false where
+// that is more than FOLLOW_STEPS away: the colour it has then is one to go on from.
+__device__ inline bool follow(const CsrForest& f, int v, bool again)
+{
+    const int c = f.colour[v];
+    int r = c;
+    bool end = false;
+    for (int s = 0; s < FOLLOW_STEPS && !end; ++s) {
+        if (!in_range(r, f.V)) { report(f, 13); return true; }
+        const int h = *reinterpret_cast<volatile int32_t*>(f.hook + r);
+        end = h == r;
+        r = h;
+    }
+    if (r != c) {
+        f.colour[v] = r;
+        if (end || again) f.hook[c] = r;
+    }
+    return end;
+}
+__global__ void __launch_bounds__(TB) k_csr_follow(CsrForest f, int round, int again)
+{
+    if (f.words[CSR_ERROR] != 0 || (!again && f.words[CSR_CHAINS] != 0)) return;
+    const int n = f.words[CSR_ACTIVE + (round + 1) % 3];
+    const int32_t* list = f.active[(round + 1) & 1];
+    for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n; i += (long long)gridDim.x * TB)
+        if (!follow(f, list[i], again != 0)) atomicMax(f.words + CSR_CHAINS, round + 1);
+}
+
+// All rounds from `round` on in one workgroup, once few vertices are active: a round's four launches take 30 us whatever they do.
+// A call with 1600 vertices: 202 us with rounds over all vertices, 199 over lists, 150 so; 4096 to 4900 vertices: 223 so and 201 by
+// launches; 14 400: 480 and 250.  So up to 2048.
+__global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
+{
+    __shared__ int s_active, s_roots, s_edges, s_chain;
+    const int tid = threadIdx.x;
+    int n = f.words[CSR_ACTIVE + round % 3], nr = f.words[CSR_ROOTS + round % 3], rounds = round;
+    bool done = halted(f) || f.words[CSR_EDGES] >= f.V - 1;
+    if (tid == 0) s_edges = f.words[CSR_EDGES];
+    __syncthreads();
+    for (int r = round; !done; ++r) {
+        const int32_t* from = f.active[r & 1];
+        int32_t* to = f.active[(r + 1) & 1];
+        uint32_t *best_w = f.best_w[r & 1], *next_w = f.best_w[(r + 1) & 1];
+        unsigned long long *best_e = f.best_e[r & 1], *next_e = f.best_e[(r + 1) & 1];
+        const int before = s_edges;
+        if (tid == 0) { s_active = s_roots = 0; }
+        __syncthreads();
+        for (int i0 = 0; i0 < n; i0 += WIDE) {
+            const int i = i0 + tid;
+            int v = -1, u = -1, c = 0;
+            uint32_t w = INF_BITS;
+            if (i < n) {
+                v = from[i];
+                c = f.colour[v];
+                if (!in_range(c, f.V)) { report(f, 11); c = 0; }
+                else u = row_edge<false>(f, v, c, &w);
+                if (u >= 0) {
+                    f.cand_u[v] = u;
+                    f.cand_w[v] = __uint_as_float(w);
+                    to[atomicAdd(&s_active, 1)] = v;
+                } else f.colour[v] = ~c;
+            }
+            wave_min_into(best_w, c, w, u >= 0);
+        }
+        __syncthreads();
+        n = s_active;
+        for (int i = tid; i < n; i += WIDE) {
+            const int v = to[i], u = f.cand_u[v], c = f.colour[v];
+            if (__float_as_uint(f.cand_w[v]) != __hip_atomic_load(best_w + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
+            const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
+            min_into(&best_e[c], ((unsigned long long)lo << 32) | hi);
+        }
+        __syncthreads();
+        for (int i = tid; i < nr; i += WIDE) {
+            const int c = f.roots[r & 1][i];
+            const uint32_t w = __hip_atomic_load(best_w + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (w == INF_BITS) continue;
+            const unsigned long long e = __hip_atomic_load(best_e + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const int lo = (int)(e >> 32), hi = (int)(e & 0xffffffffull);
+            if (!in_range(lo, f.V) || !in_range(hi, f.V)) { report(f, 8); continue; }
+            const int cl = f.colour[lo], ch = f.colour[hi];
+            const int other = cl == c ? ch : (ch == c ? cl : -1);
+            if (!in_range(other, f.V) || other == c) { report(f, 9); continue; }
+            const bool mutual = __hip_atomic_load(best_w + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == w &&
+                                __hip_atomic_load(best_e + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == e;
+            if (!mutual || c < other) {
+                const int slot = atomicAdd(&s_edges, 1);
+                if (slot < f.V - 1) { f.e_lo[slot] = lo; f.e_hi[slot] = hi; f.e_w[slot] = __uint_as_float(w); }
+            }
+            if (mutual && c < other) {
+                f.roots[(r + 1) & 1][atomicAdd(&s_roots, 1)] = c;
+                __hip_atomic_store(next_w + c, INF_BITS, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+                __hip_atomic_store(next_e + c, ~0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            } else f.hook[c] = other;
+        }
+        __syncthreads();
+        nr = s_roots;
+        for (int turn = 0;; ++turn) {
+            if (tid == 0) s_chain = 0;
+            __syncthreads();
+            for (int i = tid; i < n; i += WIDE)
+                if (!follow(f, to[i], true)) s_chain = 1;
+            __syncthreads();
+            if (s_chain == 0 || turn > 64) break;
+            __syncthreads();
+        }
+        if (tid == 0 && s_chain != 0) report(f, 10);
+        ++rounds;
+        __syncthreads();
+        done = s_edges == before || s_edges >= f.V - 1 || rounds > 64 + round || f.words[CSR_ERROR] != 0;
+        __syncthreads();
+    }
+    if (tid == 0) {
+        f.words[CSR_EDGES] = s_edges;
+        const int said[CSR_TOLD] = {rounds, s_edges, f.words[CSR_CHAINS], f.words[CSR_ERROR]};
+        for (int i = 0; i < CSR_TOLD; ++i)
+            __hip_atomic_store(host + i, ((unsigned long long)seq << 32) | (unsigned int)said[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+}
+
+// (a colour was up to date when its vertex stopped being active)
+__global__ void __launch_bounds__(TB) k_csr_colours(CsrForest f, int32_t* __restrict__ out)
+{
+    const int v = blockIdx.x * TB + threadIdx.x;
+    if (v >= f.V) return;
+    int r = f.colour[v];
+    r = r < 0 ? ~r : r;
+    for (int s = 0; s < f.V; ++s) {
+        if (!in_range(r, f.V)) { report(f, 14); r = -1; break; }
+        const int h = f.hook[r];
+        if (h == r) break;
+        r = h;
+    }
+    out[v] = r;
+}
+
+__global__ void __launch_bounds__(64) k_csr_words(int32_t* __restrict__ words)
+{
+    words[threadIdx.x] = 0;
+}
+
+hipError_t csr_start(const CsrForest& f, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_csr_words, dim3(1), dim3(64), 0, s, f.words);
+    hipLaunchKernelGGL(k_csr_first, dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f);
+    hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f, 0);
+    hipLaunchKernelGGL(k_csr_follow, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, 0, 0);
+    return hipGetLastError();
+}
+
+hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s)
+{
+    const dim3 per_vertex(blocks_for(vertices < 1 ? 1 : vertices));
+    hipLaunchKernelGGL(k_csr_scan, dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
+    hipLaunchKernelGGL(k_csr_select, per_vertex, dim3(TB), 0, s, f, round);
+    hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(roots)), dim3(WIDE), 0, s, f, round);
+    hipLaunchKernelGGL(k_csr_follow, per_vertex, dim3(TB), 0, s, f, round, 0);
+    return hipGetLastError();
+}
+
+hipError_t csr_follow_again(const CsrForest& f, int round, int vertices, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_csr_follow, dim3(blocks_for(vertices < 1 ? 1 : vertices)), dim3(TB), 0, s, f, round, 1);
+    return hipGetLastError();
+}
+
+hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uint32_t seq, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_csr_tail, dim3(1), dim3(WIDE), 0, s, f, round, host, seq);
+    return hipGetLastError();
+}
+
+hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_csr_colours, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, out);
+    return hipGetLastError();
+}
+
+// ------------------------------------------------------------------------------- sort
+// By (weight, smaller end, larger end).  The smaller ends are counted and the edges placed by them, which takes a few passes of
+// random words where a radix sort by both ends takes five over all of them; each vertex then orders its few edges by the other
+// end, and one stable sort by weight follows.  A vertex with more than LO_MOST edges to larger ones raises a flag, and the caller takes
+// edge_sort instead.  1M edges: 240 us with two radix sorts, 205 so.
+constexpr int LO_MOST = 32;
+__global__ void __launch_bounds__(TB) k_lo_clear(int32_t* __restrict__ count, int V, int32_t* __restrict__ flag)
+{
+    const int v = blockIdx.x * TB + threadIdx.x;
+    if (v <= V) count[v] = 0;
+    if (v == 0) *flag = 0;
+}
+__global__ void __launch_bounds__(TB) k_lo_count(const int32_t* __restrict__ lo, int E, int32_t* __restrict__ count, int32_t* __restrict__ rank)
+{
+    const int e = blockIdx.x * TB + threadIdx.x;
+    if (e < E) rank[e] = atomicAdd(count + lo[e], 1);
+}
+__global__ void __launch_bounds__(TB) k_lo_place(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi, const float* __restrict__ w, int E,
+                                                 const int32_t* __restrict__ offset, const int32_t* __restrict__ rank, uint32_t* __restrict__ wbits,
+                                                 unsigned long long* __restrict__ ends)
+{
+    const int e = blockIdx.x * TB + threadIdx.x;
+    if (e >= E) return;
+    const int at = offset[lo[e]] + rank[e];
+    wbits[at] = __float_as_uint(w[e]);
+    ends[at] = ((unsigned long long)(unsigned int)lo[e] << 32) | (unsigned int)hi[e];
+}
+__global__ void __launch_bounds__(TB) k_lo_order(const int32_t* __restrict__ offset, int V, uint32_t* __restrict__ wbits, unsigned long long* __restrict__ ends,
+                                                 int32_t* __restrict__ flag)
+{
+    const int v = blockIdx.x * TB + threadIdx.x;
+    if (v >= V) return;
+    const int a = offset[v], b = offset[v + 1];
+    if (b - a < 2) return;
+    if (b - a > LO_MOST) { *flag = 1; return; }
+    for (int i = a + 1; i < b; ++i) {
+        const unsigned long long e = ends[i];
+        const uint32_t w = wbits[i];
+        int j = i - 1;
+        for (; j >= a && ends[j] > e; --j) { ends[j + 1] = ends[j]; wbits[j + 1] = wbits[j]; }
+        ends[j + 1] = e; wbits[j + 1] = w;
+    }
+}
+__global__ void __launch_bounds__(TB) k_lo_unpack(const unsigned long long* __restrict__ ends, const uint32_t* __restrict__ wbits, int E, int32_t* __restrict__ lo,
+                                                  int32_t* __restrict__ hi, float* __restrict__ w)
+{
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i >= E) return;
+    lo[i] = (int)(ends[i] >> 32); hi[i] = (int)(ends[i] & 0xffffffffull); w[i] = __uint_as_float(wbits[i]);
+}
+
+// (radix passes from 32 768 pairs on, as in edge_sort)
+using radix_passes = rocprim::radix_sort_config<rocprim::default_config, rocprim::default_config, rocprim::default_config, 32768>;
+bool csr_sort_fits(int V, int E, size_t temp_bytes)
+{
+    size_t a = 0, b = 0;
+    int32_t* i = nullptr; uint32_t* k32 = nullptr; unsigned long long* k64 = nullptr;
+    (void)rocprim::exclusive_scan(nullptr, a, i, i, 0, (size_t)V + 1, rocprim::plus<int32_t>(), (hipStream_t)0);
+    (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, b, k32, k32, k64, k64, (size_t)E, 0, 32, (hipStream_t)0);
+    return a <= temp_bytes && b <= temp_bytes;
+}
+hipError_t csr_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w,
+                    int32_t* flag, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_lo_clear, dim3(blocks_for((long long)V + 1)), dim3(TB), 0, s, t.count, V, flag);
+    hipLaunchKernelGGL(k_lo_count, dim3(blocks_for(E)), dim3(TB), 0, s, lo, E, t.count, t.rank);
+    hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    size_t tb = t.temp_bytes;
+    e = rocprim::exclusive_scan(t.temp, tb, t.count, t.offset, 0, (size_t)V + 1, rocprim::plus<int32_t>(), s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lo_place, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, E, t.offset, t.rank, t.wbits_a, t.ends_a);
+    hipLaunchKernelGGL(k_lo_order, dim3(blocks_for(V)), dim3(TB), 0, s, t.offset, V, t.wbits_a, t.ends_a, flag);
+    e = hipGetLastError();
+    if (e != hipSuccess) return e;
+    tb = t.temp_bytes;
+    e = rocprim::radix_sort_pairs<radix_passes>(t.temp, tb, t.wbits_a, t.wbits_b, t.ends_a, t.ends_b, (size_t)E, 0, 32, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_lo_unpack, dim3(blocks_for(E)), dim3(TB), 0, s, t.ends_b, t.wbits_b, E, out_lo, out_hi, out_w);
+    return hipGetLastError();
+}
+
+}  // namespace slhc

@@ -26,8 +26,7 @@ struct ForestState {
     int32_t* hook;               // [N] per component: component it attaches to this round
     int32_t* qlist;              // [N] rows sent to the cross-component 1-NN
     int32_t* counters;           // 0 = queries this round, 1 = edges so far, 2 = a hook chain waits for the host,
-                                 // 3 = site of the first failed index check (0 = none), 4 = forest complete,
-                                 // 5 = edges at the last forest_publish with `steady`, 6 = rounds (forest_small)
+                                 // 3 = site of the first failed index check (0 = none), 6 = rounds (forest_small)
     int32_t* e_lo;               // [N-1] committed edges
     int32_t* e_hi;
     float* e_w;
@@ -60,22 +59,13 @@ hipError_t forest_commit(const ForestState& f, hipStream_t s);
 hipError_t forest_jump(const ForestState& f, int steps, bool flag, hipStream_t s);
 // colour[v] = end of the chain of hooks from colour[v]; the per-component minima are cleared for the next round.  A chain
 // longer than 64 hooks sets counters[2], and the rounds enqueued behind do nothing: the host finishes the chains
-// (forest_jump), clears the word and calls again with `again`.
-hipError_t forest_follow(const ForestState& f, bool again, hipStream_t s);
-// counters[0 .. 7] to host memory (host[1 ..]) and then `seq` to host[0].  With `steady` the forest also counts as
-// complete when no edge has been added since the last such call.
-hipError_t forest_publish(const ForestState& f, bool steady, int32_t* host, int32_t seq, hipStream_t s);
+// (forest_jump), clears the word and calls again.
+hipError_t forest_follow(const ForestState& f, hipStream_t s);
+// counters[0 .. 7] to host memory (host[1 ..]) and then `seq` to host[0].
+hipError_t forest_publish(const ForestState& f, int32_t* host, int32_t seq, hipStream_t s);
 // Rounds of a small forest in one launch, until it is complete or rows have to be queried (counters[0] of them in qlist).
 constexpr int FOREST_SMALL_MAX = 12288;
 hipError_t forest_small(const ForestState& f, bool first, hipStream_t s);
-
-// CSR input (offsets [V+1], indices [E], weights [E]).  forest_csr_check flags malformed arrays or
-// weights that are negative / not finite in f.counters[3]; forest_csr_scan fills cand_w / cand_u with
-// every vertex's first outgoing edge in the (w, lo, hi) order and folds the weights into best_w.
-hipError_t forest_csr_check(const int32_t* offsets, const int32_t* indices, const float* weights, int V, int E,
-                            int32_t* counters, hipStream_t s);
-hipError_t forest_csr_scan(const int32_t* offsets, const int32_t* indices, const float* weights, int E,
-                           const ForestState& f, hipStream_t s);
 
 // Sort E edges ascending by (w, lo, hi).  keys/vals are scratch of E elements each; `temp` of
 // edge_sort_temp_bytes(E).  Result in out_lo/out_hi/out_w.

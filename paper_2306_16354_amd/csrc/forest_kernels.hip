@@ -46,9 +46,8 @@ __device__ inline void report_with(const ForestState& f, int site, int a, int b,
     }
 }
 
-// Rounds may be enqueued ahead of the host's reading: they do nothing once the forest is complete (counters[4], set by
-// k_publish) or while a hook chain of an earlier round waits for the host (counters[2]).
-__device__ inline bool forest_halted(const ForestState& f) { return (f.counters[2] | f.counters[4]) != 0; }
+// While a hook chain of an earlier round waits for the host, what is enqueued behind does nothing.
+__device__ inline bool forest_halted(const ForestState& f) { return f.counters[2] != 0; }
 
 __global__ void __launch_bounds__(TB) k_forest_init(ForestState f)
 {
@@ -362,10 +361,10 @@ __global__ void __launch_bounds__(TB) k_jump(ForestState f, int steps, int flag)
 // always), takes that root as its colour, and clears its slots of the per-component minima for the next round.  A root
 // shortens its own hook on the way, which can only help the others.  A chain longer than `steps` leaves its vertices as
 // they are and sets counters[2]: the host finishes it with k_jump and launches this kernel again.
-__global__ void __launch_bounds__(TB) k_follow(ForestState f, int steps, int again)
+__global__ void __launch_bounds__(TB) k_follow(ForestState f, int steps)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N || (!again && f.counters[4] != 0)) return;
+    if (v >= f.N) return;
     if (v == 0) f.counters[0] = 0;
     f.best_w[v] = INF_BITS;
     f.best_e[v] = ~0ull;
@@ -385,15 +384,9 @@ __global__ void __launch_bounds__(TB) k_follow(ForestState f, int steps, int aga
 }
 
 // The counters, to host memory: words 1 .. n hold counters[0 .. n-1] and word 0 the sequence number, written last.
-// Also notes whether the forest is complete: all N - 1 edges, or (steady != 0) a round that added none.
-__global__ void __launch_bounds__(64) k_publish(int32_t* __restrict__ counters, int N, int steady, int n, int32_t* __restrict__ host,
-                                                int32_t seq)
+__global__ void __launch_bounds__(64) k_publish(const int32_t* __restrict__ counters, int n, int32_t* __restrict__ host, int32_t seq)
 {
     const int i = threadIdx.x;
-    if (i == 0 && steady && counters[2] == 0) {
-        if (counters[1] >= N - 1 || counters[1] == counters[5]) counters[4] = 1;
-        counters[5] = counters[1];
-    }
     if (i < n) __hip_atomic_store(host + 1 + i, counters[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     __threadfence_system();
     if (i == 0) __hip_atomic_store(host, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
@@ -561,65 +554,6 @@ __global__ void __launch_bounds__(TB) k_component_sizes(const int32_t* __restric
     if (active) atomicAdd(&sizes[c], 1);
 }
 
-// ------------------------------------------------------------------------------- CSR graphs
-// Sec. 3.2 takes the graph in CSR form.  Input check: offsets monotone from 0 to E, indices in
-// range, weights finite and non-negative (the edge order compares weight bit patterns).  A failed
-// check records its site in counters[3].
-__global__ void __launch_bounds__(TB) k_csr_check(const int32_t* __restrict__ offsets,
-                                                  const int32_t* __restrict__ indices,
-                                                  const float* __restrict__ weights, int V, int E,
-                                                  int32_t* __restrict__ counters)
-{
-    const long long i = (long long)blockIdx.x * TB + threadIdx.x;
-    if (i < V) {
-        const int o0 = offsets[i], o1 = offsets[i + 1];
-        if (o0 < 0 || o1 < o0 || o1 > E) atomicCAS(&counters[3], 0, 20);
-        if (i == 0 && o0 != 0) atomicCAS(&counters[3], 0, 21);
-        if (i == V - 1 && o1 != E) atomicCAS(&counters[3], 0, 22);
-    }
-    if (i < E) {
-        if (!in_range(indices[i], V)) atomicCAS(&counters[3], 0, 23);
-        const float w = weights[i];
-        if (!(w >= 0.f) || w == __builtin_inff()) atomicCAS(&counters[3], 0, 24);
-    }
-}
-
-// Minimum outgoing edge of every vertex (Sec. 3.2.2 "Minimum Edge Per Vertex"): one thread scans
-// the vertex's row for the edge to another colour that is first in the order (w, lo, hi).  The
-// paper gives a warp to each vertex; road-like graphs have 2-3 edges per vertex, where a 64-wide
-// wavefront per vertex would idle, so a thread per vertex is used (a row with thousands of edges
-// is then scanned by one thread: correct, slow).
-__global__ void __launch_bounds__(TB) k_csr_scan(const int32_t* __restrict__ offsets,
-                                                 const int32_t* __restrict__ indices,
-                                                 const float* __restrict__ weights, int E, ForestState f)
-{
-    const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.N || forest_halted(f)) return;
-    // f.ptr[v] != 0: an earlier round found every neighbour of v in v's own component.  Components only
-    // grow, so v never has an outgoing edge again; its cand_u stays -1 and its row is not read any more
-    // (after a few rounds that is most vertices).
-    if (f.ptr[v] != 0) return;
-    const int c = f.colour[v];
-    if (!in_range(c, f.N)) { report(f, 25); return; }
-    int o0 = offsets[v], o1 = offsets[v + 1];
-    o0 = o0 < 0 ? 0 : o0;
-    o1 = o1 > E ? E : o1;
-    uint32_t bw = INF_BITS;
-    unsigned int blo = ~0u, bhi = ~0u;
-    int bu = -1;
-    for (int e = o0; e < o1; ++e) {
-        const int u = indices[e];
-        if (!in_range(u, f.N) || f.colour[u] == c) continue;      // also drops self loops
-        const uint32_t wb = __float_as_uint(weights[e]);
-        const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
-        if (wb < bw || (wb == bw && (lo < blo || (lo == blo && hi < bhi)))) { bw = wb; blo = lo; bhi = hi; bu = u; }
-    }
-    f.cand_u[v] = bu;
-    f.cand_w[v] = __uint_as_float(bw);
-    if (bu >= 0) min_into(&f.best_w[c], bw);
-    else f.ptr[v] = 1;
-}
-
 #define LAUNCH1(kern, n, s, ...)                                                       \
     do {                                                                               \
         hipLaunchKernelGGL(kern, dim3(blocks_for(n)), dim3(TB), 0, s, __VA_ARGS__);    \
@@ -670,10 +604,10 @@ hipError_t forest_commit(const ForestState& f, hipStream_t s)
     return hipGetLastError();
 }
 hipError_t forest_jump(const ForestState& f, int steps, bool flag, hipStream_t s) { LAUNCH1(k_jump, f.N, s, f, steps, flag ? 1 : 0); }
-hipError_t forest_follow(const ForestState& f, bool again, hipStream_t s) { LAUNCH1(k_follow, f.N, s, f, FOLLOW_STEPS, again ? 1 : 0); }
-hipError_t forest_publish(const ForestState& f, bool steady, int32_t* host, int32_t seq, hipStream_t s)
+hipError_t forest_follow(const ForestState& f, hipStream_t s) { LAUNCH1(k_follow, f.N, s, f, FOLLOW_STEPS); }
+hipError_t forest_publish(const ForestState& f, int32_t* host, int32_t seq, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, f.counters, f.N, steady ? 1 : 0, 8, host, seq);
+    hipLaunchKernelGGL(k_publish, dim3(1), dim3(64), 0, s, f.counters, 8, host, seq);
     return hipGetLastError();
 }
 hipError_t forest_small(const ForestState& f, bool first, hipStream_t s)
@@ -683,18 +617,6 @@ hipError_t forest_small(const ForestState& f, bool first, hipStream_t s)
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_forest_small, dim3(1), dim3(1024), lds, s, f, first ? 0 : 1);
     return hipGetLastError();
-}
-
-hipError_t forest_csr_check(const int32_t* offsets, const int32_t* indices, const float* weights, int V, int E,
-                            int32_t* counters, hipStream_t s)
-{
-    LAUNCH1(k_csr_check, (V > E ? V : E), s, offsets, indices, weights, V, E, counters);
-}
-
-hipError_t forest_csr_scan(const int32_t* offsets, const int32_t* indices, const float* weights, int E,
-                           const ForestState& f, hipStream_t s)
-{
-    LAUNCH1(k_csr_scan, f.N, s, offsets, indices, weights, E, f);
 }
 
 // ------------------------------------------------------------------------------- edge sort

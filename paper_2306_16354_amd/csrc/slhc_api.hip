@@ -20,6 +20,7 @@
 
 #include "../../include/slhc.h"
 #include "cluster_kernels.h"
+#include "csr_kernels.h"
 #include "forest_kernels.h"
 #include "near_kernels.h"
 #include "direct_kernels.h"
@@ -436,7 +437,7 @@ struct Mailbox {
     {
         const hipError_t e = box.alloc((WORDS + 16) * sizeof(uint32_t));
         if (e != hipSuccess) return e;
-        slot()[0] = 0u;
+        for (int i = 0; i < 16; ++i) slot()[i] = 0u;         // (another user's sequence numbers)
         return hipSuccess;
     }
     volatile uint32_t* slot() { return static_cast<volatile uint32_t*>(box.p); }
@@ -445,8 +446,22 @@ struct Mailbox {
     // until the sequence number last handed out has arrived
     hipError_t wait()
     {
+        return until([&] { return __atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq; });
+    }
+    // until it has arrived in the high halves of the first n 64-bit words
+    hipError_t wait_tagged(int n)
+    {
+        return until([&] {
+            for (int i = 0; i < n; ++i)
+                if ((uint32_t)(__atomic_load_n(reinterpret_cast<unsigned long long*>(box.p) + i, __ATOMIC_ACQUIRE) >> 32) != seq) return false;
+            return true;
+        });
+    }
+    template <typename F>
+    hipError_t until(F&& arrived)
+    {
         for (unsigned spins = 0;; ++spins) {
-            if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+            if (arrived()) return hipSuccess;
 #if defined(__x86_64__)
             __builtin_ia32_pause();
 #endif
@@ -454,10 +469,10 @@ struct Mailbox {
                 // an error ends the wait; so does a stream that has run dry without the number
                 const hipError_t q = hipStreamQuery(s);
                 if (q == hipErrorNotReady) continue;
-                if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+                if (arrived()) return hipSuccess;
                 if (q != hipSuccess) return q;
                 const hipError_t w = hipStreamSynchronize(s);
-                if (__atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq) return hipSuccess;
+                if (arrived()) return hipSuccess;
                 return w != hipSuccess ? w : hipErrorUnknown;
             }
         }
@@ -1797,7 +1812,7 @@ struct CsrWs {
     {
         Carver c(ws);
         const size_t n = (size_t)V;
-        colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);
+        colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);       // (ptr and ext_idx serve as one array in the end)
         cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
         ext_dist = c.take<float>(n); ext_low = c.take<float>(n); cand_w = c.take<float>(n); e_w = c.take<float>(n);
@@ -1842,89 +1857,118 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         CsrWs ws(workspace, V);
         if (workspace_bytes < ws.bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, ws.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
         hipStream_t s = static_cast<hipStream_t>(stream);
-        slhc::ForestState f{};
-        f.N = (int)V; f.k = 1;
-        f.colour = ws.colour; f.ptr = ws.ptr; f.ext_idx = ws.ext_idx; f.ext_dist = ws.ext_dist; f.ext_low = ws.ext_low;
-        f.cand_w = ws.cand_w; f.cand_u = ws.cand_u; f.best_w = ws.best_w; f.best_e = ws.best_e;
-        f.hook = ws.hook; f.qlist = ws.ptr; f.counters = ws.counters;
+        slhc::CsrForest f{};
+        f.offsets = offsets; f.indices = indices; f.weights = weights; f.V = (int)V; f.E = (int)E;
+        f.colour = ws.colour; f.hook = ws.hook; f.cand_u = ws.cand_u; f.cand_w = ws.cand_w;
+        f.best_w[0] = ws.best_w; f.best_w[1] = ws.vals_a; f.best_e[0] = ws.best_e; f.best_e[1] = ws.keys_a;
+        f.active[0] = ws.ptr; f.active[1] = ws.ext_idx;
+        f.roots[0] = reinterpret_cast<int32_t*>(ws.ext_dist); f.roots[1] = reinterpret_cast<int32_t*>(ws.ext_low);
         f.e_lo = ws.e_lo; f.e_hi = ws.e_hi; f.e_w = ws.e_w;
-        HIP_TRY(slhc::forest_init(f, s));
-        HIP_TRY(slhc::forest_csr_check(offsets, indices, weights, (int)V, (int)E, ws.counters, s));
-        // Rounds are enqueued one ahead of the host's reading (two mailboxes in turn): the device goes from round to round
-        // without waiting for the host, and the round enqueued behind the last one finds the forest complete and does
-        // nothing.
+        f.words = ws.counters;
+        // Alg. "MST Algorithm": min edge per vertex, min edge per supervertex, label propagation, until a round adds no edge (the
+        // graph's components are then the forest's trees).  Rounds are enqueued one ahead of the host's reading (two mailboxes in
+        // turn): the device goes from round to round without waiting for the host.  Once few vertices are active one launch does the
+        // rest.
         Mailbox mail[2] = {Mailbox(s), Mailbox(s)};
         HIP_TRY(mail[0].open());
         HIP_TRY(mail[1].open());
         int max_rounds = 2;
         for (int64_t t = 1; t < V; t *= 2) ++max_rounds;
         int edges = 0, nrounds = 0;
-        auto publish = [&](int which) -> int {
-            HIP_TRY(slhc::forest_publish(f, true, reinterpret_cast<int32_t*>(mail[which].words()), (int32_t)mail[which].next(), s));
+        // as far as known: active vertices, and roots, of which a round leaves half at most
+        int64_t vertices = V, roots = V;
+        auto enqueue_round = [&](int round) -> int {
+            Mailbox& m = mail[round & 1];
+            roots = roots / 2 + 1;
+            HIP_TRY(slhc::csr_round(f, round, (int)vertices, (int)roots, static_cast<unsigned long long*>(m.box.p), m.next(), s));
             return SLHC_OK;
         };
-        // Alg. "MST Algorithm": min edge per vertex, min edge per supervertex, label propagation, until a
-        // round adds no edge (the graph's components are then the forest's trees)
-        auto enqueue_round = [&](int which) -> int {
-            HIP_TRY(slhc::forest_csr_scan(offsets, indices, weights, (int)E, f, s));
-            HIP_TRY(slhc::forest_select_edges(f, s));
-            HIP_TRY(slhc::forest_commit(f, s));
-            HIP_TRY(slhc::forest_follow(f, false, s));
-            return publish(which);
-        };
-        auto read = [&](int which, int32_t* out) -> int {
-            HIP_TRY(mail[which].wait());
-            std::memcpy(out, mail[which].words() + 1, 8 * sizeof(int32_t));
-            return SLHC_OK;
-        };
-        int32_t h_cnt[8];
-        HIP_TRY(mail[0].fetch(ws.counters, 4, h_cnt));
-        if (h_cnt[3] != 0) {
-            set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", h_cnt[3]);
-            return SLHC_INVALID_ARG;
-        }
-        if (V > 1) {
-            int rc2 = enqueue_round(0);
-            if (rc2 != SLHC_OK) return rc2;
-            for (int at = 0;; at ^= 1) {
-                rc2 = enqueue_round(at ^ 1);                     // the round after the one that is read now
-                if (rc2 != SLHC_OK) return rc2;
-                rc2 = read(at, h_cnt);
-                if (rc2 != SLHC_OK) return rc2;
-                if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
-                if (++nrounds > max_rounds) { set_err("no steady state after %d rounds", max_rounds); return SLHC_INTERNAL; }
-                if (h_cnt[2] != 0) {
-                    // hook chains longer than a launch follows: the round enqueued behind did nothing; finish the chains
-                    // with the host in the loop and take the round up again
-                    rc2 = read(at ^ 1, h_cnt);
-                    if (rc2 != SLHC_OK) return rc2;
-                    for (int jumps = 0; h_cnt[2] != 0; ++jumps) {
-                        if (jumps > 64) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
-                        hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(ws.counters + 2), 1);
-                        HIP_TRY(hipGetLastError());
-                        HIP_TRY(slhc::forest_jump(f, 32, true, s));
-                        HIP_TRY(mail[0].fetch(ws.counters, 8, h_cnt));
-                        if (h_cnt[3] != 0) { set_err("forest state check %d failed", h_cnt[3]); return SLHC_INTERNAL; }
-                    }
-                    HIP_TRY(slhc::forest_follow(f, true, s));
-                    rc2 = publish(at);
-                    if (rc2 == SLHC_OK) rc2 = read(at, h_cnt);
-                    if (rc2 != SLHC_OK) return rc2;
-                    if (h_cnt[4] == 0) {
-                        rc2 = enqueue_round(at ^ 1);
-                        if (rc2 != SLHC_OK) return rc2;
-                    }
-                }
-                if (h_cnt[1] < edges || h_cnt[1] > V - 1) { set_err("round left %d edges (had %d)", h_cnt[1], edges); return SLHC_INTERNAL; }
-                edges = h_cnt[1];
-                if (h_cnt[4] != 0) break;                 // steady state: a spanning forest
+        int32_t said[slhc::CSR_TOLD];
+        auto read = [&](int which) -> int {
+            HIP_TRY(mail[which].wait_tagged(slhc::CSR_TOLD));
+            for (int i = 0; i < slhc::CSR_TOLD; ++i) said[i] = (int32_t)static_cast<volatile unsigned long long*>(mail[which].box.p)[i];
+            if (said[3] >= 20) {
+                set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", said[3]);
+                return SLHC_INVALID_ARG;
             }
+            if (said[3] == 10) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
+            if (said[3] != 0) { set_err("forest state check %d failed", said[3]); return SLHC_INTERNAL; }
+            return SLHC_OK;
+        };
+        // hook chains of `round` longer than a launch follows: finish them with the host in the loop
+        auto finish_chains = [&](int round) -> int {
+            int32_t left = 1;
+            for (int jumps = 0; left != 0; ++jumps) {
+                if (jumps > 64) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
+                hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(f.words + slhc::CSR_CHAINS), 1);
+                HIP_TRY(hipGetLastError());
+                HIP_TRY(slhc::csr_follow_again(f, round, (int)vertices, s));
+                HIP_TRY(mail[0].fetch(f.words + slhc::CSR_CHAINS, 1, &left));
+            }
+            return SLHC_OK;
+        };
+        HIP_TRY(slhc::csr_start(f, s));
+        int rc2 = SLHC_OK, next = 1;                       // the round to enqueue next
+        if (V > slhc::CSR_TAIL) { rc2 = enqueue_round(next++); if (rc2 != SLHC_OK) return rc2; }
+        // what round `round - 1` left comes back with round `round`, behind which the next one is enqueued already
+        for (int round = 1; vertices > slhc::CSR_TAIL; ++round) {
+            rc2 = enqueue_round(next++);
+            if (rc2 == SLHC_OK) rc2 = read(round & 1);
+            if (rc2 != SLHC_OK) return rc2;
+            if (said[2] != 0) {
+                // this round and the one behind it did nothing: take both up again
+                rc2 = read((round + 1) & 1);
+                if (rc2 == SLHC_OK) rc2 = finish_chains(round - 1);
+                roots = V;
+                next = round;
+                for (int i = 0; i < 2 && rc2 == SLHC_OK; ++i) rc2 = enqueue_round(next++);
+                if (rc2 == SLHC_OK) rc2 = read(round & 1);
+                if (rc2 != SLHC_OK) return rc2;
+            }
+            if (said[1] < edges || said[1] > V - 1 || said[0] < 0 || said[0] > V) { set_err("round left %d edges (had %d)", said[1], edges); return SLHC_INTERNAL; }
+            const bool added = said[1] > edges;
+            edges = said[1];
+            vertices = said[0];
+            nrounds = round;
+            if (!added || edges == V - 1) break;           // steady state: a spanning forest
+            if (nrounds > max_rounds) { set_err("no steady state after %d rounds", max_rounds); return SLHC_INTERNAL; }
+            nrounds = 0;
         }
-        if (edges > 0)
-            HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
-                                    ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
-        HIP_TRY(hipMemcpyAsync(colours, ws.colour, (size_t)V * sizeof(int32_t), hipMemcpyDeviceToDevice, s));
-        HIP_TRY(hipStreamSynchronize(s));
+        while (nrounds == 0) {
+            HIP_TRY(slhc::csr_tail(f, next, static_cast<unsigned long long*>(mail[1].box.p), mail[1].next(), s));
+            rc2 = read(1);
+            if (rc2 != SLHC_OK) return rc2;
+            if (said[2] != 0) {                            // (of a round before, behind which nothing was done)
+                next = said[2];
+                rc2 = finish_chains(next - 1);
+                if (rc2 != SLHC_OK) return rc2;
+                continue;
+            }
+            nrounds = said[0];
+            edges = said[1];
+            if (edges < 0 || edges > V - 1 || nrounds < 1) { set_err("rounds left %d edges", edges); return SLHC_INTERNAL; }
+        }
+        if (V == 1) nrounds = 0;
+        HIP_TRY(slhc::csr_colours(f, colours, s));
+        int32_t* flag = f.words + slhc::CSR_FLAG;
+        int32_t many = 0;
+        if (edges > 0) {
+            // (the arrays of the rounds are free by now)
+            slhc::CsrSortScratch t{};
+            t.count = reinterpret_cast<int32_t*>(ws.best_e); t.offset = reinterpret_cast<int32_t*>(ws.keys_a);
+            t.rank = ws.cand_u; t.wbits_a = ws.best_w; t.wbits_b = ws.vals_a; t.ends_a = ws.keys_b;
+            t.ends_b = reinterpret_cast<unsigned long long*>(ws.ptr);          // (and ext_idx behind it)
+            t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
+            many = V > 65536 && slhc::csr_sort_fits((int)V, edges, ws.sort_temp_bytes) ? 0 : 1;        // (up to there edge_sort needs one sort)
+            if (!many) {
+                HIP_TRY(slhc::csr_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, t, mst_src, mst_dst, mst_w, flag, s));
+                HIP_TRY(mail[0].fetch(flag, 1, &many));
+            }
+            if (many)
+                HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
+                                        ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
+        }
+        if (edges == 0 || many) HIP_TRY(hipStreamSynchronize(s));
         mail[0].box.idle();
         mail[1].box.idle();
         *n_edges = edges;
@@ -2195,7 +2239,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         return SLHC_OK;
     };
     auto read_counters = [&]() -> int {
-        HIP_TRY(slhc::forest_publish(f, false, reinterpret_cast<int32_t*>(mail.words()), (int32_t)mail.next(), s));
+        HIP_TRY(slhc::forest_publish(f, reinterpret_cast<int32_t*>(mail.words()), (int32_t)mail.next(), s));
         HIP_TRY(mail.wait());
         std::memcpy(h_cnt, mail.words() + 1, 8 * sizeof(int32_t));
         if (h_cnt[3] != 0) {
@@ -2240,7 +2284,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     rc = read_counters();
                     if (rc != SLHC_OK) return rc;
                 }
-                HIP_TRY(slhc::forest_follow(f, true, s));
+                HIP_TRY(slhc::forest_follow(f, s));
                 rc = enqueue_scan();
                 if (rc != SLHC_OK) return rc;
                 rc = read_counters();
@@ -2529,7 +2573,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
         if (small_forest) { HIP_TRY(slhc::forest_small(f, false, s)); continue; }
         HIP_TRY(slhc::forest_select_edges(f, s));
         HIP_TRY(slhc::forest_commit(f, s));
-        HIP_TRY(slhc::forest_follow(f, false, s));            // hooks -> new colours
+        HIP_TRY(slhc::forest_follow(f, s));           // hooks -> new colours
         rc = enqueue_scan();                                  // next round's scan; its counters are read at the top
         if (rc != SLHC_OK) return rc;
     }

@@ -1,0 +1,78 @@
+"""Rounds over lists of active vertices and roots, and the sort by the smaller ends (csr_kernels.hip), against the oracle's Kruskal:
+graphs whose rounds, lists, hook chains and edge counts per vertex end differently."""
+import numpy as np
+import pytest
+
+import oracle
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2306_16354_amd as slhc
+    slhc.load_library()
+    assert torch.cuda.is_available()
+    return slhc
+
+
+def csr(V, a, b, w, shuffled=None):
+    src, dst, ww = np.r_[a, b], np.r_[b, a], np.r_[w, w].astype(np.float32)
+    order = np.argsort(src, kind="stable") if shuffled is None else np.lexsort((shuffled.random(len(src)), src))
+    offsets = np.r_[0, np.cumsum(np.bincount(src, minlength=V))].astype(np.int32)
+    return offsets, dst[order].astype(np.int32), ww[order]
+
+
+def check(lib, V, offsets, indices, weights):
+    got = lib.csr_msf(*(torch.from_numpy(x).cuda() for x in (offsets, indices, weights)))
+    torch.cuda.synchronize()
+    lo, hi, w, comp = oracle.csr_msf(offsets, indices, weights)
+    assert np.array_equal(got["mst_src"].cpu().numpy(), lo) and np.array_equal(got["mst_dst"].cpu().numpy(), hi)
+    assert np.array_equal(got["mst_w"].cpu().numpy(), w.astype(np.float32))
+    c = got["colours"].cpu().numpy()
+    assert len(np.unique(c)) == V - len(lo) and np.array_equal(c[lo], c[hi]) and np.array_equal(c[c], c)
+
+
+# a vertex of more tree edges than are ordered in place, as the smaller and as the larger end, with ties and without; 32 and 33 edges
+@pytest.mark.parametrize("V", [2, 33, 34, 35, 300, 70_000])
+@pytest.mark.parametrize("hub", ["first", "last"])
+@pytest.mark.parametrize("ties", [True, False])
+def test_stars(lib, V, hub, ties):
+    print(f"csr star V={V} hub={hub} ties={ties}", flush=True)
+    rng = np.random.default_rng(V)
+    a = np.zeros(V - 1, np.int64) if hub == "first" else np.full(V - 1, V - 1)
+    b = np.arange(1, V) if hub == "first" else np.arange(V - 1)
+    w = rng.integers(1, 4, V - 1) if ties else rng.permutation(V - 1) + 0.5
+    check(lib, V, *csr(V, a, b, w, rng))
+
+
+# rows in no order, several edges between two vertices, self loops, vertices without edges, many trees; weights of few values and of many, 0 included
+@pytest.mark.parametrize("V,degree,values", [(1, 0, 1), (500, 0.4, 3), (3000, 1.0, 1), (5000, 3.0, 2), (20_000, 1.3, 1000), (100_000, 2.5, 10), (66_000, 8.0, 1_000_000)])
+def test_random_graphs(lib, V, degree, values):
+    print(f"csr random V={V} degree={degree} values={values}", flush=True)
+    rng = np.random.default_rng(V)
+    E = int(V * degree / 2)
+    a, b = rng.integers(0, V, E), rng.integers(0, V, E)
+    w = rng.integers(0, values, E).astype(np.float32)
+    a, b, w = np.r_[a, a[:E // 10]], np.r_[b, b[:E // 10]], np.r_[w, w[:E // 10] + 1]
+    keep = a != b
+    loops = rng.integers(0, V, V // 50)
+    offsets, indices, weights = csr(V, np.r_[a[keep]], np.r_[b[keep]], w[keep], rng)
+    if len(loops):                       # (one entry each)
+        src = np.repeat(np.arange(V), np.diff(offsets))
+        src, dst, ww = np.r_[src, loops], np.r_[indices, loops], np.r_[weights, np.full(len(loops), 0.0, np.float32)]
+        order = np.argsort(src, kind="stable")
+        offsets = np.r_[0, np.cumsum(np.bincount(src, minlength=V))].astype(np.int32)
+        indices, weights = dst[order].astype(np.int32), ww[order].astype(np.float32)
+    check(lib, V, offsets, indices, weights)
+
+
+# hook chains of a round from one to all vertices long: weights rising along paths of `run` vertices, which meet at their ends
+@pytest.mark.parametrize("run", [2, 63, 64, 65, 66, 4097, 100_000])
+def test_chains(lib, run):
+    print(f"csr chains of {run}", flush=True)
+    V = 100_000 // run * run
+    a = np.arange(V - 1)
+    w = np.where((a + 1) % run == 0, 1e6 + a, (a % run).astype(np.float64))
+    check(lib, V, *csr(V, a, a + 1, w.astype(np.float32)))
