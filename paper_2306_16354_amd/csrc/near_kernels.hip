@@ -330,6 +330,7 @@ struct NearSweep {
     // Searches in a row order with two copies: `local` (side 1) holds every tile relative to its region and serves the pairs
     // inside one region, the other copy (side 2) all others.  region[tile] < 0: no region.  Entries of side 2 carry `mark`.
     const int32_t* region; int side; unsigned int mark;
+    const int32_t* tile_colour;        // listed, coloured: the colour all rows of a tile share, -1 where they differ
     int append;                        // emit: the buffers hold the entries of an earlier launch, whose values do not compare
     float* maxima; int parts, groups;  // maxima: [nseg * parts][queries of the batch][groups], groups 32 or 8
     uint2* entries; int32_t* counts; int capl;      // emit: [queries of the batch][2 nseg][capl], [queries][2 nseg]
@@ -433,13 +434,14 @@ struct NearLane {
 
     // acc[query block][candidate block]: value r of a lane belongs to candidate 8 (r / 4) + 4 lhalf + r % 4 of its block;
     // pos0: position of the first of the 64 candidates, col: their colours (LDS)
-    // ok: whether the lane's queries and the candidates' tile are of the side in hand
+    // ok: whether the lane's queries and the candidates' tile are of the side in hand (and of different colours, with one_colour,
+    // which all lanes share: the 32 compares and selects per 16 values of a query are as much as a third of all vector instructions)
     __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf,
-                                                               bool ok0 = true, bool ok1 = true)
+                                                               bool ok0 = true, bool ok1 = true, bool one_colour = false)
     {
         const bool ok[2] = {ok0, ok1};
         const int lane = threadIdx.x & 63;
-        if (COLOURED) {
+        if (COLOURED && !one_colour) {
 #pragma unroll
             for (int cb = 0; cb < 2; ++cb)
 #pragma unroll
@@ -712,13 +714,15 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     };
     int next = ntiles > 0 ? tile_at(0) : 0;
     if (ntiles > 0) stage(0, next);
+    int next_colour = LISTED && COLOURED && ntiles > 0 ? p.tile_colour[next] : -1;
     const int per_part = MODE == NEAR_MAXIMA ? (ntiles + p.parts - 1) / p.parts : 0;
     int part = 0, part_end = per_part;
     for (int i = 0; i < ntiles; ++i) {
         near_lds_ready();
-        const int pos0 = next * TILE;
+        const int pos0 = next * TILE, colour_here = next_colour;
         if (i + 1 < ntiles) {
             next = tile_at(i + 1);
+            if (LISTED && COLOURED) next_colour = p.tile_colour[next];
             stage(i + 1, next);
         }
         const unsigned char* tb = near_smem + (i & 1) * BUF;
@@ -727,6 +731,11 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
             const int tile_reg = p.region[pos0 >> 7];
             ok0 = (tile_reg >= 0 && tile_reg == mine.reg[0]) == (p.side == 1);
             ok1 = (tile_reg >= 0 && tile_reg == mine.reg[1]) == (p.side == 1);
+        }
+        const int tile_col = LISTED && COLOURED ? colour_here : -1;
+        if (LISTED && COLOURED) {
+            ok0 = ok0 && tile_col != mine.qcol[0];           // (colours are not negative)
+            ok1 = ok1 && tile_col != mine.qcol[1];
         }
         if (!LISTED || (mine_here && __any(ok0 || ok1)))
 #pragma unroll
@@ -761,7 +770,7 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
                     for (int qb = 0; qb < 2; ++qb)
                         acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
             }
-            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1);
+            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1, tile_col >= 0);
         }
         if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == ntiles)) {
             mine.flush(p, seg * p.parts + part, lhalf, live && mine_here);
@@ -2473,6 +2482,7 @@ hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBu
     if (batch_panels > 8192) batch_panels = 8192;
     NearSweep p{};
     p.qcolour = p.ccolour = o.all.colour; p.c_tiles = T;
+    p.tile_colour = o.tile_colour;
     p.d = a.d; p.steps = near_steps(a.d); p.e = near_e(p.steps); p.nu = near_nu(p.steps);
     p.stride = 1; p.used = T; p.kk = 1;
     p.qpos = a.qpos; p.n_q = a.n; p.best_at = a.best_at;
