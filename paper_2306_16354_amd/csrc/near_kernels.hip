@@ -945,7 +945,7 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
                                                           float nu, int steps, int d, float* __restrict__ bound, float* __restrict__ reach,
                                                           const int32_t* __restrict__ step, int panel_queries,
                                                           const int32_t* __restrict__ region, const float* __restrict__ negh_local,
-                                                          const NearScale* __restrict__ sc_local, int32_t* __restrict__ limit_counts)
+                                                          const NearScale* __restrict__ sc_local, int32_t* __restrict__ limit_counts, int32_t* __restrict__ limit_last)
 {
     const int lane = threadIdx.x & 63;
     const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -987,7 +987,7 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
         const NearBoundArgs a = near_args(sc, steps, d, e, nu);
         const float made = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
         if (LIMIT) {                    // of a row for pairs_emit; none where there is no row or it goes to the list kernels
-            limit_counts[lq] = 0;
+            limit_counts[lq] = limit_last[lq] = 0;
             bound[lq] = !(fabsf(nh) < INF) ? NEVER : made == LOWEST ? LOWEST : made + nh;
             return;
         }
@@ -1101,6 +1101,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     // gather the entries of all buffers: counts side by side over the lanes, running totals, then every lane looks up
     // the buffer its entry lies in
     int n = 0;
+    const float base = p.pair_lists ? nh : 0.f;
     bool lost = nh == INF || (p.region && p.negh_local[qcopy] == INF);
     {
         const int mine = lane < p.nsub ? p.counts[p.by_position ? (size_t)qpos : (size_t)lq * p.nsub + lane] : 0;
@@ -1124,7 +1125,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
             const int begin = __shfl(upto - mine, sub & 63);
             if (at < n) {
                 const unsigned long long x = e[(size_t)sub * p.capl + (at - begin)];
-                keys[at] = p.pair_lists ? (x & 0xffffffff00000000ull) | __float_as_uint(__uint_as_float((unsigned int)x) - nh) : x;
+                keys[at] = (x & 0xffffffff00000000ull) | __float_as_uint(__uint_as_float((unsigned int)x) - base);
             }
         }
     }
@@ -1528,13 +1529,14 @@ struct PairPlan {
 };
 // Who gains: up to 64 columns a block's comparisons (66 instructions of its wavefront) take as long as its products, and of the rows of a
 // small search every block holds a few that pass.  Each side in us, products once per row and once per pair: 5000 x 40, k = 10: 76 and 65;
-// 10 000 x 64, 20: 151 and 128; 20 000 x 128, 32: 356 and 370; 20 011 x 50, 10: 224 and 237; 120 000 x 64, 32: 4220 and 4780; 250 000 x 33, 40:
-// 13.1 and 13.6 ms; 50 000 x 96, 32: 1700 and 1360; 200 000 x 128, 16: 17.2 and 12.4 ms; 5000 x 200, 10: 146 and 105; 250 000 x 784, 16: 126 and 62 ms.
-// (up to 12 800 rows it is the fewer, longer shares of the candidates that gain)
+// 10 000 x 64, 20: 151 and 128; 20 000 x 128, 32: 356 and 370; 40 000 x 70, 10: 616 and 646; 50 000 x 70, 10: 979 and 898; 60 000 x 80, 32: 1472
+// and 1468; 120 000 x 64, 32: 4220 and 4780; 120 000 x 100, 10: 4247 and 3648; 250 000 x 33, 40: 13.1 and 13.6 ms; 300 000 x 128, 32: 34.7 and
+// 21.8 ms; 5000 x 200, 10: 146 and 105; 250 000 x 784, 16: 126 and 62 ms.  (Up to 12 800 rows it is the fewer, longer shares of the
+// candidates that gain.)
 static bool pair_search_wanted(int T, int steps)
 {
     if (T < 32 || T >= (1 << 17)) return false;
-    return steps > REG_STEPS || (T <= 100 ? steps >= 3 : T >= 256 && steps >= 5);
+    return steps > REG_STEPS || (T <= 100 ? steps >= 3 : T >= 384 && steps >= 5);
 }
 // from here on rows whose lists overflow are searched for on their own before the list kernels take their panels; below, the five
 // launches cost more (20 us) than a panel or two
@@ -1554,8 +1556,8 @@ static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
     p.blocks = (T + bt - 1) / bt;
     const int half = p.blocks / 2 + 1;
     // What a sample of one tile in `stride` costs, and one band (0) or a first one of the sample's share and b more that see
-    // g times as much each, in us: the products of the sample (1.1e15 a second), 15 us per band, 0.1 ns per entry, of which
-    // rounding makes twice what is asked for on average.
+    // g times as much each, in us: the products of the sample (1.1e15 a second), 15 us per band and 1 ns per row for the tightening
+    // before it, 0.1 ns per entry, of which rounding makes twice what is asked for on average.
     const double all = (double)n * n * 32.0 * (steps < 6 ? 6 : steps) / 1.1e9, entry = 2e-4 * n * kk, most = p.cap / (3.5 * kk);
     double best = 1e300;
     int stride = 1, more = 0;
@@ -1563,7 +1565,7 @@ static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
         for (int b = 0; b <= 7; ++b) {
             const double g = b > 0 ? pow((double)s, 1.0 / b) : s;
             if (g > most && s > 1 && b < 7) continue;
-            const double cost = all / s + 15.0 * (b + 1) + entry * (b > 0 ? 1.0 + b * (g - 1.0) : g);
+            const double cost = all / s + 15.0 * (b + 1) + 1e-3 * n * b + entry * (b > 0 ? 1.0 + b * (g - 1.0) : g);
             if (cost < best) { best = cost; stride = s; more = b; }
         }
     const double g = more > 0 ? pow((double)stride, 1.0 / more) : 1.0;
@@ -1632,14 +1634,14 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
         hipLaunchKernelGGL((near_bounds_kernel<true>), dim3((unsigned)(p.nq_batch / 4)), dim3(256), 0, s, maxima, q.max_sets, q.groups == GROUPS ? 5 : 3, p.nq_batch,
                            t0 * TILE, kk, c.negh, b.scale, e, nu, steps, a.d, limit + (size_t)t0 * TILE, static_cast<float*>(nullptr),
                            static_cast<const int32_t*>(nullptr), 1, static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr),
-                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE);
+                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE);
     }
     NearPairs r{};
     r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks;
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
     for (int i = 0; i < plan.bands; ++i) {
         if (i > 0) {
-            err = pairs_tighten(r, kk, b.scale, e, nu, a.d, s);
+            err = pairs_tighten(r, kk, b.scale, e, nu, a.d, left.row, s);       // (no rows are left yet)
             if (err != hipSuccess) return err;
         }
         r.from = i > 0 ? plan.to[i - 1] : 0; r.to = plan.to[i]; r.nseg = plan.nseg[i];
@@ -1749,7 +1751,7 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
         }
         hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
                            plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound, static_cast<float*>(nullptr), static_cast<const int32_t*>(nullptr), 1,
-                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr), static_cast<int32_t*>(nullptr));
+                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr), static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr));
         p.nseg = plan.nseg; p.nsub = plan.nsub;
         sel.nsub = plan.nsub; sel.by_position = 0; sel.merge = 0; sel.next_bound = nullptr;
         if (plan.stages == 2) {
@@ -2173,7 +2175,7 @@ hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const N
         sel.nq_batch = nqb; sel.q0 = t0 * TILE;
         auto bounds = [&](int sets, const int32_t* steps_of) {
             hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, sets, 5, nqb, t0 * TILE, kk, o.all.negh, b.scale, p.e, p.nu,
-                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale, static_cast<int32_t*>(nullptr));
+                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale, static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr));
         };
         NearList l{};
         l.gap = o.gap; l.T = T; l.region = o.region; l.reach = reach; l.n_pos = T * TILE; l.q0 = t0 * TILE; l.nq = nqb;

@@ -29,6 +29,7 @@ hipError_t pairs_left(const NearPairs& p, int kk, const NearScale* sc, float e, 
 // The n rows left from `first` on, with lists [n][cap] of (product value, position): those that overflowed get the distance that follows
 // and an empty list, the others a distance that nothing is within.
 hipError_t pairs_again(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int first, int n, const PairsLeft& left, hipStream_t s);
-hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, hipStream_t s);
+// last: by position, entries after the last call, 0 at first
+hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int32_t* last, hipStream_t s);
 
 }  // namespace slhc
