@@ -15,6 +15,7 @@
 namespace slhc {
 
 typedef float v4f __attribute__((ext_vector_type(4)));
+typedef float v4f_word __attribute__((ext_vector_type(4), aligned(4)));      // global loads of 16 bytes need the alignment of a word only
 constexpr float INF = __builtin_inff();
 constexpr int WAVES = 4;                   // per workgroup
 constexpr int SLAB = 64;                   // features of a row in LDS at a time
@@ -27,8 +28,9 @@ __device__ inline v4f direct_quad(const float* __restrict__ X, long long row, in
     if (row < 0 || t >= d) return v;
     const float* x = X + (size_t)row * d + t;
     if (vec4) return *reinterpret_cast<const v4f*>(x);
+    if (t + 4 <= d) return *reinterpret_cast<const v4f_word*>(x);
 #pragma unroll
-    for (int e = 0; e < 4; ++e)
+    for (int e = 0; e < 3; ++e)
         if (t + e < d) v[e] = x[e];
     return v;
 }

@@ -216,8 +216,16 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
                 } else {
+                    // (rows that begin on any word; 16-byte loads of them: 1000 x 100 000 x 99 fused search 134 us by single values, 122 so)
+                    const int left = src[i] < 0 ? 0 : p.d - col;
+                    if (left >= 8) {
+                        const v4f a = reinterpret_cast<const v4f_word*>(x)[0], b = reinterpret_cast<const v4f_word*>(x)[1];
 #pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = (src[i] >= 0 && col + e < p.d) ? x[e] : 0.f;
+                        for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+                    } else {
+#pragma unroll
+                        for (int e = 0; e < 8; ++e) v[e] = e < left ? x[e] : 0.f;
+                    }
                 }
                 v8h h;
 #pragma unroll
