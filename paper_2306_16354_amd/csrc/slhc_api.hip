@@ -558,6 +558,12 @@ constexpr float LOWER_FACTOR = SLHC_LOWER_FACTOR;
 #define SLHC_LOWER_MIN_ROWS 4096
 #endif
 constexpr int LOWER_MIN_ROWS = SLHC_LOWER_MIN_ROWS;
+// ... and components of any size where there are this many rows in all: a row that the falling threshold cuts off costs no evaluation,
+// and the row it has met last still bounds its component in the next round.  Large components only / all, in us: 300k x 32 in
+// clusters of 100 21 100 and 16 600, 500k x 16 in tight ones of 250 12 400 and 10 300, 150k x 8 8800 and 7400, 2M x 32 in tight
+// ones of 100 44 000 and 41 000, 1M x 16 in a thousand zipf ones the same; 60k x 20 and 20k x 64 the same, where which rows are asked
+// again then stays the same in every run.
+constexpr int64_t LOWER_ALL_ROWS = 131072;
 constexpr int NESTED_K = 8;
 // pruned connection sweeps: a launch with fewer non-empty panels than this splits every panel's scan into parts
 // so that about this many work items result, at most SPLIT_MAX_PARTS per panel
@@ -2315,8 +2321,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                 HIP_TRY(slhc::order_tile_colours(o.colour_s, o.Ns, o.tile_colour, s));
                 // rows per component (vals_b is free until the edge sort): which components may lower
                 // their shared threshold during the sweep
-                HIP_TRY(slhc::order_fill_i32(reinterpret_cast<int32_t*>(ws.vals_b), (int)N, 0, s));
-                HIP_TRY(slhc::forest_component_sizes(o.colour_s, o.Ns, (int)N, reinterpret_cast<int32_t*>(ws.vals_b), s));
+                if (N < LOWER_ALL_ROWS) {
+                    HIP_TRY(slhc::order_fill_i32(reinterpret_cast<int32_t*>(ws.vals_b), (int)N, 0, s));
+                    HIP_TRY(slhc::forest_component_sizes(o.colour_s, o.Ns, (int)N, reinterpret_cast<int32_t*>(ws.vals_b), s));
+                }
             }
             float ms_round_kernels = 0.f;
             // one cross-colour 1-NN sweep for `n` listed rows, and its answers applied to the forest
@@ -2375,7 +2383,7 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
 #ifndef SLHC_STUDY_NO_LOWERING
                     p.comp_best_lower = ws.vals_a;      // lowered in place; forest_apply_queries reads the final values
                     p.comp_lower_factor = LOWER_FACTOR;
-                    p.comp_size = reinterpret_cast<const int32_t*>(ws.vals_b);
+                    p.comp_size = N < LOWER_ALL_ROWS ? reinterpret_cast<const int32_t*>(ws.vals_b) : nullptr;
                     p.comp_lower_min_size = LOWER_MIN_ROWS;
 #endif
 #ifdef SLHC_PHASE_TIMERS

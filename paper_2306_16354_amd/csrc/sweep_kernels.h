@@ -88,8 +88,7 @@ struct SweepParams {
     // 1.4 times the distance to the nearest foreign row.
     float comp_lower_factor;
     // optional: comp_size[c] = rows of component c; only components of at least comp_lower_min_size rows
-    // lower their word.  A component that fits a few panels gains little from a falling threshold, and
-    // every row that ends without an exact answer has to be asked again in the next round.
+    // lower their word then.
     const int32_t* comp_size;
     int comp_lower_min_size;
     unsigned int* panel_counter;  // optional device word, zero at launch: panels are taken from it one at

@@ -353,6 +353,53 @@ __device__ inline void group8_list_insert(bool want, unsigned long long key, int
     }
 }
 
+// Lists of one key (k = 1), rows of up to 64 columns: 32 pairs per pass, four to each group of 8 lanes.  A pass is a chain of waits (queue,
+// rows in the L2, reduction, minimum) whatever it holds, and an LDS minimum takes the keys in any order.  The sums are group8_sqdist's.
+// In clusters that lie many radii apart these passes were half of a connection sweep: 2M x 32 in tight clusters of 100 rows, 18.3 ms of
+// sweeps by eight pairs with a seed per lane and only large components lowering their threshold, 15.3 by 32 pairs with a seed per query,
+// 12.7 with all components lowering theirs and a seed of every eight lanes.
+constexpr int RESOLVE_WIDE_D = 64;
+template <bool VEC4, typename Entry>
+__device__ inline void resolve_pairs_of_32(const SweepLds<1>& L, int qcount, Entry entry, const float* __restrict__ Xq_, const float* __restrict__ Xc_,
+                                           const int32_t* __restrict__ c_id, int d)
+{
+    const int lane = threadIdx.x & 63, grp = lane >> 3, g8 = lane & 7;
+    const int w32 = (threadIdx.x >> 6) * 32;
+    const global_floats Xq = (global_floats)Xq_, Xc = (global_floats)Xc_;
+    for (int s = 0; s < qcount; s += 32) {
+        int ql[4], cid[4];
+        v4f a0[4], a1[4], b0[4], b1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) {
+            const int e = s + 8 * u + grp;
+            int cg;
+            entry(e < qcount ? e : s, &ql[u], &cg);                     // (beyond the end: the first one again)
+            const int qrow = L.qid[w32 + ql[u]];
+            const global_floats xa = Xq + (size_t)qrow * d, xb = Xc + (size_t)cg * d;
+            cid[u] = c_id ? ((global_ints)c_id)[cg] : cg;
+            a0[u] = load_quad<VEC4>(xa, 4 * g8, d); b0[u] = load_quad<VEC4>(xb, 4 * g8, d);
+            a1[u] = load_quad<VEC4>(xa, 4 * g8 + 32, d); b1[u] = load_quad<VEC4>(xb, 4 * g8 + 32, d);
+        }
+        float s0[4], s1[4];
+#pragma unroll
+        for (int u = 0; u < 4; ++u) { s0[u] = quad_sqdist(a0[u], b0[u], 0.f); s1[u] = quad_sqdist(a1[u], b1[u], 0.f); }
+#pragma unroll
+        for (int o = 1; o < 8; o <<= 1) {
+#pragma unroll
+            for (int u = 0; u < 4; ++u) { s0[u] += __shfl_xor(s0[u], o); s1[u] += __shfl_xor(s1[u], o); }
+        }
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (g8 == 0 && s + 8 * u + grp < qcount) atomicMin(&L.lists[w32 + ql[u]], make_key(s0[u] + s1[u], cid[u]));
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+            if (g8 == 0 && s + 8 * u + grp < qcount)
+                L.bounds[w32 + ql[u]] = L.hqs[w32 + ql[u]] - 0.5f * __uint_as_float((unsigned int)(L.lists[w32 + ql[u]] >> 32));
+    }
+    __builtin_amdgcn_wave_barrier();
+}
+
 // resolve_queue: re-evaluates every queued pair exactly (eight pairs per pass, 8 lanes each),
 // drops those that do not beat their query's current k-th entry, inserts the rest into the query
 // lists and refreshes the bounds.
@@ -368,6 +415,13 @@ __device__ __attribute__((noinline)) void resolve_queue(int qcount, int col0, co
     unsigned long long* mylists = L.lists + (size_t)wave * 32 * KL;
     __builtin_amdgcn_wave_barrier();
     const int grp = lane >> 3, g8 = lane & 7;
+    if constexpr (KL == 1) {
+        if (d <= RESOLVE_WIDE_D && qcount > 8) {
+            resolve_pairs_of_32<VEC4>(L, qcount, [&](int e, int* ql, int* cg) { const unsigned int x = myq[e]; *ql = (int)(x >> 8); *cg = col0 + (int)(x & 255u); },
+                                      Xq, Xc, c_id, d);
+            return;
+        }
+    }
     for (int s = 0; s < qcount; s += 8) {
         const int e = s + grp;
         const bool valid = e < qcount;
@@ -437,14 +491,25 @@ __device__ __attribute__((noinline)) SeedPick seed_block(v16f t, int b, SeedPick
 template <int KL, bool VEC4>
 __device__ __attribute__((noinline)) void seed_resolve(SeedPick pick, int col0, const float* __restrict__ Xq,
                                                        const float* __restrict__ Xc,
-                                                       const int32_t* __restrict__ c_id, int d, int k)
+                                                       const int32_t* __restrict__ c_id, int d, int k, bool few)
 {
     const SweepLds<KL> L(sweep_smem);
     const int lane = threadIdx.x & 63;
     const int wave = threadIdx.x >> 6;
     const int l32 = lane & 31;
     unsigned short* myq = L.queues + wave * QCAP;
-    const bool has = pick.cl >= 0 && L.qid[wave * 32 + l32] >= 0;
+    // (of the two lanes that hold a query's accumulators, the one with the larger)
+    const float other = __shfl_xor(pick.cl >= 0 ? pick.v : -__builtin_inff(), 32);
+    bool has = pick.cl >= 0 && L.qid[wave * 32 + l32] >= 0 && (pick.v > other || (pick.v == other && lane < 32));
+    if (few) {
+        // only the lightest edge is of use: of every 8 lanes the one whose pair looks nearest, together one pass
+        const float near = has ? L.hqs[wave * 32 + l32] - pick.v : __builtin_inff();
+        float least = near;
+        least = fminf(least, __shfl_xor(least, 1));
+        least = fminf(least, __shfl_xor(least, 2));
+        least = fminf(least, __shfl_xor(least, 4));
+        has = has && near == least;
+    }
     const unsigned long long mask = __ballot(has);
     if (mask == 0ull) return;
     const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(mask >> 32),
@@ -869,7 +934,7 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel(SweepParams p)
                 pick = seed_block<KL, MASKED>(acc[1], 1, pick, seed_tag, col0, 0, N);
                 pick = seed_block<KL, MASKED>(acc[2], 2, pick, seed_tag, col0, 0, N);
                 pick = seed_block<KL, MASKED>(acc[3], 3, pick, seed_tag, col0, 0, N);
-                seed_resolve<KL, VEC4>(pick, col0, Xq, Xc, p.c_id, d, k);
+                seed_resolve<KL, VEC4>(pick, col0, Xq, Xc, p.c_id, d, k, false);
                 bound = bounds[my_q_local];
             }
             // ---- tile epilogue: filter (hot), then compact / re-evaluate / select (rare) ----
@@ -1444,6 +1509,23 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
             wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 8));
             wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 16));
         };
+        auto lower_word = [&]() {
+            if constexpr (KL == 1 && MASKED) {
+                // the lightest exact edge any query of this wavefront holds now
+                unsigned int best = my_qrow >= 0 ? (unsigned int)(mylists[l32] >> 32) : 0x7f800000u;
+#pragma unroll
+                for (int o = 16; o > 0; o >>= 1) {
+                    const unsigned int other = (unsigned int)__shfl_xor((int)best, o);
+                    best = other < best ? other : best;
+                }
+                // the word is lowered to `lower_factor` times that edge, not to the edge itself (see SweepParams)
+                const float target = p.comp_lower_factor * __uint_as_float(best);
+                if (target < thr_c) {
+                    if (lane == 0) atomicMin(p.comp_best_lower + panel_colour, __float_as_uint(target));
+                    thr_c = target;
+                }
+            }
+        };
         // a launch that starts from lists already written: their thresholds decide from the first tile on
         float first_thr = __builtin_inff();
         if (REGIONS && lists_in) {
@@ -1633,8 +1715,9 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
                 pick = seed_block<KL, MASKED>(acc[1], 1, pick, seed_tag, col0, tpar, N);
                 pick = seed_block<KL, MASKED>(acc[2], 2, pick, seed_tag, col0, tpar, N);
                 pick = seed_block<KL, MASKED>(acc[3], 3, pick, seed_tag, col0, tpar, N);
-                seed_resolve<KL, true>(pick, col0, Xq, Xc, p.c_id, d, k);
+                seed_resolve<KL, true>(pick, col0, Xq, Xc, p.c_id, d, k, lowering);
                 bound = bounds[my_q_local];
+                if (lowering) lower_word();
                 if (prune) refresh_wave_thr();     // the tile may leave no survivor to do it below
             }
             // ---- tile epilogue: filter (hot), then compact / re-evaluate / select (rare) ----
@@ -1744,30 +1827,15 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
                         pick = seed_block<KL, MASKED>(acc[2], 2, pick, my_tag, col0, tpar, N);
                         pick = seed_block<KL, MASKED>(acc[3], 3, pick, my_tag, col0, tpar, N);
                         if (!(pick.v >= bound)) pick.cl = -1;
-                        seed_resolve<KL, true>(pick, col0, Xq, Xc, p.c_id, d, k);
+                        seed_resolve<KL, true>(pick, col0, Xq, Xc, p.c_id, d, k, lowering);
                         bound = bounds[my_q_local];
+                        if (lowering) lower_word();
                         if (shared_thr) bound = fmaxf(bound, hqs[my_q_local] - 0.5f * thr_c);
                     }
                     const int colbuf_ = tpar;
                     SLHC_SELECT_TILE(KL, MASKED, true);
                     if (shared_thr) bound = bounds[my_q_local];         // this query's own bound again
-                    if constexpr (KL == 1 && MASKED) {
-                        if (lowering) {
-                            // the lightest exact edge any query of this wavefront holds now
-                            unsigned int best = my_qrow >= 0 ? (unsigned int)(mylists[l32] >> 32) : 0x7f800000u;
-#pragma unroll
-                            for (int o = 16; o > 0; o >>= 1) {
-                                const unsigned int other = (unsigned int)__shfl_xor((int)best, o);
-                                best = other < best ? other : best;
-                            }
-                            // the word is lowered to `lower_factor` times that edge, not to the edge itself (see SweepParams)
-                            const float target = p.comp_lower_factor * __uint_as_float(best);
-                            if (target < thr_c) {
-                                if (lane == 0) atomicMin(p.comp_best_lower + panel_colour, __float_as_uint(target));
-                                thr_c = target;
-                            }
-                        }
-                    }
+                    if (lowering) lower_word();
                 } else {
                     // few survivors: queue them for a later batch.  Blocks with many (the first tiles
                     // of a panel) are resolved at once afterwards, behind what already waits; their
