@@ -1804,61 +1804,55 @@ struct NearList {
     int most; int32_t *todo, *todo_mark;
 };
 constexpr int LIST_QUERIES = 512;          // per panel at most
+// Threads per panel: a list is a walk over thousands of tiles in the table, bound by the wait for each step's loads, and there are no
+// more panels than CUs.  Clustering 1M x 128, with 256 threads whose loads waited for one another: 4.4 ms of lists and 0.9 of first
+// tiles; 1.5 and 0.2 so.
+constexpr int LIST_THREADS = 1024, LIST_WAVES = LIST_THREADS / 64;
+static_assert(LIST_THREADS >= LIST_QUERIES, "near_segments gives every query a thread");
 
 struct NearSegments {
     int tile[LIST_QUERIES], lo[LIST_QUERIES], hi[LIST_QUERIES], reg[LIST_QUERIES];
     unsigned int reach[LIST_QUERIES];
-    int heads[8], count;
+    int heads[LIST_WAVES], count, wants;
 };
 // Returns the number of distinct tiles (runs of them) of the panel's `mine` queries; a barrier at the end.
 __device__ inline int near_segments(const NearList& p, NearSegments& g, int base, int mine)
 {
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     if (tid == 0) g.count = 0;
-    for (int i = tid; i < mine; i += 256) { g.lo[i] = 0x7fffffff; g.hi[i] = -1; g.reach[i] = 0u; }
+    if (tid < mine) { const int i = tid; g.lo[i] = 0x7fffffff; g.hi[i] = -1; g.reach[i] = 0u; }
     auto pos_of = [&](int i) -> int { return p.pos ? p.pos[p.q0 + base + i] : p.q0 + base + i; };
-    int at_pos[2];
-    bool head[2];
-    unsigned long long heads[2];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int i = tid + 256 * r;
-        at_pos[r] = i < mine ? pos_of(i) : -1;
-        head[r] = i < mine && (i == 0 || (pos_of(i - 1) >> 7) != (at_pos[r] >> 7));
-        heads[r] = __ballot(head[r]);
-        if (lane == 0) g.heads[r * 4 + wave] = __popcll(heads[r]);
-    }
+    const int at_pos = tid < mine ? pos_of(tid) : -1;
+    const bool head = tid < mine && (tid == 0 || (pos_of(tid - 1) >> 7) != (at_pos >> 7));
+    const unsigned long long heads = __ballot(head);
+    if (lane == 0) g.heads[wave] = __popcll(heads);
     __syncthreads();
     int nseg = 0;
-    for (int w = 0; w < 8; ++w) nseg += g.heads[w];
-#pragma unroll
-    for (int r = 0; r < 2; ++r) {
-        const int i = tid + 256 * r;
-        if (i < mine) {
-            int at = -1;
-            for (int w = 0; w < r * 4 + wave; ++w) at += g.heads[w];
-            at += __popcll(heads[r] & (~0ull >> (63 - lane)));
-            const int t = at_pos[r] >> 7;
-            const bool fine = at_pos[r] >= 0 && at_pos[r] < p.n_pos;
-            if (head[r]) { g.tile[at] = fine ? t : -1; g.reg[at] = fine ? p.region[t] : -1; }
-            float reach = -1.f;
-            if (!fine) {}
-            else if (p.colour) {
-                const int c = p.colour[at_pos[r]];
-                if ((unsigned int)c < (unsigned int)p.n_rows) {
-                    reach = __uint_as_float(p.threshold[c]);
-                    atomicMin(&g.lo[at], c); atomicMax(&g.hi[at], c);
-                }
-            } else reach = p.reach[base + i];
-            // (what a bound on a table entry's rounding can hide; 0 is left for a tile none of whose queries needs anything)
-            if (reach >= 0.f) atomicMax(&g.reach[at], __float_as_uint(fmaxf(reach * (1.f + 1e-5f), 1e-37f)));
-        }
+    for (int w = 0; w < LIST_WAVES; ++w) nseg += g.heads[w];
+    if (tid < mine) {
+        int at = -1;
+        for (int w = 0; w < wave; ++w) at += g.heads[w];
+        at += __popcll(heads & (~0ull >> (63 - lane)));
+        const int t = at_pos >> 7;
+        const bool fine = at_pos >= 0 && at_pos < p.n_pos;
+        if (head) { g.tile[at] = fine ? t : -1; g.reg[at] = fine ? p.region[t] : -1; }
+        float reach = -1.f;
+        if (!fine) {}
+        else if (p.colour) {
+            const int c = p.colour[at_pos];
+            if ((unsigned int)c < (unsigned int)p.n_rows) {
+                reach = __uint_as_float(p.threshold[c]);
+                atomicMin(&g.lo[at], c); atomicMax(&g.hi[at], c);
+            }
+        } else reach = p.reach[base + tid];
+        // (what a bound on a table entry's rounding can hide; 0 is left for a tile none of whose queries needs anything)
+        if (reach >= 0.f) atomicMax(&g.reach[at], __float_as_uint(fmaxf(reach * (1.f + 1e-5f), 1e-37f)));
     }
     __syncthreads();
     return nseg;
 }
 
-__global__ void __launch_bounds__(256) near_list_kernel(NearList p)
+__global__ void __launch_bounds__(LIST_THREADS) near_list_kernel(NearList p)
 {
     __shared__ NearSegments g;
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
@@ -1893,45 +1887,84 @@ __global__ void __launch_bounds__(256) near_list_kernel(NearList p)
     // (panels of few queries per tile have many tiles: several workgroups share the candidates of one, see gridDim.y)
     const bool shared = gridDim.y > 1;
     int32_t* counter = shared ? p.list_len + panel : &g.count;
+    // (two strips of 64 tiles and four of the panel's own at a time, their eight table entries read side by side whether they decide or not,
+    // where any of them may)
     auto scan = [&]() {
-        for (int i0 = (blockIdx.y * 4 + wave) * 64; i0 < n; i0 += 256 * gridDim.y) {
-            const int i = i0 + lane;
-            const int t = i < n ? (from ? (int)from[i] : i) : -1;
-            bool keep = false;
-            const bool fine = t >= 0 && t < p.T;
-            const int tc = fine && p.colour ? p.tile_colour[t] : -1, tr = fine ? p.region[t] : -1;
-            for (int s0 = 0; s0 < nseg && __any(fine && !keep); s0 += 4) {
-                bool k4[4];
+        for (int i0 = (blockIdx.y * LIST_WAVES + wave) * 128; i0 < n; i0 += 2 * LIST_THREADS * gridDim.y) {
+            int t[2], tc[2], tr[2];
+            bool fine[2], keep[2] = {false, false};
 #pragma unroll
-                for (int e = 0; e < 4; ++e) k4[e] = fine && s0 + e < nseg && needs(s0 + e, t, tc, tr);      // (loads side by side)
-                keep = keep || k4[0] || k4[1] || k4[2] || k4[3];
+            for (int u = 0; u < 2; ++u) {
+                const int i = i0 + 64 * u + lane;
+                t[u] = i < n ? (from ? (int)from[i] : i) : -1;
+                fine[u] = t[u] >= 0 && t[u] < p.T;
+                if (!fine[u]) t[u] = 0;
             }
-            const unsigned long long m = __ballot(keep);
-            int at = 0;
-            if (lane == 0 && m) at = atomicAdd(counter, __popcll(m));
-            at = __shfl(at, 0);
-            if (keep) list[at + __popcll(m & (lane ? ~0ull >> (64 - lane) : 0ull))] = (unsigned short)t;
+#pragma unroll
+            for (int u = 0; u < 2; ++u) { tc[u] = p.colour ? p.tile_colour[t[u]] : -1; tr[u] = p.region[t[u]]; }
+            for (int s0 = 0; s0 < nseg && __any((fine[0] && !keep[0]) || (fine[1] && !keep[1])); s0 += 4) {
+                bool may[2][4], any = false;
+                unsigned int row[4];
+                float r[4], gap[2][4];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) {
+                    const int seg = s0 + e < nseg ? s0 + e : nseg - 1;
+                    const int st = __builtin_amdgcn_readfirstlane(g.tile[seg]), sr = __builtin_amdgcn_readfirstlane(g.reg[seg]);
+                    const int lo = __builtin_amdgcn_readfirstlane(g.lo[seg]), hi = __builtin_amdgcn_readfirstlane(g.hi[seg]);
+                    const unsigned int reach = (unsigned int)__builtin_amdgcn_readfirstlane((int)g.reach[seg]);
+                    r[e] = __uint_as_float(reach);
+                    row[e] = (unsigned int)(st < 0 ? 0 : st);
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        may[u][e] = fine[u] && reach != 0u && st >= 0 && !(tc[u] >= 0 && lo == tc[u] && hi == tc[u]) &&
+                                    (sr >= 0 && sr == tr[u]) == (p.what == LIST_LOCAL);
+                        any = any || may[u][e];
+                    }
+                }
+                if (!__any(any)) continue;
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) gap[u][e] = p.gap[(size_t)row[e] * p.T + t[u]];
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) keep[u] = keep[u] || (may[u][e] && gap[u][e] <= r[e]);      // (NaN: no)
+            }
+#pragma unroll
+            for (int u = 0; u < 2; ++u) {
+                const unsigned long long m = __ballot(keep[u]);
+                int at = 0;
+                if (lane == 0 && m) at = atomicAdd(counter, __popcll(m));
+                at = __shfl(at, 0);
+                if (keep[u]) list[at + __popcll(m & (lane ? ~0ull >> (64 - lane) : 0ull))] = (unsigned short)t[u];
+            }
         }
         __syncthreads();
     };
     scan();
     if (p.most > 0 && g.count > p.most) {
         // which of the panel's tiles want that many (there are few such tiles: rows with fewer near rows than they ask for)
-        __syncthreads();
-        for (int seg = wave; seg < nseg; seg += 4) {
+        for (int seg = 0; seg < nseg; ++seg) {
+            __syncthreads();
+            if (tid == 0) g.wants = 0;
+            __syncthreads();
             int wants = 0;
-            for (int t = lane; t < p.T; t += 64) wants += needs(seg, t, p.colour ? p.tile_colour[t] : -1, p.region[t]) ? 1 : 0;
+            for (int t = tid; t < p.T; t += LIST_THREADS) wants += needs(seg, t, p.colour ? p.tile_colour[t] : -1, p.region[t]) ? 1 : 0;
 #pragma unroll
             for (int o = 32; o > 0; o >>= 1) wants += __shfl_xor(wants, o);
-            if (lane == 0 && wants > p.most) {
+            if (lane == 0 && wants) atomicAdd(&g.wants, wants);
+            __syncthreads();
+            if (tid == 0 && g.wants > p.most) {
                 g.reach[seg] = 0u;
                 const int st = g.tile[seg];
                 if (atomicExch(p.todo_mark + st, 1) == 0) p.todo[2 + atomicAdd(p.todo, 1)] = st;
             }
         }
+        __syncthreads();
         if (tid == 0) g.count = 0;
         __syncthreads();
-        for (int i = tid; i < mine; i += 256) {
+        for (int i = tid; i < mine; i += LIST_THREADS) {
             const int t = (p.q0 + base + i) >> 7;               // (queries in order)
             for (int seg = 0; seg < nseg; ++seg)
                 if (g.tile[seg] == t && g.reach[seg] == 0u) p.reach[base + i] = -1.f;
@@ -1957,30 +1990,32 @@ __global__ void __launch_bounds__(256) near_list_kernel(NearList p)
 // tiles, the nearest in each of four interleaved quarters of all tiles.
 constexpr int FIRST_TILES = 32;
 static int near_list_stride(int T) { return T > FIRST_TILES ? T : FIRST_TILES; }
-__global__ void __launch_bounds__(256) near_first_kernel(NearList p)
+__global__ void __launch_bounds__(LIST_THREADS) near_first_kernel(NearList p)
 {
     __shared__ NearSegments g;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int panel = blockIdx.x, base = panel * p.panel_queries;
     const int mine = p.nq - base < p.panel_queries ? p.nq - base : p.panel_queries;
     if (mine <= 0) { if (tid == 0) p.list_len[panel] = 0; return; }
     const int nseg = near_segments(p, g, base, mine);
     unsigned short* list = p.list + (size_t)panel * p.list_stride;
     const int picks = nseg < 8 ? nseg : 8;
-    for (int i = 0; i < picks; ++i) {
+    for (int i = wave >> 2; i < picks; i += LIST_WAVES / 4) {                  // (four wavefronts to a tile, a quarter each)
         const int s = (int)((long long)i * nseg / picks);
         const int st = g.tile[s];
         unsigned long long best = ~0ull;
-        if (st >= 0)
-            for (int t = tid; t < p.T; t += 256) {
+        if (st >= 0) {
+            const float* gaps = p.gap + (size_t)st * p.T;
+            const int colour = g.lo[s] == g.hi[s] ? g.lo[s] : -2;
+#pragma unroll 4
+            for (int t = tid & 255; t < p.T; t += 256) {                                  // (both read whether they decide or not)
                 const int tc = p.tile_colour[t];
-                if (tc >= 0 && g.lo[s] == tc && g.hi[s] == tc) continue;
-                const float gap = p.gap[(size_t)st * p.T + t];
-                if (!(gap >= 0.f)) continue;
+                const float gap = gaps[t];
                 const unsigned int off = (unsigned int)(t > st ? t - st : st - t);
                 const unsigned long long key = ((unsigned long long)__float_as_uint(gap) << 32) | (off << 16) | (unsigned int)t;
-                best = key < best ? key : best;
+                if (gap >= 0.f && !(tc >= 0 && tc == colour)) best = key < best ? key : best;
             }
+        }
 #pragma unroll
         for (int o = 32; o > 0; o >>= 1) {
             const unsigned long long other = __shfl_xor(best, o);
@@ -2193,7 +2228,7 @@ hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const N
         auto make_list = [&](int what, int from, int to, int32_t* step_to) {
             l.what = what; l.from = from >= 0 ? list[from] : nullptr; l.from_len = from >= 0 ? len[from] : nullptr;
             l.list = list[to]; l.list_len = len[to]; l.list_step = step_to;
-            hipLaunchKernelGGL(near_list_kernel, per_panel, dim3(256), 0, s, l);
+            hipLaunchKernelGGL(near_list_kernel, per_panel, dim3(LIST_THREADS), 0, s, l);
         };
         hipError_t e = hipSuccess;
         // 1. the tiles around every panel: first bounds (of each query in the copy that holds its region, or in the other)
@@ -2526,8 +2561,8 @@ hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBu
             l.q0 = (int)q0; l.nq = nq; l.panel_queries = panel_queries;
             for (int i = 0; i <= pass; ++i) {
                 l.what = i ? LIST_CROSS : LIST_LOCAL; l.list = list[i]; l.list_len = len[i];
-                if (pass) hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels), dim3(256), 0, s, l);
-                else hipLaunchKernelGGL(near_first_kernel, dim3((unsigned)panels), dim3(256), 0, s, l);
+                if (pass) hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels), dim3(LIST_THREADS), 0, s, l);
+                else hipLaunchKernelGGL(near_first_kernel, dim3((unsigned)panels), dim3(LIST_THREADS), 0, s, l);
                 hipLaunchKernelGGL(near_items_kernel, dim3(1), dim3(1024), 0, s, len[i], panels, items[i], panel_queries, nq,
                                    pass ? o.tile_steps : nullptr);
             }
@@ -2550,7 +2585,7 @@ hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBu
     r.threshold0 = a.threshold0;
     hipLaunchKernelGGL(near_split_kernel, per_row, dim3(256), 0, s, r);
     // the few that are left
-    constexpr int capl = 256, left_waves = 4, left_queries = 256, left_slices = 16;
+    constexpr int capl = 256, left_waves = 4, left_queries = 256, left_slices = 8;
     l.pos = a.pos_left; l.n_dev = r.count_left; l.panel_queries = left_queries;
     p.qpos = a.pos_left; p.n_dev = r.count_left;
     p.counts = a.counts_left; p.capl = capl; p.reach = a.reach_left;
@@ -2582,7 +2617,7 @@ hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBu
         hipLaunchKernelGGL(near_todo_clear_kernel, dim3(8), dim3(256), 0, s, len[0], (long long)(reinterpret_cast<unsigned char*>(items[0]) - reinterpret_cast<unsigned char*>(len[0])) / 4);
         for (int i = 0; i < 2; ++i) {
             l.what = i ? LIST_CROSS : LIST_LOCAL; l.list = list[i]; l.list_len = len[i];
-            hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels, left_slices), dim3(256), 0, s, l);
+            hipLaunchKernelGGL(near_list_kernel, dim3((unsigned)panels, left_slices), dim3(LIST_THREADS), 0, s, l);
             hipLaunchKernelGGL(near_items_kernel, dim3(1), dim3(1024), 0, s, len[i], panels, items[i], left_queries, nq, static_cast<unsigned long long*>(nullptr));
         }
         p.panels = panels;
