@@ -700,13 +700,17 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     const bool mine_here = !(LISTED && MODE == NEAR_MAXIMA && p.side) || (p.side == 1) == (first_reg >= 0);
 
     const int ntiles = seg < used ? (used - seg + nseg - 1) / nseg : 0;
-    // (called for i = 0, 1, ...: a lane holds one of 64 entries of the list)
-    int listed = 0;
+    // (called for i = 0, 1, ...: a lane holds one of 64 entries of the list, and that tile's region and colour: a load of one word
+    // per tile makes every tile wait for it, behind the stage for the next tile as well.  Clustering 100k x 64, connection rounds: 1.69 ms of
+    // sweeps for first edges and 0.49 for nearest rows, 1.59 and 0.42 so; 1M x 128: 9.9 and 1.6 ms, 9.3 and 1.4, emission 17.9 and 17.4)
+    int listed = 0, listed_reg = -1, listed_colour = -1;
     auto tile_at = [&](int i) -> int {
         if (!LISTED) return near_tile_at(p, seg, nseg, i);
         if ((i & 63) == 0) {
             const int j = seg + (i + lane) * nseg;
             listed = j < used ? (int)list[j * list_step] : 0;
+            if (p.side) listed_reg = p.region[listed];
+            if (COLOURED) listed_colour = p.tile_colour[listed];
         }
         return __builtin_amdgcn_readlane(listed, i & 63);
     };
@@ -722,21 +726,22 @@ __global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
     };
     int next = ntiles > 0 ? tile_at(0) : 0;
     if (ntiles > 0) stage(0, next);
-    int next_colour = LISTED && COLOURED && ntiles > 0 ? p.tile_colour[next] : -1;
+    int next_colour = LISTED && COLOURED ? __builtin_amdgcn_readlane(listed_colour, 0) : -1;
+    int next_reg = LISTED ? __builtin_amdgcn_readlane(listed_reg, 0) : -1;
     const int per_part = MODE == NEAR_MAXIMA ? (ntiles + p.parts - 1) / p.parts : 0;
     int part = 0, part_end = per_part;
     for (int i = 0; i < ntiles; ++i) {
         near_lds_ready();
-        const int pos0 = next * TILE, colour_here = next_colour;
+        const int pos0 = next * TILE, colour_here = next_colour, tile_reg = next_reg;
         if (i + 1 < ntiles) {
             next = tile_at(i + 1);
-            if (LISTED && COLOURED) next_colour = p.tile_colour[next];
+            if (LISTED && COLOURED) next_colour = __builtin_amdgcn_readlane(listed_colour, (i + 1) & 63);
+            if (LISTED) next_reg = __builtin_amdgcn_readlane(listed_reg, (i + 1) & 63);
             stage(i + 1, next);
         }
         const unsigned char* tb = near_smem + (i & 1) * BUF;
         bool ok0 = true, ok1 = true;
         if (LISTED && p.side) {
-            const int tile_reg = p.region[pos0 >> 7];
             ok0 = (tile_reg >= 0 && tile_reg == mine.reg[0]) == (p.side == 1);
             ok1 = (tile_reg >= 0 && tile_reg == mine.reg[1]) == (p.side == 1);
         }
