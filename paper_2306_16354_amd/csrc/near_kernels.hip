@@ -216,12 +216,20 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
 #pragma unroll
                     for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
                 } else {
-                    // (rows that begin on any word; 16-byte loads of them: 1000 x 100 000 x 99 fused search 134 us by single values, 122 so)
+                    // rows that begin on any word, 16 bytes at a time all the same; the last values of a row come from its last eight, moved
+                    // down (a branch of its own for them costs another wait: 20 011 x 50 11.5 us, 9.4 so, by single values 8.4;
+                    // 1000 x 100 000 x 99 fused search 133 us by single values, 122 so)
                     const int left = src[i] < 0 ? 0 : p.d - col;
-                    if (left >= 8) {
-                        const v4f a = reinterpret_cast<const v4f_word*>(x)[0], b = reinterpret_cast<const v4f_word*>(x)[1];
+                    if (p.d >= 8) {
+                        const int by = left >= 8 ? 0 : 8 - left;
+                        v4f a = {0.f, 0.f, 0.f, 0.f}, b = {0.f, 0.f, 0.f, 0.f};
+                        if (left > 0) { a = reinterpret_cast<const v4f_word*>(x - by)[0]; b = reinterpret_cast<const v4f_word*>(x - by)[1]; }
 #pragma unroll
                         for (int e = 0; e < 4; ++e) { v[e] = a[e]; v[4 + e] = b[e]; }
+#pragma unroll
+                        for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+                            for (int e = 0; e < 8; ++e) v[e] = (by & o) ? (e + o < 8 ? v[e + o < 8 ? e + o : e] : 0.f) : v[e];
                     } else {
 #pragma unroll
                         for (int e = 0; e < 8; ++e) v[e] = e < left ? x[e] : 0.f;
