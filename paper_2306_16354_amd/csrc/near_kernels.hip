@@ -52,11 +52,16 @@ __global__ void __launch_bounds__(256) near_runs_kernel(const float* __restrict_
     const int run = blockIdx.x, tid = threadIdx.x;
     const int c0 = blockIdx.y * 256;
     const int cols = d - c0 < 256 ? d - c0 : 256;
-    int width = 1;
-    while (width < cols) width <<= 1;                       // threads per row
-    const int sub = 256 / width;                            // rows side by side
-    const int c = tid % width, g = tid / width;
-    const int samples = n < SAMPLE_RUNS * SAMPLE_PER_RUN ? n : SAMPLE_RUNS * SAMPLE_PER_RUN;
+    int log = 0;
+    while (1 << log < cols) ++log;
+    const int width = 1 << log, sub = 256 >> log;           // threads per row, rows side by side
+    const int c = tid & (width - 1), g = tid >> log;
+    // (sample i is row i n / samples; `samples` is n or a power of two, and must not be divided by: a division of 64 bits per sample made this
+    // kernel 31 KB of code, read anew by every call: 6.9 us, 4.9 so)
+    constexpr int MOST = SAMPLE_RUNS * SAMPLE_PER_RUN;
+    static_assert((MOST & (MOST - 1)) == 0, "the division below is a shift");
+    const bool every = n < MOST;
+    const int samples = every ? n : MOST;
     const int i0 = (int)((long long)run * samples / SAMPLE_RUNS), i1 = (int)((long long)(run + 1) * samples / SAMPLE_RUNS);
     float v[SAMPLE_PER_RUN];
     float sum = 0.f, cnt = 0.f;
@@ -64,7 +69,7 @@ __global__ void __launch_bounds__(256) near_runs_kernel(const float* __restrict_
     for (int j = 0; j < SAMPLE_PER_RUN; ++j) {
         const int i = i0 + g + j * sub;
         v[j] = __builtin_nanf("");
-        if (c < cols && i < i1) v[j] = X[(size_t)((long long)i * n / samples) * d + c0 + c];
+        if (c < cols && i < i1) v[j] = X[(every ? (size_t)i : (size_t)i * (size_t)n / MOST) * d + c0 + c];
     }
 #pragma unroll
     for (int j = 0; j < SAMPLE_PER_RUN; ++j)
