@@ -8,7 +8,8 @@ already resident in HBM.  Prints ONE JSON line:
   value      fused k-NN distance pairs per second = N^2 / (norm kernel + k-NN sweep kernel time),
              kernel times taken with HIP events on the launch stream inside every timed step
   ms_per_step   wall time of the whole step (the end-to-end single-linkage seconds x 1000)
-  roofline   the k-NN search against the MFMA peak of the multiply it runs (2*d FLOP per ordered pair); also against
+  roofline   the k-NN search against the MFMA peak of the multiply it runs (2*d FLOP per ordered pair; large searches multiply
+             a pair once for both orders, which frac_executed counts); also against
              the rate a register-only loop of that multiply sustains in the same run (empirical_peak)
   roofline_connect / roofline_forest   the connection sweeps (MFMA) and the Boruvka rounds (HBM)
   cpu_baseline  the CPU oracle's brute-force k-NN on a bounded sample of query rows, and its dense Prim +
@@ -17,8 +18,7 @@ already resident in HBM.  Prints ONE JSON line:
   pruned     the same workload through the default entry point (tile pruning on), outside the
              timed region: end-to-end seconds, stage times and the share of tile steps multiplied
 
-The timed step multiplies every (query panel, candidate tile) pair, as the paper's method does, so
-that pairs/s and the roofline fraction count real multiply-adds only.
+The timed step searches every pair of rows, as the paper's method does: no tile is skipped.
 
     python bench.py [--gpus 1] [--steps K] [--warmup W] [--workload c3]
 """
@@ -148,7 +148,8 @@ def main():
     # evaluated in float32 in each case, so the outputs are the same bits.
     half = args.knn_only or bool(stats[-1]["half_products"])
     split = half or bool(stats[-1]["split_products"])
-    products = 3.0 if split and not half else 1.0      # per multiply-add
+    once = half and (4096 <= N and d > 128 or 49_152 <= N and d > 64) and N < 1 << 24     # one product for both orders of a pair
+    products = 3.0 if split and not half else 0.5 if once else 1.0      # per multiply-add
     multiply = "v_mfma_f32_32x32x16_f16" if half else "v_mfma_f32_32x32x16_bf16" if split else "v_mfma_f32_32x32x2_f32"
     empirical_16bit_tflops = slhc.probe_f16_mfma(dev) if half else slhc.probe_bf16_mfma(dev)     # the same for that multiply
     peak_tflops = PEAK_16BIT_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
@@ -200,7 +201,9 @@ def main():
         "slhc_seconds": None if args.knn_only else ms_per_step / 1e3,
         "pct_fp32_mfma_peak": None if split else 100.0 * achieved_tflops / PEAK_FP32_MFMA_TFLOPS,
         "roofline": {
-            "kernel": "near_sweep_kernel / near_wide_kernel (maxima of a sample, emission), near_bounds_kernel, near_select_kernel" if half
+            "kernel": ("near_sweep_kernel / near_wide_kernel (maxima of a sample), near_bounds_kernel, " +
+                       ("pairs_kernel / pairs_wide_kernel" if once else "near_sweep_kernel / near_wide_kernel (emission)") +
+                       ", near_select_kernel") if half
                       else "sweep_kernel (fused distance tile + filter + top-k)" + (", products from split bf16 halves" if split else ""),
             "bound": "mfma",
             "achieved": achieved_tflops,
@@ -212,8 +215,8 @@ def main():
             "algorithmic_flop_per_launch": flops,
             "executed_mfma_flop_per_launch": products * flops,
             "frac_executed": products * achieved_tflops / peak_tflops,
-            "note": ("achieved counts the algorithmic 2 d N^2; the search executes one float16 product per multiply-add, and those "
-                     "of a sample of the candidates (every fifth tile at most) once more for its bounds, which frac_executed "
+            "note": ("achieved counts the algorithmic 2 d N^2; the search executes one float16 product per multiply-add"
+                     + (" of an unordered pair" if once else "") + ", and those of a sample of the candidates once more for its bounds, which frac_executed "
                      "leaves out; launch_ms holds the bounds and the exact evaluation of what is emitted too") if half else
                     ("achieved counts the algorithmic 2 d N^2 against the bf16 MFMA peak; the kernel executes three "
                      "bf16 products per multiply-add (frac_executed)") if split else "",

@@ -2531,8 +2531,9 @@ size_t near_linked_batch_bytes(long long rows)
 
 // The same in a row order: the queries (rows, qpos: ascending positions) meet the tiles only whose distance does not exceed their
 // component's threshold, which a pass over a few of the nearest tiles of other colours sets first.  Bound by the products of
-// the listed pairs (half of the time) and the lists.  1M x 128, five rounds of 1.3 million queries: 50 ms with the list kernels
-// (128 queries share what they stage, three products), 21 ms; with lists in equal shares per panel instead of equal items 36 ms.
+// the listed pairs (half of the time) and the exact edges.  1M x 128, five rounds of 1.3 million queries: 50 ms with the list kernels
+// (128 queries share what they stage, three products), 21 ms; with lists in equal shares per panel instead of equal items 36 ms;
+// 16 ms with lists walked by a thousand threads and what is read of a tile held by lanes.
 hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBuffers& b, hipStream_t s)
 {
     const int T = o.tiles;

@@ -1182,12 +1182,13 @@ slhc::NearOrder near_order_of(const OrderWs& o)
 // be the one that is wanted: of 700 rows (7 tiles) the search takes 14.4 ms and the list kernels 1.5 ms, of 1000 rows (8 tiles)
 // 1.8 and 1.55 ms, of 100 rows 3.3 and 0.8 ms (2M x 32: 22 and 4.7 ms).  Clusters a few radii apart do not need it, and there the
 // search costs little where it does not gain, and the connection rounds gain on both sides of the line: 200k x 64 in clusters of
-// 800 rows 1.4 and 1.7 ms, rounds 7.0 and 17.3 ms; of 120 rows 1.2 and 0.7 ms, rounds 5.9 and 11.6 ms.
+// 800 rows 1.4 and 1.7 ms, rounds 7.0 and 17.3 ms; of 120 rows 1.2 and 0.7 ms, rounds 5.9 and 11.6 ms.  (Both kinds of rounds have
+// become shorter since, by a quarter to a third.)
 constexpr unsigned long long NEAR_REGION_TILES = REGION_TILES;
 // Connection rounds go there too unless the clusters are tight against their distances: a row of another cluster is then known
 // up to a few 1e-4 of the spread of all rows, and where that is as much as a cluster's radius every row of a component may be the
 // one that is nearest (2M x 32 in clusters of 100 rows, a thousand radii apart: all rows are left to be searched, 57 ms of
-// rounds against the list kernels' 30).  The spread is about 0.6 sqrt(d) times the largest deviation of a column, so the line is
+// rounds against the list kernels' 30, which are 13 now).  The spread is about 0.6 sqrt(d) times the largest deviation of a column, so the line is
 // drawn where the rounding of two rows reaches a quarter of the radius.
 constexpr float NEAR_LINK_SPREAD = 360.f;
 

@@ -1416,7 +1416,8 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
             while (i < nscan) {
                 // connection sweeps, whose panels read thousands of bounds for the tiles they multiply, share the positions out
                 // among the wavefronts (all of them come here together, see thr_c0):
-                // 2M x 32, 20 000 bounds for 15 tiles, 24.4 -> 18.4 ms of connection sweeps (30 ms before scan_tile's runs of 32)
+                // 2M x 32, 20 000 bounds for 15 tiles, 24.4 -> 18.4 ms of connection sweeps (30 ms before scan_tile's runs of 32;
+                // 12.9 with the evaluation of 32 pairs at a time)
                 const int i_from = i;
                 if (SHARED_SCAN) i += wave * 64 * SCAN_AHEAD;
                 int found = 0x7fffffff;
