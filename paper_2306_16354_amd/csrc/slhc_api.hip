@@ -426,42 +426,43 @@ __global__ void __launch_bounds__(256) k_fetch_words(const uint32_t* __restrict_
 }
 
 // A few words from the device without a copy and a synchronisation (20 us): a kernel behind the work writes them to host
-// memory, with a sequence number last, and the host watches for that number.
+// memory, and the host watches for a sequence number there.  Either the words with the number last, in a word before them, or
+// 64-bit words with the number in the high half of each.  Each of the two has memory of its own: the number of one would be looked for
+// where the other keeps words of any value.
 struct Mailbox {
     PinnedHost box;
     hipStream_t s;
     uint32_t seq = 0;
-    static constexpr int WORDS = 4096;
+    static constexpr int WORDS = 4096, TAGGED = 8;
+    static constexpr size_t BYTES = TAGGED * sizeof(unsigned long long) + (WORDS + 16) * sizeof(uint32_t);
     explicit Mailbox(hipStream_t stream) : box(stream), s(stream) {}
     hipError_t open()
     {
-        const hipError_t e = box.alloc((WORDS + 16) * sizeof(uint32_t));
+        const hipError_t e = box.alloc(BYTES);
         if (e != hipSuccess) return e;
-        for (int i = 0; i < 16; ++i) slot()[i] = 0u;         // (another user's sequence numbers)
+        for (int i = 0; i < TAGGED; ++i) static_cast<volatile unsigned long long*>(tagged())[i] = 0ull;         // (another user's sequence numbers)
+        for (int i = 0; i < 16; ++i) static_cast<volatile uint32_t*>(words())[i] = 0u;
         return hipSuccess;
     }
-    volatile uint32_t* slot() { return static_cast<volatile uint32_t*>(box.p); }
-    uint32_t* words() { return static_cast<uint32_t*>(box.p); }
+    unsigned long long* tagged() { return static_cast<unsigned long long*>(box.p); }
+    uint32_t* words() { return reinterpret_cast<uint32_t*>(tagged() + TAGGED); }
     uint32_t next() { return ++seq; }
-    // until the sequence number last handed out has arrived
-    hipError_t wait()
+    // whether the sequence number last handed out has arrived
+    bool arrived() { return __atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq; }
+    // ... in the first n tagged words
+    bool arrived_tagged(int n)
     {
-        return until([&] { return __atomic_load_n(words(), __ATOMIC_ACQUIRE) == seq; });
+        for (int i = 0; i < n; ++i)
+            if ((uint32_t)(__atomic_load_n(tagged() + i, __ATOMIC_ACQUIRE) >> 32) != seq) return false;
+        return true;
     }
-    // until it has arrived in the high halves of the first n 64-bit words
-    hipError_t wait_tagged(int n)
-    {
-        return until([&] {
-            for (int i = 0; i < n; ++i)
-                if ((uint32_t)(__atomic_load_n(reinterpret_cast<unsigned long long*>(box.p) + i, __ATOMIC_ACQUIRE) >> 32) != seq) return false;
-            return true;
-        });
-    }
+    hipError_t wait() { return until([&] { return arrived(); }); }
+    hipError_t wait_tagged(int n) { return until([&] { return arrived_tagged(n); }); }
     template <typename F>
-    hipError_t until(F&& arrived)
+    hipError_t until(F&& there)
     {
         for (unsigned spins = 0;; ++spins) {
-            if (arrived()) return hipSuccess;
+            if (there()) return hipSuccess;
 #if defined(__x86_64__)
             __builtin_ia32_pause();
 #endif
@@ -469,10 +470,10 @@ struct Mailbox {
                 // an error ends the wait; so does a stream that has run dry without the number
                 const hipError_t q = hipStreamQuery(s);
                 if (q == hipErrorNotReady) continue;
-                if (arrived()) return hipSuccess;
+                if (there()) return hipSuccess;
                 if (q != hipSuccess) return q;
                 const hipError_t w = hipStreamSynchronize(s);
-                if (arrived()) return hipSuccess;
+                if (there()) return hipSuccess;
                 return w != hipSuccess ? w : hipErrorUnknown;
             }
         }
@@ -1887,13 +1888,13 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         auto enqueue_round = [&](int round) -> int {
             Mailbox& m = mail[round & 1];
             roots = roots / 2 + 1;
-            HIP_TRY(slhc::csr_round(f, round, (int)vertices, (int)roots, static_cast<unsigned long long*>(m.box.p), m.next(), s));
+            HIP_TRY(slhc::csr_round(f, round, (int)vertices, (int)roots, m.tagged(), m.next(), s));
             return SLHC_OK;
         };
         int32_t said[slhc::CSR_TOLD];
         auto read = [&](int which) -> int {
             HIP_TRY(mail[which].wait_tagged(slhc::CSR_TOLD));
-            for (int i = 0; i < slhc::CSR_TOLD; ++i) said[i] = (int32_t)static_cast<volatile unsigned long long*>(mail[which].box.p)[i];
+            for (int i = 0; i < slhc::CSR_TOLD; ++i) said[i] = (int32_t)static_cast<volatile unsigned long long*>(mail[which].tagged())[i];
             if (said[3] >= 20) {
                 set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", said[3]);
                 return SLHC_INVALID_ARG;
@@ -1942,7 +1943,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             nrounds = 0;
         }
         while (nrounds == 0) {
-            HIP_TRY(slhc::csr_tail(f, next, static_cast<unsigned long long*>(mail[1].box.p), mail[1].next(), s));
+            HIP_TRY(slhc::csr_tail(f, next, mail[1].tagged(), mail[1].next(), s));
             rc2 = read(1);
             if (rc2 != SLHC_OK) return rc2;
             if (said[2] != 0) {                            // (of a round before, behind which nothing was done)

@@ -1,4 +1,4 @@
-"""Workspace layouts, on the host: the layout code is compiled without its kernels and asked directly."""
+"""Workspace layouts and mailboxes, on the host: their code is compiled without the kernels and asked directly."""
 import os
 import subprocess
 
@@ -7,21 +7,30 @@ import pytest
 ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
 
 
-@pytest.fixture(scope="module")
-def report(tmp_path_factory):
+def host_program(name, out):
+    """The lines that tests/<name>.hip prints."""
     from paper_2306_16354_amd import binding, build
     if not os.path.exists(binding.library_path()):
         build.build_library(verbose=False)
     hipcc = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
-    out = tmp_path_factory.mktemp("layouts")
-    obj, exe = str(out / "layouts.o"), str(out / "layouts")
+    obj, exe = str(out / (name + ".o")), str(out / name)
     where = os.path.dirname(binding.library_path())
     subprocess.run([hipcc, "-O1", "--cuda-host-only", "--offload-arch=gfx950", "-std=c++17", "-w", "-c",
-                    os.path.join(ROOT, "tests", "workspace_layouts.hip"), "-o", obj], check=True, capture_output=True)
+                    os.path.join(ROOT, "tests", name + ".hip"), "-o", obj], check=True, capture_output=True)
     # (the device half of the file is not there)
     subprocess.run([hipcc, "-o", exe, obj, "-L" + where, "-lslhc", "-Wl,-rpath," + where, "-Wl,--unresolved-symbols=ignore-all"],
                    check=True, capture_output=True)
     return subprocess.run([exe], check=True, capture_output=True, text=True).stdout.splitlines()
+
+
+@pytest.fixture(scope="module")
+def report(tmp_path_factory):
+    return host_program("workspace_layouts", tmp_path_factory.mktemp("layouts"))
+
+
+# A mailbox that has carried one kind of message takes nothing of it for the other's sequence number.
+def test_messages_of_two_kinds_in_one_mailbox(tmp_path):
+    assert host_program("mailboxes", tmp_path) == ["checked 800"]
 
 
 def test_layouts_keep_within_their_bytes(report):
