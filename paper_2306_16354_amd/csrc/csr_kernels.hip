@@ -44,19 +44,20 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
     uint32_t best = INF_BITS;
     unsigned int lo = ~0u, hi = ~0u;
     int to = -1;
-    // (four entries side by side: their loads wait for memory together)
-    for (int e0 = o0; e0 < o1; e0 += 4) {
+    // (four entries side by side: their loads wait for memory together; unsigned, because the step behind the last ones may lie beyond 2^31)
+    const unsigned int end = o1 < 0 ? 0u : (unsigned int)o1;
+    for (unsigned int e0 = (unsigned int)o0; e0 < end; e0 += 4) {
         int u[4], cu[4];
         float w[4];
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
-            u[j] = e0 + j < o1 ? f.indices[e0 + j] : -1;
-            w[j] = e0 + j < o1 ? f.weights[e0 + j] : 0.f;
+            u[j] = e0 + j < end ? f.indices[e0 + j] : -1;
+            w[j] = e0 + j < end ? f.weights[e0 + j] : 0.f;
         }
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (FIRST) {
-                if (e0 + j < o1 && !in_range(u[j], f.V)) report(f, 23);
+                if (e0 + j < end && !in_range(u[j], f.V)) report(f, 23);
                 if (!(w[j] >= 0.f) || w[j] == __builtin_inff()) report(f, 24);
                 cu[j] = u[j];
             } else cu[j] = in_range(u[j], f.V) ? *reinterpret_cast<volatile int32_t*>(f.colour + u[j]) : -1;

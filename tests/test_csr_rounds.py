@@ -76,3 +76,27 @@ def test_chains(lib, run):
     a = np.arange(V - 1)
     w = np.where((a + 1) % run == 0, 1e6 + a, (a % run).astype(np.float64))
     check(lib, V, *csr(V, a, a + 1, w.astype(np.float32)))
+
+
+# as many entries as the call takes: the last row ends on the last number of 32 bits.  A path whose edges are stored 256 times in every row, the
+# weights in an order that makes chains of five vertices
+def test_largest_entry_count(lib):
+    V, L = 1 << 22, 512
+    E = V * L - 1
+    print(f"csr V={V} E={E}", flush=True)
+    dev = torch.device("cuda")
+    v = torch.arange(V, device=dev, dtype=torch.int32)
+    path_w = (torch.arange(V - 1, device=dev, dtype=torch.int32) * 3 % 5 + 1).float()
+    indices = torch.empty(V * L, dtype=torch.int32, device=dev)
+    weights = torch.empty(V * L, dtype=torch.float32, device=dev)
+    left, right = torch.where(v == 0, 1, v - 1), torch.where(v == V - 1, V - 2, v + 1)      # (the ends have one neighbour)
+    for table, a, b in ((indices, left, right), (weights, path_w[left.minimum(v).long()], path_w[right.minimum(v).long()])):
+        rows = table.view(V, L)
+        rows[:, 0::2] = a[:, None]
+        rows[:, 1::2] = b[:, None]
+    offsets = (torch.arange(V + 1, device=dev, dtype=torch.int64) * L).clamp_(max=E).to(torch.int32)
+    got = lib.csr_msf(offsets, indices[:E], weights[:E])
+    torch.cuda.synchronize()
+    order = torch.argsort(path_w, stable=True)
+    assert torch.equal(got["mst_src"].long(), order) and torch.equal(got["mst_dst"].long(), order + 1) and torch.equal(got["mst_w"], path_w[order])
+    assert bool((got["colours"] == got["colours"][0]).all())
