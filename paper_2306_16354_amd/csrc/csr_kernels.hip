@@ -65,7 +65,7 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (!in_range(u[j], f.V) || cu[j] < 0 || cu[j] == c) continue;
-            const uint32_t wb = __float_as_uint(w[j]);
+            const uint32_t wb = __float_as_uint(w[j]) & 0x7fffffffu;       // (-0 is 0)
             const unsigned int l = (unsigned int)(v < u[j] ? v : u[j]), h = (unsigned int)(v < u[j] ? u[j] : v);
             if (wb < best || (wb == best && (l < lo || (l == lo && h < hi)))) { best = wb; lo = l; hi = h; to = u[j]; }
         }

@@ -68,6 +68,17 @@ def test_random_graphs(lib, V, degree, values):
     check(lib, V, offsets, indices, weights)
 
 
+# -0.0 is a weight of 0, also where the other row has +0.0
+@pytest.mark.parametrize("V", [2, 40, 5000])
+def test_negative_zero(lib, V):
+    print(f"csr negative zero V={V}", flush=True)
+    a = np.arange(V - 1)
+    offsets, indices, weights = csr(V, a, a + 1, (a % 3).astype(np.float32))
+    weights[np.flatnonzero(weights == 0)[::2]] = -0.0
+    assert np.signbit(weights).any()
+    check(lib, V, offsets, indices, weights)
+
+
 # hook chains of a round from one to all vertices long: weights rising along paths of `run` vertices, which meet at their ends
 @pytest.mark.parametrize("run", [2, 63, 64, 65, 66, 4097, 100_000])
 def test_chains(lib, run):
