@@ -347,8 +347,10 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k,
  *   weights   DEVICE in   [E] float32, finite and >= 0 (SLHC_INVALID_ARG otherwise; the maximum
  *                         spanning tree by negated weights is not supported)
  *             Every undirected edge must be stored in both rows with the same weight; self loops and
- *             parallel edges are allowed.  An asymmetric graph can make the components hook in a cycle,
- *             which is reported as SLHC_INTERNAL.
+ *             parallel edges are allowed; -0 counts as 0.  An asymmetric graph is reported as SLHC_INTERNAL where
+ *             it shows: a component whose lightest edge comes after one that leads to it, or an entry that leads
+ *             from one tree to another in the end.  One-sided entries that do neither are not found; the trees then span
+ *             the components, but need not be the lightest.
  *   mst_src   DEVICE out  [V-1 capacity] int32, smaller endpoint     } the first *n_edges entries,
  *   mst_dst   DEVICE out  [V-1 capacity] int32, larger endpoint      } ascending by (w, src, dst)
  *   mst_w     DEVICE out  [V-1 capacity] float32                     }

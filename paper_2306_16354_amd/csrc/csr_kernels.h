@@ -29,6 +29,7 @@ hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, uns
 constexpr int CSR_TAIL = 2048;
 hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uint32_t seq, hipStream_t s);
 hipError_t csr_follow_again(const CsrForest& f, int round, int vertices, hipStream_t s);
+// Colours of all vertices, and the check that no entry leads from one tree to another (words[CSR_ERROR]).  The input has passed round 0's check.
 hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s);
 
 // Edges by (weight, smaller end, larger end); *flag is set where they have to be sorted by edge_sort instead.

@@ -151,6 +151,13 @@ __global__ void __launch_bounds__(TB) k_csr_select(CsrForest f, int round)
     }
 }
 
+// Whether component `other` has no edge that is e or comes before it, though e leads to it: then e is not in both rows.  Hooks that
+// pass this never form a cycle.
+__device__ inline bool one_sided(uint32_t other_w, unsigned long long other_e, uint32_t w, unsigned long long e)
+{
+    return other_w > w || (other_w == w && other_e > e);
+}
+
 // One thread per root: append the component's edge (once per undirected edge) and hook it to the component at the other end.  Two
 // that chose the same edge keep the smaller root; roots that stay get cleared minima for the next round.
 __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
@@ -180,10 +187,15 @@ __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
                     if (!in_range(other, f.V) || other == c) { report(f, 9); other = -1; }
                 }
                 if (other >= 0) {
-                    const bool mutual = best_w[other] == w && best_e[other] == e;
-                    adds = !mutual || c < other;
-                    stays = mutual && c < other;
-                    if (!stays) f.hook[c] = other;
+                    const uint32_t other_w = best_w[other];
+                    const unsigned long long other_e = other_w == w ? best_e[other] : 0ull;
+                    const bool mutual = other_w == w && other_e == e;
+                    if (one_sided(other_w, other_e, w, e)) report(f, 15);
+                    else {
+                        adds = !mutual || c < other;
+                        stays = mutual && c < other;
+                        if (!stays) f.hook[c] = other;
+                    }
                 }
             }
         }
@@ -279,8 +291,10 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
             const int cl = f.colour[lo], ch = f.colour[hi];
             const int other = cl == c ? ch : (ch == c ? cl : -1);
             if (!in_range(other, f.V) || other == c) { report(f, 9); continue; }
-            const bool mutual = __hip_atomic_load(best_w + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == w &&
-                                __hip_atomic_load(best_e + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == e;
+            const uint32_t other_w = __hip_atomic_load(best_w + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            const unsigned long long other_e = __hip_atomic_load(best_e + other, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (one_sided(other_w, other_e, w, e)) { report(f, 15); continue; }
+            const bool mutual = other_w == w && other_e == e;
             if (!mutual || c < other) {
                 const int slot = atomicAdd(&s_edges, 1);
                 if (slot < f.V - 1) { f.e_lo[slot] = lo; f.e_hi[slot] = hi; f.e_w[slot] = __uint_as_float(w); }
@@ -332,6 +346,25 @@ __global__ void __launch_bounds__(TB) k_csr_colours(CsrForest f, int32_t* __rest
     out[v] = r;
 }
 
+// Every entry leads to the same tree as its row belongs to.  (The rounds take an entry to a vertex that is no longer active for one
+// inside the component, which it is only where the other row has it too.)
+__global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* __restrict__ colours)
+{
+    const int v = blockIdx.x * TB + threadIdx.x;
+    if (v >= f.V) return;
+    const int c = colours[v];
+    const unsigned int end = (unsigned int)f.offsets[v + 1];
+    bool closed = true;
+    for (unsigned int e0 = (unsigned int)f.offsets[v]; e0 < end; e0 += 4) {
+        int u[4];
+#pragma unroll
+        for (int j = 0; j < 4; ++j) u[j] = e0 + j < end ? f.indices[e0 + j] : v;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) closed = closed && colours[u[j]] == c;
+    }
+    if (!closed) report(f, 16);
+}
+
 __global__ void __launch_bounds__(64) k_csr_words(int32_t* __restrict__ words)
 {
     words[threadIdx.x] = 0;
@@ -371,6 +404,7 @@ hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uin
 hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s)
 {
     hipLaunchKernelGGL(k_csr_colours, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, out);
+    hipLaunchKernelGGL(k_csr_closed, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, out);
     return hipGetLastError();
 }
 

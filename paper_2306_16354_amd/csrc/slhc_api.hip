@@ -1892,6 +1892,11 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             return SLHC_OK;
         };
         int32_t said[slhc::CSR_TOLD];
+        auto state = [&](int32_t check) -> int {
+            if (check == 0) return SLHC_OK;
+            set_err("forest state check %d failed (is every edge stored in both rows with one weight?)", check);
+            return SLHC_INTERNAL;
+        };
         auto read = [&](int which) -> int {
             HIP_TRY(mail[which].wait_tagged(slhc::CSR_TOLD));
             for (int i = 0; i < slhc::CSR_TOLD; ++i) said[i] = (int32_t)static_cast<volatile unsigned long long*>(mail[which].tagged())[i];
@@ -1899,9 +1904,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
                 set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", said[3]);
                 return SLHC_INVALID_ARG;
             }
-            if (said[3] == 10) { set_err("component hooks do not form a forest (is every edge stored in both rows with one weight?)"); return SLHC_INTERNAL; }
-            if (said[3] != 0) { set_err("forest state check %d failed", said[3]); return SLHC_INTERNAL; }
-            return SLHC_OK;
+            return state(said[3]);
         };
         // hook chains of `round` longer than a launch follows: finish them with the host in the loop
         auto finish_chains = [&](int round) -> int {
@@ -1959,7 +1962,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         if (V == 1) nrounds = 0;
         HIP_TRY(slhc::csr_colours(f, colours, s));
         int32_t* flag = f.words + slhc::CSR_FLAG;
-        int32_t many = 0;
+        int32_t many = 0, check = 0;
         if (edges > 0) {
             // (the arrays of the rounds are free by now)
             slhc::CsrSortScratch t{};
@@ -1976,9 +1979,11 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
                 HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
                                         ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
         }
-        if (edges == 0 || many) HIP_TRY(hipStreamSynchronize(s));
+        HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 1, &check));          // (the end of all work)
         mail[0].box.idle();
         mail[1].box.idle();
+        rc2 = state(check);
+        if (rc2 != SLHC_OK) return rc2;
         *n_edges = edges;
         if (rounds) *rounds = nrounds;
         return SLHC_OK;

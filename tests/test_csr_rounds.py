@@ -68,6 +68,45 @@ def test_random_graphs(lib, V, degree, values):
     check(lib, V, offsets, indices, weights)
 
 
+# Entries that only one of the two rows has, or with another weight there: an error, never a forest that leaves a component in parts.
+# A row of (neighbour, weight) per vertex.
+ONE_SIDED = {
+    "both edges of a tree's root": [[(3, 1), (1, 9)], [(2, 2)], [], []],
+    "the only edge": [[(1, 1)], []],
+    "a later round's": [[(1, .1), (2, 1)], [(0, .1)], [(3, .5)], [(2, .5)]],
+    "two weights": [[(1, 1), (2, 2)], [(0, 3), (2, 4)], [(0, 2), (1, 4)]],
+    "a cycle": [[(1, 1)], [(2, 2)], [(0, 3)]],
+    "one of two with equal weights": [[(1, 1), (2, 1)], [(2, 1)], [(0, 1), (1, 1)]],
+}
+
+
+@pytest.mark.parametrize("case", ONE_SIDED)
+@pytest.mark.parametrize("more", [0, 3000, 70_000])          # (as many vertices beside it: one launch, launches per round, the other sort)
+def test_one_sided_entries(lib, case, more):
+    print(f"csr one-sided: {case}, {more} more", flush=True)
+    rows = ONE_SIDED[case]
+    at = len(rows)
+    a = np.arange(more - 1) if more else np.zeros(0, np.int64)
+    offsets, indices, weights = csr(at + more, a + at, a + 1 + at, (a % 7 + 1).astype(np.float32)) if more else (np.zeros(at + 1, np.int32), np.zeros(0, np.int32), np.zeros(0, np.float32))
+    ends = np.cumsum([len(r) for r in rows])
+    offsets = np.r_[0, ends, ends[-1] + offsets[at + 1:]].astype(np.int32)
+    indices = np.r_[np.array([u for r in rows for u, _ in r]), indices].astype(np.int32)
+    weights = np.r_[np.array([w for r in rows for _, w in r]), weights].astype(np.float32)
+    with pytest.raises(lib.SlhcError, match="both rows"):
+        lib.csr_msf(*(torch.from_numpy(x).cuda() for x in (offsets, indices, weights)))
+
+
+def test_graph_stored_once(lib):
+    rng = np.random.default_rng(5)
+    V = 20_000
+    a, b = rng.integers(0, V, 3 * V), rng.integers(0, V, 3 * V)
+    lo, hi = np.minimum(a, b), np.maximum(a, b)
+    order = np.argsort(lo, kind="stable")
+    offsets = np.r_[0, np.cumsum(np.bincount(lo, minlength=V))].astype(np.int32)
+    with pytest.raises(lib.SlhcError, match="both rows"):
+        lib.csr_msf(*(torch.from_numpy(x).cuda() for x in (offsets, hi[order].astype(np.int32), rng.random(3 * V).astype(np.float32))))
+
+
 # -0.0 is a weight of 0, also where the other row has +0.0
 @pytest.mark.parametrize("V", [2, 40, 5000])
 def test_negative_zero(lib, V):
