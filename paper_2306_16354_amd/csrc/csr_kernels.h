@@ -29,10 +29,12 @@ hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, uns
 constexpr int CSR_TAIL = 2048;
 hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uint32_t seq, hipStream_t s);
 hipError_t csr_follow_again(const CsrForest& f, int round, int vertices, hipStream_t s);
-// Colours of all vertices, and the check that no entry leads from one tree to another (words[CSR_ERROR]).  The input has passed round 0's check.
+// Colours of all vertices, and the check that no entry leads from one tree to another (words[CSR_ERROR]); nothing after a failed check
+// or with hooks not followed to their end.
 hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s);
 
-// Edges by (weight, smaller end, larger end); *flag is set where they have to be sorted by edge_sort instead.
+// Edges by (weight, smaller end, larger end), in two steps: the first sets *flag where edge_sort has to do it instead, and tells host[0],
+// with `seq` above the flag.
 struct CsrSortScratch {
     int32_t *count, *offset;                   // [V + 1]
     int32_t* rank;                             // [E]
@@ -40,7 +42,8 @@ struct CsrSortScratch {
     void* temp; size_t temp_bytes;
 };
 bool csr_sort_fits(int V, int E, size_t temp_bytes);
-hipError_t csr_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w,
-                    int32_t* flag, hipStream_t s);
+hipError_t csr_sort_ends(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* flag, unsigned long long* host, uint32_t seq,
+                         hipStream_t s);
+hipError_t csr_sort_weights(int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s);
 
 }  // namespace slhc

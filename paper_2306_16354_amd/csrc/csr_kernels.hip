@@ -28,25 +28,22 @@ __device__ inline void report(const CsrForest& f, int site) { atomicCAS(f.words 
 // a failed check, or hooks that are not followed to their end yet, leave all rounds enqueued to the host
 __device__ inline bool halted(const CsrForest& f) { return (f.words[CSR_ERROR] | f.words[CSR_CHAINS]) != 0; }
 
-// The edge of v's row out of component c that is first in the order (weight, smaller end, larger end).  One thread per vertex: road-like
-// graphs have two or three edges per vertex (a row with thousands is scanned by one thread: correct, slow).
+// A row of more entries than this is read by the whole wavefront, one of up to so many by its vertex's thread (road-like graphs have
+// two or three edges per vertex).  A thread takes 0.2 us per entry.  Calls with long rows by threads and by wavefronts: a star of 70 000
+// vertices 27 and 0.5 ms (one scan less, too: see k_csr_scan), a random graph of 1M vertices whose longest row has 65 583 entries
+// 97 and 9.6.  The line, random graphs of 200 000 vertices with 24, 48 and 96 entries on average: 956, 1420 and 1466 us with wavefronts
+// from 33 entries on, 888, 1486 and 1478 from 49 on, 889, 1757 and 1573 from 65 on.
+constexpr unsigned int LONG_ROW = 48;
+
+// Entries of v's row: from `at` on, four side by side (their loads wait for memory together), then `step` further.  Returns the first in
+// the order (weight, smaller end, larger end) that leads out of component c, as its weight's bits and the other end; among the edges of
+// one vertex that is the order of the ends.  (Unsigned, because the step behind the last ones may lie beyond 2^31.)
+constexpr unsigned long long NO_EDGE = ((unsigned long long)INF_BITS << 32) | 0xffffffffull;
 template <bool FIRST>
-__device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits)
+__device__ inline unsigned long long row_part(const CsrForest& f, int v, int c, unsigned int at, unsigned int end, unsigned int step)
 {
-    int o0 = f.offsets[v], o1 = f.offsets[v + 1];
-    if (FIRST) {
-        if (o0 < 0 || o1 < o0 || o1 > f.E) report(f, 20);
-        if (v == 0 && o0 != 0) report(f, 21);
-        if (v == f.V - 1 && o1 != f.E) report(f, 22);
-    }
-    o0 = o0 < 0 ? 0 : o0;
-    o1 = o1 > f.E ? f.E : o1;
-    uint32_t best = INF_BITS;
-    unsigned int lo = ~0u, hi = ~0u;
-    int to = -1;
-    // (four entries side by side: their loads wait for memory together; unsigned, because the step behind the last ones may lie beyond 2^31)
-    const unsigned int end = o1 < 0 ? 0u : (unsigned int)o1;
-    for (unsigned int e0 = (unsigned int)o0; e0 < end; e0 += 4) {
+    unsigned long long best = NO_EDGE;
+    for (unsigned int e0 = at; e0 < end; e0 += step) {
         int u[4], cu[4];
         float w[4];
 #pragma unroll
@@ -65,13 +62,43 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
             if (!in_range(u[j], f.V) || cu[j] < 0 || cu[j] == c) continue;
-            const uint32_t wb = __float_as_uint(w[j]) & 0x7fffffffu;       // (-0 is 0)
-            const unsigned int l = (unsigned int)(v < u[j] ? v : u[j]), h = (unsigned int)(v < u[j] ? u[j] : v);
-            if (wb < best || (wb == best && (l < lo || (l == lo && h < hi)))) { best = wb; lo = l; hi = h; to = u[j]; }
+            const unsigned long long key = ((unsigned long long)(__float_as_uint(w[j]) & 0x7fffffffu) << 32) | (unsigned int)u[j];       // (-0 is 0)
+            best = key < best ? key : best;
         }
     }
-    *wbits = best;
-    return to;
+    return best;
+}
+
+// The edge of v's row out of component c (v < 0: none).  Every lane of the wavefront must call it.
+template <bool FIRST>
+__device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits)
+{
+    unsigned int at = 0, end = 0;
+    if (v >= 0) {
+        const int o0 = f.offsets[v], o1 = f.offsets[v + 1];
+        if (FIRST) {
+            if (o0 < 0 || o1 < o0 || o1 > f.E) report(f, 20);
+            if (v == 0 && o0 != 0) report(f, 21);
+            if (v == f.V - 1 && o1 != f.E) report(f, 22);
+        }
+        at = o0 < 0 ? 0u : (unsigned int)o0;
+        end = o1 < 0 ? 0u : o1 > f.E ? (unsigned int)f.E : (unsigned int)o1;
+    }
+    const bool is_long = at < end && end - at > LONG_ROW;
+    unsigned long long best = is_long ? NO_EDGE : row_part<FIRST>(f, v, c, at, end, 4);
+    const int lane = threadIdx.x & 63;
+    for (unsigned long long todo = __ballot(is_long); todo != 0; todo &= todo - 1) {
+        const int owner = __builtin_ctzll(todo);
+        unsigned long long key = row_part<FIRST>(f, __shfl(v, owner), __shfl(c, owner), (unsigned int)__shfl((int)at, owner) + 4 * lane, (unsigned int)__shfl((int)end, owner), 256);
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            const unsigned long long other = __shfl_xor(key, o);
+            key = other < key ? other : key;
+        }
+        if (lane == owner) best = key;
+    }
+    *wbits = (uint32_t)(best >> 32);
+    return best == NO_EDGE ? -1 : (int)(best & 0xffffffffull);
 }
 
 // Round 0: every vertex is a component.
@@ -79,10 +106,9 @@ __global__ void __launch_bounds__(WIDE) k_csr_first(CsrForest f)
 {
     for (long long base = (long long)blockIdx.x * WIDE; base < f.V; base += (long long)gridDim.x * WIDE) {
         const long long v = base + threadIdx.x;
-        int u = -1;
-        uint32_t w = INF_BITS;
+        uint32_t w;
+        const int u = row_edge<true>(f, v < f.V ? (int)v : -1, (int)v, &w);
         if (v < f.V) {
-            u = row_edge<true>(f, (int)v, (int)v, &w);
             const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
             f.colour[v] = (int)v;
             f.hook[v] = (int)v;
@@ -107,25 +133,25 @@ __global__ void __launch_bounds__(WIDE) k_csr_scan(CsrForest f, int round, unsig
         const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR};
         __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | (unsigned int)f.words[at[threadIdx.x]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    if (halted(f)) return;
+    if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;       // (one tree: nothing is left to find)
     const int n = f.words[CSR_ACTIVE + round % 3];
     const int32_t* from = f.active[round & 1];
     int32_t* to = f.active[(round + 1) & 1];
     uint32_t* best_w = f.best_w[round & 1];
     for (long long base = (long long)blockIdx.x * WIDE; base < n; base += (long long)gridDim.x * WIDE) {
         const long long i = base + threadIdx.x;
-        int v = -1, u = -1, c = 0;
-        uint32_t w = INF_BITS;
+        int v = -1, c = 0;
+        uint32_t w;
         if (i < n) {
             v = from[i];
             c = f.colour[v];
-            if (!in_range(c, f.V)) { report(f, 11); c = 0; }
-            else u = row_edge<false>(f, v, c, &w);
-            if (u >= 0) {
-                f.cand_u[v] = u;
-                f.cand_w[v] = __uint_as_float(w);
-            } else f.colour[v] = ~c;
+            if (!in_range(c, f.V)) { report(f, 11); v = -1; }
         }
+        const int u = row_edge<false>(f, v, c, &w);
+        if (u >= 0) {
+            f.cand_u[v] = u;
+            f.cand_w[v] = __uint_as_float(w);
+        } else if (v >= 0) f.colour[v] = ~c;
         wave_min_into(best_w, c, w, u >= 0);
         const int at = block_append<WIDE>(u >= 0, f.words + CSR_ACTIVE + (round + 1) % 3);
         if (u >= 0) to[at] = v;
@@ -257,19 +283,19 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
         __syncthreads();
         for (int i0 = 0; i0 < n; i0 += WIDE) {
             const int i = i0 + tid;
-            int v = -1, u = -1, c = 0;
-            uint32_t w = INF_BITS;
+            int v = -1, c = 0;
+            uint32_t w;
             if (i < n) {
                 v = from[i];
                 c = f.colour[v];
-                if (!in_range(c, f.V)) { report(f, 11); c = 0; }
-                else u = row_edge<false>(f, v, c, &w);
-                if (u >= 0) {
-                    f.cand_u[v] = u;
-                    f.cand_w[v] = __uint_as_float(w);
-                    to[atomicAdd(&s_active, 1)] = v;
-                } else f.colour[v] = ~c;
+                if (!in_range(c, f.V)) { report(f, 11); v = -1; }
             }
+            const int u = row_edge<false>(f, v, c, &w);
+            if (u >= 0) {
+                f.cand_u[v] = u;
+                f.cand_w[v] = __uint_as_float(w);
+                to[atomicAdd(&s_active, 1)] = v;
+            } else if (v >= 0) f.colour[v] = ~c;
             wave_min_into(best_w, c, w, u >= 0);
         }
         __syncthreads();
@@ -334,7 +360,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
 __global__ void __launch_bounds__(TB) k_csr_colours(CsrForest f, int32_t* __restrict__ out)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.V) return;
+    if (v >= f.V || halted(f)) return;
     int r = f.colour[v];
     r = r < 0 ? ~r : r;
     for (int s = 0; s < f.V; ++s) {
@@ -348,19 +374,31 @@ __global__ void __launch_bounds__(TB) k_csr_colours(CsrForest f, int32_t* __rest
 
 // Every entry leads to the same tree as its row belongs to.  (The rounds take an entry to a vertex that is no longer active for one
 // inside the component, which it is only where the other row has it too.)
-__global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* __restrict__ colours)
+__device__ inline bool closed_part(const CsrForest& f, const int32_t* __restrict__ colours, int c, unsigned int at, unsigned int end, unsigned int step)
 {
-    const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= f.V) return;
-    const int c = colours[v];
-    const unsigned int end = (unsigned int)f.offsets[v + 1];
     bool closed = true;
-    for (unsigned int e0 = (unsigned int)f.offsets[v]; e0 < end; e0 += 4) {
+    for (unsigned int e0 = at; e0 < end; e0 += step) {
         int u[4];
 #pragma unroll
-        for (int j = 0; j < 4; ++j) u[j] = e0 + j < end ? f.indices[e0 + j] : v;
+        for (int j = 0; j < 4; ++j) u[j] = e0 + j < end ? f.indices[e0 + j] : -1;
 #pragma unroll
-        for (int j = 0; j < 4; ++j) closed = closed && colours[u[j]] == c;
+        for (int j = 0; j < 4; ++j) closed = closed && (u[j] < 0 || colours[u[j]] == c);
+    }
+    return closed;
+}
+__global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* __restrict__ colours)
+{
+    const int v = blockIdx.x * TB + threadIdx.x, lane = threadIdx.x & 63;
+    // (a failed check or unfollowed hooks: no colours, and perhaps no rows that may be read; one tree: nothing to leave it for)
+    if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;
+    const bool mine = v < f.V;
+    const int c = mine ? colours[v] : 0;
+    const unsigned int at = mine ? (unsigned int)f.offsets[v] : 0u, end = mine ? (unsigned int)f.offsets[v + 1] : 0u;
+    const bool is_long = end - at > LONG_ROW;
+    bool closed = is_long || closed_part(f, colours, c, at, end, 4);
+    for (unsigned long long todo = __ballot(is_long); todo != 0; todo &= todo - 1) {
+        const int owner = __builtin_ctzll(todo);
+        closed &= closed_part(f, colours, __shfl(c, owner), (unsigned int)__shfl((int)at, owner) + 4 * lane, (unsigned int)__shfl((int)end, owner), 256);
     }
     if (!closed) report(f, 16);
 }
@@ -411,8 +449,9 @@ hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s)
 // ------------------------------------------------------------------------------- sort
 // By (weight, smaller end, larger end).  The smaller ends are counted and the edges placed by them, which takes a few passes of
 // random words where a radix sort by both ends takes five over all of them; each vertex then orders its few edges by the other
-// end, and one stable sort by weight follows.  A vertex with more than LO_MOST edges to larger ones raises a flag, and the caller takes
-// edge_sort instead.  1M edges: 240 us with two radix sorts, 205 so.
+// end, and one stable sort by weight follows.  A vertex with more than LO_MOST edges to larger ones raises a flag while they are
+// counted; nothing is placed then, and the caller, whom the placing tells, takes edge_sort instead.  1M edges: 240 us with two radix
+// sorts, 205 so.
 constexpr int LO_MOST = 32;
 __global__ void __launch_bounds__(TB) k_lo_clear(int32_t* __restrict__ count, int V, int32_t* __restrict__ flag)
 {
@@ -420,29 +459,43 @@ __global__ void __launch_bounds__(TB) k_lo_clear(int32_t* __restrict__ count, in
     if (v <= V) count[v] = 0;
     if (v == 0) *flag = 0;
 }
-__global__ void __launch_bounds__(TB) k_lo_count(const int32_t* __restrict__ lo, int E, int32_t* __restrict__ count, int32_t* __restrict__ rank)
+// Additions to one word come one after another: a star of 1M vertices, 12 ms with one for every edge.  So a wavefront adds once for all
+// edges of its first one's vertex, and looks for the flag first; LO_COUNT_BLOCKS bounds how many can add before they see it.
+constexpr int LO_COUNT_BLOCKS = 1024;
+__global__ void __launch_bounds__(TB) k_lo_count(const int32_t* __restrict__ lo, int E, int32_t* __restrict__ count, int32_t* __restrict__ rank, int32_t* __restrict__ flag)
 {
-    const int e = blockIdx.x * TB + threadIdx.x;
-    if (e < E) rank[e] = atomicAdd(count + lo[e], 1);
+    for (long long base = (long long)blockIdx.x * TB; base < E; base += (long long)gridDim.x * TB) {
+        if (*reinterpret_cast<volatile int32_t*>(flag) != 0) return;
+        const long long e = base + threadIdx.x;
+        const int v = e < E ? lo[e] : -1;
+        const unsigned long long same = __ballot(v >= 0 && v == __builtin_amdgcn_readfirstlane(v));
+        int r = 0;
+        if (same >> (threadIdx.x & 63) & 1) {
+            const int first = __builtin_ctzll(same);
+            if ((threadIdx.x & 63) == first) r = atomicAdd(count + v, __popcll(same));
+            r = __shfl(r, first) + __builtin_amdgcn_mbcnt_hi((unsigned int)(same >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)same, 0u));
+        } else if (v >= 0) r = atomicAdd(count + v, 1);
+        if (e < E) rank[e] = r;
+        if (r >= LO_MOST) *flag = 1;
+    }
 }
 __global__ void __launch_bounds__(TB) k_lo_place(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi, const float* __restrict__ w, int E,
                                                  const int32_t* __restrict__ offset, const int32_t* __restrict__ rank, uint32_t* __restrict__ wbits,
-                                                 unsigned long long* __restrict__ ends)
+                                                 unsigned long long* __restrict__ ends, const int32_t* __restrict__ flag, unsigned long long* __restrict__ host, uint32_t seq)
 {
     const int e = blockIdx.x * TB + threadIdx.x;
-    if (e >= E) return;
+    if (e == 0) __hip_atomic_store(host, ((unsigned long long)seq << 32) | (unsigned int)*flag, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+    if (e >= E || *flag != 0) return;
     const int at = offset[lo[e]] + rank[e];
     wbits[at] = __float_as_uint(w[e]);
     ends[at] = ((unsigned long long)(unsigned int)lo[e] << 32) | (unsigned int)hi[e];
 }
 __global__ void __launch_bounds__(TB) k_lo_order(const int32_t* __restrict__ offset, int V, uint32_t* __restrict__ wbits, unsigned long long* __restrict__ ends,
-                                                 int32_t* __restrict__ flag)
+                                                 const int32_t* __restrict__ flag)
 {
     const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= V) return;
+    if (v >= V || *flag != 0) return;
     const int a = offset[v], b = offset[v + 1];
-    if (b - a < 2) return;
-    if (b - a > LO_MOST) { *flag = 1; return; }
     for (int i = a + 1; i < b; ++i) {
         const unsigned long long e = ends[i];
         const uint32_t w = wbits[i];
@@ -469,22 +522,25 @@ bool csr_sort_fits(int V, int E, size_t temp_bytes)
     (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, b, k32, k32, k64, k64, (size_t)E, 0, 32, (hipStream_t)0);
     return a <= temp_bytes && b <= temp_bytes;
 }
-hipError_t csr_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w,
-                    int32_t* flag, hipStream_t s)
+hipError_t csr_sort_ends(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* flag, unsigned long long* host, uint32_t seq,
+                         hipStream_t s)
 {
     hipLaunchKernelGGL(k_lo_clear, dim3(blocks_for((long long)V + 1)), dim3(TB), 0, s, t.count, V, flag);
-    hipLaunchKernelGGL(k_lo_count, dim3(blocks_for(E)), dim3(TB), 0, s, lo, E, t.count, t.rank);
+    const int blocks = blocks_for(E);
+    hipLaunchKernelGGL(k_lo_count, dim3(blocks < LO_COUNT_BLOCKS ? blocks : LO_COUNT_BLOCKS), dim3(TB), 0, s, lo, E, t.count, t.rank, flag);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
     size_t tb = t.temp_bytes;
     e = rocprim::exclusive_scan(t.temp, tb, t.count, t.offset, 0, (size_t)V + 1, rocprim::plus<int32_t>(), s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_lo_place, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, E, t.offset, t.rank, t.wbits_a, t.ends_a);
+    hipLaunchKernelGGL(k_lo_place, dim3(blocks_for(E)), dim3(TB), 0, s, lo, hi, w, E, t.offset, t.rank, t.wbits_a, t.ends_a, flag, host, seq);
     hipLaunchKernelGGL(k_lo_order, dim3(blocks_for(V)), dim3(TB), 0, s, t.offset, V, t.wbits_a, t.ends_a, flag);
-    e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    tb = t.temp_bytes;
-    e = rocprim::radix_sort_pairs<radix_passes>(t.temp, tb, t.wbits_a, t.wbits_b, t.ends_a, t.ends_b, (size_t)E, 0, 32, s);
+    return hipGetLastError();
+}
+hipError_t csr_sort_weights(int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s)
+{
+    size_t tb = t.temp_bytes;
+    const hipError_t e = rocprim::radix_sort_pairs<radix_passes>(t.temp, tb, t.wbits_a, t.wbits_b, t.ends_a, t.ends_b, (size_t)E, 0, 32, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_lo_unpack, dim3(blocks_for(E)), dim3(TB), 0, s, t.ends_b, t.wbits_b, E, out_lo, out_hi, out_w);
     return hipGetLastError();

@@ -1945,8 +1945,10 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             if (nrounds > max_rounds) { set_err("no steady state after %d rounds", max_rounds); return SLHC_INTERNAL; }
             nrounds = 0;
         }
+        const bool tail = nrounds == 0;
         while (nrounds == 0) {
             HIP_TRY(slhc::csr_tail(f, next, mail[1].tagged(), mail[1].next(), s));
+            HIP_TRY(slhc::csr_colours(f, colours, s));         // (while the host waits for the tail)
             rc2 = read(1);
             if (rc2 != SLHC_OK) return rc2;
             if (said[2] != 0) {                            // (of a round before, behind which nothing was done)
@@ -1960,25 +1962,24 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             if (edges < 0 || edges > V - 1 || nrounds < 1) { set_err("rounds left %d edges", edges); return SLHC_INTERNAL; }
         }
         if (V == 1) nrounds = 0;
-        HIP_TRY(slhc::csr_colours(f, colours, s));
-        int32_t* flag = f.words + slhc::CSR_FLAG;
-        int32_t many = 0, check = 0;
-        if (edges > 0) {
-            // (the arrays of the rounds are free by now)
-            slhc::CsrSortScratch t{};
-            t.count = reinterpret_cast<int32_t*>(ws.best_e); t.offset = reinterpret_cast<int32_t*>(ws.keys_a);
-            t.rank = ws.cand_u; t.wbits_a = ws.best_w; t.wbits_b = ws.vals_a; t.ends_a = ws.keys_b;
-            t.ends_b = reinterpret_cast<unsigned long long*>(ws.ptr);          // (and ext_idx behind it)
-            t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
-            many = V > 65536 && slhc::csr_sort_fits((int)V, edges, ws.sort_temp_bytes) ? 0 : 1;        // (up to there edge_sort needs one sort)
-            if (!many) {
-                HIP_TRY(slhc::csr_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, t, mst_src, mst_dst, mst_w, flag, s));
-                HIP_TRY(mail[0].fetch(flag, 1, &many));
-            }
-            if (many)
-                HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
-                                        ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
+        if (!tail) HIP_TRY(slhc::csr_colours(f, colours, s));
+        // (the arrays of the rounds are free by now)
+        slhc::CsrSortScratch t{};
+        t.count = reinterpret_cast<int32_t*>(ws.best_e); t.offset = reinterpret_cast<int32_t*>(ws.keys_a);
+        t.rank = ws.cand_u; t.wbits_a = ws.best_w; t.wbits_b = ws.vals_a; t.ends_a = ws.keys_b;
+        t.ends_b = reinterpret_cast<unsigned long long*>(ws.ptr);          // (and ext_idx behind it)
+        t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
+        const bool by_ends = edges > 0 && V > 65536 && slhc::csr_sort_fits((int)V, edges, ws.sort_temp_bytes);        // (up to there edge_sort needs one sort)
+        int32_t many = 1, check = 0;
+        if (by_ends) {
+            HIP_TRY(slhc::csr_sort_ends(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, t, f.words + slhc::CSR_FLAG, mail[0].tagged(), mail[0].next(), s));
+            HIP_TRY(mail[0].wait_tagged(1));
+            many = (int32_t)static_cast<volatile unsigned long long*>(mail[0].tagged())[0];
         }
+        if (!many) HIP_TRY(slhc::csr_sort_weights(edges, t, mst_src, mst_dst, mst_w, s));
+        else if (edges > 0)
+            HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
+                                    ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
         HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 1, &check));          // (the end of all work)
         mail[0].box.idle();
         mail[1].box.idle();

@@ -68,6 +68,24 @@ def test_random_graphs(lib, V, degree, values):
     check(lib, V, offsets, indices, weights)
 
 
+# rows that a thread reads and rows that a wavefront reads, side by side and far apart: lengths around the line between them and around the wavefront's
+# steps; hubs whose tree edges are few, many and on either end.  (One launch, launches per round, the sort by the smaller ends.)
+@pytest.mark.parametrize("V", [1500, 20_000, 90_000])
+@pytest.mark.parametrize("spread", [1, 61])
+@pytest.mark.parametrize("values", [3, 1_000_000])
+def test_hubs(lib, V, spread, values):
+    print(f"csr hubs V={V} spread={spread} values={values}", flush=True)
+    rng = np.random.default_rng(V + spread)
+    lengths = [0, 1, 3, 5, 31, 32, 33, 47, 48, 49, 51, 52, 53, 64, 128, 255, 256, 257, 260, 511, 1000, 1400]
+    hubs = np.r_[np.arange(len(lengths)), V - 1 - np.arange(len(lengths))]
+    hubs = np.where(hubs < V // 2, hubs * spread, V - 1 - (V - 1 - hubs) * spread)
+    a = np.concatenate([np.full(n, h) for h, n in zip(hubs, lengths * 2)])
+    b = np.concatenate([(h + 1 + rng.permutation(V - 1)[:n]) % V for h, n in zip(hubs, lengths * 2)])
+    path = rng.permutation(V)[:V // 2]
+    a, b = np.r_[a, path[:-1]], np.r_[b, path[1:]]
+    check(lib, V, *csr(V, a, b, rng.integers(0, values, len(a)).astype(np.float32), rng))
+
+
 # Entries that only one of the two rows has, or with another weight there: an error, never a forest that leaves a component in parts.
 # A row of (neighbour, weight) per vertex.
 ONE_SIDED = {
