@@ -148,8 +148,8 @@ def main():
     # evaluated in float32 in each case, so the outputs are the same bits.
     half = args.knn_only or bool(stats[-1]["half_products"])
     split = half or bool(stats[-1]["split_products"])
-    once = half and (4096 <= N and d > 128 or 49_152 <= N and d > 64) and N < 1 << 24     # one product for both orders of a pair
-    products = 3.0 if split and not half else 0.5 if once else 1.0      # per multiply-add
+    products = slhc.probe_knn_products(N, d, k) if half else 3.0 if split else 1.0      # per multiply-add
+    once = products < 1.0                               # one product for both orders of a pair
     multiply = "v_mfma_f32_32x32x16_f16" if half else "v_mfma_f32_32x32x16_bf16" if split else "v_mfma_f32_32x32x2_f32"
     empirical_16bit_tflops = slhc.probe_f16_mfma(dev) if half else slhc.probe_bf16_mfma(dev)     # the same for that multiply
     peak_tflops = PEAK_16BIT_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
@@ -277,8 +277,11 @@ def main():
             line["roofline_connect"] = {"kernel": "near_link: one pass per round, a search for the queries that are left" if half
                                                   else "sweep_kernel (cross-component 1-NN)", "bound": "mfma",
                                         "achieved": ct, "peak": peak_tflops, "unit": "TFLOP/s",
-                                        "frac": ct / peak_tflops, "traffic": None,
-                                        "frac_executed": products * ct / peak_tflops}
+                                        "frac": ct / peak_tflops, "traffic": None}
+            # (the engine multiplies each queried row by all rows; beyond 128 columns its first round is one product for
+            # both orders of a pair and the others are not, which no counter tells apart)
+            if not half or d <= 128:
+                line["roofline_connect"]["frac_executed"] = (1.0 if half else products) * ct / peak_tflops
             attach_traffic(line["roofline_connect"], "connect_half" if half else "connect_sweeps_split" if split else "connect_sweeps")
 
     if not args.knn_only:

@@ -81,7 +81,8 @@ typedef struct slhc_stats {
     int32_t components_after_knn;    /* components when the k-NN lists alone could add no edge     */
     int32_t order_pivots;            /* pivots of the row order (0 when not pruned)                */
     int64_t knn_filter_survivors;    /* pairs the k-NN search evaluated exactly (passed the MFMA filter) */
-    int64_t connect_query_rows;      /* sum over connection rounds of queried rows                 */
+    int64_t connect_query_rows;      /* sum over connection rounds of queried rows; from 131 072 rows on, pruned rounds of
+                                        the list kernels ask again rows that depend on timing (the outputs do not)  */
     int64_t connect_filter_survivors;
     float ms_knn;                    /* norms + fused k-NN (host clock, includes the sync)         */
     float ms_boruvka;                /* all min-edge / commit / relabel kernels                    */
@@ -93,8 +94,9 @@ typedef struct slhc_stats {
     float ms_knn_kernel;             /* HIP-event time of the k-NN search's kernels                */
     float ms_connect_kernels;        /* HIP-event time summed over the cross-component 1-NN sweeps */
     float ms_order;                  /* HIP-event time of building the row order + tile balls     */
-    int64_t knn_tile_steps;          /* (query panel, candidate tile) pairs the k-NN sweep multiplied;
-                                        ceil(N/128)^2 when nothing is pruned                       */
+    int64_t knn_tile_steps;          /* (query panel, candidate tile) pairs the k-NN search covered;
+                                        ceil(N/128)^2 when nothing is pruned, also where one product
+                                        stands for both orders of a pair                           */
     int64_t connect_tile_steps;      /* same, summed over the connection sweeps                    */
     int32_t pruned;                  /* 1 when tile pruning was active in this call                */
     int32_t order_padded_rows;       /* rows of the reordered copy incl. padding (0 when not pruned) */
@@ -102,7 +104,8 @@ typedef struct slhc_stats {
                                         copies or split bfloat16 halves, see half_products), 0 when all were in
                                         float32 (see SLHC_FP32_FILTER)                                */
     int32_t half_products;           /* 1 when the half-precision engine ran the k-NN search: one product of
-                                        float16 copies per pair; 0: the list kernels' split bfloat16 halves
+                                        float16 copies per pair, or for both orders of a pair
+                                        (slhc_probe_knn_products); 0: the list kernels' split bfloat16 halves
                                         (three products per pair) or float32                          */
 } slhc_stats;
 
@@ -233,6 +236,13 @@ int slhc_probe_bf16_mfma_values(const float* A, const float* B, const float* C, 
 /* The same for v_mfma_f32_32x32x16_f16, on values that float16 holds: the half-precision engine discards a pair only if
  * its product value misses a bound by more than this instruction can be off. */
 int slhc_probe_f16_mfma_values(const float* A, const float* B, const float* C, float* D, int32_t trials, void* stream);
+
+/*
+ * Multiply-adds that an every-tile k-NN search of N rows executes by default, with a workspace of the reported size, per ordered pair of
+ * rows and column (HOST out; no device work): 0.5 where the half-precision engine multiplies every pair once for both of its rows, 1
+ * where it does so for each, 3 for the list kernels' split bfloat16 halves.  The sample that bounds come from is not counted.
+ */
+int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products);
 
 /*
  * Measurement aid like slhc_probe_fp32_mfma, for the panel loop of the sweeps (paper Sec. 3.1.1, the

@@ -73,6 +73,8 @@ def load_library():
         rate.restype = values.restype = ctypes.c_int
     lib.slhc_probe_panel_loop.argtypes = [i32, ctypes.POINTER(ctypes.c_double), vp, sz, vp]
     lib.slhc_probe_panel_loop.restype = ctypes.c_int
+    lib.slhc_probe_knn_products.argtypes = [i64, i32, i32, ctypes.POINTER(ctypes.c_double)]
+    lib.slhc_probe_knn_products.restype = ctypes.c_int
     lib.slhc_cross_1nn_workspace_bytes.argtypes = [i64, i32, i64, ctypes.POINTER(sz)]
     lib.slhc_cross_1nn.argtypes = [vp, i64, i32, vp, vp, i64, vp, vp, vp, sz, vp]
     lib.slhc_workspace_bytes.argtypes = [i64, i32, i32, ctypes.POINTER(sz)]
@@ -206,6 +208,13 @@ def probe_f16_mfma(device="cuda"):
 def probe_fp32_mfma(device="cuda"):
     """slhc_probe_fp32_mfma: TFLOP/s a register-only fp32 MFMA loop sustains on the current device."""
     return _probe_rate(load_library().slhc_probe_fp32_mfma, device)
+
+
+def probe_knn_products(N, d, k):
+    """slhc_probe_knn_products: multiply-adds per ordered pair of rows and column that the default every-tile search executes."""
+    out = ctypes.c_double(0.0)
+    _check(load_library().slhc_probe_knn_products(int(N), int(d), int(k), ctypes.byref(out)))
+    return out.value
 
 
 def probe_panel_loop(steps, workspace):

@@ -1571,6 +1571,20 @@ int slhc_knn_workspace_bytes(int64_t N, int32_t d, int32_t k, size_t* bytes)
     });
 }
 
+int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products)
+{
+    return guarded([&]() -> int {
+        if (!products) { set_err("products is NULL"); return SLHC_INVALID_ARG; }
+        const int rc = check_shape(N, d, k, true);
+        if (rc != SLHC_OK) return rc;
+        const int32_t dw = working_columns(N, d);
+        const KnnWs ws(nullptr, N, dw, true, k, false);
+        const size_t pairs = slhc::near_pairs_bytes(N, dw, k + 1);
+        *products = !ws.near.ok ? 3.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
+        return SLHC_OK;
+    });
+}
+
 int slhc_knn_graph_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist,
                        void* workspace, size_t workspace_bytes, void* stream, uint32_t flags)
 {

@@ -151,3 +151,14 @@ def test_binding_refuses_cpu_tensors():
     import paper_2306_16354_amd as slhc
     with pytest.raises(TypeError):
         slhc.knn_graph(torch.zeros((8, 4)), 2)
+
+
+# what the default search multiplies, on both sides of the lines in its rule; narrow searches of many and of few rows, wide ones, the smallest
+@pytest.mark.parametrize("N,d,k,products", [
+    (1_000_000, 128, 32, 0.5), (250_000, 784, 16, 0.5), (2_000_000, 32, 8, 1.0), (100_000, 64, 32, 1.0), (49_152, 65, 10, 0.5), (49_024, 65, 10, 1.0),
+    (12_800, 33, 10, 0.5), (12_801, 33, 10, 1.0), (12_800, 32, 10, 1.0), (3968, 200, 10, 1.0), (3969, 200, 10, 0.5), (500, 200, 10, 1.0)])
+def test_products_of_the_default_search(cdll, N, d, k, products):
+    out = ctypes.c_double(0.0)
+    assert cdll.slhc_probe_knn_products(N, d, k, ctypes.byref(out)) == 0
+    assert out.value == products
+    assert cdll.slhc_probe_knn_products(N, d, N, ctypes.byref(out)) == 1 and cdll.slhc_probe_knn_products(N, d, k, None) == 1
