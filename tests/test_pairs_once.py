@@ -22,15 +22,17 @@ def blobs(N, d, seed, spread=8.0, rows=400):
     return centres[label] + torch.randn((N, d), generator=g, device="cuda")
 
 
-# the smallest search of its kind and one row less and more; an odd and an even circle of blocks, the last of one to four tiles;
-# every number of 16-column steps; whole and partial chunks beyond 128 columns; lists from 128 entries to 1024; one to several bands
+# the smallest search of its kind and, of both orders of every pair, the one of a row less; an odd and an even circle of blocks, the last of
+# one to four tiles; every number of 16-column steps; whole and partial chunks beyond 128 columns; lists from 256 entries to 1024; one to
+# several bands; the smallest search of 384 tiles
 @pytest.mark.parametrize("N,d,k", [
     (3968, 33, 8), (3969, 33, 8), (4096, 48, 1), (4097, 49, 64), (4609, 64, 15), (5120, 65, 31), (6001, 81, 7), (7000, 97, 3), (8191, 113, 16),
-    (9000, 128, 33), (9217, 128, 2), (4100, 129, 5), (4353, 192, 64), (5000, 321, 20), (12_545, 784, 9), (30_011, 50, 10), (50_000, 40, 50), (150_000, 64, 24),
+    (9000, 128, 33), (9217, 128, 2), (4100, 129, 5), (4353, 192, 64), (5000, 321, 20), (12_545, 784, 9), (49_025, 66, 10), (50_000, 100, 50), (150_000, 80, 24),
     (70_000, 200, 12), (200_000, 128, 40),
 ])
 def test_lists(lib, N, d, k):
     print(f"pairs once N={N} d={d} k={k}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == (0.5 if N > 3968 else 1.0)
     X = blobs(N, d, N + d)
     want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
     torch.cuda.synchronize()
@@ -43,6 +45,7 @@ def test_lists(lib, N, d, k):
 @pytest.mark.parametrize("N,d,k", [(5000, 64, 12), (4500, 160, 12)])
 def test_lists_of_unlike_rows(lib, kind, N, d, k):
     print(f"pairs once, {kind}, N={N} d={d}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == 0.5
     X = blobs(N, d, 7)
     if kind == "beyond_float16":
         X[::600] *= 1e7
@@ -62,6 +65,29 @@ def test_lists_of_unlike_rows(lib, kind, N, d, k):
         rows[N // 3] = rows[N // 5] = False
         assert torch.equal(want[0][rows], got[0][rows]) and torch.equal(want[1][rows], got[1][rows])
         return
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
+# From 128 tiles on, rows whose lists overflow are searched for on their own, in lists of 1024.  A row has to be met by all copies of its
+# point and by all rows beyond float16, whatever its limit: more of them than a list of 256 holds, none or all of the other rows
+# left with them, in one to several batches; as many as the second list holds, and more, which the list kernels finish.
+@pytest.mark.parametrize("kind,many", [("copies", 300), ("copies", 900), ("copies", 1030), ("copies", 5000), ("two_points", 400),
+                                       ("beyond_float16", 257), ("beyond_float16", 1023), ("beyond_float16", 1200), ("both", 300)])
+@pytest.mark.parametrize("N,d,k", [(16_257, 160, 12), (20_000, 129, 20), (50_000, 100, 12), (49_030, 65, 7)])
+def test_rows_left_over(lib, kind, many, N, d, k):
+    print(f"pairs once, rows left over, {many} {kind}, N={N} d={d} k={k}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == 0.5 and 12 * (k + 1) <= 256
+    X = blobs(N, d, many)
+    at = torch.randperm(N, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    if kind in ("copies", "both"):
+        X[at[:many]] = X[at[0]].clone()
+    if kind == "two_points":
+        X[at[:many]] = X[at[0]].clone()
+        X[at[many:2 * many]] = X[at[many]].clone()
+    if kind in ("beyond_float16", "both"):
+        X[at[-many:]] *= 1e7
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
