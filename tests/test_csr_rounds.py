@@ -34,7 +34,7 @@ def check(lib, V, offsets, indices, weights):
     assert len(np.unique(c)) == V - len(lo) and np.array_equal(c[lo], c[hi]) and np.array_equal(c[c], c)
 
 
-# a vertex of more tree edges than are ordered in place, as the smaller and as the larger end, with ties and without; 32 and 33 edges
+# one vertex with all tree edges, as the smaller and as the larger end, with ties and without
 @pytest.mark.parametrize("V", [2, 33, 34, 35, 300, 70_000])
 @pytest.mark.parametrize("hub", ["first", "last"])
 @pytest.mark.parametrize("ties", [True, False])
@@ -45,6 +45,24 @@ def test_stars(lib, V, hub, ties):
     b = np.arange(1, V) if hub == "first" else np.arange(V - 1)
     w = rng.integers(1, 4, V - 1) if ties else rng.permutation(V - 1) + 0.5
     check(lib, V, *csr(V, a, b, w, rng))
+
+
+# vertices with as many tree edges to larger ones as are ordered in place, one less and one more, on both sides of the line from which on the
+# sort takes the smaller ends first; the rest of the tree a chain between them
+@pytest.mark.parametrize("V", [65_536, 65_537, 90_000])
+@pytest.mark.parametrize("edges", [31, 32, 33])
+@pytest.mark.parametrize("values", [1, 3, 1_000_000])
+def test_edges_per_smaller_end(lib, V, edges, values):
+    print(f"csr V={V}, {edges} edges per smaller end, {values} weights", flush=True)
+    rng = np.random.default_rng(V + edges)
+    n = V // (edges + 1)
+    hubs, others = rng.permutation(n), n + rng.permutation(V - n)
+    own = others[:n * (edges - 1)].reshape(n, edges - 1)
+    link = others[n * (edges - 1):][:n]                          # the last edge of a hub; the next hub's, too, would be one too many
+    a = np.r_[np.repeat(hubs, edges - 1), hubs, link[:-1]]
+    b = np.r_[own.ravel(), link, own[1:, 0]]
+    assert np.bincount(np.minimum(a, b), minlength=V)[:n].tolist() == [edges] * n
+    check(lib, V, *csr(V, a, b, rng.integers(0, values, len(a)), rng))
 
 
 # rows in no order, several edges between two vertices, self loops, vertices without edges, many trees; weights of few values and of many, 0 included
