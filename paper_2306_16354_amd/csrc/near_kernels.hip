@@ -658,8 +658,10 @@ constexpr int ITEM_TILES = 64;
 // the candidate tiles, which the workgroup's wavefronts bring into LDS together (double buffered, one barrier per
 // tile).  A lane's 16 values of a 32 x 32 block belong to one query, so bounds and counts are registers.
 // Fragment order in memory makes every load and every LDS read consecutive over the lanes.
+// (Emission of up to 32 columns is held to 128 registers, with which two workgroups of eight wavefronts share a CU: with one more, 300 000 x 10
+// rows without clusters in the row order took 9.9 ms of it instead of 7.1.)
 template <int KS, int MODE, bool COLOURED, bool LISTED>
-__global__ void __launch_bounds__(512, 2) near_sweep_kernel(NearSweep p)
+__global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : 2) near_sweep_kernel(NearSweep p)
 {
     extern __shared__ __align__(16) unsigned char near_smem[];
     constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, colours
