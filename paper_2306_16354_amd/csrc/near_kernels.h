@@ -15,8 +15,7 @@ struct NearScale {
 };
 
 // The rows of a matrix rounded to float16, in tiles of 128 in the order the matrix instruction reads them.
-// Position p of the copy holds row (p % 128) * tiles + p / 128, so every tile is an even sample of the rows; with
-// `in_order` it holds row p.
+// Every tile is an even sample of the rows, whatever order they are in (near_row); with `in_order` position p holds row p.
 struct NearCopy {
     unsigned char* frag;       // [tiles][steps of 16 columns][4 blocks of 32 rows][64 lanes][16 bytes]
     float* negh;               // [tiles * 128] minus the half norm; -inf: no such row, +inf: values beyond float16

@@ -197,7 +197,7 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     for (int i = 0; i < PASSES; ++i) {
         nn[i] = rr[i] = xx[i] = 0.f; huge[i] = false;
         const int in_tile = blk * 32 + sub + i * ROWS;
-        const long long at = p.in_order ? (long long)t * TILE + in_tile : (long long)in_tile * p.tiles + t;
+        const long long at = near_row(t * TILE + in_tile, p.tiles, p.in_order);
         long long row = mine && at < n_in && !empty ? (p.rows ? (long long)p.rows[at] : at) : -1;
         if (row >= p.n_src) row = -1;
         src[i] = row;
@@ -333,8 +333,9 @@ struct NearSweep {
     const unsigned char* cfrag; const float* cnegh; const int32_t* ccolour; int c_tiles;
     const NearScale* sc; float e, nu; int d, steps;
     // item = panel * nseg + seg; seg takes tiles seg, seg + nseg, ... of a list of `used` candidate tiles: every
-    // stride-th one (skip = 0), or all but those (skip = 1)
-    int nseg, stride, used, skip;
+    // stride-th one (skip = 0), or all but those (skip = 1); spread: near_spread(used) or 0 (maxima, not listed: in that order, so that a
+    // part of them is an even sample of the rows too)
+    int nseg, stride, used, skip, spread;
     // queries counted on the device (n_dev, over all batches): the panels that exist share `slots` workgroups in at most
     // most_seg segments each
     const int32_t* n_dev; int slots, most_seg;
@@ -646,9 +647,11 @@ __device__ inline NearShare near_share(const NearSweep& p, int item, int panel_t
     return r;
 }
 
-__device__ inline int near_tile_at(const NearSweep& p, int seg, int nseg, int i)
+// the j-th candidate tile
+template <int MODE>
+__device__ inline int near_tile_at(const NearSweep& p, int j)
 {
-    const int j = seg + i * nseg;
+    if (MODE == NEAR_MAXIMA && p.spread) j = near_spread_at(j, p.spread, p.used);
     return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride;
 }
 
@@ -659,9 +662,9 @@ constexpr int ITEM_TILES = 64;
 // tile).  A lane's 16 values of a 32 x 32 block belong to one query, so bounds and counts are registers.
 // Fragment order in memory makes every load and every LDS read consecutive over the lanes.
 // (Emission of up to 32 columns is held to 128 registers, with which two workgroups of eight wavefronts share a CU: with one more, 300 000 x 10
-// rows without clusters in the row order took 9.9 ms of it instead of 7.1.)
+// rows without clusters in the row order took 9.9 ms of it instead of 7.1.  Likewise maxima of 80 columns to 168 registers, three workgroups of four.)
 template <int KS, int MODE, bool COLOURED, bool LISTED>
-__global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : 2) near_sweep_kernel(NearSweep p)
+__global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 5 && MODE == NEAR_MAXIMA ? 3 : 2) near_sweep_kernel(NearSweep p)
 {
     extern __shared__ __align__(16) unsigned char near_smem[];
     constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, colours
@@ -720,7 +723,7 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : 2) nea
     // sweeps for first edges and 0.49 for nearest rows, 1.59 and 0.42 so; 1M x 128: 9.9 and 1.6 ms, 9.3 and 1.4, emission 17.9 and 17.4)
     int listed = 0, listed_reg = -1, listed_colour = -1;
     auto tile_at = [&](int i) -> int {
-        if (!LISTED) return near_tile_at(p, seg, nseg, i);
+        if (!LISTED) return near_tile_at<MODE>(p, seg + i * nseg);
         if ((i & 63) == 0) {
             const int j = seg + (i + lane) * nseg;
             listed = j < used ? (int)list[j * list_step] : 0;
@@ -854,7 +857,7 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
 
     const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
     const int nmine = seg < npairs ? (npairs - seg + nseg - 1) / nseg : 0;
-    auto listed = [&](int j) -> int { return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride; };
+    auto listed = [&](int j) -> int { return near_tile_at<MODE>(p, j); };
     const int total = nmine * nchunks;
     // positions of the queries whose pieces this wavefront brings in (wavefronts 0 to 3, one tile each for two)
     int q_src[4] = {0, 0, 0, 0};
@@ -1648,6 +1651,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     p.sc = b.scale; p.d = a.d; p.steps = steps; p.e = e; p.nu = nu; p.kk = kk;
     const NearPlan& q = plan.sample;
     p.stride = q.stride; p.used = q.used; p.nseg = q.max_seg; p.parts = q.max_parts; p.groups = q.groups;
+    p.spread = near_spread(q.used);
     float* maxima = reinterpret_cast<float*>(entries);              // (the lists are empty yet)
     const size_t per_tile = (size_t)TILE * q.max_sets * q.groups * 4;
     long long batch = (long long)(lists_bytes / per_tile) / q.panel_tiles * q.panel_tiles;
@@ -1665,7 +1669,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
                            static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE);
     }
     NearPairs r{};
-    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks;
+    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks; r.spread = near_spread(r.blocks);
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
     for (int i = 0; i < plan.bands; ++i) {
         if (i > 0) {
@@ -2424,7 +2428,7 @@ __global__ void __launch_bounds__(256) near_pair_best_kernel(const unsigned long
     const int row = rows[q];
     unsigned long long out = ~0ull;
     if ((unsigned int)row < (unsigned int)n_rows) {
-        const int pos = row % tiles * TILE + row / tiles;               // (see near_row)
+        const int pos = near_pos(row, tiles);
         const unsigned long long key = best[pos];
         const float w = __uint_as_float((unsigned int)(key >> 32)), h = -negh[pos];
         if (w < INF && fabsf(h) < INF) {
@@ -2440,7 +2444,7 @@ static hipError_t near_link_pairs(const NearLink& a, const NearCopy& q, const Ne
 {
     NearPairs r{};
     r.frag = c.frag; r.negh = c.negh_best; r.colour = c.colour; r.tiles = c.tiles; r.steps = near_steps(a.d);
-    r.blocks = (c.tiles + 1) / 2;
+    r.blocks = (c.tiles + 1) / 2; r.spread = near_spread(r.blocks);
     r.best = reinterpret_cast<unsigned long long*>(b.batch);
     const int n = c.tiles * TILE, half = r.blocks / 2 + 1, cus = near_cus();
     hipLaunchKernelGGL(near_pair_best_clear_kernel, dim3((unsigned)((n + 255) / 256)), dim3(256), 0, s, r.best, n);
@@ -2684,11 +2688,11 @@ __global__ void __launch_bounds__(256) near_unpack_kernel(const unsigned long lo
     const long long t = (long long)blockIdx.x * 256 + threadIdx.x;
     const int p = (int)(t >> 3), g = (int)(t & 7);
     if (p >= q_tiles * TILE) return;
-    const long long qi = (long long)(p & (TILE - 1)) * q_tiles + (p >> 7);
+    const long long qi = near_row(p, q_tiles, 0);
     if (qi >= nq) return;
     const unsigned long long key = best_at[p];
     const int pos = (int)(unsigned int)key;
-    const long long cand = (long long)(pos & (TILE - 1)) * c_tiles + (pos >> 7);
+    const long long cand = near_row(pos, c_tiles, 0);
     const bool fine = key != 0ull && cand < nc && fabsf(qnegh[p]) < 1e37f;
     float s = 0.f;
     if (fine) {

@@ -154,9 +154,37 @@ __device__ inline void near_lds_ready()
     asm volatile("" ::: "memory");
 }
 
+// Where the rows of a matrix lie in a copy that is not in their order: row b * tiles + i, i < tiles, in tile i + near_shift(b) and there at
+// place b - near_turn(tile), round and round.  So a tile has one row of every stretch of `tiles` rows and is an even sample of them,
+// whatever order they are in.  The shift: where row i is of cluster i % n, and n and `tiles` have a divisor in common, tile i would have the rows
+// of a few clusters only.  The turn: where rows lie in the order of their clusters, the same place of all tiles would have the
+// rows of one, and the groups that a sample's maxima are taken of are places.
+__device__ inline int near_turn(int tile) { return (int)(((unsigned int)tile * 0x9e3779b1u) >> 25); }
+__device__ inline int near_shift(int b, int tiles) { return (int)__umulhi((unsigned int)b * 0x9e3779b1u, (unsigned int)tiles); }
 __device__ inline long long near_row(int pos, int tiles, int in_order)
 {
-    return in_order ? (long long)pos : (long long)(pos & (TILE - 1)) * tiles + (pos >> 7);
+    if (in_order) return pos;
+    const int t = pos >> 7, b = (pos + near_turn(t)) & (TILE - 1), i = t - near_shift(b, tiles);
+    return (long long)b * tiles + (i < 0 ? i + tiles : i);
 }
+__device__ inline int near_pos(int row, int tiles)             // (not in order)
+{
+    const int b = row / tiles, i = row - b * tiles + near_shift(b, tiles), t = i < tiles ? i : i - tiles;
+    return t * TILE + ((b - near_turn(t)) & (TILE - 1));
+}
+
+// i * near_spread(n) % n for i = 0, 1, ...: the numbers below n in an order whose every stretch is spread evenly over them (n times the
+// golden ratio, or the next number that has no divisor in common with n).  Products below 2^32: up to n = 2^17, beyond that as they are.
+inline int near_spread(int n)
+{
+    if (n > 1 << 17) return 1;
+    int m = (int)(0.6180339887498949 * n);
+    for (m = m < 1 ? 1 : (m > 32000 ? 32000 : m);; ++m) {
+        int a = m, b = n;
+        while (b) { const int r = a % b; a = b; b = r; }
+        if (a == 1) return m;
+    }
+}
+__device__ inline int near_spread_at(int i, int spread, int n) { return (int)((unsigned int)i * (unsigned int)spread % (unsigned int)n); }
 
 }  // namespace slhc

@@ -13,6 +13,7 @@ struct NearPairs {
     const unsigned char* frag; const float* negh; const int32_t* colour;      // the copy (colour: pairs_best)
     int tiles, steps;
     int blocks, from, to, nseg;            // block i meets the blocks i + from .. i + to - 1, in nseg shares
+    int spread;                            // near_spread(blocks): place i of the circle has block i * spread % blocks of the copy
     float* limit;                          // pairs_emit: by position, the u from which on a pair matters to the row (NaN: none does)
     uint2* entries; int32_t* counts; int cap;      // pairs_emit: lists [rows][cap] of (u, position), appended to; counts beyond cap: some were lost
     // pairs_best: by position (w, position of the first of the 16 rows about it), w = max(0, -u) of the nearest row of another

@@ -7,9 +7,12 @@
 // half norm off.  A value is held against the limit of its query, a register, and against that of its candidate, which
 // comes through LDS with the candidate's norm.
 //
-// The copy is cut into blocks of consecutive tiles; block i meets the blocks i, i + 1, ... up to half way round the circle of
-// all blocks, so every pair of blocks meets once, every block has the same number of meetings, and a launch over a range of
-// these offsets has shown every row the same share of all others.
+// The copy is cut into blocks of consecutive tiles, laid out round a circle; the block at place i meets those at the places i, i + 1, ...
+// up to half way round, so every pair of blocks meets once, every block has the same number of meetings, and a launch over a
+// range of these offsets has shown every row the same share of all others.  Of those that are like it, too: rows that lie together in the
+// matrix lie in neighbouring tiles, so neighbouring blocks are far apart on the circle (near_spread).  With blocks in the order of the copy,
+// and rows in its tiles as their numbers give it, the lists of rows in the order of their clusters overflowed: clusters of 500 rows, k = 12,
+// 60 000 x 128 5.5 ms, 300 000 x 128 60 ms; 1.4 and 16.6 so (in no order 1.5 and 18.5).
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "near_kernels.h"
@@ -142,26 +145,27 @@ __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float 
 
 // Which blocks a workgroup's block meets: offsets [from, from + len) in an order in which all blocks of one stretch of the circle
 // meet the same block at the same time, so that it is in L2.
-struct PairRange { int block, from, len, j0, j1, turn; };
+struct PairRange { int at, block, from, len, j0, j1, turn; };      // at: of the circle, block: of the copy
 __device__ inline PairRange pair_range(const NearPairs& p, int item)
 {
     PairRange r;
-    r.block = item / p.nseg;
-    const int seg = item - r.block * p.nseg;
+    r.at = item / p.nseg;
+    r.block = near_spread_at(r.at, p.spread, p.blocks);
+    const int seg = item - r.at * p.nseg;
     // half way round an even circle two blocks meet from both sides
-    const int to = 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.block >= p.blocks ? p.to - 1 : p.to;
+    const int to = 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.at >= p.blocks ? p.to - 1 : p.to;
     r.from = p.from;
     r.len = to > p.from ? to - p.from : 0;
     r.j0 = (int)((long long)r.len * seg / p.nseg);
     r.j1 = (int)((long long)r.len * (seg + 1) / p.nseg);
-    r.turn = r.len > 0 ? r.len - r.block % r.len : 0;
+    r.turn = r.len > 0 ? r.len - r.at % r.len : 0;
     return r;
 }
 __device__ inline int pair_offset(const PairRange& r, int j) { return r.from + (j + r.turn) % r.len; }
 __device__ inline int pair_other(const NearPairs& p, const PairRange& r, int offset)
 {
-    const int c = r.block + offset;
-    return c >= p.blocks ? c - p.blocks : c;
+    const int c = r.at + offset;
+    return near_spread_at(c >= p.blocks ? c - p.blocks : c, p.spread, p.blocks);
 }
 
 // Up to 128 columns: as near_sweep_kernel, a wavefront keeps the fragments of 64 queries in registers and the candidate tiles pass
@@ -198,10 +202,12 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
     int next_tile = 0;
     bool next_own = false;
     auto advance = [&]() {
-        const int off = pair_offset(range, step_j);
-        next_tile = pair_other(p, range, off) * bt + step_t;
-        next_own = off == 0;
-        if (++step_t == bt) { step_t = 0; ++step_j; }
+        if (step_t == 0) {
+            const int off = pair_offset(range, step_j++);
+            next_tile = pair_other(p, range, off) * bt;
+            next_own = off == 0;
+        } else ++next_tile;
+        if (++step_t == bt) step_t = 0;
     };
     auto stage = [&](int i, int tile) {
         const size_t t = tile < p.tiles ? tile : p.tiles - 1;
@@ -581,7 +587,7 @@ __global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, c
 // ---------------------------------------------------------------------------------------------- launches
 hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
 {
-    if (p.tiles < 1 || p.tiles >= (1 << PAIR_TILE_BITS) || p.cap < 1 || p.cap > PAIRS_MOST || p.nseg < 1) return hipErrorInvalidValue;
+    if (p.tiles < 1 || p.tiles >= (1 << PAIR_TILE_BITS) || p.cap < 1 || p.cap > PAIRS_MOST || p.nseg < 1 || p.spread < 1) return hipErrorInvalidValue;
     const bool wide = p.steps > REG_STEPS;
     const int bt = wide ? 2 : waves / 2;
     if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > p.blocks / 2 + 1) return hipErrorInvalidValue;
@@ -607,7 +613,7 @@ hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
 
 hipError_t pairs_best(const NearPairs& p, hipStream_t s)
 {
-    if (p.tiles < 1 || p.steps <= REG_STEPS || p.nseg < 1 || p.blocks != (p.tiles + 1) / 2 || p.from < 0 || p.to > p.blocks) return hipErrorInvalidValue;
+    if (p.tiles < 1 || p.steps <= REG_STEPS || p.nseg < 1 || p.spread < 1 || p.blocks != (p.tiles + 1) / 2 || p.from < 0 || p.to > p.blocks) return hipErrorInvalidValue;
     hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&pairs_wide_kernel<true>), hipFuncAttributeMaxDynamicSharedMemorySize, WIDE_LDS);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL((pairs_wide_kernel<true>), dim3((unsigned)(p.blocks * p.nseg)), dim3(512), WIDE_LDS, s, p);

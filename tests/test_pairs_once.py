@@ -91,6 +91,42 @@ def test_rows_left_over(lib, kind, many, N, d, k):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
+# Rows in the order of their clusters, one of every cluster in turn, rows along a path: the same lists as in no order, in about the same time
+# (up to 60 times as long where the places of the rows in the copy went by their numbers alone)
+@pytest.mark.parametrize("kind", ["in_order", "in_turn", "path"])
+@pytest.mark.parametrize("N,d,k", [(12_800, 48, 12), (25_000, 160, 12), (60_000, 128, 12), (60_000, 128, 50), (150_000, 80, 50)])
+def test_rows_in_some_order(lib, kind, N, d, k):
+    print(f"pairs once, rows {kind}, N={N} d={d} k={k}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    row = torch.arange(N, device="cuda")
+    X = torch.randn((N, d), generator=g, device="cuda")
+    if kind == "path":
+        X += torch.cumsum(0.1 * torch.randn((N, d), generator=g, device="cuda"), 0)
+    else:
+        clusters = N // 500 if kind == "in_order" else 50
+        centres = (2 * torch.rand((clusters, d), generator=g, device="cuda") - 1) * 20
+        X += centres[row * clusters // N if kind == "in_order" else row % clusters]
+    order = torch.randperm(N, generator=g, device="cuda")
+    workspace = torch.empty(lib.knn_workspace_bytes(N, d, k), dtype=torch.uint8, device="cuda")
+
+    def search(rows):
+        least = float("inf")
+        for _ in range(6):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            lists = lib.knn_graph(rows, k, workspace=workspace)
+            end.record()
+            end.synchronize()
+            least = min(least, begin.elapsed_time(end))
+        return lists, least
+
+    got, ms = search(X)
+    shuffled, ms_shuffled = search(X[order].contiguous())
+    assert torch.equal(got[1][order], shuffled[1])
+    assert (got[0][order] == order[shuffled[0].long()]).float().mean() > 0.999          # (else: ties)
+    assert ms < 1.6 * ms_shuffled, (ms, ms_shuffled)
+
+
 # the first connection round asks for most rows; few and many components, copies, a far row
 @pytest.mark.parametrize("kind", ["clusters", "pairs", "copies", "far_row"])
 @pytest.mark.parametrize("N,d", [(4097, 130), (6000, 256), (20_001, 300)])
