@@ -713,6 +713,8 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
             for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const v8h*>(src + ks * FRAG_STEP);
         }
     }
+    // (a second search of the rows left over: whose lists overflowed, see pairs_again)
+    if (MODE == NEAR_NEAREST && !LISTED && !__syncthreads_or(!(mine.bound[0] != mine.bound[0] && mine.bound[1] != mine.bound[1]))) return;
     // first bounds come from the one copy that holds all of a query's region
     const int first_reg = LISTED && MODE == NEAR_MAXIMA && p.side ? __builtin_amdgcn_readfirstlane(mine.reg[0]) : 0;
     const bool mine_here = !(LISTED && MODE == NEAR_MAXIMA && p.side) || (p.side == 1) == (first_reg >= 0);
@@ -855,6 +857,7 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     NearLane<MODE, COLOURED> mine;
     mine.start(p, qtile, qblk, l32, sub, live);
 
+    if (MODE == NEAR_NEAREST && !__syncthreads_or(!(mine.bound[0] != mine.bound[0] && mine.bound[1] != mine.bound[1]))) return;      // (as in near_sweep_kernel)
     const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
     const int nmine = seg < npairs ? (npairs - seg + nseg - 1) / nseg : 0;
     auto listed = [&](int j) -> int { return near_tile_at<MODE>(p, j); };
@@ -976,7 +979,8 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
                                                           float nu, int steps, int d, float* __restrict__ bound, float* __restrict__ reach,
                                                           const int32_t* __restrict__ step, int panel_queries,
                                                           const int32_t* __restrict__ region, const float* __restrict__ negh_local,
-                                                          const NearScale* __restrict__ sc_local, int32_t* __restrict__ limit_counts, int32_t* __restrict__ limit_last)
+                                                          const NearScale* __restrict__ sc_local, int32_t* __restrict__ limit_counts, int32_t* __restrict__ limit_last,
+                                                          int32_t* __restrict__ limit_lost)
 {
     const int lane = threadIdx.x & 63;
     const int lq = blockIdx.x * 4 + (threadIdx.x >> 6);
@@ -1019,6 +1023,7 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
         const float made = have < kk ? LOWEST : fmaxf(LOWEST, near_bound_from(lo, -nh, a));
         if (LIMIT) {                    // of a row for pairs_emit; none where there is no row or it goes to the list kernels
             limit_counts[lq] = limit_last[lq] = 0;
+            if (lq == 0) *limit_lost = 0;
             bound[lq] = !(fabsf(nh) < INF) ? NEVER : made == LOWEST ? LOWEST : made + nh;
             return;
         }
@@ -1550,7 +1555,9 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
 // then the offsets round the circle of blocks in a few bands; between two bands every row's limit is tightened by what its list
 // holds.  A list needs room for what passes before the next tightening: kk * g entries and what rounding adds, if a band has
 // seen g times as many rows at its end as at its beginning (every tile is an even sample of the rows).  Rows whose lists
-// overflow all the same are searched for on their own, with the buffers and the tightening of the sweeps.
+// overflow all the same are searched for on their own, with the buffers and the tightening of the sweeps.  A row has to keep all its copies,
+// so where every point is there some hundred times most rows overflow; the rest of the bands is left out then, and every row
+// searched for: 150 000 x 80, k = 12, 2000 copies each, 202 ms without that, 142 so.
 // (Sorting the rows by their nearest of a few hundred pivots first, so that what passes comes together, was tried: limits then come from
 // a row's own surroundings and say nothing about the other rows, a third of the rows overflowed, 1M x 128 took 250 ms
 // without their panels against 200 ms.)
@@ -1572,7 +1579,10 @@ static bool pair_search_wanted(int T, int steps)
 // from here on rows whose lists overflow are searched for on their own before the list kernels take their panels; below, the five
 // launches cost more (20 us) than a panel or two
 constexpr int PAIR_AGAIN_TILES = 128;
-static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
+// bytes: of the memory for them (0: the least there may be).  Lists are as long as it allows, up to PAIRS_MOST, which costs nothing where they
+// stay short (5000 x 200 and 16 000 x 300, lists of 256 and 1024: the same times) and leaves fewer rows over.
+static size_t pair_lists_bytes(int T, int cap) { return (size_t)T * TILE * (24 + 8 * (size_t)cap) + 4096; }
+static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* out)
 {
     const int T = near_tiles(n), steps = near_steps(d);
     if (kk < 2 || !pair_search_wanted(T, steps)) return false;
@@ -1620,6 +1630,7 @@ static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
     seg = seg > limit ? limit : seg;
     seg = seg > units ? units : seg;
     near_sample(q, stride, T, kk, wide, seg < 1 ? 1 : seg);
+    while (p.cap + 64 <= PAIRS_MOST && pair_lists_bytes(T, p.cap + 64) <= bytes) p.cap += 64;
     *out = p;
     return true;
 }
@@ -1627,8 +1638,7 @@ static bool near_pair_plan(long long n, int d, int kk, PairPlan* out)
 size_t near_pairs_bytes(long long n, int d, int kk)
 {
     PairPlan p;
-    if (!near_pair_plan(n, d, kk, &p)) return 0;
-    return (size_t)near_tiles(n) * TILE * (24 + 8 * (size_t)p.cap) + 4096;
+    return near_pair_plan(n, d, kk, 0, &p) ? pair_lists_bytes(near_tiles(n), p.cap) : 0;
 }
 
 static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, const NearBuffers& b, const PairPlan& plan, bool vec4, hipStream_t s)
@@ -1644,6 +1654,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     left.row = reinterpret_cast<int32_t*>(take((size_t)rows * 4)); left.pos = reinterpret_cast<int32_t*>(take((size_t)rows * 4));
     left.counts = reinterpret_cast<int32_t*>(take((size_t)rows * 4)); left.reach = reinterpret_cast<float*>(take((size_t)rows * 4));
     left.count = b.todo + 1;
+    int32_t* lost = reinterpret_cast<int32_t*>(take(4));
     const size_t lists_bytes = (size_t)rows * (size_t)plan.cap * 8;
     uint2* entries = reinterpret_cast<uint2*>(take(lists_bytes));
     NearSweep p{};
@@ -1666,11 +1677,13 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
         hipLaunchKernelGGL((near_bounds_kernel<true>), dim3((unsigned)(p.nq_batch / 4)), dim3(256), 0, s, maxima, q.max_sets, q.groups == GROUPS ? 5 : 3, p.nq_batch,
                            t0 * TILE, kk, c.negh, b.scale, e, nu, steps, a.d, limit + (size_t)t0 * TILE, static_cast<float*>(nullptr),
                            static_cast<const int32_t*>(nullptr), 1, static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr),
-                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE);
+                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE, lost);
     }
     NearPairs r{};
     r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks; r.spread = near_spread(r.blocks);
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
+    const bool again = c.tiles >= PAIR_AGAIN_TILES;
+    r.lost = lost; r.lost_most = again ? a.nq / 2 : rows;
     for (int i = 0; i < plan.bands; ++i) {
         if (i > 0) {
             err = pairs_tighten(r, kk, b.scale, e, nu, a.d, left.row, s);       // (no rows are left yet)
@@ -1680,7 +1693,6 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
         err = pairs_emit(r, plan.waves, s);
         if (err != hipSuccess) return err;
     }
-    const bool again = c.tiles >= PAIR_AGAIN_TILES;
     if (again) {
         err = pairs_left(r, kk, b.scale, e, nu, a.d, a.nq, left, s);
         if (err != hipSuccess) return err;
@@ -1733,8 +1745,8 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
         return hipErrorInvalidValue;
     const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
     PairPlan pairs;
-    if (a.exclude_self && q.frag == c.frag && !c.in_order && b.pairs && near_pair_plan(a.nc, a.d, kk, &pairs) &&
-        b.pairs_bytes >= near_pairs_bytes(a.nc, a.d, kk))
+    if (a.exclude_self && q.frag == c.frag && !c.in_order && b.pairs && near_pair_plan(a.nc, a.d, kk, b.pairs_bytes, &pairs) &&
+        b.pairs_bytes >= pair_lists_bytes(c.tiles, pairs.cap))
         return near_search_pairs(a, c, b, pairs, vec4, s);
     NearSweep p{};
     p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour;
@@ -1783,7 +1795,8 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
         }
         hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, plan.used ? plan.max_sets : 0,
                            plan.groups == GROUPS ? 5 : 3, nqb, t0 * TILE, kk, q.negh, b.scale, p.e, p.nu, p.steps, a.d, bound, static_cast<float*>(nullptr), static_cast<const int32_t*>(nullptr), 1,
-                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr), static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+                           static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr), static_cast<const NearScale*>(nullptr), static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+                           static_cast<int32_t*>(nullptr));
         p.nseg = plan.nseg; p.nsub = plan.nsub;
         sel.nsub = plan.nsub; sel.by_position = 0; sel.merge = 0; sel.next_bound = nullptr;
         if (plan.stages == 2) {
@@ -2242,7 +2255,8 @@ hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const N
         sel.nq_batch = nqb; sel.q0 = t0 * TILE;
         auto bounds = [&](int sets, const int32_t* steps_of) {
             hipLaunchKernelGGL((near_bounds_kernel<false>), per_query, dim3(256), 0, s, maxima, sets, 5, nqb, t0 * TILE, kk, o.all.negh, b.scale, p.e, p.nu,
-                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale, static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr));
+                               p.steps, a.d, bound, reach, steps_of, plan.panel_tiles * TILE, o.region, o.local.negh, o.local_scale, static_cast<int32_t*>(nullptr), static_cast<int32_t*>(nullptr),
+                           static_cast<int32_t*>(nullptr));
         };
         NearList l{};
         l.gap = o.gap; l.T = T; l.region = o.region; l.reach = reach; l.n_pos = T * TILE; l.q0 = t0 * TILE; l.nq = nqb;

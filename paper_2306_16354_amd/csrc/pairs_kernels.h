@@ -16,6 +16,8 @@ struct NearPairs {
     int spread;                            // near_spread(blocks): place i of the circle has block i * spread % blocks of the copy
     float* limit;                          // pairs_emit: by position, the u from which on a pair matters to the row (NaN: none does)
     uint2* entries; int32_t* counts; int cap;      // pairs_emit: lists [rows][cap] of (u, position), appended to; counts beyond cap: some were lost
+    // pairs_emit: rows whose lists overflowed, as far as pairs_tighten has counted them; beyond lost_most of them pairs_emit does nothing
+    int32_t* lost; int lost_most;
     // pairs_best: by position (w, position of the first of the 16 rows about it), w = max(0, -u) of the nearest row of another
     // colour so far; not 0x7f.. / all ones in the beginning.  both = 0: the block's own rows only are served
     unsigned long long* best; int both;
@@ -23,12 +25,12 @@ struct NearPairs {
 // waves: wavefronts per workgroup up to 128 columns (a block is half as many tiles; beyond, two)
 hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s);
 hipError_t pairs_best(const NearPairs& p, hipStream_t s);
-// Rows whose lists overflowed: their number in the matrix, position, an upper end of the squared distance of their kk-th nearest row,
-// a counter set to 0; the list's counter becomes 0.
+// Rows whose lists overflowed, or all of them after more than lost_most: their number in the matrix, position, an upper end of the squared
+// distance of their kk-th nearest row, a counter set to 0; the list's counter becomes 0.
 struct PairsLeft { int32_t *row, *pos, *counts, *count; float* reach; };
 hipError_t pairs_left(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int n_rows, const PairsLeft& out, hipStream_t s);
 // The n rows left from `first` on, with lists [n][cap] of (product value, position): those that overflowed get the distance that follows
-// and an empty list, the others a distance that nothing is within.
+// and an empty list, the others a distance that nothing is within, and so does one to whom the distance is no news: its list would overflow again.
 hipError_t pairs_again(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int first, int n, const PairsLeft& left, hipStream_t s);
 // last: by position, entries after the last call, 0 at first
 hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int32_t* last, hipStream_t s);

@@ -178,6 +178,7 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6, bt = waves >> 1;
+    if (*p.lost > p.lost_most) return;
     const PairRange range = pair_range(p, blockIdx.x);
     const int qtile = range.block * bt + (wave >> 1);
     const bool live = qtile < p.tiles;                   // (whole wavefronts)
@@ -294,6 +295,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int qg = wave >> 1, cg = wave & 1;                            // 64 queries, 128 candidates of the 256 x 256
+    if (!BEST && *p.lost > p.lost_most) return;
     int item = blockIdx.x;
     {
         // workgroups b, b + 8, ... share an XCD: they get the shares of neighbouring blocks, whose rows stay in its L2
@@ -516,7 +518,11 @@ __global__ void __launch_bounds__(256) pairs_tighten_kernel(NearPairs p, int kk,
     if (row >= p.tiles * TILE) return;
     const int n = __builtin_amdgcn_readfirstlane(p.counts[row]);
     if (n > p.cap) {                                                    // some were lost: nothing more (see pairs_left)
-        if (lane == 0) { p.counts[row] = p.cap + 1; p.limit[row] = NEVER; }
+        if (lane == 0 && p.limit[row] == p.limit[row]) {
+            p.counts[row] = p.cap + 1; p.limit[row] = NEVER;
+            // (one word, so no more additions than count)
+            if (__hip_atomic_load(p.lost, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) <= p.lost_most) atomicAdd(p.lost, 1);
+        }
         return;
     }
     const float h = -p.negh[row];
@@ -548,21 +554,37 @@ __device__ inline float pair_reach(float value, float h, const NearBoundArgs& a,
     const float t = value > LOWEST ? near_distance_from(value, h, a) / sc->scale : INF;
     return (t * t * (1.f + a.gamma) + (float)d * 2.350988701644575e-38f) * (1.f + 1e-6f);
 }
-__global__ void __launch_bounds__(256) pairs_left_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int n_rows,
+// (one addition to the word of all rows left for LEFT_ROWS rows: 60 000 of them 0.7 ms with one for each)
+constexpr int LEFT_ROWS = 16;
+__global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int n_rows,
                                                          PairsLeft out)
 {
-    const int pos = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (pos >= p.tiles * TILE || p.counts[pos] <= p.cap) return;
+    __shared__ int s_here, s_from;
+    const int pos = blockIdx.x * LEFT_ROWS + (threadIdx.x >> 6), lane = threadIdx.x & 63;
+    const bool over = p.counts[pos] > p.cap;
     const float h = -p.negh[pos];
     const long long row = near_row(pos, p.tiles, 0);
-    if (!(fabsf(h) < INF) || row >= n_rows) return;
-    uint2 mine[PAIR_WORDS];
-    pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
-    const float kth = pair_kth(mine, p.cap, kk);
+    const bool left = (over || *p.lost > p.lost_most) && fabsf(h) < INF && row < n_rows;
+    if (threadIdx.x == 0) s_here = 0;
+    __syncthreads();
+    int at = 0;
+    if (left && lane == 0) at = atomicAdd(&s_here, 1);
+    __syncthreads();
+    if (threadIdx.x == 0) s_from = s_here > 0 ? atomicAdd(out.count, s_here) : 0;
+    __syncthreads();
+    if (!left) return;
+    // a value that kk rows reach: of the list, or what the row's limit, itself below such a value, comes from
+    float value = LOWEST;
+    if (over) {
+        uint2 mine[PAIR_WORDS];
+        pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
+        const float kth = pair_kth(mine, p.cap, kk);
+        if (kth != LOWEST) value = kth + h;
+    } else if (p.limit[pos] > LOWEST) value = p.limit[pos] + h;
     if (lane != 0) return;
-    const int i = atomicAdd(out.count, 1);
+    const int i = s_from + at;
     out.row[i] = (int)row; out.pos[i] = pos; out.counts[i] = 0;
-    out.reach[i] = pair_reach(kth == LOWEST ? LOWEST : kth + h, h, near_args(sc, p.steps, d, e, nu), sc, d);
+    out.reach[i] = pair_reach(value, h, near_args(sc, p.steps, d, e, nu), sc, d);
     p.counts[pos] = 0;
 }
 __global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int first, int n,
@@ -580,8 +602,10 @@ __global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, c
     pair_list(mine, p.entries + (size_t)i * (size_t)p.cap, p.cap);
     const float kth = pair_kth(mine, p.cap, kk);
     if (lane != 0) return;
-    left.counts[at] = 0;
-    left.reach[at] = fminf(left.reach[at], pair_reach(kth, h, near_args(sc, p.steps, d, e, nu), sc, d));
+    const float reach = pair_reach(kth, h, near_args(sc, p.steps, d, e, nu), sc, d);
+    const bool news = reach < 0.999f * left.reach[at];
+    if (news) left.counts[at] = 0;                                      // (else: overflowed for good, which near_select finds)
+    left.reach[at] = news ? reach : -1.f;
 }
 
 // ---------------------------------------------------------------------------------------------- launches
@@ -628,7 +652,7 @@ hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float 
 
 hipError_t pairs_left(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int n_rows, const PairsLeft& out, hipStream_t s)
 {
-    hipLaunchKernelGGL(pairs_left_kernel, dim3((unsigned)(p.tiles * (TILE / 4))), dim3(256), 0, s, p, kk, sc, e, nu, d, n_rows, out);
+    hipLaunchKernelGGL(pairs_left_kernel, dim3((unsigned)(p.tiles * (TILE / LEFT_ROWS))), dim3(64 * LEFT_ROWS), 0, s, p, kk, sc, e, nu, d, n_rows, out);
     return hipGetLastError();
 }
 

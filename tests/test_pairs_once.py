@@ -68,14 +68,16 @@ def test_lists_of_unlike_rows(lib, kind, N, d, k):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
-# From 128 tiles on, rows whose lists overflow are searched for on their own, in lists of 1024.  A row has to be met by all copies of its
-# point and by all rows beyond float16, whatever its limit: more of them than a list of 256 holds, none or all of the other rows
-# left with them, in one to several batches; as many as the second list holds, and more, which the list kernels finish.
-@pytest.mark.parametrize("kind,many", [("copies", 300), ("copies", 900), ("copies", 1030), ("copies", 5000), ("two_points", 400),
-                                       ("beyond_float16", 257), ("beyond_float16", 1023), ("beyond_float16", 1200), ("both", 300)])
+# Rows whose lists overflow are searched for on their own from 128 tiles on, in lists of 1024.  A row has to be met by all copies of its point
+# and by all rows beyond float16, whatever its limit.  As many of them as a list holds and more, with the memory for lists of 1024
+# (all of the workspace) and of 256 or 320 (35 % of it): none, some or all of the rows left over, in one to several batches; as
+# many as the second list holds, and more, which the list kernels finish.
+@pytest.mark.parametrize("share", [1.0, 0.35])
+@pytest.mark.parametrize("kind,many", [("copies", 340), ("copies", 900), ("copies", 1030), ("copies", 5000), ("two_points", 400), ("all_points", 340), ("all_points", 700),
+                                       ("beyond_float16", 330), ("beyond_float16", 1023), ("beyond_float16", 1200), ("both", 340)])
 @pytest.mark.parametrize("N,d,k", [(16_257, 160, 12), (20_000, 129, 20), (50_000, 100, 12), (49_030, 65, 7)])
-def test_rows_left_over(lib, kind, many, N, d, k):
-    print(f"pairs once, rows left over, {many} {kind}, N={N} d={d} k={k}", flush=True)
+def test_rows_left_over(lib, kind, many, N, d, k, share):
+    print(f"pairs once, rows left over, {many} {kind}, N={N} d={d} k={k}, {share} of the workspace", flush=True)
     assert lib.probe_knn_products(N, d, k) == 0.5 and 12 * (k + 1) <= 256
     X = blobs(N, d, many)
     at = torch.randperm(N, generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
@@ -84,11 +86,38 @@ def test_rows_left_over(lib, kind, many, N, d, k):
     if kind == "two_points":
         X[at[:many]] = X[at[0]].clone()
         X[at[many:2 * many]] = X[at[many]].clone()
+    if kind == "all_points":
+        X = X[at % (N // many)].contiguous()
     if kind in ("beyond_float16", "both"):
         X[at[-many:]] *= 1e7
-    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    workspace = torch.empty(int(lib.knn_workspace_bytes(N, d, k) * share), dtype=torch.uint8, device="cuda")
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k, workspace=workspace)
     torch.cuda.synchronize()
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
+def least_ms(call):
+    least = float("inf")
+    for _ in range(6):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        out = call()
+        end.record()
+        end.synchronize()
+        least = min(least, begin.elapsed_time(end))
+    return out, least
+
+
+# Every point 300 times: lists that hold 300 rows for k = 12, in up to four times the time of a search without copies (6 to 20 times where rows
+# overflowed lists of 256)
+@pytest.mark.parametrize("N,d", [(5000, 200), (12_800, 48), (60_000, 128), (100_000, 400)])
+def test_time_of_copies(lib, N, d):
+    print(f"pairs once, copies, N={N} d={d}", flush=True)
+    X = blobs(N, d, N)
+    copies = X[torch.arange(N, device="cuda") % (N // 300)].contiguous()
+    workspace = torch.empty(lib.knn_workspace_bytes(N, d, 12), dtype=torch.uint8, device="cuda")
+    ms, ms_copies = (least_ms(lambda: lib.knn_graph(rows, 12, workspace=workspace))[1] for rows in (X, copies))
+    assert ms_copies < 4 * ms, (ms_copies, ms)
 
 
 # Rows in the order of their clusters, one of every cluster in turn, rows along a path: the same lists as in no order, in about the same time
@@ -109,17 +138,7 @@ def test_rows_in_some_order(lib, kind, N, d, k):
     order = torch.randperm(N, generator=g, device="cuda")
     workspace = torch.empty(lib.knn_workspace_bytes(N, d, k), dtype=torch.uint8, device="cuda")
 
-    def search(rows):
-        least = float("inf")
-        for _ in range(6):
-            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-            begin.record()
-            lists = lib.knn_graph(rows, k, workspace=workspace)
-            end.record()
-            end.synchronize()
-            least = min(least, begin.elapsed_time(end))
-        return lists, least
-
+    search = lambda rows: least_ms(lambda: lib.knn_graph(rows, k, workspace=workspace))
     got, ms = search(X)
     shuffled, ms_shuffled = search(X[order].contiguous())
     assert torch.equal(got[1][order], shuffled[1])
