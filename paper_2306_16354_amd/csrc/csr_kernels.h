@@ -25,13 +25,18 @@ hipError_t csr_start(const CsrForest& f, hipStream_t s);
 // `seq` above it.
 constexpr int CSR_TOLD = 4;
 hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s);
-// All rounds from `round` on; host[0] gets the rounds there were in all.  For at most CSR_TAIL active vertices.
-constexpr int CSR_TAIL = 2048;
+// All rounds from `round` on; host[0] gets the rounds there were in all.  For at most csr_tail_most active vertices (see k_csr_tail).
+inline long long csr_tail_most(long long V, long long E)
+{
+    constexpr long long most = 2048, entries = 12;
+    return E <= entries * V ? most : most * entries * V / E + 128;
+}
 hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uint32_t seq, hipStream_t s);
 hipError_t csr_follow_again(const CsrForest& f, int round, int vertices, hipStream_t s);
-// Colours of all vertices, and the check that no entry leads from one tree to another (words[CSR_ERROR]); nothing after a failed check
-// or with hooks not followed to their end.
+// Colours of all vertices.  And the check that no entry leads from one tree to another (words[CSR_ERROR]), for which they have to be
+// there and more than one.  Nothing after a failed check or with hooks not followed to their end.
 hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s);
+hipError_t csr_closed(const CsrForest& f, const int32_t* colours, hipStream_t s);
 
 // Edges by (weight, smaller end, larger end), in two steps: the first sets *flag where edge_sort has to do it instead, and tells host[0],
 // with `seq` above the flag.

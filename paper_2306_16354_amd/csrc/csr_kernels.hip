@@ -21,6 +21,10 @@ constexpr uint32_t INF_BITS = 0x7f800000u;
 constexpr int TB = 256, WIDE = 1024;      // (WIDE: kernels that append to a list, one atomic per workgroup)
 constexpr int FOLLOW_STEPS = 64;       // hooks followed in one launch
 static inline int blocks_for(long long n, int threads = TB) { return (int)((n + threads - 1) / threads); }
+// Up to FEW vertices rows are read by workgroups of TB threads: the fewer CUs read, the longer they take, and there are few additions to a list
+// then.  Calls with 1024 threads and 256, in us, 2.5 entries a vertex: 20 000 vertices 305 and 270, 130 000 470 and 431, 200 000 493
+// and 466; 20 entries: 395 and 303, 627 and 547, 804 and 821.
+constexpr int FEW = 131072;
 static inline int append_blocks(long long n) { const int b = blocks_for(n < 1 ? 1 : n, WIDE); return b > 512 ? 512 : b; }
 
 __device__ inline bool in_range(int i, int n) { return (unsigned int)i < (unsigned int)n; }
@@ -28,12 +32,13 @@ __device__ inline void report(const CsrForest& f, int site) { atomicCAS(f.words 
 // a failed check, or hooks that are not followed to their end yet, leave all rounds enqueued to the host
 __device__ inline bool halted(const CsrForest& f) { return (f.words[CSR_ERROR] | f.words[CSR_CHAINS]) != 0; }
 
-// A row of more entries than this is read by the whole wavefront, one of up to so many by its vertex's thread (road-like graphs have
-// two or three edges per vertex).  A thread takes 0.2 us per entry.  Calls with long rows by threads and by wavefronts: a star of 70 000
-// vertices 27 and 0.5 ms (one scan less, too: see k_csr_scan), a random graph of 1M vertices whose longest row has 65 583 entries
-// 97 and 9.6.  The line, random graphs of 200 000 vertices with 24, 48 and 96 entries on average: 956, 1420 and 1466 us with wavefronts
-// from 33 entries on, 888, 1486 and 1478 from 49 on, 889, 1757 and 1573 from 65 on.
-constexpr unsigned int LONG_ROW = 48;
+// A row of up to LONG_ROW entries is read by its vertex's thread (road-like graphs have two or three edges per vertex), which takes 0.2 us per
+// entry; one of up to HUGE_ROW by 16 lanes, four such rows at once; a longer one by the whole wavefront.  Calls with long rows by
+// threads and so: a star of 70 000 vertices 27 and 0.5 ms (one scan less, too: see k_csr_scan), 300 000 vertices with 300
+// hubs 4.6 and 0.7; with 80 entries on average 20 000 vertices 1.46 and 0.56, 500 000 6.2 and 2.4.  (One row at a time by the whole wavefront:
+// 20 000 vertices with 80 entries 0.87; the line at 32, 48 and 64, 200 000 vertices with 24 and 48 entries: 956, 888, 889 and
+// 1420, 1486, 1757 us.)
+constexpr unsigned int LONG_ROW = 48, HUGE_ROW = 1024;
 
 // Entries of v's row: from `at` on, four side by side (their loads wait for memory together), then `step` further.  Returns the first in
 // the order (weight, smaller end, larger end) that leads out of component c, as its weight's bits and the other end; among the edges of
@@ -84,10 +89,29 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
         at = o0 < 0 ? 0u : (unsigned int)o0;
         end = o1 < 0 ? 0u : o1 > f.E ? (unsigned int)f.E : (unsigned int)o1;
     }
-    const bool is_long = at < end && end - at > LONG_ROW;
-    unsigned long long best = is_long ? NO_EDGE : row_part<FIRST>(f, v, c, at, end, 4);
-    const int lane = threadIdx.x & 63;
-    for (unsigned long long todo = __ballot(is_long); todo != 0; todo &= todo - 1) {
+    const unsigned int length = at < end ? end - at : 0u;
+    unsigned long long best = length > LONG_ROW ? NO_EDGE : row_part<FIRST>(f, v, c, at, end, 4);
+    const int lane = threadIdx.x & 63, group = lane >> 4;
+    // four rows at once: group g takes the g-th of those that are left
+    unsigned long long todo = __ballot(length > LONG_ROW && length <= HUGE_ROW);
+    while (todo != 0) {
+        unsigned long long m = todo;
+        for (int i = 0; i < group; ++i) m &= m - 1;
+        const int owner = m != 0 ? __builtin_ctzll(m) : 0;
+        const unsigned int o_at = (unsigned int)__shfl((int)at, owner), o_end = (unsigned int)__shfl((int)end, owner);
+        const int o_v = __shfl(v, owner), o_c = __shfl(c, owner);
+        unsigned long long key = m != 0 ? row_part<FIRST>(f, o_v, o_c, o_at + 4 * (lane & 15), o_end, 64) : NO_EDGE;
+#pragma unroll
+        for (int o = 8; o > 0; o >>= 1) {
+            const unsigned long long other = __shfl_xor(key, o);
+            key = other < key ? other : key;
+        }
+        const int mine = __builtin_amdgcn_mbcnt_hi((unsigned int)(todo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)todo, 0u));       // (this lane's, if it has one)
+        const unsigned long long result = __shfl(key, (mine & 3) * 16);
+        if ((todo >> lane & 1) != 0 && mine < 4) best = result;
+        for (int i = 0; i < 4; ++i) todo &= todo - 1;              // (0 & ~0 is 0)
+    }
+    for (todo = __ballot(length > HUGE_ROW); todo != 0; todo &= todo - 1) {
         const int owner = __builtin_ctzll(todo);
         unsigned long long key = row_part<FIRST>(f, __shfl(v, owner), __shfl(c, owner), (unsigned int)__shfl((int)at, owner) + 4 * lane, (unsigned int)__shfl((int)end, owner), 256);
 #pragma unroll
@@ -102,9 +126,10 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
 }
 
 // Round 0: every vertex is a component.
-__global__ void __launch_bounds__(WIDE) k_csr_first(CsrForest f)
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) k_csr_first(CsrForest f)
 {
-    for (long long base = (long long)blockIdx.x * WIDE; base < f.V; base += (long long)gridDim.x * WIDE) {
+    for (long long base = (long long)blockIdx.x * THREADS; base < f.V; base += (long long)gridDim.x * THREADS) {
         const long long v = base + threadIdx.x;
         uint32_t w;
         const int u = row_edge<true>(f, v < f.V ? (int)v : -1, (int)v, &w);
@@ -119,7 +144,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_first(CsrForest f)
             f.best_e[0][v] = u < 0 ? ~0ull : ((unsigned long long)lo << 32) | hi;
             f.best_e[1][v] = ~0ull;
         }
-        const int at = block_append<WIDE>(u >= 0, f.words + CSR_ACTIVE + 1);
+        const int at = block_append<THREADS>(u >= 0, f.words + CSR_ACTIVE + 1);
         if (u >= 0) f.active[1][at] = (int)v;
         __syncthreads();
     }
@@ -127,7 +152,8 @@ __global__ void __launch_bounds__(WIDE) k_csr_first(CsrForest f)
 
 // Round r: the active vertices' edges, and the weight of every component's lightest.  Also tells the host how the round before
 // ended, in words that carry `seq` each (so no fence has to stand between them and one number for all).
-__global__ void __launch_bounds__(WIDE) k_csr_scan(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
+template <int THREADS>
+__global__ void __launch_bounds__(THREADS) k_csr_scan(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
 {
     if (blockIdx.x == 0 && threadIdx.x < CSR_TOLD) {
         const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR};
@@ -138,7 +164,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_scan(CsrForest f, int round, unsig
     const int32_t* from = f.active[round & 1];
     int32_t* to = f.active[(round + 1) & 1];
     uint32_t* best_w = f.best_w[round & 1];
-    for (long long base = (long long)blockIdx.x * WIDE; base < n; base += (long long)gridDim.x * WIDE) {
+    for (long long base = (long long)blockIdx.x * THREADS; base < n; base += (long long)gridDim.x * THREADS) {
         const long long i = base + threadIdx.x;
         int v = -1, c = 0;
         uint32_t w;
@@ -153,7 +179,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_scan(CsrForest f, int round, unsig
             f.cand_w[v] = __uint_as_float(w);
         } else if (v >= 0) f.colour[v] = ~c;
         wave_min_into(best_w, c, w, u >= 0);
-        const int at = block_append<WIDE>(u >= 0, f.words + CSR_ACTIVE + (round + 1) % 3);
+        const int at = block_append<THREADS>(u >= 0, f.words + CSR_ACTIVE + (round + 1) % 3);
         if (u >= 0) to[at] = v;
         __syncthreads();
     }
@@ -264,7 +290,8 @@ __global__ void __launch_bounds__(TB) k_csr_follow(CsrForest f, int round, int a
 
 // All rounds from `round` on in one workgroup, once few vertices are active: a round's four launches take 30 us whatever they do.
 // A call with 1600 vertices: 202 us with rounds over all vertices, 199 over lists, 150 so; 4096 to 4900 vertices: 223 so and 201 by
-// launches; 14 400: 480 and 250.  So up to 2048.
+// launches; 14 400: 480 and 250.  So up to 2048; and fewer where they have more than 12 entries each, which one CU reads: 1500 vertices with 40
+// entries 402 so and 280 by launches, 300 with 80 260 and 297.
 __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
 {
     __shared__ int s_active, s_roots, s_edges, s_chain;
@@ -389,8 +416,8 @@ __device__ inline bool closed_part(const CsrForest& f, const int32_t* __restrict
 __global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* __restrict__ colours)
 {
     const int v = blockIdx.x * TB + threadIdx.x, lane = threadIdx.x & 63;
-    // (a failed check or unfollowed hooks: no colours, and perhaps no rows that may be read; one tree: nothing to leave it for)
-    if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;
+    // (a failed check or unfollowed hooks: no colours, and perhaps no rows that may be read)
+    if (halted(f)) return;
     const bool mine = v < f.V;
     const int c = mine ? colours[v] : 0;
     const unsigned int at = mine ? (unsigned int)f.offsets[v] : 0u, end = mine ? (unsigned int)f.offsets[v + 1] : 0u;
@@ -411,7 +438,8 @@ __global__ void __launch_bounds__(64) k_csr_words(int32_t* __restrict__ words)
 hipError_t csr_start(const CsrForest& f, hipStream_t s)
 {
     hipLaunchKernelGGL(k_csr_words, dim3(1), dim3(64), 0, s, f.words);
-    hipLaunchKernelGGL(k_csr_first, dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f);
+    if (f.V > FEW) hipLaunchKernelGGL((k_csr_first<WIDE>), dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f);
+    else hipLaunchKernelGGL((k_csr_first<TB>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
     hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f, 0);
     hipLaunchKernelGGL(k_csr_follow, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, 0, 0);
     return hipGetLastError();
@@ -420,7 +448,8 @@ hipError_t csr_start(const CsrForest& f, hipStream_t s)
 hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s)
 {
     const dim3 per_vertex(blocks_for(vertices < 1 ? 1 : vertices));
-    hipLaunchKernelGGL(k_csr_scan, dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
+    if (vertices > FEW) hipLaunchKernelGGL((k_csr_scan<WIDE>), dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
+    else hipLaunchKernelGGL((k_csr_scan<TB>), per_vertex, dim3(TB), 0, s, f, round, host, seq);
     hipLaunchKernelGGL(k_csr_select, per_vertex, dim3(TB), 0, s, f, round);
     hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(roots)), dim3(WIDE), 0, s, f, round);
     hipLaunchKernelGGL(k_csr_follow, per_vertex, dim3(TB), 0, s, f, round, 0);
@@ -442,7 +471,12 @@ hipError_t csr_tail(const CsrForest& f, int round, unsigned long long* host, uin
 hipError_t csr_colours(const CsrForest& f, int32_t* out, hipStream_t s)
 {
     hipLaunchKernelGGL(k_csr_colours, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, out);
-    hipLaunchKernelGGL(k_csr_closed, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, out);
+    return hipGetLastError();
+}
+
+hipError_t csr_closed(const CsrForest& f, const int32_t* colours, hipStream_t s)
+{
+    hipLaunchKernelGGL(k_csr_closed, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, colours);
     return hipGetLastError();
 }
 

@@ -1933,10 +1933,11 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             return SLHC_OK;
         };
         HIP_TRY(slhc::csr_start(f, s));
+        const int64_t tail_most = slhc::csr_tail_most(V, E);
         int rc2 = SLHC_OK, next = 1;                       // the round to enqueue next
-        if (V > slhc::CSR_TAIL) { rc2 = enqueue_round(next++); if (rc2 != SLHC_OK) return rc2; }
+        if (V > tail_most) { rc2 = enqueue_round(next++); if (rc2 != SLHC_OK) return rc2; }
         // what round `round - 1` left comes back with round `round`, behind which the next one is enqueued already
-        for (int round = 1; vertices > slhc::CSR_TAIL; ++round) {
+        for (int round = 1; vertices > tail_most; ++round) {
             rc2 = enqueue_round(next++);
             if (rc2 == SLHC_OK) rc2 = read(round & 1);
             if (rc2 != SLHC_OK) return rc2;
@@ -1977,6 +1978,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         }
         if (V == 1) nrounds = 0;
         if (!tail) HIP_TRY(slhc::csr_colours(f, colours, s));
+        if (edges < V - 1) HIP_TRY(slhc::csr_closed(f, colours, s));
         // (the arrays of the rounds are free by now)
         slhc::CsrSortScratch t{};
         t.count = reinterpret_cast<int32_t*>(ws.best_e); t.offset = reinterpret_cast<int32_t*>(ws.keys_a);

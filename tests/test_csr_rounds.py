@@ -65,8 +65,10 @@ def test_edges_per_smaller_end(lib, V, edges, values):
     check(lib, V, *csr(V, a, b, rng.integers(0, values, len(a)), rng))
 
 
-# rows in no order, several edges between two vertices, self loops, vertices without edges, many trees; weights of few values and of many, 0 included
-@pytest.mark.parametrize("V,degree,values", [(1, 0, 1), (500, 0.4, 3), (3000, 1.0, 1), (5000, 3.0, 2), (20_000, 1.3, 1000), (100_000, 2.5, 10), (66_000, 8.0, 1_000_000)])
+# rows in no order, several edges between two vertices, self loops, vertices without edges, many trees; weights of few values and of many, 0 included;
+# wavefronts with rows of 49 entries and more, from a few to all
+@pytest.mark.parametrize("V,degree,values", [(1, 0, 1), (500, 0.4, 3), (3000, 1.0, 1), (5000, 3.0, 2), (20_000, 1.3, 1000), (100_000, 2.5, 10), (66_000, 8.0, 1_000_000),
+                                             (60, 50.0, 1000), (300, 80.0, 3), (1500, 45.0, 1_000_000), (6000, 80.0, 1000), (70_000, 49.0, 10)])
 def test_random_graphs(lib, V, degree, values):
     print(f"csr random V={V} degree={degree} values={values}", flush=True)
     rng = np.random.default_rng(V)
@@ -94,7 +96,7 @@ def test_random_graphs(lib, V, degree, values):
 def test_hubs(lib, V, spread, values):
     print(f"csr hubs V={V} spread={spread} values={values}", flush=True)
     rng = np.random.default_rng(V + spread)
-    lengths = [0, 1, 3, 5, 31, 32, 33, 47, 48, 49, 51, 52, 53, 64, 128, 255, 256, 257, 260, 511, 1000, 1400]
+    lengths = [0, 1, 3, 5, 31, 32, 33, 47, 48, 49, 51, 52, 53, 64, 128, 255, 256, 257, 260, 511, 1000, 1023, 1024, 1025, 1400]
     hubs = np.r_[np.arange(len(lengths)), V - 1 - np.arange(len(lengths))]
     hubs = np.where(hubs < V // 2, hubs * spread, V - 1 - (V - 1 - hubs) * spread)
     a = np.concatenate([np.full(n, h) for h, n in zip(hubs, lengths * 2)])
@@ -152,6 +154,26 @@ def test_negative_zero(lib, V):
     weights[np.flatnonzero(weights == 0)[::2]] = -0.0
     assert np.signbit(weights).any()
     check(lib, V, offsets, indices, weights)
+
+
+# Rows of 80 entries cost the time of rows of 3 and a half more, twice or so in all (five times where few CUs read them, one thread a row)
+def test_time_of_dense_graphs(lib):
+    V, ms = 20_000, []
+    rng = np.random.default_rng(3)
+    for degree in (3, 80):
+        a, b = rng.integers(0, V, V * degree // 2), rng.integers(0, V, V * degree // 2)
+        keep = a != b
+        graph = [torch.from_numpy(x).cuda() for x in csr(V, a[keep], b[keep], rng.random(keep.sum()).astype(np.float32))]
+        least = float("inf")
+        for _ in range(12):
+            begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            begin.record()
+            lib.csr_msf(*graph)
+            end.record()
+            end.synchronize()
+            least = min(least, begin.elapsed_time(end))
+        ms.append(least)
+    assert ms[1] < 3 * ms[0], ms
 
 
 # hook chains of a round from one to all vertices long: weights rising along paths of `run` vertices, which meet at their ends
