@@ -154,23 +154,24 @@ __device__ inline void near_lds_ready()
     asm volatile("" ::: "memory");
 }
 
-// Where the rows of a matrix lie in a copy that is not in their order: row b * tiles + i, i < tiles, in tile i + near_shift(b) and there at
-// place b - near_turn(tile), round and round.  So a tile has one row of every stretch of `tiles` rows and is an even sample of them,
-// whatever order they are in.  The shift: where row i is of cluster i % n, and n and `tiles` have a divisor in common, tile i would have the rows
-// of a few clusters only.  The turn: where rows lie in the order of their clusters, the same place of all tiles would have the
-// rows of one, and the groups that a sample's maxima are taken of are places.
-__device__ inline int near_turn(int tile) { return (int)(((unsigned int)tile * 0x9e3779b1u) >> 25); }
+// Where the rows of a matrix lie in a copy that is not in their order: row b * tiles + i, i < tiles, in tile i + near_shift(b) and there, in
+// the same 32 as place b, at place b - near_turn(tile), both round and round.  So a tile has one row of every stretch of `tiles` rows and is
+// an even sample of them, whatever order they are in.  The shift: where row i is of cluster i % n, and n and `tiles` have a divisor in
+// common, tile i would have the rows of a few clusters only.  The turn: where rows lie in the order of their clusters, the same place of all
+// tiles would have the rows of one, and the groups that a sample's maxima are taken of are places of 32.  (Turned by up to 128, short rows
+// that share a cache line are read by workgroups of several XCDs: near_make of 400 000 x 8 40.4 us, 37.8 so.)
+__device__ inline int near_turn(int tile) { return (int)(((unsigned int)tile * 0x9e3779b1u) >> 27); }
 __device__ inline int near_shift(int b, int tiles) { return (int)__umulhi((unsigned int)b * 0x9e3779b1u, (unsigned int)tiles); }
 __device__ inline long long near_row(int pos, int tiles, int in_order)
 {
     if (in_order) return pos;
-    const int t = pos >> 7, b = (pos + near_turn(t)) & (TILE - 1), i = t - near_shift(b, tiles);
+    const int t = pos >> 7, b = (pos & 96) | ((pos + near_turn(t)) & 31), i = t - near_shift(b, tiles);
     return (long long)b * tiles + (i < 0 ? i + tiles : i);
 }
 __device__ inline int near_pos(int row, int tiles)             // (not in order)
 {
     const int b = row / tiles, i = row - b * tiles + near_shift(b, tiles), t = i < tiles ? i : i - tiles;
-    return t * TILE + ((b - near_turn(t)) & (TILE - 1));
+    return t * TILE + ((b & 96) | ((b - near_turn(t)) & 31));
 }
 
 // i * near_spread(n) % n for i = 0, 1, ...: the numbers below n in an order whose every stretch is spread evenly over them (n times the
