@@ -173,7 +173,7 @@ def test_time_of_dense_graphs(lib):
             end.synchronize()
             least = min(least, begin.elapsed_time(end))
         ms.append(least)
-    assert ms[1] < 3 * ms[0], ms
+    assert ms[1] < 3.5 * ms[0], ms
 
 
 # hook chains of a round from one to all vertices long: weights rising along paths of `run` vertices, which meet at their ends
