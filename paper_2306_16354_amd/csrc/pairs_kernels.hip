@@ -21,14 +21,14 @@
 
 namespace slhc {
 
-constexpr int QUEUE = 320;                 // pairs of a wavefront that wait for their slots in the rows' lists
+constexpr int QUEUE = 192;                 // pairs of a wavefront that wait for their slots in the rows' lists
 constexpr int PAIR_TILE_BITS = 17;         // of a tile's number in a queued pair
 
 // Pairs that pass wait in LDS until a wavefront's worth is there; then the limits of both rows are read at one tile, the pairs'
 // slots in the rows' lists are asked for at the next and used at the one after that, so nobody waits for memory.
 struct PairQueue {
     uint2* at;                             // LDS, QUEUE entries
-    int n;                                 // waiting (the same for all lanes)
+    int n, records;                        // waiting, and records behind the queue (the same for all lanes)
     bool read, asked;                      // 64 pairs at the first and at the second step (the same for all lanes)
     unsigned int u, code, u2, code2;       // of this lane's at the two steps
     float q_limit, c_limit;
@@ -95,27 +95,45 @@ __device__ inline void pair_push(uint2* at, unsigned int u, unsigned int code)
     asm volatile("ds_write_b64 %0, %1" ::"v"((unsigned int)(uintptr_t)(__attribute__((address_space(3))) void*)at), "v"(e) : "memory");
 }
 
-// v[r], r < 16 by lane (in bits: from conditions the compiler makes an array in memory)
-__device__ inline float pair_value(const v16f& v, unsigned int r)
+// A lane's 16 values of a block of which some pass, until the tile they belong to is done with.
+constexpr int RECORDS = 16;
+constexpr int WAVE_LDS = QUEUE * 8 + RECORDS * 80;             // of a wavefront: pairs that wait, records' values and words
+__device__ inline unsigned int lds_word(const void* at)
 {
-    unsigned int a[16];
-#pragma unroll
-    for (int i = 0; i < 16; ++i) a[i] = __float_as_uint(v[i]);
-#pragma unroll
-    for (int w = 8; w > 0; w >>= 1) {
-        const unsigned int take = 0u - (unsigned int)((r & (unsigned int)w) != 0u);
-#pragma unroll
-        for (int i = 0; i < w; ++i) a[i] = (a[w + i] & take) | (a[i] & ~take);
+    return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const void*)at;
+}
+// The records' values, four records at a time, against the limits of both rows; tile_limit: LDS, of the tile's candidates.  (Reads past the compiler
+// as well, see pair_push.)
+__device__ inline void pair_sift(PairQueue& w, const NearPairs& p, int q0, const unsigned char* tile_limit)
+{
+    const int lane = threadIdx.x & 63;
+    const unsigned int values = lds_word(w.at + QUEUE) + lane * 4, words = lds_word(w.at + QUEUE) + RECORDS * 64 + (lane >> 4) * 16;
+#pragma unroll 1
+    for (int at = 0; at < w.records; at += 4) {
+        float x, limit;
+        v4f word;
+        asm volatile("ds_read_b32 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x), "=&v"(word) : "v"(values + at * 64), "v"(words + at * 16) : "memory");
+        const unsigned int code = __float_as_uint(word[0]) + ((((lane & 12u) << 1) | (lane & 3u)) << 8);
+        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(limit) : "v"(lds_word(tile_limit) + ((code >> 6) & 508u)) : "memory");
+        const bool pass = at + (lane >> 4) < w.records && (x >= word[1] || x - limit >= word[2]);
+        const unsigned long long m = __ballot(pass);
+        if (w.n > QUEUE - 64) pair_finish(w, p, q0);
+        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+        if (pass) pair_push(w.at + w.n + pre, __float_as_uint(x - word[3]), code);
+        w.n += __popcll(m);
     }
-    return __uint_as_float(a[0]);
+    w.records = 0;
 }
 
 // One 32 x 32 block of values.  limit: of this lane's 16 candidates; bound: the query's limit plus its half norm h; other: h, or
 // NaN where the block's pairs are met in both orders anyway.  code: of the lane's first candidate.
-// Where rows are few, every block holds something (20 000 x 128, k = 32: two or three pairs, 71 us for products and test and 80 for what
-// follows), so what follows the test has no branch per value (with one per value 90).
+// Bound by the test, 36 instructions for 16 values; of 1M x 128 in clusters by Zipf's law every second block holds something, so what
+// follows has to be short: the lane's values go to LDS as they are, and which of them pass is found for four lanes at once.  With
+// the wavefront looking for them there and then (a bit per value, the value picked out of 16 registers, a turn per pair of a lane) the
+// emission of 1M x 128, k = 32, took 171 ms; 146 so, 115 with nothing after the test, 94 with the products alone (1.37 PFLOP/s at 1.9 GHz).
 __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float bound, float h, float other, unsigned int code,
-                                 PairQueue& w, const NearPairs& p, int q0)
+                                 PairQueue& w, const NearPairs& p, int q0, const unsigned char* tile_limit)
 {
     float f = max3(v[0], v[1], v[2]), t = max3(v[0] - limit[0], v[1] - limit[1], v[2] - limit[2]);
 #pragma unroll
@@ -125,21 +143,23 @@ __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float 
     }
     f = fmaxf(f, v[15]);
     t = fmaxf(t, v[15] - limit[15]);
-    if (!__any(f >= bound || t >= other)) return;
-    unsigned int bits = 0u;                                    // value r: bit 31 - r
-#pragma unroll
-    for (int r = 0; r < 16; ++r) bits = bits + bits + (v[r] >= bound || v[r] - limit[r] >= other ? 1u : 0u);
-    bits <<= 16;
-    unsigned long long m = __ballot(bits != 0u);
+    bool some = f >= bound || t >= other;
+    unsigned long long m = __ballot(some);
     while (m) {
-        if (w.n > QUEUE - 64) pair_finish(w, p, q0);
-        const unsigned int r = (unsigned int)__clz((int)bits) & 15u;
-        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
-        const float x = pair_value(v, r);
-        if (bits != 0u) pair_push(w.at + w.n + pre, __float_as_uint(x - h), code + ((((r & 12u) << 1) | (r & 3u)) << 8));
-        w.n += __popcll(m);
-        bits &= ~(0x80000000u >> r);
-        m = __ballot(bits != 0u);
+        const int at = w.records + __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+        if (some && at < RECORDS) {
+            const unsigned int values = lds_word(w.at + QUEUE) + at * 64, words = lds_word(w.at + QUEUE) + RECORDS * 64 + at * 16;
+            const v4f word = {__uint_as_float(code), bound, other, h};
+            const v4f v0 = {v[0], v[1], v[2], v[3]}, v1 = {v[4], v[5], v[6], v[7]}, v2 = {v[8], v[9], v[10], v[11]}, v3 = {v[12], v[13], v[14], v[15]};
+            asm volatile("ds_write_b128 %0, %2\n\tds_write_b128 %0, %3 offset:16\n\tds_write_b128 %0, %4 offset:32\n\tds_write_b128 %0, %5 offset:48\n\tds_write_b128 %1, %6"
+                         ::"v"(values), "v"(words), "v"(v0), "v"(v1), "v"(v2), "v"(v3), "v"(word) : "memory");
+            some = false;
+        }
+        w.records += __popcll(m);
+        if (w.records < RECORDS) return;
+        w.records = w.records < RECORDS ? w.records : RECORDS;
+        pair_sift(w, p, q0, tile_limit);
+        m = __ballot(some);
     }
 }
 
@@ -195,8 +215,8 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
         for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const v8h*>(src + ks * FRAG_STEP);
     }
     PairQueue w;
-    w.at = reinterpret_cast<uint2*>(pairs_smem + 2 * BUF) + wave * QUEUE;
-    w.n = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
+    w.at = reinterpret_cast<uint2*>(pairs_smem + 2 * BUF + wave * WAVE_LDS);
+    w.n = w.records = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
 
     const int total = (range.j1 - range.j0) * bt;        // tiles to pass over (some may not be there)
     int step_j = range.j0, step_t = 0;                   // of the tile that is brought in next
@@ -272,9 +292,11 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
                 }
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb)
-                    pair_emit(acc[qb][cb], limit, bound[qb], h[qb], other[qb], pair_code(tile, half * 64 + cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0);
+                    pair_emit(acc[qb][cb], limit, bound[qb], h[qb], other[qb], pair_code(tile, half * 64 + cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0,
+                              tb + KS * FRAG_STEP + 512);
             }
         }
+        pair_sift(w, p, q0, tb + KS * FRAG_STEP + 512);
     }
     if (live) pair_finish(w, p, q0);
 }
@@ -318,8 +340,8 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
         else if (live) bound[qb] = p.limit[at] + h[qb];
     }
     PairQueue w;
-    w.at = reinterpret_cast<uint2*>(pairs_smem + WIDE_LDS) + wave * QUEUE;
-    w.n = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
+    w.at = reinterpret_cast<uint2*>(pairs_smem + WIDE_LDS + wave * WAVE_LDS);
+    w.n = w.records = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
 
     const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
     const int nmine = range.j1 - range.j0;
@@ -427,7 +449,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
                 for (int qb = 0; qb < 2; ++qb) {
                     if (!BEST) {
                         pair_emit(acc[qb][cb], limit, bound[qb], h[qb], own ? NEVER : h[qb],
-                                  pair_code(tile, cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0);
+                                  pair_code(tile, cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0, rows + 1024 + cg * 512);
                         continue;
                     }
                     v16f& v = acc[qb][cb];
@@ -452,6 +474,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
                     }
                 }
             }
+            if (!BEST) pair_sift(w, p, q0, rows + 1024 + cg * 512);
         }
         block = next;
     }
@@ -616,7 +639,7 @@ hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
     const int bt = wide ? 2 : waves / 2;
     if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > p.blocks / 2 + 1) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.blocks * p.nseg)), block((unsigned)(64 * (wide ? 8 : waves)));
-    const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024)) + (size_t)(wide ? 8 : waves) * QUEUE * 8;
+    const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024)) + (size_t)(wide ? 8 : waves) * WAVE_LDS;
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;

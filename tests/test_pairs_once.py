@@ -68,6 +68,19 @@ def test_lists_of_unlike_rows(lib, kind, N, d, k):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
+# As many lanes of one block with something to keep as a wavefront keeps records of, one less, one more, and all of them
+@pytest.mark.parametrize("many", [4, 15, 16, 17, 31, 64])
+@pytest.mark.parametrize("N,d,k", [(4100, 40, 20), (4500, 160, 20), (50_000, 100, 20)])
+def test_lanes_of_a_block(lib, many, N, d, k):
+    print(f"pairs once, blocks of {many} lanes, N={N} d={d}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == 0.5
+    X = blobs(N, d, many)
+    X = X[torch.arange(N, device="cuda") % (N // many)].contiguous()
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
 # Rows whose lists overflow are searched for on their own from 128 tiles on, in lists of 1024.  A row has to be met by all copies of its point
 # and by all rows beyond float16, whatever its limit.  As many of them as a list holds and more, with the memory for lists of 1024
 # (all of the workspace) and of 256 to 384 (40 % of it): none, some or all of the rows left over, in one to several batches; as
