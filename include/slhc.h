@@ -105,7 +105,8 @@ typedef struct slhc_stats {
                                         float32 (see SLHC_FP32_FILTER)                                */
     int32_t half_products;           /* 1 when the half-precision engine ran the k-NN search: one product of
                                         float16 copies per pair, or for both orders of a pair
-                                        (slhc_probe_knn_products); 0: the list kernels' split bfloat16 halves
+                                        (slhc_probe_knn_products), or took its place where rows are so few
+                                        that every pair is evaluated; 0: the list kernels' split bfloat16 halves
                                         (three products per pair) or float32                          */
 } slhc_stats;
 
@@ -240,7 +241,8 @@ int slhc_probe_f16_mfma_values(const float* A, const float* B, const float* C, f
 /*
  * Multiply-adds that an every-tile k-NN search of N rows executes by default, with a workspace of the reported size, per ordered pair of
  * rows and column (HOST out; no device work): 0.5 where the half-precision engine multiplies every pair once for both of its rows, 1
- * where it does so for each, 3 for the list kernels' split bfloat16 halves.  The sample that bounds come from is not counted.
+ * where it does so for each, 3 for the list kernels' split bfloat16 halves, 0 for a search so small that every pair is evaluated and
+ * nothing is multiplied.  The sample that bounds come from is not counted.
  */
 int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products);
 

@@ -1,14 +1,19 @@
-// Small 1-NN searches: every pair is evaluated exactly, by the vector units.
+// Small searches: every pair is evaluated exactly, by the vector units.
 //
-// The half-precision engine (near_kernels.hip) takes nine launches of 4 us and more each, which for a million pairs is more than all
-// of them cost: a pair is 2 d operations, a wavefront evaluates 64 at a time, one candidate per lane.  The candidates of a
-// workgroup pass through LDS, 16 bytes of every row side by side (no bank is met twice); the queries' values are the same for
-// all lanes.  Every distance is the float32 sum of the list kernels in their order of additions (group8_sqdist): slabs of 64
-// features, sixteen chains of four features each, the chains of either half added in a tree.  Bound by its three launches
-// and one round trip to memory per 64 candidates.  439 x 2414 x 16: 42 -> 17 us.  (The same for k-NN graphs, all distances of
-// eight rows in LDS, lost: 2048 x 32, k = 8, 65 us against the engine's 47.)
+// The half-precision engine (near_kernels.hip) takes eight or nine launches of 4 us and more each, which for some million pairs is more than
+// all of them cost: a pair is 2 d operations, a wavefront evaluates 64 at a time, one candidate per lane; the queries' values are the
+// same for all lanes.  Every distance is the float32 sum of the list kernels in their order of additions (group8_sqdist): slabs of 64
+// features, sixteen chains of four features each, the chains of either half added in a tree.
+//
+// 1-NN searches of few queries (direct_1nn): the candidates of a workgroup pass through LDS, 16 bytes of every row side by side (no bank is
+// met twice).  Bound by its three launches and one round trip to memory per 64 candidates.  439 x 2414 x 16: 42 -> 17 us.
+//
+// Searches of the rows among themselves (direct_knn): with the candidates in LDS as well a wavefront's reads took longer than its
+// sums (2048 x 32, k = 8, 65 us against the engine's 47); with four of them in a lane's registers it is bound by the sums, 8 us of 20, and by the
+// way of the rows into the registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+#include <type_traits>
 #include "direct_kernels.h"
 #include "wave_ops.h"
 
@@ -201,6 +206,423 @@ __global__ void __launch_bounds__(256) direct_unpack_kernel(const unsigned long 
     out_dist[i] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
 }
 
+// ---------------------------------------------------------------------------------------------- blocks of pairs in registers
+// Searches of the rows among themselves: a lane holds C candidates in registers, and a wavefront passes over the workgroup's queries, whose values
+// come from LDS, the same for all lanes.  NQ: four features each, up to 128; what is beyond d is 0 and adds nothing.  The sum is that of
+// direct_sum: chain j adds features 4 j .. 4 j + 3 and the same 64 on.
+constexpr int BLOCK = 512;                 // threads, and candidates that are brought in at a time
+constexpr int SLAB_QUADS = 8;              // quads of a row in LDS at a time
+__host__ __device__ constexpr int block_pitch(int NQ) { return (NQ < SLAB_QUADS ? NQ : SLAB_QUADS) | 1; }      // in quads; odd: no bank is met twice
+__host__ __device__ constexpr int block_most(int NQ) { return NQ <= 8 ? 4 : NQ <= 16 ? 2 : 1; }                // candidates of a lane
+
+// adds sixteen chains, those from n on being 0
+template <int N>
+__device__ inline float block_tree(const float (&p)[N])
+{
+    float s[2];
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+        float t[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) t[i] = 8 * half + i < N ? p[8 * half + i < N ? 8 * half + i : 0] : 0.f;
+        // (0 is added to sums of squares only, which it leaves as they are)
+        auto add = [&](int a, int b, bool there) { return there ? t[a] + t[b] : t[a]; };
+        const float u0 = add(0, 1, 8 * half + 1 < N), u1 = add(2, 3, 8 * half + 3 < N), u2 = add(4, 5, 8 * half + 5 < N), u3 = add(6, 7, 8 * half + 7 < N);
+        const float v0 = 8 * half + 2 < N ? u0 + u1 : u0, v1 = 8 * half + 6 < N ? u2 + u3 : u2;
+        s[half] = 8 * half + 4 < N ? v0 + v1 : v0;
+    }
+    return N > 8 ? s[0] + s[1] : s[0];
+}
+
+// The candidates on their way into registers: 512 rows, a slab of their features, a step; AHEAD steps are under way, so that the loads pass while the
+// rows before are evaluated.  All threads go through it together.
+struct BlockRows { const float* Xc; int nc, d, queries; };
+template <int NQ>
+struct BlockStream {
+    static constexpr int SLABS = (NQ + SLAB_QUADS - 1) / SLAB_QUADS, PITCH = block_pitch(NQ), WIDTH = NQ < SLAB_QUADS ? NQ : SLAB_QUADS;
+    static constexpr int AHEAD = NQ <= 4 ? 4 : NQ == 16 ? 1 : 2;         // (what registers are left)
+    BlockRows x;
+    v4f* tile;
+    v4f next[AHEAD][WIDTH];
+    int step;                                                           // of next[0]
+    template <int SLAB>
+    __device__ inline __attribute__((always_inline)) void fetch(v4f (&to)[WIDTH], int row0)
+    {
+        constexpr int J0 = SLAB * SLAB_QUADS, W = NQ - J0 < WIDTH ? NQ - J0 : WIDTH;
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            // consecutive lanes read consecutive pieces of a row
+            const int at = threadIdx.x + i * BLOCK, r = at / W, j = at - r * W;
+            to[i] = quad(row0 + r < x.nc ? row0 + r : x.nc - 1, 4 * (J0 + j));
+        }
+    }
+    // Without branches that lanes part at: the row's last four features stand in for what ends beyond them, which `bring` puts right.
+    __device__ inline v4f quad(int row, int t) const
+    {
+        if (x.d < 4) return direct_quad(x.Xc, row, t, x.d, false);
+        return *reinterpret_cast<const v4f_word*>(x.Xc + (size_t)row * x.d + (t + 4 <= x.d ? t : x.d - 4));
+    }
+    __device__ inline void start(const BlockRows& x_, v4f* tile_)
+    {
+        x = x_; tile = tile_; step = 0;
+        fetch<0>(next[0], 0);
+        if constexpr (AHEAD > 1) fetch<1 % SLABS>(next[1], 1 / SLABS * BLOCK);
+        if constexpr (AHEAD > 2) { fetch<2 % SLABS>(next[2], 2 / SLABS * BLOCK); fetch<3 % SLABS>(next[3], 3 / SLABS * BLOCK); }
+    }
+    // the lane's row of the next 512, features of slab SLAB
+    template <int SLAB>
+    __device__ inline __attribute__((always_inline)) void bring(v4f (&b)[NQ])
+    {
+        constexpr int J0 = SLAB * SLAB_QUADS, W = NQ - J0 < WIDTH ? NQ - J0 : WIDTH;
+        __syncthreads();                            // the rows of the step before are used up
+#pragma unroll
+        for (int i = 0; i < W; ++i) {
+            const int at = threadIdx.x + i * BLOCK, r = at / W, j = at - r * W;
+            tile[r * PITCH + j] = next[0][i];
+        }
+#pragma unroll
+        for (int a = 0; a + 1 < AHEAD; ++a)
+#pragma unroll
+            for (int i = 0; i < WIDTH; ++i) next[a][i] = next[a + 1][i];
+        fetch<(SLAB + AHEAD) % SLABS>(next[AHEAD - 1], (step + AHEAD) / SLABS * BLOCK);
+        ++step;
+        __syncthreads();
+#pragma unroll
+        for (int j = 0; j < W; ++j) b[J0 + j] = tile[threadIdx.x * PITCH + j];
+        if (x.d < 4 * NQ && x.d >= 4) {
+#pragma unroll
+            for (int j = 0; j < W; ++j) {
+                const int over = 4 * (J0 + j) + 4 - x.d;                     // (the same for all lanes)
+                v4f& v = b[J0 + j];
+                if (over >= 4) v = v4f{0.f, 0.f, 0.f, 0.f};
+                else if (over == 3) v = v4f{v[3], 0.f, 0.f, 0.f};
+                else if (over == 2) v = v4f{v[2], v[3], 0.f, 0.f};
+                else if (over == 1) v = v4f{v[1], v[2], v[3], 0.f};
+            }
+        }
+    }
+};
+// The queries qs [queries][NQ] against the next 512 C candidates: visit(q, distances), not looked at for rows that are not finite; ready(c):
+// before that, for the lane's c-th candidate.
+template <int C, int NQ, typename R, typename V>
+__device__ inline __attribute__((always_inline)) void block_pass(BlockStream<NQ>& s, const v4f* qs, R&& ready, V&& visit)
+{
+    v4f b[C][NQ];
+#pragma unroll
+    for (int c = 0; c < C; ++c) {
+        s.template bring<0>(b[c]);
+        if constexpr (NQ > SLAB_QUADS) s.template bring<1>(b[c]);
+        if constexpr (NQ > 2 * SLAB_QUADS) s.template bring<2>(b[c]);
+        if constexpr (NQ > 3 * SLAB_QUADS) s.template bring<3>(b[c]);
+    }
+#pragma unroll
+    for (int c = 0; c < C; ++c) ready(c);
+    constexpr int CHAINS = NQ < 16 ? NQ : 16;
+#pragma unroll 1
+    for (int q = 0; q < s.x.queries; ++q) {
+        float p[C][CHAINS];
+#pragma unroll
+        for (int j = 0; j < NQ; ++j) {
+            const v4f a = qs[q * NQ + j];
+#pragma unroll
+            for (int c = 0; c < C; ++c) {
+                float t = j < 16 ? 0.f : p[c][j & 15];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) { const float z = a[e] - b[c][j][e]; t = j < 16 && e == 0 ? z * z : __builtin_fmaf(z, z, t); }
+                p[c][j & 15] = t;
+            }
+        }
+        float v[C];
+#pragma unroll
+        for (int c = 0; c < C; ++c) v[c] = block_tree<CHAINS>(p[c]);
+        visit(q, v);
+    }
+}
+// Whether some of the distances of a query are so large that the candidate may not be finite (NaN: yes).
+template <int C>
+__device__ inline bool block_suspect(const float (&v)[C])
+{
+    bool some = false;
+#pragma unroll
+    for (int c = 0; c < C; ++c) some = some || !(v[c] < 2e38f);
+    return __any(some);
+}
+// all candidates, and no places beyond the last 512: pass(how many times 512, the first of them)
+template <int NQ, typename F>
+__device__ inline __attribute__((always_inline)) void block_passes(int nc, F&& pass)
+{
+    int base = 0;
+    if constexpr (block_most(NQ) >= 4)
+        for (; nc - base > 3 * BLOCK; base += 4 * BLOCK) pass(std::integral_constant<int, 4>{}, base);
+    if constexpr (block_most(NQ) >= 2)
+        for (; nc - base > BLOCK; base += 2 * BLOCK) pass(std::integral_constant<int, 2>{}, base);
+    for (; nc - base > 0; base += BLOCK) pass(std::integral_constant<int, 1>{}, base);
+}
+
+// The k nearest rows of every row.  All distances of a workgroup's QB rows are kept in LDS; then a wavefront per row takes what is not beyond the k-th
+// smallest of its lanes' minima, of which k at least are, and ranks that.
+// Time (k = 12, us; engine, this): 500 x 4 42, 9; 1000 x 16 42, 9; 2048 x 32 48, 20; 2048 x 32, k = 64, 74, 23; 1500 x 128 60, 38; 3198 x 16 55, 39.
+struct DirectKnn {
+    const float* X; int n, d, k, rows; bool vec4;         // rows: per workgroup, KNN_ROWS at most
+    int32_t* out_idx; float* out_dist; int32_t* evaluated; unsigned int* nonfinite;
+};
+constexpr int KNN_ROWS = 8, KNN_KEEP = 512;       // (a wavefront each); pairs that a row keeps to be ranked
+
+// LDS: the candidates' rows, later the pairs to be ranked; the queries' rows and norms; all distances
+__host__ __device__ inline size_t direct_knn_head(int NQ, int rows)
+{
+    const size_t tile = (size_t)BLOCK * block_pitch(NQ) * 16, keep = (size_t)rows * KNN_KEEP * 8;
+    return tile > keep ? tile : keep;
+}
+__host__ __device__ inline size_t direct_knn_bytes(int NQ, int rows, int n)
+{
+    return direct_knn_head(NQ, rows) + (size_t)rows * NQ * 16 + KNN_ROWS * 4 + (size_t)rows * ((n + BLOCK - 1) / BLOCK * BLOCK) * 4;
+}
+
+template <int NQ>
+__global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
+{
+    extern __shared__ __align__(16) unsigned char direct_smem[];
+    v4f* tile = reinterpret_cast<v4f*>(direct_smem);
+    v4f* qs = reinterpret_cast<v4f*>(direct_smem + direct_knn_head(NQ, p.rows));
+    float* norms = reinterpret_cast<float*>(qs + p.rows * NQ);
+    float* dist = norms + KNN_ROWS;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n64 = (p.n + 63) / 64, pitch = (p.n + BLOCK - 1) / BLOCK * BLOCK;
+    const int q0 = blockIdx.x * p.rows;
+    BlockStream<NQ> stream;
+    stream.start(BlockRows{p.X, p.n, p.d, p.rows}, tile);
+    for (int i = tid; i < p.rows * NQ; i += BLOCK) qs[i] = direct_quad(p.X, q0 + i / NQ < p.n ? q0 + i / NQ : -1, 4 * (i % NQ), p.d, p.vec4);
+    if (wave < p.rows) {
+        const float norm = direct_norm(p.X, q0 + wave < p.n ? q0 + wave : -1, p.d, lane);
+        if (lane == 0) norms[wave] = norm;
+    }
+    __syncthreads();
+    // (a row beside one that is not of moderate norm, or at such a distance, may be no finite one)
+    bool large = false;
+    for (int q = 0; q < p.rows; ++q) large = large || !(norms[q] < 1e36f);
+    auto pass = [&](auto per, int base) {
+        constexpr int C = decltype(per)::value;
+        block_pass<C>(stream, qs, [](int) {}, [&](int q, float (&v)[C]) {
+            if (large || block_suspect(v)) {
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    const int cand = base + c * BLOCK + tid;
+                    if (cand < p.n && v[c] < INF && direct_bad_row(p.X, cand, p.d)) v[c] = INF;
+                    v[c] = v[c] < INF ? v[c] : INF;                          // (NaN: +inf)
+                }
+            }
+#pragma unroll
+            for (int c = 0; c < C; ++c) dist[q * pitch + base + c * BLOCK + tid] = v[c];
+        });
+    };
+    block_passes<NQ>(p.n, pass);
+    __syncthreads();
+    const int row = q0 + wave;
+    if (wave >= p.rows || row >= p.n) return;
+    float* mine = dist + wave * pitch;
+    if (lane == 0) mine[row] = INF;                                           // itself, and no rows
+    if (p.n + lane < n64 * 64) mine[p.n + lane] = INF;
+    __builtin_amdgcn_wave_barrier();
+    unsigned long long* keep = reinterpret_cast<unsigned long long*>(direct_smem) + wave * KNN_KEEP;      // (the candidates' rows are used up)
+    const bool fine = norms[wave] < INF;
+    if (p.nonfinite && !fine && lane == 0) atomicOr(p.nonfinite, 1u);
+    // the row's distances, 16 of a lane's at a time: what(first of them, values), +inf from n64 on
+    auto all = [&](auto&& what) {
+        for (int i0 = 0; i0 < n64; i0 += 16) {
+            float v[16];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) v[i] = i0 + i < n64 ? mine[(i0 + i) * 64 + lane] : INF;
+            what(i0, v);
+        }
+    };
+    // a value that k of the row's do not exceed, and few others: the k-th smallest minimum of a lane's values or, from sixteen on, of every fourth of them
+    float limit;
+    if (p.k <= 16) {
+        float least = INF;
+        all([&](int, const float (&v)[16]) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) least = fminf(least, v[i]);
+        });
+        int rank = 0;
+#pragma unroll
+        for (int j = 0; j < 64; ++j) rank += __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(least), j)) < least ? 1 : 0;
+        limit = rank < p.k ? least : 0.f;                                     // (distances are not negative)
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) limit = fmaxf(limit, __shfl_xor(limit, o));
+    } else {
+        float least[4] = {INF, INF, INF, INF};
+        all([&](int, const float (&v)[16]) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) least[i & 3] = fminf(least[i & 3], v[i]);
+        });
+        float lo = INF, hi = 0.f;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) { lo = fminf(lo, least[j]); hi = least[j] < INF ? fmaxf(hi, least[j]) : hi; }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+        auto reach = [&](float upto) {
+            int n = 0;
+#pragma unroll
+            for (int j = 0; j < 4; ++j) n += __popcll(__ballot(least[j] <= upto));
+            return n;
+        };
+        limit = INF;
+        if (reach(hi) >= p.k) {
+            limit = hi;
+            for (int it = 0; it < 14; ++it) {
+                const float mid = 0.5f * lo + 0.5f * limit;
+                if (reach(mid) >= p.k) limit = mid; else lo = mid;
+            }
+        }
+    }
+    // what does not exceed it, in the order of the rows
+    auto prefix = [&](unsigned long long m) { return (int)__builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u)); };
+    int kept = 0;
+    auto take = [&](auto&& passes) {                                          // passes(value), called by all lanes together
+        kept = 0;
+        all([&](int i0, const float (&v)[16]) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) {
+                const bool in = passes(v[i]) && v[i] < INF;
+                const unsigned long long m = __ballot(in);
+                if (m == 0ull) continue;
+                const int at = kept + prefix(m);
+                if (in && at < KNN_KEEP) keep[at] = ((unsigned long long)__float_as_uint(v[i]) << 32) | (unsigned int)((i0 + i) * 64 + lane);
+                kept += __popcll(m);
+            }
+        });
+    };
+    auto count = [&](float upto) {
+        int n = 0;
+        all([&](int, const float (&v)[16]) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) n += __popcll(__ballot(v[i] <= upto));
+        });
+        return n;
+    };
+    if (!fine) kept = 0;
+    else {
+        take([&](float v) { return v <= limit; });
+        if (kept > 2 * p.k + 64) {
+            // copies by the hundred, or k near the number of lanes: the k-th smallest value itself, and of those equal to it the first
+            // (bits of floats that are not negative are in their order)
+            unsigned int lo = 0u, hi = __float_as_uint(limit < INF ? limit : 3.4028234663852886e38f);
+            while (lo < hi) {
+                const unsigned int mid = lo + (hi - lo) / 2;
+                if (count(__uint_as_float(mid)) >= p.k) hi = mid; else lo = mid + 1;
+            }
+            const float kth = __uint_as_float(hi);
+            int room = p.k - (hi > 0u ? count(__uint_as_float(hi - 1u)) : 0);
+            take([&](float v) {
+                const unsigned long long ties = __ballot(v == kth);
+                const bool in = v < kth || (v == kth && prefix(ties) < room);
+                room -= __popcll(ties);
+                return in;
+            });
+        }
+        __builtin_amdgcn_wave_barrier();
+    }
+    // ranks by (distance, row)
+    for (int i = 0; i < kept; i += 64) {
+        const unsigned long long key = i + lane < kept ? keep[i + lane] : ~0ull;
+        int at = 0;
+        for (int j = 0; j < kept; ++j) at += keep[j] < key ? 1 : 0;
+        if (i + lane < kept && at < p.k) {
+            p.out_idx[(size_t)row * p.k + at] = (int32_t)(unsigned int)key;
+            p.out_dist[(size_t)row * p.k + at] = __uint_as_float((unsigned int)(key >> 32));
+        }
+    }
+    for (int j = kept + lane; j < p.k; j += 64) { p.out_idx[(size_t)row * p.k + j] = -1; p.out_dist[(size_t)row * p.k + j] = INF; }
+    if (p.evaluated && lane == 0) p.evaluated[row] = fine ? p.n - 1 : 0;
+}
+
+// The nearest row (of another colour) of many queries: as direct_knn_kernel, with one (distance, row) per query in LDS instead of all distances.
+struct DirectNear {
+    const float* Xq; const float* Xc; const int32_t* q_rows; const int32_t* colour;
+    int m, nq_rows, nc, d, rows;
+    int32_t* out_idx; float* out_dist; unsigned long long* pairs;
+};
+constexpr int NEAR_ROWS = 32;              // queries of a workgroup at most
+
+template <int NQ>
+__global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
+{
+    extern __shared__ __align__(16) unsigned char direct_smem[];
+    __shared__ unsigned long long best[NEAR_ROWS];
+    __shared__ float norms[NEAR_ROWS];
+    __shared__ int row_of[NEAR_ROWS], colour_of[NEAR_ROWS];
+    v4f* tile = reinterpret_cast<v4f*>(direct_smem);
+    v4f* qs = tile + BLOCK * block_pitch(NQ);
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int q0 = blockIdx.x * p.rows;
+    BlockStream<NQ> stream;
+    stream.start(BlockRows{p.Xc, p.nc, p.d, p.rows}, tile);
+    if (tid < p.rows) {
+        const int i = q0 + tid;
+        int row = i < p.m ? (p.q_rows ? p.q_rows[i] : i) : -1;
+        if (row >= p.nq_rows) row = -1;
+        row_of[tid] = row;
+        colour_of[tid] = p.colour && row >= 0 ? p.colour[row] : -1;
+        best[tid] = ~0ull;
+    }
+    if (p.pairs && blockIdx.x == 0 && tid == 0) atomicAdd(p.pairs, (unsigned long long)p.m * (unsigned long long)p.nc);
+    __syncthreads();
+    const bool vec4 = p.d % 4 == 0 && (reinterpret_cast<uintptr_t>(p.Xq) & 15) == 0;
+    for (int i = tid; i < p.rows * NQ; i += BLOCK) qs[i] = direct_quad(p.Xq, row_of[i / NQ], 4 * (i % NQ), p.d, vec4);
+    for (int q = wave; q < p.rows; q += BLOCK / 64) {
+        const float norm = direct_norm(p.Xq, row_of[q], p.d, lane);
+        if (lane == 0) norms[q] = norm;
+    }
+    __syncthreads();
+    bool large = false;
+    for (int q = 0; q < p.rows; ++q) large = large || !(norms[q] < 1e36f);
+    block_passes<NQ>(p.nc, [&](auto per, int base) {
+        constexpr int C = decltype(per)::value;
+        int colour[C];
+        block_pass<C>(stream, qs,
+            [&](int c) {
+                const int cand = base + c * BLOCK + tid;
+                colour[c] = p.colour && cand < p.nc ? p.colour[cand] : -2;
+            },
+            [&](int q, float (&v)[C]) {
+                if (large || block_suspect(v)) {
+#pragma unroll
+                    for (int c = 0; c < C; ++c) {
+                        const int cand = base + c * BLOCK + tid;
+                        if (cand < p.nc && v[c] < INF && direct_bad_row(p.Xc, cand, p.d)) v[c] = INF;
+                        v[c] = v[c] < INF ? v[c] : INF;                      // (NaN: +inf)
+                    }
+                }
+                const int mine = colour_of[q];
+                float least = INF;
+#pragma unroll
+                for (int c = 0; c < C; ++c) {
+                    v[c] = colour[c] == mine || base + c * BLOCK + tid >= p.nc ? INF : v[c];
+                    least = fminf(least, v[c]);
+                }
+                // (the distance's word alone: another wavefront may be at it)
+                const float upto = __uint_as_float(*(volatile unsigned int*)(reinterpret_cast<unsigned int*>(best + q) + 1));
+                if (!__any(least < INF && !(least > upto))) return;          // (all ones, nothing yet, are a NaN)
+                unsigned long long key = ~0ull;
+#pragma unroll
+                for (int c = C - 1; c >= 0; --c)
+                    if (v[c] == least && v[c] < INF) key = ((unsigned long long)__float_as_uint(v[c]) << 32) | (unsigned int)(base + c * BLOCK + tid);
+#pragma unroll
+                for (int o = 32; o > 0; o >>= 1) {
+                    const unsigned long long other = __shfl_xor(key, o);
+                    key = other < key ? other : key;
+                }
+                if (lane == 0) atomicMin(best + q, key);
+            });
+    });
+    __syncthreads();
+    if (tid < p.rows && q0 + tid < p.m) {
+        const bool some = best[tid] != ~0ull && row_of[tid] >= 0 && norms[tid] < INF;
+        p.out_idx[q0 + tid] = some ? (int32_t)(unsigned int)best[tid] : -1;
+        p.out_dist[q0 + tid] = some ? __uint_as_float((unsigned int)(best[tid] >> 32)) : INF;
+    }
+}
+
 // Where every pair is evaluated instead of the engine's search, measured on both sides of the lines (us a call among others, this
 // against the engine).  What the operations cost is one part, what it takes to bring every candidate once to each panel of eight
 // queries, 64 at a time, the other; it grows with the candidates, and with their width where a step is more than one slab.
@@ -233,6 +655,93 @@ hipError_t direct_1nn(const float* Xq, int m, int nq_rows, const int32_t* q_rows
     hipLaunchKernelGGL(direct_1nn_kernel, dim3((unsigned)(panels * segments)), dim3(64 * WAVES), 0, s, p);
     if (segments > 1) hipLaunchKernelGGL(direct_unpack_kernel, per_m, dim3(256), 0, s, keys, m, out_idx, out_dist);
     return hipGetLastError();
+}
+
+// quads that the kernels are made for
+static int direct_quads(int d)
+{
+    const int q = (d + 3) / 4;
+    return q <= 2 ? 2 : q <= 4 ? 4 : q <= 8 ? 8 : q <= 12 ? 12 : q <= 16 ? 16 : q <= 24 ? 24 : 32;
+}
+template <typename F>
+static hipError_t direct_by_quads(int nq, F&& f)
+{
+    switch (nq) {
+        case 2: return f(std::integral_constant<int, 2>{});
+        case 4: return f(std::integral_constant<int, 4>{});
+        case 8: return f(std::integral_constant<int, 8>{});
+        case 12: return f(std::integral_constant<int, 12>{});
+        case 16: return f(std::integral_constant<int, 16>{});
+        case 24: return f(std::integral_constant<int, 24>{});
+        default: return f(std::integral_constant<int, 32>{});
+    }
+}
+constexpr size_t DIRECT_LDS = 160 << 10;
+static int direct_cus()
+{
+    int dev = 0, v = 0;
+    if (hipGetDevice(&dev) != hipSuccess || hipDeviceGetAttribute(&v, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess || v < 1) return 256;
+    return v;
+}
+
+// Rows per workgroup, 0: none fit.  Workgroups of one row more each where that saves a round of them.
+static int direct_knn_rows(long long n, int d)
+{
+    const int nq = direct_quads(d), cus = direct_cus();
+    for (int rounds = 1; rounds <= 64; ++rounds) {
+        const long long rows = (n + (long long)cus * rounds - 1) / ((long long)cus * rounds);
+        if (rows <= KNN_ROWS && direct_knn_bytes(nq, (int)rows, (int)n) <= DIRECT_LDS) return (int)rows;
+        if (rows <= 1) return 0;
+    }
+    return 0;
+}
+// The line, in instructions of a lane (two per feature, and about 24 for the rest of a pair and its share of the selection), measured on both
+// sides (us, engine and this, k = 12): 700 M: 2154 x 64 60 and 54, 1557 x 128 57 and 47, 2453 x 48 60 and 47, 4008 x 8 56 and 43; 750 M: 4330 x 2 72 and
+// 65, 2924 x 32 58 and 43; 850 M: 3843 x 16 62 and 56, 2658 x 40 60 and 59; 930 M: 2067 x 70 64 and 87, 3291 x 24 63 and 74, 4818 x 8 71 and 67;
+// 1100 M: 3535 x 20 64 and 73, 5303 x 2 88 and 97.  Where the caller waits for the lists, nothing hides the host's way through eight
+// launches: clustering 4096 x 16 (940 M) 470 and 428, 5000 x 16 (1400 M) 573 and 548.
+bool direct_knn_wanted(long long n, int d, int k, bool waited_for)
+{
+    return d <= 128 && k <= 64 && n <= 16384 && n * n * (8LL * direct_quads(d) + 24) <= (waited_for ? 1600000000LL : 800000000LL) && direct_knn_rows(n, d) > 0;
+}
+
+hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, int32_t* evaluated, unsigned int* nonfinite, hipStream_t s)
+{
+    const int rows = direct_knn_rows(n, d);
+    if (rows < 1) return hipErrorInvalidValue;
+    const DirectKnn p{X, n, d, k, rows, d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0, out_idx, out_dist, evaluated, nonfinite};
+    return direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
+        constexpr int NQ = decltype(quads)::value;
+        const size_t lds = direct_knn_bytes(NQ, rows, n);
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&direct_knn_kernel<NQ>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((direct_knn_kernel<NQ>), dim3((unsigned)((n + rows - 1) / rows)), dim3(BLOCK), lds, s, p);
+        return hipGetLastError();
+    });
+}
+
+// The line, for a round of connecting components against near_link's ten launches (us a clustering, without this and with lines at 600 M,
+// 1000 M, 2000 M, 3000 M): 2000 x 32 in tight clusters 451, 331, 314, 338, 332; 4096 x 16 499, 483, 449, 478, 467; 6000 x 64 711, 716, 702,
+// 729, 880; 3000 x 128 485, 479, 468, 574, 575.
+bool direct_near_wanted(long long m, long long nc, int d)
+{
+    return d <= 128 && m >= 1 && nc <= (1LL << 20) && m <= (1LL << 20) && m * nc * (8LL * direct_quads(d) + 24) <= 1000000000LL;
+}
+
+hipError_t direct_near(const float* Xq, int m, int nq_rows, const int32_t* q_rows, const float* Xc, int nc, int d, const int32_t* colour,
+                       int32_t* out_idx, float* out_dist, unsigned long long* pairs, hipStream_t s)
+{
+    if (m < 1) return hipSuccess;
+    const int cus = direct_cus(), rounds = (m + cus * NEAR_ROWS - 1) / (cus * NEAR_ROWS), rows = (m + cus * rounds - 1) / (cus * rounds);
+    const DirectNear p{Xq, Xc, q_rows, colour, m, nq_rows, nc, d, rows, out_idx, out_dist, pairs};
+    return direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
+        constexpr int NQ = decltype(quads)::value;
+        const size_t lds = ((size_t)BLOCK * block_pitch(NQ) + (size_t)rows * NQ) * 16;
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&direct_near_kernel<NQ>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL((direct_near_kernel<NQ>), dim3((unsigned)((m + rows - 1) / rows)), dim3(BLOCK), lds, s, p);
+        return hipGetLastError();
+    });
 }
 
 }  // namespace slhc

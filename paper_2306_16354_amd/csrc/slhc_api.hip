@@ -1136,10 +1136,26 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
 
 // The every-tile k-NN graph by the half-precision engine: any d, no padded copy, same lists as the list kernels.
 bool near_wanted(const NearWs& near, uint32_t flags) { return near.ok && !(flags & (SLHC_FP32_FILTER | SLHC_PANEL_ORDER)); }
+// (counted: somebody reads the counters, `hn` and the float16 copy may be missing afterwards all the same, see ws.near_ready)
 int run_knn_near(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist, unsigned long long* counters,
-                 float* hn, const NearWs& near, hipStream_t stream, int32_t* evaluated = nullptr, EventPair* ev_norm = nullptr,
+                 float* hn, const NearWs& near, hipStream_t stream, bool counted, int32_t* evaluated = nullptr, EventPair* ev_norm = nullptr,
                  EventPair* ev_sweep = nullptr)
 {
+    if (slhc::direct_knn_wanted(N, d, k, counted)) {
+        if (counted) {
+            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(counters), 64);
+            HIP_TRY(hipGetLastError());
+        }
+        if (ev_norm) { HIP_TRY(hipEventRecord(ev_norm->a, stream)); HIP_TRY(hipEventRecord(ev_norm->b, stream)); }
+        if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->a, stream));
+        HIP_TRY(slhc::direct_knn(X, (int)N, d, k, nbr_idx, nbr_dist, evaluated, counted ? reinterpret_cast<unsigned int*>(counters + 4) : nullptr, stream));
+        if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->b, stream));
+        if (evaluated) {
+            hipLaunchKernelGGL(k_sum_words, dim3(64), dim3(256), 0, stream, evaluated, (int)N, counters);
+            HIP_TRY(hipGetLastError());
+        }
+        return SLHC_OK;
+    }
     if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->a, stream));
     HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, reinterpret_cast<uint32_t*>(counters), 64, stream));
     HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, near.b, near.c, hn, reinterpret_cast<unsigned int*>(counters + 4), stream));
@@ -1222,8 +1238,8 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         if (pruned_out) *pruned_out = false;
         if (ev_order) { HIP_TRY(hipEventRecord(ev_order->a, stream)); HIP_TRY(hipEventRecord(ev_order->b, stream)); }
         ws.near_done = true;
-        ws.near_ready = true;
-        return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream,
+        ws.near_ready = !slhc::direct_knn_wanted(N, d, k, pruned_out != nullptr);
+        return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream, pruned_out != nullptr,
                             ev_sweep ? reinterpret_cast<int32_t*>(ws.hn_split) : nullptr, ev_norm, ev_sweep);
     }
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(ws.counters), 64);
@@ -1580,7 +1596,7 @@ int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products)
         const int32_t dw = working_columns(N, d);
         const KnnWs ws(nullptr, N, dw, true, k, false);
         const size_t pairs = slhc::near_pairs_bytes(N, dw, k + 1);
-        *products = !ws.near.ok ? 3.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
+        *products = !ws.near.ok ? 3.0 : slhc::direct_knn_wanted(N, d, k, false) ? 0.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
         return SLHC_OK;
     });
 }
@@ -1639,7 +1655,7 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k, int32
             NearWs near;
             near.carve(c, N, 0, d, k + 1, false, STATIC_SCRATCH_BYTES);
             if (near.ok && c.off <= STATIC_SCRATCH_BYTES)
-                return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream));
+                return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream), false);
         }
         KnnWs ws(ptr, N, d, false, 0, false);       // counters (cleared by run_knn) + half norms (all N written)
         if (ws.bytes > STATIC_SCRATCH_BYTES) { set_err("scratch layout %zu > %zu bytes", ws.bytes, STATIC_SCRATCH_BYTES); return SLHC_INTERNAL; }
@@ -2152,8 +2168,10 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
         }
         const int rc = check_shape(N, d, k, true);
         if (rc != SLHC_OK) return rc;
-        const int32_t dw = working_columns(N, d);
-        const size_t head = padded_copy_bytes(N, d);
+        // (the list kernels see a panel or two at most: the rows as they are)
+        const bool direct = !(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true);
+        const int32_t dw = direct ? d : working_columns(N, d);
+        const size_t head = direct ? 0 : padded_copy_bytes(N, d);
         const size_t need = head + SlhcWs(nullptr, N, dw, k, true, workspace_bytes > head ? workspace_bytes - head : 0).bytes;
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         if (dw != d) {
@@ -2464,11 +2482,14 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     p.todo = kws.near.b.todo;
                     p.tiles_done = nullptr;
                     HIP_TRY(slhc::launch_cross_1nn_sweep(p, s));
+                } else if (!round_pruned && near_wanted(kws.near, flags) && slhc::direct_near_wanted(n, N, d)) {
+                    HIP_TRY(slhc::direct_near(X, n, (int)N, rows, X, (int)N, d, ws.colour, ws.q_idx, ws.q_dist, kws.counters + 1, s));
+                    near_tile_steps += (unsigned long long)((n + 127) / 128) * tiles_1d;
                 } else if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;
                     if (!kws.near_ready) {
                         HIP_TRY(slhc::near_stats(X, (int)N, d, near.b, nullptr, 0, s));
-                        HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, near.b, near.c, nullptr, nullptr, s));
+                        HIP_TRY(slhc::near_make(X, (int)N, d, nullptr, (int)N, nullptr, near.b, near.c, kws.hn, nullptr, s));
                         kws.near_ready = true;
                     }
                     slhc::NearCopy q = near.q;

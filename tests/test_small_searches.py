@@ -1,0 +1,116 @@
+"""Searches small enough to evaluate every pair in registers (direct_kernels.hip): lists and trees against the float32-product list
+kernels, bit for bit."""
+import ctypes
+
+import pytest
+
+torch = pytest.importorskip("torch")
+
+
+@pytest.fixture(scope="module")
+def lib():
+    import paper_2306_16354_amd as slhc
+    slhc.load_library()
+    assert torch.cuda.is_available()
+    return slhc
+
+
+def rows(N, d, seed, spread=8.0):
+    g = torch.Generator(device="cuda").manual_seed(seed)
+    centres = (2 * torch.rand((max(2, N // 300), d), generator=g, device="cuda") - 1) * spread
+    return centres[torch.randint(len(centres), (N,), generator=g, device="cuda")] + torch.randn((N, d), generator=g, device="cuda")
+
+
+def same_lists(lib, X, k):
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    static = (torch.full_like(got[0], -7), torch.full_like(got[1], -7.0))
+    lib.knn_graph_static(X, k, static)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+    assert torch.equal(want[0], static[0]) and torch.equal(want[1], static[1])
+
+
+# every number of quads the kernel is made for, whole and in part, less than one quad; parts of a wavefront, of 512 rows and of the 1, 2 and 4
+# times 512 a lane holds; one round of workgroups and several, one row per workgroup and eight; both ways to a limit (16 and 17 neighbours),
+# all other rows; on both sides of the last search of its kind
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d,k", [
+    (2, 1, 1), (3, 3, 2), (63, 4, 8), (65, 5, 64), (66, 2, 17), (255, 7, 16), (257, 8, 2), (511, 9, 30), (512, 15, 1), (513, 16, 16), (700, 17, 17), (769, 31, 40),
+    (1024, 32, 9), (1025, 33, 3), (1100, 47, 12), (1281, 48, 64), (1535, 49, 5), (1537, 50, 10), (1300, 63, 7), (1793, 64, 33), (1000, 65, 4), (1409, 96, 21),
+    (1025, 97, 6), (900, 127, 64), (1690, 128, 16), (2047, 36, 8), (2049, 20, 11), (2561, 24, 5), (3073, 12, 19), (3700, 6, 25), (4097, 1, 13), (4472, 8, 3), (4473, 8, 3),
+])
+def test_lists(lib, N, d, k):
+    print(f"small k-NN N={N} d={d} k={k}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == (0.0 if N < 4473 else 1.0)
+    same_lists(lib, rows(N, d, N + d), k)
+
+
+# copies of a point by the tens and hundreds (as many as a row keeps and more, all rows equal), rows that are not finite or close to it, rows that do
+# not begin on 16 bytes
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["copies_30", "copies_130", "copies_600", "one_point", "lattice", "far_rows", "large", "not_finite", "odd_address"])
+@pytest.mark.parametrize("N,d,k", [(900, 6, 20), (1700, 32, 8), (1300, 61, 64)])
+def test_lists_of_unlike_rows(lib, kind, N, d, k):
+    print(f"small k-NN, {kind}, N={N} d={d} k={k}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == 0.0
+    X = rows(N, d, N)
+    if kind.startswith("copies"):
+        X = X[torch.arange(N, device="cuda") % (N // int(kind[7:]))].contiguous()
+    elif kind == "one_point":
+        X[:] = X[0].clone()
+    elif kind == "lattice":
+        X = (X / 4).round()
+    elif kind == "far_rows":
+        X[::70] *= 1e15
+    elif kind == "large":
+        X *= 3e17
+        X[5] = 0.0
+    elif kind == "not_finite":
+        X[N // 3] = float("nan")
+        X[N // 5, 2] = float("inf")
+        X[N // 7] = 3e19
+    elif kind == "odd_address":
+        X = torch.cat([X.new_zeros(1), X.reshape(-1)])[1:].reshape(N, d)
+        assert X.data_ptr() % 16 == 4
+    if kind != "not_finite":
+        same_lists(lib, X, k)
+        return
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
+    bad = torch.tensor([N // 3, N // 5, N // 7], device="cuda")
+    fine = torch.ones(N, dtype=torch.bool, device="cuda")
+    fine[bad] = False
+    assert torch.equal(want[0][fine], got[0][fine]) and torch.equal(want[1][fine], got[1][fine])
+    assert (got[0][bad] == -1).all() and torch.isinf(got[1][bad]).all() and not torch.isin(got[0], bad.to(torch.int32)).any()
+
+
+# the same where the pairs can be counted on the host: which searches go this way does not depend on a GPU
+@pytest.mark.parametrize("N,d,k,products", [(2048, 32, 8, 0.0), (4472, 8, 3, 0.0), (4473, 8, 3, 1.0), (1690, 128, 16, 0.0), (1691, 128, 16, 1.0), (500, 129, 4, 1.0)])
+def test_searches_that_multiply_nothing(N, d, k, products):
+    import paper_2306_16354_amd as slhc
+    lib = slhc.load_library()
+    out = ctypes.c_double(-1.0)
+    assert lib.slhc_probe_knn_products(N, d, k, ctypes.byref(out)) == 0 and out.value == products
+
+
+# rounds of connecting components: clusters too far apart for the lists, several rounds, copies in other components, few and many queries; rows that
+# are read as they are (16 columns) and with columns of zeros; a forest of one workgroup and of many
+@pytest.mark.gpu
+@pytest.mark.parametrize("kind", ["clusters", "tight", "copies", "lattice", "large"])
+@pytest.mark.parametrize("N,d,k", [(3, 2, 1), (70, 5, 3), (513, 16, 2), (1025, 33, 4), (1537, 64, 8), (2049, 7, 3), (3100, 16, 4), (3500, 30, 6), (1800, 128, 5), (12_500, 4, 6)])
+def test_trees(lib, kind, N, d, k):
+    print(f"small trees, {kind}, N={N} d={d} k={k}", flush=True)
+    X = rows(N, d, N, 200.0)
+    if kind == "tight":
+        X = (X / 20).round() * 20 + 1e-2 * rows(N, d, N + 1, 0.0)
+    elif kind == "copies":
+        X = X[torch.arange(N, device="cuda") % (N // 9 + 2)].contiguous()
+        X[::2] += 3000.0
+    elif kind == "lattice":
+        X = (X / 60).round()
+    elif kind == "large":
+        X *= 1e16
+    want, got = lib.slhc(X, k, prune=False, fp32_filter=True), lib.slhc(X, k, prune=False)
+    torch.cuda.synchronize()
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
