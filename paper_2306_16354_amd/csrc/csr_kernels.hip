@@ -101,11 +101,7 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
         const unsigned int o_at = (unsigned int)__shfl((int)at, owner), o_end = (unsigned int)__shfl((int)end, owner);
         const int o_v = __shfl(v, owner), o_c = __shfl(c, owner);
         unsigned long long key = m != 0 ? row_part<FIRST>(f, o_v, o_c, o_at + 4 * (lane & 15), o_end, 64) : NO_EDGE;
-#pragma unroll
-        for (int o = 8; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other < key ? other : key;
-        }
+        key = lanes_min<8>(lanes_min<4>(lanes_min<2>(lanes_min<1>(key))));
         const int mine = __builtin_amdgcn_mbcnt_hi((unsigned int)(todo >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)todo, 0u));       // (this lane's, if it has one)
         const unsigned long long result = __shfl(key, (mine & 3) * 16);
         if ((todo >> lane & 1) != 0 && mine < 4) best = result;
@@ -114,11 +110,7 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
     for (todo = __ballot(length > HUGE_ROW); todo != 0; todo &= todo - 1) {
         const int owner = __builtin_ctzll(todo);
         unsigned long long key = row_part<FIRST>(f, __shfl(v, owner), __shfl(c, owner), (unsigned int)__shfl((int)at, owner) + 4 * lane, (unsigned int)__shfl((int)end, owner), 256);
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other < key ? other : key;
-        }
+        key = wave_min(key);
         if (lane == owner) best = key;
     }
     *wbits = (uint32_t)(best >> 32);

@@ -177,11 +177,7 @@ __global__ void __launch_bounds__(64 * WAVES) direct_1nn_kernel(Direct1nn p)
     for (int q = 0; q < QW1; ++q) {
         const int i = (panel * WAVES + wave) * QW1 + q;
         unsigned long long key = at[q] >= 0 && row[q] >= 0 && norm[q] < INF ? ((unsigned long long)__float_as_uint(best[q]) << 32) | (unsigned int)at[q] : ~0ull;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other < key ? other : key;
-        }
+        key = wave_min(key);
         if (lane == 0 && i < p.m) {
             if (p.segments > 1) { if (key != ~0ull) atomicMin(p.keys + i, key); }
             else {
@@ -447,8 +443,7 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
 #pragma unroll
         for (int j = 0; j < 64; ++j) rank += __uint_as_float((unsigned int)__builtin_amdgcn_readlane((int)__float_as_uint(least), j)) < least ? 1 : 0;
         limit = rank < p.k ? least : 0.f;                                     // (distances are not negative)
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) limit = fmaxf(limit, __shfl_xor(limit, o));
+        limit = wave_max(limit);
     } else {
         float least[4] = {INF, INF, INF, INF};
         all([&](int, const float (&v)[16]) {
@@ -458,8 +453,7 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
         float lo = INF, hi = 0.f;
 #pragma unroll
         for (int j = 0; j < 4; ++j) { lo = fminf(lo, least[j]); hi = least[j] < INF ? fmaxf(hi, least[j]) : hi; }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+        lo = wave_min(lo); hi = wave_max(hi);
         auto reach = [&](float upto) {
             int n = 0;
 #pragma unroll
@@ -607,11 +601,7 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
 #pragma unroll
                 for (int c = C - 1; c >= 0; --c)
                     if (v[c] == least && v[c] < INF) key = ((unsigned long long)__float_as_uint(v[c]) << 32) | (unsigned int)(base + c * BLOCK + tid);
-#pragma unroll
-                for (int o = 32; o > 0; o >>= 1) {
-                    const unsigned long long other = __shfl_xor(key, o);
-                    key = other < key ? other : key;
-                }
+                key = wave_min(key);
                 if (lane == 0) atomicMin(best + q, key);
             });
     });

@@ -267,12 +267,9 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     }
 #pragma unroll
     for (int i = 0; i < PASSES; ++i) {
-        float n = nn[i], r = rr[i], x = xx[i];
-        int hg = huge[i] ? 1 : 0;
-#pragma unroll
-        for (int o = 1; o < LPR; o <<= 1) {
-            n += __shfl_xor(n, o); r += __shfl_xor(r, o); x += __shfl_xor(x, o); hg |= __shfl_xor(hg, o);
-        }
+        float n = lanes_add8(nn[i]), r = lanes_add8(rr[i]), x = lanes_add8(xx[i]);
+        int hg = lanes_or<4>(lanes_or<2>(lanes_or<1>(huge[i] ? 1 : 0)));
+        if (LPR == 16) { n = lanes_add<8>(n); r = lanes_add<8>(r); x = lanes_add<8>(x); hg = lanes_or<8>(hg); }
         if (part == 0 && mine) {
             const int at = t * TILE + blk * 32 + sub + i * ROWS;
             float nh = -p.h_of_n * n;
@@ -1004,8 +1001,7 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
             hi = fine ? fmaxf(hi, v[j]) : hi;
             v[j] = fine ? v[j] : -INF;
         }
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    lo = wave_min(lo); hi = wave_max(hi);
     if (have >= kk)
         for (int it = 0; it < (LIMIT ? BISECT_FAR : BISECT); ++it) {
             const float mid = 0.5f * lo + 0.5f * hi;
@@ -1101,9 +1097,7 @@ __device__ inline float near_exact(const v4f (&q)[4], const float* __restrict__ 
         s0 = near_quad_sqdist(a00, b00, s0); s0 = near_quad_sqdist(a01, b01, s0);
         s1 = near_quad_sqdist(a10, b10, s1); s1 = near_quad_sqdist(a11, b11, s1);
     }
-    s0 += __shfl_xor(s0, 1); s0 += __shfl_xor(s0, 2); s0 += __shfl_xor(s0, 4);
-    s1 += __shfl_xor(s1, 1); s1 += __shfl_xor(s1, 2); s1 += __shfl_xor(s1, 4);
-    return s0 + s1;
+    return lanes_add8(s0) + lanes_add8(s1);
 }
 template <bool VEC4>
 __device__ inline void near_first_quads(v4f (&q)[4], const float* __restrict__ xa, int d, int g)
@@ -1460,9 +1454,7 @@ __global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
     for (int turn = 0; turn < 128; ++turn) {
         // the lane with the largest value that may still hide the nearest
         const float mine = fmaxf(pending[0] ? m1[0] : -INF, pending[1] ? m1[1] : -INF);
-        float mx = mine;
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) mx = fmaxf(mx, __shfl_xor(mx, o));
+        const float mx = wave_max(mine);
         if (!(mx > -INF) || mx < bound) break;
         const int who = __builtin_ctzll(__ballot(mine == mx));
         const bool second = !(pending[0] && m1[0] == mx);
@@ -1478,11 +1470,7 @@ __global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
             const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
             if (fine && dist < INF && k < key) key = k;
         }
-#pragma unroll
-        for (int o = 8; o < 64; o <<= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other < key ? other : key;
-        }
+        key = wave_min<8>(key);                                      // (eight lanes have one pair)
         evaluated += 16;
         if (key != ~0ull) bound = fmaxf(LOWEST, near_bound_at(__uint_as_float((unsigned int)(key >> 32)) * p.sc->scale * p.sc->scale, -nh, a));
     }
@@ -2053,11 +2041,7 @@ __global__ void __launch_bounds__(LIST_THREADS) near_first_kernel(NearList p)
                 if (gap >= 0.f && !(tc >= 0 && tc == colour)) best = key < best ? key : best;
             }
         }
-#pragma unroll
-        for (int o = 32; o > 0; o >>= 1) {
-            const unsigned long long other = __shfl_xor(best, o);
-            best = other < best ? other : best;
-        }
+        best = wave_min(best);
         if (lane == 0 && best != ~0ull) list[atomicAdd(&g.count, 1)] = (unsigned short)(best & 0xffffu);
     }
     __syncthreads();
@@ -2360,11 +2344,7 @@ __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
             const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
             if (fine && dist < INF && k < key) key = k;
         }
-#pragma unroll
-        for (int o = 8; o < 64; o <<= 1) {
-            const unsigned long long other = __shfl_xor(key, o);
-            key = other < key ? other : key;
-        }
+        key = wave_min<8>(key);                                      // (eight lanes have one pair)
     }
     if (lane == 0) {
         if (p.edge_at) {
@@ -2714,7 +2694,7 @@ __global__ void __launch_bounds__(256) near_unpack_kernel(const unsigned long lo
         const float* b = Xc + (size_t)cand * d;
         for (int c = 4 * g; c < d; c += 32) s = near_quad_sqdist(near_quad<VEC4>(a, c, d), near_quad<VEC4>(b, c, d), s);
     }
-    s += __shfl_xor(s, 1); s += __shfl_xor(s, 2); s += __shfl_xor(s, 4);
+    s = lanes_add8(s);
     if (g == 0) {
         out_idx[qi] = fine ? (int32_t)cand : 0;
         out_dist[qi] = fine ? s : INF;

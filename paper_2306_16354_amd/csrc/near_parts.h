@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "near_kernels.h"
+#include "wave_ops.h"
 
 namespace slhc {
 
@@ -123,8 +124,7 @@ __device__ inline float near_kth(int n, int kk, V&& value)
         hi = fine ? fmaxf(hi, x) : hi;
     }
     if (have < kk) return LOWEST;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    lo = wave_min(lo); hi = wave_max(hi);
     for (int it = 0; it < BISECT; ++it) {
         const float mid = 0.5f * lo + 0.5f * hi;
         int reach = 0;

@@ -513,8 +513,7 @@ __device__ inline float pair_kth(const uint2 (&mine)[PAIR_WORDS], int n, int kk)
             hi = fine ? fmaxf(hi, x) : hi;
         }
     if (have < kk) return LOWEST;
-#pragma unroll
-    for (int o = 32; o > 0; o >>= 1) { lo = fminf(lo, __shfl_xor(lo, o)); hi = fmaxf(hi, __shfl_xor(hi, o)); }
+    lo = wave_min(lo); hi = wave_max(hi);
     for (int it = 0; it < BISECT_FAR; ++it) {
         const float mid = 0.5f * lo + 0.5f * hi;
         int reach = 0;

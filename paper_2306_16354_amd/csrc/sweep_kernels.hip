@@ -35,6 +35,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "sweep_kernels.h"
+#include "wave_ops.h"
 
 namespace slhc {
 
@@ -146,13 +147,7 @@ __device__ inline float group8_sqdist(const float* __restrict__ a_, const float*
             s1 = quad_sqdist(a11, b11, s1);
         }
     }
-    s0 += __shfl_xor(s0, 1);
-    s0 += __shfl_xor(s0, 2);
-    s0 += __shfl_xor(s0, 4);
-    s1 += __shfl_xor(s1, 1);
-    s1 += __shfl_xor(s1, 2);
-    s1 += __shfl_xor(s1, 4);
-    return s0 + s1;
+    return lanes_add8(s0) + lanes_add8(s1);
 }
 
 // h_i = (1-c)/2 * ||x_i||^2 ; one 16-lane group per row.
@@ -194,10 +189,7 @@ __global__ void __launch_bounds__(256) half_norm_kernel(const float* __restrict_
             }
         }
     }
-    s += __shfl_xor(s, 1);
-    s += __shfl_xor(s, 2);
-    s += __shfl_xor(s, 4);
-    s += __shfl_xor(s, 8);
+    s = lanes_add<8>(lanes_add8(s));
     if (active && lane16 == 0) {
         hn[row] = scale * s;
         if (nonfinite && !(s < __builtin_inff())) atomicOr(nonfinite, 1u);      // NaN fails the compare too
@@ -384,10 +376,7 @@ __device__ inline void resolve_pairs_of_32(const SweepLds<1>& L, int qcount, Ent
 #pragma unroll
         for (int u = 0; u < 4; ++u) { s0[u] = quad_sqdist(a0[u], b0[u], 0.f); s1[u] = quad_sqdist(a1[u], b1[u], 0.f); }
 #pragma unroll
-        for (int o = 1; o < 8; o <<= 1) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) { s0[u] += __shfl_xor(s0[u], o); s1[u] += __shfl_xor(s1[u], o); }
-        }
+        for (int u = 0; u < 4; ++u) { s0[u] = lanes_add8(s0[u]); s1[u] = lanes_add8(s1[u]); }
 #pragma unroll
         for (int u = 0; u < 4; ++u)
             if (g8 == 0 && s + 8 * u + grp < qcount) atomicMin(&L.lists[w32 + ql[u]], make_key(s0[u] + s1[u], cid[u]));
@@ -504,10 +493,7 @@ __device__ __attribute__((noinline)) void seed_resolve(SeedPick pick, int col0, 
     if (few) {
         // only the lightest edge is of use: of every 8 lanes the one whose pair looks nearest, together one pass
         const float near = has ? L.hqs[wave * 32 + l32] - pick.v : __builtin_inff();
-        float least = near;
-        least = fminf(least, __shfl_xor(least, 1));
-        least = fminf(least, __shfl_xor(least, 2));
-        least = fminf(least, __shfl_xor(least, 4));
+        const float least = lanes_min<4>(lanes_min<2>(lanes_min<1>(near)));
         has = has && near == least;
     }
     const unsigned long long mask = __ballot(has);
@@ -1497,28 +1483,16 @@ __global__ void __launch_bounds__(WG_THREADS, 2) sweep_kernel_qreg(SweepParams p
         // largest threshold of this wavefront's 32 queries, from their bounds: thr = 2 (h_q - bound)
         auto refresh_wave_thr = [&]() {
             float t = (my_qrow >= 0) ? 2.f * (hqs[my_q_local] - bound) : 0.f;
-            t = fmaxf(t, __shfl_xor(t, 1));
-            t = fmaxf(t, __shfl_xor(t, 2));
-            t = fmaxf(t, __shfl_xor(t, 4));
-            t = fmaxf(t, __shfl_xor(t, 8));
-            t = fmaxf(t, __shfl_xor(t, 16));
+            t = lanes_max<16>(lanes_max<8>(lanes_max<4>(lanes_max<2>(lanes_max<1>(t)))));
             // 2 (h_q - bound) reproduces the threshold up to a few ulps of h_q; widen it
             wave_thr_max = t + 4.f * 1.1920929e-07f * fmaxf(fabsf(hqs[my_q_local]), t);
-            wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 1));
-            wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 2));
-            wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 4));
-            wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 8));
-            wave_thr_max = fmaxf(wave_thr_max, __shfl_xor(wave_thr_max, 16));
+            wave_thr_max = lanes_max<16>(lanes_max<8>(lanes_max<4>(lanes_max<2>(lanes_max<1>(wave_thr_max)))));
         };
         auto lower_word = [&]() {
             if constexpr (KL == 1 && MASKED) {
                 // the lightest exact edge any query of this wavefront holds now
                 unsigned int best = my_qrow >= 0 ? (unsigned int)(mylists[l32] >> 32) : 0x7f800000u;
-#pragma unroll
-                for (int o = 16; o > 0; o >>= 1) {
-                    const unsigned int other = (unsigned int)__shfl_xor((int)best, o);
-                    best = other < best ? other : best;
-                }
+                best = lanes_min<16>(lanes_min<8>(lanes_min<4>(lanes_min<2>(lanes_min<1>(best)))));
                 // the word is lowered to `lower_factor` times that edge, not to the edge itself (see SweepParams)
                 const float target = p.comp_lower_factor * __uint_as_float(best);
                 if (target < thr_c) {
