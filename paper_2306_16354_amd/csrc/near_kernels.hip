@@ -735,10 +735,10 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
         const size_t t = tile;
         unsigned char* dst = near_smem + (i & 1) * BUF;
         const unsigned char* src = p.cfrag + t * (KS * FRAG_STEP);
-        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
+        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src, j * 1024, dst + j * 1024, true);
         for (int j = wave; j < (COLOURED ? 4 : 2); j += waves) {
-            const void* g = j < 2 ? (const void*)(p.cnegh + t * TILE + j * 64 + lane) : (const void*)(p.ccolour + t * TILE + (j - 2) * 64 + lane);
-            near_lds_load(g, dst + KS * FRAG_STEP + j * 256, false);
+            const void* rows = j < 2 ? (const void*)(p.cnegh + t * TILE) : (const void*)(p.ccolour + t * TILE);
+            near_lds_load(rows, (j & 1) * 256, dst + KS * FRAG_STEP + j * 256, false);
         }
     };
     int next = ntiles > 0 ? tile_at(0) : 0;
@@ -878,21 +878,20 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
         for (int x = 0; x < 8; ++x) {
             const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block]
             const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
-            const unsigned char* src;
             if (side == 0) {
                 const int at_q = q_src[blk];
-                src = p.qfrag + ((size_t)(at_q >> 7) * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + ((at_q >> 5) & 3) * 1024 + (lhalf * 32 + (at_q & 31)) * 16;
+                near_lds_gather(p.qfrag + ((size_t)(at_q >> 7) * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + ((at_q >> 5) & 3) * 1024 + (lhalf * 32 + (at_q & 31)) * 16,
+                                dst + piece * 1024);
             } else {
                 const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
-                src = p.cfrag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16;
+                near_lds_load(p.cfrag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP, blk * 1024, dst + piece * 1024, true);
             }
-            near_lds_load(src, dst + piece * 1024, true);
         }
         if (chunk == 0 && wave < (COLOURED ? 8 : 4)) {
             const int tile = (wave >> 1) & 1, half = wave & 1;
             const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
-            const void* g = wave < 4 ? (const void*)(p.cnegh + t * TILE + half * 64 + lane) : (const void*)(p.ccolour + t * TILE + half * 64 + lane);
-            near_lds_load(g, near_smem + 2 * WIDE_BUF + (i & 1) * 2048 + wave * 256, false);
+            const void* rows = wave < 4 ? (const void*)(p.cnegh + t * TILE) : (const void*)(p.ccolour + t * TILE);
+            near_lds_load(rows, half * 256, near_smem + 2 * WIDE_BUF + (i & 1) * 2048 + wave * 256, false);
         }
     };
     const int per_part = MODE == NEAR_MAXIMA ? (nmine + p.parts - 1) / p.parts : 0;

@@ -234,10 +234,9 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
         const size_t t = tile < p.tiles ? tile : p.tiles - 1;
         unsigned char* dst = pairs_smem + (i & 1) * BUF;
         const unsigned char* src = p.frag + t * (KS * FRAG_STEP);
-        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src + j * 1024 + lane * 16, dst + j * 1024, true);
+        for (int j = wave; j < KS * 4; j += waves) near_lds_load(src, j * 1024, dst + j * 1024, true);
         for (int j = wave; j < 4; j += waves) {
-            const float* g = (j < 2 ? p.negh : p.limit) + t * TILE + (j & 1) * 64 + lane;
-            near_lds_load(g, dst + KS * FRAG_STEP + j * 256, false);
+            near_lds_load((j < 2 ? p.negh : p.limit) + t * TILE, (j & 1) * 256, dst + KS * FRAG_STEP + j * 256, false);
         }
     };
     if (total > 0) { advance(); stage(0, next_tile); }
@@ -356,19 +355,19 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
             const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
             const int b2 = (side ? block : range.block) * 2;
             const size_t t = b2 + tile < p.tiles ? b2 + tile : b2;
-            const unsigned char* src = p.frag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + blk * 1024 + lane * 16;
-            near_lds_load(src, dst + piece * 1024, true);
+            near_lds_load(p.frag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP, blk * 1024, dst + piece * 1024, true);
         }
         if (chunk == 0) {
             unsigned char* rows = pairs_smem + 2 * WIDE_BUF + (i & 1) * WIDE_ROWS;
             for (int piece = wave; piece < (BEST ? 12 : 8); piece += 8) {
                 const int what = piece >> 2, tile = (piece >> 1) & 1, half = piece & 1;
                 const size_t t = block * 2 + tile < p.tiles ? block * 2 + tile : block * 2;
-                const size_t r = t * TILE + half * 64 + lane;
-                const void* g = what == 0 ? (const void*)(p.negh + r)
+                const size_t r = t * TILE;
+                const void* base = what == 0 ? (const void*)(p.negh + r)
                               : what == 2 ? (const void*)(p.colour + r)
                               : BEST ? (const void*)(reinterpret_cast<const uint32_t*>(p.best + r) + 1) : (const void*)(p.limit + r);
-                near_lds_load(g, rows + piece * 256, false);
+                const int stride = BEST && what == 1 ? 8 : 4;
+                near_lds_load(base, half * 64 * stride, rows + piece * 256, false, stride);
             }
         }
     };
