@@ -1667,7 +1667,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
                            static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE, lost);
     }
     NearPairs r{};
-    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.blocks = plan.blocks; r.spread = near_spread(r.blocks);
+    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.filled = (a.d + 15) / 16; r.blocks = plan.blocks; r.spread = near_spread(r.blocks);
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
     const bool again = c.tiles >= PAIR_AGAIN_TILES;
     r.lost = lost; r.lost_most = again ? a.nq / 2 : rows;
@@ -2436,7 +2436,7 @@ __global__ void __launch_bounds__(256) near_pair_best_kernel(const unsigned long
 static hipError_t near_link_pairs(const NearLink& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
 {
     NearPairs r{};
-    r.frag = c.frag; r.negh = c.negh_best; r.colour = c.colour; r.tiles = c.tiles; r.steps = near_steps(a.d);
+    r.frag = c.frag; r.negh = c.negh_best; r.colour = c.colour; r.tiles = c.tiles; r.steps = near_steps(a.d); r.filled = (a.d + 15) / 16;
     r.blocks = (c.tiles + 1) / 2; r.spread = near_spread(r.blocks);
     r.best = reinterpret_cast<unsigned long long*>(b.batch);
     const int n = c.tiles * TILE, half = r.blocks / 2 + 1, cus = near_cus();

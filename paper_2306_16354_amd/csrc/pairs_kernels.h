@@ -11,7 +11,7 @@ constexpr int PAIRS_MOST = 1024;           // entries of a row's list at most
 
 struct NearPairs {
     const unsigned char* frag; const float* negh; const int32_t* colour;      // the copy (colour: pairs_best)
-    int tiles, steps;
+    int tiles, steps, filled;              // steps of 16 columns a row's place has, and how many of them hold columns
     int blocks, from, to, nseg;            // block i meets the blocks i + from .. i + to - 1, in nseg shares
     int spread;                            // near_spread(blocks): place i of the circle has block i * spread % blocks of the copy
     float* limit;                          // pairs_emit: by position, the u from which on a pair matters to the row (NaN: none does)

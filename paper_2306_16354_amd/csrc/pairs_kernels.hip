@@ -303,11 +303,19 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
 // Beyond 128 columns: 256 x 256 rows per meeting, both sides streamed through LDS, as near_wide_kernel; a block is two tiles.
 //   BEST = false  pairs within either row's limit go to that row's list
 //   BEST = true   rows of another colour: every row's smallest w = max(0, -u), with the place of the 16 rows about it
-constexpr int WIDE_STEPS = 4;
-constexpr int WIDE_HALF = 2 * WIDE_STEPS * FRAG_STEP;                   // two tiles' steps: 32 KiB
-constexpr int WIDE_BUF = 2 * WIDE_HALF;
+//
+// A step of the pipeline is a chunk of 32 columns of both sides, 32 KiB, in one of four buffers: the loads run three chunks ahead, and the
+// fragments of a chunk's first 16 columns are read while the last ones of the chunk before are multiplied, so that after a barrier there is
+// something to multiply at once.  250k x 784, the pass for the k-NN graph and that for the first connection round: 48.6 and 49.1 ms with chunks of 64
+// columns in two buffers, every fragment read after the chunk's barrier and all reads waited for at once; 44.8 and 46.4 so (1.09 PFLOP/s of
+// products made once, the matrix pipe 54 % busy at 1.92 GHz, to which it throttles).
+constexpr int CHUNK_STEPS = 2;
+constexpr int CHUNK_TILE = CHUNK_STEPS * FRAG_STEP;
+constexpr int CHUNK_SIDE = 2 * CHUNK_TILE;
+constexpr int CHUNK = 2 * CHUNK_SIDE;
+constexpr int CHUNKS = 4;                                               // buffers
 constexpr int WIDE_ROWS = 3072;                                         // half norms, limits or smallest w, colours of 256 rows
-constexpr int WIDE_LDS = 2 * WIDE_BUF + 2 * WIDE_ROWS;
+constexpr int WIDE_LDS = CHUNKS * CHUNK + 2 * WIDE_ROWS;
 
 template <bool BEST>
 __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
@@ -342,27 +350,24 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
     w.at = reinterpret_cast<uint2*>(pairs_smem + WIDE_LDS + wave * WAVE_LDS);
     w.n = w.records = 0; w.read = w.asked = false; w.u = w.code = w.u2 = w.code2 = 0u; w.q_limit = w.c_limit = NEVER; w.q_slot = w.c_slot = -1;
 
-    const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
+    const int nchunks = (p.filled + CHUNK_STEPS - 1) / CHUNK_STEPS;     // (at least five, beyond 128 columns)
+    const bool odd = (p.filled & 1) != 0;                               // the last chunk has one step
     const int nmine = range.j1 - range.j0;
     const int total = nmine * nchunks;
     auto block_at = [&](int i) { return pair_other(p, range, pair_offset(range, range.j0 + i)); };
-    // the loads of step `at` (meeting, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the rows' words with chunk 0
-    auto stage = [&](int i, int block, int chunk, int at) {
-        unsigned char* dst = pairs_smem + (at & 1) * WIDE_BUF;
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block of 32]
-            const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
-            const int b2 = (side ? block : range.block) * 2;
-            const size_t t = b2 + tile < p.tiles ? b2 + tile : b2;
-            near_lds_load(p.frag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP, blk * 1024, dst + piece * 1024, true);
-        }
-        if (chunk == 0) {
-            unsigned char* rows = pairs_smem + 2 * WIDE_BUF + (i & 1) * WIDE_ROWS;
+    // the next chunk's loads: a wavefront has one step of one tile of one side, four pieces of 1 KiB, and with a meeting's first chunk the rows' words
+    int staged = 0, stage_i = 0, stage_chunk = 0, stage_block = nmine > 0 ? block_at(0) : 0;
+    auto stage = [&]() {
+        const int side = wave >> 2, tile = (wave >> 1) & 1, st = wave & 1;
+        const int b2 = (side ? stage_block : range.block) * 2;
+        const size_t t = b2 + tile < p.tiles ? b2 + tile : b2;
+        const unsigned char* src = p.frag + (t * p.steps + stage_chunk * CHUNK_STEPS + st) * FRAG_STEP;
+        unsigned char* dst = pairs_smem + (staged & (CHUNKS - 1)) * CHUNK + wave * FRAG_STEP;
+        if (stage_chunk == 0) {
+            unsigned char* rows = pairs_smem + CHUNKS * CHUNK + (stage_i & 1) * WIDE_ROWS;
             for (int piece = wave; piece < (BEST ? 12 : 8); piece += 8) {
-                const int what = piece >> 2, tile = (piece >> 1) & 1, half = piece & 1;
-                const size_t t = block * 2 + tile < p.tiles ? block * 2 + tile : block * 2;
-                const size_t r = t * TILE;
+                const int what = piece >> 2, half = piece & 1;
+                const size_t r = (stage_block * 2 + ((piece >> 1) & 1) < p.tiles ? stage_block * 2 + ((piece >> 1) & 1) : stage_block * 2) * (size_t)TILE;
                 const void* base = what == 0 ? (const void*)(p.negh + r)
                               : what == 2 ? (const void*)(p.colour + r)
                               : BEST ? (const void*)(reinterpret_cast<const uint32_t*>(p.best + r) + 1) : (const void*)(p.limit + r);
@@ -370,43 +375,41 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
                 near_lds_load(base, half * 64 * stride, rows + piece * 256, false, stride);
             }
         }
+#pragma unroll
+        for (int blk = 0; blk < 4; ++blk) near_lds_load(src, blk * 1024, dst + blk * 1024, true);
+        ++staged;
+        if (++stage_chunk == nchunks) {
+            stage_chunk = 0;
+            if (++stage_i < nmine) stage_block = block_at(stage_i);
+        }
     };
-    int block = nmine > 0 ? block_at(0) : 0;
-    if (total > 0) stage(0, block, 0, 0);
-    int at = 0;
+    v16f acc[2][4];                                                     // [query block][candidate block]
+    v8h qf[2][2], cf[2][4];                                             // [step of the chunk]
+    auto read = [&](int at, int st) {
+        const unsigned char* qs = pairs_smem + (at & (CHUNKS - 1)) * CHUNK + (qg >> 1) * CHUNK_TILE + st * FRAG_STEP + (qg & 1) * 2048 + lane * 16;
+        const unsigned char* cs = pairs_smem + (at & (CHUNKS - 1)) * CHUNK + CHUNK_SIDE + cg * CHUNK_TILE + st * FRAG_STEP + lane * 16;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) qf[st][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) cf[st][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
+        __builtin_amdgcn_sched_barrier(0);                              // (ahead of the multiplies that follow)
+    };
+    auto multiply = [&](int st, int from, int to) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+                if (cb >= from && cb < to) acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st][cb], qf[st][qb], acc[qb][cb], 0, 0, 0);
+    };
+    for (int i = 0; i < CHUNKS - 1 && i < total; ++i) stage();
+    near_lds_ready();
+    int at = 0, block = nmine > 0 ? block_at(0) : 0;
     for (int i = 0; i < nmine; ++i) {
-        const unsigned char* rows = pairs_smem + 2 * WIDE_BUF + (i & 1) * WIDE_ROWS;
+        const unsigned char* rows = pairs_smem + CHUNKS * CHUNK + (i & 1) * WIDE_ROWS;
         const bool own = block == range.block;
         const int tile = block * 2 + cg;
-        const int next = i + 1 < nmine ? block_at(i + 1) : block;
-        v16f acc[2][4];                                                 // [query block][candidate block]
-        auto step = [&]() {
-            const unsigned char* qs = pairs_smem + (at & 1) * WIDE_BUF + (qg >> 1) * (WIDE_STEPS * FRAG_STEP) + (qg & 1) * 2048 + lane * 16;
-            const unsigned char* cs = pairs_smem + (at & 1) * WIDE_BUF + WIDE_HALF + cg * (WIDE_STEPS * FRAG_STEP) + lane * 16;
-            v8h qf[2][2], cf[2][4];
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) qf[0][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
-#pragma unroll
-            for (int st = 0; st < WIDE_STEPS; ++st) {
-                if (st + 1 < WIDE_STEPS) {
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb) qf[(st + 1) & 1][qb] = *reinterpret_cast<const v8h*>(qs + (st + 1) * FRAG_STEP + qb * 1024);
-#pragma unroll
-                    for (int cb = 0; cb < 4; ++cb) cf[(st + 1) & 1][cb] = *reinterpret_cast<const v8h*>(cs + (st + 1) * FRAG_STEP + cb * 1024);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb)
-                        acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st & 1][cb], qf[st & 1][qb], acc[qb][cb], 0, 0, 0);
-            }
-        };
-        near_lds_ready();
-        if (!BEST) { if (live) pair_turn(w, p, q0, 64); }
-        if (at + 1 < total) stage(nchunks > 1 ? i : i + 1, nchunks > 1 ? block : next, nchunks > 1 ? 1 : 0, at + 1);
+        // (the chunk and the rows' words have been there since the last barrier)
+        read(at, 0);
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             v16f hv;
@@ -417,16 +420,35 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
             }
             acc[0][cb] = hv; acc[1][cb] = hv;
         }
-        step();
-        ++at;
+        // The next chunk is in LDS once all loads are done but the four of the chunk after that, and every wavefront has read the chunk before
+        // this one, whose buffer is filled next: what may still be on its way are the six fragments of this chunk's first step.
+        auto ready = [&]() {
+            asm volatile("" ::: "memory");
+            __builtin_amdgcn_sched_barrier(0);
+            if (at + 2 < total) __builtin_amdgcn_s_waitcnt(0x0674);     // vmcnt(4) lgkmcnt(6)
+            else __builtin_amdgcn_s_waitcnt(0x0670);
+            __builtin_amdgcn_s_barrier();
+            asm volatile("" ::: "memory");
+        };
+#pragma unroll 1
         for (int chunk = 1; chunk < nchunks; ++chunk, ++at) {
-            near_lds_ready();
-            if (at + 1 < total) {
-                const bool wrap = chunk + 1 == nchunks;
-                stage(wrap ? i + 1 : i, wrap ? next : block, wrap ? 0 : chunk + 1, at + 1);
-            }
-            step();
+            ready();
+            read(at, 1);
+            multiply(0, 0, 2);
+            if (staged < total) stage();
+            multiply(0, 2, 4);
+            __builtin_amdgcn_sched_barrier(0);
+            read(at + 1, 0);
+            multiply(1, 0, 4);
         }
+        ready();
+        read(at, 1);
+        multiply(0, 0, 4);
+        if (!odd) multiply(1, 0, 4);
+        if (staged < total) stage();
+        ++at;
+        if (!BEST && live) pair_turn(w, p, q0, 64);
+        const int next = i + 1 < nmine ? block_at(i + 1) : block;
         if (live && tile < p.tiles) {
 #pragma unroll
             for (int cb = 0; cb < 4; ++cb) {
