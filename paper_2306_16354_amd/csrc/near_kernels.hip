@@ -818,13 +818,14 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
     }
 }
 
-// Beyond 128 columns: 256 queries x 256 candidates per workgroup, both streamed through LDS 64 columns at a time
-// (double buffered), a wavefront holding 64 x 128 of the products.  Consecutive items of an XCD are the segments of
+// Beyond 128 columns: 256 queries x 256 candidates per workgroup, both streamed through LDS 32 columns at a time
+// (four buffers, the pipeline of pairs_wide_kernel), a wavefront holding 64 x 128 of the products.  Consecutive items of an XCD are the segments of
 // neighbouring panels: its 32 workgroups share 8 panels of queries, which stay in its L2, and read the same candidates.
-constexpr int WIDE_STEPS = 4;
-constexpr int WIDE_HALF = 2 * WIDE_STEPS * FRAG_STEP;                   // two tiles' steps: 32 KiB
-constexpr int WIDE_BUF = 2 * WIDE_HALF;
-constexpr int WIDE_LDS = 2 * WIDE_BUF + 2 * 2048;                       // + half norms and colours of 256 candidates, twice
+// Bound by the products and what is not done under them (first fragments, the test of the values).  k-NN 3900 x 160 104 -> 91 us, 60 000 x 256 2.42 ->
+// 2.14 ms, 1-NN 5000 in 200 000 x 200 602 -> 492 us, 1000 in 100 000 x 256 171 -> 156 us against chunks of 64 columns in two buffers, waited
+// for all at once; the sample of 250k x 784 7.6 -> 6.1 ms.
+constexpr int WIDE_ROWS = 2048;                                         // half norms and colours of 256 candidates
+constexpr int WIDE_LDS = CHUNKS * CHUNK + 2 * WIDE_ROWS;
 
 template <int MODE, bool COLOURED>
 __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
@@ -855,80 +856,82 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
     mine.start(p, qtile, qblk, l32, sub, live);
 
     if (MODE == NEAR_NEAREST && !__syncthreads_or(!(mine.bound[0] != mine.bound[0] && mine.bound[1] != mine.bound[1]))) return;      // (as in near_sweep_kernel)
-    const int nchunks = p.steps / WIDE_STEPS;                           // (near_steps: whole chunks)
+    const int filled = (p.d + 15) / 16, nchunks = (filled + CHUNK_STEPS - 1) / CHUNK_STEPS;
+    const bool odd = (filled & 1) != 0;                                 // the last chunk has one step
     const int nmine = seg < npairs ? (npairs - seg + nseg - 1) / nseg : 0;
     auto listed = [&](int j) -> int { return near_tile_at<MODE>(p, j); };
     const int total = nmine * nchunks;
-    // positions of the queries whose pieces this wavefront brings in (wavefronts 0 to 3, one tile each for two)
-    int q_src[4] = {0, 0, 0, 0};
+    // a wavefront brings in one step of one tile of one side, four pieces of 1 KiB: of the queries, where they are
+    const int my_tile = (wave >> 1) & 1, my_st = wave & 1;
+    const unsigned char* q_src[4] = {p.qfrag, p.qfrag, p.qfrag, p.qfrag};
     if (wave < 4) {
         const int n_q = p.n_dev ? *p.n_dev : p.n_q;
 #pragma unroll
         for (int blk = 0; blk < 4; ++blk) {
-            const int t = qtile0 + (wave >> 1) < q_tile1 ? qtile0 + (wave >> 1) : qtile0;
+            const int t = qtile0 + my_tile < q_tile1 ? qtile0 + my_tile : qtile0;
             const int i = t * TILE + blk * 32 + l32;
-            q_src[blk] = !p.qpos ? i : i < n_q ? p.qpos[i] : 0;
+            const int at_q = !p.qpos ? i : i < n_q ? p.qpos[i] : 0;
+            q_src[blk] = p.qfrag + ((size_t)(at_q >> 7) * p.steps + my_st) * FRAG_STEP + ((at_q >> 5) & 3) * 1024 + (lhalf * 32 + (at_q & 31)) * 16;
         }
     }
-    // the loads of step `at` (pair, chunk): 64 KiB in pieces of 1 KiB, eight per wavefront, and the norms with chunk 0
-    auto stage = [&](int i, int chunk, int at) {
-        unsigned char* dst = near_smem + (at & 1) * WIDE_BUF;
-        const int j0 = 2 * (seg + i * nseg);
-#pragma unroll
-        for (int x = 0; x < 8; ++x) {
-            const int piece = wave * 8 + x;                             // [queries, candidates][tile][step][block]
-            const int side = piece >> 5, tile = (piece >> 4) & 1, st = (piece >> 2) & 3, blk = piece & 3;
-            if (side == 0) {
-                const int at_q = q_src[blk];
-                near_lds_gather(p.qfrag + ((size_t)(at_q >> 7) * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP + ((at_q >> 5) & 3) * 1024 + (lhalf * 32 + (at_q & 31)) * 16,
-                                dst + piece * 1024);
-            } else {
-                const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
-                near_lds_load(p.cfrag + (t * p.steps + chunk * WIDE_STEPS + st) * FRAG_STEP, blk * 1024, dst + piece * 1024, true);
-            }
-        }
-        if (chunk == 0 && wave < (COLOURED ? 8 : 4)) {
-            const int tile = (wave >> 1) & 1, half = wave & 1;
-            const size_t t = listed(j0 + tile < p.used ? j0 + tile : j0);
+    // the next chunk's loads, and with a pair's first chunk the norms and colours
+    int staged = 0, stage_i = 0, stage_chunk = 0, stage_t0 = 0, stage_t1 = 0;
+    auto stage_tiles = [&]() {
+        const int j0 = 2 * (seg + stage_i * nseg);
+        stage_t0 = listed(j0);
+        stage_t1 = listed(j0 + 1 < p.used ? j0 + 1 : j0);
+    };
+    if (nmine > 0) stage_tiles();
+    auto stage = [&]() {
+        unsigned char* dst = near_smem + (staged & (CHUNKS - 1)) * CHUNK + wave * FRAG_STEP;
+        if (stage_chunk == 0 && wave < (COLOURED ? 8 : 4)) {
+            const size_t t = my_tile ? stage_t1 : stage_t0;
             const void* rows = wave < 4 ? (const void*)(p.cnegh + t * TILE) : (const void*)(p.ccolour + t * TILE);
-            near_lds_load(rows, half * 256, near_smem + 2 * WIDE_BUF + (i & 1) * 2048 + wave * 256, false);
+            near_lds_load(rows, my_st * 256, near_smem + CHUNKS * CHUNK + (stage_i & 1) * WIDE_ROWS + wave * 256, false);
+        }
+        if (wave < 4) {
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk) near_lds_gather(q_src[blk] + (size_t)stage_chunk * (CHUNK_STEPS * FRAG_STEP), dst + blk * 1024);
+        } else {
+            const unsigned char* src = p.cfrag + ((size_t)(my_tile ? stage_t1 : stage_t0) * p.steps + stage_chunk * CHUNK_STEPS + my_st) * FRAG_STEP;
+#pragma unroll
+            for (int blk = 0; blk < 4; ++blk) near_lds_load(src, blk * 1024, dst + blk * 1024, true);
+        }
+        ++staged;
+        if (++stage_chunk == nchunks) {
+            stage_chunk = 0;
+            if (++stage_i < nmine) stage_tiles();
         }
     };
     const int per_part = MODE == NEAR_MAXIMA ? (nmine + p.parts - 1) / p.parts : 0;
     int part = 0, part_end = per_part;
-    if (total > 0) stage(0, 0, 0);
+    v16f acc[2][2][2];                                                  // [pair of candidate blocks][query block][candidate block]
+    v8h qf[2][2], cf[2][4];                                             // [step of the chunk]
+    auto read = [&](int at, int st) {
+        const unsigned char* qs = near_smem + (at & (CHUNKS - 1)) * CHUNK + (qg >> 1) * CHUNK_TILE + st * FRAG_STEP + qblk * 1024 + lane * 16;
+        const unsigned char* cs = near_smem + (at & (CHUNKS - 1)) * CHUNK + CHUNK_SIDE + cg * CHUNK_TILE + st * FRAG_STEP + lane * 16;
+#pragma unroll
+        for (int qb = 0; qb < 2; ++qb) qf[st][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb) cf[st][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
+        __builtin_amdgcn_sched_barrier(0);                              // (ahead of the multiplies that follow)
+    };
+    auto multiply = [&](int st, int from, int to) {
+#pragma unroll
+        for (int cb = 0; cb < 4; ++cb)
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+                if (cb >= from && cb < to)
+                    acc[cb >> 1][qb][cb & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st][cb], qf[st][qb], acc[cb >> 1][qb][cb & 1], 0, 0, 0);
+    };
+    for (int i = 0; i < CHUNKS - 1 && i < total; ++i) stage();
+    near_lds_ready();
     int at = 0;
     for (int i = 0; i < nmine; ++i) {
-        const unsigned char* nb = near_smem + 2 * WIDE_BUF + (i & 1) * 2048;
-        v16f acc[2][2][2];                                              // [pair of candidate blocks][query block][candidate block]
+        const unsigned char* nb = near_smem + CHUNKS * CHUNK + (i & 1) * WIDE_ROWS;
         const bool half_pair = 2 * (seg + i * nseg) + cg >= p.used;   // the second tile of the last pair may be missing
-        auto step = [&]() {
-            const unsigned char* qs = near_smem + (at & 1) * WIDE_BUF + (qg >> 1) * (WIDE_STEPS * FRAG_STEP) + qblk * 1024 + lane * 16;
-            const unsigned char* cs = near_smem + (at & 1) * WIDE_BUF + WIDE_HALF + cg * (WIDE_STEPS * FRAG_STEP) + lane * 16;
-            v8h qf[2][2], cf[2][4];
-#pragma unroll
-            for (int qb = 0; qb < 2; ++qb) qf[0][qb] = *reinterpret_cast<const v8h*>(qs + qb * 1024);
-#pragma unroll
-            for (int cb = 0; cb < 4; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(cs + cb * 1024);
-#pragma unroll
-            for (int st = 0; st < WIDE_STEPS; ++st) {
-                if (st + 1 < WIDE_STEPS) {
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb) qf[(st + 1) & 1][qb] = *reinterpret_cast<const v8h*>(qs + (st + 1) * FRAG_STEP + qb * 1024);
-#pragma unroll
-                    for (int cb = 0; cb < 4; ++cb) cf[(st + 1) & 1][cb] = *reinterpret_cast<const v8h*>(cs + (st + 1) * FRAG_STEP + cb * 1024);
-                    __builtin_amdgcn_sched_barrier(0);
-                }
-#pragma unroll
-                for (int cb = 0; cb < 4; ++cb)
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb)
-                        acc[cb >> 1][qb][cb & 1] =
-                            __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[st & 1][cb], qf[st & 1][qb], acc[cb >> 1][qb][cb & 1], 0, 0, 0);
-            }
-        };
-        near_lds_ready();
-        if (at + 1 < total) stage(nchunks > 1 ? i : i + 1, nchunks > 1 ? 1 : 0, at + 1);
+        // (the chunk, the norms and the colours have been there since the last barrier)
+        read(at, 0);
 #pragma unroll
         for (int cb = 0; cb < 4; ++cb) {
             v16f hv;
@@ -939,16 +942,23 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
             }
             acc[cb >> 1][0][cb & 1] = hv; acc[cb >> 1][1][cb & 1] = hv;
         }
-        step();
-        ++at;
+#pragma unroll 1
         for (int chunk = 1; chunk < nchunks; ++chunk, ++at) {
-            near_lds_ready();
-            if (at + 1 < total) {
-                const bool wrap = chunk + 1 == nchunks;
-                stage(wrap ? i + 1 : i, wrap ? 0 : chunk + 1, at + 1);
-            }
-            step();
+            near_chunk_ready(at + 2 < total);
+            read(at, 1);
+            multiply(0, 0, 2);
+            if (staged < total) stage();
+            multiply(0, 2, 4);
+            __builtin_amdgcn_sched_barrier(0);
+            read(at + 1, 0);
+            multiply(1, 0, 4);
         }
+        near_chunk_ready(at + 2 < total);
+        read(at, 1);
+        multiply(0, 0, 4);
+        if (!odd) multiply(1, 0, 4);
+        if (staged < total) stage();
+        ++at;
         const int j = 2 * (seg + i * nseg) + cg;
         const int pos0 = listed(j < p.used ? j : 0) * TILE;
         if (!half_pair) {

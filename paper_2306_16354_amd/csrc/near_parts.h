@@ -168,6 +168,30 @@ __device__ inline void near_lds_ready()
     asm volatile("" ::: "memory");
 }
 
+// Beyond 128 columns a step of the pipeline is a chunk of 32 columns of both sides, 32 KiB, in one of four buffers: the loads run three chunks ahead, and the
+// fragments of a chunk's first 16 columns are read while the last ones of the chunk before are multiplied, so that after a barrier there is
+// something to multiply at once.  250k x 784, the pass for the k-NN graph and that for the first connection round: 48.6 and 49.1 ms with chunks of 64
+// columns in two buffers, every fragment read after the chunk's barrier and all reads waited for at once; 44.8 and 46.4 so (1.09 PFLOP/s of
+// products made once, the matrix pipe 54 % busy at 1.92 GHz, to which it throttles).
+constexpr int CHUNK_STEPS = 2;
+constexpr int CHUNK_TILE = CHUNK_STEPS * FRAG_STEP;
+constexpr int CHUNK_SIDE = 2 * CHUNK_TILE;
+constexpr int CHUNK = 2 * CHUNK_SIDE;
+constexpr int CHUNKS = 4;                                               // buffers
+
+// In the pass over a chunk, before its second step is read.  The next chunk is in LDS once all of this wavefront's loads are done but the
+// four of the chunk after that (one_after: there is one), and every wavefront has read the chunk before this one, whose buffer is filled next:
+// what may still be on its way are the six fragments of this chunk's first step.
+__device__ inline void near_chunk_ready(bool one_after)
+{
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_sched_barrier(0);
+    if (one_after) __builtin_amdgcn_s_waitcnt(0x0674);     // vmcnt(4) lgkmcnt(6)
+    else __builtin_amdgcn_s_waitcnt(0x0670);
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+}
+
 // Where the rows of a matrix lie in a copy that is not in their order: row b * tiles + i, i < tiles, in tile i + near_shift(b) and there, in
 // the same 32 as place b, at place b - near_turn(tile), both round and round.  So a tile has one row of every stretch of `tiles` rows and is
 // an even sample of them, whatever order they are in.  The shift: where row i is of cluster i % n, and n and `tiles` have a divisor in

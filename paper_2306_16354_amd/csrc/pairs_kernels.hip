@@ -303,17 +303,6 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
 // Beyond 128 columns: 256 x 256 rows per meeting, both sides streamed through LDS, as near_wide_kernel; a block is two tiles.
 //   BEST = false  pairs within either row's limit go to that row's list
 //   BEST = true   rows of another colour: every row's smallest w = max(0, -u), with the place of the 16 rows about it
-//
-// A step of the pipeline is a chunk of 32 columns of both sides, 32 KiB, in one of four buffers: the loads run three chunks ahead, and the
-// fragments of a chunk's first 16 columns are read while the last ones of the chunk before are multiplied, so that after a barrier there is
-// something to multiply at once.  250k x 784, the pass for the k-NN graph and that for the first connection round: 48.6 and 49.1 ms with chunks of 64
-// columns in two buffers, every fragment read after the chunk's barrier and all reads waited for at once; 44.8 and 46.4 so (1.09 PFLOP/s of
-// products made once, the matrix pipe 54 % busy at 1.92 GHz, to which it throttles).
-constexpr int CHUNK_STEPS = 2;
-constexpr int CHUNK_TILE = CHUNK_STEPS * FRAG_STEP;
-constexpr int CHUNK_SIDE = 2 * CHUNK_TILE;
-constexpr int CHUNK = 2 * CHUNK_SIDE;
-constexpr int CHUNKS = 4;                                               // buffers
 constexpr int WIDE_ROWS = 3072;                                         // half norms, limits or smallest w, colours of 256 rows
 constexpr int WIDE_LDS = CHUNKS * CHUNK + 2 * WIDE_ROWS;
 
@@ -420,19 +409,9 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
             }
             acc[0][cb] = hv; acc[1][cb] = hv;
         }
-        // The next chunk is in LDS once all loads are done but the four of the chunk after that, and every wavefront has read the chunk before
-        // this one, whose buffer is filled next: what may still be on its way are the six fragments of this chunk's first step.
-        auto ready = [&]() {
-            asm volatile("" ::: "memory");
-            __builtin_amdgcn_sched_barrier(0);
-            if (at + 2 < total) __builtin_amdgcn_s_waitcnt(0x0674);     // vmcnt(4) lgkmcnt(6)
-            else __builtin_amdgcn_s_waitcnt(0x0670);
-            __builtin_amdgcn_s_barrier();
-            asm volatile("" ::: "memory");
-        };
 #pragma unroll 1
         for (int chunk = 1; chunk < nchunks; ++chunk, ++at) {
-            ready();
+            near_chunk_ready(at + 2 < total);
             read(at, 1);
             multiply(0, 0, 2);
             if (staged < total) stage();
@@ -441,7 +420,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
             read(at + 1, 0);
             multiply(1, 0, 4);
         }
-        ready();
+        near_chunk_ready(at + 2 < total);
         read(at, 1);
         multiply(0, 0, 4);
         if (!odd) multiply(1, 0, 4);

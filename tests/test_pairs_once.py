@@ -39,6 +39,25 @@ def test_lists(lib, N, d, k):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
+# 9 to 13 steps of 16 columns: chunks of two with one step or two in the last, places of rows with up to three empty steps; both orders of
+# every pair (fewer rows) and one, an odd number of tiles; 1-NN, of few queries with several segments
+@pytest.mark.parametrize("d", [129, 145, 161, 177, 193, 208])
+def test_chunks_of_columns(lib, d):
+    print(f"chunks of columns d={d}", flush=True)
+    for N in (2500, 4700):
+        assert lib.probe_knn_products(N, d, 9) == (0.5 if N > 4000 else 1.0)
+        X = blobs(N, d, d)
+        want, got = lib.knn_graph(X, 9, fp32_filter=True), lib.knn_graph(X, 9)
+        torch.cuda.synchronize()
+        assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+        # (a float32 sum of d squares is off by (d + 2) 2^-24 of its value at most, 1.3e-5)
+        best = torch.cdist(X[:200].double().cpu(), X[200:].double().cpu()).square().min(1).values
+        assert torch.allclose(lib.fused_1nn(X[:200], X[200:])[1].double().cpu(), best, rtol=2e-5, atol=0)
+        colour = (torch.arange(N, device="cuda") < 200).to(torch.int32)
+        rows = torch.arange(200, dtype=torch.int32, device="cuda")
+        assert torch.allclose(lib.cross_1nn(X, colour, rows=rows)[1].double().cpu(), best, rtol=2e-5, atol=0)
+
+
 # values beyond float16 on either side of a pair, rows with more ties than a list holds, one row that no other is near, rows in the
 # order of their clusters
 @pytest.mark.parametrize("kind", ["beyond_float16", "ties", "far_row", "sorted", "not_finite"])
