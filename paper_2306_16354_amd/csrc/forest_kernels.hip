@@ -397,11 +397,17 @@ __global__ void __launch_bounds__(64) k_publish(const int32_t* __restrict__ coun
 // 5 rounds 0.33 ms as separate launches).  Colours, hooks and the per-component minima live in LDS; an edge's end
 // points fit one word there.  Same rules, same edges as the separate kernels.
 //   stage 0: first launch;  1: after a round's queries were applied (k_apply_queries): continue at the selection.
+// One workgroup has one CU's loads in flight, so the walks along the lists are bound by their latency: a thread has I vertices, tid, tid + 1024, ..,
+// whose places in their lists and candidates are registers, and takes four entries of four of them at a time.  With an entry of a vertex
+// at a time and candidates in memory the three launches of 10 000 rows, k = 20, took 308 us, of 4096 rows, k = 16, 109; 214 and 82 so (keeping candidates that still lead out: no faster).
+typedef int v4i_word __attribute__((ext_vector_type(4), aligned(4)));        // (loads of 16 bytes need the alignment of a word only)
+template <int I>
 __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
 {
     extern __shared__ __align__(16) unsigned char small_smem[];
     __shared__ int s_edges, s_queries, s_bad;
-    const int N = f.N, tid = threadIdx.x;
+    const int N = f.N;
+    int tid = threadIdx.x;
     unsigned int* bw = reinterpret_cast<unsigned int*>(small_smem);
     unsigned int* be = bw + N;
     unsigned short* col = reinterpret_cast<unsigned short*>(be + N);
@@ -411,62 +417,119 @@ __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
         s_edges = stage == 0 ? 0 : f.counters[1];
         s_bad = 0;
     }
-    for (int v = tid; v < N; v += 1024) {
+    int ptr[I], cand_u[I];
+    float cand_w[I];
+#pragma unroll
+    for (int i = 0; i < I; ++i) {
+        const int v = tid + i * 1024;
+        ptr[i] = 0; cand_u[i] = -1; cand_w[i] = 0.f;
+        if (v >= N) continue;
         if (stage == 0) {
             col[v] = (unsigned short)v;
-            f.ptr[v] = 0; f.ext_idx[v] = -1; f.ext_dist[v] = 0.f; f.ext_low[v] = __builtin_inff();
+            f.ext_idx[v] = -1; f.ext_dist[v] = 0.f; f.ext_low[v] = __builtin_inff();
         } else {
             const int c = f.colour[v];
             col[v] = (unsigned short)(in_range(c, N) ? c : 0);
             bw[v] = f.best_w[v];
+            ptr[i] = f.ptr[v]; cand_u[i] = f.cand_u[v]; cand_w[i] = f.cand_w[v];
         }
     }
     __syncthreads();
     int rounds = stage == 0 ? 0 : f.counters[6];
     bool selected = stage == 1;               // the candidates of this round are complete
     for (int guard = 0; guard < 64; ++guard) {
+        asm volatile("" : "+v"(tid));             // (every round works its addresses out: kept, they push the candidates out of the registers)
         if (!selected) {
             if (tid == 0) s_queries = 0;
-            for (int v = tid; v < N; v += 1024) bw[v] = INF_BITS;
+#pragma unroll
+            for (int i = 0; i < I; ++i)
+                if (tid + i * 1024 < N) bw[tid + i * 1024] = INF_BITS;
             __syncthreads();
             ++rounds;
-            for (int v = tid; v < N; v += 1024) {
-                const unsigned int c = col[v];
-                int found = -1;
-                float w = 0.f;
-                int u = -1;
-                for (int e = f.ptr[v]; e < f.k; ++e) {
-                    u = f.nbr_idx[(size_t)v * f.k + e];
-                    if (!in_range(u, N)) { report(f, 1); continue; }
-                    if (col[u] != c) { found = e; break; }
+#pragma unroll
+            for (int i0 = 0; i0 < I; i0 += 4) {
+                // every vertex's first foreign entry from ptr on (f.k: there is none)
+                unsigned int c[4];
+                bool more[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = tid + (i0 + j) * 1024;
+                    c[j] = v < N ? col[v] : 0u;
+                    more[j] = v < N && ptr[i0 + j] < f.k;
+                    if (v < N) cand_u[i0 + j] = -1;
                 }
-                bool exact = true;
-                float reach = INFINITY;              // an edge that need not be v's lightest (see k_scan_lists)
-                if (found >= 0) w = f.nbr_dist[(size_t)v * f.k + found];
-                else {
-                    const int eu = f.ext_idx[v];
-                    const float ed = f.ext_dist[v], el = f.ext_low[v];
-                    const bool edge = eu >= 0 && eu < N && col[eu] != c;
-                    if (edge && !(el < INFINITY)) { w = ed; u = eu; }
-                    else {
-                        w = fmaxf(f.nbr_dist[(size_t)v * f.k + f.k - 1], fminf(ed, el));
-                        if (edge) reach = ed;
-                        u = -1;
-                        exact = false;
+                while (more[0] || more[1] || more[2] || more[3]) {
+                    int u[4][4];
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (!more[j]) continue;
+                        // (the last quad of a list starts where it ends with the list)
+                        const int p = ptr[i0 + j], e = p + 4 <= f.k ? p : f.k - 4;
+                        const unsigned int list = (unsigned int)((tid + (i0 + j) * 1024) * f.k);
+                        if (f.k >= 4) {
+                            const v4i_word q = *reinterpret_cast<const v4i_word*>(f.nbr_idx + (list + (unsigned int)e));
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) u[j][t] = q[t];
+                        } else {
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) u[j][t] = e + t >= 0 ? f.nbr_idx[list + (unsigned int)(e + t)] : -1;
+                        }
+                    }
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        if (!more[j]) continue;
+                        const int p = ptr[i0 + j], e = p + 4 <= f.k ? p : f.k - 4;
+                        int at = f.k;
+#pragma unroll
+                        for (int t = 3; t >= 0; --t) {
+                            if (e + t < p) continue;
+                            if (!in_range(u[j][t], N)) { report(f, 1); continue; }
+                            if (col[u[j][t]] != c[j]) { at = e + t; cand_u[i0 + j] = u[j][t]; }
+                        }
+                        more[j] = at == f.k && e + 4 < f.k;
+                        ptr[i0 + j] = more[j] ? e + 4 : at;
                     }
                 }
-                f.ptr[v] = found >= 0 ? found : f.k;
-                f.cand_w[v] = w;
-                f.cand_u[v] = u;
-                if (exact) reach = w;
-                if (reach < INFINITY) atomicMin(&bw[c], __float_as_uint(reach));
+                float w[4];
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = tid + (i0 + j) * 1024;
+                    w[j] = 0.f;
+                    if (v < N) w[j] = f.nbr_dist[(unsigned int)(v * f.k) + (unsigned int)(ptr[i0 + j] < f.k ? ptr[i0 + j] : f.k - 1)];
+                }
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int v = tid + (i0 + j) * 1024;
+                    if (v >= N) continue;
+                    float reach = INFINITY;              // an edge that need not be v's lightest (see k_scan_lists)
+                    if (cand_u[i0 + j] >= 0) reach = w[j];
+                    else if (stage == 1) {               // (nothing has been asked for before)
+                        const int eu = f.ext_idx[v];
+                        const float ed = f.ext_dist[v], el = f.ext_low[v];
+                        const bool edge = eu >= 0 && eu < N && col[eu] != c[j];
+                        if (edge) reach = ed;
+                        if (edge && !(el < INFINITY)) { w[j] = ed; cand_u[i0 + j] = eu; }
+                        else w[j] = fmaxf(w[j], fminf(ed, el));
+                    } else w[j] = fmaxf(w[j], 0.f);
+                    cand_w[i0 + j] = w[j];
+                    if (reach < INFINITY) atomicMin(&bw[c[j]], __float_as_uint(reach));
+                }
             }
             __syncthreads();
-            for (int v = tid; v < N; v += 1024)
-                if (f.cand_u[v] < 0 && __float_as_uint(f.cand_w[v]) <= bw[col[v]]) f.qlist[atomicAdd(&s_queries, 1)] = v;
+#pragma unroll
+            for (int i = 0; i < I; ++i) {
+                const int v = tid + i * 1024;
+                if (v < N && cand_u[i] < 0 && __float_as_uint(cand_w[i]) <= bw[col[v]]) f.qlist[atomicAdd(&s_queries, 1)] = v;
+            }
             __syncthreads();
             if (s_queries > 0) {
-                for (int v = tid; v < N; v += 1024) { f.colour[v] = col[v]; f.best_w[v] = bw[v]; }
+#pragma unroll
+                for (int i = 0; i < I; ++i) {
+                    const int v = tid + i * 1024;
+                    if (v >= N) continue;
+                    f.colour[v] = col[v]; f.best_w[v] = bw[v];
+                    f.ptr[v] = ptr[i]; f.cand_u[v] = cand_u[i]; f.cand_w[v] = cand_w[i];
+                }
                 if (tid == 0) { f.counters[0] = s_queries; f.counters[1] = s_edges; f.counters[6] = rounds; }
                 return;
             }
@@ -475,12 +538,13 @@ __global__ void __launch_bounds__(1024) k_forest_small(ForestState f, int stage)
         // the component's edge among those of its lightest weight
         for (int v = tid; v < N; v += 1024) be[v] = ~0u;
         __syncthreads();
-        for (int v = tid; v < N; v += 1024) {
-            const int u = f.cand_u[v];
-            if (u < 0) continue;
+#pragma unroll
+        for (int i = 0; i < I; ++i) {
+            const int v = tid + i * 1024, u = cand_u[i];
+            if (v >= N || u < 0) continue;
             const unsigned int c = col[v];
             if (u >= N) { report(f, 7); continue; }
-            if (__float_as_uint(f.cand_w[v]) != bw[c]) continue;
+            if (__float_as_uint(cand_w[i]) != bw[c]) continue;
             const unsigned int lo = v < u ? v : u, hi = v < u ? u : v;
             atomicMin(&be[c], (lo << 16) | hi);
         }
@@ -613,10 +677,16 @@ hipError_t forest_publish(const ForestState& f, int32_t* host, int32_t seq, hipS
 hipError_t forest_small(const ForestState& f, bool first, hipStream_t s)
 {
     const size_t lds = (size_t)f.N * 12;
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&k_forest_small), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_forest_small, dim3(1), dim3(1024), lds, s, f, first ? 0 : 1);
-    return hipGetLastError();
+    auto run = [&](auto kernel) -> hipError_t {
+        hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+        if (e != hipSuccess) return e;
+        hipLaunchKernelGGL(kernel, dim3(1), dim3(1024), lds, s, f, first ? 0 : 1);
+        return hipGetLastError();
+    };
+    if (f.N <= 4 * 1024) return run(&k_forest_small<4>);
+    if (f.N <= 8 * 1024) return run(&k_forest_small<8>);
+    static_assert(FOREST_SMALL_MAX <= 12 * 1024, "");
+    return run(&k_forest_small<12>);
 }
 
 // ------------------------------------------------------------------------------- edge sort

@@ -38,6 +38,24 @@ def test_forest_of_a_path(lib, N, rising):
     assert np.array_equal(got["mst_dst"].cpu().numpy(), by_weight + 1)
 
 
+# forests whose rounds run in one workgroup: one to twelve vertices a thread, lists shorter than a load of four entries and of every
+# remainder, clusters smaller than the lists (walked to their end, several rounds of queries) and larger, rows at equal distances
+@pytest.mark.parametrize("N,k", [(2, 1), (5, 3), (600, 1), (1023, 2), (1025, 3), (4096, 4), (4097, 5), (8192, 7), (8193, 18), (12_288, 6), (12_289, 6)])
+@pytest.mark.parametrize("rows_per_cluster", [3, 300])
+def test_forest_of_points(lib, N, k, rows_per_cluster):
+    print(f"forest of points N={N} k={k} clusters of {rows_per_cluster}", flush=True)
+    rng = np.random.default_rng(N + k)
+    centres = rng.integers(-50, 50, size=(max(1, N // rows_per_cluster), 3))
+    X = (centres[rng.integers(0, len(centres), N)] + rng.integers(0, 8, size=(N, 3)) / 16).astype(np.float32)
+    out = lib.slhc(torch.from_numpy(X).cuda(), k)
+    torch.cuda.synchronize()
+    ref = oracle.slhc(X)
+    # (distances of such points are exact in float32, so the weights are)
+    assert np.array_equal(np.sort(out["mst_w"].cpu().numpy()).astype(np.float64), np.sort(np.asarray(ref["heights"], dtype=np.float64)))
+    lo, hi = out["mst_src"].cpu().numpy(), out["mst_dst"].cpu().numpy()
+    assert np.array_equal(((X[lo].astype(np.float64) - X[hi]) ** 2).sum(1), out["mst_w"].cpu().numpy())
+
+
 def cuts(N):
     return sorted({k for k in (0, 1, 2, 7, 8, 9, 63, 64, 65, 512, 4096, N // 2, N - 2, N - 1) if 0 <= k < N})
 
