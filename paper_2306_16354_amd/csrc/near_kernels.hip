@@ -122,8 +122,9 @@ __device__ inline float near_median64(float x, bool valid, int lane)
 
 // shift[c] = the median of the runs' means (a single far row cannot drag it; a value beyond 2^50 is replaced by 0), and
 // the scale: the power of two that brings the median run's largest value near 2^7.  float16 then has room for rows
-// 500 times larger and keeps its full relative precision for values 2 million times smaller.
-__global__ void __launch_bounds__(256) near_shift_kernel(const float* __restrict__ partial, const float* __restrict__ run_max, int d,
+// 500 times larger and keeps its full relative precision for values 2 million times smaller.  The runs' means of column 0 become the words
+// in which near_make's workgroups meet: 0.
+__global__ void __launch_bounds__(256) near_shift_kernel(float* __restrict__ partial, const float* __restrict__ run_max, int d,
                                                          float* __restrict__ shift, NearScale* __restrict__ sc)
 {
     const int lane = threadIdx.x & 63;
@@ -132,6 +133,7 @@ __global__ void __launch_bounds__(256) near_shift_kernel(const float* __restrict
         const float x = partial[(size_t)lane * d + c];
         const float m = near_median64(x, fabsf(x) < INF, lane);
         if (lane == 0) shift[c] = fabsf(m) <= 1.125899906842624e15f ? m : 0.f;
+        if (c == 0) partial[(size_t)lane * d] = 0.f;
     } else if (c == d) {
         float x = -1.f;
         const int parts = (d + 255) / 256;
@@ -163,6 +165,7 @@ struct NearMake {
     const float* X; const int32_t* rows; const int32_t* colour; const float* shift; NearScale* sc;
     const int32_t* shift_row;            // optional: tile t is taken relative to row shift_row[t] of `shift` (-1: is left empty)
     unsigned char* frag; float *negh, *negh_best; int32_t* out_colour; float* hn; unsigned int* nonfinite;
+    unsigned int* eps_of;                // optional: 64 words, d apart, none above what sc->eps_bits will be
     int n_src, n, d, tiles, steps, in_order; float h_of_n, hn_scale, absent;
     const int32_t* n_dev;
     int32_t* count; unsigned long long* best_at;
@@ -170,7 +173,10 @@ struct NearMake {
 };
 
 // One workgroup per block of 32 rows of a tile; LPR lanes share a row, eight columns each at a time.  The pieces go
-// through LDS so that they leave in whole lines.  Bound by reading X once and writing half of it.
+// through LDS so that they leave in whole lines.  Bound by reading X once and writing half of it (1M x 128: 180 us, 4.3 TB/s; 215 with the shift
+// read a word at a time), and below a million rows by the workgroups' reports at its end: 100 000 x 64 29 us, 17 with the words in 64 lines, 14
+// without; 100 000 x 128 28 and 22.  (The 64 words in one line: 26 us, and 40 if they are read first.  A thousand workgroups that pass over the blocks:
+// 23, but 240 us for 1M x 128.)
 constexpr int MAKE_STEPS = 8;
 template <int LPR, bool VEC4>
 __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
@@ -208,7 +214,17 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
             const int col = 16 * s0 + 8 * oct;
             float m[8];
 #pragma unroll
-            for (int e = 0; e < 8; ++e) m[e] = col + e < p.d ? shift[col + e] : 0.f;
+            for (int e = 0; e < 8; ++e) m[e] = 0.f;
+            if (VEC4) {
+#pragma unroll
+                for (int e = 0; e < 8; e += 4)
+                    if (col + e + 4 <= p.d) {
+                        const v4f a = *reinterpret_cast<const v4f*>(shift + col + e);
+                        m[e] = a[0]; m[e + 1] = a[1]; m[e + 2] = a[2]; m[e + 3] = a[3];
+                    }
+            } else
+#pragma unroll
+                for (int e = 0; e < 8; ++e) m[e] = col + e < p.d ? shift[col + e] : 0.f;
 #pragma unroll
             for (int i = 0; i < PASSES; ++i) {
                 const int r = sub + i * ROWS;
@@ -292,8 +308,10 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     // (2 units in the last place for the roundings of the two sums and of the difference from the shift)
     if (tid == 0 && eps_max != 0u) {
         const unsigned int mine_bits = __float_as_uint(__uint_as_float(eps_max) * (1.f + 1e-4f));
-        // most workgroups find the word already there and leave it alone
-        if (__hip_atomic_load(&p.sc->eps_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mine_bits) atomicMax(&p.sc->eps_bits, mine_bits);
+        // Most workgroups find the word already there and leave it alone; but the first two thousand of a launch end together and would
+        // queue for it (9 ns each), so they meet at 64 words in lines of their own, and a few of each 32 go on.
+        const bool first = !p.eps_of || atomicMax(p.eps_of + (size_t)(blockIdx.x & 63) * p.d, mine_bits) < mine_bits;
+        if (first && __hip_atomic_load(&p.sc->eps_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mine_bits) atomicMax(&p.sc->eps_bits, mine_bits);
     }
 }
 
@@ -307,6 +325,7 @@ hipError_t near_make(const float* X, int n_src, int d, const int32_t* rows, int 
     p.frag = out.frag; p.negh = out.negh; p.out_colour = out.colour; p.hn = hn; p.nonfinite = nonfinite;
     p.n_src = n_src; p.n = n; p.d = d; p.tiles = out.tiles; p.steps = near_steps(d); p.h_of_n = 0.5f - 0.5f * near_nu(p.steps) - near_e(p.steps);
     p.shift_row = shift_row;
+    p.eps_of = reinterpret_cast<unsigned int*>(b.partial);
     p.count = out.count; p.best_at = out.best_at;
     p.negh_best = out.negh_best; p.in_order = out.in_order; p.n_dev = n_dev;
     p.absent = out.finite_padding ? -1e38f : -INF;
@@ -2141,6 +2160,7 @@ hipError_t near_make_ordered(const float* X, int n_src, int d, const NearOrder& 
     NearBuffers bl = b;
     bl.scale = o.local_scale;
     bl.shift = const_cast<float*>(tile_c);
+    bl.partial = nullptr;                            // (its words belong to the other copies' scale)
     return near_make(X, n_src, d, o.perm, o.rows, nullptr, bl, o.local, nullptr, nullptr, s, false, nullptr, tile_first);
 }
 
