@@ -2168,12 +2168,14 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
         }
         const int rc = check_shape(N, d, k, true);
         if (rc != SLHC_OK) return rc;
-        // (the list kernels see a panel or two at most: the rows as they are)
-        const bool direct = !(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true);
-        const int32_t dw = direct ? d : working_columns(N, d);
-        const size_t head = direct ? 0 : padded_copy_bytes(N, d);
+        int32_t dw = working_columns(N, d);
+        size_t head = padded_copy_bytes(N, d);
         const size_t need = head + SlhcWs(nullptr, N, dw, k, true, workspace_bytes > head ? workspace_bytes - head : 0).bytes;
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
+        // Where every pair is evaluated the list kernels see a panel or two at most: the rows as they are.  (Without an engine in the workspace
+        // they see all of them.)
+        if (!(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true) &&
+            SlhcWs(nullptr, N, d, k, true, workspace_bytes).knn->near.ok) { dw = d; head = 0; }
         if (dw != d) {
             const int rp = pad_columns(X, N, d, dw, static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
             if (rp != SLHC_OK) return rp;

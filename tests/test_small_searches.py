@@ -93,6 +93,19 @@ def test_searches_that_multiply_nothing(N, d, k, products):
     assert lib.slhc_probe_knn_products(N, d, k, ctypes.byref(out)) == 0 and out.value == products
 
 
+# a workspace that is too small is one whichever search would run in it (refused before anything is launched)
+@pytest.mark.parametrize("N,d,k", [(600, 4, 3), (1500, 50, 8), (2048, 32, 8), (4096, 15, 16), (1690, 127, 16)])
+def test_small_trees_ask_for_no_less(N, d, k):
+    import paper_2306_16354_amd as slhc
+    lib = slhc.load_library()
+
+    def refusal(flags):
+        some = ctypes.c_void_p(256)
+        rc = lib.slhc_slhc_opt(some, N, d, k, some, some, some, some, some, some, None, some, 256, None, flags)
+        return rc, lib.slhc_last_error().decode()
+    assert refusal(0)[0] == 3 and refusal(0) == refusal(slhc.binding.SLHC_FP32_FILTER)
+
+
 # rounds of connecting components: clusters too far apart for the lists, several rounds, copies in other components, few and many queries; rows that
 # are read as they are (16 columns) and with columns of zeros; a forest of one workgroup and of many
 @pytest.mark.gpu
