@@ -1239,8 +1239,11 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         if (ev_order) { HIP_TRY(hipEventRecord(ev_order->a, stream)); HIP_TRY(hipEventRecord(ev_order->b, stream)); }
         ws.near_done = true;
         ws.near_ready = !slhc::direct_knn_wanted(N, d, k, pruned_out != nullptr);
+        // a word per row for the counts: the split copy's half norms, which nobody reads; where every pair is evaluated the rows may have a
+        // width without such a copy, and `hn` is not made
+        float* counts = !ev_sweep ? nullptr : ws.near_ready ? ws.hn_split : ws.hn;
         return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream, pruned_out != nullptr,
-                            ev_sweep ? reinterpret_cast<int32_t*>(ws.hn_split) : nullptr, ev_norm, ev_sweep);
+                            reinterpret_cast<int32_t*>(counts), ev_norm, ev_sweep);
     }
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(ws.counters), 64);
     HIP_TRY(hipGetLastError());

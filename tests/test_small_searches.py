@@ -127,3 +127,13 @@ def test_trees(lib, kind, N, d, k):
     torch.cuda.synchronize()
     for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
         assert torch.equal(want[key], got[key]), key
+
+
+# pairs evaluated exactly, as they are reported: all of them, of rows with and without a copy in split halves; beyond the last such search
+# the engine's few
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d,all_pairs", [(3, 1, True), (700, 16, True), (900, 50, True), (1100, 64, True), (600, 127, True), (9000, 50, False), (9000, 64, False)])
+def test_evaluated_pairs_are_counted(lib, N, d, all_pairs):
+    print(f"evaluated pairs N={N} d={d}", flush=True)
+    count = lib.slhc(rows(N, d, N), 2, prune=False)["stats"]["knn_filter_survivors"]
+    assert count == N * (N - 1) if all_pairs else 2 * N <= count < 100 * N
