@@ -22,6 +22,7 @@ namespace slhc {
 typedef float v4f __attribute__((ext_vector_type(4)));
 typedef float v4f_word __attribute__((ext_vector_type(4), aligned(4)));      // global loads of 16 bytes need the alignment of a word only
 constexpr float INF = __builtin_inff();
+constexpr float NONE = __builtin_nanf("");
 constexpr int WAVES = 4;                   // per workgroup
 constexpr int SLAB = 64;                   // features of a row in LDS at a time
 constexpr int QUADS = SLAB / 4;
@@ -355,8 +356,9 @@ __device__ inline __attribute__((always_inline)) void block_passes(int nc, F&& p
     for (; nc - base > 0; base += BLOCK) pass(std::integral_constant<int, 1>{}, base);
 }
 
-// The k nearest rows of every row.  All distances of a workgroup's QB rows are kept in LDS; then a wavefront per row takes what is not beyond the k-th
-// smallest of its lanes' minima, of which k at least are, and ranks that.
+// The k nearest rows of every row.  All distances of a workgroup's QB rows are kept in LDS, NaN where there is no row; then a wavefront per row takes what
+// is not beyond the k-th smallest of its lanes' minima, of which k at least are, and ranks that.  Rows so far away that the distance is no
+// float32 are neighbours all the same, at +inf, behind all others.
 // Time (k = 12, us; engine, this): 500 x 4 42, 9; 1000 x 16 42, 9; 2048 x 32 48, 20; 2048 x 32, k = 64, 74, 23; 1500 x 128 60, 38; 3198 x 16 55, 39.
 struct DirectKnn {
     const float* X; int n, d, k, rows; bool vec4;         // rows: per workgroup, KNN_ROWS at most
@@ -403,8 +405,7 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
                     const int cand = base + c * BLOCK + tid;
-                    if (cand < p.n && v[c] < INF && direct_bad_row(p.X, cand, p.d)) v[c] = INF;
-                    v[c] = v[c] < INF ? v[c] : INF;                          // (NaN: +inf)
+                    if (cand < p.n && direct_bad_row(p.X, cand, p.d)) v[c] = NONE;
                 }
             }
 #pragma unroll
@@ -416,18 +417,18 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
     const int row = q0 + wave;
     if (wave >= p.rows || row >= p.n) return;
     float* mine = dist + wave * pitch;
-    if (lane == 0) mine[row] = INF;                                           // itself, and no rows
-    if (p.n + lane < n64 * 64) mine[p.n + lane] = INF;
+    if (lane == 0) mine[row] = NONE;                                          // itself, and no rows
+    if (p.n + lane < n64 * 64) mine[p.n + lane] = NONE;
     __builtin_amdgcn_wave_barrier();
     unsigned long long* keep = reinterpret_cast<unsigned long long*>(direct_smem) + wave * KNN_KEEP;      // (the candidates' rows are used up)
     const bool fine = norms[wave] < INF;
     if (p.nonfinite && !fine && lane == 0) atomicOr(p.nonfinite, 1u);
-    // the row's distances, 16 of a lane's at a time: what(first of them, values), +inf from n64 on
+    // the row's distances, 16 of a lane's at a time: what(first of them, values), NaN from n64 on
     auto all = [&](auto&& what) {
         for (int i0 = 0; i0 < n64; i0 += 16) {
             float v[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = i0 + i < n64 ? mine[(i0 + i) * 64 + lane] : INF;
+            for (int i = 0; i < 16; ++i) v[i] = i0 + i < n64 ? mine[(i0 + i) * 64 + lane] : NONE;
             what(i0, v);
         }
     };
@@ -514,6 +515,16 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
                 return in;
             });
         }
+        if (kept < p.k)
+            all([&](int i0, const float (&v)[16]) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const unsigned long long m = __ballot(v[i] == INF);
+                    const int at = kept + prefix(m), n = __popcll(m);
+                    if (v[i] == INF && at < p.k) keep[at] = ((unsigned long long)__float_as_uint(INF) << 32) | (unsigned int)((i0 + i) * 64 + lane);
+                    kept = kept + n < p.k ? kept + n : p.k;
+                }
+            });
         __builtin_amdgcn_wave_barrier();
     }
     // ranks by (distance, row)

@@ -21,13 +21,18 @@ def rows(N, d, seed, spread=8.0):
     return centres[torch.randint(len(centres), (N,), generator=g, device="cuda")] + torch.randn((N, d), generator=g, device="cuda")
 
 
-def same_lists(lib, X, k):
+def same_lists(lib, X, k, bad=()):
+    """bad: rows that are not finite, which have no list and are in none."""
     want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
     static = (torch.full_like(got[0], -7), torch.full_like(got[1], -7.0))
     lib.knn_graph_static(X, k, static)
     torch.cuda.synchronize()
-    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
-    assert torch.equal(want[0], static[0]) and torch.equal(want[1], static[1])
+    bad = torch.tensor(list(bad), dtype=torch.int64, device="cuda")
+    fine = torch.ones(len(X), dtype=torch.bool, device="cuda")
+    fine[bad] = False
+    for idx, dist in (got, static):
+        assert torch.equal(want[0][fine], idx[fine]) and torch.equal(want[1][fine], dist[fine])
+        assert (idx[bad] == -1).all() and torch.isinf(dist[bad]).all() and not torch.isin(idx, bad.to(torch.int32)).any()
 
 
 # every number of quads the kernel is made for, whole and in part, less than one quad; parts of a wavefront, of 512 rows and of the 1, 2 and 4
@@ -48,7 +53,7 @@ def test_lists(lib, N, d, k):
 # copies of a point by the tens and hundreds (as many as a row keeps and more, all rows equal), rows that are not finite or close to it, rows that do
 # not begin on 16 bytes
 @pytest.mark.gpu
-@pytest.mark.parametrize("kind", ["copies_30", "copies_130", "copies_600", "one_point", "lattice", "far_rows", "large", "not_finite", "odd_address"])
+@pytest.mark.parametrize("kind", ["copies_30", "copies_130", "copies_600", "one_point", "lattice", "far_rows", "large", "not_finite", "out_of_reach", "odd_address"])
 @pytest.mark.parametrize("N,d,k", [(900, 6, 20), (1700, 32, 8), (1300, 61, 64)])
 def test_lists_of_unlike_rows(lib, kind, N, d, k):
     print(f"small k-NN, {kind}, N={N} d={d} k={k}", flush=True)
@@ -69,19 +74,18 @@ def test_lists_of_unlike_rows(lib, kind, N, d, k):
         X[N // 3] = float("nan")
         X[N // 5, 2] = float("inf")
         X[N // 7] = 3e19
+    elif kind == "out_of_reach":
+        X *= 1e14
+        X[:, 0] += 1.5e19
+        X[:40:8, 0] -= 3e19                      # (five rows, each within reach of four others and of row 7: fewer than k)
+        X[7] = 0.0
+        X[9], X[N - 2] = float("nan"), 3e19
     elif kind == "odd_address":
         X = torch.cat([X.new_zeros(1), X.reshape(-1)])[1:].reshape(N, d)
         assert X.data_ptr() % 16 == 4
-    if kind != "not_finite":
-        same_lists(lib, X, k)
-        return
-    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
-    torch.cuda.synchronize()
-    bad = torch.tensor([N // 3, N // 5, N // 7], device="cuda")
-    fine = torch.ones(N, dtype=torch.bool, device="cuda")
-    fine[bad] = False
-    assert torch.equal(want[0][fine], got[0][fine]) and torch.equal(want[1][fine], got[1][fine])
-    assert (got[0][bad] == -1).all() and torch.isinf(got[1][bad]).all() and not torch.isin(got[0], bad.to(torch.int32)).any()
+    bad = {"not_finite": [N // 3, N // 5, N // 7], "out_of_reach": [9, N - 2]}.get(kind, [])
+    same_lists(lib, X, k, bad)
+    assert kind != "out_of_reach" or torch.isinf(lib.knn_graph(X, k)[1][:40:8, 5:]).all()
 
 
 # the same where the pairs can be counted on the host: which searches go this way does not depend on a GPU
@@ -137,3 +141,19 @@ def test_evaluated_pairs_are_counted(lib, N, d, all_pairs):
     print(f"evaluated pairs N={N} d={d}", flush=True)
     count = lib.slhc(rows(N, d, N), 2, prune=False)["stats"]["knn_filter_survivors"]
     assert count == N * (N - 1) if all_pairs else 2 * N <= count < 100 * N
+
+
+# rows so far from each other that the distance is no float32, and one row between them that both reach (lists of one such distance, of a quad and a part of
+# one, of all rows but the far one)
+@pytest.mark.gpu
+@pytest.mark.parametrize("near,far,k", [(30, 1, 31), (30, 1, 8), (30, 1, 30), (29, 2, 3), (61, 2, 63), (4, 1, 5), (1, 1, 1)])
+def test_trees_of_rows_out_of_reach(lib, near, far, k):
+    print(f"rows out of reach, {near} + 1 + {far}, k={k}", flush=True)
+    X = 1e14 * torch.randn((near + 1 + far, 4), generator=torch.Generator(device="cuda").manual_seed(1), device="cuda")
+    X[:near, 0] += 1.5e19
+    X[near + 1:, 0] -= 1.5e19
+    want, got = lib.slhc(X, k, prune=False, fp32_filter=True), lib.slhc(X, k, prune=False)
+    torch.cuda.synchronize()
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
+    assert torch.isfinite(got["mst_w"]).all()
