@@ -299,10 +299,12 @@ struct BlockStream {
         }
     }
 };
-// The queries qs [queries][NQ] against the next 512 C candidates: visit(q, distances), not looked at for rows that are not finite; ready(c):
-// before that, for the lane's c-th candidate.
+// The queries qs [queries][NQ] against the next 512 C candidates: visit(q, distances), NaN for candidates that are not finite; ready(c): before that,
+// for the lane's c-th candidate.  large: a query's norm is not moderate, see direct_bad_row.  Whether the candidates are finite is looked at once,
+// as soon as a distance of the wavefront's is so large that one may not be: the row is in registers, and NaN from then on if it is not.  (With a look at
+// the row in memory per pair 2048 x 32, k = 8, all rows of such norms, took 484 us, one row NaN 207; 18 both, as without such rows.)
 template <int C, int NQ, typename R, typename V>
-__device__ inline __attribute__((always_inline)) void block_pass(BlockStream<NQ>& s, const v4f* qs, R&& ready, V&& visit)
+__device__ inline __attribute__((always_inline)) void block_pass(BlockStream<NQ>& s, const v4f* qs, bool large, R&& ready, V&& visit)
 {
     v4f b[C][NQ];
 #pragma unroll
@@ -314,13 +316,32 @@ __device__ inline __attribute__((always_inline)) void block_pass(BlockStream<NQ>
     }
 #pragma unroll
     for (int c = 0; c < C; ++c) ready(c);
-    constexpr int CHAINS = NQ < 16 ? NQ : 16;
+    // (AHEAD: quads read before they are used.  With one candidate a lane the compiler reads and waits quad by quad: 1300 x 100 45 us, 37 so.)
+    constexpr int CHAINS = NQ < 16 ? NQ : 16, AHEAD = C == 1 && NQ >= 24 ? 2 : 0;
+    auto look = [&]() {
+#pragma unroll
+        for (int c = 0; c < C; ++c) {
+            float norm = 0.f;
+#pragma unroll
+            for (int j = 0; j < NQ; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) norm = __builtin_fmaf(b[c][j][e], b[c][j][e], norm);
+            if (!(norm < INF)) b[c][0][0] = NONE;
+        }
+    };
+    if (large) look();
+    bool looked = large;
 #pragma unroll 1
     for (int q = 0; q < s.x.queries; ++q) {
         float p[C][CHAINS];
+        v4f ahead[AHEAD + 1];
+#pragma unroll
+        for (int j = 0; j < AHEAD; ++j) ahead[j] = qs[q * NQ + j];
 #pragma unroll
         for (int j = 0; j < NQ; ++j) {
-            const v4f a = qs[q * NQ + j];
+            if (AHEAD > 0) __builtin_amdgcn_sched_barrier(0);
+            if (j + AHEAD < NQ) ahead[(j + AHEAD) % (AHEAD + 1)] = qs[q * NQ + j + AHEAD];
+            const v4f a = ahead[j % (AHEAD + 1)];
 #pragma unroll
             for (int c = 0; c < C; ++c) {
                 float t = j < 16 ? 0.f : p[c][j & 15];
@@ -332,17 +353,19 @@ __device__ inline __attribute__((always_inline)) void block_pass(BlockStream<NQ>
         float v[C];
 #pragma unroll
         for (int c = 0; c < C; ++c) v[c] = block_tree<CHAINS>(p[c]);
+        if (!looked) {
+            bool some = false;
+#pragma unroll
+            for (int c = 0; c < C; ++c) some = some || !(v[c] < 2e38f);
+            if (__any(some)) {
+                look();
+                looked = true;
+#pragma unroll
+                for (int c = 0; c < C; ++c) v[c] = b[c][0][0] != b[c][0][0] ? NONE : v[c];
+            }
+        }
         visit(q, v);
     }
-}
-// Whether some of the distances of a query are so large that the candidate may not be finite (NaN: yes).
-template <int C>
-__device__ inline bool block_suspect(const float (&v)[C])
-{
-    bool some = false;
-#pragma unroll
-    for (int c = 0; c < C; ++c) some = some || !(v[c] < 2e38f);
-    return __any(some);
 }
 // all candidates, and no places beyond the last 512: pass(how many times 512, the first of them)
 template <int NQ, typename F>
@@ -395,19 +418,12 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
         if (lane == 0) norms[wave] = norm;
     }
     __syncthreads();
-    // (a row beside one that is not of moderate norm, or at such a distance, may be no finite one)
     bool large = false;
     for (int q = 0; q < p.rows; ++q) large = large || !(norms[q] < 1e36f);
+    large = __any(large);
     auto pass = [&](auto per, int base) {
         constexpr int C = decltype(per)::value;
-        block_pass<C>(stream, qs, [](int) {}, [&](int q, float (&v)[C]) {
-            if (large || block_suspect(v)) {
-#pragma unroll
-                for (int c = 0; c < C; ++c) {
-                    const int cand = base + c * BLOCK + tid;
-                    if (cand < p.n && direct_bad_row(p.X, cand, p.d)) v[c] = NONE;
-                }
-            }
+        block_pass<C>(stream, qs, large, [](int) {}, [&](int q, float (&v)[C]) {
 #pragma unroll
             for (int c = 0; c < C; ++c) dist[q * pitch + base + c * BLOCK + tid] = v[c];
         });
@@ -423,12 +439,13 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
     unsigned long long* keep = reinterpret_cast<unsigned long long*>(direct_smem) + wave * KNN_KEEP;      // (the candidates' rows are used up)
     const bool fine = norms[wave] < INF;
     if (p.nonfinite && !fine && lane == 0) atomicOr(p.nonfinite, 1u);
-    // the row's distances, 16 of a lane's at a time: what(first of them, values), NaN from n64 on
+    // the row's distances, 16 of a lane's at a time: what(first of them, values), +inf from n64 on (not NaN, which the compiler
+    // would take out of the minima, and read one value after the other)
     auto all = [&](auto&& what) {
         for (int i0 = 0; i0 < n64; i0 += 16) {
             float v[16];
 #pragma unroll
-            for (int i = 0; i < 16; ++i) v[i] = i0 + i < n64 ? mine[(i0 + i) * 64 + lane] : NONE;
+            for (int i = 0; i < 16; ++i) v[i] = i0 + i < n64 ? mine[(i0 + i) * 64 + lane] : INF;
             what(i0, v);
         }
     };
@@ -515,16 +532,13 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
                 return in;
             });
         }
-        if (kept < p.k)
-            all([&](int i0, const float (&v)[16]) {
-#pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const unsigned long long m = __ballot(v[i] == INF);
-                    const int at = kept + prefix(m), n = __popcll(m);
-                    if (v[i] == INF && at < p.k) keep[at] = ((unsigned long long)__float_as_uint(INF) << 32) | (unsigned int)((i0 + i) * 64 + lane);
-                    kept = kept + n < p.k ? kept + n : p.k;
-                }
-            });
+        for (int i = 0; kept < p.k && i < n64; ++i) {
+            const bool in = mine[i * 64 + lane] == INF;
+            const unsigned long long m = __ballot(in);
+            const int at = kept + prefix(m);
+            if (in && at < p.k) keep[at] = ((unsigned long long)__float_as_uint(INF) << 32) | (unsigned int)(i * 64 + lane);
+            kept = kept + __popcll(m) < p.k ? kept + __popcll(m) : p.k;
+        }
         __builtin_amdgcn_wave_barrier();
     }
     // ranks by (distance, row)
@@ -581,23 +595,16 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
     __syncthreads();
     bool large = false;
     for (int q = 0; q < p.rows; ++q) large = large || !(norms[q] < 1e36f);
+    large = __any(large);
     block_passes<NQ>(p.nc, [&](auto per, int base) {
         constexpr int C = decltype(per)::value;
         int colour[C];
-        block_pass<C>(stream, qs,
+        block_pass<C>(stream, qs, large,
             [&](int c) {
                 const int cand = base + c * BLOCK + tid;
                 colour[c] = p.colour && cand < p.nc ? p.colour[cand] : -2;
             },
             [&](int q, float (&v)[C]) {
-                if (large || block_suspect(v)) {
-#pragma unroll
-                    for (int c = 0; c < C; ++c) {
-                        const int cand = base + c * BLOCK + tid;
-                        if (cand < p.nc && v[c] < INF && direct_bad_row(p.Xc, cand, p.d)) v[c] = INF;
-                        v[c] = v[c] < INF ? v[c] : INF;                      // (NaN: +inf)
-                    }
-                }
                 const int mine = colour_of[q];
                 float least = INF;
 #pragma unroll

@@ -88,6 +88,32 @@ def test_lists_of_unlike_rows(lib, kind, N, d, k):
     assert kind != "out_of_reach" or torch.isinf(lib.knn_graph(X, k)[1][:40:8, 5:]).all()
 
 
+# rows of large norms or one that is not finite cost a look at each row, not at each pair (which took 25 and 10 times as long)
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d,k", [(2048, 32, 8), (4000, 8, 8), (1300, 100, 8)])
+def test_large_rows_take_no_longer(lib, N, d, k):
+    print(f"small k-NN, time with large rows, N={N} d={d} k={k}", flush=True)
+    X = rows(N, d, N)
+    large, nan = X * 3e17, X.clone()
+    large[5], nan[N // 2] = 0.0, float("nan")
+    out = (torch.empty((N, k), dtype=torch.int32, device="cuda"), torch.empty((N, k), dtype=torch.float32, device="cuda"))
+
+    def least(X):
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(8):
+                lib.knn_graph_static(X, k, out)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        return min(times[2:])
+    plain, with_large, with_nan = least(X), least(large), least(nan)
+    print(f"  {125 * plain:.1f} us, {125 * with_large:.1f} with large rows, {125 * with_nan:.1f} with a NaN", flush=True)
+    assert with_large < 3 * plain and with_nan < 3 * plain
+
+
 # the same where the pairs can be counted on the host: which searches go this way does not depend on a GPU
 @pytest.mark.parametrize("N,d,k,products", [(2048, 32, 8, 0.0), (4472, 8, 3, 0.0), (4473, 8, 3, 1.0), (1690, 128, 16, 0.0), (1691, 128, 16, 1.0), (500, 129, 4, 1.0)])
 def test_searches_that_multiply_nothing(N, d, k, products):
