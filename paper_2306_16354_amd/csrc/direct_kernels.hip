@@ -256,8 +256,11 @@ struct BlockStream {
     // Without branches that lanes part at: the row's last four features stand in for what ends beyond them, which `bring` puts right.
     __device__ inline v4f quad(int row, int t) const
     {
-        if (x.d < 4) return direct_quad(x.Xc, row, t, x.d, false);
-        return *reinterpret_cast<const v4f_word*>(x.Xc + (size_t)row * x.d + (t + 4 <= x.d ? t : x.d - 4));
+        if constexpr (NQ <= 2)                           // (the only ones for rows so narrow)
+            if (x.d < 4) return direct_quad(x.Xc, row, t, x.d, false);
+        // (an offset of 32 bits: a million rows of 128 columns at most)
+        const unsigned int at = ((unsigned int)row * (unsigned int)x.d + (unsigned int)(t + 4 <= x.d ? t : x.d - 4)) * 4u;
+        return *reinterpret_cast<const v4f_word*>(reinterpret_cast<const char*>(x.Xc) + at);
     }
     __device__ inline void start(const BlockRows& x_, v4f* tile_)
     {
@@ -555,11 +558,14 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
     if (p.evaluated && lane == 0) p.evaluated[row] = fine ? p.n - 1 : 0;
 }
 
-// The nearest row (of another colour) of many queries: as direct_knn_kernel, with one (distance, row) per query in LDS instead of all distances.
+// The nearest row (of another colour): as direct_knn_kernel, with one (distance, row) per query in LDS instead of all distances.  A workgroup has a panel of
+// queries and a segment of the candidates; where there are several segments, they meet at a word per query.
+// (Without segments, for rounds of 9 to 46 queries: 24 000 x 128 0.69 ms, 100 000 x 128 3.8, 300 000 x 100 9, 1M x 16 10; the engine 0.15, 0.35, 0.4, 1.0; so
+// 0.06, 0.13, 0.11, 0.15.)
 struct DirectNear {
     const float* Xq; const float* Xc; const int32_t* q_rows; const int32_t* colour;
-    int m, nq_rows, nc, d, rows;
-    int32_t* out_idx; float* out_dist; unsigned long long* pairs;
+    int m, nq_rows, nc, d, rows, segments, per_segment;
+    int32_t* out_idx; float* out_dist; unsigned long long *keys, *pairs;
 };
 constexpr int NEAR_ROWS = 32;              // queries of a workgroup at most
 
@@ -573,9 +579,11 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
     v4f* tile = reinterpret_cast<v4f*>(direct_smem);
     v4f* qs = tile + BLOCK * block_pitch(NQ);
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int q0 = blockIdx.x * p.rows;
+    const int panel = blockIdx.x / p.segments, c0 = (blockIdx.x - panel * p.segments) * p.per_segment;
+    const int q0 = panel * p.rows, nc = p.nc - c0 < p.per_segment ? p.nc - c0 : p.per_segment;
+    const int32_t* c_colour = p.colour ? p.colour + c0 : nullptr;
     BlockStream<NQ> stream;
-    stream.start(BlockRows{p.Xc, p.nc, p.d, p.rows}, tile);
+    stream.start(BlockRows{p.Xc + (size_t)c0 * p.d, nc, p.d, p.rows}, tile);
     if (tid < p.rows) {
         const int i = q0 + tid;
         int row = i < p.m ? (p.q_rows ? p.q_rows[i] : i) : -1;
@@ -596,36 +604,41 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
     bool large = false;
     for (int q = 0; q < p.rows; ++q) large = large || !(norms[q] < 1e36f);
     large = __any(large);
-    block_passes<NQ>(p.nc, [&](auto per, int base) {
+    block_passes<NQ>(nc, [&](auto per, int base) {
         constexpr int C = decltype(per)::value;
         int colour[C];
         block_pass<C>(stream, qs, large,
             [&](int c) {
+                // (beyond the last candidate stands the last one again, with a larger index: it is never the smallest key)
                 const int cand = base + c * BLOCK + tid;
-                colour[c] = p.colour && cand < p.nc ? p.colour[cand] : -2;
+                colour[c] = c_colour ? c_colour[cand < nc ? cand : nc - 1] : -2;
             },
             [&](int q, float (&v)[C]) {
                 const int mine = colour_of[q];
                 float least = INF;
 #pragma unroll
                 for (int c = 0; c < C; ++c) {
-                    v[c] = colour[c] == mine || base + c * BLOCK + tid >= p.nc ? INF : v[c];
+                    v[c] = colour[c] == mine ? INF : v[c];
                     least = fminf(least, v[c]);
                 }
                 // (the distance's word alone: another wavefront may be at it)
                 const float upto = __uint_as_float(*(volatile unsigned int*)(reinterpret_cast<unsigned int*>(best + q) + 1));
                 if (!__any(least < INF && !(least > upto))) return;          // (all ones, nothing yet, are a NaN)
-                unsigned long long key = ~0ull;
+                int at = 0;
 #pragma unroll
-                for (int c = C - 1; c >= 0; --c)
-                    if (v[c] == least && v[c] < INF) key = ((unsigned long long)__float_as_uint(v[c]) << 32) | (unsigned int)(base + c * BLOCK + tid);
-                key = wave_min(key);
+                for (int c = C - 1; c > 0; --c) at = v[c] == least ? c * BLOCK : at;
+                at = v[0] == least ? 0 : at;
+                const unsigned long long key = wave_min(least < INF ? ((unsigned long long)__float_as_uint(least) << 32) | (unsigned int)(c0 + base + at + tid) : ~0ull);
                 if (lane == 0) atomicMin(best + q, key);
             });
     });
     __syncthreads();
     if (tid < p.rows && q0 + tid < p.m) {
         const bool some = best[tid] != ~0ull && row_of[tid] >= 0 && norms[tid] < INF;
+        if (p.segments > 1) {
+            if (some) atomicMin(p.keys + q0 + tid, best[tid]);
+            return;
+        }
         p.out_idx[q0 + tid] = some ? (int32_t)(unsigned int)best[tid] : -1;
         p.out_dist[q0 + tid] = some ? __uint_as_float((unsigned int)(best[tid] >> 32)) : INF;
     }
@@ -736,20 +749,45 @@ bool direct_near_wanted(long long m, long long nc, int d)
     return d <= 128 && m >= 1 && nc <= (1LL << 20) && m <= (1LL << 20) && m * nc * (8LL * direct_quads(d) + 24) <= 1000000000LL;
 }
 
+// Queries of a workgroup, and segments of the candidates: what takes least, in the instructions of direct_near_wanted.  512 candidates take a workgroup as
+// long as 130 + 26 per quad to bring (24 000 rows for one query of a workgroup: 128 columns 230 us, 64 112, 32 66), 8 per quad and 24 for a query;
+// the two launches that segments need take 1300, and a workgroup has a CU to itself.
+struct NearSplit { int rows, segments, per_segment; };
+static NearSplit direct_near_split(int m, int nc, int d)
+{
+    const int nq = direct_quads(d), cus = direct_cus(), steps = (nc + BLOCK - 1) / BLOCK;
+    NearSplit best{};
+    long long least = 0;
+    for (int rows = 1; rows <= NEAR_ROWS; ++rows) {
+        const int panels = (m + rows - 1) / rows;
+        int segments = panels < cus ? cus / panels : 1;
+        const int per = (steps + segments - 1) / segments;
+        segments = (steps + per - 1) / per;
+        const long long time = (long long)((panels + cus - 1) / cus) * per * (130 + 26 * nq + (long long)rows * (8 * nq + 24)) + (segments > 1 ? 1300 : 0);
+        if (rows == 1 || time < least) { least = time; best = NearSplit{rows, segments, per * BLOCK}; }
+    }
+    return best;
+}
+
 hipError_t direct_near(const float* Xq, int m, int nq_rows, const int32_t* q_rows, const float* Xc, int nc, int d, const int32_t* colour,
-                       int32_t* out_idx, float* out_dist, unsigned long long* pairs, hipStream_t s)
+                       int32_t* out_idx, float* out_dist, unsigned long long* keys, unsigned long long* pairs, hipStream_t s)
 {
     if (m < 1) return hipSuccess;
-    const int cus = direct_cus(), rounds = (m + cus * NEAR_ROWS - 1) / (cus * NEAR_ROWS), rows = (m + cus * rounds - 1) / (cus * rounds);
-    const DirectNear p{Xq, Xc, q_rows, colour, m, nq_rows, nc, d, rows, out_idx, out_dist, pairs};
-    return direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
+    const NearSplit split = direct_near_split(m, nc, d);
+    const DirectNear p{Xq, Xc, q_rows, colour, m, nq_rows, nc, d, split.rows, split.segments, split.per_segment, out_idx, out_dist, keys, pairs};
+    const dim3 per_m((unsigned)((m + 255) / 256));
+    if (split.segments > 1) hipLaunchKernelGGL(direct_fill_kernel, per_m, dim3(256), 0, s, keys, m);
+    const hipError_t e = direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
         constexpr int NQ = decltype(quads)::value;
-        const size_t lds = ((size_t)BLOCK * block_pitch(NQ) + (size_t)rows * NQ) * 16;
+        const size_t lds = ((size_t)BLOCK * block_pitch(NQ) + (size_t)split.rows * NQ) * 16;
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(&direct_near_kernel<NQ>), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
-        hipLaunchKernelGGL((direct_near_kernel<NQ>), dim3((unsigned)((m + rows - 1) / rows)), dim3(BLOCK), lds, s, p);
+        hipLaunchKernelGGL((direct_near_kernel<NQ>), dim3((unsigned)((m + split.rows - 1) / split.rows * split.segments)), dim3(BLOCK), lds, s, p);
         return hipGetLastError();
     });
+    if (e != hipSuccess) return e;
+    if (split.segments > 1) hipLaunchKernelGGL(direct_unpack_kernel, per_m, dim3(256), 0, s, keys, m, out_idx, out_dist);
+    return hipGetLastError();
 }
 
 }  // namespace slhc

@@ -2488,7 +2488,8 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     p.tiles_done = nullptr;
                     HIP_TRY(slhc::launch_cross_1nn_sweep(p, s));
                 } else if (!round_pruned && near_wanted(kws.near, flags) && slhc::direct_near_wanted(n, N, d)) {
-                    HIP_TRY(slhc::direct_near(X, n, (int)N, rows, X, (int)N, d, ws.colour, ws.q_idx, ws.q_dist, kws.counters + 1, s));
+                    // (keys_a is free until the edge sort)
+                    HIP_TRY(slhc::direct_near(X, n, (int)N, rows, X, (int)N, d, ws.colour, ws.q_idx, ws.q_dist, ws.keys_a, kws.counters + 1, s));
                     near_tile_steps += (unsigned long long)((n + 127) / 128) * tiles_1d;
                 } else if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;

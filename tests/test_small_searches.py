@@ -183,3 +183,40 @@ def test_trees_of_rows_out_of_reach(lib, near, far, k):
     for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
         assert torch.equal(want[key], got[key]), key
     assert torch.isfinite(got["mst_w"]).all()
+
+
+def rows_and_groups(N, d, k, groups):
+    """One blob that the lists connect, and groups of k + 1 rows far from it and from each other, which have to ask for their nearest other row."""
+    g = torch.Generator(device="cuda").manual_seed(N + d)
+    X = torch.randn((N, d), generator=g, device="cuda")
+    away = torch.randn((groups, d), generator=g, device="cuda")
+    away *= 60 * d ** 0.5 / away.norm(dim=1, keepdim=True)
+    at = torch.randperm(N, generator=g, device="cuda")[:groups * (k + 1)]
+    X[at] = away.repeat_interleave(k + 1, 0) + 0.01 * torch.randn((len(at), d), generator=g, device="cuda")
+    return X
+
+
+# rounds that ask for few rows: one workgroup's queries and several, candidates in segments of one step and of many, the last of them in part; every number of
+# quads the kernel is made for
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d,k,groups", [(5000, 4, 2, 1), (5000, 12, 3, 9), (20_481, 30, 8, 4), (12_801, 48, 8, 16), (9000, 61, 8, 1), (7777, 90, 8, 30), (24_000, 128, 8, 1),
+                                          (24_100, 128, 8, 16), (60_000, 100, 5, 2), (150_000, 7, 8, 20), (250_000, 16, 4, 3)])
+def test_few_rows_that_have_to_be_connected(lib, N, d, k, groups):
+    print(f"few queries, N={N} d={d} k={k} {groups} groups", flush=True)
+    X = rows_and_groups(N, d, k, groups)
+    want, got = lib.slhc(X, k, prune=False, fp32_filter=True), lib.slhc(X, k, prune=False)
+    torch.cuda.synchronize()
+    for key in ("mst_src", "mst_dst", "mst_w", "children", "heights", "sizes"):
+        assert torch.equal(want[key], got[key]), key
+    assert groups * (k + 1) <= got["stats"]["connect_query_rows"]
+
+
+# ... occupy the chip (with all candidates passing by each workgroup of a few queries the first took 3.8 ms, the second 9; 0.11 and 0.23 now)
+@pytest.mark.gpu
+@pytest.mark.parametrize("N,d,k,limit", [(100_000, 128, 8, 1.0), (300_000, 100, 16, 3.0)])
+def test_few_queries_take_their_share(lib, N, d, k, limit):
+    print(f"few queries, time, N={N} d={d}", flush=True)
+    X = rows_and_groups(N, d, k, 1)
+    took = [lib.slhc(X, k, prune=False)["stats"]["ms_connect_kernels"] for _ in range(4)]
+    print("  ms", took, flush=True)
+    assert 0 < min(took) < limit
