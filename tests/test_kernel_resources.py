@@ -33,3 +33,11 @@ def kernels(tmp_path_factory):
 def test_narrow_emission(kernels, steps, listed):
     registers, scratch = kernels[f"_ZN4slhc17near_sweep_kernelILi{steps}ELi1ELb0ELb{listed}EEEvNS_9NearSweepE"]
     assert registers <= 128 and scratch <= 64
+
+
+# blocks of pairs in registers: all a CU has for two wavefronts per SIMD, and no scratch
+@pytest.mark.parametrize("quads", [2, 4, 8, 12, 16, 24, 32])
+@pytest.mark.parametrize("name", ["17direct_knn_kernelILi{}EEEvNS_9DirectKnnE", "18direct_near_kernelILi{}EEEvNS_10DirectNearE"])
+def test_blocks_of_pairs(kernels, name, quads):
+    registers, scratch = kernels["_ZN4slhc" + name.format(quads)]
+    assert registers <= (128 if quads == 2 else 256) and scratch == 0
