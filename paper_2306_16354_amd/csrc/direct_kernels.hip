@@ -751,7 +751,7 @@ bool direct_near_wanted(long long m, long long nc, int d)
 
 // Queries of a workgroup, and segments of the candidates: what takes least, in the instructions of direct_near_wanted.  512 candidates take a workgroup as
 // long as 130 + 26 per quad to bring (24 000 rows for one query of a workgroup: 128 columns 230 us, 64 112, 32 66), 8 per quad and 24 for a query;
-// the two launches that segments need take 1300, and a workgroup has a CU to itself.
+// the two launches that segments need take 3000 (2 us and 4, and what lies between), and a workgroup has a CU to itself.
 struct NearSplit { int rows, segments, per_segment; };
 static NearSplit direct_near_split(int m, int nc, int d)
 {
@@ -763,7 +763,7 @@ static NearSplit direct_near_split(int m, int nc, int d)
         int segments = panels < cus ? cus / panels : 1;
         const int per = (steps + segments - 1) / segments;
         segments = (steps + per - 1) / per;
-        const long long time = (long long)((panels + cus - 1) / cus) * per * (130 + 26 * nq + (long long)rows * (8 * nq + 24)) + (segments > 1 ? 1300 : 0);
+        const long long time = (long long)((panels + cus - 1) / cus) * per * (130 + 26 * nq + (long long)rows * (8 * nq + 24)) + (segments > 1 ? 3000 : 0);
         if (rows == 1 || time < least) { least = time; best = NearSplit{rows, segments, per * BLOCK}; }
     }
     return best;
