@@ -716,14 +716,23 @@ static int direct_knn_rows(long long n, int d)
     }
     return 0;
 }
-// The line, in instructions of a lane (two per feature, and about 24 for the rest of a pair and its share of the selection), measured on both
-// sides (us, engine and this, k = 12): 700 M: 2154 x 64 60 and 54, 1557 x 128 57 and 47, 2453 x 48 60 and 47, 4008 x 8 56 and 43; 750 M: 4330 x 2 72 and
-// 65, 2924 x 32 58 and 43; 850 M: 3843 x 16 62 and 56, 2658 x 40 60 and 59; 930 M: 2067 x 70 64 and 87, 3291 x 24 63 and 74, 4818 x 8 71 and 67;
-// 1100 M: 3535 x 20 64 and 73, 5303 x 2 88 and 97.  Where the caller waits for the lists, nothing hides the host's way through eight
-// launches: clustering 4096 x 16 (940 M) 470 and 428, 5000 x 16 (1400 M) 573 and 548.
+// What a step, 512 candidates for a workgroup's rows, takes: 130 + 26 per quad to bring them, 8 per quad and 24 for a row; about 4 ns each.
+static long long direct_step(int nq, int rows) { return 130 + 26 * nq + (long long)rows * (8 * nq + 24); }
+
+// The line.  Where the caller waits for the lists (clusterings): what the workgroups' rounds take against the engine's eight launches, 45 us and 5 more per thousand
+// rows.  Us a clustering of one blob, which has nothing to connect, k = 12, engine and this, below the line and above it: 8 columns 4873 rows 314 and 310,
+// 5123 318 and 334; 16 columns 4531 305 and 294, 4724 308 and 329; 32 columns 2919 248 and 239, 3107 254 and 270; 48 columns 2958 259 and 257, 3095 255 and
+// 284; 64 columns 2500 237 and 240, 2628 281 and 292; 96 columns 1983 222 and 216, 2097 236 and 263; 128 columns 2026 227 and 227, 2112 274 and 308.
+// Calls among others: instructions of a lane, two per feature and about 24 for the rest of a pair and its share of the selection.  700 M (k = 12, us): 4183 x 8
+// 67 and 51, 2820 x 32 56 and 42, 2415 x 40 56 and 50, 2145 x 64 58 and 53, 1581 x 128 54 and 46; 800 M: 3779 x 16 60 and 50, 3015 x 32 55 and 42,
+// 2581 x 40 56 and 58, 2294 x 64 57 and 54; 900 M: 4743 x 8 67 and 65, 3198 x 32 60 and 67, 2738 x 40 57 and 59, 2041 x 96 53 and 41.
 bool direct_knn_wanted(long long n, int d, int k, bool waited_for)
 {
-    return d <= 128 && k <= 64 && n <= 16384 && n * n * (8LL * direct_quads(d) + 24) <= (waited_for ? 1600000000LL : 800000000LL) && direct_knn_rows(n, d) > 0;
+    if (d > 128 || k > 64 || n > 16384) return false;
+    const int nq = direct_quads(d), rows = direct_knn_rows(n, d), cus = direct_cus();
+    if (rows < 1 || (!waited_for && n * n * (8LL * nq + 24) > 800000000LL)) return false;
+    const long long rounds = ((n + rows - 1) / rows + cus - 1) / cus, steps = (n + BLOCK - 1) / BLOCK;
+    return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6;
 }
 
 hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, int32_t* evaluated, unsigned int* nonfinite, hipStream_t s)
@@ -741,17 +750,17 @@ hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, flo
     });
 }
 
-// The line, for a round of connecting components against near_link's ten launches (us a clustering, without this and with lines at 600 M,
-// 1000 M, 2000 M, 3000 M): 2000 x 32 in tight clusters 451, 331, 314, 338, 332; 4096 x 16 499, 483, 449, 478, 467; 6000 x 64 711, 716, 702,
-// 729, 880; 3000 x 128 485, 479, 468, 574, 575.
+// The line, for a round of connecting components, in the instructions of direct_knn_wanted, against near_link's ten launches (us, kernels of all rounds
+// of a clustering whose last one asks for as many rows as make 1000 M, near_link and this): 6000 x 64 173 and 77, 6000 x 128 178 and 83, 24 000 x 32 164 and
+// 97, 24 000 x 128 191 and 128, 100 000 x 32 262 and 207, 100 000 x 128 391 and 392.  2000 M: 24 000 x 32 175 and 132, 24 000 x 128 197 and 157,
+// 100 000 x 32 271 and 231, 100 000 x 128 390 and 426; 4000 M: 356 and 1266 (all rows once), 204 and 215, 282 and 287, 399 and 490.
 bool direct_near_wanted(long long m, long long nc, int d)
 {
     return d <= 128 && m >= 1 && nc <= (1LL << 20) && m <= (1LL << 20) && m * nc * (8LL * direct_quads(d) + 24) <= 1000000000LL;
 }
 
-// Queries of a workgroup, and segments of the candidates: what takes least, in the instructions of direct_near_wanted.  512 candidates take a workgroup as
-// long as 130 + 26 per quad to bring (24 000 rows for one query of a workgroup: 128 columns 230 us, 64 112, 32 66), 8 per quad and 24 for a query;
-// the two launches that segments need take 3000 (2 us and 4, and what lies between), and a workgroup has a CU to itself.
+// Queries of a workgroup, and segments of the candidates: what takes least by direct_step (24 000 candidates for one query of a workgroup: 128 columns 230 us,
+// 64 112, 32 66); the two launches that segments need take 3000 (2 us and 4, and what lies between), and a workgroup has a CU to itself.
 struct NearSplit { int rows, segments, per_segment; };
 static NearSplit direct_near_split(int m, int nc, int d)
 {
@@ -763,7 +772,7 @@ static NearSplit direct_near_split(int m, int nc, int d)
         int segments = panels < cus ? cus / panels : 1;
         const int per = (steps + segments - 1) / segments;
         segments = (steps + per - 1) / per;
-        const long long time = (long long)((panels + cus - 1) / cus) * per * (130 + 26 * nq + (long long)rows * (8 * nq + 24)) + (segments > 1 ? 3000 : 0);
+        const long long time = (long long)((panels + cus - 1) / cus) * per * direct_step(nq, rows) + (segments > 1 ? 3000 : 0);
         if (rows == 1 || time < least) { least = time; best = NearSplit{rows, segments, per * BLOCK}; }
     }
     return best;

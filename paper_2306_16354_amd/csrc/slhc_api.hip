@@ -887,7 +887,7 @@ size_t slhc_ws_bytes(int64_t N, int32_t d, int32_t k, bool with_order, bool with
 
 int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, int32_t* mst_dst, float* mst_w,
              int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace, size_t workspace_bytes,
-             hipStream_t s, uint32_t flags, bool with_order);
+             hipStream_t s, uint32_t flags, bool with_order, const float* X_given, int32_t d_given);
 
 int bits_for(long long n) { int b = 1; while (b < 32 && (1LL << b) < n) ++b; return b; }
 
@@ -1051,7 +1051,7 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
     if (P >= 2) {
         const int32_t kp = P - 1 < NESTED_K ? P - 1 : NESTED_K;
         rc = run_slhc(o.Xp, P, d, kp, o.n_src, o.n_dst, o.n_w, nullptr, nullptr, nullptr, nullptr,
-                      o.nested_ws, o.nested_bytes, s, 0u, false);
+                      o.nested_ws, o.nested_bytes, s, 0u, false, o.Xp, d);
         if (rc != SLHC_OK) return rc;
         const size_t E = (size_t)(P - 1);
         HIP_TRY(hipMemcpyAsync(h_src, o.n_src, E * 4, hipMemcpyDeviceToHost, s));
@@ -2179,13 +2179,14 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
         // they see all of them.)
         if (!(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true) &&
             SlhcWs(nullptr, N, d, k, true, workspace_bytes).knn->near.ok) { dw = d; head = 0; }
+        const float* X_given = X;
         if (dw != d) {
             const int rp = pad_columns(X, N, d, dw, static_cast<float*>(workspace), static_cast<hipStream_t>(stream));
             if (rp != SLHC_OK) return rp;
             X = static_cast<const float*>(workspace);
         }
         return run_slhc(X, N, dw, k, mst_src, mst_dst, mst_w, children, heights, sizes, stats,
-                        static_cast<unsigned char*>(workspace) + head, workspace_bytes - head, static_cast<hipStream_t>(stream), flags, true);
+                        static_cast<unsigned char*>(workspace) + head, workspace_bytes - head, static_cast<hipStream_t>(stream), flags, true, X_given, d);
     });
 }
 
@@ -2194,10 +2195,10 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
 namespace {
 
 // The whole pipeline on validated arguments.  `with_order` selects the workspace layout (the
-// nested call that clusters the pivots of the row order runs without one).
+// nested call that clusters the pivots of the row order runs without one).  X_given: the rows without columns of zeros.
 int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, int32_t* mst_dst, float* mst_w,
              int32_t* children, float* heights, int32_t* sizes, slhc_stats* stats, void* workspace, size_t workspace_bytes,
-             hipStream_t s, uint32_t flags, bool with_order)
+             hipStream_t s, uint32_t flags, bool with_order, const float* X_given, int32_t d_given)
 {
     int rc = SLHC_OK;
     SlhcWs ws(workspace, N, d, k, with_order, workspace_bytes);
@@ -2487,9 +2488,9 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
                     p.todo = kws.near.b.todo;
                     p.tiles_done = nullptr;
                     HIP_TRY(slhc::launch_cross_1nn_sweep(p, s));
-                } else if (!round_pruned && near_wanted(kws.near, flags) && slhc::direct_near_wanted(n, N, d)) {
+                } else if (!round_pruned && near_wanted(kws.near, flags) && slhc::direct_near_wanted(n, N, d_given)) {
                     // (keys_a is free until the edge sort)
-                    HIP_TRY(slhc::direct_near(X, n, (int)N, rows, X, (int)N, d, ws.colour, ws.q_idx, ws.q_dist, ws.keys_a, kws.counters + 1, s));
+                    HIP_TRY(slhc::direct_near(X_given, n, (int)N, rows, X_given, (int)N, d_given, ws.colour, ws.q_idx, ws.q_dist, ws.keys_a, kws.counters + 1, s));
                     near_tile_steps += (unsigned long long)((n + 127) / 128) * tiles_1d;
                 } else if (!round_pruned && near_wanted(kws.near, flags)) {
                     const NearWs& near = kws.near;

@@ -169,6 +169,15 @@ def test_evaluated_pairs_are_counted(lib, N, d, all_pairs):
     assert count == N * (N - 1) if all_pairs else 2 * N <= count < 100 * N
 
 
+# the last clustering of a width that evaluates every pair, and the first that does not (4100 x 32 took 334 us instead of 275 with all pairs)
+@pytest.mark.gpu
+@pytest.mark.parametrize("d,most", [(8, 5120), (16, 4608), (32, 3072), (48, 3072), (64, 2560), (96, 2048), (128, 2048)])
+def test_last_clusterings_of_all_pairs(lib, d, most):
+    print(f"last clustering of all pairs, {most} x {d}", flush=True)
+    counts = [lib.slhc(rows(N, d, N), 4, prune=False)["stats"]["knn_filter_survivors"] for N in (most, most + 1)]
+    assert counts[0] == most * (most - 1) and counts[1] < most * most // 4
+
+
 # rows so far from each other that the distance is no float32, and one row between them that both reach (lists of one such distance, of a quad and a part of
 # one, of all rows but the far one)
 @pytest.mark.gpu
