@@ -474,22 +474,39 @@ struct NearLane {
     // pos0: position of the first of the 64 candidates, col: their colours (LDS)
     // ok: whether the lane's queries and the candidates' tile are of the side in hand (and of different colours, with one_colour,
     // which all lanes share: the 32 compares and selects per 16 values of a query are as much as a third of all vector instructions)
+    // EARLY: words of colours read ahead, of four candidates each.  Eight compares are made before the eight selects that need them (left alone, the compiler puts every
+    // compare right before its select, with two idle cycles between, and how much of it passes under multiplies is its choice): connection rounds of 1M x 128 without a
+    // row order 313 -> 285 ms, 100 000 x 100 8.4 -> 6.3 ms.  (The more words ahead, the more registers: with all eight 309 ms, and up to 48 columns one
+    // workgroup less on a CU, 200 000 x 16 13.8 -> 14.8 ms; with two 13.4.)
+    template <int EARLY>
     __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf,
                                                                bool ok0 = true, bool ok1 = true, bool one_colour = false)
     {
         const bool ok[2] = {ok0, ok1};
         const int lane = threadIdx.x & 63;
         if (COLOURED && !one_colour) {
+            v4i cc[8];                                              // of four candidates each
+            auto read = [&](int i) { cc[i] = *reinterpret_cast<const v4i*>(col + ((i >> 2) * 32 + 8 * (i & 3) + 4 * lhalf) * 4); };
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb)
+            for (int i = 0; i < EARLY; ++i) read(i);
+            __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const v4i cc = *reinterpret_cast<const v4i*>(col + (cb * 32 + 8 * g + 4 * lhalf) * 4);
+            for (int i = 0; i < 8; ++i) {
+                unsigned long long same[2][4];
 #pragma unroll
-                    for (int e = 0; e < 4; ++e)
+                for (int e = 0; e < 4; ++e)
 #pragma unroll
-                        for (int qb = 0; qb < 2; ++qb) acc[qb][cb][4 * g + e] = cc[e] == qcol[qb] ? -INF : acc[qb][cb][4 * g + e];
-                }
+                    for (int qb = 0; qb < 2; ++qb) same[qb][e] = __ballot(cc[i][e] == qcol[qb]);
+                if (i + EARLY < 8) read(i + EARLY);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int e = 0; e < 4; ++e)
+#pragma unroll
+                    for (int qb = 0; qb < 2; ++qb) {
+                        const int r = 4 * (i & 3) + e;
+                        acc[qb][i >> 2][r] = __builtin_amdgcn_inverse_ballot_w64(same[qb][e]) ? -INF : acc[qb][i >> 2][r];
+                    }
+            }
         }
         if (MODE == NEAR_MAXIMA) {
 #pragma unroll
@@ -819,7 +836,7 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
                     for (int qb = 0; qb < 2; ++qb)
                         acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
             }
-            mine.take(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1, tile_col >= 0);
+            mine.template take<KS <= 3 ? 2 : 4>(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1, tile_col >= 0);
         }
         if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == ntiles)) {
             mine.flush(p, seg * p.parts + part, lhalf, live && mine_here);
@@ -981,8 +998,8 @@ __global__ void __launch_bounds__(512, 2) near_wide_kernel(NearSweep p)
         const int j = 2 * (seg + i * nseg) + cg;
         const int pos0 = listed(j < p.used ? j : 0) * TILE;
         if (!half_pair) {
-            mine.take(p, acc[0], pos0, nb + 1024 + cg * 512, lhalf);
-            mine.take(p, acc[1], pos0 + 64, nb + 1024 + cg * 512 + 256, lhalf);
+            mine.template take<4>(p, acc[0], pos0, nb + 1024 + cg * 512, lhalf);
+            mine.template take<4>(p, acc[1], pos0 + 64, nb + 1024 + cg * 512 + 256, lhalf);
         }
         if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == nmine)) {
             mine.flush(p, (2 * seg + cg) * p.parts + part, lhalf, live);

@@ -41,3 +41,11 @@ def test_narrow_emission(kernels, steps, listed):
 def test_blocks_of_pairs(kernels, name, quads):
     registers, scratch = kernels["_ZN4slhc" + name.format(quads)]
     assert registers <= (128 if quads == 2 else 256) and scratch == 0
+
+
+# searches by colours of up to 48 columns: four wavefronts per SIMD, where their masks leave the registers
+@pytest.mark.parametrize("steps", [1, 2, 3])
+@pytest.mark.parametrize("mode", [2, 5])
+def test_narrow_searches_by_colours(kernels, steps, mode):
+    registers, scratch = kernels[f"_ZN4slhc17near_sweep_kernelILi{steps}ELi{mode}ELb1ELb0EEEvNS_9NearSweepE"]
+    assert registers <= 128 and scratch == 0
