@@ -35,6 +35,7 @@ sys.path.insert(0, ROOT)
 
 PEAK_FP32_MFMA_TFLOPS = 157.3      # MI355X published dense fp32 matrix peak
 PEAK_16BIT_MFMA_TFLOPS = 2500.0    # MI355X published dense bf16 and f16 matrix peak
+PEAK_FP32_VECTOR_TFLOPS = 157.3    # MI355X published fp32 vector peak
 PEAK_HBM_GBS = 8000.0
 
 
@@ -149,7 +150,11 @@ def main():
     half = args.knn_only or bool(stats[-1]["half_products"])
     split = half or bool(stats[-1]["split_products"])
     products = slhc.probe_knn_products(N, d, k) if half else 3.0 if split else 1.0      # per multiply-add
-    once = products < 1.0                               # one product for both orders of a pair
+    # (a search so small that every pair is evaluated multiplies nothing; the probe answers for k-NN graphs alone, whose line is another)
+    every_pair = half and (products == 0.0 if args.knn_only else int(stats[-1]["knn_filter_survivors"]) == N * (N - 1))
+    if every_pair:
+        products = 0.0
+    once = 0.0 < products < 1.0                         # one product for both orders of a pair
     multiply = "v_mfma_f32_32x32x16_f16" if half else "v_mfma_f32_32x32x16_bf16" if split else "v_mfma_f32_32x32x2_f32"
     empirical_16bit_tflops = slhc.probe_f16_mfma(dev) if half else slhc.probe_bf16_mfma(dev)     # the same for that multiply
     peak_tflops = PEAK_16BIT_MFMA_TFLOPS if split else PEAK_FP32_MFMA_TFLOPS
@@ -188,7 +193,7 @@ def main():
         "higher_is_better": True,
         "scaling": "weak",
         "vs_baseline": None,
-        "dtype": "f32 (tile products of " + ("float16 copies" if half else "split bf16 halves") + ", accumulated in f32, decide which "
+        "dtype": "f32" if every_pair else "f32 (tile products of " + ("float16 copies" if half else "split bf16 halves") + ", accumulated in f32, decide which "
                  "pairs are evaluated; every listed pair evaluated in f32)" if split else "f32",
         "data": "synthetic",
         "config": {
@@ -230,6 +235,13 @@ def main():
         },
         "input_generation_s": gen_s,
     }
+    if every_pair:
+        # one launch on the vector units: a difference and a multiply-add per feature, no matrix instruction
+        line["roofline"] = {
+            "kernel": "direct_knn_kernel", "bound": "vector_fp32", "achieved": achieved_tflops, "peak": PEAK_FP32_VECTOR_TFLOPS,
+            "unit": "TFLOP/s", "frac": achieved_tflops / PEAK_FP32_VECTOR_TFLOPS, "traffic": None, "launch_ms": knn_kernel_ms,
+            "algorithmic_flop_per_launch": flops, "executed_mfma_flop_per_launch": 0.0,
+            "note": "achieved counts the algorithmic 2 d N^2; every pair is evaluated, and launch_ms holds the selection of the k nearest too"}
     if fp32_ms is not None:
         ft = flops / (fp32_ms * 1e-3) / 1e12
         line["roofline_fp32_products"] = {
@@ -239,8 +251,8 @@ def main():
             "frac_of_empirical_peak": ft / empirical_tflops}
         # the metric's "% FP32-MFMA peak" belongs to the sweep that multiplies on the fp32 MFMA
         line["pct_fp32_mfma_peak"] = 100.0 * ft / PEAK_FP32_MFMA_TFLOPS
-        line["pct_fp32_mfma_peak_note"] = ("of the k-NN sweep with float32 tile products (roofline_fp32_products); the timed "
-                                           "default forms its products in 16 bits and is priced in `roofline`")
+        line["pct_fp32_mfma_peak_note"] = ("of the k-NN sweep with float32 tile products (roofline_fp32_products); the timed default "
+                                           + ("evaluates every pair" if every_pair else "forms its products in 16 bits") + " and is priced in `roofline`")
     # HBM traffic is not measurable from inside the run; it comes from the committed rocprofv3 counter runs
     # of this same workload (profiles/traffic.json: one entry per kernel, keyed by workload and kernel name,
     # FETCH_SIZE + WRITE_SIZE scaled by what the same counters read for a plain copy of known size)
@@ -260,7 +272,8 @@ def main():
             obj["traffic_unit"] = ent["per"]
             obj["traffic_kernel"] = ent["kernel"]
 
-    attach_traffic(line["roofline"], "knn_half" if half else "knn_sweep_split" if split else "knn_sweep")
+    if not every_pair:
+        attach_traffic(line["roofline"], "knn_half" if half else "knn_sweep_split" if split else "knn_sweep")
     if "roofline_fp32_products" in line:
         attach_traffic(line["roofline_fp32_products"], "knn_sweep")
     if not args.knn_only:
@@ -274,13 +287,14 @@ def main():
         cq = float(s0["connect_query_rows"])
         if cq > 0 and mean("ms_connect_kernels") > 0:
             ct = 2.0 * d * cq * N / (mean("ms_connect_kernels") * 1e-3) / 1e12
-            line["roofline_connect"] = {"kernel": "near_link: one pass per round, a search for the queries that are left" if half
+            line["roofline_connect"] = {"kernel": "near_link: one pass per round, a search for the queries that are left (direct_near_kernel, without "
+                                                  "products, where they are few)" if half
                                                   else "sweep_kernel (cross-component 1-NN)", "bound": "mfma",
                                         "achieved": ct, "peak": peak_tflops, "unit": "TFLOP/s",
                                         "frac": ct / peak_tflops, "traffic": None}
             # (the engine multiplies each queried row by all rows; beyond 128 columns its first round is one product for
             # both orders of a pair and the others are not, which no counter tells apart)
-            if not half or d <= 128:
+            if not half or (d <= 128 and not every_pair):
                 line["roofline_connect"]["frac_executed"] = (1.0 if half else products) * ct / peak_tflops
             attach_traffic(line["roofline_connect"], "connect_half" if half else "connect_sweeps_split" if split else "connect_sweeps")
 
