@@ -26,11 +26,13 @@ def same_lists(lib, X, k):
 
 
 # one tile and its edges, the workgroup sizes' edges, one wavefront's 64 queries, 16-column steps, both kernels (128 / 129
-# columns), whole and partial chunks of 64, every list width, one- and two-stage plans
+# columns), whole and partial chunks of 64, every list width, one- and two-stage plans; the fewest rows of every width that the engine
+# sees (the pairs of fewer are all evaluated, in direct_kernels.hip)
 @pytest.mark.parametrize("N,d,k", [
     (2, 3, 1), (64, 16, 63), (127, 17, 5), (128, 1, 8), (129, 15, 64), (255, 31, 9), (257, 33, 2), (385, 112, 64),
     (1025, 113, 16), (2047, 127, 33), (3000, 128, 1), (3001, 129, 7), (2500, 192, 64), (2600, 193, 17), (700, 321, 3),
     (8193, 64, 12), (33_000, 48, 40), (40_000, 200, 1), (66_001, 20, 31), (140_000, 130, 16),
+    (4480, 8, 64), (3841, 16, 9), (3073, 31, 33), (2689, 48, 2), (2305, 63, 64), (2049, 96, 17), (1793, 112, 5), (1793, 113, 16),
 ])
 def test_lists_at_the_edges(lib, N, d, k):
     print(f"half-precision lists N={N} d={d} k={k}", flush=True)
