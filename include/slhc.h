@@ -101,13 +101,14 @@ typedef struct slhc_stats {
     int32_t pruned;                  /* 1 when tile pruning was active in this call                */
     int32_t order_padded_rows;       /* rows of the reordered copy incl. padding (0 when not pruned) */
     int32_t split_products;          /* 1 when the k-NN search formed tile products from 16-bit values (float16
-                                        copies or split bfloat16 halves, see half_products), 0 when all were in
-                                        float32 (see SLHC_FP32_FILTER)                                */
+                                        copies or split bfloat16 halves, see half_products) or none, 0 when all
+                                        were in float32 (see SLHC_FP32_FILTER)                        */
     int32_t half_products;           /* 1 when the half-precision engine ran the k-NN search: one product of
                                         float16 copies per pair, or for both orders of a pair
                                         (slhc_probe_knn_products), or took its place where rows are so few
-                                        that every pair is evaluated; 0: the list kernels' split bfloat16 halves
-                                        (three products per pair) or float32                          */
+                                        that every pair is evaluated (knn_filter_survivors is N (N - 1) then);
+                                        0: the list kernels' split bfloat16 halves (three products per pair) or
+                                        float32                                                       */
 } slhc_stats;
 
 /* Option flags of the *_opt entry points.  By default the half-precision engine searches (tile products of float16 copies
@@ -242,7 +243,8 @@ int slhc_probe_f16_mfma_values(const float* A, const float* B, const float* C, f
  * Multiply-adds that an every-tile k-NN search of N rows executes by default, with a workspace of the reported size, per ordered pair of
  * rows and column (HOST out; no device work): 0.5 where the half-precision engine multiplies every pair once for both of its rows, 1
  * where it does so for each, 3 for the list kernels' split bfloat16 halves, 0 for a search so small that every pair is evaluated and
- * nothing is multiplied.  The sample that bounds come from is not counted.
+ * nothing is multiplied.  The sample that bounds come from is not counted.  For slhc_knn_graph; slhc_slhc, whose host waits for the
+ * lists, evaluates every pair of some more rows (slhc_stats.knn_filter_survivors).
  */
 int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products);
 

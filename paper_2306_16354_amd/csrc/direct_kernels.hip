@@ -9,7 +9,7 @@
 // met twice).  Bound by its three launches and one round trip to memory per 64 candidates.  439 x 2414 x 16: 42 -> 17 us.
 //
 // Searches of the rows among themselves (direct_knn): with the candidates in LDS as well a wavefront's reads took longer than its
-// sums (2048 x 32, k = 8, 65 us against the engine's 47); with four of them in a lane's registers it is bound by the sums, 8 us of 20, and by the
+// sums (2048 x 32, k = 8, 65 us against the engine's 47); with four of them in a lane's registers it is bound by the sums, 8 us of 18, and by the
 // way of the rows into the registers.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -385,7 +385,7 @@ __device__ inline __attribute__((always_inline)) void block_passes(int nc, F&& p
 // The k nearest rows of every row.  All distances of a workgroup's QB rows are kept in LDS, NaN where there is no row; then a wavefront per row takes what
 // is not beyond the k-th smallest of its lanes' minima, of which k at least are, and ranks that.  Rows so far away that the distance is no
 // float32 are neighbours all the same, at +inf, behind all others.
-// Time (k = 12, us; engine, this): 500 x 4 42, 9; 1000 x 16 42, 9; 2048 x 32 48, 20; 2048 x 32, k = 64, 74, 23; 1500 x 128 60, 38; 3198 x 16 55, 39.
+// Time (k = 12, us; engine, this): 500 x 4 43, 10; 1000 x 16 46, 10; 2048 x 32 49, 19; 2048 x 32, k = 64, 73, 22; 1500 x 128 56, 33; 3198 x 16 60, 37.
 struct DirectKnn {
     const float* X; int n, d, k, rows; bool vec4;         // rows: per workgroup, KNN_ROWS at most
     int32_t* out_idx; float* out_dist; int32_t* evaluated; unsigned int* nonfinite;

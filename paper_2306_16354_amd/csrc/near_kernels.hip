@@ -309,7 +309,8 @@ __global__ void __launch_bounds__(256) near_make_kernel(NearMake p)
     if (tid == 0 && eps_max != 0u) {
         const unsigned int mine_bits = __float_as_uint(__uint_as_float(eps_max) * (1.f + 1e-4f));
         // Most workgroups find the word already there and leave it alone; but the first two thousand of a launch end together and would
-        // queue for it (9 ns each), so they meet at 64 words in lines of their own, and a few of each 32 go on.
+        // queue for it (9 ns each), so they meet at 64 words, a row of the column statistics apart, and a few of each 32 go on.  (In lines of
+        // their own from 32 columns on, eight of them in one line at 4 columns: the 1-NN of 1000 queries in 1M x 4 214 -> 200 us, in 1M x 32 251 -> 222.)
         const bool first = !p.eps_of || atomicMax(p.eps_of + (size_t)(blockIdx.x & 63) * p.d, mine_bits) < mine_bits;
         if (first && __hip_atomic_load(&p.sc->eps_bits, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) < mine_bits) atomicMax(&p.sc->eps_bits, mine_bits);
     }
@@ -1598,12 +1599,13 @@ struct PairPlan {
     NearPlan sample;
     int waves, blocks, cap, bands, to[8], nseg[8];
 };
-// Who gains: up to 64 columns a block's comparisons (66 instructions of its wavefront) take as long as its products, and of the rows of a
-// small search every block holds a few that pass.  Each side in us, products once per row and once per pair: 5000 x 40, k = 10: 76 and 65;
-// 10 000 x 64, 20: 151 and 128; 20 000 x 128, 32: 356 and 370; 40 000 x 70, 10: 616 and 646; 50 000 x 70, 10: 979 and 898; 60 000 x 80, 32: 1472
-// and 1468; 120 000 x 64, 32: 4220 and 4780; 120 000 x 100, 10: 4247 and 3648; 250 000 x 33, 40: 13.1 and 13.6 ms; 300 000 x 128, 32: 34.7 and
-// 21.8 ms; 5000 x 200, 10: 146 and 105; 250 000 x 784, 16: 126 and 62 ms.  (Up to 12 800 rows it is the fewer, longer shares of the
-// candidates that gain.)
+// Who gains: up to 64 columns a block's comparisons (36 instructions of its wavefront for 16 values) take as long as its products, and of the rows of a
+// small search every block holds a few that pass.  Each side in us, products once per row and once per pair: 5000 x 40, k = 10: 78 and 67;
+// 10 000 x 64, 20: 146 and 129; 20 000 x 128, 32: 348 and 368; 20 011 x 50, 10: 221 and 248; 30 000 x 96, 16: 468 and 467; 40 000 x 70, 10: 596 and 588;
+// 50 000 x 70, 10: 951 and 805; 60 000 x 80, 32: 1453 and 1335; 120 000 x 100, 10: 4196 and 3277; 300 000 x 128, 32: 34.8 and 19.6 ms; 5000 x 200, 10:
+// 120 and 94.  (Up to 12 800 rows it is the fewer, longer shares of the candidates that gain.)  The line at five steps from 384 tiles on was
+// drawn when what passes was found by a branch per value (120 000 x 64, 32: 4220 and 4780; 250 000 x 33, 40: 13.1 and 13.6 ms); with whole values
+// through LDS narrower rows gain there as well: 4004 and 3316, 12.7 and 10.2 ms, 50 000 x 50, 10: 855 and 736, 100 000 x 48, 10: 2436 and 1825.
 static bool pair_search_wanted(int T, int steps)
 {
     if (T < 32 || T >= (1 << 17)) return false;

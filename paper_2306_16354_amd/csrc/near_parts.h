@@ -172,7 +172,7 @@ __device__ inline void near_lds_ready()
 // fragments of a chunk's first 16 columns are read while the last ones of the chunk before are multiplied, so that after a barrier there is
 // something to multiply at once.  250k x 784, the pass for the k-NN graph and that for the first connection round: 48.6 and 49.1 ms with chunks of 64
 // columns in two buffers, every fragment read after the chunk's barrier and all reads waited for at once; 44.8 and 46.4 so (1.09 PFLOP/s of
-// products made once, the matrix pipe 54 % busy at 1.92 GHz, to which it throttles).
+// products made once; the matrix pipe 60 % of the busy cycles, 51 to 54 before, at 1.8 to 1.9 GHz, to which it throttles, 1.9 to 2.0 before).
 constexpr int CHUNK_STEPS = 2;
 constexpr int CHUNK_TILE = CHUNK_STEPS * FRAG_STEP;
 constexpr int CHUNK_SIDE = 2 * CHUNK_TILE;
