@@ -723,6 +723,10 @@ static long long direct_step(int nq, int rows) { return 130 + 26 * nq + (long lo
 // rows.  Us a clustering of one blob, which has nothing to connect, k = 12, engine and this, below the line and above it: 8 columns 4873 rows 314 and 310,
 // 5123 318 and 334; 16 columns 4531 305 and 294, 4724 308 and 329; 32 columns 2919 248 and 239, 3107 254 and 270; 48 columns 2958 259 and 257, 3095 255 and
 // 284; 64 columns 2500 237 and 240, 2628 281 and 292; 96 columns 1983 222 and 216, 2097 236 and 263; 128 columns 2026 227 and 227, 2112 274 and 308.
+// Lists of 40 others and more the engine collects in half as many segments (near_plan), on half the chip: 20 us more.  k = 36 and 48: 5000 x 16 373 and 369,
+// 402 and 380; 3800 x 24 286 and 291, 310 and 290; 3500 x 32 297 and 311, 312 and 309; 2700 x 64 268 and 277, 285 and 276; k = 40: 5900 x 8 409 and 387; but
+// 2400 x 96 263 and 280, 2100 x 128 266 and 294.  Up to 8 columns, where rows are most, its selection takes the engine as much longer
+// from 24 others on (5300 x 8: k = 8 321 and 324, 24 350 and 338, 36 385 and 364).
 // Calls among others: instructions of a lane, two per feature and about 24 for the rest of a pair and its share of the selection.  700 M (k = 12, us): 4183 x 8
 // 67 and 51, 2820 x 32 56 and 42, 2415 x 40 56 and 50, 2145 x 64 58 and 53, 1581 x 128 54 and 46; 800 M: 3779 x 16 60 and 50, 3015 x 32 55 and 42,
 // 2581 x 40 56 and 58, 2294 x 64 57 and 54; 900 M: 4743 x 8 67 and 65, 3198 x 32 60 and 67, 2738 x 40 57 and 59, 2041 x 96 53 and 41.
@@ -732,7 +736,8 @@ bool direct_knn_wanted(long long n, int d, int k, bool waited_for)
     const int nq = direct_quads(d), rows = direct_knn_rows(n, d), cus = direct_cus();
     if (rows < 1 || (!waited_for && n * n * (8LL * nq + 24) > 800000000LL)) return false;
     const long long rounds = ((n + rows - 1) / rows + cus - 1) / cus, steps = (n + BLOCK - 1) / BLOCK;
-    return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6;
+    const long long longer = d <= 64 && k >= (d <= 8 ? 24 : 40) ? 5200 : 0;
+    return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6 + longer;
 }
 
 hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, int32_t* evaluated, unsigned int* nonfinite, hipStream_t s)

@@ -169,12 +169,14 @@ def test_evaluated_pairs_are_counted(lib, N, d, all_pairs):
     assert count == N * (N - 1) if all_pairs else 2 * N <= count < 100 * N
 
 
-# the last clustering of a width that evaluates every pair, and the first that does not (4100 x 32 took 334 us instead of 275 with all pairs)
+# the last clustering of a width that evaluates every pair, and the first that does not (4100 x 32 took 334 us instead of 275 with all pairs); where lists
+# are long the engine takes longer (5000 x 16, k = 48, 402 us instead of 380)
 @pytest.mark.gpu
-@pytest.mark.parametrize("d,most", [(8, 5120), (16, 4608), (32, 3072), (48, 3072), (64, 2560), (96, 2048), (128, 2048)])
-def test_last_clusterings_of_all_pairs(lib, d, most):
-    print(f"last clustering of all pairs, {most} x {d}", flush=True)
-    counts = [lib.slhc(rows(N, d, N), 4, prune=False)["stats"]["knn_filter_survivors"] for N in (most, most + 1)]
+@pytest.mark.parametrize("d,k,most", [(8, 4, 5120), (16, 4, 4608), (32, 4, 3072), (48, 4, 3072), (64, 4, 2560), (96, 4, 2048), (128, 4, 2048), (8, 23, 5120), (8, 24, 5632),
+                                      (9, 39, 4608), (16, 40, 5120), (32, 39, 3072), (32, 64, 3840), (64, 40, 3072), (65, 64, 2048)])
+def test_last_clusterings_of_all_pairs(lib, d, k, most):
+    print(f"last clustering of all pairs, {most} x {d}, k={k}", flush=True)
+    counts = [lib.slhc(rows(N, d, N), k, prune=False)["stats"]["knn_filter_survivors"] for N in (most, most + 1)]
     assert counts[0] == most * (most - 1) and counts[1] < most * most // 4
 
 
