@@ -388,7 +388,7 @@ __device__ inline __attribute__((always_inline)) void block_passes(int nc, F&& p
 // Time (k = 12, us; engine, this): 500 x 4 43, 10; 1000 x 16 46, 10; 2048 x 32 49, 19; 2048 x 32, k = 64, 73, 22; 1500 x 128 56, 33; 3198 x 16 60, 37.
 struct DirectKnn {
     const float* X; int n, d, k, rows; bool vec4;         // rows: per workgroup, KNN_ROWS at most
-    int32_t* out_idx; float* out_dist; int32_t* evaluated; unsigned int* nonfinite;
+    int32_t* out_idx; float* out_dist; unsigned long long* pairs; unsigned int* nonfinite;
 };
 constexpr int KNN_ROWS = 8, KNN_KEEP = 512;       // (a wavefront each); pairs that a row keeps to be ranked
 
@@ -415,6 +415,7 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
     const int q0 = blockIdx.x * p.rows;
     BlockStream<NQ> stream;
     stream.start(BlockRows{p.X, p.n, p.d, p.rows}, tile);
+    if (p.pairs && blockIdx.x == 0 && tid == 0) atomicAdd(p.pairs, (unsigned long long)p.n * (unsigned long long)(p.n - 1));
     for (int i = tid; i < p.rows * NQ; i += BLOCK) qs[i] = direct_quad(p.X, q0 + i / NQ < p.n ? q0 + i / NQ : -1, 4 * (i % NQ), p.d, p.vec4);
     if (wave < p.rows) {
         const float norm = direct_norm(p.X, q0 + wave < p.n ? q0 + wave : -1, p.d, lane);
@@ -555,7 +556,6 @@ __global__ void __launch_bounds__(BLOCK) direct_knn_kernel(DirectKnn p)
         }
     }
     for (int j = kept + lane; j < p.k; j += 64) { p.out_idx[(size_t)row * p.k + j] = -1; p.out_dist[(size_t)row * p.k + j] = INF; }
-    if (p.evaluated && lane == 0) p.evaluated[row] = fine ? p.n - 1 : 0;
 }
 
 // The nearest row (of another colour): as direct_knn_kernel, with one (distance, row) per query in LDS instead of all distances.  A workgroup has a panel of
@@ -740,11 +740,11 @@ bool direct_knn_wanted(long long n, int d, int k, bool waited_for)
     return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6 + longer;
 }
 
-hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, int32_t* evaluated, unsigned int* nonfinite, hipStream_t s)
+hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, unsigned long long* pairs, unsigned int* nonfinite, hipStream_t s)
 {
     const int rows = direct_knn_rows(n, d);
     if (rows < 1) return hipErrorInvalidValue;
-    const DirectKnn p{X, n, d, k, rows, d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0, out_idx, out_dist, evaluated, nonfinite};
+    const DirectKnn p{X, n, d, k, rows, d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0, out_idx, out_dist, pairs, nonfinite};
     return direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
         constexpr int NQ = decltype(quads)::value;
         const size_t lds = direct_knn_bytes(NQ, rows, n);

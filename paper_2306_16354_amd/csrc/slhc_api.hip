@@ -1148,12 +1148,9 @@ int run_knn_near(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_i
         }
         if (ev_norm) { HIP_TRY(hipEventRecord(ev_norm->a, stream)); HIP_TRY(hipEventRecord(ev_norm->b, stream)); }
         if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->a, stream));
-        HIP_TRY(slhc::direct_knn(X, (int)N, d, k, nbr_idx, nbr_dist, evaluated, counted ? reinterpret_cast<unsigned int*>(counters + 4) : nullptr, stream));
+        HIP_TRY(slhc::direct_knn(X, (int)N, d, k, nbr_idx, nbr_dist, counted ? counters : nullptr,
+                                 counted ? reinterpret_cast<unsigned int*>(counters + 4) : nullptr, stream));
         if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->b, stream));
-        if (evaluated) {
-            hipLaunchKernelGGL(k_sum_words, dim3(64), dim3(256), 0, stream, evaluated, (int)N, counters);
-            HIP_TRY(hipGetLastError());
-        }
         return SLHC_OK;
     }
     if (ev_norm) HIP_TRY(hipEventRecord(ev_norm->a, stream));
@@ -1239,11 +1236,8 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         if (ev_order) { HIP_TRY(hipEventRecord(ev_order->a, stream)); HIP_TRY(hipEventRecord(ev_order->b, stream)); }
         ws.near_done = true;
         ws.near_ready = !slhc::direct_knn_wanted(N, d, k, pruned_out != nullptr);
-        // a word per row for the counts: the split copy's half norms, which nobody reads; where every pair is evaluated the rows may have a
-        // width without such a copy, and `hn` is not made
-        float* counts = !ev_sweep ? nullptr : ws.near_ready ? ws.hn_split : ws.hn;
         return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream, pruned_out != nullptr,
-                            reinterpret_cast<int32_t*>(counts), ev_norm, ev_sweep);
+                            ev_sweep ? reinterpret_cast<int32_t*>(ws.hn_split) : nullptr, ev_norm, ev_sweep);
     }
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(ws.counters), 64);
     HIP_TRY(hipGetLastError());
