@@ -102,26 +102,34 @@ __device__ inline unsigned int lds_word(const void* at)
 {
     return (unsigned int)(uintptr_t)(__attribute__((address_space(3))) const void*)at;
 }
-// The records' values, four records at a time, against the limits of both rows; tile_limit: LDS, of the tile's candidates.  (Reads past the compiler
-// as well, see pair_push.)
+// The records' values, twice four records at a time, against the limits of both rows; tile_limit: LDS, of the tile's candidates.  (Reads past the compiler
+// as well, see pair_push.)  Where lists are long and rows few, most lanes of every block hold something, and it is bound by its waits for LDS: with four
+// records at a time, and the queue emptied whenever it was full, 4500 x 128, k = 64, took 139 us, 12 000 x 128 273, 300 000 x 128, k = 32, 24.6 ms; 129,
+// 256, 24.4 so.  (Values looked for in registers there, as before whole values went to LDS: 130, 277 and, for its registers and code, 26.7.)
 __device__ inline void pair_sift(PairQueue& w, const NearPairs& p, int q0, const unsigned char* tile_limit)
 {
     const int lane = threadIdx.x & 63;
     const unsigned int values = lds_word(w.at + QUEUE) + lane * 4, words = lds_word(w.at + QUEUE) + RECORDS * 64 + (lane >> 4) * 16;
 #pragma unroll 1
-    for (int at = 0; at < w.records; at += 4) {
-        float x, limit;
-        v4f word;
-        asm volatile("ds_read_b32 %0, %2\n\tds_read_b128 %1, %3\n\ts_waitcnt lgkmcnt(0)"
-                     : "=&v"(x), "=&v"(word) : "v"(values + at * 64), "v"(words + at * 16) : "memory");
-        const unsigned int code = __float_as_uint(word[0]) + ((((lane & 12u) << 1) | (lane & 3u)) << 8);
-        asm volatile("ds_read_b32 %0, %1\n\ts_waitcnt lgkmcnt(0)" : "=&v"(limit) : "v"(lds_word(tile_limit) + ((code >> 6) & 508u)) : "memory");
-        const bool pass = at + (lane >> 4) < w.records && (x >= word[1] || x - limit >= word[2]);
-        const unsigned long long m = __ballot(pass);
-        if (w.n > QUEUE - 64) pair_finish(w, p, q0);
-        const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
-        if (pass) pair_push(w.at + w.n + pre, __float_as_uint(x - word[3]), code);
-        w.n += __popcll(m);
+    for (int at = 0; at < w.records; at += 8) {
+        float x[2], limit[2];
+        v4f word[2];
+        asm volatile("ds_read_b32 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b32 %2, %4 offset:256\n\tds_read_b128 %3, %5 offset:64\n\ts_waitcnt lgkmcnt(0)"
+                     : "=&v"(x[0]), "=&v"(word[0]), "=&v"(x[1]), "=&v"(word[1]) : "v"(values + at * 64), "v"(words + at * 16) : "memory");
+        const unsigned int place = (((lane & 12u) << 1) | (lane & 3u)) << 8;
+        const unsigned int code[2] = {__float_as_uint(word[0][0]) + place, __float_as_uint(word[1][0]) + place};
+        asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(limit[0]), "=&v"(limit[1])
+                     : "v"(lds_word(tile_limit) + ((code[0] >> 6) & 508u)), "v"(lds_word(tile_limit) + ((code[1] >> 6) & 508u)) : "memory");
+#pragma unroll 1
+        while (w.n > QUEUE - 128) pair_turn(w, p, q0, 64);
+#pragma unroll
+        for (int i = 0; i < 2; ++i) {
+            const bool pass = at + 4 * i + (lane >> 4) < w.records && (x[i] >= word[i][1] || x[i] - limit[i] >= word[i][2]);
+            const unsigned long long m = __ballot(pass);
+            const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
+            if (pass) pair_push(w.at + w.n + pre, __float_as_uint(x[i] - word[i][3]), code[i]);
+            w.n += __popcll(m);
+        }
     }
     w.records = 0;
 }

@@ -39,6 +39,21 @@ def test_lists(lib, N, d, k):
     assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
 
 
+# blocks of which every lane holds pairs that pass (one blob, long lists) or every pair does (half the rows one point): more than are looked through at a time, and
+# than wait for their slots
+@pytest.mark.parametrize("kind", ["blob", "point"])
+@pytest.mark.parametrize("N,d,k", [(3969, 33, 64), (4500, 64, 50), (6500, 100, 64), (12_000, 128, 64), (4300, 129, 64), (4500, 320, 39)])
+def test_crowded_blocks(lib, kind, N, d, k):
+    print(f"pairs once, crowded, {kind}, N={N} d={d} k={k}", flush=True)
+    assert lib.probe_knn_products(N, d, k) == 0.5
+    X = torch.randn((N, d), generator=torch.Generator(device="cuda").manual_seed(N), device="cuda")
+    if kind == "point":
+        X[::2] = X[0]
+    want, got = lib.knn_graph(X, k, fp32_filter=True), lib.knn_graph(X, k)
+    torch.cuda.synchronize()
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+
+
 # 9 to 13 steps of 16 columns: chunks of two with one step or two in the last, places of rows with up to three empty steps; both orders of
 # every pair (fewer rows) and one, an odd number of tiles; 1-NN, of few queries with several segments
 @pytest.mark.parametrize("d", [129, 145, 161, 177, 193, 208])
