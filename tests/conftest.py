@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -10,6 +11,13 @@ if ROOT not in sys.path:
 
 def pytest_configure(config):
     config.addinivalue_line("markers", "gpu: needs a real MI355X")
+
+
+@pytest.fixture(scope="module", autouse=True)
+def leave_no_cycles():
+    """Tensors held by reference cycles (frames of errors that were asked for) go before the next module, whose tests may count what is allocated."""
+    yield
+    gc.collect()
 
 
 def load_golden(name):
