@@ -13,9 +13,9 @@ hipError_t direct_1nn(const float* Xq, int m, int nq_rows, const int32_t* q_rows
                       int32_t* out_idx, float* out_dist, unsigned long long* keys, hipStream_t s);
 
 // The k nearest other rows of every row, in one launch.  pairs (optional): what is evaluated is added; nonfinite (optional): set where a row is not finite.
-// (waited_for: the caller waits for the lists)
-bool direct_knn_wanted(long long n, int d, int k, bool waited_for);
-hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, unsigned long long* pairs, unsigned int* nonfinite, hipStream_t s);
+// direct_knn_wanted: rows per workgroup where it is what searches, else 0 (waited_for: the caller waits for the lists).
+int direct_knn_wanted(long long n, int d, int k, bool waited_for);
+hipError_t direct_knn(const float* X, int n, int d, int k, int rows, int32_t* out_idx, float* out_dist, unsigned long long* pairs, unsigned int* nonfinite, hipStream_t s);
 
 // As direct_1nn, by blocks of pairs in registers: in one launch where the queries alone occupy the chip; pairs (optional): what is evaluated is added.
 bool direct_near_wanted(long long m, long long nc, int d);

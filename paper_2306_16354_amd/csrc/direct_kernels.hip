@@ -706,9 +706,8 @@ static int direct_cus()
 }
 
 // Rows per workgroup, 0: none fit.  Workgroups of one row more each where that saves a round of them.
-static int direct_knn_rows(long long n, int d)
+static int direct_knn_rows(long long n, int nq, int cus)
 {
-    const int nq = direct_quads(d), cus = direct_cus();
     for (int rounds = 1; rounds <= 64; ++rounds) {
         const long long rows = (n + (long long)cus * rounds - 1) / ((long long)cus * rounds);
         if (rows <= KNN_ROWS && direct_knn_bytes(nq, (int)rows, (int)n) <= DIRECT_LDS) return (int)rows;
@@ -730,20 +729,19 @@ static long long direct_step(int nq, int rows) { return 130 + 26 * nq + (long lo
 // Calls among others: instructions of a lane, two per feature and about 24 for the rest of a pair and its share of the selection.  700 M (k = 12, us): 4183 x 8
 // 67 and 51, 2820 x 32 56 and 42, 2415 x 40 56 and 50, 2145 x 64 58 and 53, 1581 x 128 54 and 46; 800 M: 3779 x 16 60 and 50, 3015 x 32 55 and 42,
 // 2581 x 40 56 and 58, 2294 x 64 57 and 54; 900 M: 4743 x 8 67 and 65, 3198 x 32 60 and 67, 2738 x 40 57 and 59, 2041 x 96 53 and 41.
-bool direct_knn_wanted(long long n, int d, int k, bool waited_for)
+int direct_knn_wanted(long long n, int d, int k, bool waited_for)
 {
-    if (d > 128 || k > 64 || n > 16384) return false;
-    const int nq = direct_quads(d), rows = direct_knn_rows(n, d), cus = direct_cus();
-    if (rows < 1 || (!waited_for && n * n * (8LL * nq + 24) > 800000000LL)) return false;
+    if (d > 128 || k > 64 || n > 16384) return 0;
+    const int nq = direct_quads(d), cus = direct_cus(), rows = direct_knn_rows(n, nq, cus);
+    if (rows < 1 || (!waited_for && n * n * (8LL * nq + 24) > 800000000LL)) return 0;
     const long long rounds = ((n + rows - 1) / rows + cus - 1) / cus, steps = (n + BLOCK - 1) / BLOCK;
     const long long longer = d <= 64 && k >= (d <= 8 ? 24 : 40) ? 5200 : 0;
-    return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6 + longer;
+    return rounds * steps * direct_step(nq, rows) <= 11000 + n + n / 6 + longer ? rows : 0;
 }
 
-hipError_t direct_knn(const float* X, int n, int d, int k, int32_t* out_idx, float* out_dist, unsigned long long* pairs, unsigned int* nonfinite, hipStream_t s)
+hipError_t direct_knn(const float* X, int n, int d, int k, int rows, int32_t* out_idx, float* out_dist, unsigned long long* pairs, unsigned int* nonfinite, hipStream_t s)
 {
-    const int rows = direct_knn_rows(n, d);
-    if (rows < 1) return hipErrorInvalidValue;
+    if (rows < 1 || rows > KNN_ROWS || d > 128 || direct_knn_bytes(direct_quads(d), rows, n) > DIRECT_LDS) return hipErrorInvalidValue;
     const DirectKnn p{X, n, d, k, rows, d % 4 == 0 && (reinterpret_cast<uintptr_t>(X) & 15) == 0, out_idx, out_dist, pairs, nonfinite};
     return direct_by_quads(direct_quads(d), [&](auto quads) -> hipError_t {
         constexpr int NQ = decltype(quads)::value;

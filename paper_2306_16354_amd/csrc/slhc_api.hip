@@ -1136,19 +1136,20 @@ int build_order(const float* X, int64_t N, int32_t d, const float* hn, const uns
 
 // The every-tile k-NN graph by the half-precision engine: any d, no padded copy, same lists as the list kernels.
 bool near_wanted(const NearWs& near, uint32_t flags) { return near.ok && !(flags & (SLHC_FP32_FILTER | SLHC_PANEL_ORDER)); }
-// (counted: somebody reads the counters, `hn` and the float16 copy may be missing afterwards all the same, see ws.near_ready)
+// (direct: what direct_knn_wanted says; counted: somebody reads the counters, `hn` and the float16 copy may be missing afterwards all the same, see
+// ws.near_ready)
 int run_knn_near(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, float* nbr_dist, unsigned long long* counters,
-                 float* hn, const NearWs& near, hipStream_t stream, bool counted, int32_t* evaluated = nullptr, EventPair* ev_norm = nullptr,
+                 float* hn, const NearWs& near, hipStream_t stream, int direct, bool counted, int32_t* evaluated = nullptr, EventPair* ev_norm = nullptr,
                  EventPair* ev_sweep = nullptr)
 {
-    if (slhc::direct_knn_wanted(N, d, k, counted)) {
+    if (direct > 0) {
         if (counted) {
             hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(counters), 64);
             HIP_TRY(hipGetLastError());
         }
         if (ev_norm) { HIP_TRY(hipEventRecord(ev_norm->a, stream)); HIP_TRY(hipEventRecord(ev_norm->b, stream)); }
         if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->a, stream));
-        HIP_TRY(slhc::direct_knn(X, (int)N, d, k, nbr_idx, nbr_dist, counted ? counters : nullptr,
+        HIP_TRY(slhc::direct_knn(X, (int)N, d, k, direct, nbr_idx, nbr_dist, counted ? counters : nullptr,
                                  counted ? reinterpret_cast<unsigned int*>(counters + 4) : nullptr, stream));
         if (ev_sweep) HIP_TRY(hipEventRecord(ev_sweep->b, stream));
         return SLHC_OK;
@@ -1235,8 +1236,9 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
         if (pruned_out) *pruned_out = false;
         if (ev_order) { HIP_TRY(hipEventRecord(ev_order->a, stream)); HIP_TRY(hipEventRecord(ev_order->b, stream)); }
         ws.near_done = true;
-        ws.near_ready = !slhc::direct_knn_wanted(N, d, k, pruned_out != nullptr);
-        return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream, pruned_out != nullptr,
+        const int direct = slhc::direct_knn_wanted(N, d, k, pruned_out != nullptr);
+        ws.near_ready = direct == 0;
+        return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, ws.counters, ws.hn, ws.near, stream, direct, pruned_out != nullptr,
                             ev_sweep ? reinterpret_cast<int32_t*>(ws.hn_split) : nullptr, ev_norm, ev_sweep);
     }
     hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, stream, reinterpret_cast<uint32_t*>(ws.counters), 64);
@@ -1593,7 +1595,7 @@ int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products)
         const int32_t dw = working_columns(N, d);
         const KnnWs ws(nullptr, N, dw, true, k, false);
         const size_t pairs = slhc::near_pairs_bytes(N, dw, k + 1);
-        *products = !ws.near.ok ? 3.0 : slhc::direct_knn_wanted(N, d, k, false) ? 0.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
+        *products = !ws.near.ok ? 3.0 : slhc::direct_knn_wanted(N, d, k, false) > 0 ? 0.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
         return SLHC_OK;
     });
 }
@@ -1652,7 +1654,8 @@ int slhc_knn_graph_static(const float* X, int64_t N, int32_t d, int32_t k, int32
             NearWs near;
             near.carve(c, N, 0, d, k + 1, false, STATIC_SCRATCH_BYTES);
             if (near.ok && c.off <= STATIC_SCRATCH_BYTES)
-                return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream), false);
+                return run_knn_near(X, N, d, k, nbr_idx, nbr_dist, counters, hn, near, static_cast<hipStream_t>(stream),
+                                    slhc::direct_knn_wanted(N, d, k, false), false);
         }
         KnnWs ws(ptr, N, d, false, 0, false);       // counters (cleared by run_knn) + half norms (all N written)
         if (ws.bytes > STATIC_SCRATCH_BYTES) { set_err("scratch layout %zu > %zu bytes", ws.bytes, STATIC_SCRATCH_BYTES); return SLHC_INTERNAL; }
@@ -2171,7 +2174,7 @@ int slhc_slhc_opt(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_
         if (workspace_bytes < need) { set_err("workspace %zu < %zu bytes", workspace_bytes, need); return SLHC_WORKSPACE_TOO_SMALL; }
         // Where every pair is evaluated the list kernels see a panel or two at most: the rows as they are.  (Without an engine in the workspace
         // they see all of them.)
-        if (!(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true) &&
+        if (!(flags & (SLHC_PRUNE | SLHC_FP32_FILTER | SLHC_PANEL_ORDER)) && slhc::direct_knn_wanted(N, d, k, true) > 0 &&
             SlhcWs(nullptr, N, d, k, true, workspace_bytes).knn->near.ok) { dw = d; head = 0; }
         const float* X_given = X;
         if (dw != d) {
