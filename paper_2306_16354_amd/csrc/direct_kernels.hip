@@ -772,11 +772,13 @@ static NearSplit direct_near_split(int m, int nc, int d)
     long long least = 0;
     for (int rows = 1; rows <= NEAR_ROWS; ++rows) {
         const int panels = (m + rows - 1) / rows;
-        int segments = panels < cus ? cus / panels : 1;
-        const int per = (steps + segments - 1) / segments;
-        segments = (steps + per - 1) / per;
-        const long long time = (long long)((panels + cus - 1) / cus) * per * direct_step(nq, rows) + (segments > 1 ? 3000 : 0);
-        if (rows == 1 || time < least) { least = time; best = NearSplit{rows, segments, per * BLOCK}; }
+        // all candidates, or as many segments as there are CUs for
+        for (int most = panels < cus ? cus / panels : 1;; most = 1) {
+            const int per = (steps + most - 1) / most, segments = (steps + per - 1) / per;
+            const long long time = (long long)((panels + cus - 1) / cus) * per * direct_step(nq, rows) + (segments > 1 ? 3000 : 0);
+            if (best.rows == 0 || time < least) { least = time; best = NearSplit{rows, segments, per * BLOCK}; }
+            if (most == 1) break;
+        }
     }
     return best;
 }
