@@ -6,7 +6,7 @@
 // features, sixteen chains of four features each, the chains of either half added in a tree.
 //
 // 1-NN searches of few queries (direct_1nn): the candidates of a workgroup pass through LDS, 16 bytes of every row side by side (no bank is
-// met twice).  Bound by its three launches and one round trip to memory per 64 candidates.  439 x 2414 x 16: 42 -> 17 us.
+// met twice).  Bound by its three launches and one round trip to memory per 64 candidates.  439 x 2414 x 16: 42 -> 13 us.
 //
 // Searches of the rows among themselves (direct_knn): with the candidates in LDS as well a wavefront's reads took longer than its
 // sums (2048 x 32, k = 8, 65 us against the engine's 47); with four of them in a lane's registers it is bound by the sums, 8 us of 18, and by the
@@ -174,18 +174,25 @@ __global__ void __launch_bounds__(64 * WAVES) direct_1nn_kernel(Direct1nn p)
         }
         if (v < best[q]) { best[q] = v; at[q] = cand; }              // (ascending candidates: the smallest index of equals)
     });
+    // The segments of a panel end together, and queue for its queries' words: they are met by one instruction for the eight of them, not by one each
+    // (us on the GPU, one each after reductions through LDS, one each after vector instructions, by which more end at once, this: 440 x 2678 x 30 18.1, 18.5,
+    // 17.7; 1432 x 2103 x 12 18.2, 19.1, 18.5; 1000 x 3000 x 20 20.3, 19.8, 19.4; 100 x 30 000 x 16 30.4, 30.0, 19.9; 20 x 100 000 x 6 -, 54.6, 18.7).
+    unsigned long long* keys = reinterpret_cast<unsigned long long*>(tile);
+    __syncthreads();                                // the last tile is used up
 #pragma unroll
     for (int q = 0; q < QW1; ++q) {
-        const int i = (panel * WAVES + wave) * QW1 + q;
-        unsigned long long key = at[q] >= 0 && row[q] >= 0 && norm[q] < INF ? ((unsigned long long)__float_as_uint(best[q]) << 32) | (unsigned int)at[q] : ~0ull;
-        key = wave_min(key);
-        if (lane == 0 && i < p.m) {
-            if (p.segments > 1) { if (key != ~0ull) atomicMin(p.keys + i, key); }
-            else {
-                p.out_idx[i] = key == ~0ull ? -1 : (int32_t)(unsigned int)key;
-                p.out_dist[i] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
-            }
-        }
+        const unsigned long long key =
+            wave_min(at[q] >= 0 && row[q] >= 0 && norm[q] < INF ? ((unsigned long long)__float_as_uint(best[q]) << 32) | (unsigned int)at[q] : ~0ull);
+        if (lane == 0) keys[wave * QW1 + q] = key;
+    }
+    __syncthreads();
+    const int i = panel * WAVES * QW1 + threadIdx.x;
+    if (threadIdx.x >= WAVES * QW1 || i >= p.m) return;
+    const unsigned long long key = keys[threadIdx.x];
+    if (p.segments > 1) { if (key != ~0ull) atomicMin(p.keys + i, key); }
+    else {
+        p.out_idx[i] = key == ~0ull ? -1 : (int32_t)(unsigned int)key;
+        p.out_dist[i] = key == ~0ull ? INF : __uint_as_float((unsigned int)(key >> 32));
     }
 }
 __global__ void __launch_bounds__(256) direct_fill_kernel(unsigned long long* __restrict__ keys, int m)
@@ -647,11 +654,11 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
 // Where every pair is evaluated instead of the engine's search, measured on both sides of the lines (us a call among others, this
 // against the engine).  What the operations cost is one part, what it takes to bring every candidate once to each panel of eight
 // queries, 64 at a time, the other; it grows with the candidates, and with their width where a step is more than one slab.
-//   up to 100 M operations: 1250 x 4000 x 4 22 and 45, 178 x 4000 x 64 24 and 39, 22 x 32 000 x 64 35 and 45, 64 x 50 000 x 8 37 and 43;
-//     the worst of 40 shapes 24 x 8000 x 250 78 and 72, 20 x 100 000 x 6 57 and 50;
-//   up to 200 M: 1136 x 4000 x 16 25 and 45, 694 x 4000 x 30 27 and 47, 173 x 16 000 x 30 32 and 48, 142 x 32 000 x 16 33 and 38; the worst
-//     of 33 shapes up to 65 536 candidates 43 x 64 000 x 30 55 and 49; beyond those 32 x 111 642 x 21 70 and 57, 16 x 300 000 x 16 88 and 85;
-//   300 M: even on the whole (1704 x 4000 x 16 37 and 47, 3750 x 4000 x 4 47 and 50, 360 x 32 000 x 7 45 and 41, 73 x 8000 x 250 94 and 76).
+//   up to 100 M operations: 1250 x 4000 x 4 20 and 45, 178 x 4000 x 64 23 and 39, 22 x 32 000 x 64 23 and 45, 64 x 50 000 x 8 19 and 43,
+//     20 x 100 000 x 6 19 and 50; the worst of 40 shapes 24 x 8000 x 250 66 and 72;
+//   up to 200 M: 1136 x 4000 x 16 23 and 45, 694 x 4000 x 30 25 and 47, 173 x 16 000 x 30 26 and 48, 142 x 32 000 x 16 24 and 38, 43 x 64 000 x 30 29 and 49.
+// The lines were drawn when the segments met at each query's word by itself: beyond 65 536 candidates 32 x 111 642 x 21 took 70 and 57,
+// 16 x 300 000 x 16 88 and 85; of 300 M 1704 x 4000 x 16 37 and 47, 3750 x 4000 x 4 47 and 50, 360 x 32 000 x 7 45 and 41, 73 x 8000 x 250 94 and 76.
 bool direct_1nn_wanted(long long m, long long nc, int d)
 {
     return m <= (1LL << 20) && nc <= (1LL << 24) && m * nc * (2LL * d + 12) <= (nc <= 65536 ? 200000000LL : 100000000LL);

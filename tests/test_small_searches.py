@@ -231,3 +231,30 @@ def test_few_queries_take_their_share(lib, N, d, k, limit):
     took = [lib.slhc(X, k, prune=False)["stats"]["ms_connect_kernels"] for _ in range(4)]
     print("  ms", took, flush=True)
     assert 0 < min(took) < limit
+
+
+# the segments of few queries' candidates queue for one line, not for eight words of it one by one (20 in 100 000 x 6 took 55 us, 2.7 times what the few segments
+# of 1250 in 4000 x 4 take; 19 and 20 now)
+@pytest.mark.gpu
+@pytest.mark.parametrize("m,n,d", [(20, 100_000, 6), (61, 50_000, 8)])
+def test_segments_of_few_queries_meet_at_a_line(lib, m, n, d):
+    print(f"small 1-NN, time, m={m} n={n} d={d}", flush=True)
+
+    def least(m, n, d):
+        Q, Y = rows(m, d, m), rows(n, d, n)
+        out = (torch.empty(m, dtype=torch.int32, device="cuda"), torch.empty(m, dtype=torch.float32, device="cuda"))
+        times = []
+        for _ in range(12):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(16):
+                lib.fused_1nn(Q, Y, out=out)
+            b.record()
+            b.synchronize()
+            times.append(a.elapsed_time(b))
+        distances = ((Q[:, None, :] - Y[None]) ** 2).sum(2)
+        assert torch.allclose(out[1], distances.min(1).values, rtol=1e-5) and (out[0] == distances.argmin(1)).float().mean() >= 0.95
+        return min(times[2:])
+    few_segments, many = least(1250, 4000, 4), least(m, n, d)
+    print(f"  {62.5 * few_segments:.1f} us with few segments, {62.5 * many:.1f} with many", flush=True)
+    assert many < 1.7 * few_segments
