@@ -36,7 +36,7 @@
  *     of the calling thread.
  *   - Device memory: the library allocates none; everything it needs is in `workspace`.  Host
  *     memory: the synchronous entry points (slhc_slhc*, slhc_csr_msf, and slhc_knn_graph_opt with
- *     SLHC_PRUNE) use pinned staging buffers (slhc_slhc: up to 28 bytes per row for the host dendrogram pass, plus 16
+ *     SLHC_PRUNE) use pinned staging buffers (slhc_slhc: below 19 000 rows 20 bytes per row for the host dendrogram pass, plus 16
  *     bytes per row of pageable memory) and HIP events.  Pinned buffers are kept for later calls, at most 256 MiB of
  *     them over all threads; what goes beyond is given back at once.
  *     The library keeps no other mutable state between calls than the thread-local error text
@@ -88,7 +88,7 @@ typedef struct slhc_stats {
     float ms_boruvka;                /* all min-edge / commit / relabel kernels                    */
     float ms_connect;                /* all cross-component 1-NN sweeps                            */
     float ms_sort;                   /* edge sort                                                  */
-    float ms_dendrogram;             /* device->host copy, host union-find, host->device copy      */
+    float ms_dendrogram;             /* children and sizes, on the device or (few rows) on the host */
     float ms_total;
     float ms_norm_kernel;            /* HIP-event time of the half norms and the float16 copy       */
     float ms_knn_kernel;             /* HIP-event time of the k-NN search's kernels                */
@@ -325,10 +325,8 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
  *   heights   DEVICE out  [N-1] float32 = mst_w (merge i has the weight of sorted edge i)
  *   sizes     DEVICE out  [N-1] int32 rows under node N+i
  *   stats     HOST   out  optional
- * Synchronous: returns after the outputs are complete (the dendrogram pass runs on the host, as
- * in the paper, so the call has to wait for the device anyway).  From 200 000 rows on that pass starts
- * host threads of its own, at most 16 and at most the number of hardware threads; SLHC_HOST_THREADS in
- * the environment sets another number (1: none).  The result does not depend on it.
+ * Synchronous: returns after the outputs are complete (the rounds are steered by the host, and below 19 000 rows the dendrogram
+ * pass runs there, as in the paper).
  */
 int slhc_workspace_bytes(int64_t N, int32_t d, int32_t k, size_t* bytes /* HOST out */);
 int slhc_slhc(const float* X, int64_t N, int32_t d, int32_t k,

@@ -11,7 +11,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libslhc.so")
-SOURCES = ["sweep_kernels.hip", "near_kernels.hip", "pairs_kernels.hip", "direct_kernels.hip", "forest_kernels.hip", "csr_kernels.hip", "order_kernels.hip", "cluster_kernels.hip",
+SOURCES = ["sweep_kernels.hip", "near_kernels.hip", "pairs_kernels.hip", "direct_kernels.hip", "forest_kernels.hip", "dendrogram_kernels.hip", "csr_kernels.hip", "order_kernels.hip", "cluster_kernels.hip",
            "static_scratch.hip", "slhc_api.hip"]
 HIPCC_FLAGS = [
     "-O3", "--offload-arch=gfx950", "-std=c++17", "-fPIC",

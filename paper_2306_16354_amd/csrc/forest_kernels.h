@@ -69,29 +69,16 @@ hipError_t forest_small(const ForestState& f, bool first, hipStream_t s);
 
 // Sort E edges ascending by (w, lo, hi).  keys/vals are scratch of E elements each; `temp` of
 // edge_sort_temp_bytes(E).  Result in out_lo/out_hi/out_w.
-// Copies of the sorted edges (each nullptr for none): the weights as heights, the end points from edge `from` on in host memory.
-struct EdgeCopies { float* heights; int32_t* host_lo; int32_t* host_hi; int from; };
+// Copies of the sorted edges (each nullptr for none): the weights as heights, the end points in host memory.
+struct EdgeCopies { float* heights; int32_t* host_lo; int32_t* host_hi; };
 size_t edge_sort_temp_bytes(int E);
 hipError_t edge_sort(const int32_t* lo, const int32_t* hi, const float* w, int E, int N /* ids are below N */,
                      unsigned long long* keys_a, unsigned long long* keys_b,
                      uint32_t* vals_a, uint32_t* vals_b, void* temp, size_t temp_bytes,
                      int32_t* out_lo, int32_t* out_hi, float* out_w, const EdgeCopies& copies, hipStream_t s);
 
-// Components of the forest made of edges 0..R-1 of a tree's edge list (lo, hi < N): one pass hooks every
-// edge's larger root under the smaller and flattens the labels; `first` initialises label[v] = v.  The
-// caller clears *changed before a pass and repeats passes until one leaves it 0; label[v] is then the
-// smallest vertex id of v's component.  prefix_forest_keys: key[e] = label[lo[e]], val[e] = e for e < R.
-hipError_t prefix_forest_pass(const int32_t* lo, const int32_t* hi, int R, int N, int32_t* label, int32_t* changed,
-                              bool first, hipStream_t s);
-hipError_t prefix_forest_keys(const int32_t* lo, const int32_t* label, int R, int N, uint32_t* key, uint32_t* val,
-                              hipStream_t s);
-
-// The grouped edges in list order into host memory (end points, labels, edge numbers), and the way back: children and
-// sizes of all E merges from host memory, the first R in list order.
-hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, const uint32_t* key, int R, int32_t* glo,
-                                int32_t* ghi, uint32_t* gkey, uint32_t* ids, hipStream_t s);
-hipError_t linkage_upload(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int E, int32_t* children,
-                          int32_t* sizes, hipStream_t s);
+// Children and sizes of E merges from host memory.
+hipError_t linkage_upload(const int32_t* cj, const int32_t* sj, int E, int32_t* children, int32_t* sizes, hipStream_t s);
 
 // Stable sort of n (key, value) pairs of 32-bit words by key (keys below 2^key_bits).
 size_t pair_sort_temp_bytes(int n);

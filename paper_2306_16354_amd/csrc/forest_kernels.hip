@@ -702,121 +702,20 @@ __global__ void __launch_bounds__(TB) k_pack_edges(const int32_t* __restrict__ l
     vals[i] = __float_as_uint(w[i]);
 }
 
-// ---- components of the forest made of the first R edges of a weight-sorted tree (for the dendrogram) ----
-// label[v] ends as the smallest vertex id of v's component.  Labels only ever decrease and label[x] <= x,
-// so every chain of labels descends strictly and every walk below ends.
-__global__ void __launch_bounds__(256) k_prefix_init(int32_t* __restrict__ label, int N)
-{
-    const int v = blockIdx.x * 256 + threadIdx.x;
-    if (v < N) label[v] = v;
-}
-
-__device__ __forceinline__ int prefix_root(const int32_t* label, int v)
-{
-    for (;;) {
-        const int up = __hip_atomic_load(label + v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (up == v) return v;
-        v = up;
-    }
-}
-
-// every edge hooks the larger of its two roots under the smaller one; *changed is set when any edge still
-// joined two different roots (the hook may lose against a smaller one: the next pass sees to it)
-__global__ void __launch_bounds__(256) k_prefix_hook(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
-                                                     int R, int N, int32_t* __restrict__ label,
-                                                     int32_t* __restrict__ changed)
-{
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    const int a = e < R ? lo[e] : -1, b = e < R ? hi[e] : -1;
-    const bool fine = (unsigned int)a < (unsigned int)N && (unsigned int)b < (unsigned int)N;
-    const int ra = fine ? prefix_root(label, a) : 0, rb = fine ? prefix_root(label, b) : 0;
-    const bool joins = ra != rb;
-    if (joins) {
-        // (the roots of large components are wanted by thousands of edges at once, and all but a few come too late: a word is read
-        // by all of them together, but changed by one at a time.  1M edges, six passes: 1.8 ms without the look, 0.37 so)
-        int32_t* at = label + (ra > rb ? ra : rb);
-        const int to = ra > rb ? rb : ra;
-        if (__hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > to) atomicMin(at, to);
-    }
-    if (__ballot(joins) != 0ull && (threadIdx.x & 63) == 0 && __hip_atomic_load(changed, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == 0)
-        __hip_atomic_store(changed, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-}
-
-__global__ void __launch_bounds__(256) k_prefix_flatten(int32_t* __restrict__ label, int N)
-{
-    const int v = blockIdx.x * 256 + threadIdx.x;
-    if (v < N) label[v] = prefix_root(label, v);
-}
-
-// key[e] = label of edge e's component, val[e] = e
-__global__ void __launch_bounds__(256) k_prefix_keys(const int32_t* __restrict__ lo, const int32_t* __restrict__ label,
-                                                     int R, int N, uint32_t* __restrict__ key, uint32_t* __restrict__ val)
-{
-    const int e = blockIdx.x * 256 + threadIdx.x;
-    if (e >= R) return;
-    const int a = lo[e];
-    key[e] = (unsigned int)a < (unsigned int)N ? (uint32_t)label[a] : 0u;
-    val[e] = (uint32_t)e;
-}
-
-// The grouped edges in list order, straight into host memory: end points, group labels and edge numbers.
-__global__ void __launch_bounds__(256) k_prefix_gather(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi,
-                                                       const uint32_t* __restrict__ listed, const uint32_t* __restrict__ key, int R,
-                                                       int32_t* __restrict__ glo, int32_t* __restrict__ ghi,
-                                                       uint32_t* __restrict__ gkey, uint32_t* __restrict__ ids)
-{
-    const int j = blockIdx.x * 256 + threadIdx.x;
-    if (j >= R) return;
-    const uint32_t e = listed[j];
-    const bool ok = e < (uint32_t)R;
-    glo[j] = ok ? lo[e] : -1;
-    ghi[j] = ok ? hi[e] : -1;
-    gkey[j] = key[j];
-    ids[j] = e;
-}
-
-// children / sizes from host memory: the first R merges in list order back to edge order (listed), the rest as they are
-__global__ void __launch_bounds__(256) k_linkage_upload(const uint32_t* __restrict__ listed, const int2* __restrict__ cj,
-                                                        const int32_t* __restrict__ sj, int R, int E,
+// children / sizes of all merges from host memory
+__global__ void __launch_bounds__(256) k_linkage_upload(const int32_t* __restrict__ cj, const int32_t* __restrict__ sj, int E,
                                                         int32_t* __restrict__ children, int32_t* __restrict__ sizes)
 {
     const int j = blockIdx.x * 256 + threadIdx.x;
     if (j >= E) return;
-    const uint32_t e = j < R ? listed[j] : (uint32_t)j;
-    if (e >= (uint32_t)E) return;
-    const int2 c = cj[j];
-    children[2 * (size_t)e] = c.x;
-    children[2 * (size_t)e + 1] = c.y;
-    sizes[e] = sj[j];
+    children[2 * j] = cj[2 * j];
+    children[2 * j + 1] = cj[2 * j + 1];
+    sizes[j] = sj[j];
 }
 
-hipError_t prefix_forest_gather(const int32_t* lo, const int32_t* hi, const uint32_t* listed, const uint32_t* key, int R, int32_t* glo,
-                                int32_t* ghi, uint32_t* gkey, uint32_t* ids, hipStream_t s)
+hipError_t linkage_upload(const int32_t* cj, const int32_t* sj, int E, int32_t* children, int32_t* sizes, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_prefix_gather, dim3((R + 255) / 256), dim3(256), 0, s, lo, hi, listed, key, R, glo, ghi, gkey, ids);
-    return hipGetLastError();
-}
-
-hipError_t linkage_upload(const uint32_t* listed, const int32_t* cj, const int32_t* sj, int R, int E, int32_t* children,
-                          int32_t* sizes, hipStream_t s)
-{
-    hipLaunchKernelGGL(k_linkage_upload, dim3((E + 255) / 256), dim3(256), 0, s, listed, reinterpret_cast<const int2*>(cj), sj, R, E, children, sizes);
-    return hipGetLastError();
-}
-
-hipError_t prefix_forest_pass(const int32_t* lo, const int32_t* hi, int R, int N, int32_t* label, int32_t* changed,
-                              bool first, hipStream_t s)
-{
-    if (first) hipLaunchKernelGGL(k_prefix_init, dim3((N + 255) / 256), dim3(256), 0, s, label, N);
-    hipLaunchKernelGGL(k_prefix_hook, dim3((R + 255) / 256), dim3(256), 0, s, lo, hi, R, N, label, changed);
-    hipLaunchKernelGGL(k_prefix_flatten, dim3((N + 255) / 256), dim3(256), 0, s, label, N);
-    return hipGetLastError();
-}
-
-hipError_t prefix_forest_keys(const int32_t* lo, const int32_t* label, int R, int N, uint32_t* key, uint32_t* val,
-                              hipStream_t s)
-{
-    hipLaunchKernelGGL(k_prefix_keys, dim3((R + 255) / 256), dim3(256), 0, s, lo, label, R, N, key, val);
+    hipLaunchKernelGGL(k_linkage_upload, dim3((E + 255) / 256), dim3(256), 0, s, cj, sj, E, children, sizes);
     return hipGetLastError();
 }
 
@@ -846,7 +745,7 @@ __global__ void __launch_bounds__(TB) k_unpack_edges(const unsigned long long* _
     const float x = __uint_as_float(wbits ? wbits[i] : (uint32_t)(e >> 32));
     lo[i] = a; hi[i] = b; w[i] = x;
     if (c.heights) c.heights[i] = x;
-    if (c.host_lo && i >= c.from) { c.host_lo[i] = a; c.host_hi[i] = b; }
+    if (c.host_lo) { c.host_lo[i] = a; c.host_hi[i] = b; }
 }
 
 size_t edge_sort_temp_bytes(int E)

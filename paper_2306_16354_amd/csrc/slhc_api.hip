@@ -15,12 +15,12 @@
 #include <memory>
 #include <new>
 #include <optional>
-#include <thread>
 #include <vector>
 
 #include "../../include/slhc.h"
 #include "cluster_kernels.h"
 #include "csr_kernels.h"
+#include "dendrogram_kernels.h"
 #include "forest_kernels.h"
 #include "near_kernels.h"
 #include "direct_kernels.h"
@@ -585,11 +585,10 @@ constexpr double SPLIT_MIN_STEPS = SLHC_SPLIT_MIN_STEPS;
 #define SLHC_TILE_GAP_MAX_TILES 32768
 #endif
 constexpr int TILE_GAP_MAX_TILES = SLHC_TILE_GAP_MAX_TILES;
-// dendrogram: from this many rows on, host threads share the light edges (see build_dendrogram_parallel)
-#ifndef SLHC_DENDROGRAM_THREADS_MIN_ROWS
-#define SLHC_DENDROGRAM_THREADS_MIN_ROWS 200000
-#endif
-constexpr int64_t DENDROGRAM_THREADS_MIN_ROWS = SLHC_DENDROGRAM_THREADS_MIN_ROWS;
+// The dendrogram from this many rows on is made on the device (dendrogram_kernels.hip), below on the host, whose pass over so few rows
+// stays in its caches.  Sort and dendrogram, three kinds of data, host / device: 12 000 rows 130 / 172 us, 16 000 152 / 165, 18 000 177 / 188,
+// 20 000 215 / 190, 24 000 255 / 190.
+constexpr int64_t DENDROGRAM_DEVICE_MIN_ROWS = 19000;
 bool prunable(int64_t N, int32_t d) { return d % 4 == 0 && d <= 128 && N >= PRUNE_MIN_ROWS; }
 #ifndef SLHC_PIVOT_STRIDE
 #define SLHC_PIVOT_STRIDE 64
@@ -872,7 +871,7 @@ struct SlhcWs {
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
-        sort_temp_bytes = std::max(slhc::edge_sort_temp_bytes((int)(N - 1)), slhc::pair_sort_temp_bytes((int)N));   // the second: grouping the dendrogram's edges
+        sort_temp_bytes = std::max(slhc::edge_sort_temp_bytes((int)(N - 1)), slhc::pair_sort_temp_bytes((int)N));   // the second: the dendrogram's chains
         sort_temp = c.take<unsigned char>(sort_temp_bytes);
         // the k-NN part takes what is left, without the engine's lower ends of the queries' answers
         const size_t low = up(n * sizeof(float));
@@ -1420,112 +1419,48 @@ int run_knn(const float* X, int64_t N, int32_t d, int32_t k, int32_t* nbr_idx, f
     return SLHC_OK;
 }
 
-// Linkage arrays from weight-sorted tree edges (paper Sec. 3.3.1): a union-find over the N points
+// Linkage arrays from weight-sorted tree edges (paper Sec. 3.3.1) of few rows, on the host as in the paper: a union-find over the N points
 // (union by size, path halving) in which every set carries the dendrogram node created by its last
 // merge; merge i creates node N+i.  The edges arrive in weight order, so their end points are
 // scattered over the whole array: one 16-byte record per point keeps a find step to one cache
 // line, and the records of the edges a few iterations ahead, then their parents, are prefetched.
-//
-// Merges inside different components of the forest made of the first R edges do not see each other, so
-// those components can be worked through by different threads, each in edge order, on one shared array (no
-// two of them touch the same record); the edges from R on follow on one thread.  `listed`: those first R
-// edge indices grouped by component, ascending inside a component.
-struct DendrogramBuilder {
+// End points outside [0, N) (never produced by a correct caller) are skipped and reported by `false`.
+bool build_dendrogram(const int32_t* lo, const int32_t* hi, int64_t N, int32_t* children, int32_t* sizes)
+{
     struct PointSet { int32_t up, count, node, unused; };
-    std::unique_ptr<PointSet[]> set;
-    int64_t N;
-    static constexpr int64_t AHEAD = 16;
-
-    explicit DendrogramBuilder(int64_t N_) : set(new PointSet[(size_t)N_]), N(N_) {}
-    void init(int64_t v0, int64_t v1) { for (int64_t v = v0; v < v1; ++v) set[(size_t)v] = PointSet{(int32_t)v, 1, (int32_t)v, 0}; }
-    int32_t root(int32_t a)
-    {
+    constexpr int64_t AHEAD = 16;
+    std::unique_ptr<PointSet[]> set(new PointSet[(size_t)N]);
+    for (int64_t v = 0; v < N; ++v) set[(size_t)v] = PointSet{(int32_t)v, 1, (int32_t)v, 0};
+    auto root = [&](int32_t a) {
         while (set[(size_t)a].up != a) {
             set[(size_t)a].up = set[(size_t)set[(size_t)a].up].up;
             a = set[(size_t)a].up;
         }
         return a;
-    }
-    // Edges j0 .. j1-1 of the streams lo / hi, in order; edge j is merge `first_merge + j`, or merge ids[j]
-    // when `ids` is given; its children go to children[2 j ..], its size to sizes[j].  End points outside
-    // [0, N) (never produced by a correct caller) are skipped and reported by `false`.
-    bool run(const int32_t* lo, const int32_t* hi, const uint32_t* ids, int64_t first_merge, int64_t j0, int64_t j1,
-             int32_t* children, int32_t* sizes)
-    {
-        bool good = true;
-        const uint32_t n = (uint32_t)N;
-        for (int64_t j = j0; j < j1; ++j) {
-            if (j + AHEAD < j1 && (uint32_t)lo[j + AHEAD] < n && (uint32_t)hi[j + AHEAD] < n) {
-                __builtin_prefetch(&set[(size_t)lo[j + AHEAD]]);
-                __builtin_prefetch(&set[(size_t)hi[j + AHEAD]]);
-                // and, half way, the records those point to (their own have arrived by now)
-                __builtin_prefetch(&set[(size_t)set[(size_t)lo[j + AHEAD / 2]].up]);
-                __builtin_prefetch(&set[(size_t)set[(size_t)hi[j + AHEAD / 2]].up]);
-            }
-            if ((uint32_t)lo[j] >= n || (uint32_t)hi[j] >= n) { good = false; continue; }
-            int32_t ra = root(lo[j]), rb = root(hi[j]);
-            const int32_t a = set[(size_t)ra].node, b = set[(size_t)rb].node;
-            children[2 * j] = a < b ? a : b;
-            children[2 * j + 1] = a < b ? b : a;
-            if (set[(size_t)ra].count < set[(size_t)rb].count) std::swap(ra, rb);
-            set[(size_t)rb].up = ra;
-            set[(size_t)ra].count += set[(size_t)rb].count;
-            set[(size_t)ra].node = (int32_t)(N + (ids ? (int64_t)ids[j] : first_merge + j));
-            sizes[j] = set[(size_t)ra].count;
-        }
-        return good;
-    }
-};
-
-bool build_dendrogram(const int32_t* lo, const int32_t* hi, int64_t N, int32_t* children, int32_t* sizes)
-{
-    DendrogramBuilder b(N);
-    b.init(0, N);
-    return b.run(lo, hi, nullptr, 0, 0, N - 1, children, sizes);
-}
-
-// The same with `threads` host threads for the first R merges.  Those come grouped by component (`key`,
-// equal keys adjacent) and in merge order inside a group: glo / ghi / ids [R] are their end points and merge
-// numbers in that order, and their children and sizes are written in that order too (cj [2R], sj [R]).
-// Thread t takes the t-th share of the list, moved forward at both ends to the next group boundary.
-// The merges from R on follow on one thread: tlo / thi are their end points, tc / ts their output.
-bool build_dendrogram_parallel(int64_t N, int64_t R, const uint32_t* key, const int32_t* glo, const int32_t* ghi,
-                               const uint32_t* ids, int32_t* cj, int32_t* sj, const int32_t* tlo, const int32_t* thi,
-                               int32_t* tc, int32_t* ts, int threads)
-{
-    // joins what was started even when starting another thread throws
-    struct Pool {
-        std::vector<std::thread> v;
-        void join() { for (auto& th : v) if (th.joinable()) th.join(); }
-        ~Pool() { join(); }
     };
-    DendrogramBuilder b(N);
-    {
-        Pool pool;
-        for (int t = 0; t < threads; ++t)
-            pool.v.emplace_back([&b, N, t, threads] { b.init(N * t / threads, N * (t + 1) / threads); });
-        pool.join();
-    }
-    {
-        auto boundary = [&](int64_t j) { while (j > 0 && j < R && key[j] == key[j - 1]) ++j; return j; };
-        std::vector<char> good((size_t)threads, 1);
-        Pool pool;
-        for (int t = 0; t < threads; ++t) {
-            const int64_t j0 = boundary(R * t / threads), j1 = t + 1 == threads ? R : boundary(R * (t + 1) / threads);
-            char* mine = &good[(size_t)t];
-            pool.v.emplace_back([&b, glo, ghi, ids, cj, sj, j0, j1, mine] { *mine = b.run(glo, ghi, ids, 0, j0, j1, cj, sj) ? 1 : 0; });
+    bool good = true;
+    const uint32_t n = (uint32_t)N;
+    const int64_t E = N - 1;
+    for (int64_t j = 0; j < E; ++j) {
+        if (j + AHEAD < E && (uint32_t)lo[j + AHEAD] < n && (uint32_t)hi[j + AHEAD] < n) {
+            __builtin_prefetch(&set[(size_t)lo[j + AHEAD]]);
+            __builtin_prefetch(&set[(size_t)hi[j + AHEAD]]);
+            // and, half way, the records those point to (their own have arrived by now)
+            __builtin_prefetch(&set[(size_t)set[(size_t)lo[j + AHEAD / 2]].up]);
+            __builtin_prefetch(&set[(size_t)set[(size_t)hi[j + AHEAD / 2]].up]);
         }
-        pool.join();
-        for (char g : good) if (!g) return false;
+        if ((uint32_t)lo[j] >= n || (uint32_t)hi[j] >= n) { good = false; continue; }
+        int32_t ra = root(lo[j]), rb = root(hi[j]);
+        const int32_t a = set[(size_t)ra].node, b = set[(size_t)rb].node;
+        children[2 * j] = a < b ? a : b;
+        children[2 * j + 1] = a < b ? b : a;
+        if (set[(size_t)ra].count < set[(size_t)rb].count) std::swap(ra, rb);
+        set[(size_t)rb].up = ra;
+        set[(size_t)ra].count += set[(size_t)rb].count;
+        set[(size_t)ra].node = (int32_t)(N + j);
+        sizes[j] = set[(size_t)ra].count;
     }
-    return b.run(tlo, thi, nullptr, R, 0, N - 1 - R, tc, ts);
-}
-
-int host_threads()
-{
-    int t = (int)std::thread::hardware_concurrency();
-    if (const char* e = std::getenv("SLHC_HOST_THREADS")) { const int v = std::atoi(e); if (v >= 1) t = v; }
-    return t < 1 ? 1 : (t > 16 ? 16 : t);
+    return good;
 }
 
 // ---- scratch of slhc_knn_graph_static: the workspace of the every-tile k-NN path as a fixed device array
@@ -2219,10 +2154,10 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     rc = run_knn(X, N, d, k, ws.nbr_idx, ws.nbr_dist, kws, s, flags, &pruned, timed ? &ev_norm : nullptr, timed ? &ev_order : nullptr,
                  timed ? &ev_knn : nullptr);
     if (rc != SLHC_OK) return rc;
-    // The pinned staging of the dendrogram pass is taken here, while the k-NN sweep runs: where the pool has none,
-    // pinning 28 bytes per row takes the host 2 to 3 ms at a million rows.
+    // The pinned staging of the host's dendrogram pass is taken here, while the k-NN sweep runs.
+    const bool host_dendrogram = children && N < DENDROGRAM_DEVICE_MIN_ROWS;
     PinnedHost pin_edges(s);
-    if (children) HIP_TRY(pin_edges.alloc((7 * (size_t)(N - 1) + 16) * sizeof(int32_t)));
+    if (host_dendrogram) HIP_TRY(pin_edges.alloc(5 * (size_t)(N - 1) * sizeof(int32_t)));
     Mailbox mail(s);
     HIP_TRY(mail.open());
     unsigned long long h_surv[8];
@@ -2657,71 +2592,63 @@ int run_slhc(const float* X, int64_t N, int32_t d, int32_t k, int32_t* mst_src, 
     st.ms_connect = (float)ms_connect;
     st.ms_boruvka = (float)(t_forest - t_knn - ms_connect);
 
-    // ---- sort by weight (Sec. 3.3.1), then the sequential relabelling on the host
+    // ---- sort by weight (Sec. 3.3.1), then the linkage arrays
     const size_t E = (size_t)(N - 1);
-    // Large trees: all but the heaviest sixteenth of the edges are grouped by the component they lie in when
-    // only those edges are there (labels on the device, a stable sort by label), and host threads share the
-    // groups; see build_dendrogram_parallel.  The arrays of the forest rounds are free by now.
-    const int threads = host_threads();
-    const bool grouped = children && N >= DENDROGRAM_THREADS_MIN_ROWS && threads >= 2;
-    const int64_t heavy = (int64_t)E / 16 > 4096 ? (int64_t)E / 16 : 4096;
-    int64_t R = grouped ? (int64_t)E - heavy : 0;
-    // host staging: end points (grouped part in list order, then the rest in edge order), keys and merge numbers
-    // of the grouped part, children and sizes in the same two parts.  Kernels write and read it in place.
-    int32_t* h_lo = static_cast<int32_t*>(pin_edges.p);     // [R] grouped, [E - R] rest (5 E + 2 R words in all)
+    // host staging: end points, children and sizes.  Kernels write and read it in place.
+    int32_t* h_lo = static_cast<int32_t*>(pin_edges.p);
     int32_t* h_hi = h_lo + E;
-    int32_t* h_children = h_hi + E;                         // 2E entries, same two parts
+    int32_t* h_children = h_hi + E;
     int32_t* h_sizes = h_children + 2 * E;
-    uint32_t* h_key = reinterpret_cast<uint32_t*>(h_sizes + E);
-    uint32_t* h_ids = h_key + R;
     slhc::EdgeCopies copies{};
     copies.heights = heights;
-    if (children) { copies.host_lo = h_lo; copies.host_hi = h_hi; copies.from = (int)R; }
+    if (host_dendrogram) { copies.host_lo = h_lo; copies.host_hi = h_hi; }
     HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, (int)(N - 1), (int)N, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
                             ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, copies, s));
     if (!children) {                                        // (the pivots' tree: its edges are all that is wanted)
         mail.box.idle();
         return SLHC_OK;
     }
-    uint32_t* key_sorted = reinterpret_cast<uint32_t*>(ws.ptr);
-    uint32_t* listed = reinterpret_cast<uint32_t*>(ws.hook);
     double t_sort = t_forest;
-    if (grouped) {
-        int32_t* changed = ws.counters + 8;
-        int32_t h_changed = 0;
-        bool settled = false;
-        for (int pass = 0; pass < 64 && !settled; ++pass) {
-            hipLaunchKernelGGL(k_zero_words, dim3(1), dim3(64), 0, s, reinterpret_cast<uint32_t*>(changed), 1);
-            HIP_TRY(hipGetLastError());
-            HIP_TRY(slhc::prefix_forest_pass(mst_src, mst_dst, (int)R, (int)N, ws.colour, changed, pass == 0, s));
-            HIP_TRY(mail.fetch(changed, 1, &h_changed));
-            if (pass == 0) t_sort = now_ms();
-            settled = h_changed == 0;
+    if (host_dendrogram) {
+        HIP_TRY(mail.fetch(ws.counters, 1, h_cnt));         // everything staged is in host memory
+        t_sort = now_ms();
+        if (!build_dendrogram(h_lo, h_hi, N, h_children, h_sizes)) { set_err("dendrogram: an edge of the sorted tree has an end point outside [0, N)"); return SLHC_INTERNAL; }
+        log.mark("dendrogram: union-find on the host");
+        HIP_TRY(slhc::linkage_upload(h_children, h_sizes, (int)E, children, sizes, s));
+    } else {
+        // the arrays of the forest rounds and of the sort are free by now
+        slhc::DendrogramWork dw{};
+        dw.lightest = reinterpret_cast<uint32_t*>(ws.keys_a);
+        dw.up = reinterpret_cast<int32_t*>(ws.keys_b);
+        dw.hook = ws.hook;
+        const size_t half = E / 2 / 32 * 32;                // (the lists of odd levels hold half the vertices at most, the others a quarter)
+        dw.edge[0] = ws.vals_a; dw.edge[1] = reinterpret_cast<uint32_t*>(ws.e_w);
+        dw.ends[0] = reinterpret_cast<int2*>(ws.best_e); dw.ends[1] = dw.ends[0] + half;
+        dw.key = reinterpret_cast<uint32_t*>(ws.ptr); dw.val = ws.vals_b;
+        dw.key_sorted = reinterpret_cast<uint32_t*>(ws.colour); dw.listed = reinterpret_cast<uint32_t*>(ws.qlist);
+        dw.chain = reinterpret_cast<int2*>(ws.best_e);
+        dw.carry = reinterpret_cast<unsigned long long*>(ws.ext_idx);
+        dw.counters = ws.cand_u;
+        if (timed) hipLaunchKernelGGL(k_fetch_words, dim3(1), dim3(256), 0, s, reinterpret_cast<const uint32_t*>(ws.counters), 1, mail.words(), mail.next());
+        HIP_TRY(slhc::dendrogram_chains(mst_src, mst_dst, (int)N, dw, children, s));
+        if (timed) { HIP_TRY(mail.wait()); t_sort = now_ms(); }
+        // the merges per level come back while the pairs are sorted
+        int32_t h_levels[slhc::DENDRO_WORDS];
+        hipLaunchKernelGGL(k_fetch_words, dim3(1), dim3(256), 0, s, reinterpret_cast<const uint32_t*>(dw.counters), slhc::DENDRO_WORDS, mail.words(), mail.next());
+        HIP_TRY(hipGetLastError());
+        HIP_TRY(slhc::pair_sort_u32(dw.key, dw.key_sorted, dw.val, dw.listed, (int)E, bits_for(N), ws.sort_temp, ws.sort_temp_bytes, s));
+        HIP_TRY(mail.wait());
+        std::memcpy(h_levels, mail.words() + 1, sizeof(h_levels));
+        int64_t merges = 0;
+        for (int l = 0; l < slhc::DENDRO_LEVELS; ++l) merges += h_levels[slhc::DENDRO_MERGES + l];
+        if (h_levels[slhc::DENDRO_ERROR] != 0 || merges != (int64_t)E) {
+            set_err("dendrogram: check %d failed, %lld of %zu merges in chains", h_levels[slhc::DENDRO_ERROR], (long long)merges, E);
+            return SLHC_INTERNAL;
         }
-        if (!settled) {                                     // (never seen) the sequential pass on all edges
-            HIP_TRY(hipMemcpyAsync(h_lo, mst_src, E * 4, hipMemcpyDeviceToHost, s));
-            HIP_TRY(hipMemcpyAsync(h_hi, mst_dst, E * 4, hipMemcpyDeviceToHost, s));
-            R = 0;
-        } else {
-        HIP_TRY(slhc::prefix_forest_keys(mst_src, ws.colour, (int)R, (int)N, ws.vals_a, ws.vals_b, s));
-        HIP_TRY(slhc::pair_sort_u32(ws.vals_a, key_sorted, ws.vals_b, listed, (int)R, bits_for(N), ws.sort_temp,
-                                    ws.sort_temp_bytes, s));
-        HIP_TRY(slhc::prefix_forest_gather(mst_src, mst_dst, listed, key_sorted, (int)R, h_lo, h_hi, h_key, h_ids, s));
-        }
+        log.mark("dendrogram: %d levels", h_levels[slhc::DENDRO_DEPTH]);
+        HIP_TRY(slhc::dendrogram_sizes((int)N, h_levels + slhc::DENDRO_MERGES, dw, children, sizes, s));
     }
-    HIP_TRY(hipGetLastError());
-    HIP_TRY(mail.fetch(ws.counters, 1, h_cnt));             // everything staged is in host memory
-    if (!grouped) t_sort = now_ms();
     st.ms_sort = (float)(t_sort - t_forest);
-    const size_t Rz = (size_t)R;
-    log.mark("dendrogram: %zu edges staged on the host (%lld grouped for %d threads)", E, (long long)R, threads);
-    const bool good = Rz ? build_dendrogram_parallel(N, R, h_key, h_lo, h_hi, h_ids, h_children, h_sizes, h_lo + Rz, h_hi + Rz,
-                                                     h_children + 2 * Rz, h_sizes + Rz, threads)
-                         : build_dendrogram(h_lo, h_hi, N, h_children, h_sizes);
-    if (!good) { set_err("dendrogram: an edge of the sorted tree has an end point outside [0, N)"); return SLHC_INTERNAL; }
-    log.mark("dendrogram: union-find");
-    // (the grouped part goes back to edge order on the device)
-    HIP_TRY(slhc::linkage_upload(listed, h_children, h_sizes, (int)R, (int)E, children, sizes, s));
     HIP_TRY(hipStreamSynchronize(s));
     pin_edges.idle();
     mail.box.idle();
