@@ -2,18 +2,15 @@
 // roots by ascending node id, give every row the number of the root above it (paper Sec. 3.3.2,
 // Alg. "extract_flattened_clusters", Alg. "inherit_labels").
 //
-// The paper's inherit_labels lets every node walk up its parents until it meets a labelled one.
-// Single-linkage dendrograms are often chains thousands of levels deep, so here the walk is cut into passes: in each,
-// every merge follows a few links and keeps where it got to, so a pass divides the remaining depth by that number; rows are
-// linked once and look their end up last.  1M rows: 202 us with doubling over all 2N nodes (21 passes), then 160, 138, 133
-// and 140 us with 2, 3, 4 and 8 links; 40 000 rows: 58, 45, 38 and 30.5 us.  So eight links, where a pass costs its launch,
-// and four at the size where its walks do; the line at a quarter million merges lies between the two sizes timed.
-// The paper finds the roots by sorting the children of the last merges; here a node is a root iff
-// it exists at the cut and nothing kept points above it, and the numbering is an exclusive prefix
-// sum of that flag over the node ids (the same ascending order, no sort).
+// The paper's inherit_labels lets every node walk up its parents until it meets a labelled one, and finds the roots by sorting the children of
+// the last merges.  Here a node is a root iff it exists at the cut and nothing kept points above it, and its number is the count of roots
+// before it.  Single-linkage dendrograms are often chains thousands of levels deep, and a pass in which every merge follows some links costs
+// what the card can read at random (460 G words a second, 9 us for a million merges and four links).  So the merges are thinned: one of every
+// eight, chosen by a hash (not by its number, whose last bits a chain may share), is one of the next stage, every merge walks towards the next such
+// merge above it, of those one in sixteen does the same, and so on until few are left, whose walks are finished in LDS.  1M rows, 1000
+// clusters: nine passes in which every merge followed four links took 79 of 129 us; the stages take 42 of 86, and the scattered writes of the
+// links and labels most of the rest.  40 000 rows 30.5 -> 25 us.
 #include <hip/hip_runtime.h>
-#include <cstring>
-#include <rocprim/rocprim.hpp>
 #include <stdint.h>
 #include "cluster_kernels.h"
 
@@ -22,64 +19,224 @@ namespace slhc {
 constexpr int TB = 256;
 static inline int blocks_for(long long n) { return (int)((n + TB - 1) / TB); }
 
+// Stage r + 1 holds merge i iff its number in stage r is the one that its group of eight (r = 0) or sixteen sends up.
+constexpr int group_bits(int r) { return r == 0 ? 3 : 4; }
+constexpr int stage_bits(int r) { return r == 0 ? 0 : group_bits(r - 1) + stage_bits(r - 1); }
+template <int r> __device__ __forceinline__ unsigned int sent_up(unsigned int group)
+{
+    unsigned int h = group * 0x9e3779b1u;
+    h = (h ^ (h >> 15)) * 0x85ebca6bu;
+    return (h ^ (h >> 13)) & ((1u << group_bits(r)) - 1u);
+}
+// number n of stage r in stage 0, and whether it is in stage r of what is number n of stage `from`
+template <int r> __device__ __forceinline__ unsigned int stage_merge(unsigned int n)
+{
+    if constexpr (r == 0) return n;
+    else return stage_merge<r - 1>((n << group_bits(r - 1)) + sent_up<r - 1>(n));
+}
+template <int r, int from = 0> __device__ __forceinline__ bool in_stage(unsigned int n)
+{
+    if constexpr (from == r) return true;
+    else {
+        const unsigned int group = n >> group_bits(from);
+        return sent_up<from>(group) == (n & ((1u << group_bits(from)) - 1u)) && in_stage<r, from + 1>(group);
+    }
+}
+// Links that a merge follows per stage.  A wavefront walks as long as its longest, and what is left is walked later, so a few less than
+// the walks' mean: 6 and 12; 1M rows 85.8 us, 8 and 12 88, 12 and 20 (with groups of 4 and 8) 95.7; groups of 8, 16, 8 86.9; of 4, 8, 8 91.7; of 16, 16, 4 93.5.
+constexpr int most_links(int r) { return r == 0 ? 6 : 12; }
+constexpr int TOP_MAX = 16384;       // merges of the last stage in LDS, a word each: the third stage up to 33 million merges
 
-// above[v] = v, and merge i < kept puts node N+i above its two children.  A child whose merge is kept is below N + kept, so
-// each word has one writer: the thread of a node that is nobody's kept child, or that of its merge (`self` first).
-__global__ void __launch_bounds__(TB) k_above_self(int32_t* __restrict__ above, int nodes)
+// above[i]: the merge above merge i, itself for a root, -1 - number once it is known.  joined[v]: whether a kept merge has row v as a child.
+__global__ void __launch_bounds__(TB) k_cut_init(int32_t* __restrict__ above, int kept, uint32_t* __restrict__ joined, int words)
 {
     const int v = (blockIdx.x * TB + threadIdx.x) * 4;
-    if (v + 3 < nodes) *reinterpret_cast<int4*>(above + v) = make_int4(v, v + 1, v + 2, v + 3);
+    if (v + 3 < kept) *reinterpret_cast<int4*>(above + v) = make_int4(v, v + 1, v + 2, v + 3);
     else
-        for (int i = v; i < nodes; ++i) above[i] = i;
+        for (int i = v; i < kept; ++i) above[i] = i;
+    if (v / 4 < words) joined[v / 4] = 0u;
 }
 
-__global__ void __launch_bounds__(TB) k_above_kept(const int32_t* __restrict__ children, int N, int kept,
-                                                   int32_t* __restrict__ above)
+// A child whose merge is kept has one parent, so each word has one writer.  Rows are marked by a byte: 1 MB of marks takes the scattered
+// writes of 1M rows better than 4 MB of links.  A well-formed dendrogram only joins nodes that already exist; anything else is ignored.
+__global__ void __launch_bounds__(TB) k_cut_links(const int2* __restrict__ children, int N, int kept, int32_t* __restrict__ above,
+                                                  unsigned char* __restrict__ joined)
 {
     const int i = blockIdx.x * TB + threadIdx.x;
     if (i >= kept) return;
-    const int a = children[2 * i], b = children[2 * i + 1];
-    // a well-formed dendrogram only joins nodes that already exist; anything else is ignored
-    if ((unsigned int)a < (unsigned int)(N + i)) above[a] = N + i;
-    if ((unsigned int)b < (unsigned int)(N + i)) above[b] = N + i;
+    const int2 c = children[i];
+#pragma unroll
+    for (int side = 0; side < 2; ++side) {
+        const int v = side ? c.y : c.x;
+        if ((unsigned int)v >= (unsigned int)(N + i)) continue;
+        if (v < N) joined[v] = 1;
+        else above[v - N] = i;
+    }
 }
 
-// a node that exists at the cut (v < limit) and has nothing above it is a root
-struct RootFlag {
-    const int32_t* above;
-    int limit;
-    __host__ __device__ int32_t operator()(int v) const { return v < limit && above[v] == v ? 1 : 0; }
-};
-
-// Merges only (nodes from N on): a row is linked once and looks its end up in k_labels.  Reading a value another thread
-// has already advanced only gets there sooner; links lead to higher nodes, so walks end.
-__global__ void __launch_bounds__(TB) k_above_follow(int32_t* __restrict__ above, int N, int limit, int hops)
+// Merge i of stage R walks to the next merge of stage R + 1 above it, or to its root.  Links lead to higher merges, so walks end; reading a
+// link that another thread has already advanced only gets there sooner.
+template <int R>
+__device__ __forceinline__ void walk_up(int32_t* above, int kept, unsigned int j)
 {
-    const int v = N + blockIdx.x * TB + threadIdx.x;
-    if (v >= limit) return;
-    const int first = above[v];
+    const unsigned int i = stage_merge<R>(j);
+    if (i >= (unsigned int)kept) return;
+    const int first = above[i];
+    if (first < 0 || first == (int)i) return;
     int a = first;
-    for (int h = 1; h < hops; ++h) {
-        const int up = above[(unsigned int)a < (unsigned int)limit ? a : v];
+    for (int h = 0; h < most_links(R) && !in_stage<R + 1>((unsigned int)a); ++h) {
+        const int up = above[a];
         if (up == a) break;
         a = up;
+        if (a < 0) break;
     }
-    if (a != first) above[v] = a;
+    if (a != first) above[i] = a;
 }
 
-// the last walk, and the label at its end
-__global__ void __launch_bounds__(TB) k_labels(const int32_t* __restrict__ above, const int32_t* __restrict__ rank,
-                                               int N, int nodes, int hops, int32_t* __restrict__ labels)
+// Roots are counted span by span, the rows' spans first: `turns` times 16 rows or 4 merges per thread, one wide load each.
+struct RootSpans {
+    unsigned int N, kept, turns;
+    __host__ __device__ unsigned int rows() const { return (N + turns * TB * 16 - 1) / (turns * TB * 16); }
+    __host__ __device__ unsigned int all() const { return rows() + (kept + turns * TB * 4 - 1) / (turns * TB * 4); }
+};
+static RootSpans root_spans(unsigned int N, unsigned int kept) { return RootSpans{N, kept, 1u + (N >> 20)}; }       // 1300 spans at most
+
+// What this thread looks at in turn t of a span: a bit per root; the first node in `at`.
+__device__ __forceinline__ unsigned int root_flags(const int32_t* above, const unsigned char* joined, const RootSpans& r, unsigned int span, unsigned int t, unsigned int& at)
 {
-    const int v = blockIdx.x * TB + threadIdx.x;
-    if (v >= N) return;
-    int r = above[v];
-    for (int h = 0; h < hops && (unsigned int)r < (unsigned int)nodes; ++h) {
-        const int up = above[r];
-        if (up == r) break;
-        r = up;
+    unsigned int flags = 0;
+    if (span < r.rows()) {
+        at = ((span * r.turns + t) * TB + threadIdx.x) * 16;
+        if (at >= r.N) return 0;
+        const uint4 m = *reinterpret_cast<const uint4*>(joined + at);          // (a mark is 0 or 1)
+        const unsigned int w[4] = {m.x, m.y, m.z, m.w};
+#pragma unroll
+        for (int q = 0; q < 4; ++q) flags |= ((((w[q] ^ 0x01010101u) * 0x01020408u) >> 24) & 15u) << (4 * q);
+        if (r.N - at < 16) flags &= (1u << (r.N - at)) - 1u;
+    } else {
+        at = (((span - r.rows()) * r.turns + t) * TB + threadIdx.x) * 4;
+        if (at >= r.kept) return 0;
+        const int4 a = *reinterpret_cast<const int4*>(above + at);
+        flags = (a.x == (int)at) | (a.y == (int)at + 1) << 1 | (a.z == (int)at + 2) << 2 | (a.w == (int)at + 3) << 3;
+        if (r.kept - at < 4) flags &= (1u << (r.kept - at)) - 1u;
     }
-    labels[v] = (unsigned int)r < (unsigned int)nodes ? rank[r] : -1;
+    return flags;
+}
+__device__ __forceinline__ int block_sum(int x, int* wave_part)
+{
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) x += __shfl_xor(x, o);
+    __syncthreads();
+    if ((threadIdx.x & 63) == 0) wave_part[threadIdx.x >> 6] = x;
+    __syncthreads();
+    int all = 0;
+    for (int w = 0; w < TB / 64; ++w) all += wave_part[w];
+    return all;
+}
+
+// First stage; the workgroups beyond its merges count roots.
+__global__ void __launch_bounds__(TB) k_cut_first(int32_t* __restrict__ above, const unsigned char* __restrict__ joined, RootSpans r,
+                                                  int walkers, int32_t* __restrict__ counts)
+{
+    __shared__ int part[TB / 64];
+    if ((int)blockIdx.x < walkers) { walk_up<0>(above, (int)r.kept, blockIdx.x * TB + threadIdx.x); return; }
+    const unsigned int span = blockIdx.x - walkers;
+    int n = 0;
+    for (unsigned int t = 0, at; t < r.turns; ++t) n += __popc(root_flags(above, joined, r, span, t, at));
+    n = block_sum(n, part);
+    if (threadIdx.x == 0) counts[span] = n;
+}
+
+// Second stage; the workgroups beyond its merges number the roots.  (A walk may find a root with or without its number.)
+__global__ void __launch_bounds__(TB) k_cut_second(int32_t* __restrict__ above, const unsigned char* __restrict__ joined, RootSpans r,
+                                                   int walkers, const int32_t* __restrict__ counts, int32_t* __restrict__ labels)
+{
+    __shared__ int part[TB / 64];
+    if ((int)blockIdx.x < walkers) { walk_up<1>(above, (int)r.kept, blockIdx.x * TB + threadIdx.x); return; }
+    const unsigned int span = blockIdx.x - walkers;
+    if (counts[span] == 0) return;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int before = 0;
+    for (unsigned int s = threadIdx.x; s < span; s += TB) before += counts[s];
+    before = block_sum(before, part);
+    for (unsigned int t = 0; t < r.turns; ++t) {
+        unsigned int v0 = 0;
+        unsigned int flags = root_flags(above, joined, r, span, t, v0);
+        int upto = __popc(flags);
+#pragma unroll
+        for (int o = 1; o < 64; o <<= 1) {
+            const int x = __shfl_up(upto, o);
+            if (lane >= o) upto += x;
+        }
+        __syncthreads();
+        if (lane == 63) part[wave] = upto;
+        __syncthreads();
+        int at = before + upto - __popc(flags);
+        for (int w = 0; w < TB / 64; ++w) {
+            if (w < wave) at += part[w];
+            before += part[w];
+        }
+        for (; flags; flags &= flags - 1, ++at) {
+            const unsigned int v = v0 + __builtin_ctz(flags);
+            if (span < r.rows()) labels[v] = at;
+            else above[v] = -1 - at;
+        }
+    }
+}
+
+template <int R>
+__global__ void __launch_bounds__(TB) k_cut_stage(int32_t* __restrict__ above, int kept)
+{
+    walk_up<R>(above, kept, blockIdx.x * TB + threadIdx.x);
+}
+
+// What is left of the last stage, in LDS by its numbers there: walks over links of four until every one has its root's number.
+template <int STAGES>
+__global__ void __launch_bounds__(1024) k_cut_top(int32_t* __restrict__ above, int kept, int n)
+{
+    extern __shared__ int link[];
+    volatile int* at = link;
+    for (int j = threadIdx.x; j < n; j += 1024) {
+        const unsigned int i = stage_merge<STAGES>((unsigned int)j);
+        int a = -1;
+        if (i < (unsigned int)kept) {
+            a = above[i];
+            while (a >= 0 && !in_stage<STAGES>((unsigned int)a)) a = above[a];
+            if (a >= 0) a >>= stage_bits(STAGES);
+        }
+        at[j] = a;
+    }
+    for (;;) {
+        __syncthreads();
+        int open = 0;
+        for (int j = threadIdx.x; j < n; j += 1024) {
+            int a = at[j];
+            if (a < 0) continue;
+            for (int h = 0; h < 4 && a >= 0; ++h) a = at[a];
+            at[j] = a;
+            open |= a >= 0;
+        }
+        if (!__syncthreads_or(open)) break;
+    }
+    for (int j = threadIdx.x; j < n; j += 1024) {
+        const unsigned int i = stage_merge<STAGES>((unsigned int)j);
+        if (i < (unsigned int)kept) above[i] = at[j];
+    }
+}
+
+// Every merge's rows take the number at the end of its walk, one link per stage as a rule.
+__global__ void __launch_bounds__(TB) k_cut_labels(const int2* __restrict__ children, int N, int kept, const int32_t* __restrict__ above,
+                                                   int32_t* __restrict__ labels)
+{
+    const int i = blockIdx.x * TB + threadIdx.x;
+    if (i >= kept) return;
+    const int2 c = children[i];
+    const bool x = (unsigned int)c.x < (unsigned int)N, y = (unsigned int)c.y < (unsigned int)N;
+    if (!x && !y) return;
+    int a = above[i];
+    while (a >= 0) a = above[a];
+    if (x) labels[c.x] = -1 - a;
+    if (y) labels[c.y] = -1 - a;
 }
 
 // All of it for at most FLAT_SMALL rows, in one workgroup with 16-bit links in LDS: the five to ten launches above cost more
@@ -132,42 +289,41 @@ __global__ void __launch_bounds__(1024) k_flat_small(const int32_t* __restrict__
     for (int v = tid; v < N; v += 1024) labels[v] = above[labels[v]];
 }
 
-static auto root_flags(const int32_t* above, int limit)
+// Stage R of n merges and those after it.
+template <int R>
+static void cut_stages(int32_t* above, int kept, unsigned int n, hipStream_t s)
 {
-    return rocprim::make_transform_iterator(rocprim::make_counting_iterator<int>(0), RootFlag{above, limit});
+    hipLaunchKernelGGL(k_cut_stage<R>, dim3(blocks_for(n)), dim3(TB), 0, s, above, kept);
+    const unsigned int up = (n + (1u << group_bits(R)) - 1) >> group_bits(R);
+    if constexpr (R < 4) {
+        if (up > TOP_MAX) { cut_stages<R + 1>(above, kept, up, s); return; }
+    }
+    hipLaunchKernelGGL(k_cut_top<R + 1>, dim3(1), dim3(1024), (size_t)up * 4, s, above, kept, (int)up);     // (2^30 merges: 2048 of stage 5)
 }
 
-size_t flat_clusters_scan_temp_bytes(int N)
-{
-    size_t bytes = 0;
-    int32_t* out = nullptr;
-    (void)rocprim::exclusive_scan(nullptr, bytes, root_flags(nullptr, 0), out, 0, (size_t)(2 * (size_t)N), rocprim::plus<int32_t>());
-    return bytes;
-}
+size_t flat_clusters_spans(int64_t N) { return root_spans((unsigned int)N, (unsigned int)N).all(); }
 
-hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t* labels, int32_t* above,
-                         int32_t* rank, void* scan_temp, size_t scan_temp_bytes, hipStream_t s)
+hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t* labels, int32_t* above, unsigned char* joined,
+                         int32_t* counts, hipStream_t s)
 {
-    const int nodes = 2 * N - 1;
     const int kept = N - n_clusters;
     if (N <= FLAT_SMALL) {
         const size_t lds = (size_t)(N + kept) * 2;
         hipLaunchKernelGGL(k_flat_small, dim3(1), dim3(1024), lds, s, children, N, kept, labels);
         return hipGetLastError();
     }
-    hipLaunchKernelGGL(k_above_self, dim3(blocks_for((nodes + 3) / 4)), dim3(TB), 0, s, above, nodes);
-    if (kept > 0)
-        hipLaunchKernelGGL(k_above_kept, dim3(blocks_for(kept)), dim3(TB), 0, s, children, N, kept, above);
-    hipError_t e = hipGetLastError();
-    if (e != hipSuccess) return e;
-    e = rocprim::exclusive_scan(scan_temp, scan_temp_bytes, root_flags(above, N + kept), rank, 0, (size_t)nodes, rocprim::plus<int32_t>(), s);
-    if (e != hipSuccess) return e;
-    // nodes from N + kept on were never linked; k_labels takes the last links
-    const int hops = kept > (1 << 18) ? 4 : 8;
-    long long reach = hops;
-    for (; reach < (long long)kept + 1; reach *= hops)
-        hipLaunchKernelGGL(k_above_follow, dim3(blocks_for(kept)), dim3(TB), 0, s, above, N, N + kept, hops);
-    hipLaunchKernelGGL(k_labels, dim3(blocks_for(N)), dim3(TB), 0, s, above, rank, N, nodes, hops, labels);
+    const int2* c = reinterpret_cast<const int2*>(children);
+    const int words = (N + 3) / 4, quads = (kept + 3) / 4;
+    hipLaunchKernelGGL(k_cut_init, dim3(blocks_for(words > quads ? words : quads)), dim3(TB), 0, s, above, kept, reinterpret_cast<uint32_t*>(joined), words);
+    if (kept > 0) hipLaunchKernelGGL(k_cut_links, dim3(blocks_for(kept)), dim3(TB), 0, s, c, N, kept, above, joined);
+    const RootSpans spans = root_spans((unsigned int)N, (unsigned int)kept);
+    const unsigned int stage1 = ((unsigned int)kept + (1u << group_bits(0)) - 1) >> group_bits(0);
+    hipLaunchKernelGGL(k_cut_first, dim3(blocks_for(kept) + (int)spans.all()), dim3(TB), 0, s, above, joined, spans, blocks_for(kept), counts);
+    hipLaunchKernelGGL(k_cut_second, dim3(blocks_for(stage1) + (int)spans.all()), dim3(TB), 0, s, above, joined, spans, blocks_for(stage1), counts, labels);
+    if (kept > 0) {
+        cut_stages<2>(above, kept, (stage1 + (1u << group_bits(1)) - 1) >> group_bits(1), s);
+        hipLaunchKernelGGL(k_cut_labels, dim3(blocks_for(kept)), dim3(TB), 0, s, c, N, kept, above, labels);
+    }
     return hipGetLastError();
 }
 

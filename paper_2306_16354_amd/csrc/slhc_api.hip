@@ -2025,19 +2025,21 @@ int slhc_fused_1nn(const float* Q, int64_t m, const float* Y, int64_t n, int32_t
     });
 }
 
-static int flat_clusters_layout(void* ws, int64_t N, int32_t** above, int32_t** rank, void** temp,
-                                size_t* temp_bytes, size_t* total)
-{
-    Carver c(ws);
-    const size_t nodes = 2 * (size_t)N;
-    *above = c.take<int32_t>(nodes);
-    (void)c.take<int32_t>(nodes);          // (not used; it keeps the size that is reported what it was)
-    *rank = c.take<int32_t>(nodes);
-    *temp_bytes = slhc::flat_clusters_scan_temp_bytes((int)N);
-    *temp = c.take<unsigned char>(*temp_bytes);
-    *total = c.off;
-    return SLHC_OK;
-}
+namespace {
+struct FlatWs {
+    int32_t *above, *counts;
+    unsigned char* joined;
+    size_t bytes;
+    FlatWs(void* ws, int64_t N)
+    {
+        Carver c(ws);
+        above = c.take<int32_t>((size_t)N + 4);                // (read four words and sixteen marks at a time)
+        joined = c.take<unsigned char>((size_t)N + 16);
+        counts = c.take<int32_t>(slhc::flat_clusters_spans(N));
+        bytes = c.off;
+    }
+};
+}  // namespace
 
 int slhc_flat_clusters_workspace_bytes(int64_t N, size_t* bytes)
 {
@@ -2045,8 +2047,8 @@ int slhc_flat_clusters_workspace_bytes(int64_t N, size_t* bytes)
         if (!bytes) { set_err("bytes is NULL"); return SLHC_INVALID_ARG; }
         if (N < 2) { set_err("need N >= 2 (N=%lld)", (long long)N); return SLHC_INVALID_ARG; }
         if (N > 1073741823LL) { set_err("2N exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
-        int32_t *a, *r; void* t; size_t tb;
-        return flat_clusters_layout(nullptr, N, &a, &r, &t, &tb, bytes);
+        *bytes = FlatWs(nullptr, N).bytes;
+        return SLHC_OK;
     });
 }
 
@@ -2058,11 +2060,9 @@ int slhc_flat_clusters(const int32_t* children, int64_t N, int64_t n_clusters, i
         if (N < 2) { set_err("need N >= 2 (N=%lld)", (long long)N); return SLHC_INVALID_ARG; }
         if (N > 1073741823LL) { set_err("2N exceeds 2^31-1"); return SLHC_UNSUPPORTED; }
         if (n_clusters < 1 || n_clusters > N) { set_err("need 1 <= n_clusters <= N (n_clusters=%lld)", (long long)n_clusters); return SLHC_INVALID_ARG; }
-        int32_t *above, *rank; void* temp; size_t temp_bytes, total;
-        flat_clusters_layout(workspace, N, &above, &rank, &temp, &temp_bytes, &total);
-        if (workspace_bytes < total) { set_err("workspace %zu < %zu bytes", workspace_bytes, total); return SLHC_WORKSPACE_TOO_SMALL; }
-        HIP_TRY(slhc::flat_clusters(children, (int)N, (int)n_clusters, labels, above, rank, temp, temp_bytes,
-                                    static_cast<hipStream_t>(stream)));
+        const FlatWs w(workspace, N);
+        if (workspace_bytes < w.bytes) { set_err("workspace %zu < %zu bytes", workspace_bytes, w.bytes); return SLHC_WORKSPACE_TOO_SMALL; }
+        HIP_TRY(slhc::flat_clusters(children, (int)N, (int)n_clusters, labels, w.above, w.joined, w.counts, static_cast<hipStream_t>(stream)));
         return SLHC_OK;
     });
 }
