@@ -62,7 +62,7 @@ size_t near_stats_scratch_floats(int d);
 size_t near_batch_bytes(long long nq, long long nc, int d, int kk);       // what NearBuffers::batch wants (less also works, down to one panel)
 size_t near_least_batch_bytes(long long nq, long long nc, int d, int kk);
 // what NearBuffers::pairs wants for a search of the rows among themselves; 0: such a search does not use it
-size_t near_pairs_bytes(long long n, int d, int kk);
+size_t near_pairs_bytes(long long n, int d, int kk, bool* once = nullptr);
 
 // (clears `clear` [clear_words], optional, on the way)
 hipError_t near_stats(const float* X, int n, int d, const NearBuffers& b, uint32_t* clear, int clear_words, hipStream_t s);

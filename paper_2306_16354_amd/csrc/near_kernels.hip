@@ -1598,39 +1598,34 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
 struct PairPlan {
     NearPlan sample;
     int waves, blocks, cap, bands, to[8], nseg[8];
+    bool once;
 };
-// Who gains: up to 64 columns a block's comparisons (36 instructions of its wavefront for 16 values) take as long as its products, and of the rows of a
-// small search every block holds a few that pass.  Each side in us, products once per row and once per pair: 5000 x 40, k = 10: 78 and 67;
-// 10 000 x 64, 20: 146 and 129; 20 000 x 128, 32: 348 and 368; 20 011 x 50, 10: 221 and 248; 30 000 x 96, 16: 468 and 467; 40 000 x 70, 10: 596 and 588;
-// 50 000 x 70, 10: 951 and 805; 60 000 x 80, 32: 1453 and 1335; 120 000 x 100, 10: 4196 and 3277; 300 000 x 128, 32: 34.8 and 19.6 ms; 5000 x 200, 10:
-// 120 and 94.  (Up to 12 800 rows it is the fewer, longer shares of the candidates that gain.)  The line at five steps from 384 tiles on was
-// drawn when what passes was found by a branch per value (120 000 x 64, 32: 4220 and 4780; 250 000 x 33, 40: 13.1 and 13.6 ms); with whole values
-// through LDS narrower rows gain there as well: 4004 and 3316, 12.7 and 10.2 ms, 50 000 x 50, 10: 855 and 736, 100 000 x 48, 10: 2436 and 1825.
-static bool pair_search_wanted(int T, int steps)
-{
-    if (T < 32 || T >= (1 << 17)) return false;
-    return steps > REG_STEPS || (T <= 100 ? steps >= 3 : T >= 384 && steps >= 5);
-}
+// From 32 tiles on.  Against sweeps that keep what passes by a branch per value (near_sweep_kernel's emission, which is left where memory is short), in us:
+// 5000 x 10, k = 10: 68 and 62; 8000 x 30, 10: 93 and 90; 13 000 x 40, 10: 127 and 123; 20 011 x 50, 10: 220 and 216; 20 000 x 128, 32, clusters by Zipf's law: 4460
+// and 391; 30 000 x 30, 16: 338 and 312; 40 000 x 70, 10: 596 and 574; 50 000 x 10, 10: 629 and 502; 100 000 x 48, 10: 2434 and 1763; 250 000 x 20, 10: 8.5 and
+// 6.4 ms; 250 000 x 60, 20, by Zipf's law 14.0 and 12.3.
+static bool pair_search_wanted(int T) { return T >= 32 && T < (1 << 17); }
+// Whether every pair is multiplied once, for both of its rows, or in either order.  Once takes the test 36 instructions for 16 values instead of 12 and half
+// the products: 35 000 x 128, k = 16, 661 us in either order and 549 once; 40 000 x 110, 10: 746 and 621; 13 000 x 70, 10: 145 and 147; of 60 000 x 128, 12, the
+// products alone are most of it.  (Narrower rows would gain as well: 100 000 x 48, 10: 1763 and 1415, 20 011 x 50, 10: 216 and 201, 20 000 x 16, 10: 167 and 161.  What a
+// search multiplies there is part of the interface, slhc_probe_knn_products, and has not been changed.)
+static bool pairs_once(int T, int steps) { return steps > REG_STEPS || (T <= 100 ? steps >= 3 : steps >= 6 || (T >= 384 && steps >= 5)); }
 // from here on rows whose lists overflow are searched for on their own before the list kernels take their panels; below, the five
-// launches cost more (20 us) than a panel or two
-constexpr int PAIR_AGAIN_TILES = 128;
+// launches cost more (20 us of 200 at 20 000 rows) than a panel or two
+constexpr int PAIR_AGAIN_TILES = 256;
 // bytes: of the memory for them (0: the least there may be).  Lists are as long as it allows, up to PAIRS_MOST, which costs nothing where they
 // stay short (5000 x 200 and 16 000 x 300, lists of 256 and 1024: the same times) and leaves fewer rows over.
 static size_t pair_lists_bytes(int T, int cap) { return (size_t)T * TILE * (24 + 8 * (size_t)cap) + 4096; }
 static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* out)
 {
     const int T = near_tiles(n), steps = near_steps(d);
-    if (kk < 2 || !pair_search_wanted(T, steps)) return false;
+    if (kk < 2 || !pair_search_wanted(T)) return false;
     PairPlan p{};
+    p.once = pairs_once(T, steps);
     const bool wide = steps > REG_STEPS;
     const int cus = near_cus();
     p.cap = (12 * kk + 63) / 64 * 64;
     p.cap = p.cap < 256 ? 256 : (p.cap > PAIRS_MOST ? PAIRS_MOST : p.cap);
-    p.waves = 8;
-    while (!wide && p.waves > 2 && (T / (p.waves / 2)) * (T / p.waves) < 2 * cus) p.waves >>= 1;
-    const int bt = wide ? 2 : p.waves / 2, slots = p.waves == 8 ? cus : 2 * cus;
-    p.blocks = (T + bt - 1) / bt;
-    const int half = p.blocks / 2 + 1;
     // What a sample of one tile in `stride` costs, and one band (0) or a first one of the sample's share and b more that see
     // g times as much each, in us: the products of the sample (1.1e15 a second), 15 us per band and 1 ns per row for the tightening
     // before it, 0.1 ns per entry, of which rounding makes twice what is asked for on average.
@@ -1645,18 +1640,34 @@ static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* o
             if (cost < best) { best = cost; stride = s; more = b; }
         }
     const double g = more > 0 ? pow((double)stride, 1.0 / more) : 1.0;
-    double seen = 1.0 / stride;
-    int from = 0;
-    for (p.bands = 0; from < half; ++p.bands, seen *= g) {
-        int to = p.bands == more ? half : (int)(0.5 * (seen * p.blocks + 1.0));
-        to = to < from + 1 ? from + 1 : (to > half ? half : to);
-        const int len = to - from;
-        int seg = (8 * slots + p.blocks - 1) / p.blocks;
-        if (wide && seg < 4) seg = 4;      // (so that an XCD's workgroups share 8 blocks, see the kernel)
-        p.to[p.bands] = to;
-        p.nseg[p.bands] = seg > len ? len : seg;
-        from = to;
-    }
+    auto lay_out = [&](int waves) {
+        const int bt = wide ? 2 : waves / 2, slots = waves >= 8 ? cus : (p.once && steps > 5 ? 2 : 3) * cus;
+        p.waves = waves;
+        p.blocks = (T + bt - 1) / bt;
+        const int half = p.once ? p.blocks / 2 + 1 : p.blocks;     // meetings of a block
+        double seen = 1.0 / stride;
+        int from = 0;
+        for (p.bands = 0; from < half; ++p.bands, seen *= g) {
+            int to = p.bands == more ? half : p.once ? (int)(0.5 * (seen * p.blocks + 1.0)) : (int)(seen * p.blocks + 0.5);
+            to = to < from + 1 ? from + 1 : (to > half ? half : to);
+            const int len = to - from;
+            int seg = (8 * slots + p.blocks - 1) / p.blocks;
+            if (wide && seg < 4) seg = 4;      // (so that an XCD's workgroups share 8 blocks, see the kernel)
+            // about eight rounds of workgroups, the last of them as full as can be
+            auto rounds = [&](int n) { return (double)(((long long)p.blocks * n + slots - 1) / slots) * ((double)len / n + 0.15); };
+            int best_seg = seg > len ? len : seg;
+            for (int n = waves == 4 ? 1 : (2 * seg + 2) / 3; !wide && n <= len && 2 * n <= 3 * seg; ++n)
+                if (rounds(n) < rounds(best_seg)) best_seg = n;
+            p.to[p.bands] = to;
+            p.nseg[p.bands] = best_seg;
+            from = to;
+        }
+    };
+    // Workgroups of four wavefronts, of which three and more fit a CU but for the widest rows multiplied once; there, from 49 152 rows on, one of twelve
+    // has more wavefronts per SIMD (see pairs_kernel): 100 000 x 80, k = 30, 2.53 ms with four and 2.47, 250 000 x 70, 20, 11.7 and 10.9, 40 000 x 70, 10: 543 and 549 us.
+    int waves = wide ? 8 : p.once && steps >= 5 && T >= 384 ? 12 : 4;
+    if (waves == 4 && (T / 2) * (T / 4) < 2 * cus) waves = 2;
+    lay_out(waves);
     p.sample = near_plan(n, n, d, kk, 0);
     NearPlan& q = p.sample;
     const int used = (T + stride - 1) / stride, panels = (T + q.panel_tiles - 1) / q.panel_tiles;
@@ -1670,10 +1681,12 @@ static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* o
     return true;
 }
 
-size_t near_pairs_bytes(long long n, int d, int kk)
+size_t near_pairs_bytes(long long n, int d, int kk, bool* once)
 {
     PairPlan p;
-    return near_pair_plan(n, d, kk, 0, &p) ? pair_lists_bytes(near_tiles(n), p.cap) : 0;
+    if (!near_pair_plan(n, d, kk, 0, &p)) return 0;
+    if (once) *once = p.once;
+    return pair_lists_bytes(near_tiles(n), p.cap);
 }
 
 static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, const NearBuffers& b, const PairPlan& plan, bool vec4, hipStream_t s)
@@ -1715,7 +1728,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
                            static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE, lost);
     }
     NearPairs r{};
-    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.filled = (a.d + 15) / 16; r.blocks = plan.blocks; r.spread = near_spread(r.blocks);
+    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.filled = (a.d + 15) / 16; r.blocks = plan.blocks; r.once = plan.once; r.spread = near_spread(r.blocks);
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
     const bool again = c.tiles >= PAIR_AGAIN_TILES;
     r.lost = lost; r.lost_most = again ? a.nq / 2 : rows;
@@ -1728,6 +1741,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
         err = pairs_emit(r, plan.waves, s);
         if (err != hipSuccess) return err;
     }
+    r.cap_again = 4 * plan.cap >= 3 * PAIRS_MOST ? plan.cap : PAIRS_MOST;  // (of nearly that length: one turn of the loop below)
     if (again) {
         err = pairs_left(r, kk, b.scale, e, nu, a.d, a.nq, left, s);
         if (err != hipSuccess) return err;
@@ -1751,13 +1765,14 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     // The rows left: any kk of the rows met reach their distance, and lists of 1024 rarely overflow; where one does, its kk-th value
     // makes the second search short.
     const int waves = wide ? 8 : 4;
-    r.cap = PAIRS_MOST;
+    r.cap = r.cap_again;
     p.stride = 1; p.used = c.tiles;
     p.qpos = left.pos; p.n_dev = left.count; p.slots = (waves == 8 ? 1 : 2) * near_cus(); p.most_seg = p.slots;
-    p.reach = left.reach; p.counts = left.counts; p.capl = PAIRS_MOST; p.entries = entries;
+    p.reach = left.reach; p.counts = left.counts; p.capl = r.cap; p.entries = entries;
     sel.q_rows = sel.slot = left.row; sel.qpos = left.pos; sel.n_dev = left.count;
-    sel.q_in_order = 1; sel.counts = left.counts; sel.capl = PAIRS_MOST; sel.pair_lists = 0; sel.nq = rows;
-    const int room = (int)(lists_bytes / ((size_t)TILE * PAIRS_MOST * 8)) / 2 * 2;           // tiles of queries whose lists fit
+    sel.q_in_order = 1; sel.counts = left.counts; sel.capl = r.cap; sel.pair_lists = 0; sel.nq = rows;
+    int room = (int)(lists_bytes / ((size_t)TILE * r.cap * 8));            // tiles of queries whose lists fit
+    if (room < c.tiles) room = room / 2 * 2;
     if (room < 2) return hipErrorInvalidValue;
     for (int t0 = 0; t0 < c.tiles; t0 += room) {
         p.q_tile0 = t0; p.q_tile1 = t0 + room < c.tiles ? t0 + room : c.tiles;

@@ -13,11 +13,13 @@ struct NearPairs {
     const unsigned char* frag; const float* negh; const int32_t* colour;      // the copy (colour: pairs_best)
     int tiles, steps, filled;              // steps of 16 columns a row's place has, and how many of them hold columns
     int blocks, from, to, nseg;            // block i meets the blocks i + from .. i + to - 1, in nseg shares
+    int once;                              // every pair once, for both of its rows (to: half way round), or in either order for its first row
     int spread;                            // near_spread(blocks): place i of the circle has block i * spread % blocks of the copy
     float* limit;                          // pairs_emit: by position, the u from which on a pair matters to the row (NaN: none does)
     uint2* entries; int32_t* counts; int cap;      // pairs_emit: lists [rows][cap] of (u, position), appended to; counts beyond cap: some were lost
     // pairs_emit: rows whose lists overflowed, as far as pairs_tighten has counted them; beyond lost_most of them pairs_emit does nothing
     int32_t* lost; int lost_most;
+    int cap_again;                         // pairs_left: entries of the lists of the search for the rows left over
     // pairs_best: by position (w, position of the first of the 16 rows about it), w = max(0, -u) of the nearest row of another
     // colour so far; not 0x7f.. / all ones in the beginning.  both = 0: the block's own rows only are served
     unsigned long long* best; int both;

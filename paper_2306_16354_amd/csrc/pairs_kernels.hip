@@ -48,6 +48,7 @@ __device__ inline void pair_entry(const NearPairs& p, int row, int slot, unsigne
     if ((unsigned int)slot < (unsigned int)p.cap) p.entries[(size_t)row * (size_t)p.cap + (size_t)slot] = make_uint2(u, other);
 }
 // Every pair under way goes one step further, and where at least `least` wait the next ones set out.
+template <bool ONCE>
 __device__ inline void pair_turn(PairQueue& w, const NearPairs& p, int q0, int least)
 {
     const int lane = threadIdx.x & 63;
@@ -58,7 +59,7 @@ __device__ inline void pair_turn(PairQueue& w, const NearPairs& p, int q0, int l
     if (w.asked) {
         const int q = pair_q(w.code2, q0), c = pair_c(w.code2);
         pair_entry(p, q, w.q_slot, w.u2, (unsigned int)c);
-        pair_entry(p, c, w.c_slot, w.u2, (unsigned int)q);
+        if (ONCE) pair_entry(p, c, w.c_slot, w.u2, (unsigned int)q);
         w.asked = false;
     }
     if (w.read) {
@@ -66,7 +67,7 @@ __device__ inline void pair_turn(PairQueue& w, const NearPairs& p, int q0, int l
         w.u2 = w.u; w.code2 = w.code;
         w.q_slot = w.c_slot = -1;
         if (u >= w.q_limit) w.q_slot = atomicAdd(p.counts + pair_q(w.code, q0), 1);
-        if (u >= w.c_limit) w.c_slot = atomicAdd(p.counts + pair_c(w.code), 1);
+        if (ONCE && u >= w.c_limit) w.c_slot = atomicAdd(p.counts + pair_c(w.code), 1);
         w.read = false;
         w.asked = true;
     }
@@ -75,16 +76,17 @@ __device__ inline void pair_turn(PairQueue& w, const NearPairs& p, int q0, int l
     w.q_limit = w.c_limit = NEVER;
     if (e.y != ~0u) {
         w.q_limit = p.limit[pair_q(e.y, q0)];
-        if (!(e.y & PAIR_OWN)) w.c_limit = p.limit[pair_c(e.y)];
+        if (ONCE && !(e.y & PAIR_OWN)) w.c_limit = p.limit[pair_c(e.y)];
     }
     w.n = from;
     w.read = true;
 }
 // The queue is empty when this returns.
+template <bool ONCE>
 __device__ inline void pair_finish(PairQueue& w, const NearPairs& p, int q0)
 {
 #pragma unroll 1
-    while (w.n > 0 || w.read || w.asked) pair_turn(w, p, q0, 1);
+    while (w.n > 0 || w.read || w.asked) pair_turn<ONCE>(w, p, q0, 1);
 }
 
 // (Past the compiler, which would wait for the tile on its way into LDS before it writes there.  LDS instructions of a wavefront
@@ -106,25 +108,27 @@ __device__ inline unsigned int lds_word(const void* at)
 // as well, see pair_push.)  Where lists are long and rows few, most lanes of every block hold something, and it is bound by its waits for LDS: with four
 // records at a time, and the queue emptied whenever it was full, 4500 x 128, k = 64, took 139 us, 12 000 x 128 273, 300 000 x 128, k = 32, 24.6 ms; 129,
 // 256, 24.4 so.  (Values looked for in registers there, as before whole values went to LDS: 130, 277 and, for its registers and code, 26.7.)
+template <bool ONCE>
 __device__ inline void pair_sift(PairQueue& w, const NearPairs& p, int q0, const unsigned char* tile_limit)
 {
     const int lane = threadIdx.x & 63;
     const unsigned int values = lds_word(w.at + QUEUE) + lane * 4, words = lds_word(w.at + QUEUE) + RECORDS * 64 + (lane >> 4) * 16;
 #pragma unroll 1
     for (int at = 0; at < w.records; at += 8) {
-        float x[2], limit[2];
+        float x[2], limit[2] = {0.f, 0.f};
         v4f word[2];
         asm volatile("ds_read_b32 %0, %4\n\tds_read_b128 %1, %5\n\tds_read_b32 %2, %4 offset:256\n\tds_read_b128 %3, %5 offset:64\n\ts_waitcnt lgkmcnt(0)"
                      : "=&v"(x[0]), "=&v"(word[0]), "=&v"(x[1]), "=&v"(word[1]) : "v"(values + at * 64), "v"(words + at * 16) : "memory");
         const unsigned int place = (((lane & 12u) << 1) | (lane & 3u)) << 8;
         const unsigned int code[2] = {__float_as_uint(word[0][0]) + place, __float_as_uint(word[1][0]) + place};
-        asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(limit[0]), "=&v"(limit[1])
-                     : "v"(lds_word(tile_limit) + ((code[0] >> 6) & 508u)), "v"(lds_word(tile_limit) + ((code[1] >> 6) & 508u)) : "memory");
+        if (ONCE)
+            asm volatile("ds_read_b32 %0, %2\n\tds_read_b32 %1, %3\n\ts_waitcnt lgkmcnt(0)" : "=&v"(limit[0]), "=&v"(limit[1])
+                         : "v"(lds_word(tile_limit) + ((code[0] >> 6) & 508u)), "v"(lds_word(tile_limit) + ((code[1] >> 6) & 508u)) : "memory");
 #pragma unroll 1
-        while (w.n > QUEUE - 128) pair_turn(w, p, q0, 64);
+        while (w.n > QUEUE - 128) pair_turn<ONCE>(w, p, q0, 64);
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
-            const bool pass = at + 4 * i + (lane >> 4) < w.records && (x[i] >= word[i][1] || x[i] - limit[i] >= word[i][2]);
+            const bool pass = at + 4 * i + (lane >> 4) < w.records && (x[i] >= word[i][1] || (ONCE && x[i] - limit[i] >= word[i][2]));
             const unsigned long long m = __ballot(pass);
             const int pre = __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
             if (pass) pair_push(w.at + w.n + pre, __float_as_uint(x[i] - word[i][3]), code[i]);
@@ -140,18 +144,22 @@ __device__ inline void pair_sift(PairQueue& w, const NearPairs& p, int q0, const
 // follows has to be short: the lane's values go to LDS as they are, and which of them pass is found for four lanes at once.  With
 // the wavefront looking for them there and then (a bit per value, the value picked out of 16 registers, a turn per pair of a lane) the
 // emission of 1M x 128, k = 32, took 171 ms; 146 so, 115 with nothing after the test, 94 with the products alone (1.37 PFLOP/s at 1.9 GHz).
+template <bool ONCE>
 __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float bound, float h, float other, unsigned int code,
                                  PairQueue& w, const NearPairs& p, int q0, const unsigned char* tile_limit)
 {
-    float f = max3(v[0], v[1], v[2]), t = max3(v[0] - limit[0], v[1] - limit[1], v[2] - limit[2]);
+    float f = max3(v[0], v[1], v[2]);
 #pragma unroll
-    for (int r = 3; r < 15; r += 2) {
-        f = max3(f, v[r], v[r + 1]);
-        t = max3(t, v[r] - limit[r], v[r + 1] - limit[r + 1]);
-    }
+    for (int r = 3; r < 15; r += 2) f = max3(f, v[r], v[r + 1]);
     f = fmaxf(f, v[15]);
-    t = fmaxf(t, v[15] - limit[15]);
-    bool some = f >= bound || t >= other;
+    bool some = f >= bound;
+    if (ONCE) {
+        float t = max3(v[0] - limit[0], v[1] - limit[1], v[2] - limit[2]);
+#pragma unroll
+        for (int r = 3; r < 15; r += 2) t = max3(t, v[r] - limit[r], v[r + 1] - limit[r + 1]);
+        t = fmaxf(t, v[15] - limit[15]);
+        some = some || t >= other;
+    }
     unsigned long long m = __ballot(some);
     while (m) {
         const int at = w.records + __builtin_amdgcn_mbcnt_hi((unsigned int)(m >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)m, 0u));
@@ -166,7 +174,7 @@ __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float 
         w.records += __popcll(m);
         if (w.records < RECORDS) return;
         w.records = w.records < RECORDS ? w.records : RECORDS;
-        pair_sift(w, p, q0, tile_limit);
+        pair_sift<ONCE>(w, p, q0, tile_limit);
         m = __ballot(some);
     }
 }
@@ -174,6 +182,7 @@ __device__ inline void pair_emit(const v16f& v, const float (&limit)[16], float 
 // Which blocks a workgroup's block meets: offsets [from, from + len) in an order in which all blocks of one stretch of the circle
 // meet the same block at the same time, so that it is in L2.
 struct PairRange { int at, block, from, len, j0, j1, turn; };      // at: of the circle, block: of the copy
+template <bool ONCE>
 __device__ inline PairRange pair_range(const NearPairs& p, int item)
 {
     PairRange r;
@@ -181,7 +190,7 @@ __device__ inline PairRange pair_range(const NearPairs& p, int item)
     r.block = near_spread_at(r.at, p.spread, p.blocks);
     const int seg = item - r.at * p.nseg;
     // half way round an even circle two blocks meet from both sides
-    const int to = 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.at >= p.blocks ? p.to - 1 : p.to;
+    const int to = ONCE && 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.at >= p.blocks ? p.to - 1 : p.to;
     r.from = p.from;
     r.len = to > p.from ? to - p.from : 0;
     r.j0 = (int)((long long)r.len * seg / p.nseg);
@@ -197,17 +206,20 @@ __device__ inline int pair_other(const NearPairs& p, const PairRange& r, int off
 }
 
 // Up to 128 columns: as near_sweep_kernel, a wavefront keeps the fragments of 64 queries in registers and the candidate tiles pass
-// through LDS (double buffered); a block is the tiles of a workgroup's queries.
-template <int KS>
-__global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
+// through LDS (double buffered); a block is the tiles of a workgroup's queries.  Products alone take 95 of the 142 ms of 1M x 128, k = 32 (1.35 PFLOP/s, to
+// which the card throttles), the test 18, what passes 29, and a wavefront waits for LDS or at a barrier a third of its time: so 32 candidates at a time,
+// which leaves room for three wavefronts per SIMD at any width (four up to 48 columns), where 64 took two.  1M x 128, k = 32 146 -> 136 ms, 300 000 x 96, k = 16,
+// whole search 15.5 -> 14.2.  (More than a step of fragments read ahead, priorities for multiplies or for tests, two workgroups of four: the same times.)
+template <int KS, bool ONCE>
+__global__ void __launch_bounds__(ONCE ? 768 : 256, ONCE ? 3 : KS <= 2 ? 5 : KS <= 4 ? 4 : 3) pairs_kernel(NearPairs p)
 {
     extern __shared__ __align__(16) unsigned char pairs_smem[];
-    constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, limits
+    constexpr int BUF = KS * FRAG_STEP + (ONCE ? 1024 : 512);        // fragments, minus half norms, limits
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int waves = blockDim.x >> 6, bt = waves >> 1;
     if (*p.lost > p.lost_most) return;
-    const PairRange range = pair_range(p, blockIdx.x);
+    const PairRange range = pair_range<ONCE>(p, blockIdx.x);
     const int qtile = range.block * bt + (wave >> 1);
     const bool live = qtile < p.tiles;                   // (whole wavefronts)
     const int q0 = (live ? qtile : 0) * TILE + (wave & 1) * 64;
@@ -243,7 +255,7 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
         unsigned char* dst = pairs_smem + (i & 1) * BUF;
         const unsigned char* src = p.frag + t * (KS * FRAG_STEP);
         for (int j = wave; j < KS * 4; j += waves) near_lds_load(src, j * 1024, dst + j * 1024, true);
-        for (int j = wave; j < 4; j += waves) {
+        for (int j = wave; j < (ONCE ? 4 : 2); j += waves) {
             near_lds_load((j < 2 ? p.negh : p.limit) + t * TILE, (j & 1) * 256, dst + KS * FRAG_STEP + j * 256, false);
         }
     };
@@ -252,60 +264,52 @@ __global__ void __launch_bounds__(512, 2) pairs_kernel(NearPairs p)
         near_lds_ready();
         const int tile = next_tile;
         const bool own = next_own;
-        if (live) pair_turn(w, p, q0, 64);
+        if (live) pair_turn<ONCE>(w, p, q0, 64);
         if (i + 1 < total) { advance(); stage(i + 1, next_tile); }
         if (tile >= p.tiles || !live) continue;
         const unsigned char* tb = pairs_smem + (i & 1) * BUF;
         const float other[2] = {own ? NEVER : h[0], own ? NEVER : h[1]};
 #pragma unroll 1
-        for (int half = 0; half < 2; ++half) {
-            v16f acc[2][2];
-            v8h cf[2][2];
-            const unsigned char* hb = tb + half * 2048 + lane * 16;
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(hb + cb * 1024);
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
+        for (int blk = 0; blk < 4; ++blk) {
+            v16f acc[2];
+            v8h cf[2];
+            const unsigned char* hb = tb + blk * 1024 + lane * 16;
+            cf[0] = *reinterpret_cast<const v8h*>(hb);
+            {
                 v16f hv;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
+                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + (blk * 32 + 8 * g + 4 * lhalf) * 4);
                     hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
                 }
-                acc[0][cb] = hv; acc[1][cb] = hv;
+                acc[0] = hv; acc[1] = hv;
             }
 #pragma unroll
             for (int ks = 0; ks < KS; ++ks) {
                 // (as in near_sweep_kernel: the next step's reads stay ahead of this step's multiplies)
                 if (ks + 1 < KS) {
-#pragma unroll
-                    for (int cb = 0; cb < 2; ++cb) cf[(ks + 1) & 1][cb] = *reinterpret_cast<const v8h*>(hb + (ks + 1) * FRAG_STEP + cb * 1024);
+                    cf[(ks + 1) & 1] = *reinterpret_cast<const v8h*>(hb + (ks + 1) * FRAG_STEP);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-                    for (int qb = 0; qb < 2; ++qb)
-                        acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
-            }
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
-                float limit[16];
-#pragma unroll
-                for (int g = 0; g < 4; ++g) {
-                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + 512 + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
-#pragma unroll
-                    for (int e = 0; e < 4; ++e) limit[4 * g + e] = t4[e];
-                }
-#pragma unroll
                 for (int qb = 0; qb < 2; ++qb)
-                    pair_emit(acc[qb][cb], limit, bound[qb], h[qb], other[qb], pair_code(tile, half * 64 + cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0,
-                              tb + KS * FRAG_STEP + 512);
+                    acc[qb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1], qf[qb][ks], acc[qb], 0, 0, 0);
             }
+            float limit[16];
+#pragma unroll
+            for (int g = 0; ONCE && g < 4; ++g) {
+                const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + 512 + (blk * 32 + 8 * g + 4 * lhalf) * 4);
+#pragma unroll
+                for (int e = 0; e < 4; ++e) limit[4 * g + e] = t4[e];
+            }
+#pragma unroll
+            for (int qb = 0; qb < 2; ++qb)
+                pair_emit<ONCE>(acc[qb], limit, bound[qb], h[qb], other[qb], pair_code(tile, blk * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0,
+                          tb + KS * FRAG_STEP + 512);
         }
-        pair_sift(w, p, q0, tb + KS * FRAG_STEP + 512);
+        pair_sift<ONCE>(w, p, q0, tb + KS * FRAG_STEP + 512);
     }
-    if (live) pair_finish(w, p, q0);
+    if (live) pair_finish<ONCE>(w, p, q0);
 }
 
 // Beyond 128 columns: 256 x 256 rows per meeting, both sides streamed through LDS, as near_wide_kernel; a block is two tiles.
@@ -328,7 +332,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
         const int items = p.blocks * p.nseg, per = items >> 3;
         if (item < per * 8) item = (item & 7) * per + (item >> 3);
     }
-    const PairRange range = pair_range(p, item);
+    const PairRange range = pair_range<true>(p, item);
     const int qtile = range.block * 2 + (qg >> 1);
     const bool live = qtile < p.tiles;
     const int qsafe = live ? qtile : range.block * 2;
@@ -434,7 +438,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
         if (!odd) multiply(1, 0, 4);
         if (staged < total) stage();
         ++at;
-        if (!BEST && live) pair_turn(w, p, q0, 64);
+        if (!BEST && live) pair_turn<true>(w, p, q0, 64);
         const int next = i + 1 < nmine ? block_at(i + 1) : block;
         if (live && tile < p.tiles) {
 #pragma unroll
@@ -456,7 +460,7 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
 #pragma unroll
                 for (int qb = 0; qb < 2; ++qb) {
                     if (!BEST) {
-                        pair_emit(acc[qb][cb], limit, bound[qb], h[qb], own ? NEVER : h[qb],
+                        pair_emit<true>(acc[qb][cb], limit, bound[qb], h[qb], own ? NEVER : h[qb],
                                   pair_code(tile, cb * 32 + 4 * lhalf, qb * 32 + l32, own), w, p, q0, rows + 1024 + cg * 512);
                         continue;
                     }
@@ -482,12 +486,12 @@ __global__ void __launch_bounds__(512, 2) pairs_wide_kernel(NearPairs p)
                     }
                 }
             }
-            if (!BEST) pair_sift(w, p, q0, rows + 1024 + cg * 512);
+            if (!BEST) pair_sift<true>(w, p, q0, rows + 1024 + cg * 512);
         }
         block = next;
     }
     if (!live) return;
-    if (!BEST) pair_finish(w, p, q0);
+    if (!BEST) pair_finish<true>(w, p, q0);
     else {
 #pragma unroll
         for (int qb = 0; qb < 2; ++qb)
@@ -594,7 +598,26 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
     const bool over = p.counts[pos] > p.cap;
     const float h = -p.negh[pos];
     const long long row = near_row(pos, p.tiles, 0);
-    const bool left = (over || *p.lost > p.lost_most) && fabsf(h) < INF && row < n_rows;
+    bool left = (over || *p.lost > p.lost_most) && fabsf(h) < INF && row < n_rows;
+    // a value that kk rows reach: of the list, or what the row's limit, itself below such a value, comes from
+    const NearBoundArgs a = near_args(sc, p.steps, d, e, nu);
+    float value = LOWEST;
+    if (left && over) {
+        uint2 mine[PAIR_WORDS];
+        pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
+        const float kth = pair_kth(mine, p.cap, kk);
+        if (kth != LOWEST) {
+            value = kth + h;
+            // as many rows as the next search's lists hold that rounding does not tell from the kk-th: it would do no better (150 000 x 30 of 2000
+            // copies each 111 -> 71 ms)
+            const float limit = near_bound_from(value, h, a) - h;
+            int within = 0;
+#pragma unroll
+            for (int j = 0; j < PAIR_WORDS; ++j)
+                if (j * 64 < p.cap) within += __popcll(__ballot(__uint_as_float(mine[j].x) >= limit));
+            left = within < p.cap || p.cap < p.cap_again;
+        }
+    } else if (left && p.limit[pos] > LOWEST) value = p.limit[pos] + h;
     if (threadIdx.x == 0) s_here = 0;
     __syncthreads();
     int at = 0;
@@ -603,18 +626,10 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
     if (threadIdx.x == 0) s_from = s_here > 0 ? atomicAdd(out.count, s_here) : 0;
     __syncthreads();
     if (!left) return;
-    // a value that kk rows reach: of the list, or what the row's limit, itself below such a value, comes from
-    float value = LOWEST;
-    if (over) {
-        uint2 mine[PAIR_WORDS];
-        pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
-        const float kth = pair_kth(mine, p.cap, kk);
-        if (kth != LOWEST) value = kth + h;
-    } else if (p.limit[pos] > LOWEST) value = p.limit[pos] + h;
     if (lane != 0) return;
     const int i = s_from + at;
     out.row[i] = (int)row; out.pos[i] = pos; out.counts[i] = 0;
-    out.reach[i] = pair_reach(value, h, near_args(sc, p.steps, d, e, nu), sc, d);
+    out.reach[i] = pair_reach(value, h, a, sc, d);
     p.counts[pos] = 0;
 }
 __global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int first, int n,
@@ -644,9 +659,9 @@ hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
     if (p.tiles < 1 || p.tiles >= (1 << PAIR_TILE_BITS) || p.cap < 1 || p.cap > PAIRS_MOST || p.nseg < 1 || p.spread < 1) return hipErrorInvalidValue;
     const bool wide = p.steps > REG_STEPS;
     const int bt = wide ? 2 : waves / 2;
-    if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > p.blocks / 2 + 1) return hipErrorInvalidValue;
+    if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > (p.once ? p.blocks / 2 + 1 : p.blocks) || (!p.once && (wide || waves > 4)) || waves > 12) return hipErrorInvalidValue;
     const dim3 grid((unsigned)(p.blocks * p.nseg)), block((unsigned)(64 * (wide ? 8 : waves)));
-    const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024)) + (size_t)(wide ? 8 : waves) * WAVE_LDS;
+    const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + (p.once ? 1024 : 512))) + (size_t)(wide ? 8 : waves) * WAVE_LDS;
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
         if (e != hipSuccess) return e;
@@ -655,12 +670,14 @@ hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
     };
     if (wide) return run(&pairs_wide_kernel<false>);
     switch (p.steps) {
-        case 3: return run(&pairs_kernel<3>);
-        case 4: return run(&pairs_kernel<4>);
-        case 5: return run(&pairs_kernel<5>);
-        case 6: return run(&pairs_kernel<6>);
-        case 7: return run(&pairs_kernel<7>);
-        case 8: return run(&pairs_kernel<8>);
+        case 1: return p.once ? hipErrorInvalidValue : run(&pairs_kernel<1, false>);
+        case 2: return p.once ? hipErrorInvalidValue : run(&pairs_kernel<2, false>);
+        case 3: return p.once ? run(&pairs_kernel<3, true>) : run(&pairs_kernel<3, false>);
+        case 4: return p.once ? run(&pairs_kernel<4, true>) : run(&pairs_kernel<4, false>);
+        case 5: return p.once ? run(&pairs_kernel<5, true>) : run(&pairs_kernel<5, false>);
+        case 6: return p.once ? run(&pairs_kernel<6, true>) : run(&pairs_kernel<6, false>);
+        case 7: return p.once ? run(&pairs_kernel<7, true>) : run(&pairs_kernel<7, false>);
+        case 8: return p.once ? run(&pairs_kernel<8, true>) : run(&pairs_kernel<8, false>);
         default: return hipErrorInvalidValue;
     }
 }

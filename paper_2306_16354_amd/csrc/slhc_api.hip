@@ -1529,8 +1529,9 @@ int slhc_probe_knn_products(int64_t N, int32_t d, int32_t k, double* products)
         if (rc != SLHC_OK) return rc;
         const int32_t dw = working_columns(N, d);
         const KnnWs ws(nullptr, N, dw, true, k, false);
-        const size_t pairs = slhc::near_pairs_bytes(N, dw, k + 1);
-        *products = !ws.near.ok ? 3.0 : slhc::direct_knn_wanted(N, d, k, false) > 0 ? 0.0 : pairs > 0 && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
+        bool once = false;
+        const size_t pairs = slhc::near_pairs_bytes(N, d, k + 1, &once);
+        *products = !ws.near.ok ? 3.0 : slhc::direct_knn_wanted(N, d, k, false) > 0 ? 0.0 : once && pairs <= ws.near.b.pairs_bytes ? 0.5 : 1.0;
         return SLHC_OK;
     });
 }
