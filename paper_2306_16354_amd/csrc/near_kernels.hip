@@ -1101,12 +1101,17 @@ struct NearSelect {
     const int32_t* region; const float* negh_local; const NearScale* sc_local;
 };
 
-template <bool VEC4>
+// How rows are read: 2 by aligned quads, 1 by quads at any word, 0 by words.  Quads at any word cost a second branch for a row's end, and pay from 64
+// columns on: selection of 20 000 rows, k = 16, of 50 columns 48 us by words and 50, of 65 52 and 48, of 101 64 and 50, of 401 304 and 167.
+static int near_vec(bool aligned, int d) { return aligned ? 2 : d >= 64 ? 1 : 0; }
+template <int VEC>
 __device__ inline v4f near_quad(const float* __restrict__ row, int t, int d)
 {
     v4f v = {0.f, 0.f, 0.f, 0.f};
-    if (VEC4) {
+    if (VEC == 2) {
         if (t < d) v = *reinterpret_cast<const v4f*>(row + t);
+    } else if (VEC == 1 && t + 4 <= d) {
+        v = *reinterpret_cast<const v4f_word*>(row + t);
     } else {
 #pragma unroll
         for (int e = 0; e < 4; ++e)
@@ -1124,36 +1129,41 @@ __device__ inline float near_quad_sqdist(v4f a, v4f b, float s)
 // The exact distance of row xa to row xb by eight lanes, in the order of group8_sqdist (sweep_kernels.hip): slabs of 64
 // features, lane g of eight adds features 4g.. and 4(g + 8).. of every slab into two sums, xor butterfly 1, 2, 4.  q: what
 // lane g adds of the first 128 features of xa.
-template <bool VEC4>
-__device__ inline float near_exact(const v4f (&q)[4], const float* __restrict__ xa, const float* __restrict__ xb, int d, int g)
+template <int VEC>
+__device__ inline float near_exact(const v4f (&q)[4], const v4f (&b)[4], const float* __restrict__ xa, const float* __restrict__ xb, int d, int g)
 {
     float s0 = 0.f, s1 = 0.f;
-    {
-        const v4f b00 = near_quad<VEC4>(xb, 4 * g, d), b10 = near_quad<VEC4>(xb, 4 * g + 32, d);
-        const v4f b01 = near_quad<VEC4>(xb, 4 * g + 64, d), b11 = near_quad<VEC4>(xb, 4 * g + 96, d);
-        s0 = near_quad_sqdist(q[0], b00, s0); s0 = near_quad_sqdist(q[2], b01, s0);
-        s1 = near_quad_sqdist(q[1], b10, s1); s1 = near_quad_sqdist(q[3], b11, s1);
-    }
+    s0 = near_quad_sqdist(q[0], b[0], s0); s0 = near_quad_sqdist(q[2], b[2], s0);
+    s1 = near_quad_sqdist(q[1], b[1], s1); s1 = near_quad_sqdist(q[3], b[3], s1);
     for (int base = 128; base < d; base += 128) {
         const int t0 = base + 4 * g;
-        const v4f a00 = near_quad<VEC4>(xa, t0, d), b00 = near_quad<VEC4>(xb, t0, d);
-        const v4f a10 = near_quad<VEC4>(xa, t0 + 32, d), b10 = near_quad<VEC4>(xb, t0 + 32, d);
-        const v4f a01 = near_quad<VEC4>(xa, t0 + 64, d), b01 = near_quad<VEC4>(xb, t0 + 64, d);
-        const v4f a11 = near_quad<VEC4>(xa, t0 + 96, d), b11 = near_quad<VEC4>(xb, t0 + 96, d);
+        const v4f a00 = near_quad<VEC>(xa, t0, d), b00 = near_quad<VEC>(xb, t0, d);
+        const v4f a10 = near_quad<VEC>(xa, t0 + 32, d), b10 = near_quad<VEC>(xb, t0 + 32, d);
+        const v4f a01 = near_quad<VEC>(xa, t0 + 64, d), b01 = near_quad<VEC>(xb, t0 + 64, d);
+        const v4f a11 = near_quad<VEC>(xa, t0 + 96, d), b11 = near_quad<VEC>(xb, t0 + 96, d);
         s0 = near_quad_sqdist(a00, b00, s0); s0 = near_quad_sqdist(a01, b01, s0);
         s1 = near_quad_sqdist(a10, b10, s1); s1 = near_quad_sqdist(a11, b11, s1);
     }
     return lanes_add8(s0) + lanes_add8(s1);
 }
-template <bool VEC4>
+template <int VEC>
 __device__ inline void near_first_quads(v4f (&q)[4], const float* __restrict__ xa, int d, int g)
 {
 #pragma unroll
-    for (int j = 0; j < 4; ++j) q[j] = near_quad<VEC4>(xa, 4 * g + 32 * j, d);
+    for (int j = 0; j < 4; ++j) q[j] = near_quad<VEC>(xa, 4 * g + 32 * j, d);
+}
+template <int VEC>
+__device__ inline float near_exact(const v4f (&q)[4], const float* __restrict__ xa, const float* __restrict__ xb, int d, int g)
+{
+    v4f b[4];
+    near_first_quads<VEC>(b, xb, d, g);
+    return near_exact<VEC>(q, b, xa, xb, d, g);
 }
 
-// One wavefront per query.
-template <bool VEC4>
+// One wavefront per query.  Of 20 011 x 50, k = 10, 50 us: the entries' way into LDS 14, the bound from them 15 (two to four values a lane, looked for in LDS at every step of
+// the bisection), the exact distances 15 (eight pairs at a time, each row waited for), ranks 4.  With the values in registers where they are few, and the rows of 16 pairs
+// on their way at once, 43; 50 000 x 128, k = 32 179 -> 152, connection rounds and lists of 1M x 128 4.4 -> 3.5 ms.
+template <int VEC>
 __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
 {
     __shared__ unsigned long long keys_[4][MAX_ENTRIES + 64];
@@ -1224,10 +1234,11 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
         const float nl = p.negh_local[qcopy];
         const NearBoundArgs al = near_args(p.sc_local, p.steps, p.d, p.e, p.nu);
         if (n > p.kk + 4) {
-            const float kth = near_kth(n, p.kk, [&](int i) {
+            auto value = [&](int i) {
                 const unsigned long long e = i + lane < n ? keys[i + lane] : 0ull;
                 return i + lane < n && ((unsigned int)(e >> 32) & MARK) == first ? __uint_as_float((unsigned int)e) : -INF;
-            });
+            };
+            const float kth = n <= 128 ? near_kth_of<2>(n, p.kk, value) : n <= 256 ? near_kth_of<4>(n, p.kk, value) : near_kth(n, p.kk, value);
             if (kth != LOWEST) {
                 const NearScale* sc = first ? p.sc : p.sc_local;
                 const float t = near_distance_from(kth, first ? -nh : -nl, first ? args : al) / sc->scale;
@@ -1239,7 +1250,8 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
             }
         }
     } else if (n > p.kk + 4) {
-        const float kth = near_kth(n, p.kk, [&](int i) { return i + lane < n ? __uint_as_float((unsigned int)keys[i + lane]) : -INF; });
+        auto value = [&](int i) { return i + lane < n ? __uint_as_float((unsigned int)keys[i + lane]) : -INF; };
+        const float kth = n <= 128 ? near_kth_of<2>(n, p.kk, value) : n <= 256 ? near_kth_of<4>(n, p.kk, value) : near_kth(n, p.kk, value);
         if (kth != LOWEST) bound = near_bound_from(kth, -nh, args);
     }
     // keep what reaches it, without the query itself; positions become row numbers
@@ -1258,17 +1270,29 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
         left += __popcll(mask);
         __builtin_amdgcn_wave_barrier();
     }
-    // exact distances, eight pairs at a time
+    // exact distances, eight pairs side by side and the rows of as many more on their way
     const int grp = lane >> 3, g = lane & 7;
     const float* xa = p.Xq + (size_t)row * p.d;
     v4f qa[4];
-    near_first_quads<VEC4>(qa, xa, p.d, g);
-    for (int i = 0; i < left; i += 8) {
-        const bool valid = i + grp < left;
-        const unsigned int cand = (unsigned int)keys[valid ? i + grp : i];
-        const float dist = near_exact<VEC4>(qa, xa, p.Xc + (size_t)cand * p.d, p.d, g);
+    near_first_quads<VEC>(qa, xa, p.d, g);
+    constexpr int AT_ONCE = 2;      // (four: 188 us where two take 169, 50 000 x 128, k = 32; one 179)
+    for (int i = 0; i < left; i += 8 * AT_ONCE) {
+        unsigned int cand[AT_ONCE];
+        v4f b[AT_ONCE][4];
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+            const int at = i + 8 * u + grp;
+            cand[u] = (unsigned int)keys[at < left ? at : i];
+            if (u == 0 || i + 8 * u < left) near_first_quads<VEC>(b[u], p.Xc + (size_t)cand[u] * p.d, p.d, g);
+        }
         __builtin_amdgcn_wave_barrier();
-        if (valid && g == 0) keys[i + grp] = ((unsigned long long)__float_as_uint(dist) << 32) | cand;
+#pragma unroll
+        for (int u = 0; u < AT_ONCE; ++u) {
+            const int at = i + 8 * u + grp;
+            if (u > 0 && i + 8 * u >= left) break;
+            const float dist = near_exact<VEC>(qa, b[u], xa, p.Xc + (size_t)cand[u] * p.d, p.d, g);
+            if (at < left && g == 0) keys[at] = ((unsigned long long)__float_as_uint(dist) << 32) | cand[u];
+        }
         __builtin_amdgcn_wave_barrier();
     }
     if (p.evaluated && lane == 0) p.evaluated[qi] = left + (p.merge ? p.evaluated[qi] : 0);
@@ -1293,6 +1317,15 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     }
     for (int j = left + lane; j < p.k; j += 64) { p.out_idx[qi * p.k + j] = -1; p.out_dist[qi * p.k + j] = INF; }
     if (p.next_bound && lane == 0 && left < p.k) p.next_bound[lq] = LOWEST;
+}
+
+static void near_select(const NearSelect& p, bool aligned, dim3 grid, hipStream_t s)
+{
+    switch (near_vec(aligned, p.d)) {
+        case 2: hipLaunchKernelGGL(near_select_kernel<2>, grid, dim3(256), 0, s, p); break;
+        case 1: hipLaunchKernelGGL(near_select_kernel<1>, grid, dim3(256), 0, s, p); break;
+        default: hipLaunchKernelGGL(near_select_kernel<0>, grid, dim3(256), 0, s, p);
+    }
 }
 
 // ---------------------------------------------------------------------------------------------- launches
@@ -1454,7 +1487,7 @@ struct NearTop {
     int32_t* todo; int32_t* todo_mark;
 };
 
-template <bool VEC4>
+template <int VEC>
 __global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
 {
     const int lane = threadIdx.x & 63;
@@ -1492,7 +1525,7 @@ __global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
     const float* xa = p.Xq + (size_t)row * p.d;
     const int grp = lane >> 3, g = lane & 7;
     v4f qa[4];
-    near_first_quads<VEC4>(qa, xa, p.d, g);
+    near_first_quads<VEC>(qa, xa, p.d, g);
     const int qcol = p.qcolour ? p.qcolour[qpos] : 0;
     unsigned long long key = ~0ull;
     float bound = LOWEST;
@@ -1506,15 +1539,24 @@ __global__ void __launch_bounds__(256) near_top_kernel(NearTop p)
         const bool second = !(pending[0] && m1[0] == mx);
         const int base = __builtin_amdgcn_readlane(second ? at[1] : at[0], who);
         if (lane == who) pending[second ? 1 : 0] = false;
+        // (the colours wait beside the rows, not before them)
+        v4f xb[2][4];
+        long long cand[2];
+        bool fine[2];
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const int j = half * 8 + grp;
             const int pos = base + 8 * (j >> 2) + (j & 3);
-            const long long cand = near_row(pos, p.c_tiles, p.c_in_order);
-            const bool fine = cand >= 0 && cand < p.nc && !(p.qcolour && p.ccolour[pos] == qcol);
-            const float dist = near_exact<VEC4>(qa, xa, p.Xc + (size_t)(fine ? cand : 0) * p.d, p.d, g);
-            const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
-            if (fine && dist < INF && k < key) key = k;
+            cand[half] = near_row(pos, p.c_tiles, p.c_in_order);
+            fine[half] = cand[half] >= 0 && cand[half] < p.nc;
+            near_first_quads<VEC>(xb[half], p.Xc + (size_t)(fine[half] ? cand[half] : 0) * p.d, p.d, g);
+            fine[half] = fine[half] && !(p.qcolour && p.ccolour[pos] == qcol);
+        }
+#pragma unroll
+        for (int half = 0; half < 2; ++half) {
+            const float dist = near_exact<VEC>(qa, xb[half], xa, p.Xc + (size_t)(fine[half] ? cand[half] : 0) * p.d, p.d, g);
+            const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand[half];
+            if (fine[half] && dist < INF && k < key) key = k;
         }
         key = wave_min<8>(key);                                      // (eight lanes have one pair)
         evaluated += 16;
@@ -1559,8 +1601,11 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
     t.counts_left = q.count; t.count_left = b.todo + 1;
     t.todo = b.todo; t.todo_mark = b.todo_mark;
     const dim3 per_query((unsigned)((nqb + 3) / 4));
-    if (vec4) hipLaunchKernelGGL((near_top_kernel<true>), per_query, dim3(256), 0, s, t);
-    else hipLaunchKernelGGL((near_top_kernel<false>), per_query, dim3(256), 0, s, t);
+    switch (near_vec(vec4, a.d)) {
+        case 2: hipLaunchKernelGGL(near_top_kernel<2>, per_query, dim3(256), 0, s, t); break;
+        case 1: hipLaunchKernelGGL(near_top_kernel<1>, per_query, dim3(256), 0, s, t); break;
+        default: hipLaunchKernelGGL(near_top_kernel<0>, per_query, dim3(256), 0, s, t);
+    }
     // those with more than one near candidate in a lane
     const int waves = wide ? plan.waves : (plan.waves > 2 ? plan.waves / 2 : 2);
     p.cnegh = c.negh;
@@ -1579,8 +1624,7 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
     sel.q_tiles = q.tiles; sel.c_tiles = c.tiles; sel.q_in_order = 1; sel.c_in_order = c.in_order;
     sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
     sel.todo = b.todo; sel.todo_mark = b.todo_mark;
-    if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
-    else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+    near_select(sel, vec4, per_query, s);
     return hipGetLastError();
 }
 
@@ -1756,8 +1800,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     sel.entries = entries; sel.counts = counts; sel.nsub = 1; sel.by_position = 1; sel.capl = plan.cap; sel.pair_lists = 1;
     sel.nq_batch = rows; sel.q0 = 0;
     auto select = [&]() -> hipError_t {
-        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
-        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
+        near_select(sel, vec4, dim3((unsigned)((sel.nq_batch + 3) / 4)), s);
         return hipGetLastError();
     };
     err = select();
@@ -1822,8 +1865,7 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
         sel.nq_batch = nqb; sel.q0 = t0 * TILE;
         auto select = [&]() -> hipError_t {
             sel.entries = p.entries; sel.counts = p.counts;
-            if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
-            else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+            near_select(sel, vec4, per_query, s);
             return hipGetLastError();
         };
         hipError_t e = hipSuccess;
@@ -2349,8 +2391,7 @@ hipError_t near_search_ordered(const NearProblem& a, const NearOrder& o, const N
         if (e != hipSuccess) return e;
         p.reach = nullptr;
         sel.entries = entries; sel.counts = counts; sel.nsub = plan.nsub; sel.capl = plan.capl;
-        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), per_query, dim3(256), 0, s, sel);
-        else hipLaunchKernelGGL((near_select_kernel<false>), per_query, dim3(256), 0, s, sel);
+        near_select(sel, vec4, per_query, s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2380,7 +2421,7 @@ __global__ void __launch_bounds__(256) near_range_clear_kernel(NearRange p)
 
 // One wavefront per query: of the 16 candidates about the nearest of which is in best_at, the nearest of another colour,
 // exactly.  An edge of the query's component, which lowers the component's threshold.
-template <bool VEC4>
+template <int VEC>
 __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
 {
     const int q = blockIdx.x * 4 + (threadIdx.x >> 6), lane = threadIdx.x & 63;
@@ -2395,7 +2436,7 @@ __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
         const int grp = lane >> 3, g = lane & 7;
         const float* xa = p.X + (size_t)row * p.d;
         v4f qa[4];
-        near_first_quads<VEC4>(qa, xa, p.d, g);
+        near_first_quads<VEC>(qa, xa, p.d, g);
 #pragma unroll
         for (int half = 0; half < 2; ++half) {
             const int j = half * 8 + grp;
@@ -2403,7 +2444,7 @@ __global__ void __launch_bounds__(256) near_edge_kernel(NearRange p)
             if (p.c_ids) cand = cand < p.n_ids ? (long long)p.c_ids[cand] : -1;
             const bool real = cand >= 0 && cand < p.n_rows;
             const bool fine = real && p.colour[real ? cand : 0] != c;
-            const float dist = near_exact<VEC4>(qa, xa, p.X + (size_t)(fine ? cand : row) * p.d, p.d, g);
+            const float dist = near_exact<VEC>(qa, xa, p.X + (size_t)(fine ? cand : row) * p.d, p.d, g);
             const unsigned long long k = ((unsigned long long)__float_as_uint(dist) << 32) | (unsigned int)cand;
             if (fine && dist < INF && k < key) key = k;
         }
@@ -2459,8 +2500,12 @@ __global__ void __launch_bounds__(256) near_split_kernel(NearRange p)
 
 static void near_edges(const NearRange& r, bool vec4, hipStream_t s)
 {
-    if (vec4) hipLaunchKernelGGL((near_edge_kernel<true>), dim3((unsigned)((r.n + 3) / 4)), dim3(256), 0, s, r);
-    else hipLaunchKernelGGL((near_edge_kernel<false>), dim3((unsigned)((r.n + 3) / 4)), dim3(256), 0, s, r);
+    const dim3 grid((unsigned)((r.n + 3) / 4));
+    switch (near_vec(vec4, r.d)) {
+        case 2: hipLaunchKernelGGL(near_edge_kernel<2>, grid, dim3(256), 0, s, r); break;
+        case 1: hipLaunchKernelGGL(near_edge_kernel<1>, grid, dim3(256), 0, s, r); break;
+        default: hipLaunchKernelGGL(near_edge_kernel<0>, grid, dim3(256), 0, s, r);
+    }
 }
 
 // Where most rows are queries, one pass over all pairs of rows serves both rows of each (pairs_best) and costs half of one over
@@ -2578,8 +2623,7 @@ hipError_t near_link(const NearLink& a, const NearCopy& q, const NearCopy& c, co
         p.nq_batch = sel.nq_batch = nqb; sel.q0 = t0 * TILE;
         e = near_launch_sweep<NEAR_NEAREST, true>(p, waves, s);
         if (e != hipSuccess) return e;
-        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
-        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((nqb + 3) / 4)), dim3(256), 0, s, sel);
+        near_select(sel, vec4, dim3((unsigned)((nqb + 3) / 4)), s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2712,8 +2756,7 @@ hipError_t near_link_ordered(const NearLink& a, const NearOrder& o, const NearBu
         }
         sel.entries = p.entries;
         sel.nq_batch = panels * left_queries; sel.q0 = (int)q0;
-        if (vec4) hipLaunchKernelGGL((near_select_kernel<true>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
-        else hipLaunchKernelGGL((near_select_kernel<false>), dim3((unsigned)((sel.nq_batch + 3) / 4)), dim3(256), 0, s, sel);
+        near_select(sel, vec4, dim3((unsigned)((sel.nq_batch + 3) / 4)), s);
         e = hipGetLastError();
         if (e != hipSuccess) return e;
     }
@@ -2755,7 +2798,7 @@ __global__ void __launch_bounds__(256) near_unpack_kernel(const unsigned long lo
     if (fine) {
         const float* a = Xq + (size_t)(q_rows ? q_rows[qi] : qi) * d;
         const float* b = Xc + (size_t)cand * d;
-        for (int c = 4 * g; c < d; c += 32) s = near_quad_sqdist(near_quad<VEC4>(a, c, d), near_quad<VEC4>(b, c, d), s);
+        for (int c = 4 * g; c < d; c += 32) s = near_quad_sqdist(near_quad<VEC4 ? 2 : 0>(a, c, d), near_quad<VEC4 ? 2 : 0>(b, c, d), s);
     }
     s = lanes_add8(s);
     if (g == 0) {

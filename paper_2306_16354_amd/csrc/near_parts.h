@@ -137,6 +137,34 @@ __device__ inline float near_kth(int n, int kk, V&& value)
     return lo;
 }
 
+// The same of at most 64 W values, kept in registers on the way.
+template <int W, typename V>
+__device__ inline float near_kth_of(int n, int kk, V&& value)
+{
+    float v[W], lo = INF, hi = -INF;
+    int have = 0;
+#pragma unroll
+    for (int j = 0; j < W; ++j) v[j] = value(64 * j);
+#pragma unroll
+    for (int j = 0; j < W; ++j) {
+        const bool fine = fabsf(v[j]) < INF;
+        have += __popcll(__ballot(fine));
+        lo = fine ? fminf(lo, v[j]) : lo;
+        hi = fine ? fmaxf(hi, v[j]) : hi;
+        v[j] = fine ? v[j] : -INF;
+    }
+    if (have < kk) return LOWEST;
+    lo = wave_min(lo); hi = wave_max(hi);
+    for (int it = 0; it < BISECT; ++it) {
+        const float mid = 0.5f * lo + 0.5f * hi;
+        int reach = 0;
+#pragma unroll
+        for (int j = 0; j < W; ++j) reach += __popcll(__ballot(v[j] >= mid));
+        if (reach >= kk) lo = mid; else hi = mid;
+    }
+    return lo;
+}
+
 // 64 consecutive quads, or words `stride` bytes apart, from `at` bytes behind `base` (both the same for all lanes) to LDS, one a lane.
 // As buffer loads: with the same loads as global_load_lds, which count as accesses through flat addresses, the compiler has every wait for
 // an LDS read wait for all of them (lgkmcnt(0)), and the fragments of the next step, read ahead of a step's multiplies, are waited for before these.
