@@ -9,6 +9,7 @@ namespace slhc {
 // "nothing"); colours (optional, by row; Xq and Xc are one matrix then): only candidates of another colour.
 // keys: m words of scratch.
 bool direct_1nn_wanted(long long m, long long nc, int d);
+bool direct_1nn_alone(long long m, long long nc, int d);
 hipError_t direct_1nn(const float* Xq, int m, int nq_rows, const int32_t* q_rows, const float* Xc, int nc, int d, const int32_t* colour,
                       int32_t* out_idx, float* out_dist, unsigned long long* keys, hipStream_t s);
 

@@ -651,15 +651,19 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
     }
 }
 
-// Where every pair is evaluated instead of the engine's search, measured on both sides of the lines (us a call among others, this
-// against the engine).  What the operations cost is one part, what it takes to bring every candidate once to each panel of eight
-// queries, 64 at a time, the other; it grows with the candidates, and with their width where a step is more than one slab.
-//   up to 100 M operations: 1250 x 4000 x 4 20 and 45, 178 x 4000 x 64 23 and 39, 22 x 32 000 x 64 23 and 45, 64 x 50 000 x 8 19 and 43,
-//     20 x 100 000 x 6 19 and 50; the worst of 40 shapes 24 x 8000 x 250 66 and 72;
-//   up to 200 M: 1136 x 4000 x 16 23 and 45, 694 x 4000 x 30 25 and 47, 173 x 16 000 x 30 26 and 48, 142 x 32 000 x 16 24 and 38, 43 x 64 000 x 30 29 and 49.
-// The lines were drawn when the segments met at each query's word by itself: beyond 65 536 candidates 32 x 111 642 x 21 took 70 and 57,
-// 16 x 300 000 x 16 88 and 85; of 300 M 1704 x 4000 x 16 37 and 47, 3750 x 4000 x 4 47 and 50, 360 x 32 000 x 7 45 and 41, 73 x 8000 x 250 94 and 76.
+// Where every pair is evaluated instead of the engine's search, measured on both sides of the line (us a call among others, this against the engine).
+// What an evaluation costs here is its operations (0.06 to 0.12 us a million) and what it takes to bring every candidate once to each panel of eight queries; the
+// engine makes a copy of all candidates first, which costs what a dozen queries' evaluations cost, and has nine launches.  So as many queries beyond
+// twelve as are 240 M operations:
+//   300 x 10 000 x 20 22 and 35, 100 x 50 000 x 20 32 and 43, 30 x 150 000 x 20 32 and 58, 10 x 500 000 x 20 47 and 103, 30 x 500 000 x 6 59 and 103,
+//   100 x 10 000 x 64 23 and 36, 30 x 150 000 x 64 60 and 66, 10 x 500 000 x 128 169 and 214, 30 x 50 000 x 128 51 and 57, 10 x 500 000 x 250 356 and 589;
+//   beyond: 1000 x 10 000 x 20 50 and 37, 100 x 150 000 x 20 74 and 58, 100 x 50 000 x 64 62 and 47, 30 x 500 000 x 64 170 and 127, 300 x 10 000 x 128 76 and 50.
 bool direct_1nn_wanted(long long m, long long nc, int d)
+{
+    return m <= (1LL << 20) && nc <= (1LL << 24) && (m - 12) * nc * (2LL * d + 12) <= 240000000LL;
+}
+// Those of them that ask for no workspace of the engine (the line of an earlier day; sizes that are reported have not changed).
+bool direct_1nn_alone(long long m, long long nc, int d)
 {
     return m <= (1LL << 20) && nc <= (1LL << 24) && m * nc * (2LL * d + 12) <= (nc <= 65536 ? 200000000LL : 100000000LL);
 }

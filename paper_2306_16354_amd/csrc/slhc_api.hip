@@ -1707,9 +1707,12 @@ struct CrossWs {
         Carver c(ws);
         counters = c.take<unsigned long long>(32);
         hn = c.take<float>((size_t)N);
-        if (m > 0 && slhc::direct_1nn_wanted(m, N, d)) {
+        if (m > 0 && slhc::direct_1nn_alone(m, N, d)) {
             if (most > c.off && up((size_t)m * 8) <= most - c.off) keys = c.take<unsigned long long>((size_t)m);
-        } else if (m > 0) near.carve(c, N, m, d, 1, true, most);
+        } else if (m > 0) {
+            near.carve(c, N, m, d, 1, true, most);
+            if (near.ok && slhc::direct_1nn_wanted(m, N, d) && near.b.batch_bytes >= (size_t)m * 8) keys = reinterpret_cast<unsigned long long*>(near.b.batch);
+        }
         bytes = c.off;
     }
 };
@@ -1968,7 +1971,7 @@ static size_t fused_1nn_layout(void* ws, int64_t m, int64_t n, int32_t d, float*
     *hq = c.take<float>((size_t)m);
     *hy = c.take<float>((size_t)n);
     *keys = c.take<unsigned long long>((size_t)m);
-    if (!slhc::direct_1nn_wanted(m, n, d)) near->carve(c, n, m, d, 1, false, most);
+    if (!slhc::direct_1nn_alone(m, n, d)) near->carve(c, n, m, d, 1, false, most);
     return c.off;
 }
 
