@@ -479,26 +479,26 @@ struct NearLane {
     // compare right before its select, with two idle cycles between, and how much of it passes under multiplies is its choice): connection rounds of 1M x 128 without a
     // row order 313 -> 285 ms, 100 000 x 100 8.4 -> 6.3 ms.  (The more words ahead, the more registers: with all eight 309 ms, and up to 48 columns one
     // workgroup less on a CU, 200 000 x 16 13.8 -> 14.8 ms; with two 13.4.)
-    template <int EARLY>
-    __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][2], int pos0, const unsigned char* col, int lhalf,
+    template <int EARLY, int CB>
+    __device__ inline __attribute__((always_inline)) void take(const NearSweep& p, v16f (&acc)[2][CB], int pos0, const unsigned char* col, int lhalf,
                                                                bool ok0 = true, bool ok1 = true, bool one_colour = false)
     {
         const bool ok[2] = {ok0, ok1};
         const int lane = threadIdx.x & 63;
         if (COLOURED && !one_colour) {
-            v4i cc[8];                                              // of four candidates each
+            v4i cc[4 * CB];                                         // of four candidates each
             auto read = [&](int i) { cc[i] = *reinterpret_cast<const v4i*>(col + ((i >> 2) * 32 + 8 * (i & 3) + 4 * lhalf) * 4); };
 #pragma unroll
             for (int i = 0; i < EARLY; ++i) read(i);
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-            for (int i = 0; i < 8; ++i) {
+            for (int i = 0; i < 4 * CB; ++i) {
                 unsigned long long same[2][4];
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
 #pragma unroll
                     for (int qb = 0; qb < 2; ++qb) same[qb][e] = __ballot(cc[i][e] == qcol[qb]);
-                if (i + EARLY < 8) read(i + EARLY);
+                if (i + EARLY < 4 * CB) read(i + EARLY);
                 __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                 for (int e = 0; e < 4; ++e)
@@ -513,14 +513,14 @@ struct NearLane {
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-                for (int r = 0; r < 16; ++r) m[qb][r] = max3(m[qb][r], acc[qb][0][r], acc[qb][1][r]);
+                for (int r = 0; r < 16; ++r) m[qb][r] = CB == 2 ? max3(m[qb][r], acc[qb][0][r], acc[qb][CB - 1][r]) : fmaxf(m[qb][r], acc[qb][0][r]);
             return;
         }
         if (MODE == NEAR_BLOCK || MODE == NEAR_TOP) {
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb)
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb) {
+                for (int cb = 0; cb < CB; ++cb) {
                     const v16f& v = acc[qb][cb];
                     float mx = max3(v[0], v[1], v[2]);
 #pragma unroll
@@ -540,7 +540,7 @@ struct NearLane {
             for (int qb = 0; qb < 2; ++qb) {
                 float mx = -INF;
 #pragma unroll
-                for (int i = 0; i < 32; i += 2) {
+                for (int i = 0; i < 16 * CB; i += 2) {
                     const float a = __uint_as_float((__float_as_uint(acc[qb][i >> 4][i & 15]) & 0xffffffe0u) | (unsigned int)i);
                     const float b = __uint_as_float((__float_as_uint(acc[qb][i >> 4][(i & 15) + 1]) & 0xffffffe0u) | (unsigned int)(i + 1));
                     mx = max3(mx, a, b);
@@ -555,18 +555,19 @@ struct NearLane {
         for (int qb = 0; qb < 2; ++qb) {
             // maxima of 5, 5, 3 and 3 values of each block (three at a time in one instruction), and of all
             constexpr int from[5] = {0, 5, 10, 13, 16};
-            float g8[8];
+            float g8[4 * CB];
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
+            for (int g = 0; g < 4 * CB; ++g) {
                 const v16f& v = acc[qb][g >> 2];
                 const int r = from[g & 3];
                 g8[g] = max3(v[r], v[r + 1], v[r + 2]);
                 if ((g & 3) < 2) g8[g] = max3(g8[g], v[r + 3], v[r + 4]);
             }
-            const float mx = fmaxf(max3(max3(g8[0], g8[1], g8[2]), max3(g8[3], g8[4], g8[5]), g8[6]), g8[7]);
+            float mx = fmaxf(max3(g8[0], g8[1], g8[2]), g8[3]);
+            if constexpr (CB == 2) mx = max3(max3(g8[4], g8[5], g8[6]), mx, g8[7]);
             if (!__any(mx >= bound[qb] && ok[qb])) continue;
 #pragma unroll
-            for (int g = 0; g < 8; ++g) {
+            for (int g = 0; g < 4 * CB; ++g) {
                 if (__any(g8[g] >= bound[qb] && ok[qb])) {
 #pragma unroll
                     for (int r = from[g & 3]; r < from[(g & 3) + 1]; ++r) {
@@ -695,12 +696,18 @@ constexpr int ITEM_TILES = 64;
 // the candidate tiles, which the workgroup's wavefronts bring into LDS together (double buffered, one barrier per
 // tile).  A lane's 16 values of a 32 x 32 block belong to one query, so bounds and counts are registers.
 // Fragment order in memory makes every load and every LDS read consecutive over the lanes.
+// Where a value costs a compare of colours or an index, and in connection rounds over lists, 32 candidates at a time: 100 to 130 registers instead of 130 to
+// 220, so that two workgroups share a CU (up to 96 columns).  Nearest rows of another colour, 10 000 in 100 000 x 64, 267 -> 237 us with as many segments as that takes, 20 000 in
+// 60 000 x 10 217 -> 199; first edges over lists 1.43 -> 1.29 ms of 100k x 64, 8.9 -> 8.7 of 1M x 128; nearest pivots 3.7 -> 3.2.  (Emission, what is left over and
+// maxima are no faster so: 168 and 176, 377 and 426 us of 100k x 64.)
 // (Emission of up to 32 columns is held to 128 registers, with which two workgroups of eight wavefronts share a CU: with one more, 300 000 x 10
 // rows without clusters in the row order took 9.9 ms of it instead of 7.1.  Likewise maxima of 80 columns to 168 registers, three workgroups of four.)
 template <int KS, int MODE, bool COLOURED, bool LISTED>
 __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 5 && MODE == NEAR_MAXIMA ? 3 : 2) near_sweep_kernel(NearSweep p)
 {
     extern __shared__ __align__(16) unsigned char near_smem[];
+    constexpr int CB = (MODE == NEAR_TOP && COLOURED && KS <= 6) || MODE == NEAR_ARG || MODE == NEAR_BLOCK ? 1 : 2;       // blocks of 32 candidates at once
+    constexpr int UNROLL = MODE == NEAR_BLOCK && LISTED ? 1 : 4;
     constexpr int BUF = KS * FRAG_STEP + 1024;           // fragments, minus half norms, colours
     const int tid = threadIdx.x, lane = tid & 63, l32 = lane & 31, lhalf = lane >> 5;
     const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -805,18 +812,18 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
             ok1 = ok1 && tile_col != mine.qcol[1];
         }
         if (!LISTED || (mine_here && __any(ok0 || ok1)))
+#pragma unroll UNROLL
+        for (int part = 0; part < 4 / CB; ++part) {
+            v16f acc[2][CB];
+            v8h cf[2][CB];
 #pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            v16f acc[2][2];
-            v8h cf[2][2];
+            for (int cb = 0; cb < CB; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(tb + (part * CB + cb) * 1024 + lane * 16);
 #pragma unroll
-            for (int cb = 0; cb < 2; ++cb) cf[0][cb] = *reinterpret_cast<const v8h*>(tb + (half * 2 + cb) * 1024 + lane * 16);
-#pragma unroll
-            for (int cb = 0; cb < 2; ++cb) {
+            for (int cb = 0; cb < CB; ++cb) {
                 v16f hv;
 #pragma unroll
                 for (int g = 0; g < 4; ++g) {
-                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + ((half * 2 + cb) * 32 + 8 * g + 4 * lhalf) * 4);
+                    const v4f t4 = *reinterpret_cast<const v4f*>(tb + KS * FRAG_STEP + ((part * CB + cb) * 32 + 8 * g + 4 * lhalf) * 4);
                     hv[4 * g] = t4[0]; hv[4 * g + 1] = t4[1]; hv[4 * g + 2] = t4[2]; hv[4 * g + 3] = t4[3];
                 }
                 acc[0][cb] = hv; acc[1][cb] = hv;
@@ -827,17 +834,17 @@ __global__ void __launch_bounds__(512, KS <= 2 && MODE == NEAR_EMIT ? 4 : KS == 
                 // from sinking to their use, which leaves the whole LDS latency between two groups of multiplies)
                 if (ks + 1 < KS) {
 #pragma unroll
-                    for (int cb = 0; cb < 2; ++cb)
-                        cf[(ks + 1) & 1][cb] = *reinterpret_cast<const v8h*>(tb + (ks + 1) * FRAG_STEP + (half * 2 + cb) * 1024 + lane * 16);
+                    for (int cb = 0; cb < CB; ++cb)
+                        cf[(ks + 1) & 1][cb] = *reinterpret_cast<const v8h*>(tb + (ks + 1) * FRAG_STEP + (part * CB + cb) * 1024 + lane * 16);
                     __builtin_amdgcn_sched_barrier(0);
                 }
 #pragma unroll
-                for (int cb = 0; cb < 2; ++cb)
+                for (int cb = 0; cb < CB; ++cb)
 #pragma unroll
                     for (int qb = 0; qb < 2; ++qb)
                         acc[qb][cb] = __builtin_amdgcn_mfma_f32_32x32x16_f16(cf[ks & 1][cb], qf[qb][ks], acc[qb][cb], 0, 0, 0);
             }
-            mine.template take<KS <= 3 ? 2 : 4>(p, acc, pos0 + half * 64, tb + KS * FRAG_STEP + 512 + half * 256, lhalf, ok0, ok1, tile_col >= 0);
+            mine.template take<KS <= 3 ? 2 : 4>(p, acc, pos0 + part * 32 * CB, tb + KS * FRAG_STEP + 512 + part * 128 * CB, lhalf, ok0, ok1, tile_col >= 0);
         }
         if (MODE == NEAR_MAXIMA && (i + 1 == part_end || i + 1 == ntiles)) {
             mine.flush(p, seg * p.parts + part, lhalf, live && mine_here);
@@ -1374,7 +1381,7 @@ static void near_sample(NearPlan& p, int stride, int CT, int kk, bool wide, int 
     p.max_sets = sets * p.max_parts;
 }
 
-static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batch_bytes)
+static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batch_bytes, bool coloured = false)
 {
     NearPlan p{};
     const int cus = near_cus();
@@ -1387,6 +1394,7 @@ static NearPlan near_plan(long long nq, long long nc, int d, int kk, size_t batc
     auto segs = [&](int n, int most) {
         const int panels = (QT + p.panel_tiles - 1) / p.panel_tiles;
         int s = (p.waves == 8 ? cus : 2 * cus) / panels;
+        if (coloured && near_steps(d) <= 6 && p.waves == 8 && 2 * cus / panels <= 32) s = 2 * cus / panels;       // (two to a CU, see near_sweep_kernel)
         if (s > most) s = most;
         if (s > n) s = n;
         return s < 1 ? 1 : s;
@@ -1446,7 +1454,7 @@ static hipError_t near_launch_sweep(const NearSweep& p, int waves, hipStream_t s
     const int per_panel = wide ? 2 : waves / 2;
     const int panels = (p.q_tile1 - p.q_tile0 + per_panel - 1) / per_panel;
     // (queries counted on the device: as many workgroups as any count can use)
-    const dim3 grid((unsigned)(LISTED && (MODE == NEAR_BLOCK || MODE == NEAR_NEAREST) ? (waves == 8 ? 1 : 2) * near_cus() : p.n_dev ? (panels > p.slots ? panels : p.slots) : panels * p.nseg)), block((unsigned)(64 * waves));
+    const dim3 grid((unsigned)(LISTED && (MODE == NEAR_BLOCK || MODE == NEAR_NEAREST) ? (waves == 8 ? 2 : 4) * near_cus() : p.n_dev ? (panels > p.slots ? panels : p.slots) : panels * p.nseg)), block((unsigned)(64 * waves));
     const size_t lds = wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + 1024);
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -1832,7 +1840,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
 hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& c, const NearBuffers& b, hipStream_t s)
 {
     const int kk = a.k + (a.exclude_self ? 1 : 0);
-    const NearPlan plan = near_plan(a.nq, a.nc, a.d, kk, b.batch_bytes);
+    const NearPlan plan = near_plan(a.nq, a.nc, a.d, kk, b.batch_bytes, a.coloured != 0);
     if (plan.batch_tiles < 1 || (a.nq + 127) / 128 > b.todo_panels || (a.coloured && (kk != 1 || !q.colour || !c.colour)) ||
         (kk == 1 && (!q.left || !q.count || !c.negh_best)))
         return hipErrorInvalidValue;
