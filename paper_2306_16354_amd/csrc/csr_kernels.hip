@@ -5,9 +5,9 @@
 // and the roots of components that had one, both kept as lists.  Components only grow, so a vertex without such an edge never
 // has one again; its colour is complemented, which tells its neighbours, all in its own component, without being kept up to date.
 // (Walking up from stale colours instead: two random reads per entry where one does, 610 us of scans.)
-// What bounds it: random 4-byte reads in the first four rounds (380 us), then the chain of dependent reads and the end of every launch
+// What bounds it: random 4-byte reads in the first four rounds (330 us), then the chain of dependent reads and the end of every launch
 // (30 us a round, whatever is left of the graph).  Road-like graph of 1 048 576 vertices and 2.6 million entries: rounds over all
-// vertices 750 us, over the lists 580.
+// vertices 750 us, over the lists 580, over all vertices and an edge to a word in the first two 530.
 #include <hip/hip_runtime.h>
 #include <cstring>
 #include <rocprim/rocprim.hpp>
@@ -74,9 +74,9 @@ __device__ inline unsigned long long row_part(const CsrForest& f, int v, int c, 
     return best;
 }
 
-// The edge of v's row out of component c (v < 0: none).  Every lane of the wavefront must call it.
+// The edge of v's row out of component c (v < 0: none), as row_part has it.  Every lane of the wavefront must call it.
 template <bool FIRST>
-__device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits)
+__device__ inline unsigned long long row_edge(const CsrForest& f, int v, int c)
 {
     unsigned int at = 0, end = 0;
     if (v >= 0) {
@@ -113,66 +113,69 @@ __device__ inline int row_edge(const CsrForest& f, int v, int c, uint32_t* wbits
         key = wave_min(key);
         if (lane == owner) best = key;
     }
-    *wbits = (uint32_t)(best >> 32);
-    return best == NO_EDGE ? -1 : (int)(best & 0xffffffffull);
+    return best;
+}
+__device__ inline uint32_t edge_weight(unsigned long long e) { return (uint32_t)(e >> 32); }
+__device__ inline int edge_end(unsigned long long e) { return e == NO_EDGE ? -1 : (int)(e & 0xffffffffull); }
+// the ends of v's edge to u in their order
+__device__ inline unsigned long long edge_ends(int v, int u)
+{
+    return ((unsigned long long)(unsigned int)(v < u ? v : u) << 32) | (unsigned int)(v < u ? u : v);
 }
 
-// Round 0: every vertex is a component.
-template <int THREADS>
+// Beyond FEW vertices the lists of the first rounds would hold nearly all of them: rounds 0 to LAST_ALL make none, and what would read them goes over
+// all vertices, of which those without an edge have a complemented colour.  The words that count a list's entries say V.  (Road-like graph of 1M
+// vertices: round 0's lists 20 us with the vertices' edges, 10 without; with LAST_ALL of 1 to 4 the calls take the same, within 0.5 %.)
+constexpr int LAST_ALL = 1;
+__host__ __device__ inline bool list_is_all(const CsrForest& f, int round) { return f.V > FEW && round <= LAST_ALL; }
+
+// Round 0: every vertex is a component, and its edge the component's.
+template <int THREADS, bool ALL>
 __global__ void __launch_bounds__(THREADS) k_csr_first(CsrForest f)
 {
-    for (long long base = (long long)blockIdx.x * THREADS; base < f.V; base += (long long)gridDim.x * THREADS) {
-        const long long v = base + threadIdx.x;
-        uint32_t w;
-        const int u = row_edge<true>(f, v < f.V ? (int)v : -1, (int)v, &w);
-        if (v < f.V) {
-            const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
-            f.colour[v] = (int)v;
-            f.hook[v] = (int)v;
-            f.cand_u[v] = u;
-            f.cand_w[v] = __uint_as_float(w);
-            f.best_w[0][v] = w;
-            f.best_w[1][v] = INF_BITS;
-            f.best_e[0][v] = u < 0 ? ~0ull : ((unsigned long long)lo << 32) | hi;
-            f.best_e[1][v] = ~0ull;
-        }
-        const int at = block_append<THREADS>(u >= 0, f.words + CSR_ACTIVE + 1);
-        if (u >= 0) f.active[1][at] = (int)v;
-        __syncthreads();
+    const int v = blockIdx.x * THREADS + threadIdx.x;
+    const unsigned long long e = row_edge<true>(f, v < f.V ? v : -1, v);
+    if (v < f.V) {
+        f.colour[v] = v;
+        f.hook[v] = v;
+        f.cand[v] = e;
     }
+    if (ALL) return;
+    const int at = block_append<THREADS>(v < f.V && edge_end(e) >= 0, f.words + CSR_ACTIVE + 1);
+    if (at >= 0) f.active[1][at] = v;
 }
 
 // Round r: the active vertices' edges, and the weight of every component's lightest.  Also tells the host how the round before
 // ended, in words that carry `seq` each (so no fence has to stand between them and one number for all).
-template <int THREADS>
+template <int THREADS, bool ALL_IN, bool ALL_OUT>
 __global__ void __launch_bounds__(THREADS) k_csr_scan(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
 {
     if (blockIdx.x == 0 && threadIdx.x < CSR_TOLD) {
-        const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR};
+        const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR, CSR_TIES};
         __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | (unsigned int)f.words[at[threadIdx.x]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;       // (one tree: nothing is left to find)
-    const int n = f.words[CSR_ACTIVE + round % 3];
+    const int n = ALL_IN ? f.V : f.words[CSR_ACTIVE + round % 3];
     const int32_t* from = f.active[round & 1];
     int32_t* to = f.active[(round + 1) & 1];
     uint32_t* best_w = f.best_w[round & 1];
     for (long long base = (long long)blockIdx.x * THREADS; base < n; base += (long long)gridDim.x * THREADS) {
         const long long i = base + threadIdx.x;
         int v = -1, c = 0;
-        uint32_t w;
         if (i < n) {
-            v = from[i];
+            v = ALL_IN ? (int)i : from[i];
             c = f.colour[v];
-            if (!in_range(c, f.V)) { report(f, 11); v = -1; }
+            if (ALL_IN && c < 0 && in_range(~c, f.V)) v = -1;     // (without an edge since an earlier round)
+            else if (!in_range(c, f.V)) { report(f, 11); v = -1; }
         }
-        const int u = row_edge<false>(f, v, c, &w);
-        if (u >= 0) {
-            f.cand_u[v] = u;
-            f.cand_w[v] = __uint_as_float(w);
-        } else if (v >= 0) f.colour[v] = ~c;
-        wave_min_into(best_w, c, w, u >= 0);
-        const int at = block_append<THREADS>(u >= 0, f.words + CSR_ACTIVE + (round + 1) % 3);
-        if (u >= 0) to[at] = v;
+        const unsigned long long e = row_edge<false>(f, v, c);
+        const bool some = edge_end(e) >= 0;
+        if (some) f.cand[v] = e;
+        else if (v >= 0) f.colour[v] = ~c;
+        wave_min_into(best_w, c, edge_weight(e), some);
+        if (ALL_OUT) continue;
+        const int at = block_append<THREADS>(some, f.words + CSR_ACTIVE + (round + 1) % 3);
+        if (some) to[at] = v;
         __syncthreads();
     }
 }
@@ -182,16 +185,17 @@ __global__ void __launch_bounds__(TB) k_csr_select(CsrForest f, int round)
 {
     if (halted(f)) return;
     if (blockIdx.x == 0 && threadIdx.x == 0) {
-        f.words[CSR_ACTIVE + (round + 2) % 3] = 0;
+        f.words[CSR_ACTIVE + (round + 2) % 3] = list_is_all(f, round + 1) ? f.V : 0;
         f.words[CSR_ROOTS + (round + 2) % 3] = 0;
     }
     const int n = f.words[CSR_ACTIVE + (round + 1) % 3];
     const int32_t* list = f.active[(round + 1) & 1];
+    const bool all = list_is_all(f, round);
     for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n; i += (long long)gridDim.x * TB) {
-        const int v = list[i], u = f.cand_u[v], c = f.colour[v];
-        if (__float_as_uint(f.cand_w[v]) != f.best_w[round & 1][c]) continue;
-        const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
-        min_into(&f.best_e[round & 1][c], ((unsigned long long)lo << 32) | hi);
+        const int v = all ? (int)i : list[i], c = f.colour[v];
+        if (all && c < 0) continue;
+        const unsigned long long e = f.cand[v];
+        if (edge_weight(e) == f.best_w[round & 1][c]) min_into(&f.best_e[round & 1][c], edge_ends(v, edge_end(e)));
     }
 }
 
@@ -202,23 +206,60 @@ __device__ inline bool one_sided(uint32_t other_w, unsigned long long other_e, u
     return other_w > w || (other_w == w && other_e > e);
 }
 
+// Additions to two lists at once: `a` and `b` become the places of those of a thread's items that are on.  Every thread of the workgroup of
+// WIDE must call it.
+template <int ITEMS>
+__device__ inline void append_two(int (&a)[ITEMS], int (&b)[ITEMS], int32_t* count_a, int32_t* count_b)
+{
+    constexpr int WAVES = WIDE / 64;
+    __shared__ int count[2][WAVES], first[2];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    int na = 0, nb = 0;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const unsigned long long ma = __ballot(a[k] != 0), mb = __ballot(b[k] != 0);
+        a[k] = a[k] ? na + __popcll(ma & ((1ull << lane) - 1)) : -1;
+        b[k] = b[k] ? nb + __popcll(mb & ((1ull << lane) - 1)) : -1;
+        na += __popcll(ma);
+        nb += __popcll(mb);
+    }
+    if (lane == 0) { count[0][wave] = na; count[1][wave] = nb; }
+    __syncthreads();
+    int before_a = 0, before_b = 0, total[2] = {0, 0};
+#pragma unroll
+    for (int w = 0; w < WAVES; ++w) {
+        before_a += w < wave ? count[0][w] : 0;
+        before_b += w < wave ? count[1][w] : 0;
+        total[0] += count[0][w];
+        total[1] += count[1][w];
+    }
+    if (lane == 0 && wave < 2) first[wave] = total[wave] > 0 ? atomicAdd(wave == 0 ? count_a : count_b, total[wave]) : 0;
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        a[k] += a[k] >= 0 ? first[0] + before_a : 0;
+        b[k] += b[k] >= 0 ? first[1] + before_b : 0;
+    }
+    __syncthreads();
+}
+
 // One thread per root: append the component's edge (once per undirected edge) and hook it to the component at the other end.  Two
 // that chose the same edge keep the smaller root; roots that stay get cleared minima for the next round.
 __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
 {
     if (halted(f)) return;
-    const int n = round == 0 ? f.V : f.words[CSR_ROOTS + round % 3];
+    const int n = f.words[CSR_ROOTS + round % 3];
     const int32_t* from = f.roots[round & 1];
     int32_t* to = f.roots[(round + 1) & 1];
     const uint32_t* best_w = f.best_w[round & 1];
     const unsigned long long* best_e = f.best_e[round & 1];
     for (long long base = (long long)blockIdx.x * WIDE; base < n; base += (long long)gridDim.x * WIDE) {
         const long long i = base + threadIdx.x;
-        bool adds = false, stays = false;
+        int adds[1] = {0}, stays[1] = {0};
         int c = 0, lo = 0, hi = 0;
         uint32_t w = INF_BITS;
         if (i < n) {
-            c = round == 0 ? (int)i : from[i];
+            c = from[i];
             w = best_w[c];
             if (w != INF_BITS) {                                   // (else: a finished tree)
                 const unsigned long long e = best_e[c];
@@ -236,19 +277,55 @@ __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
                     const bool mutual = other_w == w && other_e == e;
                     if (one_sided(other_w, other_e, w, e)) report(f, 15);
                     else {
-                        adds = !mutual || c < other;
-                        stays = mutual && c < other;
-                        if (!stays) f.hook[c] = other;
+                        adds[0] = !mutual || c < other;
+                        stays[0] = mutual && c < other;
+                        if (!stays[0]) f.hook[c] = other;
                     }
                 }
             }
         }
-        const int slot = block_append<WIDE>(adds, f.words + CSR_EDGES);
-        if (adds && slot < f.V - 1) { f.e_lo[slot] = lo; f.e_hi[slot] = hi; f.e_w[slot] = __uint_as_float(w); }
-        __syncthreads();
-        const int at = block_append<WIDE>(stays, f.words + CSR_ROOTS + (round + 1) % 3);
-        if (stays) { to[at] = c; f.best_w[(round + 1) & 1][c] = INF_BITS; f.best_e[(round + 1) & 1][c] = ~0ull; }
-        __syncthreads();
+        append_two(adds, stays, f.words + CSR_EDGES, f.words + CSR_ROOTS + (round + 1) % 3);
+        if (adds[0] >= 0 && adds[0] < f.V - 1) { f.e_lo[adds[0]] = lo; f.e_hi[adds[0]] = hi; f.e_w[adds[0]] = __uint_as_float(w); }
+        if (stays[0] >= 0) { to[stays[0]] = c; f.best_w[(round + 1) & 1][c] = INF_BITS; f.best_e[(round + 1) & 1][c] = ~0ull; }
+    }
+}
+
+// ... in round 0, where every vertex is a root and what it needs of the other one is in one word.  ITEMS vertices a thread, because additions
+// to one word come one after another, about 10 ns each.  1M vertices: 47 us with weights, ends and colours in words of their own and two additions
+// per 1024 vertices, 32 with the one word, 21 with two per 4096.
+template <int ITEMS>
+__global__ void __launch_bounds__(WIDE) k_csr_commit_first(CsrForest f)
+{
+    if (halted(f)) return;
+    const long long base = (long long)blockIdx.x * (WIDE * ITEMS) + threadIdx.x;
+    unsigned long long mine[ITEMS], theirs[ITEMS];
+    int adds[ITEMS], stays[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) mine[k] = base + k * WIDE < f.V ? f.cand[base + k * WIDE] : NO_EDGE;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) theirs[k] = edge_end(mine[k]) >= 0 ? f.cand[edge_end(mine[k])] : NO_EDGE;
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int c = (int)(base + k * WIDE), other = edge_end(mine[k]);
+        const bool mutual = edge_weight(theirs[k]) == edge_weight(mine[k]) && edge_end(theirs[k]) == c;
+        adds[k] = stays[k] = 0;
+        if (other < 0) continue;
+        if (one_sided(edge_weight(theirs[k]), edge_ends(other, edge_end(theirs[k])), edge_weight(mine[k]), edge_ends(c, other))) report(f, 15);
+        else {
+            adds[k] = !mutual || c < other;
+            stays[k] = mutual && c < other;
+            if (!stays[k]) f.hook[c] = other;
+        }
+    }
+    append_two(adds, stays, f.words + CSR_EDGES, f.words + CSR_ROOTS + 1);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+        const int c = (int)(base + k * WIDE);
+        if (adds[k] >= 0 && adds[k] < f.V - 1) {
+            const unsigned long long e = edge_ends(c, edge_end(mine[k]));
+            f.e_lo[adds[k]] = (int)(e >> 32); f.e_hi[adds[k]] = (int)(e & 0xffffffffull); f.e_w[adds[k]] = __uint_as_float(edge_weight(mine[k]));
+        }
+        if (stays[k] >= 0) { f.roots[1][stays[k]] = c; f.best_w[1][c] = INF_BITS; f.best_e[1][c] = ~0ull; }
     }
 }
 
@@ -276,8 +353,12 @@ __global__ void __launch_bounds__(TB) k_csr_follow(CsrForest f, int round, int a
     if (f.words[CSR_ERROR] != 0 || (!again && f.words[CSR_CHAINS] != 0)) return;
     const int n = f.words[CSR_ACTIVE + (round + 1) % 3];
     const int32_t* list = f.active[(round + 1) & 1];
-    for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n; i += (long long)gridDim.x * TB)
-        if (!follow(f, list[i], again != 0)) atomicMax(f.words + CSR_CHAINS, round + 1);
+    const bool all = list_is_all(f, round);
+    for (long long i = (long long)blockIdx.x * TB + threadIdx.x; i < n; i += (long long)gridDim.x * TB) {
+        const int v = all ? (int)i : list[i];
+        if (all && f.colour[v] < 0) continue;
+        if (!follow(f, v, again != 0)) atomicMax(f.words + CSR_CHAINS, round + 1);
+    }
 }
 
 // All rounds from `round` on in one workgroup, once few vertices are active: a round's four launches take 30 us whatever they do.
@@ -303,27 +384,25 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
         for (int i0 = 0; i0 < n; i0 += WIDE) {
             const int i = i0 + tid;
             int v = -1, c = 0;
-            uint32_t w;
             if (i < n) {
                 v = from[i];
                 c = f.colour[v];
                 if (!in_range(c, f.V)) { report(f, 11); v = -1; }
             }
-            const int u = row_edge<false>(f, v, c, &w);
-            if (u >= 0) {
-                f.cand_u[v] = u;
-                f.cand_w[v] = __uint_as_float(w);
+            const unsigned long long e = row_edge<false>(f, v, c);
+            const bool some = edge_end(e) >= 0;
+            if (some) {
+                f.cand[v] = e;
                 to[atomicAdd(&s_active, 1)] = v;
             } else if (v >= 0) f.colour[v] = ~c;
-            wave_min_into(best_w, c, w, u >= 0);
+            wave_min_into(best_w, c, edge_weight(e), some);
         }
         __syncthreads();
         n = s_active;
         for (int i = tid; i < n; i += WIDE) {
-            const int v = to[i], u = f.cand_u[v], c = f.colour[v];
-            if (__float_as_uint(f.cand_w[v]) != __hip_atomic_load(best_w + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) continue;
-            const unsigned int lo = (unsigned int)(v < u ? v : u), hi = (unsigned int)(v < u ? u : v);
-            min_into(&best_e[c], ((unsigned long long)lo << 32) | hi);
+            const int v = to[i], c = f.colour[v];
+            const unsigned long long e = f.cand[v];
+            if (edge_weight(e) == __hip_atomic_load(best_w + c, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) min_into(&best_e[c], edge_ends(v, edge_end(e)));
         }
         __syncthreads();
         for (int i = tid; i < nr; i += WIDE) {
@@ -369,7 +448,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
     }
     if (tid == 0) {
         f.words[CSR_EDGES] = s_edges;
-        const int said[CSR_TOLD] = {rounds, s_edges, f.words[CSR_CHAINS], f.words[CSR_ERROR]};
+        const int said[CSR_TOLD] = {rounds, s_edges, f.words[CSR_CHAINS], f.words[CSR_ERROR], f.words[CSR_TIES]};
         for (int i = 0; i < CSR_TOLD; ++i)
             __hip_atomic_store(host + i, ((unsigned long long)seq << 32) | (unsigned int)said[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -422,17 +501,40 @@ __global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* _
     if (!closed) report(f, 16);
 }
 
-__global__ void __launch_bounds__(64) k_csr_words(int32_t* __restrict__ words)
+// Lowest bits of the weights that the sort of that many edges leaves to runs: three passes of 8 bits for the other 24, of which there are 65 536
+// values between powers of two.  Beyond 2^20 edges the runs would grow longer, and the fourth pass is made.
+static inline int low_bits(int E) { return E <= (1 << 20) ? 7 : 0; }
+// The words of a call; and whether many edges have the same weight in the bits that are sorted by, by a sample of the entries: each looks for its
+// weight in a table of those before it.  Many: more pairs than runs of 16 edges would give.
+constexpr int SAMPLE = 1024, SAMPLE_TABLE = 4096;
+__global__ void __launch_bounds__(SAMPLE) k_csr_words(CsrForest f, int low)
 {
-    words[threadIdx.x] = 0;
+    __shared__ uint32_t table[SAMPLE_TABLE];
+    const int tid = threadIdx.x;
+    for (int i = tid; i < SAMPLE_TABLE; i += SAMPLE) table[i] = 0xffffffffu;
+    __syncthreads();
+    bool tie = false;
+    if (f.E >= SAMPLE) {
+        const uint32_t w = (__float_as_uint(f.weights[(long long)f.E * tid / SAMPLE]) & 0x7fffffffu) >> low;
+        uint32_t at = (w * 0x9e3779b1u) >> 20;
+        for (int i = 0; i < SAMPLE_TABLE; ++i, at = (at + 1) & (SAMPLE_TABLE - 1)) {
+            const uint32_t was = atomicCAS(&table[at], 0xffffffffu, w);
+            tie = was == w;
+            if (tie || was == 0xffffffffu) break;
+        }
+    }
+    const int ties = __syncthreads_count(tie), most = 4 + (int)((16ll * SAMPLE * SAMPLE / 2) / f.V);
+    const bool all = (tid == CSR_ACTIVE + 1 && list_is_all(f, 0)) || (tid == CSR_ACTIVE + 2 && list_is_all(f, 1));
+    if (tid < 64) f.words[tid] = all ? f.V : tid == CSR_TIES && ties > most ? 1 : 0;
 }
 
 hipError_t csr_start(const CsrForest& f, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_csr_words, dim3(1), dim3(64), 0, s, f.words);
-    if (f.V > FEW) hipLaunchKernelGGL((k_csr_first<WIDE>), dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f);
-    else hipLaunchKernelGGL((k_csr_first<TB>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
-    hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(f.V)), dim3(WIDE), 0, s, f, 0);
+    hipLaunchKernelGGL(k_csr_words, dim3(1), dim3(SAMPLE), 0, s, f, low_bits(f.V));
+    if (list_is_all(f, 0)) hipLaunchKernelGGL((k_csr_first<TB, true>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
+    else hipLaunchKernelGGL((k_csr_first<TB, false>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
+    if (f.V > FEW) hipLaunchKernelGGL(k_csr_commit_first<4>, dim3(blocks_for(f.V, 4 * WIDE)), dim3(WIDE), 0, s, f);
+    else hipLaunchKernelGGL(k_csr_commit_first<1>, dim3(blocks_for(f.V, WIDE)), dim3(WIDE), 0, s, f);
     hipLaunchKernelGGL(k_csr_follow, dim3(blocks_for(f.V)), dim3(TB), 0, s, f, 0, 0);
     return hipGetLastError();
 }
@@ -440,8 +542,10 @@ hipError_t csr_start(const CsrForest& f, hipStream_t s)
 hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s)
 {
     const dim3 per_vertex(blocks_for(vertices < 1 ? 1 : vertices));
-    if (vertices > FEW) hipLaunchKernelGGL((k_csr_scan<WIDE>), dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
-    else hipLaunchKernelGGL((k_csr_scan<TB>), per_vertex, dim3(TB), 0, s, f, round, host, seq);
+    if (list_is_all(f, round)) hipLaunchKernelGGL((k_csr_scan<TB, true, true>), per_vertex, dim3(TB), 0, s, f, round, host, seq);
+    else if (list_is_all(f, round - 1)) hipLaunchKernelGGL((k_csr_scan<WIDE, true, false>), dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
+    else if (vertices > FEW) hipLaunchKernelGGL((k_csr_scan<WIDE, false, false>), dim3(append_blocks(vertices)), dim3(WIDE), 0, s, f, round, host, seq);
+    else hipLaunchKernelGGL((k_csr_scan<TB, false, false>), per_vertex, dim3(TB), 0, s, f, round, host, seq);
     hipLaunchKernelGGL(k_csr_select, per_vertex, dim3(TB), 0, s, f, round);
     hipLaunchKernelGGL(k_csr_commit, dim3(append_blocks(roots)), dim3(WIDE), 0, s, f, round);
     hipLaunchKernelGGL(k_csr_follow, per_vertex, dim3(TB), 0, s, f, round, 0);
@@ -473,7 +577,50 @@ hipError_t csr_closed(const CsrForest& f, const int32_t* colours, hipStream_t s)
 }
 
 // ------------------------------------------------------------------------------- sort
-// By (weight, smaller end, larger end).  The smaller ends are counted and the edges placed by them, which takes a few passes of
+// By (weight, smaller end, larger end).  Where few edges have nearly the same weight: one sort of weights with the edges' numbers, by all but the
+// lowest bits while the runs that leaves are short, and every edge counts those of its run that come before it.  A run of more than RUN_MOST
+// raises a flag, and another way is taken.  1M edges: 220 us by the smaller ends first (below), 165 by all bits, 140 so, of which the three passes
+// take 83 and the runs 33 (random words of the edges' ends; 41 with the neighbours' weights read from memory).
+constexpr int RUN_MOST = 64;
+__global__ void __launch_bounds__(TB) k_csr_in_runs(const uint32_t* __restrict__ wbits, const uint32_t* __restrict__ number, const int32_t* __restrict__ lo,
+                                                   const int32_t* __restrict__ hi, int E, int low, int32_t* __restrict__ out_lo, int32_t* __restrict__ out_hi,
+                                                   float* __restrict__ out_w, int32_t* __restrict__ flag)
+{
+    __shared__ uint32_t near[RUN_MOST + TB + RUN_MOST];        // the workgroup's weights and those a run can reach
+    const int first = blockIdx.x * TB, i = first + threadIdx.x;
+    for (int j = threadIdx.x; j < RUN_MOST + TB + RUN_MOST; j += TB) {
+        const int at = first - RUN_MOST + j;
+        near[j] = at >= 0 && at < E ? wbits[at] : 0u;
+    }
+    const uint32_t e = i < E ? number[i] : 0u;
+    const int a = lo[e], b = hi[e];
+    __syncthreads();
+    if (i >= E) return;
+    const uint32_t* mine = near + RUN_MOST + threadIdx.x;
+    const uint32_t w = *mine;
+    auto before = [&](int j, uint32_t o) -> int {
+        if (o != w) return o < w ? 1 : 0;
+        const uint32_t n = number[j];
+        const int oa = lo[n];
+        return oa < a || (oa == a && hi[n] < b) ? 1 : 0;
+    };
+    int from = i, to = i + 1, at = 0;
+    for (; from > 0 && i - from < RUN_MOST; --from) {
+        const uint32_t o = mine[from - 1 - i];
+        if ((o ^ w) >> low) break;
+        at += before(from - 1, o);
+    }
+    for (; to < E && to - i <= RUN_MOST; ++to) {
+        const uint32_t o = mine[to - i];
+        if ((o ^ w) >> low) break;
+        at += before(to, o);
+    }
+    if (to - from > RUN_MOST) { *flag = 1; return; }
+    at += from;
+    out_lo[at] = a; out_hi[at] = b; out_w[at] = __uint_as_float(w);
+}
+
+// Where many do: the smaller ends are counted and the edges placed by them, which takes a few passes of
 // random words where a radix sort by both ends takes five over all of them; each vertex then orders its few edges by the other
 // end, and one stable sort by weight follows.  A vertex with more than LO_MOST edges to larger ones raises a flag while they are
 // counted; nothing is placed then, and the caller, whom the placing tells, takes edge_sort instead.  1M edges: 240 us with two radix
@@ -547,6 +694,26 @@ bool csr_sort_fits(int V, int E, size_t temp_bytes)
     (void)rocprim::exclusive_scan(nullptr, a, i, i, 0, (size_t)V + 1, rocprim::plus<int32_t>(), (hipStream_t)0);
     (void)rocprim::radix_sort_pairs<radix_passes>(nullptr, b, k32, k32, k64, k64, (size_t)E, 0, 32, (hipStream_t)0);
     return a <= temp_bytes && b <= temp_bytes;
+}
+// (bits of weights that are not negative)
+static hipError_t sort_weights_numbers(void* temp, size_t& bytes, const uint32_t* w, uint32_t* w_out, uint32_t* number, int E, hipStream_t s)
+{
+    return rocprim::radix_sort_pairs<radix_passes>(temp, bytes, w, w_out, rocprim::make_counting_iterator<uint32_t>(0u), number, (size_t)E, low_bits(E), 31, s);
+}
+bool csr_sort_in_runs_fits(int E, size_t temp_bytes)
+{
+    size_t a = 0;
+    (void)sort_weights_numbers(nullptr, a, nullptr, nullptr, nullptr, E, (hipStream_t)0);
+    return a <= temp_bytes;
+}
+hipError_t csr_sort_in_runs(const int32_t* lo, const int32_t* hi, const float* w, int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi,
+                            float* out_w, int32_t* flag, hipStream_t s)
+{
+    size_t tb = t.temp_bytes;
+    const hipError_t e = sort_weights_numbers(t.temp, tb, reinterpret_cast<const uint32_t*>(w), t.wbits_b, t.number, E, s);
+    if (e != hipSuccess) return e;
+    hipLaunchKernelGGL(k_csr_in_runs, dim3(blocks_for(E)), dim3(TB), 0, s, t.wbits_b, t.number, lo, hi, E, low_bits(E), out_lo, out_hi, out_w, flag);
+    return hipGetLastError();
 }
 hipError_t csr_sort_ends(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* flag, unsigned long long* host, uint32_t seq,
                          hipStream_t s)

@@ -1779,9 +1779,9 @@ int slhc_cross_1nn(const float* X, int64_t N, int32_t d, const int32_t* colour, 
 }
 
 struct CsrWs {
-    int32_t *colour, *ptr, *ext_idx, *cand_u, *hook, *counters, *e_lo, *e_hi;
-    float *ext_dist, *ext_low, *cand_w, *e_w;
-    uint32_t *best_w, *vals_a, *vals_b;
+    int32_t *colour, *ptr, *ext_idx, *rank, *hook, *counters, *e_lo, *e_hi;
+    float *ext_dist, *ext_low, *e_w;
+    uint32_t *best_w, *vals_a, *vals_b, *number;
     unsigned long long *best_e, *keys_a, *keys_b;
     void* sort_temp; size_t sort_temp_bytes;
     size_t bytes;
@@ -1790,9 +1790,9 @@ struct CsrWs {
         Carver c(ws);
         const size_t n = (size_t)V;
         colour = c.take<int32_t>(n); ptr = c.take<int32_t>(n); ext_idx = c.take<int32_t>(n);       // (ptr and ext_idx serve as one array in the end)
-        cand_u = c.take<int32_t>(n); hook = c.take<int32_t>(n); counters = c.take<int32_t>(64);
+        rank = c.take<int32_t>(n); hook = c.take<int32_t>(n); counters = c.take<int32_t>(64);
         e_lo = c.take<int32_t>(n); e_hi = c.take<int32_t>(n);
-        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); cand_w = c.take<float>(n); e_w = c.take<float>(n);
+        ext_dist = c.take<float>(n); ext_low = c.take<float>(n); number = c.take<uint32_t>(n); e_w = c.take<float>(n);
         best_w = c.take<uint32_t>(n);
         vals_a = c.take<uint32_t>(n); vals_b = c.take<uint32_t>(n);
         best_e = c.take<unsigned long long>(n); keys_a = c.take<unsigned long long>(n); keys_b = c.take<unsigned long long>(n);
@@ -1836,7 +1836,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         hipStream_t s = static_cast<hipStream_t>(stream);
         slhc::CsrForest f{};
         f.offsets = offsets; f.indices = indices; f.weights = weights; f.V = (int)V; f.E = (int)E;
-        f.colour = ws.colour; f.hook = ws.hook; f.cand_u = ws.cand_u; f.cand_w = ws.cand_w;
+        f.colour = ws.colour; f.hook = ws.hook; f.cand = ws.keys_b;
         f.best_w[0] = ws.best_w; f.best_w[1] = ws.vals_a; f.best_e[0] = ws.best_e; f.best_e[1] = ws.keys_a;
         f.active[0] = ws.ptr; f.active[1] = ws.ext_idx;
         f.roots[0] = reinterpret_cast<int32_t*>(ws.ext_dist); f.roots[1] = reinterpret_cast<int32_t*>(ws.ext_low);
@@ -1937,21 +1937,30 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         // (the arrays of the rounds are free by now)
         slhc::CsrSortScratch t{};
         t.count = reinterpret_cast<int32_t*>(ws.best_e); t.offset = reinterpret_cast<int32_t*>(ws.keys_a);
-        t.rank = ws.cand_u; t.wbits_a = ws.best_w; t.wbits_b = ws.vals_a; t.ends_a = ws.keys_b;
+        t.rank = ws.rank; t.number = ws.number; t.wbits_a = ws.best_w; t.wbits_b = ws.vals_a; t.ends_a = ws.keys_b;
         t.ends_b = reinterpret_cast<unsigned long long*>(ws.ptr);          // (and ext_idx behind it)
         t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
-        const bool by_ends = edges > 0 && V > 65536 && slhc::csr_sort_fits((int)V, edges, ws.sort_temp_bytes);        // (up to there edge_sort needs one sort)
-        int32_t many = 1, check = 0;
-        if (by_ends) {
-            HIP_TRY(slhc::csr_sort_ends(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, t, f.words + slhc::CSR_FLAG, mail[0].tagged(), mail[0].next(), s));
-            HIP_TRY(mail[0].wait_tagged(1));
-            many = (int32_t)static_cast<volatile unsigned long long*>(mail[0].tagged())[0];
+        // (up to 65 536 vertices edge_sort needs one sort)
+        const bool large = edges > 0 && V > 65536, runs = large && said[4] == 0 && slhc::csr_sort_in_runs_fits(edges, ws.sort_temp_bytes);
+        int32_t ended[2] = {0, 1};                             // the end of all work: a failed check, and that the sort has to be made another way
+        if (runs) {
+            HIP_TRY(slhc::csr_sort_in_runs(ws.e_lo, ws.e_hi, ws.e_w, edges, t, mst_src, mst_dst, mst_w, f.words + slhc::CSR_FLAG, s));
+            HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 2, ended));
         }
-        if (!many) HIP_TRY(slhc::csr_sort_weights(edges, t, mst_src, mst_dst, mst_w, s));
-        else if (edges > 0)
-            HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
-                                    ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
-        HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 1, &check));          // (the end of all work)
+        if (ended[1] != 0) {
+            int32_t many = 1;
+            if (large && slhc::csr_sort_fits((int)V, edges, ws.sort_temp_bytes)) {
+                HIP_TRY(slhc::csr_sort_ends(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, t, f.words + slhc::CSR_FLAG, mail[0].tagged(), mail[0].next(), s));
+                HIP_TRY(mail[0].wait_tagged(1));
+                many = (int32_t)static_cast<volatile unsigned long long*>(mail[0].tagged())[0];
+            }
+            if (!many) HIP_TRY(slhc::csr_sort_weights(edges, t, mst_src, mst_dst, mst_w, s));
+            else if (edges > 0)
+                HIP_TRY(slhc::edge_sort(ws.e_lo, ws.e_hi, ws.e_w, edges, (int)V, ws.keys_a, ws.keys_b, ws.vals_a, ws.vals_b,
+                                        ws.sort_temp, ws.sort_temp_bytes, mst_src, mst_dst, mst_w, slhc::EdgeCopies{}, s));
+            HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 1, ended));
+        }
+        const int32_t check = ended[0];
         mail[0].box.idle();
         mail[1].box.idle();
         rc2 = state(check);
