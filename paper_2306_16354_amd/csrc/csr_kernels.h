@@ -7,9 +7,10 @@
 namespace slhc {
 
 // words: active vertices and roots of a round, three in turn; the number, from 1 on, of a round whose hooks are not followed to
-// their end; edges (added to along with the roots, so not in their line); the first failed check; what the sort says; whether many weights
-// are the same
+// their end; edges (added to along with the roots, so not in their line); the first failed check; what the sort says; CSR_MANY_TIES where
+// many weights are the same
 enum { CSR_ACTIVE = 0, CSR_ROOTS = 32, CSR_CHAINS = 6, CSR_EDGES = 7, CSR_ERROR = 8, CSR_FLAG = 9, CSR_TIES = 10 };
+constexpr unsigned int CSR_MANY_TIES = 0x80000000u;
 struct CsrForest {
     const int32_t *offsets, *indices; const float* weights; int V, E;
     int32_t *colour, *hook;                    // [V]
@@ -21,12 +22,12 @@ struct CsrForest {
 };
 // Round 0: the input check and every vertex's lightest edge.
 hipError_t csr_start(const CsrForest& f, hipStream_t s);
-// Round 1, 2, ... for at most so many active vertices and roots.  On the way host[0 .. 4] get what round - 1 left: active vertices, edges
-// so far, the word of hooks not followed to their end (nothing is done then), the first failed check, whether many weights are the same, each
-// in the low half of a word with `seq` above it.
-constexpr int CSR_TOLD = 5;
+// Round 1, 2, ... for at most so many active vertices and roots.  On the way host[0 .. 3] get what round - 1 left: active vertices (and
+// CSR_MANY_TIES), edges so far, the word of hooks not followed to their end (nothing is done then), the first failed check, each in the low half
+// of a word with `seq` above it.
+constexpr int CSR_TOLD = 4;
 hipError_t csr_round(const CsrForest& f, int round, int vertices, int roots, unsigned long long* host, uint32_t seq, hipStream_t s);
-// All rounds from `round` on; host[0] gets the rounds there were in all.  For at most csr_tail_most active vertices (see k_csr_tail).
+// All rounds from `round` on; host[0] gets the rounds there were in all (and CSR_MANY_TIES).  For at most csr_tail_most active vertices (see k_csr_tail).
 inline long long csr_tail_most(long long V, long long E)
 {
     constexpr long long most = 2048, entries = 12;

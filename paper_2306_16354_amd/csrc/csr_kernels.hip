@@ -151,8 +151,9 @@ template <int THREADS, bool ALL_IN, bool ALL_OUT>
 __global__ void __launch_bounds__(THREADS) k_csr_scan(CsrForest f, int round, unsigned long long* __restrict__ host, uint32_t seq)
 {
     if (blockIdx.x == 0 && threadIdx.x < CSR_TOLD) {
-        const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR, CSR_TIES};
-        __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | (unsigned int)f.words[at[threadIdx.x]], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+        const int at[CSR_TOLD] = {CSR_ACTIVE + round % 3, CSR_EDGES, CSR_CHAINS, CSR_ERROR};
+        const unsigned int word = (unsigned int)f.words[at[threadIdx.x]] | (threadIdx.x == 0 ? (unsigned int)f.words[CSR_TIES] : 0u);
+        __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
     if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;       // (one tree: nothing is left to find)
     const int n = ALL_IN ? f.V : f.words[CSR_ACTIVE + round % 3];
@@ -448,7 +449,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_tail(CsrForest f, int round, unsig
     }
     if (tid == 0) {
         f.words[CSR_EDGES] = s_edges;
-        const int said[CSR_TOLD] = {rounds, s_edges, f.words[CSR_CHAINS], f.words[CSR_ERROR], f.words[CSR_TIES]};
+        const int said[CSR_TOLD] = {rounds | f.words[CSR_TIES], s_edges, f.words[CSR_CHAINS], f.words[CSR_ERROR]};
         for (int i = 0; i < CSR_TOLD; ++i)
             __hip_atomic_store(host + i, ((unsigned long long)seq << 32) | (unsigned int)said[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
@@ -525,7 +526,7 @@ __global__ void __launch_bounds__(SAMPLE) k_csr_words(CsrForest f, int low)
     }
     const int ties = __syncthreads_count(tie), most = 4 + (int)((16ll * SAMPLE * SAMPLE / 2) / f.V);
     const bool all = (tid == CSR_ACTIVE + 1 && list_is_all(f, 0)) || (tid == CSR_ACTIVE + 2 && list_is_all(f, 1));
-    if (tid < 64) f.words[tid] = all ? f.V : tid == CSR_TIES && ties > most ? 1 : 0;
+    if (tid < 64) f.words[tid] = all ? f.V : tid == CSR_TIES && ties > most ? (int)CSR_MANY_TIES : 0;
 }
 
 hipError_t csr_start(const CsrForest& f, hipStream_t s)

@@ -1861,6 +1861,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
             return SLHC_OK;
         };
         int32_t said[slhc::CSR_TOLD];
+        bool ties = false;
         auto state = [&](int32_t check) -> int {
             if (check == 0) return SLHC_OK;
             set_err("forest state check %d failed (is every edge stored in both rows with one weight?)", check);
@@ -1869,6 +1870,8 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         auto read = [&](int which) -> int {
             HIP_TRY(mail[which].wait_tagged(slhc::CSR_TOLD));
             for (int i = 0; i < slhc::CSR_TOLD; ++i) said[i] = (int32_t)static_cast<volatile unsigned long long*>(mail[which].tagged())[i];
+            ties = ((uint32_t)said[0] & slhc::CSR_MANY_TIES) != 0;
+            said[0] = (int32_t)((uint32_t)said[0] & ~slhc::CSR_MANY_TIES);
             if (said[3] >= 20) {
                 set_err("CSR input check %d failed (20-22: offsets, 23: index out of range, 24: weight negative or not finite)", said[3]);
                 return SLHC_INVALID_ARG;
@@ -1941,7 +1944,7 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         t.ends_b = reinterpret_cast<unsigned long long*>(ws.ptr);          // (and ext_idx behind it)
         t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
         // (up to 65 536 vertices edge_sort needs one sort)
-        const bool large = edges > 0 && V > 65536, runs = large && said[4] == 0 && slhc::csr_sort_in_runs_fits(edges, ws.sort_temp_bytes);
+        const bool large = edges > 0 && V > 65536, runs = large && !ties && slhc::csr_sort_in_runs_fits(edges, ws.sort_temp_bytes);
         int32_t ended[2] = {0, 1};                             // the end of all work: a failed check, and that the sort has to be made another way
         if (runs) {
             HIP_TRY(slhc::csr_sort_in_runs(ws.e_lo, ws.e_hi, ws.e_w, edges, t, mst_src, mst_dst, mst_w, f.words + slhc::CSR_FLAG, s));
