@@ -710,7 +710,10 @@ __device__ inline int near_tile_at(const NearSweep& p, int j)
     return p.skip ? j + j / (p.stride - 1) + 1 : j * p.stride;
 }
 
-constexpr int ITEM_TILES = 64;
+// Tiles per item of a list.  The lists of a round are a few thousand tiles in all, and longer items leave CUs without one; shorter ones load a
+// panel's queries more often.  Clusterings with 64, 32, 16 and 8, in ms: 100 000 x 64 4.88, 4.58, 4.55 and 4.50; 60 000 x 100 4.05, 3.73, 3.65 and 3.53;
+// 300 000 x 96 19.07, 18.02, 17.96 and 18.06; 800 000 x 128 67.7, 67.3, 68.4 and 70.5.  (Left-over rows of 100 000 x 64, 376 and 219 us.)
+constexpr int ITEM_TILES = 32;
 
 // Up to 128 columns: a wavefront keeps the fragments of its 64 queries (two blocks of 32) in registers and passes over
 // the candidate tiles, which the workgroup's wavefronts bring into LDS together (double buffered, one barrier per
