@@ -31,6 +31,15 @@ __device__ inline bool in_range(int i, int n) { return (unsigned int)i < (unsign
 __device__ inline void report(const CsrForest& f, int site) { atomicCAS(f.words + CSR_ERROR, 0, site); }
 // a failed check, or hooks that are not followed to their end yet, leave all rounds enqueued to the host
 __device__ inline bool halted(const CsrForest& f) { return (f.words[CSR_ERROR] | f.words[CSR_CHAINS]) != 0; }
+// The same for a whole workgroup, where barriers follow: another workgroup of the launch may report while this one starts, and wavefronts that each
+// read the word could part then, the counts of those that left never written.
+__device__ inline bool all_halted(const CsrForest& f)
+{
+    __shared__ int state;
+    if (threadIdx.x == 0) state = halted(f);
+    __syncthreads();
+    return state != 0;
+}
 
 // A row of up to LONG_ROW entries is read by its vertex's thread (road-like graphs have two or three edges per vertex), which takes 0.2 us per
 // entry; one of up to HUGE_ROW by 16 lanes, four such rows at once; a longer one by the whole wavefront.  Calls with long rows by
@@ -155,7 +164,7 @@ __global__ void __launch_bounds__(THREADS) k_csr_scan(CsrForest f, int round, un
         const unsigned int word = (unsigned int)f.words[at[threadIdx.x]] | (threadIdx.x == 0 ? (unsigned int)f.words[CSR_TIES] : 0u);
         __hip_atomic_store(host + threadIdx.x, ((unsigned long long)seq << 32) | word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
     }
-    if (halted(f) || f.words[CSR_EDGES] >= f.V - 1) return;       // (one tree: nothing is left to find)
+    if ((ALL_OUT ? halted(f) : all_halted(f)) || f.words[CSR_EDGES] >= f.V - 1) return;       // (one tree: nothing is left to find)
     const int n = ALL_IN ? f.V : f.words[CSR_ACTIVE + round % 3];
     const int32_t* from = f.active[round & 1];
     int32_t* to = f.active[(round + 1) & 1];
@@ -248,7 +257,7 @@ __device__ inline void append_two(int (&a)[ITEMS], int (&b)[ITEMS], int32_t* cou
 // that chose the same edge keep the smaller root; roots that stay get cleared minima for the next round.
 __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
 {
-    if (halted(f)) return;
+    if (all_halted(f)) return;
     const int n = f.words[CSR_ROOTS + round % 3];
     const int32_t* from = f.roots[round & 1];
     int32_t* to = f.roots[(round + 1) & 1];
@@ -297,7 +306,7 @@ __global__ void __launch_bounds__(WIDE) k_csr_commit(CsrForest f, int round)
 template <int ITEMS>
 __global__ void __launch_bounds__(WIDE) k_csr_commit_first(CsrForest f)
 {
-    if (halted(f)) return;
+    if (all_halted(f)) return;
     const long long base = (long long)blockIdx.x * (WIDE * ITEMS) + threadIdx.x;
     unsigned long long mine[ITEMS], theirs[ITEMS];
     int adds[ITEMS], stays[ITEMS];
