@@ -48,8 +48,10 @@ constexpr int most_links(int r) { return r == 0 ? 6 : 12; }
 constexpr int TOP_MAX = 16384;       // merges of the last stage in LDS, a word each: the third stage up to 33 million merges
 
 // above[i]: the merge above merge i, itself for a root, -1 - number once it is known.  joined[v]: whether a kept merge has row v as a child.
-__global__ void __launch_bounds__(TB) k_cut_init(int32_t* __restrict__ above, int kept, uint32_t* __restrict__ joined, int words)
+__global__ void __launch_bounds__(TB) k_cut_init(int32_t* __restrict__ above, int kept, uint32_t* __restrict__ joined, int words,
+                                                 int32_t* __restrict__ open)
 {
+    if (blockIdx.x == 0 && threadIdx.x == 0) *open = 0;
     const int v = (blockIdx.x * TB + threadIdx.x) * 4;
     if (v + 3 < kept) *reinterpret_cast<int4*>(above + v) = make_int4(v, v + 1, v + 2, v + 3);
     else
@@ -190,7 +192,9 @@ __global__ void __launch_bounds__(TB) k_cut_stage(int32_t* __restrict__ above, i
     walk_up<R>(above, kept, blockIdx.x * TB + threadIdx.x);
 }
 
-// What is left of the last stage, in LDS by its numbers there: walks over links of four until every one has its root's number.
+// What is left of the last stage, in LDS by its numbers there: walks over links of four until every one has its root's number.  A merge that no
+// merge of the stage lies near above, and those that lead to it, are left as they are.
+constexpr int NEAR_LINKS = 64, LEFT_OPEN = -2147483647 - 1;
 template <int STAGES>
 __global__ void __launch_bounds__(1024) k_cut_top(int32_t* __restrict__ above, int kept, int n)
 {
@@ -198,10 +202,10 @@ __global__ void __launch_bounds__(1024) k_cut_top(int32_t* __restrict__ above, i
     volatile int* at = link;
     for (int j = threadIdx.x; j < n; j += 1024) {
         const unsigned int i = stage_merge<STAGES>((unsigned int)j);
-        int a = -1;
+        int a = LEFT_OPEN;
         if (i < (unsigned int)kept) {
             a = above[i];
-            while (a >= 0 && !in_stage<STAGES>((unsigned int)a)) a = above[a];
+            for (int h = 0; a >= 0 && !in_stage<STAGES>((unsigned int)a); ++h) a = h < NEAR_LINKS ? above[a] : LEFT_OPEN;
             if (a >= 0) a >>= stage_bits(STAGES);
         }
         at[j] = a;
@@ -220,13 +224,14 @@ __global__ void __launch_bounds__(1024) k_cut_top(int32_t* __restrict__ above, i
     }
     for (int j = threadIdx.x; j < n; j += 1024) {
         const unsigned int i = stage_merge<STAGES>((unsigned int)j);
-        if (i < (unsigned int)kept) above[i] = at[j];
+        if (at[j] != LEFT_OPEN) above[i] = at[j];
     }
 }
 
-// Every merge's rows take the number at the end of its walk, one link per stage as a rule.
+// Every merge's rows take the number at the end of its walk, one link per stage as a rule.  A chain may avoid the merges that the hash sends up,
+// whatever the hash is; where a walk is not through after NEAR_LINKS links, *open says so.
 __global__ void __launch_bounds__(TB) k_cut_labels(const int2* __restrict__ children, int N, int kept, const int32_t* __restrict__ above,
-                                                   int32_t* __restrict__ labels)
+                                                   int32_t* __restrict__ labels, int32_t* __restrict__ open)
 {
     const int i = blockIdx.x * TB + threadIdx.x;
     if (i >= kept) return;
@@ -234,9 +239,34 @@ __global__ void __launch_bounds__(TB) k_cut_labels(const int2* __restrict__ chil
     const bool x = (unsigned int)c.x < (unsigned int)N, y = (unsigned int)c.y < (unsigned int)N;
     if (!x && !y) return;
     int a = above[i];
-    while (a >= 0) a = above[a];
+#pragma unroll 1
+    for (int h = 0; a >= 0 && h < NEAR_LINKS; ++h) a = above[a];
+    if (a >= 0) { *open = 1; return; }
     if (x) labels[c.x] = -1 - a;
     if (y) labels[c.y] = -1 - a;
+}
+
+// Then all merges again, OPEN_SPAN at a time from the last down: what lies above a span is done, and in it every merge keeps where it got to after
+// each few links, so links grow as many times each time and a span takes a dozen turns at most.  (Past the caches, which may hold older links.)  Chains that
+// avoid all of stage 1, with walks of any length in the launches before: 20 000 rows 630 us, 60 000 2014, so 40 000 72 and 300 000 124, where a plain chain
+// takes 49.  Where nothing is open the launch costs 1.7 us (1M rows 85.6 and 87.3).
+constexpr int OPEN_BLOCKS = 256, OPEN_SPAN = OPEN_BLOCKS * TB, OPEN_LINKS = 4;
+__global__ void __launch_bounds__(TB) k_cut_open(const int2* __restrict__ children, int N, int kept, int32_t* above, int32_t* __restrict__ labels,
+                                                 const int32_t* __restrict__ open)
+{
+    if (*open == 0) return;
+    for (int i = kept - 1 - (int)(blockIdx.x * TB + threadIdx.x); i >= 0; i -= OPEN_SPAN) {
+        int a = above[i];
+        // (one loop, not one of OPEN_LINKS steps inside another: from that the compiler, clang 22 of ROCm 7.2, makes a loop whose lanes that ended in an
+        // earlier step than others go on)
+        for (int h = 1; a >= 0; ++h) {
+            a = __hip_atomic_load(above + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+            if (h % OPEN_LINKS == 0) __hip_atomic_store(above + i, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        const int2 c = children[i];
+        if ((unsigned int)c.x < (unsigned int)N) labels[c.x] = -1 - a;
+        if ((unsigned int)c.y < (unsigned int)N) labels[c.y] = -1 - a;
+    }
 }
 
 // All of it for at most FLAT_SMALL rows, in one workgroup with 16-bit links in LDS: the five to ten launches above cost more
@@ -301,7 +331,7 @@ static void cut_stages(int32_t* above, int kept, unsigned int n, hipStream_t s)
     hipLaunchKernelGGL(k_cut_top<R + 1>, dim3(1), dim3(1024), (size_t)up * 4, s, above, kept, (int)up);     // (2^30 merges: 2048 of stage 5)
 }
 
-size_t flat_clusters_spans(int64_t N) { return root_spans((unsigned int)N, (unsigned int)N).all(); }
+size_t flat_clusters_counts(int64_t N) { return (size_t)root_spans((unsigned int)N, (unsigned int)N).all() + 1; }
 
 hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t* labels, int32_t* above, unsigned char* joined,
                          int32_t* counts, hipStream_t s)
@@ -313,8 +343,9 @@ hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t
         return hipGetLastError();
     }
     const int2* c = reinterpret_cast<const int2*>(children);
+    int32_t* open = counts + flat_clusters_counts(N) - 1;
     const int words = (N + 3) / 4, quads = (kept + 3) / 4;
-    hipLaunchKernelGGL(k_cut_init, dim3(blocks_for(words > quads ? words : quads)), dim3(TB), 0, s, above, kept, reinterpret_cast<uint32_t*>(joined), words);
+    hipLaunchKernelGGL(k_cut_init, dim3(blocks_for(words > quads ? words : quads)), dim3(TB), 0, s, above, kept, reinterpret_cast<uint32_t*>(joined), words, open);
     if (kept > 0) hipLaunchKernelGGL(k_cut_links, dim3(blocks_for(kept)), dim3(TB), 0, s, c, N, kept, above, joined);
     const RootSpans spans = root_spans((unsigned int)N, (unsigned int)kept);
     const unsigned int stage1 = ((unsigned int)kept + (1u << group_bits(0)) - 1) >> group_bits(0);
@@ -322,7 +353,8 @@ hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t
     hipLaunchKernelGGL(k_cut_second, dim3(blocks_for(stage1) + (int)spans.all()), dim3(TB), 0, s, above, joined, spans, blocks_for(stage1), counts, labels);
     if (kept > 0) {
         cut_stages<2>(above, kept, (stage1 + (1u << group_bits(1)) - 1) >> group_bits(1), s);
-        hipLaunchKernelGGL(k_cut_labels, dim3(blocks_for(kept)), dim3(TB), 0, s, c, N, kept, above, labels);
+        hipLaunchKernelGGL(k_cut_labels, dim3(blocks_for(kept)), dim3(TB), 0, s, c, N, kept, above, labels, open);
+        hipLaunchKernelGGL(k_cut_open, dim3(OPEN_BLOCKS), dim3(TB), 0, s, c, N, kept, above, labels, open);
     }
     return hipGetLastError();
 }

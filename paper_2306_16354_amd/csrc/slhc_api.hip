@@ -2051,7 +2051,7 @@ struct FlatWs {
         Carver c(ws);
         above = c.take<int32_t>((size_t)N + 4);                // (read four words and sixteen marks at a time)
         joined = c.take<unsigned char>((size_t)N + 16);
-        counts = c.take<int32_t>(slhc::flat_clusters_spans(N));
+        counts = c.take<int32_t>(slhc::flat_clusters_counts(N));
         bytes = std::max(c.off, 3 * up(2 * (size_t)N * sizeof(int32_t)));       // (the larger: what is asked for has not changed)
     }
 };
