@@ -656,7 +656,8 @@ __global__ void __launch_bounds__(BLOCK) direct_near_kernel(DirectNear p)
 // engine makes a copy of all candidates first, which costs what a dozen queries' evaluations cost, and has nine launches.  So as many queries beyond
 // twelve as are 240 M operations:
 //   300 x 10 000 x 20 22 and 35, 100 x 50 000 x 20 32 and 43, 30 x 150 000 x 20 32 and 58, 10 x 500 000 x 20 47 and 103, 30 x 500 000 x 6 59 and 103,
-//   100 x 10 000 x 64 23 and 36, 30 x 150 000 x 64 60 and 66, 10 x 500 000 x 128 169 and 214, 30 x 50 000 x 128 51 and 57, 10 x 500 000 x 250 356 and 589;
+//   100 x 10 000 x 64 23 and 36, 30 x 150 000 x 64 60 and 66, 10 x 500 000 x 128 170 and 212, 30 x 50 000 x 128 51 and 57, 10 x 500 000 x 250 356 and 589;
+//   wide rows: 16 x 10 000 x 784 57 and 97, 12 x 10 000 x 2000 137 and 200, 12 x 10 000 x 8000 596 and 1746, 12 x 3000 x 12 000 795 and 2635, 16 x 30 000 x 784 75 and 144;
 //   beyond: 1000 x 10 000 x 20 50 and 37, 100 x 150 000 x 20 74 and 58, 100 x 50 000 x 64 62 and 47, 30 x 500 000 x 64 170 and 127, 300 x 10 000 x 128 76 and 50.
 bool direct_1nn_wanted(long long m, long long nc, int d)
 {
@@ -673,10 +674,12 @@ hipError_t direct_1nn(const float* Xq, int m, int nq_rows, const int32_t* q_rows
 {
     if (m < 1) return hipSuccess;
     const int per = WAVES * QW1, panels = (m + per - 1) / per;
-    // shares of the candidates: about four workgroups per CU, at least four steps each
+    // Shares of the candidates: about four workgroups per CU, of at least four slabs of 64 candidates each, which are a round trip to memory each, one after
+    // the other.  (With four steps of all slabs at least, 16 x 10 000 x 784 took 202 us, 12 x 10 000 x 2000 581, 4 x 10 000 x 8000 2711 and 8 x 1000 x 250 55; the
+    // engine 97, 186 and 1158 of the first three; so 57, 137, 598 and 19.  Two slabs a row, 8 x 3000 x 128 37 and 25, 300 x 300 x 100 29 and 22.)
     int segments = panels >= 512 ? 1 : 1024 / panels;
-    const int steps = (nc + 63) / 64;
-    if (segments > steps / 4) segments = steps / 4;
+    const int steps = (nc + 63) / 64, slabs = (d + SLAB - 1) / SLAB, least = slabs >= 4 ? 1 : (3 + slabs) / slabs;
+    if (segments > steps / least) segments = steps / least;
     if (segments < 1) segments = 1;
     const int per_segment = (steps + segments - 1) / segments * 64;
     segments = (nc + per_segment - 1) / per_segment;
