@@ -240,6 +240,13 @@ __device__ inline int near_pos(int row, int tiles)             // (not in order)
     return t * TILE + ((b & 96) | ((b - near_turn(t)) & 31));
 }
 
+// A panel of 128 rows goes to the list kernels, known before what is there of its rows' lists is looked through.
+constexpr int PANEL_GONE = 2;
+__device__ inline void near_panel_gone(int32_t* todo, int32_t* todo_mark, int panel)
+{
+    if (atomicExch(todo_mark + panel, PANEL_GONE) == 0) todo[2 + atomicAdd(todo, 1)] = panel;
+}
+
 // i * near_spread(n) % n for i = 0, 1, ...: the numbers below n in an order whose every stretch is spread evenly over them (n times the
 // golden ratio, or the next number that has no divisor in common with n).  Products below 2^32: up to n = 2^17, beyond that as they are.
 inline int near_spread(int n)

@@ -20,6 +20,8 @@ struct NearPairs {
     // pairs_emit: rows whose lists overflowed, as far as pairs_tighten has counted them; beyond lost_most of them pairs_emit does nothing
     int32_t* lost; int lost_most;
     int cap_again;                         // pairs_left: entries of the lists of the search for the rows left over
+    // (as NearBuffers) panels some of whose rows are not searched for again
+    int32_t *todo, *todo_mark; int full_gone;      // full_gone: pairs in either order, those of rows whose lists are full
     // pairs_best: by position (w, position of the first of the 16 rows about it), w = max(0, -u) of the nearest row of another
     // colour so far; not 0x7f.. / all ones in the beginning.  both = 0: the block's own rows only are served
     unsigned long long* best; int both;

@@ -1,0 +1,59 @@
+"""Searches of the rows among themselves (pairs_kernels.hip) where most rows' lists are not long enough, and the list kernels, or a second search, make them: the same
+lists, and not much longer than the list kernels take for all rows, which the calls are measured against."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def radial(N, d):
+    """Norms over orders of magnitude: the float16 copy does not tell the rows of small norm apart."""
+    g = torch.Generator(device="cuda").manual_seed(N)
+    X = torch.randn((N, d), generator=g, device="cuda")
+    return X / X.norm(dim=1, keepdim=True) * torch.rand((N, 1), generator=g, device="cuda") ** 4 * 1000
+
+
+def copies(N, d, n):
+    g = torch.Generator(device="cuda").manual_seed(N)
+    return torch.randn((N // n + 1, d), generator=g, device="cuda").repeat(n, 1)[:N][torch.randperm(N, generator=g, device="cuda")].contiguous()
+
+
+def least_ms(f):
+    f()
+    least = float("inf")
+    for _ in range(6):
+        begin, end = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        begin.record()
+        f()
+        end.record()
+        end.synchronize()
+        least = min(least, begin.elapsed_time(end))
+    return least
+
+
+def check(X, k):
+    import paper_2306_16354_amd as slhc
+    want, got = slhc.knn_graph(X, k, fp32_filter=True), slhc.knn_graph(X, k)
+    assert torch.equal(want[0], got[0]) and torch.equal(want[1], got[1])
+    took, lists = least_ms(lambda: slhc.knn_graph(X, k)), least_ms(lambda: slhc.knn_graph(X, k, fp32_filter=True))
+    print(f"  {took:.2f} ms, the list kernels {lists:.2f}: {took / lists:.2f}", flush=True)
+    return took / lists
+
+
+# 1.24 and 1.30 of sweeps that gave a row up at its first full buffer, 1.67 and 1.47 when full lists took all that passed to the end, 1.32 and 1.21 where they
+# take no more and panels that are made again are not looked through first
+@pytest.mark.parametrize("N,d,k,most", [(40_000, 24, 20, 1.5), (70_000, 60, 10, 1.35)])
+def test_full_lists_take_no_more(N, d, k, most):
+    print(f"full lists N={N} d={d} k={k}", flush=True)
+    assert check(radial(N, d), k) < most
+
+
+# few rows and all rows with full lists, in one band and in several; in either order and once; with the second search and without
+@pytest.mark.parametrize("N,d", [(5000, 12), (9000, 40), (20_011, 30), (40_000, 30), (60_000, 100), (70_000, 48), (12_000, 200)])
+@pytest.mark.parametrize("share", [0.001, 0.05, 1.0])
+def test_full_lists(N, d, share):
+    print(f"full lists N={N} d={d}, {share} of the rows", flush=True)
+    X = torch.randn((N, d), generator=torch.Generator(device="cuda").manual_seed(d), device="cuda")
+    m = max(1100, int(share * N))
+    X[:m] = copies(m, d, 1100)
+    check(X[torch.randperm(N, device="cuda")].contiguous(), 10)
