@@ -1113,6 +1113,7 @@ __global__ void __launch_bounds__(256) near_bounds_kernel(const float* __restric
 constexpr unsigned int MARK = 0x80000000u;
 struct NearSelect {
     const uint2* entries; const int32_t* counts; int nsub, capl, nq_batch, q0, by_position;
+    int list0;                       // by position: the position of the first count
     const float* qnegh; const NearScale* sc; float e, nu; int steps;
     const float* Xq; const float* Xc; const int32_t* q_rows;
     int d, k, kk, nq, nq_rows, nc, q_tiles, c_tiles, exclude_self;
@@ -1227,7 +1228,7 @@ __global__ void __launch_bounds__(256) near_select_kernel(NearSelect p)
     const float base = p.pair_lists ? nh : 0.f;
     bool lost = nh == INF || (p.region && p.negh_local[qcopy] == INF);
     {
-        const int mine = lane < p.nsub ? p.counts[p.by_position ? (size_t)qpos : (size_t)lq * p.nsub + lane] : 0;
+        const int mine = lane < p.nsub ? p.counts[p.by_position ? (size_t)(qpos - p.list0) : (size_t)lq * p.nsub + lane] : 0;
         lost = lost || __any(mine > p.capl);
         int upto = mine;
 #pragma unroll
@@ -1680,6 +1681,7 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
 struct PairPlan {
     NearPlan sample;
     int waves, blocks, cap, bands, to[8], nseg[8];
+    int batch;                             // tiles whose rows are searched for at a time
     bool once;
 };
 // From 32 tiles on.  Against sweeps that keep what passes by a branch per value (near_sweep_kernel's emission, which is left where memory is short), in us:
@@ -1697,6 +1699,7 @@ static bool pairs_once(int T, int steps) { return steps > REG_STEPS || (T <= 100
 constexpr int PAIR_AGAIN_TILES = 256;
 // bytes: of the memory for them (0: the least there may be).  Lists are as long as it allows, up to PAIRS_MOST, which costs nothing where they
 // stay short (5000 x 200 and 16 000 x 300, lists of 256 and 1024: the same times) and leaves fewer rows over.
+constexpr int PAIR_TURNS = 8;              // at most
 static size_t pair_lists_bytes(int T, int cap) { return (size_t)T * TILE * (24 + 8 * (size_t)cap) + 4096; }
 static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* out)
 {
@@ -1722,10 +1725,24 @@ static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* o
             if (cost < best) { best = cost; stride = s; more = b; }
         }
     const double g = more > 0 ? pow((double)stride, 1.0 / more) : 1.0;
+    // Lists take what memory there is.  Where that is less than PAIRS_MOST entries for every row (from some 150 000 rows on), rows whose pairs are met in either order are
+    // searched for in turns, with whole lists: rows left over cost a second search otherwise, with a branch per value that passes, or the list kernels.  k = 12, 300 000 x 10 of 600
+    // copies each 67 -> 27.8 ms, of 2000 238 -> 185; k = 10, 174 000 x 20 of 900 62 -> 20, 250 000 x 40 with norms over orders of magnitude 96 -> 88, blobs of 800 000 x 16 57 -> 39.
+    // What a turn costs beside, its launches and their ends: blobs of 160 000 x 20 3.12 and 3.00 ms, 180 000 x 10 3.27 and 3.39, 220 000 x 20 5.02 and 5.15, 250 000 x 40 7.81 and
+    // 7.80.  (Workgroups of half and of one and a half times the length in turns: 220 000 x 20 5.32 and 5.19.)
+    while (p.cap + 64 <= PAIRS_MOST && pair_lists_bytes(T, p.cap + 64) <= bytes) p.cap += 64;
+    p.batch = T;
+    const long long fit = bytes > 8192 ? (long long)((bytes - 8192) / (pair_lists_bytes(1, PAIRS_MOST) - 4096)) / 2 * 2 : 0;
+    if (!p.once && p.cap < PAIRS_MOST && fit * PAIR_TURNS >= T) {
+        const int turns = (int)((T + fit - 1) / fit);
+        p.batch = ((T + turns - 1) / turns + 1) / 2 * 2;
+        p.cap = PAIRS_MOST;
+    }
     auto lay_out = [&](int waves) {
         const int bt = wide ? 2 : waves / 2, slots = waves >= 8 ? cus : (p.once && steps > 5 ? 2 : 3) * cus;
         p.waves = waves;
         p.blocks = (T + bt - 1) / bt;
+        const int asking = (p.batch + bt - 1) / bt;
         const int half = p.once ? p.blocks / 2 + 1 : p.blocks;     // meetings of a block
         double seen = 1.0 / stride;
         int from = 0;
@@ -1733,10 +1750,10 @@ static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* o
             int to = p.bands == more ? half : p.once ? (int)(0.5 * (seen * p.blocks + 1.0)) : (int)(seen * p.blocks + 0.5);
             to = to < from + 1 ? from + 1 : (to > half ? half : to);
             const int len = to - from;
-            int seg = (8 * slots + p.blocks - 1) / p.blocks;
+            int seg = (8 * slots + asking - 1) / asking;
             if (wide && seg < 4) seg = 4;      // (so that an XCD's workgroups share 8 blocks, see the kernel)
             // about eight rounds of workgroups, the last of them as full as can be
-            auto rounds = [&](int n) { return (double)(((long long)p.blocks * n + slots - 1) / slots) * ((double)len / n + 0.15); };
+            auto rounds = [&](int n) { return (double)(((long long)asking * n + slots - 1) / slots) * ((double)len / n + 0.15); };
             int best_seg = seg > len ? len : seg;
             for (int n = waves == 4 ? 1 : (2 * seg + 2) / 3; !wide && n <= len && 2 * n <= 3 * seg; ++n)
                 if (rounds(n) < rounds(best_seg)) best_seg = n;
@@ -1752,13 +1769,12 @@ static bool near_pair_plan(long long n, int d, int kk, size_t bytes, PairPlan* o
     lay_out(waves);
     p.sample = near_plan(n, n, d, kk, 0);
     NearPlan& q = p.sample;
-    const int used = (T + stride - 1) / stride, panels = (T + q.panel_tiles - 1) / q.panel_tiles;
-    int seg = (q.waves == 8 ? cus : 2 * cus) / panels;
+    const int used = (T + stride - 1) / stride, panels = (p.batch + q.panel_tiles - 1) / q.panel_tiles;
+    int seg = (q.waves == 8 && p.batch == T ? cus : 2 * cus) / panels;       // (in turns there are few panels: two workgroups to a CU)
     const int units = wide ? (used + 1) / 2 : used, limit = wide ? 8 : 16;
     seg = seg > limit ? limit : seg;
     seg = seg > units ? units : seg;
     near_sample(q, stride, T, kk, wide, seg < 1 ? 1 : seg);
-    while (p.cap + 64 <= PAIRS_MOST && pair_lists_bytes(T, p.cap + 64) <= bytes) p.cap += 64;
     *out = p;
     return true;
 }
@@ -1771,9 +1787,11 @@ size_t near_pairs_bytes(long long n, int d, int kk, bool* once)
     return pair_lists_bytes(near_tiles(n), p.cap);
 }
 
-static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, const NearBuffers& b, const PairPlan& plan, bool vec4, hipStream_t s)
+static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, const NearBuffers& b, const PairPlan& plan, bool vec4, int first, hipStream_t s)
 {
-    const int kk = a.k + 1, steps = near_steps(a.d), rows = c.tiles * TILE;
+    // the rows of the tiles from `first` on
+    const int end = first + plan.batch < c.tiles ? first + plan.batch : c.tiles, tiles = end - first;
+    const int kk = a.k + 1, steps = near_steps(a.d), rows = tiles * TILE;
     const bool wide = steps > REG_STEPS;
     const float e = near_e(steps), nu = near_nu(steps);
     unsigned char* at = b.pairs;
@@ -1798,22 +1816,23 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     long long batch = (long long)(lists_bytes / per_tile) / q.panel_tiles * q.panel_tiles;
     if (batch < 1) return hipErrorInvalidValue;
     hipError_t err = hipSuccess;
-    for (int t0 = 0; t0 < c.tiles; t0 += (int)batch) {
-        const int t1 = t0 + batch < c.tiles ? t0 + (int)batch : c.tiles;
+    if (first > 0) hipLaunchKernelGGL(near_todo_clear_kernel, dim3(1), dim3(256), 0, s, left.count, 1);
+    for (int t0 = first; t0 < end; t0 += (int)batch) {
+        const int t1 = t0 + batch < end ? t0 + (int)batch : end, at = t0 - first;
         p.q_tile0 = t0; p.q_tile1 = t1; p.nq_batch = (t1 - t0) * TILE;
         p.maxima = maxima;
         err = near_launch_sweep<NEAR_MAXIMA, false>(p, q.waves, s);
         if (err != hipSuccess) return err;
         hipLaunchKernelGGL((near_bounds_kernel<true>), dim3((unsigned)(p.nq_batch / 4)), dim3(256), 0, s, maxima, q.max_sets, q.groups == GROUPS ? 5 : 3, p.nq_batch,
-                           t0 * TILE, kk, c.negh, b.scale, e, nu, steps, a.d, limit + (size_t)t0 * TILE, static_cast<float*>(nullptr),
+                           t0 * TILE, kk, c.negh, b.scale, e, nu, steps, a.d, limit + (size_t)at * TILE, static_cast<float*>(nullptr),
                            static_cast<const int32_t*>(nullptr), 1, static_cast<const int32_t*>(nullptr), static_cast<const float*>(nullptr),
-                           static_cast<const NearScale*>(nullptr), counts + (size_t)t0 * TILE, left.row + (size_t)t0 * TILE, lost);
+                           static_cast<const NearScale*>(nullptr), counts + (size_t)at * TILE, left.row + (size_t)at * TILE, lost);
     }
     NearPairs r{};
-    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.filled = (a.d + 15) / 16; r.blocks = plan.blocks; r.once = plan.once; r.spread = near_spread(r.blocks);
+    r.frag = c.frag; r.negh = c.negh; r.tiles = c.tiles; r.steps = steps; r.filled = (a.d + 15) / 16; r.blocks = plan.blocks; r.once = plan.once; r.first = first / (wide ? 2 : plan.waves / 2); r.row0 = first * TILE; r.rows = rows; r.spread = near_spread(r.blocks);
     r.limit = limit; r.entries = entries; r.counts = counts; r.cap = plan.cap;
     const bool again = c.tiles >= PAIR_AGAIN_TILES;
-    r.lost = lost; r.lost_most = again ? a.nq / 2 : rows;
+    r.lost = lost; r.lost_most = again ? (rows < a.nq ? rows : a.nq) / 2 : rows;
     r.todo = b.todo; r.todo_mark = b.todo_mark; r.full_gone = !again && !plan.once;
     for (int i = 0; i < plan.bands; ++i) {
         if (i > 0) {
@@ -1837,7 +1856,7 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     sel.out_idx = a.out_idx; sel.out_dist = a.out_dist; sel.evaluated = a.evaluated;
     sel.todo = b.todo; sel.todo_mark = b.todo_mark;
     sel.entries = entries; sel.counts = counts; sel.nsub = 1; sel.by_position = 1; sel.capl = plan.cap; sel.pair_lists = 1; sel.skip_gone = again || r.full_gone;
-    sel.nq_batch = rows; sel.q0 = 0;
+    sel.nq_batch = rows; sel.q0 = sel.list0 = first * TILE;
     auto select = [&]() -> hipError_t {
         near_select(sel, vec4, dim3((unsigned)((sel.nq_batch + 3) / 4)), s);
         return hipGetLastError();
@@ -1852,12 +1871,12 @@ static hipError_t near_search_pairs(const NearProblem& a, const NearCopy& c, con
     p.qpos = left.pos; p.n_dev = left.count; p.slots = (waves == 8 ? 1 : 2) * near_cus(); p.most_seg = p.slots;
     p.reach = left.reach; p.counts = left.counts; p.capl = r.cap; p.entries = entries;
     sel.q_rows = sel.slot = left.row; sel.qpos = left.pos; sel.n_dev = left.count;
-    sel.q_in_order = 1; sel.counts = left.counts; sel.capl = r.cap; sel.pair_lists = 0; sel.nq = rows;
+    sel.q_in_order = 1; sel.counts = left.counts; sel.capl = r.cap; sel.pair_lists = 0; sel.nq = rows; sel.list0 = 0;
     int room = (int)(lists_bytes / ((size_t)TILE * r.cap * 8));            // tiles of queries whose lists fit
-    if (room < c.tiles) room = room / 2 * 2;
+    if (room < tiles) room = room / 2 * 2;
     if (room < 2) return hipErrorInvalidValue;
-    for (int t0 = 0; t0 < c.tiles; t0 += room) {
-        p.q_tile0 = t0; p.q_tile1 = t0 + room < c.tiles ? t0 + room : c.tiles;
+    for (int t0 = 0; t0 < tiles; t0 += room) {
+        p.q_tile0 = t0; p.q_tile1 = t0 + room < tiles ? t0 + room : tiles;
         p.nq_batch = sel.nq_batch = (p.q_tile1 - t0) * TILE; sel.q0 = t0 * TILE;
         err = near_launch_sweep<NEAR_NEAREST, false>(p, waves, s);
         if (err == hipSuccess) err = pairs_again(r, kk, b.scale, e, nu, a.d, t0 * TILE, p.nq_batch, left, s);
@@ -1878,8 +1897,11 @@ hipError_t near_search(const NearProblem& a, const NearCopy& q, const NearCopy& 
     const bool vec4 = a.d % 4 == 0 && ((reinterpret_cast<uintptr_t>(a.Xq) | reinterpret_cast<uintptr_t>(a.Xc)) & 15) == 0;
     PairPlan pairs;
     if (a.exclude_self && q.frag == c.frag && !c.in_order && b.pairs && near_pair_plan(a.nc, a.d, kk, b.pairs_bytes, &pairs) &&
-        b.pairs_bytes >= pair_lists_bytes(c.tiles, pairs.cap))
-        return near_search_pairs(a, c, b, pairs, vec4, s);
+        b.pairs_bytes >= pair_lists_bytes(pairs.batch, pairs.cap)) {
+        hipError_t e = hipSuccess;
+        for (int first = 0; first < c.tiles && e == hipSuccess; first += pairs.batch) e = near_search_pairs(a, c, b, pairs, vec4, first, s);
+        return e;
+    }
     NearSweep p{};
     p.qfrag = q.frag; p.qnegh = q.negh; p.qcolour = q.colour;
     p.cfrag = c.frag; p.cnegh = c.negh; p.ccolour = c.colour; p.c_tiles = c.tiles;

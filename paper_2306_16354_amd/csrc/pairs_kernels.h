@@ -13,6 +13,9 @@ struct NearPairs {
     const unsigned char* frag; const float* negh; const int32_t* colour;      // the copy (colour: pairs_best)
     int tiles, steps, filled;              // steps of 16 columns a row's place has, and how many of them hold columns
     int blocks, from, to, nseg;            // block i meets the blocks i + from .. i + to - 1, in nseg shares
+    // Pairs in either order may be searched for some blocks' rows at a time, `rows` from position `row0` on, which are the first ones of block `first`:
+    // limit, counts, entries, lost and what follows are theirs.  (Else all rows: 0, 0, 128 tiles.)
+    int first, row0, rows;
     int once;                              // every pair once, for both of its rows (to: half way round), or in either order for its first row
     int spread;                            // near_spread(blocks): place i of the circle has block i * spread % blocks of the copy
     float* limit;                          // pairs_emit: by position, the u from which on a pair matters to the row (NaN: none does)

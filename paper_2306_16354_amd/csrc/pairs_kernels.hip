@@ -41,7 +41,7 @@ __device__ inline unsigned int pair_code(int tile, int c, int q, bool own)
 {
     return ((unsigned int)tile << 15) | ((unsigned int)c << 8) | ((unsigned int)q << 2) | (own ? PAIR_OWN : 0u);
 }
-// q0: position of the wavefront's first query
+// q0: the wavefront's first query among the rows of the lists
 __device__ inline int pair_q(unsigned int code, int q0) { return q0 + (int)((code >> 2) & 63u); }
 __device__ inline int pair_c(unsigned int code) { return (int)(code >> 15) * TILE + (int)((code >> 8) & 127u); }
 __device__ inline void pair_entry(const NearPairs& p, int row, int slot, unsigned int u, unsigned int other)
@@ -195,8 +195,10 @@ __device__ inline PairRange pair_range(const NearPairs& p, int item)
 {
     PairRange r;
     r.at = item / p.nseg;
-    r.block = near_spread_at(r.at, p.spread, p.blocks);
     const int seg = item - r.at * p.nseg;
+    // (in either order it is all the same where on the circle a block begins)
+    if (!ONCE) r.at += p.first;
+    r.block = ONCE ? near_spread_at(r.at, p.spread, p.blocks) : r.at;
     // half way round an even circle two blocks meet from both sides
     const int to = ONCE && 2 * (p.to - 1) == p.blocks && p.to - 1 > 0 && 2 * r.at >= p.blocks ? p.to - 1 : p.to;
     r.from = p.from;
@@ -230,14 +232,15 @@ __global__ void __launch_bounds__(ONCE ? 768 : 256, ONCE ? 3 : KS <= 2 ? 5 : KS 
     const PairRange range = pair_range<ONCE>(p, blockIdx.x);
     const int qtile = range.block * bt + (wave >> 1);
     const bool live = qtile < p.tiles;                   // (whole wavefronts)
-    const int q0 = (live ? qtile : 0) * TILE + (wave & 1) * 64;
+    const int row0 = ONCE ? 0 : p.row0;
+    const int q_pos = (live ? qtile : row0 / TILE) * TILE + (wave & 1) * 64, q0 = q_pos - row0;        // position, and among the rows of the lists
     float h[2], bound[2];
     v8h qf[2][KS];
 #pragma unroll
     for (int qb = 0; qb < 2; ++qb) {
-        const int at = q0 + qb * 32 + l32;
+        const int at = q_pos + qb * 32 + l32;
         h[qb] = live ? -p.negh[at] : NEVER;
-        bound[qb] = live ? p.limit[at] + h[qb] : NEVER;
+        bound[qb] = live ? p.limit[at - row0] + h[qb] : NEVER;
         const unsigned char* src = p.frag + (size_t)(at >> 7) * (KS * FRAG_STEP) + ((at >> 5) & 3) * 1024 + lane * 16;
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) qf[qb][ks] = *reinterpret_cast<const v8h*>(src + ks * FRAG_STEP);
@@ -254,8 +257,9 @@ __global__ void __launch_bounds__(ONCE ? 768 : 256, ONCE ? 3 : KS <= 2 ? 5 : KS 
     auto advance = [&]() {
         if (step_t == 0) {
             const int off = pair_offset(range, step_j++);
-            next_tile = pair_other(p, range, off) * bt;
-            next_own = off == 0;
+            const int block = pair_other(p, range, off);
+            next_tile = block * bt;
+            next_own = block == range.block;
         } else ++next_tile;
         if (++step_t == bt) step_t = 0;
     };
@@ -327,7 +331,7 @@ __global__ void __launch_bounds__(ONCE ? 768 : 256, ONCE ? 3 : KS <= 2 ? 5 : KS 
     if (live) pair_finish<ONCE>(w, p, q0);
     // panels of rows whose lists are full are not looked through (see near_select_kernel); the additions to these rows that this wavefront saw are all made
     if (!ONCE && p.full_gone && (ever_full || w.full) && __hip_atomic_load(p.counts + q0 + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) > p.cap)
-        near_panel_gone(p.todo, p.todo_mark, (int)(near_row(q0 + lane, p.tiles, 0) >> 7));
+        near_panel_gone(p.todo, p.todo_mark, (int)(near_row(q_pos + lane, p.tiles, 0) >> 7));
 }
 
 // Beyond 128 columns: 256 x 256 rows per meeting, both sides streamed through LDS, as near_wide_kernel; a block is two tiles.
@@ -568,7 +572,7 @@ __global__ void __launch_bounds__(256) pairs_tighten_kernel(NearPairs p, int kk,
                                                             int32_t* __restrict__ last)
 {
     const int row = blockIdx.x * 4 + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
-    if (row >= p.tiles * TILE) return;
+    if (row >= p.rows) return;
     const int n = __builtin_amdgcn_readfirstlane(p.counts[row]);
     if (n > p.cap) {                                                    // some were lost: nothing more (see pairs_left)
         if (lane == 0 && n != PAIRS_LOST) {
@@ -578,7 +582,7 @@ __global__ void __launch_bounds__(256) pairs_tighten_kernel(NearPairs p, int kk,
         }
         return;
     }
-    const float h = -p.negh[row];
+    const float h = -p.negh[p.row0 + row];
     if (n <= kk || n < __builtin_amdgcn_readfirstlane(last[row]) + (kk + 1) / 2 || !(fabsf(h) < INF)) return;
     uint2* list = p.entries + (size_t)row * (size_t)p.cap;
     uint2 mine[PAIR_WORDS];
@@ -613,8 +617,8 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
                                                          PairsLeft out)
 {
     __shared__ int s_here, s_from;
-    const int pos = blockIdx.x * LEFT_ROWS + (threadIdx.x >> 6), lane = threadIdx.x & 63;
-    const bool over = p.counts[pos] > p.cap;
+    const int of_list = blockIdx.x * LEFT_ROWS + (threadIdx.x >> 6), pos = p.row0 + of_list, lane = threadIdx.x & 63;
+    const bool over = p.counts[of_list] > p.cap;
     const float h = -p.negh[pos];
     const long long row = near_row(pos, p.tiles, 0);
     bool left = (over || *p.lost > p.lost_most) && fabsf(h) < INF && row < n_rows;
@@ -623,7 +627,7 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
     float value = LOWEST;
     if (left && over) {
         uint2 mine[PAIR_WORDS];
-        pair_list(mine, p.entries + (size_t)pos * (size_t)p.cap, p.cap);
+        pair_list(mine, p.entries + (size_t)of_list * (size_t)p.cap, p.cap);
         const float kth = pair_kth(mine, p.cap, kk);
         if (kth != LOWEST) {
             value = kth + h;
@@ -637,7 +641,7 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
             left = within < p.cap || p.cap < p.cap_again;
             if (!left && lane == 0) near_panel_gone(p.todo, p.todo_mark, (int)(row >> 7));
         }
-    } else if (left && p.limit[pos] > LOWEST) value = p.limit[pos] + h;
+    } else if (left && p.limit[of_list] > LOWEST) value = p.limit[of_list] + h;
     if (threadIdx.x == 0) s_here = 0;
     __syncthreads();
     int at = 0;
@@ -650,7 +654,7 @@ __global__ void __launch_bounds__(64 * LEFT_ROWS) pairs_left_kernel(NearPairs p,
     const int i = s_from + at;
     out.row[i] = (int)row; out.pos[i] = pos; out.counts[i] = 0;
     out.reach[i] = pair_reach(value, h, a, sc, d);
-    p.counts[pos] = 0;
+    p.counts[of_list] = 0;
 }
 __global__ void __launch_bounds__(256) pairs_again_kernel(NearPairs p, int kk, const NearScale* __restrict__ sc, float e, float nu, int d, int first, int n,
                                                           PairsLeft left)
@@ -680,7 +684,10 @@ hipError_t pairs_emit(const NearPairs& p, int waves, hipStream_t s)
     const bool wide = p.steps > REG_STEPS;
     const int bt = wide ? 2 : waves / 2;
     if (p.blocks != (p.tiles + bt - 1) / bt || p.from < 0 || p.to > (p.once ? p.blocks / 2 + 1 : p.blocks) || (!p.once && (wide || waves > 4)) || waves > 12) return hipErrorInvalidValue;
-    const dim3 grid((unsigned)(p.blocks * p.nseg)), block((unsigned)(64 * (wide ? 8 : waves)));
+    if (p.rows < 1 || p.rows % TILE != 0 || p.row0 < 0 || p.row0 != p.first * bt * TILE || p.row0 + p.rows > p.tiles * TILE || (p.once && p.rows != p.tiles * TILE) ||
+        (p.row0 + p.rows < p.tiles * TILE && p.rows % (bt * TILE) != 0)) return hipErrorInvalidValue;
+    const int blocks = (p.rows / TILE + bt - 1) / bt;
+    const dim3 grid((unsigned)(blocks * p.nseg)), block((unsigned)(64 * (wide ? 8 : waves)));
     const size_t lds = (wide ? (size_t)WIDE_LDS : 2 * ((size_t)p.steps * FRAG_STEP + (p.once ? 1024 : 512))) + (size_t)(wide ? 8 : waves) * WAVE_LDS;
     auto run = [&](auto kernel) -> hipError_t {
         hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel), hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
@@ -713,13 +720,13 @@ hipError_t pairs_best(const NearPairs& p, hipStream_t s)
 
 hipError_t pairs_tighten(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int32_t* last, hipStream_t s)
 {
-    hipLaunchKernelGGL(pairs_tighten_kernel, dim3((unsigned)(p.tiles * (TILE / 4))), dim3(256), 0, s, p, kk, sc, e, nu, d, last);
+    hipLaunchKernelGGL(pairs_tighten_kernel, dim3((unsigned)(p.rows / 4)), dim3(256), 0, s, p, kk, sc, e, nu, d, last);
     return hipGetLastError();
 }
 
 hipError_t pairs_left(const NearPairs& p, int kk, const NearScale* sc, float e, float nu, int d, int n_rows, const PairsLeft& out, hipStream_t s)
 {
-    hipLaunchKernelGGL(pairs_left_kernel, dim3((unsigned)(p.tiles * (TILE / LEFT_ROWS))), dim3(64 * LEFT_ROWS), 0, s, p, kk, sc, e, nu, d, n_rows, out);
+    hipLaunchKernelGGL(pairs_left_kernel, dim3((unsigned)(p.rows / LEFT_ROWS)), dim3(64 * LEFT_ROWS), 0, s, p, kk, sc, e, nu, d, n_rows, out);
     return hipGetLastError();
 }
 

@@ -57,3 +57,26 @@ def test_full_lists(N, d, share):
     m = max(1100, int(share * N))
     X[:m] = copies(m, d, 1100)
     check(X[torch.randperm(N, device="cuda")].contiguous(), 10)
+
+
+# from some 175 000 rows on narrow rows are searched for in turns: two and more, an odd number of tiles, the last turn shorter; lists of one row more than fit otherwise
+@pytest.mark.parametrize("N,d,k", [(174_000, 20, 10), (176_001, 20, 10), (200_100, 33, 30), (262_145, 8, 5), (300_001, 64, 12), (420_000, 5, 8)])
+@pytest.mark.parametrize("kind", ["blobs", "in order", "lattice", "copies"])
+def test_rows_in_turns(N, d, k, kind):
+    print(f"rows in turns N={N} d={d} k={k} {kind}", flush=True)
+    g = torch.Generator(device="cuda").manual_seed(N)
+    if kind == "lattice":
+        X = torch.randint(0, 6, (N, d), generator=g, device="cuda").float()
+    elif kind == "copies":
+        X = copies(N, d, 900)
+    else:
+        label = torch.randint(N // 400, (N,), generator=g, device="cuda")
+        X = 8 * torch.randn((N // 400, d), generator=g, device="cuda")[label.sort().values if kind == "in order" else label] + torch.randn((N, d), generator=g, device="cuda")
+    check(X, k)
+
+
+# 0.34 and 1.19 of sweeps, 0.60 and 1.31 with short lists for all rows and a second search for those left over, 0.25 and 1.17 in turns
+@pytest.mark.parametrize("kind,N,d,k,most", [("copies", 300_000, 10, 12, 0.4), ("radial", 250_000, 40, 10, 1.25)])
+def test_turns_have_whole_lists(kind, N, d, k, most):
+    print(f"whole lists {kind} N={N} d={d} k={k}", flush=True)
+    assert check(radial(N, d) if kind == "radial" else copies(N, d, 600), k) < most
