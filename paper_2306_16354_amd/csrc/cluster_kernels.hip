@@ -13,6 +13,7 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 #include "cluster_kernels.h"
+#include "wave_ops.h"
 
 namespace slhc {
 
@@ -61,12 +62,12 @@ __global__ void __launch_bounds__(TB) k_cut_init(int32_t* __restrict__ above, in
 
 // A child whose merge is kept has one parent, so each word has one writer.  Rows are marked by a byte: 1 MB of marks takes the scattered
 // writes of 1M rows better than 4 MB of links.  A well-formed dendrogram only joins nodes that already exist; anything else is ignored.
-__global__ void __launch_bounds__(TB) k_cut_links(const int2* __restrict__ children, int N, int kept, int32_t* __restrict__ above,
+__global__ void __launch_bounds__(TB) k_cut_links(const v2i_word* __restrict__ children, int N, int kept, int32_t* __restrict__ above,
                                                   unsigned char* __restrict__ joined)
 {
     const int i = blockIdx.x * TB + threadIdx.x;
     if (i >= kept) return;
-    const int2 c = children[i];
+    const v2i_word c = children[i];
 #pragma unroll
     for (int side = 0; side < 2; ++side) {
         const int v = side ? c.y : c.x;
@@ -230,12 +231,12 @@ __global__ void __launch_bounds__(1024) k_cut_top(int32_t* __restrict__ above, i
 
 // Every merge's rows take the number at the end of its walk, one link per stage as a rule.  A chain may avoid the merges that the hash sends up,
 // whatever the hash is; where a walk is not through after NEAR_LINKS links, *open says so.
-__global__ void __launch_bounds__(TB) k_cut_labels(const int2* __restrict__ children, int N, int kept, const int32_t* __restrict__ above,
+__global__ void __launch_bounds__(TB) k_cut_labels(const v2i_word* __restrict__ children, int N, int kept, const int32_t* __restrict__ above,
                                                    int32_t* __restrict__ labels, int32_t* __restrict__ open)
 {
     const int i = blockIdx.x * TB + threadIdx.x;
     if (i >= kept) return;
-    const int2 c = children[i];
+    const v2i_word c = children[i];
     const bool x = (unsigned int)c.x < (unsigned int)N, y = (unsigned int)c.y < (unsigned int)N;
     if (!x && !y) return;
     int a = above[i];
@@ -251,7 +252,7 @@ __global__ void __launch_bounds__(TB) k_cut_labels(const int2* __restrict__ chil
 // avoid all of stage 1, with walks of any length in the launches before: 20 000 rows 630 us, 60 000 2014, so 40 000 72 and 300 000 124, where a plain chain
 // takes 49.  Where nothing is open the launch costs 1.7 us (1M rows 85.6 and 87.3).
 constexpr int OPEN_BLOCKS = 256, OPEN_SPAN = OPEN_BLOCKS * TB, OPEN_LINKS = 4;
-__global__ void __launch_bounds__(TB) k_cut_open(const int2* __restrict__ children, int N, int kept, int32_t* above, int32_t* __restrict__ labels,
+__global__ void __launch_bounds__(TB) k_cut_open(const v2i_word* __restrict__ children, int N, int kept, int32_t* above, int32_t* __restrict__ labels,
                                                  const int32_t* __restrict__ open)
 {
     if (*open == 0) return;
@@ -263,7 +264,7 @@ __global__ void __launch_bounds__(TB) k_cut_open(const int2* __restrict__ childr
             a = __hip_atomic_load(above + a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             if (h % OPEN_LINKS == 0) __hip_atomic_store(above + i, a, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        const int2 c = children[i];
+        const v2i_word c = children[i];
         if ((unsigned int)c.x < (unsigned int)N) labels[c.x] = -1 - a;
         if ((unsigned int)c.y < (unsigned int)N) labels[c.y] = -1 - a;
     }
@@ -342,7 +343,7 @@ hipError_t flat_clusters(const int32_t* children, int N, int n_clusters, int32_t
         hipLaunchKernelGGL(k_flat_small, dim3(1), dim3(1024), lds, s, children, N, kept, labels);
         return hipGetLastError();
     }
-    const int2* c = reinterpret_cast<const int2*>(children);
+    const v2i_word* c = reinterpret_cast<const v2i_word*>(children);
     int32_t* open = counts + flat_clusters_counts(N) - 1;
     const int words = (N + 3) / 4, quads = (kept + 3) / 4;
     hipLaunchKernelGGL(k_cut_init, dim3(blocks_for(words > quads ? words : quads)), dim3(TB), 0, s, above, kept, reinterpret_cast<uint32_t*>(joined), words, open);

@@ -57,7 +57,7 @@ __global__ void __launch_bounds__(TB) k_first_edges(const int32_t* __restrict__ 
 // Contract: every edge that is the first one of an end.  That end hooks to the other; of an edge that is first on both sides the smaller end
 // is the root and takes a number (as -1 - number).  The other edges go to the next level's list.
 __global__ void __launch_bounds__(TB_WIDE) k_contract(const int32_t* __restrict__ lo, const int32_t* __restrict__ hi, DendrogramWork w,
-                                                      int level, int2* __restrict__ children)
+                                                      int level, v2i_word* __restrict__ children)
 {
     const int n = w.counters[DENDRO_ROWS + level], m = w.counters[DENDRO_EDGES + level], base = w.counters[DENDRO_BASE + level];
     if (n <= TAIL || w.counters[DENDRO_ERROR] != 0 || (int)(blockIdx.x * TB_WIDE) >= m) return;
@@ -75,7 +75,7 @@ __global__ void __launch_bounds__(TB_WIDE) k_contract(const int32_t* __restrict_
     if (fa && fb) { w.hook[small] = -1 - root; w.hook[large] = small; }
     else if (fa) w.hook[v.x] = v.y;
     else if (fb) w.hook[v.y] = v.x;
-    if (fa || fb) children[e] = make_int2(fa ? base + v.x : -1, fb ? base + v.y : -1);
+    if (fa || fb) children[e] = v2i_word{fa ? base + v.x : -1, fb ? base + v.y : -1};
     __syncthreads();                                        // (block_append's LDS is used again)
     const int at = block_append<TB_WIDE>(mine && !fa && !fb, &w.counters[DENDRO_EDGES + level + 1]);
     if (mine && !fa && !fb) {
@@ -126,7 +126,7 @@ __global__ void __launch_bounds__(TB) k_next_level(DendrogramWork w, int level, 
 }
 
 // The levels of at most TAIL vertices.
-__global__ void __launch_bounds__(TB_WIDE) k_last_levels(DendrogramWork w, int2* __restrict__ children, int N)
+__global__ void __launch_bounds__(TB_WIDE) k_last_levels(DendrogramWork w, v2i_word* __restrict__ children, int N)
 {
     __shared__ uint32_t lightest[TAIL], edge[2][TAIL], ends[2][TAIL];       // ends: 16 bits each
     __shared__ int hook[TAIL];
@@ -156,7 +156,7 @@ __global__ void __launch_bounds__(TB_WIDE) k_last_levels(DendrogramWork w, int2*
                 ends[turn ^ 1][at] = v;
                 continue;
             }
-            children[e] = make_int2(fa ? base + a : -1, fb ? base + b : -1);
+            children[e] = v2i_word{fa ? base + a : -1, fb ? base + b : -1};
             if (fa && fb) { hook[a < b ? a : b] = -1 - atomicAdd(&roots, 1); hook[a < b ? b : a] = a < b ? a : b; }
             else if (fa) hook[a] = b;
             else hook[b] = a;
@@ -191,7 +191,7 @@ __global__ void __launch_bounds__(TB_WIDE) k_last_levels(DendrogramWork w, int2*
 }
 
 // The chain of every merge (see above), and how many merges lie in chains of each level.  Chains are named by their vertex, so by level first.
-__global__ void __launch_bounds__(TB) k_chains(DendrogramWork w, const int2* __restrict__ children, int N)
+__global__ void __launch_bounds__(TB) k_chains(DendrogramWork w, const v2i_word* __restrict__ children, int N)
 {
     __shared__ int base[DENDRO_LEVELS], count[DENDRO_LEVELS];
     if (w.counters[DENDRO_ERROR] != 0) return;
@@ -200,7 +200,7 @@ __global__ void __launch_bounds__(TB) k_chains(DendrogramWork w, const int2* __r
     __syncthreads();
     const int e = blockIdx.x * TB + threadIdx.x;
     if (e < N - 1) {
-        const int2 c = children[e];
+        const v2i_word c = children[e];
         int v = w.up[c.x >= 0 ? c.x : c.y];
         while (w.lightest[v] < (uint32_t)e) v = w.up[v];    // (the last vertex has no edge)
         w.key[e] = (uint32_t)(v - N);
@@ -218,21 +218,21 @@ struct Merge {
     uint32_t e;
     bool first, last;            // of its chain
     int chain, rows;             // rows that come in here
-    int2 nodes;
+    v2i_word nodes;
 };
-__device__ __forceinline__ Merge merge_at(const DendrogramWork& w, const int2* children, int N, int p, int begin, int end)
+__device__ __forceinline__ Merge merge_at(const DendrogramWork& w, const v2i_word* children, int N, int p, int begin, int end)
 {
     Merge g;
     g.chain = (int)w.key_sorted[p];
     g.e = w.listed[p];
     g.first = p == begin || (int)w.key_sorted[p - 1] != g.chain;
     g.last = p + 1 == end || (int)w.key_sorted[p + 1] != g.chain;
-    const int2 c = children[g.e];
+    const v2i_word c = children[g.e];
     const int2 x = c.x >= N ? w.chain[c.x - N] : make_int2(c.x - N, 1), y = c.y >= N ? w.chain[c.y - N] : make_int2(c.y - N, 1);
     g.rows = (c.x >= 0 ? x.y : 0) + (c.y >= 0 ? y.y : 0);
     const int before = g.first ? 0 : (int)w.listed[p - 1];
     const int a = N + (c.x >= 0 ? x.x : before), b = N + (c.y >= 0 ? y.x : before);
-    g.nodes = make_int2(a < b ? a : b, a < b ? b : a);
+    g.nodes = v2i_word{a < b ? a : b, a < b ? b : a};
     return g;
 }
 
@@ -251,7 +251,7 @@ __device__ __forceinline__ void scan_lanes(bool& starts, int& rows)
 // Merges [begin, end) of one level: children, sizes (sums along the chains), and the chains' last merges and rows.  A workgroup posts what
 // its span ends on (1: no chain starts in it, so what is before it has to be added; 2: all of it) and adds what the spans before it post;
 // spans are handed out in the order in which workgroups start, so whoever is waited for is running.
-__global__ void __launch_bounds__(TB) k_chain_sums(DendrogramWork w, int2* __restrict__ children, int32_t* __restrict__ sizes, int N,
+__global__ void __launch_bounds__(TB) k_chain_sums(DendrogramWork w, v2i_word* __restrict__ children, int32_t* __restrict__ sizes, int N,
                                                    int begin, int end, int level, unsigned long long* __restrict__ carry)
 {
     __shared__ int span_at, wave_rows[TB / 64], wave_starts[TB / 64], before;
@@ -321,7 +321,7 @@ __global__ void __launch_bounds__(TB) k_chain_sums(DendrogramWork w, int2* __res
 }
 
 // The same for the levels from `level` on, one after the other, in one workgroup; begin: the first level's first merge.
-__global__ void __launch_bounds__(TB_WIDE) k_chain_sums_tail(DendrogramWork w, int2* __restrict__ children, int32_t* __restrict__ sizes, int N,
+__global__ void __launch_bounds__(TB_WIDE) k_chain_sums_tail(DendrogramWork w, v2i_word* __restrict__ children, int32_t* __restrict__ sizes, int N,
                                                              int begin, int level, int depth)
 {
     __shared__ int wave_rows[TB_WIDE / 64], wave_starts[TB_WIDE / 64];
@@ -358,7 +358,7 @@ __global__ void __launch_bounds__(TB_WIDE) k_chain_sums_tail(DendrogramWork w, i
 
 hipError_t dendrogram_chains(const int32_t* lo, const int32_t* hi, int N, const DendrogramWork& w, int32_t* children, hipStream_t s)
 {
-    int2* c = reinterpret_cast<int2*>(children);
+    v2i_word* c = reinterpret_cast<v2i_word*>(children);
     hipLaunchKernelGGL(k_levels_init, dim3(blocks_for(2ll * N > DENDRO_WORDS ? 2ll * N : DENDRO_WORDS, TB)), dim3(TB), 0, s, w, N, (int)dendrogram_carry_words(N));
     hipLaunchKernelGGL(k_first_edges, dim3(blocks_for(N, TB)), dim3(TB), 0, s, lo, hi, w, N);
     // a level has at most half the vertices of the one before
@@ -374,7 +374,7 @@ hipError_t dendrogram_chains(const int32_t* lo, const int32_t* hi, int N, const 
 
 hipError_t dendrogram_sizes(int N, const int32_t* merges, const DendrogramWork& w, int32_t* children, int32_t* sizes, hipStream_t s)
 {
-    int2* c = reinterpret_cast<int2*>(children);
+    v2i_word* c = reinterpret_cast<v2i_word*>(children);
     int depth = 0;
     for (int l = 1; l < DENDRO_LEVELS; ++l) if (merges[l] > 0) depth = l;
     int begin = 0;

@@ -6,6 +6,9 @@
 
 namespace slhc {
 
+// The two children of a merge: a caller's array, which may begin at any word.
+typedef int v2i_word __attribute__((ext_vector_type(2), aligned(4)));
+
 // One step of a reduction: op(x, x of lane ^ O), op commutative.  From 4 on the lanes of an aligned group of O have to hold the same value, as
 // they do after the steps 1, 2, .. O / 2: within 16 lanes the mirrored lane stands in for lane ^ O.  Vector instructions of 4 cycles, where
 // __shfl_xor goes through LDS and waits for it.

@@ -39,3 +39,19 @@ def test_children_and_sizes(N, kind):
     want = oracle.dendrogram(src, dst, w.astype(np.float64), N)
     assert np.array_equal(out["children"].cpu().numpy(), want["children"])
     assert np.array_equal(out["sizes"].cpu().numpy(), want["sizes"])
+
+
+# arrays that begin at any word; the host's dendrogram and the device's
+@pytest.mark.parametrize("N", [600, 18_999, 19_000, 40_000])
+@pytest.mark.parametrize("word", [1, 3])
+def test_arrays_at_odd_words(N, word):
+    import paper_2306_16354_amd as slhc
+    print(f"dendrogram into arrays at odd words N={N} word={word}", flush=True)
+    X = torch.from_numpy(rows("clusters", N, np.random.default_rng(N))).cuda()
+    want = slhc.slhc(X, 6)
+    types = {"mst_src": torch.int32, "mst_dst": torch.int32, "mst_w": torch.float32, "children": torch.int32, "heights": torch.float32, "sizes": torch.int32}
+    whole = {n: torch.full((2 * N + 8,), -7, dtype=t, device="cuda") for n, t in types.items()}
+    out = {n: t[word:word + want[n].numel()].view(want[n].shape) for n, t in whole.items()}
+    got = slhc.slhc(X, 6, out=out)
+    for n in types:
+        assert torch.equal(got[n], want[n]) and bool((whole[n][:word] == -7).all()) and bool((whole[n][word + want[n].numel():] == -7).all()), n
