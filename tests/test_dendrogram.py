@@ -55,3 +55,9 @@ def test_arrays_at_odd_words(N, word):
     got = slhc.slhc(X, 6, out=out)
     for n in types:
         assert torch.equal(got[n], want[n]) and bool((whole[n][:word] == -7).all()) and bool((whole[n][word + want[n].numel():] == -7).all()), n
+
+
+# one chain of more merges than 64 workgroups sum up: what comes before a span is looked for beyond the 64 spans before it
+@pytest.mark.parametrize("kind,N", [("rising", 200_000), ("rising, shuffled", 300_001), ("doubling", 200_000)])
+def test_long_chains(kind, N):
+    test_children_and_sizes(N, kind)
