@@ -244,6 +244,8 @@ __device__ inline int near_pos(int row, int tiles)             // (not in order)
 constexpr int PANEL_GONE = 2;
 __device__ inline void near_panel_gone(int32_t* todo, int32_t* todo_mark, int panel)
 {
+    // (a hundred thousand rows may say so of forty panels, one exchange after another: 5000 x 12 of 2000 copies each 4.8 ms, 4.2 with the look)
+    if (__hip_atomic_load(todo_mark + panel, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == PANEL_GONE) return;
     if (atomicExch(todo_mark + panel, PANEL_GONE) == 0) todo[2 + atomicAdd(todo, 1)] = panel;
 }
 
