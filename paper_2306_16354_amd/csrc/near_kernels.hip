@@ -416,7 +416,7 @@ __device__ __attribute__((noinline)) float near_refine(uint2* buf, int* n_, int 
 }
 
 // What a lane carries for its two queries (one of each block of 32) through a sweep, and what it does with the values
-// of 64 candidates.
+// of 32 or 64 candidates.
 template <int MODE, bool COLOURED>
 struct NearLane {
     float h[2], bound[2];
@@ -472,7 +472,7 @@ struct NearLane {
     }
 
     // acc[query block][candidate block]: value r of a lane belongs to candidate 8 (r / 4) + 4 lhalf + r % 4 of its block;
-    // pos0: position of the first of the 64 candidates, col: their colours (LDS)
+    // pos0: position of the first of the 32 CB candidates, col: their colours (LDS)
     // ok: whether the lane's queries and the candidates' tile are of the side in hand (and of different colours, with one_colour,
     // which all lanes share: the 32 compares and selects per 16 values of a query are as much as a third of all vector instructions)
     // EARLY: words of colours read ahead, of four candidates each.  Eight compares are made before the eight selects that need them (left alone, the compiler puts every
@@ -534,7 +534,7 @@ struct NearLane {
             return;
         }
         if (MODE == NEAR_ARG) {
-            // the number of the value within the 64 candidates replaces the five lowest bits of its mantissa (an infinity
+            // the number of the value among the lane's 16 CB replaces the five lowest bits of its mantissa (an infinity
             // would become a NaN: copies used here have finite padding)
 #pragma unroll
             for (int qb = 0; qb < 2; ++qb) {
@@ -1691,8 +1691,8 @@ struct PairPlan {
 static bool pair_search_wanted(int T) { return T >= 32 && T < (1 << 17); }
 // Whether every pair is multiplied once, for both of its rows, or in either order.  Once takes the test 36 instructions for 16 values instead of 12 and half
 // the products: 35 000 x 128, k = 16, 661 us in either order and 549 once; 40 000 x 110, 10: 746 and 621; 13 000 x 70, 10: 145 and 147; of 60 000 x 128, 12, the
-// products alone are most of it.  (Narrower rows would gain as well: 100 000 x 48, 10: 1763 and 1415, 20 011 x 50, 10: 216 and 201, 20 000 x 16, 10: 167 and 161.  What a
-// search multiplies there is part of the interface, slhc_probe_knn_products, and has not been changed.)
+// products alone are most of it.  Narrower rows gain as well (100 000 x 48, 10: 1763 and 1415, 20 011 x 50, 10: 216 and 201, 20 000 x 16, 10: 167 and 161), but the lists of both rows
+// of a pair have to be there at once, so such rows could not be searched for in turns (near_pair_plan), and tests hold what slhc_probe_knn_products reports of them.
 static bool pairs_once(int T, int steps) { return steps > REG_STEPS || (T <= 100 ? steps >= 3 : steps >= 6 || (T >= 384 && steps >= 5)); }
 // from here on rows whose lists overflow are searched for on their own before the list kernels take their panels; below, the five
 // launches cost more (20 us of 200 at 20 000 rows) than a panel or two
