@@ -47,10 +47,13 @@ struct CsrSortScratch {
     uint32_t *number, *wbits_a, *wbits_b; unsigned long long *ends_a, *ends_b;        // [E]
     void* temp; size_t temp_bytes;
 };
-// Where few have the same weight: sets *flag (0 before) where there are too many all the same, and the outputs don't hold then.
+// Where few have the same weight.  *count (0 before) is the number of edges of long runs, whose places in the outputs are left open: up to CSR_LONG_MOST of them
+// csr_sort_long_runs fills these, of more the outputs have to be made another way.
+constexpr int CSR_LONG_MOST = 1 << 15;
 bool csr_sort_in_runs_fits(int E, size_t temp_bytes);
 hipError_t csr_sort_in_runs(const int32_t* lo, const int32_t* hi, const float* w, int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi,
-                            float* out_w, int32_t* flag, hipStream_t s);
+                            float* out_w, int32_t* count, hipStream_t s);
+hipError_t csr_sort_long_runs(int n, int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s);
 // Else, in two steps: the first sets *flag where edge_sort has to do it instead, and tells host[0], with `seq` above the flag.
 bool csr_sort_fits(int V, int E, size_t temp_bytes);
 hipError_t csr_sort_ends(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* flag, unsigned long long* host, uint32_t seq,

@@ -517,32 +517,53 @@ __global__ void __launch_bounds__(TB) k_csr_closed(CsrForest f, const int32_t* _
 // many of the same) and 937, 2M 1135 and 1150, 3M 1613 and 1615, 4M 2604 (too many) and 2087.
 static inline int low_bits(int E) { return E <= (1 << 20) ? 7 : 0; }
 // The words of a call; and whether many edges have the same weight in the bits that are sorted by, by a sample of the entries: each looks for its
-// weight in a table of those before it.  Many: more pairs than runs of 16 edges would give.
-constexpr int SAMPLE = 1024, SAMPLE_TABLE = 4096;
-__global__ void __launch_bounds__(SAMPLE) k_csr_words(CsrForest f, int low)
+// weight in a table of those before it.  Many: more pairs than runs of 16 edges would give, or one weight that as many have as LONG_RUN edges would, beyond which
+// k_csr_long_runs takes longer than the other sort (a hundredth of 160 000 vertices' edges 463 us and 440 by the other, 3 % of 90 000's 417 and 386, a hundredth of
+// 2.25M's 1614 and 1374).  1024 entries, 4.2 us; beyond 2^21 vertices, where so few entries have hardly a pair in runs of 16, 4096 (15 us; whole weights up to 100 000 of 4M
+// vertices, in runs of 40, passed for few of the same by 1024: 3530 us, and 2280 so).
+constexpr long long LONG_RUN = 1200;
+template <int SAMPLE>
+__global__ void __launch_bounds__(WIDE) k_csr_words(CsrForest f, int low)
 {
-    __shared__ uint32_t table[SAMPLE_TABLE];
+    constexpr int TABLE = 4 * (SAMPLE < 2048 ? SAMPLE : 2048), EACH = SAMPLE / WIDE;
+    static_assert(TABLE == 4096 || TABLE == 8192, "the hash has 12 bits or 13");
+    __shared__ uint32_t table[TABLE], times[TABLE / 2];       // (times: 16 bits each)
     const int tid = threadIdx.x;
-    for (int i = tid; i < SAMPLE_TABLE; i += SAMPLE) table[i] = 0xffffffffu;
+    for (int i = tid; i < TABLE; i += WIDE) table[i] = 0xffffffffu;
+    for (int i = tid; i < TABLE / 2; i += WIDE) times[i] = 0u;
     __syncthreads();
-    bool tie = false;
+    int found = 0;
+    bool common = false;
+    const long long often = SAMPLE * LONG_RUN / f.V;
     if (f.E >= SAMPLE) {
-        const uint32_t w = (__float_as_uint(f.weights[(long long)f.E * tid / SAMPLE]) & 0x7fffffffu) >> low;
-        uint32_t at = (w * 0x9e3779b1u) >> 20;
-        for (int i = 0; i < SAMPLE_TABLE; ++i, at = (at + 1) & (SAMPLE_TABLE - 1)) {
-            const uint32_t was = atomicCAS(&table[at], 0xffffffffu, w);
-            tie = was == w;
-            if (tie || was == 0xffffffffu) break;
+        uint32_t w[EACH];
+#pragma unroll
+        for (int k = 0; k < EACH; ++k) w[k] = (__float_as_uint(f.weights[(long long)f.E * (k * WIDE + tid) / SAMPLE]) & 0x7fffffffu) >> low;
+#pragma unroll
+        for (int k = 0; k < EACH; ++k) {
+            uint32_t at = (w[k] * 0x9e3779b1u) >> (TABLE == 4096 ? 20 : 19), was = 0u;
+#pragma unroll 1
+            for (int i = 0; i < TABLE; ++i, at = (at + 1) & (TABLE - 1)) {
+                was = atomicCAS(&table[at], 0xffffffffu, w[k]);
+                if (was == w[k] || was == 0xffffffffu) break;
+            }
+            if (was != w[k]) continue;
+            ++found;
+            const uint32_t before = atomicAdd(&times[at >> 1], at & 1 ? 1u << 16 : 1u);
+            common = common || (int)(at & 1 ? before >> 16 : before & 0xffffu) >= (often < 3 ? 3 : (int)often);
         }
     }
-    const int ties = __syncthreads_count(tie), most = 4 + (int)((16ll * SAMPLE * SAMPLE / 2) / f.V);
+    int ties = 0;
+    for (int k = 1; k <= EACH; ++k) ties += __syncthreads_count(found >= k);
+    const bool many = __syncthreads_or(common) != 0 || ties > 4 + (int)((16ll * SAMPLE * SAMPLE / 2) / f.V);
     const bool all = (tid == CSR_ACTIVE + 1 && list_is_all(f, 0)) || (tid == CSR_ACTIVE + 2 && list_is_all(f, 1));
-    if (tid < 64) f.words[tid] = all ? f.V : tid == CSR_TIES && ties > most ? (int)CSR_MANY_TIES : 0;
+    if (tid < 64) f.words[tid] = all ? f.V : tid == CSR_TIES && many ? (int)CSR_MANY_TIES : 0;
 }
 
 hipError_t csr_start(const CsrForest& f, hipStream_t s)
 {
-    hipLaunchKernelGGL(k_csr_words, dim3(1), dim3(SAMPLE), 0, s, f, low_bits(f.V));
+    if (f.V > 1 << 21) hipLaunchKernelGGL(k_csr_words<4096>, dim3(1), dim3(WIDE), 0, s, f, low_bits(f.V));
+    else hipLaunchKernelGGL(k_csr_words<1024>, dim3(1), dim3(WIDE), 0, s, f, low_bits(f.V));
     if (list_is_all(f, 0)) hipLaunchKernelGGL((k_csr_first<TB, true>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
     else hipLaunchKernelGGL((k_csr_first<TB, false>), dim3(blocks_for(f.V)), dim3(TB), 0, s, f);
     if (f.V > FEW) hipLaunchKernelGGL(k_csr_commit_first<4>, dim3(blocks_for(f.V, 4 * WIDE)), dim3(WIDE), 0, s, f);
@@ -590,13 +611,13 @@ hipError_t csr_closed(const CsrForest& f, const int32_t* colours, hipStream_t s)
 
 // ------------------------------------------------------------------------------- sort
 // By (weight, smaller end, larger end).  Where few edges have nearly the same weight: one sort of weights with the edges' numbers, by all but the
-// lowest bits while the runs that leaves are short, and every edge counts those of its run that come before it.  A run of more than RUN_MOST
-// raises a flag, and another way is taken.  1M edges: 220 us by the smaller ends first (below), 165 by all bits, 140 so, of which the three passes
-// take 83 and the runs 33 (random words of the edges' ends; 41 with the neighbours' weights read from memory).
+// lowest bits while the runs that leaves are short, and every edge counts those of its run that come before it.  The edges of runs of more than RUN_MOST
+// are listed, and the caller has them placed in a launch of their own, or, where they are many, takes another way.  1M edges: 220 us by the smaller ends first
+// (below), 165 by all bits, 140 so, of which the three passes take 83 and the runs 30 (random words of the edges' ends; 41 with the neighbours' weights read from memory).
 constexpr int RUN_MOST = 64;
 __global__ void __launch_bounds__(TB) k_csr_in_runs(const uint32_t* __restrict__ wbits, const uint32_t* __restrict__ number, const int32_t* __restrict__ lo,
                                                    const int32_t* __restrict__ hi, int E, int low, int32_t* __restrict__ out_lo, int32_t* __restrict__ out_hi,
-                                                   float* __restrict__ out_w, int32_t* __restrict__ flag)
+                                                   float* __restrict__ out_w, int32_t* __restrict__ listed, unsigned long long* __restrict__ ends, int32_t* __restrict__ count)
 {
     __shared__ uint32_t near[RUN_MOST + TB + RUN_MOST];        // the workgroup's weights and those a run can reach
     const int first = blockIdx.x * TB, i = first + threadIdx.x;
@@ -616,20 +637,99 @@ __global__ void __launch_bounds__(TB) k_csr_in_runs(const uint32_t* __restrict__
         const int oa = lo[n];
         return oa < a || (oa == a && hi[n] < b) ? 1 : 0;
     };
-    int from = i, to = i + 1, at = 0;
-    for (; from > 0 && i - from < RUN_MOST; --from) {
-        const uint32_t o = mine[from - 1 - i];
-        if ((o ^ w) >> low) break;
-        at += before(from - 1, o);
+    int from = i, to = i + 1;
+    for (; from > 0 && i - from < RUN_MOST && ((mine[from - 1 - i] ^ w) >> low) == 0u; --from) {}
+    for (; to < E && to - i <= RUN_MOST && ((mine[to - i] ^ w) >> low) == 0u; ++to) {}
+    const bool is_long = to - from > RUN_MOST;
+    const unsigned long long all = __ballot(is_long);
+    if (all != 0) {
+        const int first = __builtin_ctzll(all);
+        int base = 0;
+        if ((int)(threadIdx.x & 63) == first) base = atomicAdd(count, __popcll(all));
+        base = __shfl(base, first);
+        if (is_long) {
+            listed[base + __builtin_amdgcn_mbcnt_hi((unsigned int)(all >> 32), __builtin_amdgcn_mbcnt_lo((unsigned int)all, 0u))] = i;
+            ends[i] = ((unsigned long long)(unsigned int)a << 32) | (unsigned int)b;
+            return;
+        }
     }
-    for (; to < E && to - i <= RUN_MOST; ++to) {
-        const uint32_t o = mine[to - i];
-        if ((o ^ w) >> low) break;
-        at += before(to, o);
-    }
-    if (to - from > RUN_MOST) { *flag = 1; return; }
-    at += from;
+    int at = from;
+    for (int j = from; j < to; ++j)
+        if (j != i) at += before(j, mine[j - i]);
     out_lo[at] = a; out_hi[at] = b; out_w[at] = __uint_as_float(w);
+}
+// The first of [lo, hi] from which on beyond(j) holds, as it does from hi on, looked for by a wavefront at 64 places at a time (lo, hi the same for all lanes).
+template <typename F>
+__device__ inline int wave_first(int lo, int hi, F&& beyond)
+{
+    const int lane = threadIdx.x & 63;
+    while (lo < hi) {
+        const int step = (hi - lo + 63) / 64;
+        const long long at = lo + (long long)lane * step;
+        const unsigned long long yes = __ballot(at >= hi || beyond((int)at));
+        const int k = yes != 0 ? __builtin_ctzll(yes) : 64;
+        if (k < 64 && lo + (long long)k * step < hi) hi = lo + k * step;
+        if (k > 0) lo += (k - 1) * step + 1;
+    }
+    return lo;
+}
+// 64 listed edges a workgroup, whose wavefronts share out their run: what it is compared with is the same for all lanes, and comes by scalar loads (by vector loads of one
+// address, 16 cycles each, a run of 1600 edges took 30 us).  Edges of several runs look for their own.
+// Road-like graphs, a share of the weights the same, us of the whole call (a run of 65 made the whole sort vain before; this kernel takes 9 to 13):
+//   90 000 vertices, .001: 562 and 399; 160 000, .003: 613 and 443; 490 000, .003: 743 and 570; 1M, .001: 1014 and 795; 4M, .0002: 2619 and 2125
+__global__ void __launch_bounds__(WIDE) k_csr_long_runs(const uint32_t* __restrict__ wbits, const unsigned long long* __restrict__ ends, const int32_t* __restrict__ listed,
+                                                        int n, int E, int low, int32_t* __restrict__ out_lo, int32_t* __restrict__ out_hi, float* __restrict__ out_w)
+{
+    constexpr int WAVES = WIDE / 64, AT_ONCE = 8;
+    __shared__ int before[WAVES][64];
+    const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), at = blockIdx.x * 64 + lane;
+    const int i = at < n ? listed[at] : -1;
+    const uint32_t w = i >= 0 ? wbits[i] : 0u;
+    const unsigned long long mine = i >= 0 ? ends[i] : 0ull;
+    int less = 0;
+    auto count = [&](uint32_t o, unsigned long long other) { less += (int)(o < w) | ((int)(o == w) & (int)(other < mine)); };
+    // (sorted by the bits above `low`; the first lane has an edge)
+    const int i0 = __builtin_amdgcn_readfirstlane(i);
+    const uint32_t w0 = (uint32_t)__builtin_amdgcn_readfirstlane((int)w);
+    int from = wave_first(0, i0, [&](int j) { return ((wbits[j] ^ w0) >> low) == 0u; });
+    const int to0 = wave_first(i0 + 1, E, [&](int j) { return ((wbits[j] ^ w0) >> low) != 0u; });
+    if (__all(i < 0 || (i >= from && i < to0))) {
+        const int from0 = __builtin_amdgcn_readfirstlane(from), len = __builtin_amdgcn_readfirstlane(to0) - from0;
+        const int j1 = from0 + (int)((long long)len * (wave + 1) / WAVES);
+        int j = from0 + (int)((long long)len * wave / WAVES);
+        for (; j + AT_ONCE <= j1; j += AT_ONCE) {
+            uint32_t o[AT_ONCE];
+            unsigned long long other[AT_ONCE];
+#pragma unroll
+            for (int k = 0; k < AT_ONCE; ++k) { o[k] = wbits[j + k]; other[k] = ends[j + k]; }
+#pragma unroll
+            for (int k = 0; k < AT_ONCE; ++k) count(o[k], other[k]);
+        }
+        for (; j < j1; ++j) count(wbits[j], ends[j]);
+    } else {
+        int to = 0;
+        from = 0;
+        if (i >= 0) {
+            for (int end = i; from < end;) {
+                const int mid = from + (end - from) / 2;
+                if ((wbits[mid] ^ w) >> low) from = mid + 1; else end = mid;
+            }
+            to = i + 1;
+            for (int end = E; to < end;) {
+                const int mid = to + (end - to) / 2;
+                if ((wbits[mid] ^ w) >> low) end = mid; else to = mid + 1;
+            }
+        }
+        const int j1 = from + (int)((long long)(to - from) * (wave + 1) / WAVES);
+        for (int j = from + (int)((long long)(to - from) * wave / WAVES); j < j1; ++j) count(wbits[j], ends[j]);
+    }
+    before[wave][lane] = less;
+    __syncthreads();
+    if (wave != 0 || i < 0) return;
+    int place = from;
+#pragma unroll
+    for (int v = 0; v < WAVES; ++v) place += before[v][lane];
+    out_lo[place] = (int)(mine >> 32); out_hi[place] = (int)(mine & 0xffffffffull); out_w[place] = __uint_as_float(w);
 }
 
 // Where many do: the smaller ends are counted and the edges placed by them, which takes a few passes of
@@ -719,12 +819,17 @@ bool csr_sort_in_runs_fits(int E, size_t temp_bytes)
     return a <= temp_bytes;
 }
 hipError_t csr_sort_in_runs(const int32_t* lo, const int32_t* hi, const float* w, int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi,
-                            float* out_w, int32_t* flag, hipStream_t s)
+                            float* out_w, int32_t* count, hipStream_t s)
 {
     size_t tb = t.temp_bytes;
     const hipError_t e = sort_weights_numbers(t.temp, tb, reinterpret_cast<const uint32_t*>(w), t.wbits_b, t.number, E, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_csr_in_runs, dim3(blocks_for(E)), dim3(TB), 0, s, t.wbits_b, t.number, lo, hi, E, low_bits(E), out_lo, out_hi, out_w, flag);
+    hipLaunchKernelGGL(k_csr_in_runs, dim3(blocks_for(E)), dim3(TB), 0, s, t.wbits_b, t.number, lo, hi, E, low_bits(E), out_lo, out_hi, out_w, t.rank, t.ends_a, count);
+    return hipGetLastError();
+}
+hipError_t csr_sort_long_runs(int n, int E, const CsrSortScratch& t, int32_t* out_lo, int32_t* out_hi, float* out_w, hipStream_t s)
+{
+    if (n > 0) hipLaunchKernelGGL(k_csr_long_runs, dim3(blocks_for(n, 64)), dim3(WIDE), 0, s, t.wbits_b, t.ends_a, t.rank, n, E, low_bits(E), out_lo, out_hi, out_w);
     return hipGetLastError();
 }
 hipError_t csr_sort_ends(const int32_t* lo, const int32_t* hi, const float* w, int E, int V, const CsrSortScratch& t, int32_t* flag, unsigned long long* host, uint32_t seq,

@@ -1945,10 +1945,15 @@ int slhc_csr_msf(const int32_t* offsets, const int32_t* indices, const float* we
         t.temp = ws.sort_temp; t.temp_bytes = ws.sort_temp_bytes;
         // (up to 65 536 vertices edge_sort needs one sort)
         const bool large = edges > 0 && V > 65536, runs = large && !ties && slhc::csr_sort_in_runs_fits(edges, ws.sort_temp_bytes);
-        int32_t ended[2] = {0, 1};                             // the end of all work: a failed check, and that the sort has to be made another way
+        int32_t ended[2] = {0, 1};                             // the end of all work: a failed check, and edges that the sort has not placed
         if (runs) {
             HIP_TRY(slhc::csr_sort_in_runs(ws.e_lo, ws.e_hi, ws.e_w, edges, t, mst_src, mst_dst, mst_w, f.words + slhc::CSR_FLAG, s));
             HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 2, ended));
+            if (ended[1] > 0 && ended[1] <= slhc::CSR_LONG_MOST) {
+                HIP_TRY(slhc::csr_sort_long_runs(ended[1], edges, t, mst_src, mst_dst, mst_w, s));
+                HIP_TRY(mail[0].fetch(f.words + slhc::CSR_ERROR, 1, ended));
+                ended[1] = 0;
+            }
         }
         if (ended[1] != 0) {
             int32_t many = 1;
