@@ -1674,7 +1674,8 @@ static hipError_t near_nearest(const NearProblem& a, const NearCopy& q, const Ne
 // seen g times as many rows at its end as at its beginning (every tile is an even sample of the rows).  Rows whose lists
 // overflow all the same are searched for on their own, with the buffers and the tightening of the sweeps.  A row has to keep all its copies,
 // so where every point is there some hundred times most rows overflow; the rest of the bands is left out then, and every row
-// searched for: 150 000 x 80, k = 12, 2000 copies each, 202 ms without that, 142 so.
+// searched for: 150 000 x 80, k = 12, 2000 copies each, 202 ms without that, 142 so, 91 since
+// full lists take no more entries.
 // (Sorting the rows by their nearest of a few hundred pivots first, so that what passes comes together, was tried: limits then come from
 // a row's own surroundings and say nothing about the other rows, a third of the rows overflowed, 1M x 128 took 250 ms
 // without their panels against 200 ms.)
@@ -1687,7 +1688,8 @@ struct PairPlan {
 // From 32 tiles on.  Against sweeps that keep what passes by a branch per value (near_sweep_kernel's emission, which is left where memory is short), in us:
 // 5000 x 10, k = 10: 68 and 62; 8000 x 30, 10: 93 and 90; 13 000 x 40, 10: 127 and 123; 20 011 x 50, 10: 220 and 216; 20 000 x 128, 32, clusters by Zipf's law: 4460
 // and 391; 30 000 x 30, 16: 338 and 312; 40 000 x 70, 10: 596 and 574; 50 000 x 10, 10: 629 and 502; 100 000 x 48, 10: 2434 and 1763; 250 000 x 20, 10: 8.5 and
-// 6.4 ms; 250 000 x 60, 20, by Zipf's law 14.0 and 12.3.
+// 6.4 ms; 250 000 x 60, 20, by Zipf's law 14.0 and 12.3.  k = 12, 300 copies of every row: 5000 x 12 164 and 214, 12 000 x 30 325 and 357 (an entry is an addition in
+// memory here), 20 000 x 16 3424 and 540; 600 copies: 2321 and 443, 4093 and 790, 5592 and 1213.
 static bool pair_search_wanted(int T) { return T >= 32 && T < (1 << 17); }
 // Whether every pair is multiplied once, for both of its rows, or in either order.  Once takes the test 36 instructions for 16 values instead of 12 and half
 // the products: 35 000 x 128, k = 16, 661 us in either order and 549 once; 40 000 x 110, 10: 746 and 621; 13 000 x 70, 10: 145 and 147; of 60 000 x 128, 12, the
